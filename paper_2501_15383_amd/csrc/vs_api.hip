@@ -301,9 +301,9 @@ int sparse_attn(const vs_params* p, const void* q, const vs_dca* dca, const void
   if (!dca && attn_single_token_packs(*p))
     return hip_status(launch_attention_single_token(*p, q, k, v, v_idx, v_cnt, s_idx, s_cnt, out, lse, ws, st));
   const BlockList bl = blocklist_layout(*p, false, ws);
-  hipError_t e = launch_build_blocklist(*p, s_idx, s_cnt, false, bl, st);
-  if (e != hipSuccess) return VS_ERR_HIP;
   char* sync = (char*)ws + blocklist_bytes(*p, false);
+  hipError_t e = launch_build_blocklist(*p, s_idx, s_cnt, false, bl, sync, st);
+  if (e != hipSuccess) return VS_ERR_HIP;
   return hip_status(launch_attention(*p, q, dca ? &da : nullptr, k, v, v_idx, v_cnt, false, bl, out, lse, sync,
                                      sync + attn_sync_bytes(*p), st));
 }
@@ -320,9 +320,9 @@ int dense_attn(const vs_params* p, const void* q, const vs_dca* dca, const void*
   if (rc != VS_OK) return rc;
   const BlockList bl = blocklist_layout(*p, true, ws);
   hipStream_t st = (hipStream_t)stream;
-  hipError_t e = launch_build_blocklist(*p, nullptr, nullptr, true, bl, st);
-  if (e != hipSuccess) return VS_ERR_HIP;
   char* sync = (char*)ws + blocklist_bytes(*p, true);
+  hipError_t e = launch_build_blocklist(*p, nullptr, nullptr, true, bl, sync, st);
+  if (e != hipSuccess) return VS_ERR_HIP;
   return hip_status(launch_attention(*p, q, dca ? &da : nullptr, k, v, nullptr, nullptr, true, bl, out, lse, sync,
                                      sync + attn_sync_bytes(*p), st));
 }
@@ -434,7 +434,7 @@ int vs_count_tiles(const vs_params* p, const int32_t* v_idx, const int32_t* v_cn
   if (rc != VS_OK) return rc;
   const BlockList bl = blocklist_layout(*p, false, ws);
   hipStream_t st = (hipStream_t)stream;
-  hipError_t e = launch_build_blocklist(*p, s_idx, s_cnt, false, bl, st);
+  hipError_t e = launch_build_blocklist(*p, s_idx, s_cnt, false, bl, nullptr, st);
   if (e != hipSuccess) return VS_ERR_HIP;
   return hip_status(launch_count_tiles(*p, v_idx, v_cnt, bl, tiles, st));
 }

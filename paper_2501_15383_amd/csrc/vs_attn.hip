@@ -1126,101 +1126,148 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// Block list of one head from its selected slash offsets (one workgroup per head).
+// Block list of one head from its selected slash offsets.
 // Offset o crosses, inside a 64-aligned query block, the key blocks of diagonals floor(o/64)
 // and, when o is not a multiple of 64, floor(o/64) + 1: these set the bitmap A.  The entry
 // list then holds every cc for which A has a bit in [cc - (NQB-1), cc], with the per-query-
 // block mask, in ascending order, followed by sentinels up to the end of the row.
-// ---------------------------------------------------------------------------------------------
-// With req != null the launch builds one list per (request, head), blockIdx.x = r * n_heads + h:
+// With req != null the launch builds one list per (request, head), blockIdx.y = r * n_heads + h:
 // offsets, their count, the number of key blocks and "dense" (no offsets given) come from the
 // request; a request outside the bounds the workspace was sized for gets no list (the attention
-// kernel skips it).
+// kernel skips it).  The workgroup of the first list also clears the n_zero words at `zero` (the
+// attention launch's counters).
+//
+// A sparse list is one workgroup's (blockIdx.x = 0) and bound by latency, not bytes (6,096 offsets
+// in, 16K bits and up to 64 KB of entries out).  The bitmap is collected in LDS, kBlWin words at a
+// time: neighbouring offsets fall into the same few words, and the same OR-ing done with atomics in
+// global memory stood in line there (110-228 us for 28-40 heads at 256K-1M keys by where the
+// offsets crowd, against 17-19 us now).  Entries are then written a 64-bit word pair at a time with
+// a lane per bit, so that the stores of a wave are contiguous.  A dense list needs no collecting and
+// is cut into kBlDensePart entries per workgroup.
+// ---------------------------------------------------------------------------------------------
+constexpr int kBlThreads = 1024;
+constexpr int kBlWin = 4096;        // bitmap words in LDS at a time (8.4M keys)
+constexpr int kBlDensePart = 4096;  // entries of a dense list per workgroup
 template <int NQB>
-__global__ __launch_bounds__(256) void k_build_blocklist(const int32_t* s_idx, const int32_t* s_cnt,
-                                                         int32_t s_budget, int dense, int n_blk,
-                                                         int n_words, int ent_stride, uint32_t* bm_a,
-                                                         uint32_t* ent, const vs_request* req, int n_heads,
-                                                         int64_t max_q_len, int64_t max_n_k) {
-  int h = blockIdx.x;
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  uint32_t* A = bm_a + (int64_t)blockIdx.x * n_words;
-  uint32_t* E = ent + (int64_t)blockIdx.x * ent_stride;
+__global__ __launch_bounds__(kBlThreads) void k_build_blocklist(const int32_t* s_idx, const int32_t* s_cnt,
+                                                                int32_t s_budget, int dense, int n_blk,
+                                                                int n_words, int ent_stride, uint32_t* bm_a,
+                                                                uint32_t* ent, const vs_request* req, int n_heads,
+                                                                int64_t max_q_len, int64_t max_n_k,
+                                                                uint32_t* zero, int n_zero) {
+  constexpr int NW = kBlThreads / 64;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int part = blockIdx.x, list = blockIdx.y;
+  int h = list;
+  uint32_t* const A = bm_a + (int64_t)list * n_words;
+  uint32_t* const E = ent + (int64_t)list * ent_stride;
+  if (part == 0 && list == 0)
+    for (int x = tid; x < n_zero; x += kBlThreads) zero[x] = 0u;
   if (req) {
-    const vs_request rq = req[blockIdx.x / n_heads];
-    h = blockIdx.x % n_heads;
+    const vs_request rq = req[list / n_heads];
+    h = list % n_heads;
     if (rq.q_len < 1 || rq.q_len > max_q_len || rq.q_start < 0 || rq.q_start + rq.q_len > max_n_k) return;
     dense = rq.s_idx == nullptr;
     if (!dense && !rq.s_cnt) return;
     s_idx = rq.s_idx; s_cnt = rq.s_cnt;
     n_blk = (int)((rq.q_start + rq.q_len + kBlock - 1) / kBlock);
   }
-  __shared__ uint32_t wsum[4];
-  __shared__ uint32_t running;
-  for (int w = tid; w < n_words; w += 256) {
-    uint32_t x = 0;
-    if (dense) {
-      const int lo = w * 32;
-      if (lo + 32 <= n_blk) x = ~0u;
-      else if (lo < n_blk) x = (1u << (n_blk - lo)) - 1u;
-    }
-    A[w] = x;
-  }
-  if (tid == 0) running = 0;
-  __syncthreads();
-  if (!dense) {
-    const int cnt = s_cnt[h];
-    const int32_t* so = s_idx + (int64_t)h * s_budget;
-    for (int i = tid; i < cnt; i += 256) {
-      const int o = so[i], ad = o >> 6;
-      if (ad < n_blk) atomicOr(&A[ad >> 5], 1u << (ad & 31));
-      if ((o & 63) && ad + 1 < n_blk) atomicOr(&A[(ad + 1) >> 5], 1u << ((ad + 1) & 31));
-    }
-    __syncthreads();
-  }
-  // ordered compaction of the U bits, 256 words per round
-  for (int w0 = 0; w0 < n_words; w0 += 256) {
-    const int w = w0 + tid;
-    uint32_t cur = 0, prev = 0;
-    if (w < n_words) { cur = A[w]; prev = w ? A[w - 1] : 0u; }
-    uint32_t u = cur;
-#pragma unroll
-    for (int sft = 1; sft < NQB; ++sft) u |= (cur << sft) | (prev >> (32 - sft));
-    const uint32_t c = __popc(u);
-    // exclusive scan of c over the workgroup
-    uint32_t inc = c;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const uint32_t y = __shfl_up(inc, d);
-      if (lane >= d) inc += y;
-    }
-    if (lane == 63) wsum[wv] = inc;
-    __syncthreads();
-    uint32_t pos = running + inc - c;
-    for (int x = 0; x < wv; ++x) pos += wsum[x];
-    const uint64_t a64 = ((uint64_t)cur << 32) | prev;  // bit (32 + b) = A bit 32 w + b
-    while (u) {
-      const int b = __builtin_ctz(u);
-      u &= u - 1;
-      // mask bit t = A bit (32 w + b - (NQB-1) + t)
-      const uint32_t mask = (uint32_t)(a64 >> (32 + b - (NQB - 1))) & ((1u << NQB) - 1u);
-      E[pos++] = ((uint32_t)(32 * w + b) << 4) | mask;
-    }
-    __syncthreads();
-    if (tid == 255) running = pos;
-    __syncthreads();
-  }
-  for (int i = running + tid; i < ent_stride; i += 256) E[i] = kEntSentinel;
-  // The last words of the bitmap row (beyond every diagonal): the last one tells the attention kernel how
-  // sparse the list is: sync segments of this head are 2^shift times the base size, so that a
-  // segment holds about as many listed key blocks as it would in a dense list.
-  if (tid == 0) {
-    const uint32_t n_ent = running > 0 ? running : 1u;
+  // The last two words of the bitmap row lie beyond every diagonal.  The last one tells the attention
+  // kernel how sparse the list is: sync segments of this head are 2^shift times the base size, so
+  // that a segment holds about as many listed key blocks as it would in a dense list.
+  auto write_tail = [&](uint32_t n_list) {
+    const uint32_t n_ent = n_list > 0 ? n_list : 1u;
     int shift = 0;
     while (shift < 4 && ((uint32_t)n_blk >> (shift + 1)) >= n_ent) ++shift;
     A[n_words - 1] = (uint32_t)shift;
-    A[n_words - 2] = running;  // length of the list: the head's share of the work (k_attn_schedule)
+    A[n_words - 2] = n_list;  // length of the list: the head's share of the work (k_attn_schedule)
+  };
+  if (dense) {
+    const int n_list = n_blk + NQB - 1, all = (1 << NQB) - 1;
+    for (int i = part * kBlDensePart + tid; i < ent_stride && (i < (part + 1) * kBlDensePart || (int)gridDim.x == part + 1);
+         i += kBlThreads) {
+      uint32_t e = kEntSentinel;
+      if (i < n_list) {   // mask bit t = diagonal i - (NQB - 1) + t exists
+        int mask = all;
+        if (i < NQB - 1) mask &= all << (NQB - 1 - i);
+        if (i >= n_blk) mask &= all >> (i - n_blk + 1);
+        e = ((uint32_t)i << 4) | (uint32_t)mask;
+      }
+      E[i] = e;
+    }
+    if (part == 0) {
+      for (int w = tid; w < n_words - 2; w += kBlThreads) {
+        const int lo = w * 32;
+        A[w] = lo + 32 <= n_blk ? ~0u : (lo < n_blk ? (1u << (n_blk - lo)) - 1u : 0u);
+      }
+      if (tid == 0) write_tail((uint32_t)n_list);
+    }
+    return;
   }
+  if (part != 0) return;
+
+  __shared__ uint32_t aw[kBlWin + 2];   // aw[1 + w]: bitmap word w0 + w; aw[0]: the word before the window
+  __shared__ uint32_t wsum[NW];
+  const int cnt = s_cnt[h];
+  const int32_t* const so = s_idx + (int64_t)h * s_budget;
+  uint32_t running = 0, before = 0;
+  for (int w0 = 0; w0 < n_words - 2; w0 += kBlWin) {
+    const int nw = n_words - 2 - w0 < kBlWin ? n_words - 2 - w0 : kBlWin;
+    for (int w = tid; w <= nw; w += kBlThreads) aw[w] = w ? 0u : before;
+    __syncthreads();
+    for (int i = tid; i < cnt; i += kBlThreads) {
+      const int o = so[i], ad = o >> 6;
+      const int r0 = (ad >> 5) - w0, r1 = ((ad + 1) >> 5) - w0;
+      if (ad < n_blk && r0 >= 0 && r0 < nw) atomicOr(&aw[1 + r0], 1u << (ad & 31));
+      if ((o & 63) && ad + 1 < n_blk && r1 >= 0 && r1 < nw) atomicOr(&aw[1 + r1], 1u << ((ad + 1) & 31));
+    }
+    __syncthreads();
+    for (int w = tid; w < nw; w += kBlThreads) A[w0 + w] = aw[1 + w];
+    before = aw[nw];
+    // a wave's words: wg groups of 32 words, starting at word wlo
+    const int wg = (((nw + 31) >> 5) + NW - 1) / NW, wlo = wv * wg * 32;
+    auto listed = [&](int w) -> uint32_t {  // entries cc = 32 (w0 + w) .. + 31 of the list
+      if (w >= nw) return 0u;
+      const uint32_t cur = aw[1 + w], prev = aw[w];
+      uint32_t u = cur;
+#pragma unroll
+      for (int sft = 1; sft < NQB; ++sft) u |= (cur << sft) | (prev >> (32 - sft));
+      return u;
+    };
+    uint32_t c = 0;
+    for (int g = 0; g < wg; g += 2) c += g + (lane >> 5) < wg ? __popc(listed(wlo + 32 * g + lane)) : 0u;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) c += __shfl_xor(c, d);
+    if (lane == 0) wsum[wv] = c;
+    __syncthreads();
+    uint32_t pos = running, total = 0;
+    for (int x = 0; x < NW; ++x) {
+      if (x < wv) pos += wsum[x];
+      total += wsum[x];
+    }
+    for (int w = wlo; w < wlo + 32 * wg && w < nw; w += 2) {
+      // (uniform: the same LDS words in every lane)
+      const uint64_t m = (uint64_t)listed(w) | ((uint64_t)listed(w + 1) << 32);
+      const uint64_t cur = (uint64_t)aw[1 + w] | (w + 1 < nw ? (uint64_t)aw[2 + w] << 32 : 0ull);
+      const uint32_t prev = aw[w];
+      uint32_t mask = 0;   // mask bit t = A bit (bit index - (NQB - 1) + t)
+#pragma unroll
+      for (int t = 0; t < NQB; ++t) {
+        constexpr int kTop = NQB - 1;
+        const int sh = kTop - t;
+        const uint64_t x = sh ? (cur << sh) | (prev >> (32 - sh)) : cur;
+        mask |= (uint32_t)((x >> lane) & 1ull) << t;
+      }
+      if ((m >> lane) & 1ull)
+        E[pos + __popcll(m & ((1ull << lane) - 1ull))] = ((uint32_t)(32 * (w0 + w) + lane) << 4) | mask;
+      pos += __popcll(m);
+    }
+    running += total;
+    __syncthreads();   // wsum and aw are rewritten by the next window
+  }
+  for (int i = running + tid; i < ent_stride; i += kBlThreads) E[i] = kEntSentinel;
+  if (tid == 0) write_tail(running);
 }
 
 // Union list of a sparse single-token request whose heads are packed into rows (one workgroup per
@@ -1324,16 +1371,6 @@ __global__ __launch_bounds__(256) void k_count_tiles(const int32_t* v_idx, const
 }
 
 // ---------------------------------------------------------------------------------------------
-hipError_t launch_build_blocklist(const vs_params& p, const int32_t* s_idx, const int32_t* s_cnt,
-                                  bool dense, const BlockList& bl, hipStream_t st) {
-  const int64_t n_k = p.q_start + p.q_len;
-  const int n_blk = (int)ceil_div(n_k, kBlock);
-  hipLaunchKernelGGL((k_build_blocklist<kAttnQBlocks>), dim3(bl.heads), dim3(256), 0, st, s_idx, s_cnt,
-                     p.slash_budget, dense ? 1 : 0, n_blk, (int)bl.words, (int)bl.ent_stride, bl.bm_a, bl.ent,
-                     (const vs_request*)nullptr, 1, (int64_t)0, (int64_t)0);
-  return hipGetLastError();
-}
-
 // Pace keeping of the persistent launch: key blocks per sync segment.  The members of a group
 // (one XCD) may be at most two segments apart, so about three segments of K and V (64 KiB per
 // block at D = 128) are live in the caches at a time.  0 = automatic: 64 blocks at D = 128
@@ -1454,10 +1491,12 @@ __global__ __launch_bounds__(1024) void k_attn_schedule(const AttnArgs a, int32_
     }
     return;
   }
-  if (tid == 0) {
-    double sum = 0;
-    for (int h = 0; h < a.n_q_heads; ++h) sum += (double)a.bm_a[(int64_t)h * a.bm_stride + a.bm_words - 2];
-    avg_ent = (float)(sum / a.n_q_heads);
+  if (tid < 64) {
+    uint64_t sum = 0;
+    for (int h = tid; h < a.n_q_heads; h += 64) sum += a.bm_a[(int64_t)h * a.bm_stride + a.bm_words - 2];
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) sum += __shfl_xor((unsigned long long)sum, d);
+    if (tid == 0) avg_ent = (float)((double)sum / a.n_q_heads);
   }
   __syncthreads();
   const int n_full_gr = a.n_full * a.n_q_heads;
@@ -1482,25 +1521,49 @@ __global__ __launch_bounds__(1024) void k_attn_schedule(const AttnArgs a, int32_
     order[rank] = (uint16_t)gr;
   }
   __syncthreads();
-  if (tid == 0) {
-    float load[8];
-    int cnt[8];
-    for (int g = 0; g < 8; ++g) { load[g] = 0.f; cnt[g] = 0; }
-    for (int i = 0; i < n_gr; ++i) {
-      int g = 0;
-      for (int x = 1; x < 8; ++x)
-        if (load[x] < load[g]) g = x;
-      const int gr = order[i];
-      sched[g * n_gr + cnt[g]++] = gr;
-      load[g] += w[gr];
+  // Lane g (and g + 8, ...) of the first wave keeps the load of group g.  A group's key is its load's float
+  // image (loads are >= 0, so the images are ordered like them) with the group in the low three bits: the
+  // least loaded group is three lane exchanges away.  The 64 next rounds wait in registers.  (One thread
+  // walking eight loads in memory took 0.65 us per round, 104 us for the 160 rounds of a 40-head chunk, now 26.)
+  if (tid < 64) {
+    const int g = tid & 7;
+    float load = 0.f;
+    int cnt = 0;
+    for (int i0 = 0; i0 < n_gr; i0 += 64) {
+      const int mine = i0 + tid < n_gr ? (int)order[i0 + tid] : 0;
+      const float wmine = w[mine];
+      for (int i = 0; i < 64 && i0 + i < n_gr; ++i) {
+        const uint32_t key = (__float_as_uint(load) & ~7u) | (uint32_t)g;
+        auto least = [](uint32_t x, uint32_t y) { return x < y ? x : y; };
+        uint32_t m = least(key, (uint32_t)__builtin_amdgcn_mov_dpp((int)key, 0xB1, 0xF, 0xF, true));  // lane ^ 1
+        m = least(m, (uint32_t)__builtin_amdgcn_mov_dpp((int)m, 0x4E, 0xF, 0xF, true));               // lane ^ 2
+        m = least(m, (uint32_t)__builtin_amdgcn_mov_dpp((int)m, 0x141, 0xF, 0xF, true));              // the other four of eight
+        const int gr = __builtin_amdgcn_readlane(mine, i);
+        const float wt = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(wmine), i));
+        if (key == m) {
+          if (tid < 8) sched[g * n_gr + cnt] = gr;
+          ++cnt;
+          load += wt;
+        }
+      }
     }
-    for (int g = 0; g < 8; ++g)
-      for (int r = cnt[g]; r < n_gr; ++r) sched[g * n_gr + r] = -1;
+    if (tid < 8)
+      for (int r = cnt; r < n_gr; ++r) sched[g * n_gr + r] = -1;
   }
 }
 
-__global__ __launch_bounds__(256) void k_fill_zero_u32(uint32_t* p, int64_t n) {
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) p[i] = 0u;
+// One list per head (one for all heads when dense); sync_ws: the attention launch's counters, cleared
+// on the way where that launch keeps pace (null: none to clear).
+hipError_t launch_build_blocklist(const vs_params& p, const int32_t* s_idx, const int32_t* s_cnt,
+                                  bool dense, const BlockList& bl, void* sync_ws, hipStream_t st) {
+  const int64_t n_k = p.q_start + p.q_len;
+  const int n_blk = (int)ceil_div(n_k, kBlock);
+  const int n_zero = sync_ws && attn_split(p, dense) == 1 ? (int)(attn_counter_bytes(p) / sizeof(uint32_t)) : 0;
+  const unsigned parts = dense ? (unsigned)ceil_div(bl.ent_stride, kBlDensePart) : 1u;
+  hipLaunchKernelGGL((k_build_blocklist<kAttnQBlocks>), dim3(parts, (unsigned)bl.heads), dim3(kBlThreads), 0, st, s_idx,
+                     s_cnt, p.slash_budget, dense ? 1 : 0, n_blk, (int)bl.words, (int)bl.ent_stride, bl.bm_a, bl.ent,
+                     (const vs_request*)nullptr, 1, (int64_t)0, (int64_t)0, (uint32_t*)sync_ws, n_zero);
+  return hipGetLastError();
 }
 
 // Per-device set-up, done once for each device a launch is made on (with that device current):
@@ -1616,8 +1679,6 @@ hipError_t launch_attention(const vs_params& p, const void* q, const DcaArgs* dc
   a.sched = sched;
   if (a.n_split == 1) hipLaunchKernelGGL(k_attn_schedule, dim3(1), dim3(1024), 0, st, a, sched,
                                         g_sched_in_turn.load(std::memory_order_relaxed));
-  hipLaunchKernelGGL(k_fill_zero_u32, dim3((unsigned)ceil_div(8 * (int64_t)a.n_sync, 256)), dim3(256), 0, st,
-                     a.arrive, 8 * (int64_t)a.n_sync);
   const dim3 grid((unsigned)a.n_wg), block(128 * NQB);
   const bool split = a.n_split > 1;
 #define VS_ATTN_LAUNCH(DD, DCA_, SPLIT_) \
@@ -1721,9 +1782,9 @@ hipError_t launch_attention_batch(const vs_params& p, const vs_request* req, int
   if (members < 1) members = 1;
   if (units < 8 * (int64_t)members) members = (int)ceil_div(units, 8);
   a.members = members; a.n_wg = 8 * members; a.n_full = 0; a.n_rem = 0;
-  hipLaunchKernelGGL((k_build_blocklist<NQB>), dim3((unsigned)lists), dim3(256), 0, st, (const int32_t*)nullptr,
+  hipLaunchKernelGGL((k_build_blocklist<NQB>), dim3(1, (unsigned)lists), dim3(kBlThreads), 0, st, (const int32_t*)nullptr,
                      (const int32_t*)nullptr, p.slash_budget, 0, 0, (int)words, (int)ent_stride, bm_a, ent, req,
-                     (int)p.n_q_heads, (int64_t)p.q_len, n_k);
+                     (int)p.n_q_heads, (int64_t)p.q_len, n_k, (uint32_t*)nullptr, 0);
   if (a.group > 1 && a.group <= kPackedSparseMaxGroup)
     hipLaunchKernelGGL(k_build_union, dim3((unsigned)ulists), dim3(256), 0, st, req, (int)p.n_q_heads,
                        (int)p.n_kv_heads, (int64_t)p.q_len, n_k, (int)words, (int)ent_stride, bm_a, a.bm_u, ent_u, ent_hm);
