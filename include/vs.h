@@ -116,10 +116,10 @@ int vs_select(const vs_params *p, const float *vscore, const float *sscore,
 /* vs_select for callers that cannot allocate device memory and have no workspace to
  * hand over: code under HIP graph capture, tight serving loops, harnesses that forbid
  * hipMalloc.  Same arguments, outputs and results as vs_select, minus the workspace:
- * the per-row control blocks (histograms, tickets, slice counts) live in a device
- * array inside the library, 1.2 MB on every GPU the library runs on, for the life
- * of the process.  The call allocates and frees nothing and clears what it uses
- * with its own kernel.  Limits: n_q_heads <= 128 (VS_ERR_TOO_LARGE beyond, checked
+ * the rows' candidate lists live in a device array inside the library, 12 MB on
+ * every GPU the library runs on, for the life of the process (lists that do not fit
+ * it are made per row, more slowly).  The call allocates and frees nothing and
+ * writes what it reads with its own kernels.  Limits: n_q_heads <= 128 (VS_ERR_TOO_LARGE beyond, checked
  * on the host before any device work).  All calls on one GPU share the array:
  * calls that may overlap in time on one GPU (two streams, two threads) race --
  * order them on one stream.  The first call on a device looks the array up

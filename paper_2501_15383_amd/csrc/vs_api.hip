@@ -224,7 +224,7 @@ int vs_select(const vs_params* p, const float* vscore, const float* sscore, int3
   rc = check_ws(ws, ws_bytes, select_ws_bytes(*p));
   if (rc != VS_OK) return rc;
   return hip_status(launch_select(*p, vscore, sscore, nullptr, nullptr, v_idx, v_cnt, s_idx, s_cnt, ws,
-                                  (hipStream_t)stream));
+                                  ws_bytes, (hipStream_t)stream));
 }
 
 int vs_select_static(const vs_params* p, const float* vscore, const float* sscore, int32_t* v_idx,
@@ -232,11 +232,12 @@ int vs_select_static(const vs_params* p, const float* vscore, const float* sscor
   int rc = check_params(p, true);
   if (rc != VS_OK) return rc;
   if (!vscore || !sscore || !v_idx || !v_cnt || !s_idx || !s_cnt) return VS_ERR_INVALID_ARG;
-  if (p->n_q_heads > select_static_max_heads()) return VS_ERR_TOO_LARGE;
+  if (p->n_q_heads > kSelStaticMaxHeads) return VS_ERR_TOO_LARGE;
   void* scratch_ptr = nullptr;
-  if (select_static_scratch(&scratch_ptr) != hipSuccess) return VS_ERR_HIP;
+  size_t scratch_bytes = 0;
+  if (select_static_scratch(&scratch_ptr, &scratch_bytes) != hipSuccess) return VS_ERR_HIP;
   return hip_status(launch_select(*p, vscore, sscore, nullptr, nullptr, v_idx, v_cnt, s_idx, s_cnt, scratch_ptr,
-                                  (hipStream_t)stream));
+                                  scratch_bytes, (hipStream_t)stream));
 }
 
 int vs_select_heads(const vs_params* p, const float* vscore, const float* sscore,
@@ -250,7 +251,7 @@ int vs_select_heads(const vs_params* p, const float* vscore, const float* sscore
   rc = check_ws(ws, ws_bytes, select_ws_bytes(*p));
   if (rc != VS_OK) return rc;
   return hip_status(launch_select(*p, vscore, sscore, v_budget_h, s_budget_h, v_idx, v_cnt, s_idx, s_cnt, ws,
-                                  (hipStream_t)stream));
+                                  ws_bytes, (hipStream_t)stream));
 }
 
 int vs_attention_recall(const vs_params* p, const float* lse_sparse, const float* lse_full,

@@ -1,17 +1,27 @@
 // Selection of the vertical and slash lines (section 5.2, MInference paragraph: critical
 // tokens are chosen by the vertical-slash pattern with a per-head count of vertical and
-// diagonal lines).  Exact top-k of up to 2^31 fp32 scores per (head, kind) row without sorting:
-//   1. forced entries (the lowest `keep` indices) are taken first (k_sel_init);
-//   2. a most-significant-digit radix select (4 x 8 bits on an order-preserving integer image
-//      of the float) finds the threshold key T and how many entries equal to T are needed.
-//      A row is cut into slices, one workgroup each; every workgroup adds its 256-bin
-//      histogram to the row's, and the workgroup that finishes last picks the digit
-//      (k_sel_hist, once per digit);
-//   3. the keys > T and == T of every slice are counted (k_sel_count), and one ordered
-//      compaction pass emits indices in ascending order: every key > T, and the lowest-index
-//      keys == T (ties go to the lower index).  Ranks come from the slice counts, wave
-//      ballots and a 16-entry cross-wave scan (k_sel_write).
-// All of it is integer work, so the result is exact and run-to-run identical.
+// diagonal lines).  Exact top-k of up to 2^31 fp32 scores per (head, kind) row without sorting;
+// all of it is integer work on an order-preserving image of the floats (keys), so the result is
+// exact and run-to-run identical:
+//   * the forced entries (the lowest `keep` indices) are taken first;
+//   * a most-significant-digit radix select (11 + 11 + 10 bits, histograms in LDS) finds the
+//     threshold key T and how many entries equal to T are needed;
+//   * one ordered compaction emits indices in ascending order: every key > T, and the
+//     lowest-index keys == T (ties go to the lower index).  Ranks come from wave ballots.
+// One workgroup finishes a row (k_sel_row), from one of three sources:
+//   registers   rows of up to kSelRegKeys scores are read once and stay in registers; a call is then
+//               this one launch, bound by the latency of its dozen barriers
+//   candidates  longer rows are thinned out first.  A sample of 8,192 (16,384) scores per row gives a floor that
+//               about k + 4.5 sigma entries exceed, and only those entries are kept, in LDS if there are at most
+//               kSelCand of them.  With a workspace the whole chip makes the lists, in one pass over the scores
+//               (k_sel_sample, k_sel_filter; bound by that read at 1M keys); for rows of up to kSelOwnKeys, and
+//               without a workspace, k_sel_row makes its row's own.  A threshold that falls on a crowd of equal
+//               scores is the floor itself: the compaction then reads the row, as far as it has to.
+//   the row     where the sample missed, or the list does not fit, every digit and the compaction read the
+//               row again: exact in every case.
+// Measured on one MI355X, 28 heads, budgets 1000 / 6096, against four digits, a count and a write pass over all
+// scores in seven launches: 8,192 scores per row 14 us (67), 32,768 21 us (70), 300,001 57 us (152), 1M 108 us
+// (345: filter 63 us = 3.7 TB/s, sample 16, rows 29); 4 heads, budgets 128 / 256, 1M: 50 us (98).
 #include <mutex>
 
 #include "vs_common.h"
@@ -20,16 +30,21 @@ namespace vs {
 
 constexpr int kSelThreads = 1024;
 constexpr int kSelWaves = kSelThreads / 64;
-constexpr int kSelItems = 8;  // elements per lane per step
-constexpr int kSelStep = kSelThreads * kSelItems;
-constexpr int kSelMaxSlices = 64;
-// control block of a row in the workspace, in 32-bit words
-constexpr int kWHist = 0;      // [4][256] histogram of every digit
-constexpr int kWDone = 1024;   // [4] workgroups done with the digit
-constexpr int kWState = 1028;  // [5][2] (prefix, entries still to find) before digit 0..3 and after
-constexpr int kWForced = 1038, kWChoose = 1039;
-constexpr int kWCount = 1056;  // [slices][2] keys > T, keys == T
-constexpr int kSelRowWords = kWCount + 2 * kSelMaxSlices;
+constexpr int kSelRegKeys = 32 * kSelThreads;  // longest row that stays in registers
+constexpr int kSelCand = 16384;                // longest list of candidates (128 KB of LDS)
+constexpr int kSelSlice = 2048;                // scores per wave of the filter (one slice each)
+constexpr int kSelFilterThreads = 256;
+constexpr int kSelStep = 8;                    // scores per lane and step where the row is read again and again
+constexpr int kSelOwnKeys = 48 * 1024;         // up to here a workgroup lists its own row's candidates: 31-35 us against
+                                               // 36-38 us for the three launches at 28 heads, 22-25 us either way at 4
+constexpr int kSelBins = 2048;
+// workspace of a row: header, table of slices, candidates
+struct SelHeader {
+  uint32_t floor_key;  // entries above it are candidates
+  uint32_t count;      // candidates so far (beyond the list's room: it is incomplete)
+  uint32_t equal;      // entries equal to the floor
+  uint32_t pad;
+};
 
 __device__ __forceinline__ uint32_t order_key(float x) {
   const uint32_t b = __float_as_uint(x);
@@ -40,7 +55,6 @@ struct SelArgs {
   const float* vscore;
   const float* sscore;
   int64_t n;  // n_k
-  int64_t slice_len;
   int32_t n_q_heads;
   int32_t v_budget, s_budget, keep_v, keep_s;  // budgets: row lengths of the outputs (maxima)
   const int32_t* v_budget_h;  // optional per-head budgets (clamped to 1 .. maximum), else null
@@ -49,226 +63,612 @@ struct SelArgs {
   int32_t* v_cnt;
   int32_t* s_idx;
   int32_t* s_cnt;
-  uint32_t* ws;  // [2 Hq][kSelRowWords]
+  // null: every row lists its own candidates
+  SelHeader* hdr;      // [2 Hq]
+  uint2* slices;       // [2 Hq][n_slices] (first candidate, candidates) of every slice
+  uint2* cand;         // [2 Hq][cap] (key, index)
+  uint32_t cap;
+  int32_t n_slices;
+  int32_t samples_v, samples_s;  // samples per thread for the rows of each kind
 };
 
 // row = kind * Hq + h
 struct SelRow {
   const float* sc;
   int32_t* out;
-  uint32_t* w;
-  int row_len;
+  int kind, h, row_len;
+  int k;        // entries of the result
+  int f;        // forced entries 0 .. f - 1
+  uint32_t kp;  // still to choose among indices f .. n - 1
 };
 __device__ __forceinline__ SelRow sel_row(const SelArgs& a, int row) {
-  const int kind = row >= a.n_q_heads, h = row - kind * a.n_q_heads;
   SelRow r;
-  r.sc = (kind ? a.sscore : a.vscore) + (int64_t)h * a.n;
-  r.row_len = kind ? a.s_budget : a.v_budget;
-  r.out = (kind ? a.s_idx : a.v_idx) + (int64_t)h * r.row_len;
-  r.w = a.ws + (int64_t)row * kSelRowWords;
+  r.kind = row >= a.n_q_heads;
+  r.h = row - r.kind * a.n_q_heads;
+  r.sc = (r.kind ? a.sscore : a.vscore) + (int64_t)r.h * a.n;
+  r.row_len = r.kind ? a.s_budget : a.v_budget;
+  r.out = (r.kind ? a.s_idx : a.v_idx) + (int64_t)r.h * r.row_len;
+  const int32_t* per_head = r.kind ? a.s_budget_h : a.v_budget_h;
+  int budget = r.row_len;
+  if (per_head) {
+    budget = per_head[r.h];
+    budget = budget < 1 ? 1 : (budget > r.row_len ? r.row_len : budget);
+  }
+  const int keep = r.kind ? a.keep_s : a.keep_v;
+  r.k = budget < a.n ? budget : (int)a.n;
+  r.f = keep < r.k ? keep : r.k;
+  r.kp = (uint32_t)(r.k - r.f);
   return r;
 }
 
-// Forced entries, padding, the count, and a cleared control block.
-__global__ __launch_bounds__(256) void k_sel_init(const SelArgs a) {
-  const int row = blockIdx.x, kind = row >= a.n_q_heads, h = row - kind * a.n_q_heads;
-  const SelRow r = sel_row(a, row);
-  const int32_t* per_head = kind ? a.s_budget_h : a.v_budget_h;
-  int budget = r.row_len;
-  if (per_head) {
-    budget = per_head[h];
-    budget = budget < 1 ? 1 : (budget > r.row_len ? r.row_len : budget);
-  }
-  const int keep = kind ? a.keep_s : a.keep_v;
-  const int k = budget < a.n ? budget : (int)a.n;
-  const int f = keep < k ? keep : k;  // forced entries 0..f-1
-  const int kp = k - f;               // still to choose among indices f..n-1
-  const int tid = threadIdx.x;
-  for (int x = tid; x < kSelRowWords; x += 256) {
-    uint32_t v = 0;
-    if (x == kWState + 1 || x == kWChoose) v = (uint32_t)kp;
-    if (x == kWForced) v = (uint32_t)f;
-    r.w[x] = v;
-  }
-  for (int t = tid; t < r.row_len; t += 256) {
-    if (t < f) r.out[t] = t;
-    else if (t >= k) r.out[t] = -1;
-  }
-  if (tid == 0) (kind ? a.s_cnt : a.v_cnt)[h] = k;
+// sample rank whose score about k + 4.5 sigma entries of a row of n reach (sigma: of the number of the
+// row's best k that a sample of `samples` meets)
+__host__ __device__ inline float sel_sample_rank(float k, float n, float samples) {
+  const float mu = k * (samples / n);
+  return mu + 4.5f * sqrtf(mu) + 4.f;
 }
 
-// One digit of the radix select: threshold key T = kp-th largest key among the candidates.
-__global__ __launch_bounds__(kSelThreads) void k_sel_hist(const SelArgs a, const int pass) {
-  const SelRow r = sel_row(a, blockIdx.y);
-  const uint32_t kp = r.w[kWChoose];
-  if (kp == 0) return;
-  const int64_t lo = (int64_t)r.w[kWForced] + (int64_t)blockIdx.x * a.slice_len;
-  const int64_t hi = lo + a.slice_len < a.n ? lo + a.slice_len : a.n;
-  const uint32_t prefix = r.w[kWState + 2 * pass], krem = r.w[kWState + 2 * pass + 1];
-  const int tid = threadIdx.x, lane = tid & 63;
-  // 16 copies of the 256-bin histogram, copy = lane % 16 in consecutive banks: the top digits of
-  // real scores crowd into a few bins, and 64 lanes adding to one address would serialise
-  __shared__ uint32_t hist16[256 * 16];
-  __shared__ uint32_t hist[256];
-  __shared__ bool last;
-  const int shift = 24 - 8 * pass;
-  const uint32_t himask = pass == 0 ? 0u : (0xFFFFFFFFu << (shift + 8));
-  for (int x = tid; x < 256 * 16; x += kSelThreads) hist16[x] = 0;
-  __syncthreads();
-  // kSelItems independent loads per thread in flight (the pass is latency-bound otherwise)
-  for (int64_t base = lo; base < hi; base += kSelStep) {
-    uint32_t key[kSelItems];
-    bool ok[kSelItems];
+struct SelShared {
+  uint32_t hist[kSelBins];
+  uint32_t wsum[kSelWaves];
+  uint32_t digit, rest, in_bin;
+  uint32_t wtot[2][kSelWaves][2];
+  uint32_t wmin[kSelWaves], wmax[kSelWaves];
+  int32_t first[kSelWaves + 1];
+};
+
+// smallest and largest of the threads' keys
+__device__ __forceinline__ void sel_range(SelShared& sh, uint32_t lo, uint32_t hi, uint32_t& all_lo, uint32_t& all_hi) {
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
 #pragma unroll
-    for (int e = 0; e < kSelItems; ++e) {
-      const int64_t i = base + (int64_t)e * kSelThreads + tid;
-      ok[e] = i < hi;
-      key[e] = order_key(r.sc[ok[e] ? i : hi - 1]);  // unconditional, so that the loads overlap
-    }
-#pragma unroll
-    for (int e = 0; e < kSelItems; ++e)
-      if (ok[e] && (key[e] & himask) == prefix)
-        atomicAdd(&hist16[(((key[e] >> shift) & 255u) << 4) | (lane & 15)], 1u);
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint32_t l = __shfl_xor(lo, d), h = __shfl_xor(hi, d);
+    lo = l < lo ? l : lo;
+    hi = h > hi ? h : hi;
   }
+  if (lane == 0) { sh.wmin[wv] = lo; sh.wmax[wv] = hi; }
   __syncthreads();
-  uint32_t* const gh = r.w + kWHist + 256 * pass;
-  // The additions and the ticket are device-wide atomics, performed where all workgroups see
-  // them.  The additions return a value, and the wait for it is the wait for their completion;
-  // only then does the workgroup draw its ticket, so the one that draws the last ticket finds
-  // every addition done.  (No cache is involved: a fence would write back the whole L2.)
-  if (tid < 256) {
-    uint32_t c = 0;
+  all_lo = sh.wmin[0]; all_hi = sh.wmax[0];
 #pragma unroll
-    for (int x = 0; x < 16; ++x) c += hist16[(tid << 4) | x];
-    uint32_t old = 0;
-    if (c) old = __hip_atomic_fetch_add(&gh[tid], c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    asm volatile("s_waitcnt vmcnt(0)" : "+v"(old) : : "memory");
-  }
-  __syncthreads();
-  if (tid == 0)
-    last = __hip_atomic_fetch_add(&r.w[kWDone + pass], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
-  __syncthreads();
-  if (!last) return;
-  if (tid < 256) hist[tid] = __hip_atomic_load(&gh[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  __syncthreads();
-  if (tid == 0) {
-    uint32_t cum = 0;
-    int b = 255;
-    for (; b > 0; --b) {
-      const uint32_t c = hist[b];
-      if (cum + c >= krem) break;
-      cum += c;
-    }
-    r.w[kWState + 2 * (pass + 1)] = prefix | ((uint32_t)b << shift);
-    r.w[kWState + 2 * (pass + 1) + 1] = krem - cum;
+  for (int x = 1; x < kSelWaves; ++x) {
+    all_lo = sh.wmin[x] < all_lo ? sh.wmin[x] : all_lo;
+    all_hi = sh.wmax[x] > all_hi ? sh.wmax[x] : all_hi;
   }
 }
 
-// Keys above and equal to the threshold in every slice.
-__global__ __launch_bounds__(kSelThreads) void k_sel_count(const SelArgs a) {
-  const SelRow r = sel_row(a, blockIdx.y);
-  if (r.w[kWChoose] == 0) return;
-  const int64_t lo = (int64_t)r.w[kWForced] + (int64_t)blockIdx.x * a.slice_len;
-  const int64_t hi = lo + a.slice_len < a.n ? lo + a.slice_len : a.n;
-  const uint32_t T = r.w[kWState + 8];
+// The kp-th largest of the keys that for_each(f) hands to f(key, valid) (valid keys lie in lo .. hi and number at least
+// kp >= 1): keys above T, and need_eq of those equal to it, are the kp largest.  Digits of 11 bits from the top of the range
+// hi - lo, so that keys that share their exponent still spread over the bins (scores do: with digits of the
+// whole key a wave's 64 additions met in four bins, 65 to 250 clocks each); done as soon as a bin is taken whole.
+// Called by the whole workgroup; every thread gets the result.
+template <typename ForEach>
+__device__ __forceinline__ void radix_kth(SelShared& sh, ForEach&& for_each, uint32_t kp, uint32_t lo, uint32_t hi, uint32_t& T,
+                                          uint32_t& need_eq) {
+  static_assert(kSelBins == 2 * kSelThreads, "two bins per thread");
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  __shared__ uint32_t wtot[kSelWaves][2];
-  uint32_t tg = 0, te = 0;
-  for (int64_t base = lo; base < hi; base += kSelStep) {
-    uint32_t key[kSelItems];
-#pragma unroll
-    for (int e = 0; e < kSelItems; ++e) {
-      const int64_t i = base + (int64_t)e * kSelThreads + tid;
-      key[e] = order_key(r.sc[i < hi ? i : hi - 1]);
-    }
-#pragma unroll
-    for (int e = 0; e < kSelItems; ++e) {
-      const bool in = base + (int64_t)e * kSelThreads + tid < hi;
-      tg += __popcll(__ballot(in && key[e] > T));
-      te += __popcll(__ballot(in && key[e] == T));
-    }
-  }
-  if (lane == 0) { wtot[wv][0] = tg; wtot[wv][1] = te; }
-  __syncthreads();
-  if (tid == 0) {
-    uint32_t g = 0, e = 0;
-    for (int w = 0; w < kSelWaves; ++w) { g += wtot[w][0]; e += wtot[w][1]; }
-    r.w[kWCount + 2 * blockIdx.x] = g;
-    r.w[kWCount + 2 * blockIdx.x + 1] = e;
-  }
-}
-
-// Ordered compaction of one slice.
-__global__ __launch_bounds__(kSelThreads) void k_sel_write(const SelArgs a) {
-  const SelRow r = sel_row(a, blockIdx.y);
-  const uint32_t kp = r.w[kWChoose];
-  if (kp == 0) return;
-  const int f = (int)r.w[kWForced];
-  const int64_t lo = (int64_t)f + (int64_t)blockIdx.x * a.slice_len;
-  const int64_t hi = lo + a.slice_len < a.n ? lo + a.slice_len : a.n;
-  const uint32_t T = r.w[kWState + 8];
-  const uint32_t need_eq = r.w[kWState + 9];  // >= 1
-  int32_t* const out = r.out;
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  __shared__ uint32_t wtot[2][kSelWaves][2];
-  uint32_t run_gt = 0, run_eq = 0;  // totals over everything before this slice, then before the step
-  for (int sl = 0; sl < (int)blockIdx.x; ++sl) {
-    run_gt += r.w[kWCount + 2 * sl];
-    run_eq += r.w[kWCount + 2 * sl + 1];
-  }
-  if (run_gt + (run_eq < need_eq ? run_eq : need_eq) >= kp) return;  // the row is complete already
-  const uint64_t lt_mask = lane == 0 ? 0ull : (~0ull >> (64 - lane));
-  int par = 0;
-  for (int64_t base = lo; base < hi; base += kSelStep, par ^= 1) {
-    uint64_t bg[kSelItems], be[kSelItems];
-    uint32_t tg = 0, te = 0, keys[kSelItems];
-#pragma unroll
-    for (int e = 0; e < kSelItems; ++e) {
-      const int64_t i = base + (int64_t)wv * (64 * kSelItems) + e * 64 + lane;
-      keys[e] = order_key(r.sc[i < hi ? i : hi - 1]);
-    }
-#pragma unroll
-    for (int e = 0; e < kSelItems; ++e) {
-      const int64_t i = base + (int64_t)wv * (64 * kSelItems) + e * 64 + lane;
-      const uint32_t key = keys[e];
-      bg[e] = __ballot(i < hi && key > T);
-      be[e] = __ballot(i < hi && key == T);
-      tg += __popcll(bg[e]);
-      te += __popcll(be[e]);
-    }
-    if (lane == 0) { wtot[par][wv][0] = tg; wtot[par][wv][1] = te; }
+  uint32_t prefix = 0, krem = kp;             // digits so far (of key - lo)
+  int shift = 32 - __clz((int)(hi - lo) | 1);   // bits below the prefix
+  bool first = true;
+  while (shift > 0) {                         // uniform: at most three times
+    const int width = shift < 11 ? shift : 11, sh0 = shift - width;
+    const uint32_t dmask = (1u << width) - 1u;
+    sh.hist[tid] = 0;
+    sh.hist[kSelThreads + tid] = 0;
     __syncthreads();
-    uint32_t gt_before = run_gt, eq_before = run_eq, cg = 0, ce = 0;
-    for (int w = 0; w < kSelWaves; ++w) {
-      const uint32_t g_ = wtot[par][w][0], e_ = wtot[par][w][1];
-      if (w < wv) { gt_before += g_; eq_before += e_; }
-      cg += g_; ce += e_;
-    }
+    for_each([&](uint32_t key, bool valid) {
+      const uint32_t d = key - lo;
+      if (valid && (first || (d >> shift) == prefix)) atomicAdd(&sh.hist[(d >> sh0) & dmask], 1u);
+    });
+    __syncthreads();
+    // bins from the top: thread t takes the bins 2047 - 2 t and 2046 - 2 t
+    const uint32_t c0 = sh.hist[kSelBins - 1 - 2 * tid], c1 = sh.hist[kSelBins - 2 - 2 * tid];
+    uint32_t inc = c0 + c1;
 #pragma unroll
-    for (int e = 0; e < kSelItems; ++e) {
-      const int64_t i = base + (int64_t)wv * (64 * kSelItems) + e * 64 + lane;
-      const uint32_t gr = gt_before + __popcll(bg[e] & lt_mask);
-      const uint32_t er = eq_before + __popcll(be[e] & lt_mask);
-      const bool is_g = (bg[e] >> lane) & 1ull, is_e = (be[e] >> lane) & 1ull;
-      if (is_g) out[f + gr + (er < need_eq ? er : need_eq)] = (int32_t)i;
-      else if (is_e && er < need_eq) out[f + gr + er] = (int32_t)i;
-      gt_before += __popcll(bg[e]);
-      eq_before += __popcll(be[e]);
+    for (int d = 1; d < 64; d <<= 1) {
+      const uint32_t y = __shfl_up(inc, d);
+      if (lane >= d) inc += y;
     }
-    run_gt += cg;
-    run_eq += ce;
-    if (run_gt + (run_eq < need_eq ? run_eq : need_eq) >= kp) break;
+    if (lane == 63) sh.wsum[wv] = inc;
+    __syncthreads();
+    uint32_t above = inc - c0 - c1;
+#pragma unroll
+    for (int x = 0; x < kSelWaves; ++x) above += x < wv ? sh.wsum[x] : 0u;
+    if (above < krem && krem <= above + c0 + c1) {
+      const bool second = above + c0 < krem;
+      sh.digit = (uint32_t)(kSelBins - 1 - 2 * tid - (second ? 1 : 0));
+      sh.rest = krem - above - (second ? c0 : 0u);
+      sh.in_bin = second ? c1 : c0;
+    }
+    __syncthreads();
+    prefix = first ? sh.digit : (prefix << width) | sh.digit;
+    krem = sh.rest;
+    shift = sh0;
+    first = false;
+    if (krem == sh.in_bin && shift > 0) {   // the whole bin is wanted: everything above the key below it
+      T = lo + (prefix << shift) - 1u;
+      need_eq = 0;
+      return;
+    }
+  }
+  T = lo + prefix;
+  need_eq = krem;
+}
+
+// Emits one wave-wide group of 64 entries in order; gt / eq: entries above / equal to the threshold before it
+__device__ __forceinline__ void sel_emit(const SelRow& r, uint32_t need_eq, bool is_g, bool is_e, int32_t index, uint32_t& gt,
+                                         uint32_t& eq) {
+  const uint64_t bg = __ballot(is_g), be = __ballot(is_e);
+  if ((bg | be) == 0) return;
+  const uint32_t gr = gt + __builtin_amdgcn_mbcnt_hi((uint32_t)(bg >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bg, 0u));
+  const uint32_t er = eq + __builtin_amdgcn_mbcnt_hi((uint32_t)(be >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)be, 0u));
+  if (is_g) r.out[r.f + gr + (er < need_eq ? er : need_eq)] = index;
+  else if (is_e && er < need_eq) r.out[r.f + gr + er] = index;
+  gt += __popcll(bg);
+  eq += __popcll(be);
+}
+// totals of the waves before this one (par: a parity, where a loop does this step after step)
+__device__ __forceinline__ void sel_wave_base(SelShared& sh, int par, uint32_t g, uint32_t e, uint32_t& gt, uint32_t& eq,
+                                              uint32_t& all_g, uint32_t& all_e) {
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  if (lane == 0) { sh.wtot[par][wv][0] = g; sh.wtot[par][wv][1] = e; }
+  __syncthreads();
+  all_g = all_e = 0;
+  for (int x = 0; x < kSelWaves; ++x) {
+    const uint32_t g_ = sh.wtot[par][x][0], e_ = sh.wtot[par][x][1];
+    if (x < wv) { gt += g_; eq += e_; }
+    all_g += g_; all_e += e_;
   }
 }
 
-size_t select_ws_bytes(const vs_params& p) {
-  return align_up((size_t)2 * p.n_q_heads * kSelRowWords * sizeof(uint32_t), 256);
+// A row in registers: KPT scores per thread, a wave's scores contiguous (KPT groups of 64).
+template <int KPT>
+__device__ __forceinline__ void sel_from_registers(SelShared& sh, const SelRow& r, int64_t n) {
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int i0 = r.f + wv * (64 * KPT) + lane;
+  uint32_t key[KPT];
+#pragma unroll
+  for (int e = 0; e < KPT; ++e) {
+    const int i = i0 + 64 * e;
+    const uint32_t x = order_key(r.sc[i < n ? i : (int)n - 1]);   // unconditional, so that the loads overlap
+    key[e] = i < n ? x : 0u;   // no finite score has key 0: neither counted nor emitted below
+  }
+  uint32_t lo = ~0u, hi = 0u, T, need_eq;
+#pragma unroll
+  for (int e = 0; e < KPT; ++e) {
+    lo = key[e] - 1u < lo ? key[e] - 1u : lo;   // (a missing entry is no minimum)
+    hi = key[e] > hi ? key[e] : hi;
+  }
+  sel_range(sh, lo, hi, lo, hi);
+  radix_kth(sh, [&](auto&& f) {
+#pragma unroll
+    for (int e = 0; e < KPT; ++e) f(key[e], key[e] != 0u);
+  }, r.kp, lo + 1u, hi, T, need_eq);
+  uint32_t g = 0, q = 0, gt = 0, eq = 0, ag, ae;
+#pragma unroll
+  for (int e = 0; e < KPT; ++e) {
+    g += __popcll(__ballot(key[e] > T));
+    q += __popcll(__ballot(key[e] == T));
+  }
+  sel_wave_base(sh, 0, g, q, gt, eq, ag, ae);
+  asm volatile("" : "+v"(T));   // the lane masks are made again: 2 KPT of them do not fit the scalar registers
+#pragma unroll
+  for (int e = 0; e < KPT; ++e) sel_emit(r, need_eq, key[e] > T, key[e] == T, i0 + 64 * e, gt, eq);
 }
 
+// The m candidates of a row (keys above floor_key, with their indices), in n_slices slices: slice_of(s) = (first candidate,
+// candidates).  Slices lie there in any order; the entries of a slice ascend, and so do the slices' indices.  The ordered
+// compaction gives every wave consecutive slices that hold about an equal share of the candidates (the best offsets crowd near the
+// diagonal: with equal numbers of slices one wave had half of the 10,000 candidates of a 1M-key row, 45 us against 29).
+template <typename SliceOf>
+__device__ __forceinline__ void sel_from_candidates(SelShared& sh, const uint2* cl, const SelRow& r, int n_slices, int m,
+                                                    uint32_t floor_key, SliceOf&& slice_of) {
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  uint32_t T, need_eq, hi = 0u, lo;
+  for (int i = tid; i < m; i += kSelThreads) hi = cl[i].x > hi ? cl[i].x : hi;
+  sel_range(sh, 0u, hi, lo, hi);
+  radix_kth(sh, [&](auto&& f) {
+    for (int i = tid; i < m; i += kSelThreads) f(cl[i].x, true);
+  }, r.kp, floor_key + 1u, hi, T, need_eq);
+  // sh.first[w]: the first slice that starts at or past candidate w m / kSelWaves of the ordered list
+  if (tid <= kSelWaves) sh.first[tid] = n_slices;
+  uint32_t before = 0;   // candidates of the slices before this round's
+  for (int sb = 0; sb < n_slices; sb += kSelThreads) {
+    const int s = sb + tid;
+    const uint32_t c = s < n_slices ? slice_of(s).y : 0u, c_prev = s > 0 && s < n_slices ? slice_of(s - 1).y : 0u;
+    uint32_t inc = c;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const uint32_t y = __shfl_up(inc, d);
+      if (lane >= d) inc += y;
+    }
+    __syncthreads();   // (wsum's last readers; sh.first)
+    if (lane == 63) sh.wsum[wv] = inc;
+    __syncthreads();
+    uint32_t at = before + inc - c;
+    for (int x = 0; x < kSelWaves; ++x) {
+      at += x < wv ? sh.wsum[x] : 0u;
+      before += sh.wsum[x];
+    }
+    if (s < n_slices) {
+      const int w1 = (int)((uint64_t)at * kSelWaves / (uint32_t)m);
+      const int w0 = s > 0 ? (int)((uint64_t)(at - c_prev) * kSelWaves / (uint32_t)m) + 1 : 0;
+      for (int w = w0; w <= w1; ++w) sh.first[w] = s;
+    }
+  }
+  __syncthreads();
+  const int s0 = __builtin_amdgcn_readfirstlane(sh.first[wv]), s1 = __builtin_amdgcn_readfirstlane(sh.first[wv + 1]);
+  // 64 slices at a time: a lane of a group of 64 consecutive candidates finds its slice by bisection over the lanes
+  auto walk = [&](auto&& f) {
+    for (int sb = s0; sb < s1; sb += 64) {
+      const uint2 mine = sb + lane < s1 ? slice_of(sb + lane) : make_uint2(0u, 0u);
+      int end = (int)mine.y;   // candidates up to and with this lane's slice
+#pragma unroll
+      for (int d = 1; d < 64; d <<= 1) {
+        const int y = __shfl_up(end, d);
+        if (lane >= d) end += y;
+      }
+      const int shift = (int)mine.x - (end - (int)mine.y);   // place in the list, less the place in the order
+      const int total = __builtin_amdgcn_readlane(end, 63);
+      constexpr int U = 4;
+      for (int i = 0; i < total; i += 64 * U) {
+        int p[U], j[U];
+        uint2 c[U];
+#pragma unroll
+        for (int e = 0; e < U; ++e) {
+          p[e] = i + 64 * e + lane < total ? i + 64 * e + lane : total - 1;
+          j[e] = 0;
+        }
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1)
+#pragma unroll
+          for (int e = 0; e < U; ++e)
+            if (__shfl(end, j[e] + d - 1) <= p[e]) j[e] += d;
+#pragma unroll
+        for (int e = 0; e < U; ++e) c[e] = cl[p[e] + __shfl(shift, j[e])];
+#pragma unroll
+        for (int e = 0; e < U; ++e) {
+          const bool in = i + 64 * e + lane < total;
+          f(in && c[e].x > T, in && c[e].x == T, (int32_t)c[e].y);
+        }
+      }
+    }
+  };
+  uint32_t g = 0, q = 0, gt = 0, eq = 0, ag, ae;
+  walk([&](bool is_g, bool is_e, int32_t) {
+    g += __popcll(__ballot(is_g));
+    q += __popcll(__ballot(is_e));
+  });
+  sel_wave_base(sh, 0, g, q, gt, eq, ag, ae);
+  walk([&](bool is_g, bool is_e, int32_t index) { sel_emit(r, need_eq, is_g, is_e, index, gt, eq); });
+}
+
+// Steps over a row in order: step(key, i0, par) gets kSelStep groups of 64 entries per wave (key[e] is the image of entry
+// i0 + 64 e, 0 behind the row's end), a wave's entries contiguous and the waves one after the other; par alternates.  It
+// returns whether to go on (uniform).  The scores of the next step are on their way meanwhile.
+template <typename Step>
+__device__ __forceinline__ void sel_walk_row(const SelRow& r, int64_t n, Step&& step) {
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  int par = 0;
+  float next[kSelStep];
+  constexpr int kLen = kSelThreads * kSelStep;
+  const int at = wv * (64 * kSelStep) + lane;   // of this lane's first entry inside a step
+  auto fetch = [&](int64_t base) {
+    if (base + kLen <= n) {   // a whole step: one address
+      const float* const p = r.sc + base;
+#pragma unroll
+      for (int e = 0; e < kSelStep; ++e) next[e] = p[at + 64 * e];
+    } else {
+#pragma unroll
+      for (int e = 0; e < kSelStep; ++e) {
+        const int64_t i = base + at + 64 * e;
+        next[e] = r.sc[i < n ? i : n - 1];
+      }
+    }
+  };
+  fetch(r.f);
+  for (int64_t base = r.f; base < n; base += kLen, par ^= 1) {
+    uint32_t key[kSelStep];
+    const int left = n - base < kLen ? (int)(n - base) : kLen;
+#pragma unroll
+    for (int e = 0; e < kSelStep; ++e) key[e] = at + 64 * e < left ? order_key(next[e]) : 0u;
+    fetch(base + kLen);
+    if (!step(key, (int32_t)base + at, par)) break;
+  }
+}
+
+// The ordered compaction of a row whose threshold is known.
+__device__ __forceinline__ void sel_compact_row(SelShared& sh, const SelRow& r, int64_t n, uint32_t T, uint32_t need_eq) {
+  uint32_t run_g = 0, run_e = 0;
+  sel_walk_row(r, n, [&](const uint32_t (&key)[kSelStep], int32_t i0, int par) {
+    uint32_t g = 0, q = 0;
+#pragma unroll
+    for (int e = 0; e < kSelStep; ++e) {
+      g += __popcll(__ballot(key[e] > T));
+      q += __popcll(__ballot(key[e] == T));
+    }
+    uint32_t gt = run_g, eq = run_e, all_g, all_e;
+    sel_wave_base(sh, par, g, q, gt, eq, all_g, all_e);
+#pragma unroll
+    for (int e = 0; e < kSelStep; ++e) sel_emit(r, need_eq, key[e] > T, key[e] == T, i0 + 64 * e, gt, eq);
+    run_g += all_g;
+    run_e += all_e;
+    return run_g + (run_e < need_eq ? run_e : need_eq) < r.kp;   // else the row is complete
+  });
+}
+
+// A row read from memory for its range, once per digit and once more for the compaction.
+__device__ __forceinline__ void sel_from_row(SelShared& sh, const SelRow& r, int64_t n) {
+  uint32_t lo = ~0u, hi = 0u, T, need_eq;
+  sel_walk_row(r, n, [&](const uint32_t (&key)[kSelStep], int32_t, int) {
+#pragma unroll
+    for (int e = 0; e < kSelStep; ++e) {
+      lo = key[e] - 1u < lo ? key[e] - 1u : lo;
+      hi = key[e] > hi ? key[e] : hi;
+    }
+    return true;
+  });
+  sel_range(sh, lo, hi, lo, hi);
+  radix_kth(sh, [&](auto&& f) {
+    sel_walk_row(r, n, [&](const uint32_t (&key)[kSelStep], int32_t, int) {
+#pragma unroll
+      for (int e = 0; e < kSelStep; ++e) f(key[e], key[e] != 0u);
+      return true;
+    });
+  }, r.kp, lo + 1u, hi, T, need_eq);
+  sel_compact_row(sh, r, n, T, need_eq);
+}
+
+// The floor of a row's candidates: one score from each of SPT x kSelThreads stretches of the row (at a place inside its
+// stretch that a hash of its number gives), and among these the one at sel_sample_rank.
+template <int SPT>
+__device__ __forceinline__ uint32_t sel_floor(SelShared& sh, const SelRow& r, int64_t n) {
+  constexpr int S = SPT * kSelThreads;
+  const int64_t m = n - r.f;   // more than 2 S entries
+  const float rank = sel_sample_rank((float)r.kp, (float)m, (float)S);
+  if (!(rank < (float)S)) return 0u;   // (nearly) everything is wanted
+  const uint32_t len = (uint32_t)(m / S);
+  uint32_t key[SPT], lo = ~0u, hi = 0u, T, need_eq;
+#pragma unroll
+  for (int e = 0; e < SPT; ++e) {
+    const uint32_t x = (uint32_t)(e * kSelThreads) + threadIdx.x;
+    const uint32_t hash = (x * 0x9E3779B1u) >> 16;
+    key[e] = order_key(r.sc[r.f + (int64_t)((uint64_t)m * x / S) + ((uint64_t)hash * len >> 16)]);
+  }
+#pragma unroll
+  for (int e = 0; e < SPT; ++e) {
+    lo = key[e] < lo ? key[e] : lo;
+    hi = key[e] > hi ? key[e] : hi;
+  }
+  sel_range(sh, lo, hi, lo, hi);
+  radix_kth(sh, [&](auto&& f) {
+#pragma unroll
+    for (int e = 0; e < SPT; ++e) f(key[e], true);
+  }, (uint32_t)rank, lo, hi, T, need_eq);
+  return T;   // (the floor may lie just below the sample of that rank: everything above it is a candidate)
+}
+
+// KPT: scores per thread of a row in registers; 0: a long row.
+template <int KPT>
+__global__ __launch_bounds__(kSelThreads) void k_sel_row(const SelArgs a) {
+  __shared__ SelShared sh;
+  extern __shared__ __attribute__((aligned(16))) unsigned char sel_dyn[];
+  const int tid = threadIdx.x;
+  const SelRow r = sel_row(a, blockIdx.x);
+  for (int t = tid; t < r.row_len; t += kSelThreads) {
+    if (t < r.f) r.out[t] = t;
+    else if (t >= r.k) r.out[t] = -1;
+  }
+  if (tid == 0) (r.kind ? a.s_cnt : a.v_cnt)[r.h] = r.k;
+  if (r.kp == 0) return;
+  if constexpr (KPT > 0) {
+    sel_from_registers<KPT>(sh, r, a.n);
+  } else {
+    uint2* const cl = (uint2*)sel_dyn;
+    const int samples = r.kind ? a.samples_s : a.samples_v;
+    const bool listed = a.hdr != nullptr;   // the filter made the list
+    uint32_t room = listed ? a.cap : (uint32_t)kSelCand;
+    SelHeader hd;
+    if (listed) {
+      hd = a.hdr[blockIdx.x];
+    } else {
+      hd.floor_key = samples == 8 ? sel_floor<8>(sh, r, a.n) : sel_floor<16>(sh, r, a.n);
+      hd.count = hd.equal = 0;
+      sel_walk_row(r, a.n, [&](const uint32_t (&key)[kSelStep], int32_t i0, int par) {
+        uint32_t g = 0, q = 0;
+#pragma unroll
+        for (int e = 0; e < kSelStep; ++e) {
+          g += __popcll(__ballot(key[e] > hd.floor_key));
+          q += __popcll(__ballot(key[e] == hd.floor_key));
+        }
+        uint32_t at = hd.count, eq = 0, all_g, all_e;
+        sel_wave_base(sh, par, g, q, at, eq, all_g, all_e);
+        hd.count += all_g;
+        hd.equal += all_e;
+        if (hd.count > room) return false;
+#pragma unroll
+        for (int e = 0; e < kSelStep; ++e) {
+          const uint64_t b = __ballot(key[e] > hd.floor_key);
+          if (!b) continue;
+          if (key[e] > hd.floor_key)
+            cl[at + __builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u))] =
+                make_uint2(key[e], (uint32_t)(i0 + 64 * e));
+          at += __popcll(b);
+        }
+        return true;
+      });
+      __syncthreads();
+    }
+    const int m = (int)hd.count;
+    if (hd.count > room || hd.count + hd.equal < r.kp) {   // the sample missed
+      sel_from_row(sh, r, a.n);
+    } else if (hd.count < r.kp) {   // the threshold is the floor
+      sel_compact_row(sh, r, a.n, hd.floor_key, r.kp - hd.count);
+    } else if (listed) {
+      const uint2* const cand = a.cand + (int64_t)blockIdx.x * a.cap;
+      const uint2* const slices = a.slices + (int64_t)blockIdx.x * a.n_slices;
+      auto slice_of = [&](int s) { return slices[s]; };
+      if (m <= kSelCand) {
+#pragma unroll
+        for (int e = 0; e < kSelCand / kSelThreads; ++e) {
+          const int i = e * kSelThreads + tid;
+          if (i < m) cl[i] = cand[i];
+        }
+        __syncthreads();
+        sel_from_candidates(sh, cl, r, a.n_slices, m, hd.floor_key, slice_of);
+      } else {
+        sel_from_candidates(sh, cand, r, a.n_slices, m, hd.floor_key, slice_of);
+      }
+    } else {
+      // (in order already: one slice per wave)
+      const int per = (m + kSelWaves - 1) / kSelWaves;
+      sel_from_candidates(sh, cl, r, kSelWaves, m, hd.floor_key, [&](int s) {
+        const int at = s * per < m ? s * per : m;
+        return make_uint2((uint32_t)at, (uint32_t)(m - at < per ? m - at : per));
+      });
+    }
+  }
+}
+
+// Headers of the rows with their floors: one workgroup per row.
+__global__ __launch_bounds__(kSelThreads) void k_sel_sample(const SelArgs a) {
+  __shared__ SelShared sh;
+  const SelRow r = sel_row(a, blockIdx.x);
+  SelHeader hd;
+  hd.floor_key = ~0u;   // (all entries of the row are forced: no candidates)
+  if (r.kp > 0) hd.floor_key = (r.kind ? a.samples_s : a.samples_v) == 8 ? sel_floor<8>(sh, r, a.n) : sel_floor<16>(sh, r, a.n);
+  hd.count = hd.equal = 0;
+  hd.pad = 0;
+  if (threadIdx.x == 0) a.hdr[blockIdx.x] = hd;
+}
+
+// The candidates of a row's slices: the scores are read once, counted, given room in the row's list by one atomic
+// addition per workgroup (so the slices lie there in the order of arrival; k_sel_row goes by the table) and written in order,
+// a slice per wave.
+__global__ __launch_bounds__(kSelFilterThreads) void k_sel_filter(const SelArgs a) {
+  const SelRow r = sel_row(a, blockIdx.y);
+  SelHeader* const hd = a.hdr + blockIdx.y;
+  constexpr int NW = kSelFilterThreads / 64, PER = kSelSlice / 64;
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // entries and floor as signed integers in the order of the scores.  Against a floor >= 0 (scores are) the bits of a float
+  // are that integer already: a negative float is a negative integer, whatever its place among those.
+  const uint32_t floor_key = hd->floor_key;
+  int32_t floor_x = (int32_t)(floor_key ^ 0x80000000u);
+  const int slice = blockIdx.x * NW + wv;
+  const int64_t s0 = r.f + (int64_t)slice * kSelSlice;
+  __shared__ uint32_t wcnt[NW][2], base_s;
+  int32_t x[PER];
+  if (s0 + kSelSlice <= a.n) {   // a whole slice: one address
+    const int32_t* const p = (const int32_t*)r.sc + s0;
+#pragma unroll
+    for (int e = 0; e < PER; ++e) x[e] = p[lane + 64 * e];
+  } else {
+#pragma unroll
+    for (int e = 0; e < PER; ++e) {
+      const int64_t i = s0 + lane + 64 * e;
+      const int32_t b = ((const int32_t*)r.sc)[i < a.n ? i : a.n - 1];
+      x[e] = i < a.n ? b : (int32_t)0xFFFFFFFF;   // behind the row: the image is the least one
+    }
+  }
+  if (floor_x < 0) {
+#pragma unroll
+    for (int e = 0; e < PER; ++e) x[e] ^= (x[e] >> 31) & 0x7FFFFFFF;
+  }
+  uint32_t c = 0, q = 0;
+#pragma unroll
+  for (int e = 0; e < PER; ++e) {
+    c += __popcll(__ballot(x[e] > floor_x));
+    q += __popcll(__ballot(x[e] == floor_x));
+  }
+  if (lane == 0) { wcnt[wv][0] = c; wcnt[wv][1] = q; }
+  __syncthreads();
+  uint32_t before = 0, total = 0, equal = 0;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) {
+    before += w < wv ? wcnt[w][0] : 0u;
+    total += wcnt[w][0];
+    equal += wcnt[w][1];
+  }
+  if (tid == 0) {
+    base_s = total ? __hip_atomic_fetch_add(&hd->count, total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+    if (equal) __hip_atomic_fetch_add(&hd->equal, equal, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __syncthreads();
+  const uint32_t base = base_s;
+  if (lane == 0 && slice < a.n_slices) a.slices[(int64_t)blockIdx.y * a.n_slices + slice] = make_uint2(base + before, c);
+  if (base + total > a.cap || c == 0) return;   // (the list overflows: k_sel_row reads the row instead)
+  uint2* const out = a.cand + (int64_t)blockIdx.y * a.cap + base + before;
+  uint32_t pos = 0;
+  asm volatile("" : "+s"(floor_x));   // the lane masks are made again rather than kept
+#pragma unroll
+  for (int e = 0; e < PER; ++e) {
+    const uint64_t b = __ballot(x[e] > floor_x);
+    if (b) {
+      if (x[e] > floor_x)
+        out[pos + __builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u))] =
+            make_uint2((uint32_t)x[e] ^ 0x80000000u, (uint32_t)(s0 + lane + 64 * e));
+      pos += __popcll(b);
+    }
+  }
+}
+
+// Entries that a row's list may get: what is to be expected from the sample and 4.5 sigma of it to spare.
+static int64_t sel_list_len(int64_t n, int32_t budget, int spt) {
+  const float s = (float)(spt * kSelThreads), rank = sel_sample_rank((float)budget, (float)n, s);
+  if (!(rank < s)) return n;
+  const int64_t len = (int64_t)((rank + 4.5f * sqrtf(rank)) * ((float)n / s)) + 64;
+  return len < n ? len : n;
+}
+// Samples per thread: the smaller number whose list fits the LDS, else the larger one; 0: the rows stay in registers.
+static int sel_samples(int64_t n, int32_t budget) {
+  return n <= kSelRegKeys ? 0 : (sel_list_len(n, budget, 8) <= kSelCand ? 8 : 16);
+}
+struct SelLayout {
+  size_t slices, cand, total;
+  int32_t n_slices;
+  uint32_t cap;
+  int samples_v, samples_s;
+};
+static SelLayout sel_layout(const vs_params& p) {
+  SelLayout l;
+  const int64_t n = p.q_start + p.q_len;
+  const size_t rows = 2 * (size_t)p.n_q_heads;
+  l.samples_v = sel_samples(n, p.vertical_budget);
+  l.samples_s = sel_samples(n, p.slash_budget);
+  l.n_slices = (int32_t)ceil_div(n, kSelSlice);
+  const int64_t cv = sel_list_len(n, p.vertical_budget, l.samples_v), cs = sel_list_len(n, p.slash_budget, l.samples_s);
+  l.cap = (uint32_t)(cv > cs ? cv : cs);
+  l.slices = align_up(rows * sizeof(SelHeader), 256);
+  l.cand = l.slices + align_up(rows * (size_t)l.n_slices * sizeof(uint2), 256);
+  l.total = l.samples_v ? l.cand + align_up(rows * l.cap * sizeof(uint2), 256) : 256;
+  return l;
+}
+size_t select_ws_bytes(const vs_params& p) { return sel_layout(p).total; }
+
+// Per-device set-up, done once for each device: the opt-in of k_sel_row to more than 64 KiB of LDS.
+static hipError_t sel_device_setup() {
+  constexpr int kMaxDevices = 64;
+  static std::mutex mu;
+  static bool done[kMaxDevices] = {false};
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
+  std::lock_guard<std::mutex> lock(mu);
+  if (!done[dev]) {
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_sel_row<0>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                            kSelCand * (int)sizeof(uint2));
+    if (e != hipSuccess) return e;
+    done[dev] = true;
+  }
+  return hipSuccess;
+}
+
+// ws: ws_bytes bytes; fewer than select_ws_bytes(p), or none: every row lists its own candidates
 hipError_t launch_select(const vs_params& p, const float* vscore, const float* sscore,
                          const int32_t* v_budget_h, const int32_t* s_budget_h,
                          int32_t* v_idx, int32_t* v_cnt, int32_t* s_idx, int32_t* s_cnt, void* ws,
-                         hipStream_t st) {
+                         size_t ws_bytes, hipStream_t st) {
   SelArgs a;
   a.vscore = vscore; a.sscore = sscore; a.n = p.q_start + p.q_len;
   a.n_q_heads = p.n_q_heads;
@@ -276,36 +676,44 @@ hipError_t launch_select(const vs_params& p, const float* vscore, const float* s
   a.keep_v = p.keep_first_cols; a.keep_s = p.keep_local_band;
   a.v_budget_h = v_budget_h; a.s_budget_h = s_budget_h;
   a.v_idx = v_idx; a.v_cnt = v_cnt; a.s_idx = s_idx; a.s_cnt = s_cnt;
-  a.ws = (uint32_t*)ws;
-  // slices: whole steps of the workgroup, enough of them for about 2048 workgroups in all
-  const int rows = 2 * p.n_q_heads;
-  int64_t want = 2048 / rows;
-  want = want < 1 ? 1 : (want > kSelMaxSlices ? kSelMaxSlices : want);
-  const int64_t steps = ceil_div(a.n, kSelStep);
-  a.slice_len = ceil_div(steps, want) * kSelStep;
-  const int n_slices = (int)ceil_div(a.n, a.slice_len);
-  const dim3 grid(n_slices, rows);
-  hipLaunchKernelGGL(k_sel_init, dim3(rows), dim3(256), 0, st, a);
-  for (int pass = 0; pass < 4; ++pass) hipLaunchKernelGGL(k_sel_hist, grid, dim3(kSelThreads), 0, st, a, pass);
-  hipLaunchKernelGGL(k_sel_count, grid, dim3(kSelThreads), 0, st, a);
-  hipLaunchKernelGGL(k_sel_write, grid, dim3(kSelThreads), 0, st, a);
+  a.hdr = nullptr; a.slices = nullptr; a.cand = nullptr;
+  const SelLayout l = sel_layout(p);
+  a.cap = 0;
+  a.n_slices = l.n_slices; a.samples_v = l.samples_v; a.samples_s = l.samples_s;
+  const dim3 rows(2u * (unsigned)p.n_q_heads), block(kSelThreads);
+  if (a.n <= 8 * kSelThreads) {
+    hipLaunchKernelGGL(k_sel_row<8>, rows, block, 0, st, a);
+  } else if (a.n <= 16 * kSelThreads) {
+    hipLaunchKernelGGL(k_sel_row<16>, rows, block, 0, st, a);
+  } else if (a.n <= kSelRegKeys) {
+    hipLaunchKernelGGL(k_sel_row<32>, rows, block, 0, st, a);
+  } else {
+    const hipError_t e = sel_device_setup();
+    if (e != hipSuccess) return e;
+    if (ws && ws_bytes >= l.total && a.n > kSelOwnKeys) {
+      a.hdr = (SelHeader*)ws;
+      a.slices = (uint2*)((char*)ws + l.slices);
+      a.cand = (uint2*)((char*)ws + l.cand);
+      a.cap = l.cap;
+      hipLaunchKernelGGL(k_sel_sample, rows, block, 0, st, a);
+      hipLaunchKernelGGL(k_sel_filter, dim3((unsigned)ceil_div(l.n_slices, kSelFilterThreads / 64), rows.x),
+                         dim3(kSelFilterThreads), 0, st, a);
+    }
+    hipLaunchKernelGGL(k_sel_row<0>, rows, block, kSelCand * sizeof(uint2), st, a);
+  }
   return hipGetLastError();
 }
 
 // ---- the selection for callers that cannot allocate ------------------------------------------
-// vs_select_static: the control blocks of the rows (histograms, tickets, slice counts) live in
-// a file-scope device array instead of a caller workspace.  Every device the library runs on
-// holds its own copy of the array (2 x 128 rows x 4,736 bytes = 1.2 MB) at its own address
-// until the process ends; in host code the array's name is only a handle, the address comes
-// from hipGetSymbolAddress, once per device, with that device current.  k_sel_init clears the
-// rows a call uses, so a call never sees the contents the call before it left behind; calls
+// vs_select_static: the headers, tables and candidate lists of the rows live in a file-scope device array instead of a
+// caller workspace, where they fit (28 heads at 1M keys take 7 MB); beyond that every row lists its own candidates.
+// Every device the library runs on holds its own copy of the array at its own address until the process ends; in host
+// code the array's name is only a handle, the address comes from hipGetSymbolAddress, once per device, with that
+// device current.  A call writes what it reads, so it never sees the contents the call before it left behind; calls
 // that overlap in time on one device share the array and race.
-constexpr int kSelStaticMaxHeads = 128;
-static __device__ __align__(256) uint32_t scratch[2 * kSelStaticMaxHeads * kSelRowWords];
+static __device__ __align__(256) unsigned char scratch[12 << 20];
 
-int select_static_max_heads() { return kSelStaticMaxHeads; }
-
-hipError_t select_static_scratch(void** ptr_out) {
+hipError_t select_static_scratch(void** ptr_out, size_t* bytes_out) {
   constexpr int kMaxDevices = 64;
   static std::mutex mu;
   static void* ptr_of[kMaxDevices] = {nullptr};
@@ -322,6 +730,7 @@ hipError_t select_static_scratch(void** ptr_out) {
     ptr_of[dev] = ptr;
   }
   *ptr_out = ptr_of[dev];
+  *bytes_out = sizeof(scratch);
   return hipSuccess;
 }
 

@@ -1,0 +1,54 @@
+"""The selection at the edges of its paths: rows that stay in registers, rows whose workgroup lists its own
+candidates, rows thinned out by the whole chip, and the rows that neither can serve.  Whole numbers: every
+result equals a stable full sort."""
+import pytest
+import torch
+
+import paper_2501_15383_amd as vs
+
+pytestmark = pytest.mark.gpu
+
+SIZES = [64, 65, 1000, 8192, 8193, 16384, 16385, 32768, 32769, 49152, 49153, 131071, 700001]
+
+
+def _want(sc, budget, keep):
+    hq, n = sc.shape
+    k = min(budget, n)
+    s = sc.clone()
+    s[:, :min(keep, k)] = float("inf")
+    idx = torch.full((hq, budget), -1, dtype=torch.int32, device=sc.device)
+    idx[:, :k] = torch.sort(s, dim=1, descending=True, stable=True).indices[:, :k].sort(dim=1).values.int()
+    return idx, torch.full((hq,), k, dtype=torch.int32, device=sc.device)
+
+
+def _scores(kind, hq, n, g):
+    dev = torch.device("cuda:0")
+    if kind == "spread":      # what an estimate leaves
+        return (torch.randn((hq, n), generator=g, device=dev) * 0.4).exp() / n
+    if kind == "ties":        # thousands of equal scores at every threshold
+        return torch.randint(0, 23, (hq, n), generator=g, device=dev).float() / 32
+    if kind == "equal":
+        return torch.full((hq, n), 0.25, device=dev)
+    if kind == "sparse":      # mostly zeros: the threshold may be zero itself
+        return torch.where(torch.rand((hq, n), generator=g, device=dev) < 0.002, torch.rand((hq, n), generator=g, device=dev), 0.0)
+    if kind == "crowded":     # the best entries side by side at one end
+        x = torch.rand((hq, n), generator=g, device=dev)
+        x[:, n // 3:n // 3 + max(1, n // 20)] += 1.0
+        return x
+    return torch.randn((hq, n), generator=g, device=dev)   # "signed": beyond what the interface asks for
+
+
+@pytest.mark.parametrize("kind", ["spread", "ties", "equal", "sparse", "crowded", "signed"])
+@pytest.mark.parametrize("n", SIZES)
+def test_select_equals_a_full_sort(n, kind):
+    g = torch.Generator(device="cuda:0").manual_seed(100 + n)
+    hq = 3
+    vsc, ssc = _scores(kind, hq, n, g), _scores(kind, hq, n, g)
+    # ordinary budgets; one line; more lines than any list in LDS holds; everything
+    for bv, bs, keep in ((1000, 6096, 64), (1, 70, 64), (40, 30000, 0), (n, n + 3, 64)):
+        c = min(64, n)
+        ck = vs.Chunk(hq, 1, 128, c, n - c, 0.1, vertical_budget=bv, slash_budget=bs, keep_first_cols=1, keep_local_band=keep)
+        want = (*_want(vsc, bv, 1), *_want(ssc, bs, keep))
+        for sets in (vs.select(ck, vsc, ssc), vs.select_static(ck, vsc, ssc, vs.alloc_index_sets(ck, vsc.device))):
+            for a, b, nm in zip(sets, want, ("v_idx", "v_cnt", "s_idx", "s_cnt")):
+                assert torch.equal(a, b), f"{nm}: n {n}, {kind}, budgets {bv} / {bs}"
