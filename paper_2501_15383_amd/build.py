@@ -10,7 +10,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libvs.so")
-SOURCES = ["vs_api.hip", "vs_attn.hip", "vs_estimate.hip", "vs_select.hip"]
+SOURCES = ["vs_api.hip", "vs_attn.hip", "vs_decode.hip", "vs_estimate.hip", "vs_select.hip"]
 HEADERS = [os.path.join(CSRC, "vs_common.h"), os.path.join(HERE, "..", "include", "vs.h")]
 
 FLAGS = [

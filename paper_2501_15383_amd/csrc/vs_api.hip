@@ -45,8 +45,11 @@ int check_ws(const void* ws, size_t have, size_t need) {
 
 size_t sparse_ws_bytes(const vs_params& p, bool dense) {
   const size_t own = blocklist_bytes(p, dense) + attn_sync_bytes(p) + attn_split_bytes(p, dense);
-  // (a sparse single-token call without DCA takes the packed path, a DCA one the plain path: room for either)
-  if (!dense && attn_single_token_packs(p)) return own > attn_single_token_bytes(p) ? own : attn_single_token_bytes(p);
+  // (a single token without DCA is the decode kernel's, with DCA the tile kernel's: room for either)
+  if (p.q_len == 1 && decode_fits(p)) {
+    const size_t dec = decode_bytes(p, 1, !dense);
+    return own > dec ? own : dec;
+  }
   return own;
 }
 
@@ -299,8 +302,10 @@ int sparse_attn(const vs_params* p, const void* q, const vs_dca* dca, const void
   rc = check_ws(ws, ws_bytes, sparse_ws_bytes(*p, false));
   if (rc != VS_OK) return rc;
   hipStream_t st = (hipStream_t)stream;
-  if (!dca && attn_single_token_packs(*p))
-    return hip_status(launch_attention_single_token(*p, q, k, v, v_idx, v_cnt, s_idx, s_cnt, out, lse, ws, st));
+  if (!dca && p->q_len == 1 && decode_fits(*p)) {
+    const vs_request one = {q, k, v, out, lse, v_idx, v_cnt, s_idx, s_cnt, p->q_start, p->q_len};
+    return hip_status(launch_decode(*p, &one, nullptr, 1, true, ws, st));
+  }
   const BlockList bl = blocklist_layout(*p, false, ws);
   char* sync = (char*)ws + blocklist_bytes(*p, false);
   hipError_t e = launch_build_blocklist(*p, s_idx, s_cnt, false, bl, sync, st);
@@ -319,8 +324,12 @@ int dense_attn(const vs_params* p, const void* q, const vs_dca* dca, const void*
   if (!aligned(q, 16) || !aligned(k, 16) || !aligned(v, 16) || !aligned(out, 16)) return VS_ERR_INVALID_ARG;
   rc = check_ws(ws, ws_bytes, sparse_ws_bytes(*p, true));
   if (rc != VS_OK) return rc;
-  const BlockList bl = blocklist_layout(*p, true, ws);
   hipStream_t st = (hipStream_t)stream;
+  if (!dca && p->q_len == 1 && decode_fits(*p)) {
+    const vs_request one = {q, k, v, out, lse, nullptr, nullptr, nullptr, nullptr, p->q_start, p->q_len};
+    return hip_status(launch_decode(*p, &one, nullptr, 1, false, ws, st));
+  }
+  const BlockList bl = blocklist_layout(*p, true, ws);
   char* sync = (char*)ws + blocklist_bytes(*p, true);
   hipError_t e = launch_build_blocklist(*p, nullptr, nullptr, true, bl, sync, st);
   if (e != hipSuccess) return VS_ERR_HIP;
@@ -401,6 +410,11 @@ int vs_prefill_chunk_dca(const vs_params* p, const void* q_intra, const vs_dca* 
 }
 
 namespace {
+// workspace of a batch: the decode kernel's part, then the tile kernel's
+size_t decode_part(const vs_params& p, int n_req) { return decode_fits(p) ? decode_bytes(p, n_req, true) : 0; }
+size_t batch_bytes(const vs_params& p, int n_req) {
+  return decode_part(p, n_req) + (decode_fits(p) && p.q_len == 1 ? 0 : attn_batch_bytes(p, n_req));
+}
 int check_batch(const vs_params* p, int32_t n_requests) {
   int rc = check_params(p, true);
   if (rc != VS_OK) return rc;
@@ -412,7 +426,7 @@ int check_batch(const vs_params* p, int32_t n_requests) {
 
 size_t vs_batch_workspace_bytes(const vs_params* p, int32_t n_requests) {
   if (check_batch(p, n_requests) != VS_OK) return 0;
-  return attn_batch_bytes(*p, n_requests);
+  return batch_bytes(*p, n_requests);
 }
 
 int vs_attn_batch(const vs_params* p, const vs_request* requests, int32_t n_requests, void* ws,
@@ -420,9 +434,16 @@ int vs_attn_batch(const vs_params* p, const vs_request* requests, int32_t n_requ
   int rc = check_batch(p, n_requests);
   if (rc != VS_OK) return rc;
   if (!requests || !aligned(requests, 8)) return VS_ERR_INVALID_ARG;
-  rc = check_ws(ws, ws_bytes, attn_batch_bytes(*p, n_requests));
+  rc = check_ws(ws, ws_bytes, batch_bytes(*p, n_requests));
   if (rc != VS_OK) return rc;
-  return hip_status(launch_attention_batch(*p, requests, n_requests, ws, (hipStream_t)stream));
+  // single tokens by the decode kernel, the longer requests by the tile kernel (which skips the former)
+  hipStream_t st = (hipStream_t)stream;
+  const bool decode = decode_fits(*p);
+  if (decode) {
+    const hipError_t e = launch_decode(*p, nullptr, requests, n_requests, true, ws, st);
+    if (e != hipSuccess || p->q_len == 1) return hip_status(e);
+  }
+  return hip_status(launch_attention_batch(*p, requests, n_requests, decode, (char*)ws + decode_part(*p, n_requests), st));
 }
 
 int vs_count_tiles(const vs_params* p, const int32_t* v_idx, const int32_t* v_cnt,

@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <mutex>
+
 #include "../../include/vs.h"
 
 namespace vs {
@@ -18,6 +20,36 @@ typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
 constexpr int kBlock = 64;            // B: edge of the computed slash blocks
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
+
+// a 64-bit value that is the same in every lane, moved into scalar registers
+template <typename T>
+__device__ __forceinline__ T uniform64(T x) {
+  static_assert(sizeof(T) == 8, "uniform64 takes pointers and 64-bit integers");
+  const uint64_t b = (uint64_t)x;
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)b), hi = __builtin_amdgcn_readfirstlane((uint32_t)(b >> 32));
+  return (T)(((uint64_t)hi << 32) | lo);
+}
+
+// Set-up that a device needs once (function attributes are held per device by the runtime).
+struct DeviceOnce {
+  static constexpr int kMaxDevices = 64;
+  std::mutex mu;
+  bool done[kMaxDevices] = {false};
+  template <typename F>
+  hipError_t run(F&& set_up) {
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
+    std::lock_guard<std::mutex> lock(mu);
+    if (!done[dev]) {
+      e = set_up();
+      if (e != hipSuccess) return e;
+      done[dev] = true;
+    }
+    return hipSuccess;
+  }
+};
 
 static inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 static inline size_t align_up(size_t a, size_t b) { return (a + b - 1) / b * b; }
@@ -36,6 +68,17 @@ constexpr int kAttnQBlocks = VS_X_QBLOCKS;   // timing experiment (4 = one workg
 constexpr int kAttnQBlocks = 2;       // query blocks (of 64 rows) per attention workgroup
 #endif
 constexpr uint32_t kEntSentinel = 0x7FFFFFF0u;
+
+// Block diagonals that slash offset o computes: floor(o / 64), and the next one when o is no multiple of 64.  `before` is the
+// offset in front of it in its list (-1: none): what that one sets already is left out, so that neighbouring offsets (64 of
+// which share their two diagonals, and usually their word) do not queue for one address; complete for lists in any order.
+template <typename Set>
+__device__ __forceinline__ void list_bits(int o, int before, int n_blk, Set&& set) {
+  const int ad = o >> 6;
+  const bool follows = before >= 0 && (before >> 6) == ad;
+  if (!follows && ad < n_blk) set(ad);
+  if ((o & 63) && !(follows && (before & 63)) && ad + 1 < n_blk) set(ad + 1);
+}
 
 struct BlockList {
   uint32_t* bm_a;     // [heads][words]
@@ -82,13 +125,14 @@ hipError_t launch_attention(const vs_params& p, const void* q, const DcaArgs* dc
 // several requests in one launch (short chunks, decode steps): p.q_len = the longest request,
 // p.q_start + p.q_len = the most keys any request sees; req is a device array
 size_t attn_batch_bytes(const vs_params& p, int n_req);
-hipError_t launch_attention_batch(const vs_params& p, const vs_request* req, int n_req, void* ws, hipStream_t st);
-// sparse attention of a single token with 2..16 query heads per KV head runs as a batch of one
-bool attn_single_token_packs(const vs_params& p);
-size_t attn_single_token_bytes(const vs_params& p);
-hipError_t launch_attention_single_token(const vs_params& p, const void* q, const void* k, const void* v,
-                                         const int32_t* v_idx, const int32_t* v_cnt, const int32_t* s_idx,
-                                         const int32_t* s_cnt, void* out, float* lse, void* ws, hipStream_t st);
+// (skip_single: single tokens are another kernel's)
+hipError_t launch_attention_batch(const vs_params& p, const vs_request* req, int n_req, bool skip_single, void* ws,
+                                  hipStream_t st);
+// single tokens, one request (`one`, by value; lists: it has index sets) or those of a table (req, device; lists = true)
+bool decode_fits(const vs_params& p);
+size_t decode_bytes(const vs_params& p, int n_req, bool lists);
+hipError_t launch_decode(const vs_params& p, const vs_request* one, const vs_request* req, int n_req, bool lists, void* ws,
+                         hipStream_t st);
 size_t attn_sync_bytes(const vs_params& p);
 // key split of short chunks: number of ranges (1 = none) and bytes of partial results
 int attn_split(const vs_params& p, bool dense);

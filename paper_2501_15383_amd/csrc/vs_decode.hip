@@ -1,0 +1,694 @@
+// Attention of single tokens (decode steps) against long caches, one request or many per launch, dense or with
+// the index sets of the vertical-slash pattern (section 5.2, "Integrating with Chunked prefill": decoding of other
+// requests goes on beside a long prefill).  bf16 MFMA with fp32 accumulation.
+//
+// Bound: the one read of the K and V rows; everything else is arranged around keeping that read going.
+//  * The G <= 16 query heads of a KV group are the columns of 16x16x32 MFMA tiles (S^T = K Q^T, O^T = V^T P^T), so
+//    K and V are read once per group.  A wave works alone on 32 keys at a time: it copies the rows global -> LDS into
+//    its own two buffers (the next 32 keys are on their way while these are multiplied), waits for its own copies
+//    only, and there is no barrier until the waves of the workgroup fold their results.  One workgroup of four waves
+//    fills the LDS of a compute unit: 64 to 128 KB of copies in flight.
+//  * Work is cut into equal shares of 64-key blocks over all requests and KV heads (a share may start in the
+//    middle of one and end in the middle of another), so caches of different lengths leave no workgroup idle.  Every
+//    workgroup finds its share from the lengths alone.  Partial results are folded by k_decode_combine; a (request, KV
+//    head) that lies in one share is finished on the spot.
+//  * With index sets the tokens of a group walk the UNION of the heads' block lists (k_decode_lists; per entry the
+//    heads whose own list has the diagonal: the scores of the others are -inf), then the gathered columns head by head.
+// Measured on one MI355X, 28 query / 4 KV heads, head_dim 128, against the tile kernel of vs_attn.hip with the heads as rows of
+// its 128-row tiles (copies of a step shared by four waves of which one multiplied, a barrier per step, one range count for a
+// whole batch): one token at 5,003 keys 39 -> 15 us, at 1M keys 510 -> 382 (5.7 TB/s of K and V); 24 tokens at 2K to 64K keys
+// 395 -> 228 (5.5 TB/s); 8 tokens with index sets at 262,144 keys 1,042 -> 776 (lists 252 -> 29 of it).
+#include "vs_common.h"
+
+namespace vs {
+
+constexpr int kDecThreads = 256;
+constexpr int kDecWaves = kDecThreads / 64;
+constexpr int kDecMinBlocks = 2;     // 64-key blocks per share at least: one 32-key chunk for every wave
+constexpr int kDecListThreads = 1024;
+constexpr int kDecListWords = 14336; // bitmap words of all heads of a group in LDS at a time
+
+struct DecodeArgs {
+  vs_request one;         // the request of a call without a table (req null)
+  const vs_request* req;
+  int32_t n_req;
+  int32_t n_q_heads, n_kv_heads, group;
+  int64_t q_stride_head, k_stride_tok, k_stride_head, v_stride_tok, v_stride_head, o_stride_head;
+  float scale_log2;
+  int32_t v_budget, s_budget;
+  int64_t max_q_len, max_n_k;
+  // index sets: block-diagonal bitmap per (request, head), union list and its lengths per (request, KV head)
+  uint32_t* bm;           // [n_req][Hq][words]
+  uint2* ent;             // [n_req][Hkv][ent_stride] (diagonal, heads that have it)
+  int2* len;              // [n_req][Hkv] (entries, entries + tiles of 64 gathered columns)
+  int32_t words, ent_stride;
+  // shares: plan[0] = blocks in all, plan[1] = shares, plan[2 + r] = blocks before request r
+  int64_t* plan;
+  float* part_o;          // [share + (request, KV head)][G][D]
+  float* part_ml;         // [share + (request, KV head)][G][2] (reference, sum)
+};
+
+__device__ __forceinline__ vs_request decode_request(const DecodeArgs& a, int r) {
+  vs_request rq = a.one;
+  if (a.req) {
+    rq = a.req[r];
+    rq.q = uniform64(rq.q); rq.k = uniform64(rq.k); rq.v = uniform64(rq.v); rq.out = uniform64(rq.out);
+    rq.lse = uniform64(rq.lse); rq.v_idx = uniform64(rq.v_idx); rq.v_cnt = uniform64(rq.v_cnt);
+    rq.s_idx = uniform64(rq.s_idx); rq.s_cnt = uniform64(rq.s_cnt);
+    rq.q_start = uniform64(rq.q_start); rq.q_len = uniform64(rq.q_len);
+  }
+  return rq;
+}
+// a single token inside the stated bounds
+__device__ __forceinline__ bool decode_takes(const DecodeArgs& a, const vs_request& rq) {
+  if (!rq.q || !rq.k || !rq.v || !rq.out) return false;
+  if (rq.q_len != 1 || rq.q_start < 0 || rq.q_start + 1 > a.max_n_k) return false;
+  return rq.s_idx == nullptr || (rq.v_idx && rq.v_cnt && rq.s_cnt);
+}
+__device__ __forceinline__ int decode_blocks(const vs_request& rq) { return (int)((rq.q_start + kBlock) / kBlock); }
+// share w of n covers blocks [w T / n, (w + 1) T / n)
+__device__ __forceinline__ int64_t share_start(int64_t w, int64_t n, int64_t T) { return w * T / n; }
+__device__ __forceinline__ int64_t share_of(int64_t block, int64_t n, int64_t T) { return ((block + 1) * n - 1) / T; }
+
+template <int D>
+constexpr int decode_lds_bytes() { return kDecWaves * 2 * 2 * 32 * D * 2; }
+
+// one 1 KiB copy global -> LDS: lane L's 16 bytes land at lds_addr + 16 L
+__device__ __forceinline__ void dec_dma(uint32_t lds_addr, const void* sbase, uint32_t off) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+               :: "s"(__builtin_amdgcn_readfirstlane(lds_addr)), "v"(off), "s"(uniform64(sbase)) : "memory");
+}
+__device__ __forceinline__ void dec_dma_lane(uint32_t lds_addr, const void* ptr) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
+               :: "s"(__builtin_amdgcn_readfirstlane(lds_addr)), "v"(ptr) : "memory");
+}
+
+template <int D>
+__global__ __launch_bounds__(kDecThreads, 2) void k_decode(const DecodeArgs a) {
+  constexpr int DCH = D / 8;         // 16-byte pieces per row
+  constexpr int KS = D / 32;         // MFMA steps of K Q^T
+  constexpr int DB = D / 16;         // 16-row blocks of O^T
+  constexpr int RPG = 512 / D;       // rows per 1 KiB copy
+  constexpr int NC = 32 / RPG;       // copies of 32 rows
+  constexpr int R = 128 / D;         // rows per 256 bytes of LDS
+  constexpr int TILE = 32 * D;
+  // LDS: per wave [2 buffers][K tile, V tile].  Row r of a tile starts at r D; its 16-byte piece c lies in slot c ^ f(r) for
+  // K (16 rows of one piece in one read) and c ^ g(r) for V (4 rows x 2 pieces in one transposing read): no bank conflicts.
+  extern __shared__ __attribute__((aligned(16))) unsigned char dec_lds[];
+  __shared__ int64_t scan_s[kDecWaves];
+  __shared__ int64_t at_s[2];
+  __shared__ float ml_s[kDecWaves][16][2];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int col = lane & 15, g4 = lane >> 4;   // MFMA column (query head of the group) and k-group / row-group of the lane
+  __bf16* const buf = (__bf16*)dec_lds + wv * (4 * TILE);
+  const uint32_t buf_addr = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)(const __attribute__((address_space(3))) char*)buf);
+
+  // ---- this workgroup's share ------------------------------------------------------------------
+  auto blocks_of = [&](int r) -> int64_t {
+    const vs_request rq = a.req ? a.req[r] : a.one;
+    if (!decode_takes(a, rq)) return 0;
+    if (!rq.s_idx) return (int64_t)decode_blocks(rq) * a.n_kv_heads;
+    int64_t n = 0;
+    for (int g = 0; g < a.n_kv_heads; ++g) n += a.len[(int64_t)r * a.n_kv_heads + g].y;
+    return n;
+  };
+  int64_t T = 0, first = 0;
+  if (a.n_req == 1) {
+    T = blocks_of(0);
+  } else {
+    for (int r = tid; r < a.n_req; r += kDecThreads) T += blocks_of(r);
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) T += __shfl_xor((long long)T, d);
+    if (lane == 0) scan_s[wv] = T;
+    __syncthreads();
+    T = 0;
+    for (int w = 0; w < kDecWaves; ++w) T += scan_s[w];
+  }
+  int64_t n_share = (T + kDecMinBlocks - 1) / kDecMinBlocks;
+  if (n_share > (int64_t)gridDim.x) n_share = gridDim.x;
+  if (blockIdx.x == 0 && tid == 0) { a.plan[0] = T; a.plan[1] = n_share; }
+  if (a.n_req == 1) {
+    if (blockIdx.x == 0 && tid == 0) a.plan[2] = 0;
+    if (blockIdx.x >= n_share) return;
+  } else if (blockIdx.x != 0 && blockIdx.x >= n_share) {
+    return;
+  }
+  const int64_t u_begin = n_share ? share_start(blockIdx.x, n_share, T) : 0, u_end = n_share ? share_start(blockIdx.x + 1, n_share, T) : 0;
+  int r = 0;
+  first = u_begin;
+  if (a.n_req > 1) {
+    int64_t before = 0;
+    for (int rb = 0; rb < a.n_req; rb += kDecThreads) {
+      const int64_t mine = rb + tid < a.n_req ? blocks_of(rb + tid) : 0;
+      int64_t inc = mine;
+#pragma unroll
+      for (int d = 1; d < 64; d <<= 1) {
+        const int64_t y = __shfl_up((long long)inc, d);
+        if (lane >= d) inc += y;
+      }
+      __syncthreads();
+      if (lane == 63) scan_s[wv] = inc;
+      __syncthreads();
+      for (int w = 0; w < kDecWaves; ++w) {
+        if (w < wv) inc += scan_s[w];
+      }
+      inc += before;
+      for (int w = 0; w < kDecWaves; ++w) before += scan_s[w];
+      if (blockIdx.x == 0 && rb + tid < a.n_req) a.plan[2 + rb + tid] = inc - mine;
+      if (inc - mine <= u_begin && u_begin < inc) { at_s[0] = rb + tid; at_s[1] = u_begin - (inc - mine); }
+      if (blockIdx.x != 0 && before > u_begin) break;   // (uniform; the first workgroup writes all of the plan)
+    }
+    if (n_share == 0) return;
+    __syncthreads();
+    r = __builtin_amdgcn_readfirstlane((int)at_s[0]);
+    first = uniform64(at_s[1]);
+  }
+
+  // ---- lane constants ---------------------------------------------------------------------------
+  const int lr = lane / DCH, lc = lane % DCH;   // row inside a copy, and the slot there
+  // the piece of its row that the lane fetches (the slot, swizzled): copy e of a tile holds rows e RPG + lr
+  const int vpc = lc ^ ((((lr / R) & 3) << 2) & (DCH - 1));
+  auto k_piece = [&](int e) -> int { return lc ^ (((e * RPG + lr) / R) % DCH); };
+  int64_t left = u_end - u_begin;
+  int g = 0;
+  bool fresh = true;   // the request's fields are to be read
+  vs_request rq;
+  int64_t blk = first;
+  while (left > 0) {
+    if (fresh) {
+      rq = decode_request(a, r);
+      g = 0;
+      if (!decode_takes(a, rq)) { ++r; continue; }
+      fresh = false;
+    }
+    const bool sparse = rq.s_idx != nullptr;
+    const int64_t n_k = rq.q_start + 1;
+    int n_ent = decode_blocks(rq), seg_len = n_ent;
+    if (sparse) {
+      const int2 l2 = a.len[(int64_t)r * a.n_kv_heads + g];
+      n_ent = __builtin_amdgcn_readfirstlane(l2.x);
+      seg_len = __builtin_amdgcn_readfirstlane(l2.y);
+    }
+    if (blk >= seg_len) {   // the share starts in a later KV head of this request
+      blk -= seg_len;
+      if (++g == a.n_kv_heads) { ++r; fresh = true; }
+      continue;
+    }
+    const int64_t take64 = seg_len - blk < left ? seg_len - blk : left;
+    const int b0 = (int)blk, b1 = (int)(blk + take64);
+    const bool whole = b0 == 0 && b1 == seg_len;
+    const int h0 = g * a.group;
+
+    // ---- Q^T operand: lane (head h0 + col, k-group g4); heads beyond the group are zero ------------
+    bf16x8 qreg[KS];
+    {
+      const __bf16* qp = (const __bf16*)rq.q + (int64_t)(h0 + (col < a.group ? col : 0)) * a.q_stride_head + 8 * g4;
+#pragma unroll
+      for (int st = 0; st < KS; ++st) {
+        qreg[st] = *(const bf16x8*)(qp + 32 * st);
+        if (col >= a.group)
+#pragma unroll
+          for (int x = 0; x < 8; ++x) qreg[st][x] = (__bf16)0.f;
+      }
+    }
+    f32x4 oacc[DB];
+#pragma unroll
+    for (int db = 0; db < DB; ++db) oacc[db] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float m_run = -INFINITY, l_run = 0.f;
+
+    const __bf16* const kb = (const __bf16*)rq.k + (int64_t)g * a.k_stride_head;
+    const __bf16* const vb = (const __bf16*)rq.v + (int64_t)g * a.v_stride_head;
+    const uint2* const ents = a.ent + ((int64_t)r * a.n_kv_heads + g) * a.ent_stride;
+    const int m_blk = (int)(rq.q_start / kBlock);
+    const int pos_in_block = (int)(rq.q_start % kBlock);
+
+    // chunk c: 32 keys.  Dense: keys 32 c ...; with index sets entry c / 2 of the union list, then the columns.
+    int c = 2 * b0 + wv;
+    int c_end = 2 * b1;
+    if (!sparse && c_end > (int)((n_k + 31) / 32)) c_end = (int)((n_k + 31) / 32);
+    const int cnt_cache = sparse ? rq.v_cnt[h0 + (lane < a.group ? lane : 0)] : 0;   // columns of head h0 + lane
+    uint2 ecache = make_uint2(0u, 0u);
+    int ebase = -64;
+    // what the next chunk is: its live keys (bit k: key k) and live rows (bit q), both uniform
+    struct Chunk { uint32_t keys, rows; };
+    auto issue = [&](int ci, int b) -> Chunk {
+      Chunk ch;
+      ch.keys = ~0u;
+      ch.rows = 0xFFFFu;
+      const uint32_t kd = buf_addr + (uint32_t)(b * 2 * TILE * 2), vd = kd + TILE * 2;
+      int64_t j0 = (int64_t)32 * ci;
+      bool columns = false;
+      if (sparse) {
+        const int e = ci >> 1;
+        if (e < n_ent) {
+          if (e >= ebase + 64) {
+            ebase = e;
+            const int x = ebase + lane;
+            ecache = ents[x < n_ent ? x : n_ent - 1];
+          }
+          const int diag = __builtin_amdgcn_readlane(ecache.x, e - ebase);
+          ch.rows = __builtin_amdgcn_readlane(ecache.y, e - ebase);
+          j0 = (int64_t)(m_blk - diag) * kBlock + 32 * (ci & 1);
+        } else {
+          columns = true;
+        }
+      }
+      if (!columns) {
+        const int64_t over = j0 + 32 - n_k;   // keys of the chunk behind the token
+        if (over > 0) ch.keys = over >= 32 ? 0u : ~0u >> over;
+        if (over <= 0) {
+          const char* kt = (const char*)(kb + j0 * a.k_stride_tok);
+          const char* vt = (const char*)(vb + j0 * a.v_stride_tok);
+#pragma unroll
+          for (int e = 0; e < NC; ++e)
+            dec_dma(kd + e * 1024, kt + (int64_t)e * RPG * a.k_stride_tok * 2,
+                    (uint32_t)(lr * a.k_stride_tok * 2 + k_piece(e) * 16));
+#pragma unroll
+          for (int e = 0; e < NC; ++e)
+            dec_dma(vd + e * 1024, vt + (int64_t)e * RPG * a.v_stride_tok * 2,
+                    (uint32_t)(lr * a.v_stride_tok * 2 + vpc * 16));
+        } else {
+#pragma unroll
+          for (int e = 0; e < NC; ++e) {
+            int64_t j = j0 + e * RPG + lr;
+            j = j < n_k ? j : n_k - 1;
+            dec_dma_lane(kd + e * 1024, kb + j * a.k_stride_tok + k_piece(e) * 8);
+            dec_dma_lane(vd + e * 1024, vb + j * a.v_stride_tok + vpc * 8);
+          }
+        }
+      } else {
+        // columns: 64 per unit, the heads of the group one after the other
+        int u = (ci >> 1) - n_ent, jh = 0, vc = 0;
+        for (; jh < a.group; ++jh) {
+          vc = __builtin_amdgcn_readlane(cnt_cache, jh);
+          const int nt = (vc + 63) >> 6;
+          if (u < nt) break;
+          u -= nt;
+        }
+        if (jh == a.group) { jh = 0; u = 0; vc = 0; }   // a group without any line: one unit without live keys
+        const int32_t* vi = rq.v_idx + (int64_t)(h0 + jh) * a.v_budget;
+        const uint32_t* bm = a.bm + ((int64_t)r * a.n_q_heads + h0 + jh) * a.words;
+        const int p0 = 64 * u + 32 * (ci & 1);
+        // (clamped to the list, so that the loads go out together)
+        auto column = [&](int k) -> int { return vi[p0 + k < vc ? p0 + k : vc - 1]; };
+        int j = 0, jr[NC];
+#pragma unroll
+        for (int e = 0; e < NC; ++e) jr[e] = 0;
+        const int k = lane & 31;
+        if (vc > 0) {
+          j = column(k);
+#pragma unroll
+          for (int e = 0; e < NC; ++e) jr[e] = column(e * RPG + lr);
+        }
+        // a column counts if it is not behind the token and not on a computed diagonal of its own head
+        const int ad = m_blk - (j >> 6);
+        bool ok = p0 + k < vc && ad >= 0 && !(ad == 0 && (j & 63) > pos_in_block);
+        ok = ok && !((bm[ad >= 0 ? ad >> 5 : 0] >> (ad & 31)) & 1u);
+        ch.keys = (uint32_t)__ballot(ok);
+        ch.rows = 1u << jh;
+#pragma unroll
+        for (int e = 0; e < NC; ++e) {
+          dec_dma_lane(kd + e * 1024, kb + (int64_t)jr[e] * a.k_stride_tok + k_piece(e) * 8);
+          dec_dma_lane(vd + e * 1024, vb + (int64_t)jr[e] * a.v_stride_tok + vpc * 8);
+        }
+      }
+      return ch;
+    };
+
+    Chunk cur;
+    cur.keys = cur.rows = 0u;
+    if (c < c_end) cur = issue(c, 0);
+    for (int b = 0; c < c_end; c += kDecWaves, b ^= 1) {
+      Chunk nxt;
+      nxt.keys = nxt.rows = 0u;
+      if (c + kDecWaves < c_end) {
+        nxt = issue(c + kDecWaves, b ^ 1);
+        // this chunk's copies are done when at most the next chunk's are outstanding
+        if constexpr (NC == 8) asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
+        else asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+      } else {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      }
+      const __bf16* const Kt = buf + b * 2 * TILE;
+      const __bf16* const Vt = Kt + TILE;
+      // S^T: two blocks of 16 keys; lane (head col, keys 16 jb + 4 g4 + 0..3)
+      f32x4 s[2];
+#pragma unroll
+      for (int jb = 0; jb < 2; ++jb) {
+        s[jb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int st = 0; st < KS; ++st) {
+          const int row = 16 * jb + col;
+          const bf16x8 ka = *(const bf16x8*)&Kt[row * D + (((4 * st + g4) ^ ((row / R) % DCH)) * 8)];
+          s[jb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka, qreg[st], s[jb], 0, 0, 0);
+        }
+      }
+      if (cur.keys != ~0u || cur.rows != 0xFFFFu) {   // uniform
+        const bool row_ok = (cur.rows >> col) & 1u;
+#pragma unroll
+        for (int jb = 0; jb < 2; ++jb)
+#pragma unroll
+          for (int x = 0; x < 4; ++x)
+            if (!row_ok || !((cur.keys >> (16 * jb + 4 * g4 + x)) & 1u)) s[jb][x] = -INFINITY;
+      }
+      // The probabilities are 2^(score - m_run) with a reference that moves only when a score outruns it by 2^64 (or on the
+      // first live keys of a row): a true maximum of the moment, so nothing overflows and the sums stay exact.
+      float mx = s[0][0];
+#pragma unroll
+      for (int x = 1; x < 4; ++x) mx = fmaxf(mx, s[0][x]);
+#pragma unroll
+      for (int x = 0; x < 4; ++x) mx = fmaxf(mx, s[1][x]);
+      mx *= a.scale_log2;
+      if (__any(mx > m_run + 64.f || (m_run == -INFINITY && mx != -INFINITY))) {
+        mx = fmaxf(mx, __shfl_xor(mx, 16));
+        mx = fmaxf(mx, __shfl_xor(mx, 32));
+        const float m_new = fmaxf(m_run, mx);
+        const float alpha = m_new == m_run ? 1.f : __builtin_amdgcn_exp2f(m_run - m_new);
+        m_run = m_new;
+        l_run *= alpha;
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+          for (int x = 0; x < 4; ++x) oacc[db][x] *= alpha;
+      }
+      const float m_use = m_run == -INFINITY ? 0.f : m_run;
+      bf16x8 p;   // contraction slots of the lane: keys 4 g4 + 0..3 and 16 + 4 g4 + 0..3
+      f32x8 pf;
+#pragma unroll
+      for (int x = 0; x < 8; ++x) {
+        pf[x] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[x >> 2][x & 3], a.scale_log2, -m_use));
+        l_run += pf[x];
+      }
+      p = __builtin_convertvector(pf, bf16x8);
+      // O^T += V^T P^T; V^T through the transposing read: in each 16-lane group lane L supplies V[J0 + L / 4][D0 + 4 (L % 4) ...]
+      // and receives V[J0 .. J0 + 3][D0 + L]
+#pragma unroll
+      for (int db = 0; db < DB; ++db) {
+        typedef bf16x4 __attribute__((address_space(3))) * lds_b4;
+        const int row = 4 * g4 + (col >> 2), piece = 2 * db + ((col >> 1) & 1);
+        const int slot = piece ^ ((((row / R) & 3) << 2) & (DCH - 1));
+        const __bf16* const vp = &Vt[row * D + slot * 8 + 4 * (col & 1)];
+        const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_b4)(vp));
+        const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_b4)(vp + 16 * D));
+        const bf16x8 va = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+        oacc[db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, p, oacc[db], 0, 0, 0);
+      }
+      cur = nxt;
+      // (the reads of this buffer are done: the products above have waited for them)
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    }
+
+    // ---- fold the waves and store -----------------------------------------------------------------
+    l_run += __shfl_xor(l_run, 16);
+    l_run += __shfl_xor(l_run, 32);
+    if (g4 == 0) { ml_s[wv][col][0] = m_run; ml_s[wv][col][1] = l_run; }
+    __syncthreads();   // (all tiles are done with as well: the LDS takes the accumulators)
+    float M = ml_s[0][col][0];
+#pragma unroll
+    for (int w = 1; w < kDecWaves; ++w) M = fmaxf(M, ml_s[w][col][0]);
+    const float own = m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run - M);
+    float* const fold = (float*)dec_lds;   // [wave][16 heads][D + 4]
+#pragma unroll
+    for (int db = 0; db < DB; ++db) {
+      f32x4 o4;
+#pragma unroll
+      for (int x = 0; x < 4; ++x) o4[x] = oacc[db][x] * own;
+      *(f32x4*)&fold[(wv * 16 + col) * (D + 4) + 16 * db + 4 * g4] = o4;
+    }
+    __syncthreads();
+    const int64_t slot = (int64_t)blockIdx.x + (int64_t)r * a.n_kv_heads + g;
+    for (int x = tid; x < a.group * (D / 4); x += kDecThreads) {
+      const int q = x / (D / 4), d = 4 * (x % (D / 4));
+      f32x4 o = *(const f32x4*)&fold[q * (D + 4) + d];
+#pragma unroll
+      for (int w = 1; w < kDecWaves; ++w) {
+        const f32x4 y = *(const f32x4*)&fold[(w * 16 + q) * (D + 4) + d];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] += y[e];
+      }
+      float Mq = ml_s[0][q][0];
+#pragma unroll
+      for (int w = 1; w < kDecWaves; ++w) Mq = fmaxf(Mq, ml_s[w][q][0]);
+      float L = 0.f;
+      if (Mq != -INFINITY)
+#pragma unroll
+        for (int w = 0; w < kDecWaves; ++w)
+          L += ml_s[w][q][0] == -INFINITY ? 0.f : ml_s[w][q][1] * __builtin_amdgcn_exp2f(ml_s[w][q][0] - Mq);
+      if (whole) {
+        const float inv = L > 0.f ? 1.0f / L : 0.f;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] *= inv;
+        *(bf16x4*)((__bf16*)rq.out + (int64_t)(h0 + q) * a.o_stride_head + d) = __builtin_convertvector(o, bf16x4);
+        if (rq.lse && d == 0) rq.lse[h0 + q] = L > 0.f ? (Mq + __builtin_amdgcn_logf(L)) * kLn2 : -INFINITY;
+      } else {
+        *(f32x4*)&a.part_o[(slot * a.group + q) * D + d] = o;
+        if (d == 0) {
+          a.part_ml[(slot * a.group + q) * 2] = Mq;
+          a.part_ml[(slot * a.group + q) * 2 + 1] = L;
+        }
+      }
+    }
+    __syncthreads();   // the LDS is reused by the next piece
+    left -= take64;
+    blk = 0;
+    if (++g == a.n_kv_heads) { ++r; fresh = true; }
+  }
+}
+
+// out = sum_s O_s 2^(m_s - M) / sum_s l_s 2^(m_s - M) over the shares that a (request, KV head) lies in; one workgroup per
+// (query head, request), shares folded in a fixed order (run-to-run identical): wave w takes every fourth share, then
+// the waves are added in order.
+template <int D>
+__global__ __launch_bounds__(kDecThreads) void k_decode_combine(const DecodeArgs a) {
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int h = blockIdx.x, r = blockIdx.y, g = h / a.group, q = h - g * a.group;
+  const vs_request rq = decode_request(a, r);
+  if (!decode_takes(a, rq)) return;
+  const int64_t T = a.plan[0], n = a.plan[1];
+  int64_t from = a.plan[2 + r];
+  int seg_len = decode_blocks(rq);
+  if (rq.s_idx) {
+    const int2* const len = a.len + (int64_t)r * a.n_kv_heads;
+    for (int x = 0; x < g; ++x) from += len[x].y;
+    seg_len = len[g].y;
+  } else {
+    from += (int64_t)g * seg_len;
+  }
+  const int s0 = (int)share_of(from, n, T), s1 = (int)share_of(from + seg_len - 1, n, T);
+  if (s0 == s1) return;   // finished by its one share
+  const int64_t row0 = ((int64_t)s0 + (int64_t)r * a.n_kv_heads + g) * a.group + q;   // row of share s: row0 + (s - s0) G
+  const int cnt = s1 - s0 + 1;
+  float M = -INFINITY;
+  for (int s = lane; s < cnt; s += 64) M = fmaxf(M, a.part_ml[2 * (row0 + (int64_t)s * a.group)]);
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) M = fmaxf(M, __shfl_xor(M, d));
+  constexpr int E = D / 64, U = 8;
+  float acc[E], L = 0.f;
+#pragma unroll
+  for (int e = 0; e < E; ++e) acc[e] = 0.f;
+  if (M != -INFINITY) {
+    for (int sb = wv; sb < cnt; sb += kDecWaves * U) {
+      float o[U][E], w[U], l[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int s = sb + kDecWaves * u < cnt ? sb + kDecWaves * u : cnt - 1;
+        const int64_t row = row0 + (int64_t)s * a.group;
+        w[u] = a.part_ml[2 * row];
+        l[u] = a.part_ml[2 * row + 1];
+#pragma unroll
+        for (int e = 0; e < E; ++e) o[u][e] = a.part_o[row * D + 64 * e + lane];
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if (sb + kDecWaves * u >= cnt || w[u] == -INFINITY) continue;
+        const float x = __builtin_amdgcn_exp2f(w[u] - M);
+        L += l[u] * x;
+#pragma unroll
+        for (int e = 0; e < E; ++e) acc[e] += o[u][e] * x;
+      }
+    }
+  }
+  __shared__ float acc_s[kDecWaves][D], l_s[kDecWaves];
+#pragma unroll
+  for (int e = 0; e < E; ++e) acc_s[wv][64 * e + lane] = acc[e];
+  if (lane == 0) l_s[wv] = L;
+  __syncthreads();
+  if (tid >= D) return;
+  float o = acc_s[0][tid];
+  L = l_s[0];
+#pragma unroll
+  for (int w = 1; w < kDecWaves; ++w) { o += acc_s[w][tid]; L += l_s[w]; }
+  ((__bf16*)rq.out)[(int64_t)h * a.o_stride_head + tid] = (__bf16)(L > 0.f ? o / L : 0.f);
+  if (rq.lse && tid == 0) rq.lse[h] = L > 0.f ? (M + __builtin_amdgcn_logf(L)) * kLn2 : -INFINITY;
+}
+
+// Bitmaps of the heads of a KV group and the union of their block lists, one workgroup per (KV head, request), for single
+// tokens with index sets.  Bits are collected in LDS (see k_build_blocklist), a window of all heads' words at a time;
+// entries are written 64 at a time with a lane per bit.
+__global__ __launch_bounds__(kDecListThreads) void k_decode_lists(const DecodeArgs a) {
+  constexpr int NW = kDecListThreads / 64;
+  __shared__ uint32_t bits[kDecListWords];   // [head][win]
+  __shared__ uint32_t wsum[NW];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int g = blockIdx.x, r = blockIdx.y, G = a.group;
+  const vs_request rq = decode_request(a, r);
+  if (!decode_takes(a, rq) || !rq.s_idx) return;
+  const int n_blk = decode_blocks(rq), n_words = (n_blk + 31) / 32;
+  const int win = kDecListWords / G & ~1;
+  uint2* const E = a.ent + ((int64_t)r * a.n_kv_heads + g) * a.ent_stride;
+  uint32_t* const B = a.bm + ((int64_t)r * a.n_q_heads + (int64_t)g * G) * a.words;
+  uint32_t running = 0;
+  for (int w0 = 0; w0 < n_words; w0 += win) {
+    const int nw = n_words - w0 < win ? n_words - w0 : win;
+    for (int x = tid; x < G * win; x += kDecListThreads) bits[x] = 0;
+    __syncthreads();
+    // (all heads' offsets on their way at once; what a line adds is set by the first of its neighbours, see list_bits)
+    for (int j0 = 0; j0 < G; j0 += 4) {
+      const int32_t* so[4];
+      int cnt[4], most = 0;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int h = g * G + (j0 + e < G ? j0 + e : j0);
+        so[e] = rq.s_idx + (int64_t)h * a.s_budget;
+        cnt[e] = j0 + e < G ? rq.s_cnt[h] : 0;
+        most = cnt[e] > most ? cnt[e] : most;
+      }
+      for (int i = tid; i < most; i += kDecListThreads) {
+        int o[4], before[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          o[e] = i < cnt[e] ? so[e][i] : 0;
+          before[e] = i < cnt[e] && i > 0 ? so[e][i - 1] : -1;
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (i < cnt[e])
+            list_bits(o[e], before[e], n_blk, [&](int ad) {
+              const int x = (ad >> 5) - w0;
+              if (x >= 0 && x < nw) atomicOr(&bits[(j0 + e) * win + x], 1u << (ad & 31));
+            });
+      }
+    }
+    __syncthreads();
+    for (int j = 0; j < G; ++j)
+      for (int w = tid; w < nw; w += kDecListThreads) B[(int64_t)j * a.words + w0 + w] = bits[j * win + w];
+    auto any = [&](int w) -> uint32_t {
+      uint32_t u = 0;
+      if (w < nw)
+        for (int j = 0; j < G; ++j) u |= bits[j * win + w];
+      return u;
+    };
+    const int wg = (((nw + 31) >> 5) + NW - 1) / NW, wlo = wv * wg * 32;   // groups of 32 words per wave
+    uint32_t c = 0;
+    for (int x = 0; x < wg; x += 2) c += x + (lane >> 5) < wg ? __popc(any(wlo + 32 * x + lane)) : 0u;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) c += __shfl_xor(c, d);
+    if (lane == 0) wsum[wv] = c;
+    __syncthreads();
+    uint32_t pos = running;
+    for (int x = 0; x < NW; ++x) {
+      if (x < wv) pos += wsum[x];
+      running += wsum[x];
+    }
+    for (int w = wlo; w < wlo + 32 * wg && w < nw; w += 2) {
+      const int wl = w + (lane >> 5);   // this lane's word and bit
+      uint32_t heads = 0;
+      if (wl < nw)
+        for (int j = 0; j < G; ++j) heads |= ((bits[j * win + wl] >> (lane & 31)) & 1u) << j;
+      const uint64_t m = __ballot(heads != 0);
+      if (heads)
+        E[pos + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u))] =
+            make_uint2((uint32_t)(32 * (w0 + w) + lane), heads);
+      pos += __popcll(m);
+    }
+    __syncthreads();   // wsum and bits are rewritten by the next window
+  }
+  if (tid == 0) {
+    int tiles = 0;
+    for (int j = 0; j < G; ++j) tiles += (rq.v_cnt[g * G + j] + 63) >> 6;
+    const int units = (int)running + tiles;   // (at least one: a token without any key gets its 0 / -inf too)
+    a.len[(int64_t)r * a.n_kv_heads + g] = make_int2((int)running, units > 0 ? units : 1);
+  }
+}
+
+// ---------------------------------------------------------------------------------------------------
+// the query heads of a KV group are the columns of one MFMA tile
+bool decode_fits(const vs_params& p) { return p.n_q_heads / p.n_kv_heads <= 16; }
+
+namespace {
+constexpr int kDecShares = 256;   // at most: one workgroup fills the LDS of a compute unit
+struct DecLayout {
+  size_t part_ml, plan, len, ent, bm, total;
+  int32_t words, ent_stride, shares;
+};
+DecLayout dec_layout(const vs_params& p, int n_req, bool lists) {
+  DecLayout l;
+  const int64_t n_blk = ceil_div(p.q_start + p.q_len, (int64_t)kBlock);
+  const size_t G = (size_t)(p.n_q_heads / p.n_kv_heads), segs = (size_t)n_req * p.n_kv_heads;
+  const int64_t most = ceil_div((int64_t)segs * (n_blk + (lists ? (int64_t)G * ceil_div(p.vertical_budget, 64) : 0)), kDecMinBlocks);
+  l.shares = (int32_t)(most < kDecShares ? most : kDecShares);
+  l.words = (int32_t)ceil_div(n_blk, 32);
+  l.ent_stride = (int32_t)n_blk;
+  const size_t rows = ((size_t)l.shares + segs) * G;
+  size_t off = align_up(rows * p.head_dim * sizeof(float), 256);
+  l.part_ml = off; off += align_up(rows * 2 * sizeof(float), 256);
+  l.plan = off; off += align_up((2 + (size_t)n_req) * sizeof(int64_t), 256);
+  l.len = l.ent = l.bm = off;
+  if (lists) {
+    off += align_up(segs * sizeof(int2), 256);
+    l.ent = off; off += align_up(segs * (size_t)l.ent_stride * sizeof(uint2), 256);
+    l.bm = off; off += align_up((size_t)n_req * p.n_q_heads * (size_t)l.words * sizeof(uint32_t), 256);
+  }
+  l.total = off;
+  return l;
+}
+}  // namespace
+
+size_t decode_bytes(const vs_params& p, int n_req, bool lists) { return dec_layout(p, n_req, lists).total; }
+
+hipError_t launch_decode(const vs_params& p, const vs_request* one, const vs_request* req, int n_req, bool lists, void* ws,
+                         hipStream_t st) {
+  const DecLayout l = dec_layout(p, n_req, lists);
+  DecodeArgs a = {};
+  if (one) a.one = *one;
+  a.req = req; a.n_req = n_req;
+  a.n_q_heads = p.n_q_heads; a.n_kv_heads = p.n_kv_heads; a.group = p.n_q_heads / p.n_kv_heads;
+  a.q_stride_head = p.q_stride_head; a.o_stride_head = p.o_stride_head;
+  a.k_stride_tok = p.k_stride_tok; a.k_stride_head = p.k_stride_head;
+  a.v_stride_tok = p.v_stride_tok; a.v_stride_head = p.v_stride_head;
+  a.scale_log2 = p.softmax_scale * kLog2e;
+  a.v_budget = p.vertical_budget; a.s_budget = p.slash_budget;
+  a.max_q_len = p.q_len; a.max_n_k = p.q_start + p.q_len;
+  char* const w = (char*)ws;
+  a.part_o = (float*)w;
+  a.part_ml = (float*)(w + l.part_ml);
+  a.plan = (int64_t*)(w + l.plan);
+  a.len = (int2*)(w + l.len);
+  a.ent = (uint2*)(w + l.ent);
+  a.bm = (uint32_t*)(w + l.bm);
+  a.words = l.words; a.ent_stride = l.ent_stride;
+  static DeviceOnce once;   // the opt-in to more than 64 KiB of LDS
+  const hipError_t e = once.run([]() {
+    const hipError_t e1 = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_decode<128>),
+                                              hipFuncAttributeMaxDynamicSharedMemorySize, decode_lds_bytes<128>());
+    if (e1 != hipSuccess) return e1;
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_decode<64>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                               decode_lds_bytes<64>());
+  });
+  if (e != hipSuccess) return e;
+  if (lists)
+    hipLaunchKernelGGL(k_decode_lists, dim3((unsigned)p.n_kv_heads, (unsigned)n_req), dim3(kDecListThreads), 0, st, a);
+  const dim3 grid((unsigned)l.shares), cgrid((unsigned)p.n_q_heads, (unsigned)n_req);
+  if (p.head_dim == 128) {
+    hipLaunchKernelGGL(k_decode<128>, grid, dim3(kDecThreads), decode_lds_bytes<128>(), st, a);
+    hipLaunchKernelGGL(k_decode_combine<128>, cgrid, dim3(kDecThreads), 0, st, a);
+  } else {
+    hipLaunchKernelGGL(k_decode<64>, grid, dim3(kDecThreads), decode_lds_bytes<64>(), st, a);
+    hipLaunchKernelGGL(k_decode_combine<64>, cgrid, dim3(kDecThreads), 0, st, a);
+  }
+  return hipGetLastError();
+}
+
+}  // namespace vs

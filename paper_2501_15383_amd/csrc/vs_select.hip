@@ -22,8 +22,6 @@
 // Measured on one MI355X, 28 heads, budgets 1000 / 6096, against four digits, a count and a write pass over all
 // scores in seven launches: 8,192 scores per row 14 us (67), 32,768 21 us (70), 300,001 57 us (152), 1M 108 us
 // (345: filter 63 us = 3.7 TB/s, sample 16, rows 29); 4 heads, budgets 128 / 256, 1M: 50 us (98).
-#include <mutex>
-
 #include "vs_common.h"
 
 namespace vs {
@@ -645,25 +643,6 @@ static SelLayout sel_layout(const vs_params& p) {
 }
 size_t select_ws_bytes(const vs_params& p) { return sel_layout(p).total; }
 
-// Per-device set-up, done once for each device: the opt-in of k_sel_row to more than 64 KiB of LDS.
-static hipError_t sel_device_setup() {
-  constexpr int kMaxDevices = 64;
-  static std::mutex mu;
-  static bool done[kMaxDevices] = {false};
-  int dev = 0;
-  hipError_t e = hipGetDevice(&dev);
-  if (e != hipSuccess) return e;
-  if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
-  std::lock_guard<std::mutex> lock(mu);
-  if (!done[dev]) {
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_sel_row<0>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                            kSelCand * (int)sizeof(uint2));
-    if (e != hipSuccess) return e;
-    done[dev] = true;
-  }
-  return hipSuccess;
-}
-
 // ws: ws_bytes bytes; fewer than select_ws_bytes(p), or none: every row lists its own candidates
 hipError_t launch_select(const vs_params& p, const float* vscore, const float* sscore,
                          const int32_t* v_budget_h, const int32_t* s_budget_h,
@@ -688,7 +667,11 @@ hipError_t launch_select(const vs_params& p, const float* vscore, const float* s
   } else if (a.n <= kSelRegKeys) {
     hipLaunchKernelGGL(k_sel_row<32>, rows, block, 0, st, a);
   } else {
-    const hipError_t e = sel_device_setup();
+    static DeviceOnce once;   // the opt-in to more than 64 KiB of LDS
+    const hipError_t e = once.run([]() {
+      return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_sel_row<0>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                 kSelCand * (int)sizeof(uint2));
+    });
     if (e != hipSuccess) return e;
     if (ws && ws_bytes >= l.total && a.n > kSelOwnKeys) {
       a.hdr = (SelHeader*)ws;

@@ -1,0 +1,75 @@
+"""Single tokens at the edges of the decode kernel: positions around the 32- and 64-key boundaries, group sizes from one
+head to a full MFMA tile, shares that end inside a KV head or span several requests, tokens without any line, and more
+requests than a workgroup has threads.  Against the fp64 oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2501_15383_amd as vs
+from gpu_util import assert_attn_close, chunk_of, dev
+from helpers import rand_bf16
+from test_gpu_attention import _rand_sets, _t
+
+pytestmark = pytest.mark.gpu
+
+
+def _problem(rng, hq, hkv, d, s, bv, bs, lines):
+    q, k, v = rand_bf16(rng, (1, hq, d)), rand_bf16(rng, (s + 1, hkv, d)), rand_bf16(rng, (s + 1, hkv, d))
+    pb = oracle.Problem(hq, hkv, d, 1, s, 1.0 / np.sqrt(d), vertical_budget=bv, slash_budget=bs, keep_first_cols=0, keep_local_band=0)
+    if lines == "none":
+        sets = (np.full((hq, bv), -1, np.int32), np.zeros(hq, np.int32), np.full((hq, bs), -1, np.int32), np.zeros(hq, np.int32))
+    elif lines == "columns":   # no diagonal: the union list is empty
+        sets = list(_rand_sets(rng, pb, min(bv, s + 1), 0))
+    elif lines == "both":
+        sets = _rand_sets(rng, pb, min(bv, max(1, (s + 1) // 4)), min(bs, max(1, (s + 1) // 50)), force_cols=[0], force_offs=[0])
+    else:
+        sets = None
+    return pb, q, k, v, sets
+
+
+@pytest.mark.parametrize("hq,hkv,d", [(7, 1, 128), (5, 5, 128), (32, 2, 64), (16, 1, 128)])
+@pytest.mark.parametrize("s", [0, 1, 30, 31, 32, 63, 64, 95, 127, 128, 4159, 9000])
+def test_single_tokens_at_every_boundary(hq, hkv, d, s):
+    rng = np.random.default_rng(2000 + s)
+    for lines in ("dense", "both", "columns", "none"):
+        pb, q, k, v, sets = _problem(rng, hq, hkv, d, s, 150, 90, lines)
+        if sets is None:
+            ref = oracle.dense_attention(pb, q, k, v)
+            got = vs.dense_causal_prefill(chunk_of(pb), dev(q), dev(k), dev(v), want_lse=True)
+        else:
+            ref = oracle.sparse_attention(pb, q, k, v, *sets)
+            got = vs.sparse_attn_prefill(chunk_of(pb), dev(q), dev(k), dev(v), *[_t(x) for x in sets], want_lse=True)
+        torch.cuda.synchronize()
+        assert_attn_close(*got, *ref, f"{lines} {hq}/{hkv} D={d} s={s}")
+
+
+@pytest.mark.parametrize("n_req", [2, 37, 300])
+def test_shares_over_many_requests(n_req):
+    hq, hkv, d, bv, bs = 6, 2, 64, 40, 30
+    rng = np.random.default_rng(2100 + n_req)
+    reqs, gpu = [], []
+    for i in range(n_req):
+        s = int(rng.choice([0, 5, 63, 64, 200, 3000 if n_req < 100 else 700]))
+        pb, q, k, v, sets = _problem(rng, hq, hkv, d, s, bv, bs, ("dense", "both", "none", "dense")[i % 4])
+        reqs.append((pb, q, k, v, sets))
+        gpu.append(dict(q=dev(q), k=dev(k), v=dev(v), q_start=s, out=torch.full((1, hq, d), -3.0, dtype=torch.bfloat16, device="cuda"),
+                        lse=torch.full((hq, 1), 7.0, device="cuda"), sets=None if sets is None else tuple(_t(x) for x in sets)))
+    ck = vs.Chunk(hq, hkv, d, 1, max(p.q_start for p, *_ in reqs), 1.0 / np.sqrt(d), vertical_budget=bv, slash_budget=bs)
+    table = vs.request_table(gpu, "cuda")
+    skipped = n_req // 2
+    table[skipped, 10] = 0   # a request outside the bounds, between two others
+    first = None
+    for _ in range(2):
+        vs.attn_batch(ck, table, n_req, gpu[0]["q"], gpu[0]["k"], gpu[0]["v"], gpu[0]["out"])
+        torch.cuda.synchronize()
+        now = [(g["out"].clone(), g["lse"].clone()) for g in gpu]
+        assert first is None or all(torch.equal(a[0].view(torch.int16), b[0].view(torch.int16)) and torch.equal(a[1], b[1])
+                                    for a, b in zip(first, now)), "not run-to-run identical"
+        first = now
+    for i, ((pb, q, k, v, sets), g) in enumerate(zip(reqs, gpu)):
+        if i == skipped:
+            assert (g["out"].float() == -3.0).all() and (g["lse"] == 7.0).all()
+            continue
+        ref = oracle.dense_attention(pb, q, k, v) if sets is None else oracle.sparse_attention(pb, q, k, v, *sets)
+        assert_attn_close(g["out"], g["lse"], *ref, f"request {i} of {n_req}, s={pb.q_start}")
