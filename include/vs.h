@@ -311,8 +311,10 @@ int vs_plan_chunks(int64_t n_ctx, int32_t n_chunks, int32_t model,
  *     before asking for them.
  *   VS_OPT_ATTN_KEY_SPLIT  chunks with few (query tile, head) units (a decode step, a short
  *     last chunk) have their key walk cut into ranges, one workgroup each, and a second
- *     kernel folds the partial results: 0 = automatic (up to 16 ranges, so that about 512
- *     workgroups run), 1 = never, 2..16 = that many ranges (at least 16 key blocks each).
+ *     kernel folds the partial results: 0 = automatic (up to 128 ranges of at least 8 key
+ *     blocks, so that the pieces fill 512 workgroup slots evenly; of longer chunks only the
+ *     units that whole rounds leave over are cut), 1 = never, 2..16 = that many ranges (at
+ *     least 16 key blocks each).
  *     Results agree within the rounding of the fp32 partial sums.  Changes the workspace
  *     sizes like the option above.  Single tokens (no DCA, at most 16 query heads per KV
  *     head) and vs_attn_batch always share out their keys by themselves.

@@ -32,14 +32,23 @@
 //    few sync segments of keys, so that K/V blocks are shared through the L2.  Which group
 //    takes which round is decided on the device from the lengths of the block lists.
 //  * template parameters: DCA (three rotations of the queries, chosen per (query, key)
-//    pattern; section 5.1) and SPLIT (short chunks: the key walk cut into ranges, partial
-//    results folded by k_attn_combine).  The plain kernel is its own instantiation.
+//    pattern; section 5.1) and SPLIT (short chunks, and what whole rounds leave of longer ones:
+//    the key walk cut into pieces that wait in queues, partial results folded by k_attn_combine;
+//    heads of a KV group share a tile where the rows leave half of it empty).  The plain kernel is
+//    its own instantiation.
 #include <atomic>
 #include <mutex>
 
 #include "vs_common.h"
 
 namespace vs {
+
+// Where the pieces of request r of a batch begin among those of all requests, the ranges each of its units is cut into
+// (0: the request is skipped), and its first slot of partial results.  Written by k_build_blocklist; entry n_req holds
+// the number of pieces.
+struct BatchPlan {
+  int32_t first, n_split, slot;
+};
 
 struct AttnArgs {
   const __bf16* q;
@@ -49,13 +58,25 @@ struct AttnArgs {
   const __bf16* q_succ;
   const __bf16* q_inter;
   int32_t dca_cblk, dca_wblk;
-  // Key split (template parameter SPLIT) for chunks with few query tiles: the walk of a (tile,
-  // head) is cut into n_split ranges of key-block distances, one workgroup each; every
-  // workgroup writes its unnormalised result (relative to its own reference) and k_attn_combine
-  // folds them.  part_o [n_split][Hq][q_len][D], part_ml [n_split][Hq][q_len][2] (reference, sum)
-  int32_t n_split;
+  // Key split (template parameter SPLIT) for launches of few units (a unit: a query tile of one head, or of `pack`
+  // heads).  The first n_whole units are walked whole; the walk of each of the others is cut into n_split ranges of
+  // key-block distances, and the pieces write their unnormalised results (relative to their own references), which
+  // k_attn_combine folds: part_o [n_split][n_units - n_whole][rows of a tile][D], part_ml the same with
+  // (reference, sum).  With n_split = 1 every unit is whole.  See unit_of for the order of the units.
+  // (first_piece: the whole units in front of it are another launch's.)
+  int32_t n_split, n_units, n_whole, first_piece;
   float* part_o;
   float* part_ml;
+  // where the slots from n_first_slots on lie
+  float* more_o;
+  float* more_ml;
+  int32_t n_first_slots;
+  // SPLIT: query heads of one KV group that share a tile (1, 2 or 4).  Chunks whose rows lie in one query block leave
+  // half of a tile's waves (three quarters: at most 32 rows) without rows; these waves take further heads.
+  // n_hs: tiles per KV group = ceil(group / pack)
+  int32_t pack, n_hs;
+  // SPLIT: eight queues of pieces, one per XCD (kQueueStride words apart; zero at the start of the launch)
+  uint32_t* queue;
   const __bf16* k;
   const __bf16* v;
   __bf16* out;
@@ -100,56 +121,121 @@ struct AttnArgs {
   // (written by k_attn_schedule from the lengths of the heads' block lists; n_gr entries per group)
   const int32_t* sched;
   int32_t n_gr;
-  // Several requests in one launch (template parameter BATCH, always with SPLIT): a unit is
-  // (request, head, query tile, key range); the request's pointers, position and length come
-  // from req[r] and replace the fields above (batch_view).  n_qtiles is then the tile count of
-  // the longest request, bm_a / ent hold one list per (request, head), part_o / part_ml one
-  // region of n_split x Hq x rows_cap rows per request.  Requests beyond max_q_len / max_n_k
+  // Several requests in one launch (template parameter BATCH, always with SPLIT): the pieces of all
+  // requests, one request after the other; a request's pointers, position and length come
+  // from req[r], its piece and slot counts from plan[r], and replace the fields above (batch_view).
+  // bm_a / ent hold one list per (request, head).  Requests beyond max_q_len / max_n_k
   // (the bounds the workspace was sized for) are skipped.
   const vs_request* req;
-  int32_t n_req, rows_cap, head_dim;
+  const BatchPlan* plan;
+  int32_t n_req, head_dim;
   int64_t max_q_len, max_n_k;
   int32_t skip_single;   // BATCH: single tokens are the decode kernel's
 };
 
-// The arguments as request r of a batch sees them.  False: the request is outside the stated
-// bounds or has a null pointer, and is skipped (nothing of it is read or written).
+constexpr int kOptSplit = 16;                      // most ranges that VS_OPT_ATTN_KEY_SPLIT asks for
+constexpr int kMaxSplit = 128;                     // ranges of a unit at most
+constexpr int kMinSteps = 8;                       // steps of a range at least
+constexpr double kPieceSteps = 4.0;                // what a piece costs beside its walk, in steps
+constexpr int kBatchSlots = 512, kShortSteps = 64;  // a batch of fewer steps per slot is cut into one piece per slot: 2 requests
+                                                    // of 64 rows at 46K keys 134 us -> 107
+constexpr int kMaxPieces = 2048, kBatchPieces = 1536;   // pieces with partial results: a call's, a batch's
+constexpr int kMaxQueueUnits = 4096;
+constexpr int kPaceBlocks = 4096;                  // key blocks from which whole units keep pace (see launch_attention)
+constexpr int kRun = 64;                           // workgroup slots of an XCD: members of a pace-keeping group
+constexpr int kQueueStride = 16;                   // words between two queue counters: a cache line each
+constexpr int kTileRows = 64 * kAttnQBlocks;       // rows of a query tile, of a slot of partial results
+
+// Query heads that share a tile, from the rows of the launch and the first one's place in its 64-block.  Rows of one query
+// block fill two of a tile's four waves (two SIMDs of four), at most 32 rows one; with the heads side by side all four work,
+// and K and V are copied once for them.  28 query / 4 KV heads: 64 rows at 1M keys 1,384 us -> 815 (with the finer cut and the
+// order of the pieces, see attn_cut), 4 rows at 50K keys 100 -> 46, 22 requests of up to 64 rows and 38K keys (40 heads)
+// 921 -> 308.  Heads without a group (or a second query block) have nothing to share.
+__host__ __device__ __forceinline__ int heads_per_tile(int64_t rows, int row_pad, int group) {
+  if (kAttnQBlocks != 2 || group < 2 || row_pad + rows > kBlock) return 1;
+  return rows <= 32 && group > 2 ? 4 : 2;
+}
+
+// What a request of a batch is to the launch: false for one outside the stated bounds or with a null pointer, which is
+// skipped (nothing of it is read or written).
+struct BatchShape {
+  bool dense, same_pos;
+  int32_t row_pad, pack, n_hs, n_qtiles, n_units;
+};
+__device__ __forceinline__ bool batch_shape(const vs_request& rq, int group, int n_kv_heads, int64_t max_q_len, int64_t max_n_k,
+                                            bool skip_single, BatchShape& b) {
+  if (!rq.q || !rq.k || !rq.v || !rq.out) return false;
+  if (rq.q_len < 1 || rq.q_len > max_q_len || rq.q_start < 0 || rq.q_start + rq.q_len > max_n_k) return false;
+  if (skip_single && rq.q_len == 1) return false;
+  b.dense = rq.s_idx == nullptr;
+  if (!b.dense && (!rq.v_idx || !rq.v_cnt || !rq.s_cnt)) return false;
+  b.row_pad = (int32_t)(rq.q_start % kBlock);
+  // attention of one token: the G heads of a KV group are the rows of one tile
+  b.same_pos = rq.q_len == 1 && group > 1 && b.dense;
+  b.pack = b.same_pos ? 1 : heads_per_tile(rq.q_len, b.row_pad, group);
+  b.n_hs = b.same_pos ? 1 : (group + b.pack - 1) / b.pack;
+  const int64_t rows = b.same_pos ? group : b.row_pad + rq.q_len;
+  b.n_qtiles = (int32_t)((rows + kTileRows - 1) / kTileRows);
+  b.n_units = b.n_qtiles * n_kv_heads * b.n_hs;
+  return true;
+}
+
+// The arguments as request r of a batch sees them.  False: the request is skipped.
 __device__ __forceinline__ bool batch_view(const AttnArgs& a0, int r, AttnArgs& a) {
   vs_request rq = a0.req[r];   // the same address in every lane: the fields are uniform
   rq.q = uniform64(rq.q); rq.k = uniform64(rq.k); rq.v = uniform64(rq.v); rq.out = uniform64(rq.out);
   rq.lse = uniform64(rq.lse); rq.v_idx = uniform64(rq.v_idx); rq.v_cnt = uniform64(rq.v_cnt);
   rq.s_idx = uniform64(rq.s_idx); rq.s_cnt = uniform64(rq.s_cnt);
   rq.q_start = uniform64(rq.q_start); rq.q_len = uniform64(rq.q_len);
-  if (!rq.q || !rq.k || !rq.v || !rq.out) return false;
-  if (rq.q_len < 1 || rq.q_len > a0.max_q_len || rq.q_start < 0 || rq.q_start + rq.q_len > a0.max_n_k) return false;
-  if (a0.skip_single && rq.q_len == 1) return false;
-  const bool dense = rq.s_idx == nullptr;
-  if (!dense && (!rq.v_idx || !rq.v_cnt || !rq.s_cnt)) return false;
+  BatchShape b;
+  if (!batch_shape(rq, a0.group, a0.n_kv_heads, a0.max_q_len, a0.max_n_k, a0.skip_single, b)) return false;
   a.q = (const __bf16*)rq.q; a.k = (const __bf16*)rq.k; a.v = (const __bf16*)rq.v;
   a.out = (__bf16*)rq.out; a.lse = rq.lse;
-  a.v_idx = dense ? nullptr : rq.v_idx;
-  a.v_cnt = dense ? nullptr : rq.v_cnt;
-  a.row_pad = (int32_t)(rq.q_start % kBlock);
+  a.v_idx = b.dense ? nullptr : rq.v_idx;
+  a.v_cnt = b.dense ? nullptr : rq.v_cnt;
+  a.row_pad = b.row_pad;
   a.q_start = rq.q_start - a.row_pad;
   a.q_len = rq.q_len + a.row_pad;
   a.q_rows = rq.q_len;
   a.n_k = rq.q_start + rq.q_len;
   a.bm_a = a0.bm_a + (int64_t)r * a0.n_q_heads * a0.bm_stride;
   a.ent = a0.ent + (int64_t)r * a0.n_q_heads * a0.ent_stride;
-  const int64_t slot = (int64_t)r * a0.n_split * a0.n_q_heads * a0.rows_cap;
+  const BatchPlan pl = a0.plan[r];
+  a.n_split = __builtin_amdgcn_readfirstlane(pl.n_split);
+  const int64_t slot = (int64_t)__builtin_amdgcn_readfirstlane(pl.slot) * kTileRows;
   a.part_o = a0.part_o + slot * a0.head_dim;
   a.part_ml = a0.part_ml + slot * 2;
-  if (rq.q_len == 1 && a0.group > 1 && dense) {
-    // attention of one token: the G heads of a KV group are the rows of one tile
+  a.pack = b.pack; a.n_hs = b.n_hs; a.n_qtiles = b.n_qtiles; a.n_units = b.n_units;
+  a.n_whole = a.n_split == 1 ? b.n_units : 0;
+  a.first_piece = 0;
+  a.n_first_slots = INT32_MAX;
+  if (b.same_pos) {
     a.q_stride_tok = a0.q_stride_head; a.q_stride_head = (int64_t)a0.group * a0.q_stride_head;
     a.o_stride_tok = a0.o_stride_head; a.o_stride_head = (int64_t)a0.group * a0.o_stride_head;
     a.n_q_heads = a0.n_kv_heads; a.group = 1;
     a.same_pos = 1; a.pos_in_block = a.row_pad;
     a.row_pad = 0; a.q_len = a0.group; a.q_rows = a0.group;
-    a.n_split = a0.n_split * a0.group;   // see the unit decode of k_attention
   }
-  a.n_qtiles = (int32_t)((a.q_len + 64 * kAttnQBlocks - 1) / (64 * kAttnQBlocks));
   return true;
+}
+
+// Unit e of a launch: KV group, first head and query tile.  Consecutive units share K/V rows: runs of kRun consecutive
+// tiles of one head, the latest first, heads inside (the order in which the pace-keeping kernel takes its rounds), then
+// what is left of the heads, one after the other.
+__device__ __forceinline__ void unit_of(const AttnArgs& a, int e, int& g, int& h0, int& qt) {
+  const int n_run = a.n_qtiles / kRun, n_rem = a.n_qtiles - n_run * kRun, slots = a.n_q_heads / a.group * a.n_hs;
+  int hs;
+  if (e < n_run * kRun * slots) {
+    const int run = e / kRun, c = run / slots;
+    hs = run - c * slots;
+    qt = n_rem + (n_run - c) * kRun - 1 - (e - run * kRun);
+  } else {
+    e -= n_run * kRun * slots;
+    hs = e / n_rem;
+    qt = n_rem - 1 - (e - hs * n_rem);
+  }
+  g = hs / a.n_hs;
+  h0 = g * a.group + (hs - g * a.n_hs) * a.pack;
 }
 
 __device__ __forceinline__ bool bm_test(const uint32_t* bm, int i) {
@@ -210,6 +296,7 @@ __device__ __forceinline__ uint32_t lds_address(const void* p) {
 //                   tile classification and no bookkeeping beyond the pace keeping (right results)
 // They split the time of a step into what the arithmetic stream, the operand reads, the copies
 // and the barrier cost.
+constexpr int kHeadShift = 27;   // vertical tile of packed heads: (head << kHeadShift) | tile of 64 columns (a head has at most 2^25)
 template <int D, int NQB, bool DCA, bool SPLIT, bool BATCH = false>
 __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
   static_assert(!BATCH || (SPLIT && !DCA), "several requests per launch ride on the key-split kernel");
@@ -239,8 +326,6 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave index, known uniform
-  const int t = wv >> 1;                          // query block of this wave inside the tile
-  const int il = ((wv & 1) << 5) + (lane & 31);   // row inside the query block
   const int hh = lane >> 5;
 
   // ---- persistent workgroup: one (query tile, head) per round ------------------------------
@@ -249,15 +334,27 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
   // counters below keep the group inside a window of a few sync segments, small enough for
   // the XCD's L2, so that a K/V block is fetched from memory once per group and round.
   // Waiting is bounded and only shapes the timing: results never depend on it.
+  //
+  // SPLIT: no pace keeping.  The pieces lie in eight queues, `members` consecutive ones in each in turn; a workgroup
+  // takes the piece of its own place, then from its XCD's queue (the pieces there share K/V rows in the L2), then from
+  // the queue with the most left.  The results do not depend on who takes what.
   const int grp = blockIdx.x & 7, member = blockIdx.x >> 3;
   const int n_full_gr = a0.n_full * a0.n_q_heads;   // full rounds: latest chunks first, heads inside
-  const int n_gr = SPLIT ? (a0.n_qtiles * a0.n_split * a0.n_q_heads * (BATCH ? a0.n_req : 1) + a0.members - 1) / a0.members
-                         : n_full_gr + (a0.n_rem * a0.n_q_heads + a0.members - 1) / a0.members;
+  const int n_gr = a0.n_gr;
   uint32_t* const arr = a0.arrive + (int64_t)grp * a0.n_sync;
   const int s_glob_top = (int)((a0.n_k - 1) / 64) >> a0.sync_shift;  // highest sync segment of the chunk
-  for (int rnd = 0; SPLIT ? rnd * 8 + grp < n_gr : rnd < n_gr; ++rnd) {
-  int gr = rnd * 8 + grp;
-  if constexpr (!SPLIT) {
+  int n_pieces = 0;
+  if constexpr (BATCH) n_pieces = __builtin_amdgcn_readfirstlane(a0.plan[a0.n_req].first);
+  else if constexpr (SPLIT) n_pieces = a0.n_whole - a0.first_piece + (a0.n_units - a0.n_whole) * a0.n_split;
+  int q_grp = grp, q_pos = member;   // SPLIT: the queue and the place in it of the next piece
+  for (int rnd = 0; SPLIT || rnd < n_gr; ++rnd) {
+  int gr = 0, u = 0;
+  uint32_t q_next = 0;
+  if constexpr (SPLIT) {
+    u = ((q_pos / a0.members) * 8 + q_grp) * a0.members + q_pos % a0.members;
+    // the place after this one, requested now and read at the end of the piece
+    if (n_pieces > (int)gridDim.x && tid == 0) q_next = atomicAdd(&a0.queue[grp * kQueueStride], 1u) + (uint32_t)a0.members;
+  } else {
     gr = __builtin_amdgcn_readfirstlane(a0.sched[grp * n_gr + rnd]);
     if (gr < 0) break;
   }
@@ -265,46 +362,63 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
   AttnArgs a_req;
   if constexpr (BATCH) a_req = a0;
   const AttnArgs& a = BATCH ? a_req : a0;
-  int h, qt, sp = 0;
-  if constexpr (BATCH) {
-    const int per_head = a0.n_qtiles * a0.n_split, per_req = per_head * a0.n_q_heads;
-    const int u = gr * a0.members + member;
-    const int r = u / per_req;
-    if (r >= a0.n_req) continue;
-    int v = u - r * per_req;
-    h = v / per_head;
-    v -= h * per_head;
-    qt = v / a0.n_split;
-    sp = v - qt * a0.n_split;
-    if (!batch_view(a0, r, a_req)) continue;
-    if (a.same_pos) {
-      // heads packed into rows: the unit slots of the G heads of a group become G times as many key
-      // ranges of the group's one tile
-      sp += (h % a0.group) * a0.n_split;
-      h /= a0.group;
-    }
-    if (h >= a.n_q_heads) continue;
-  } else
+  int g, h, qt, sp = 0, slot = 0;
+  bool whole = true, none = false;   // none: no tile for this workgroup in this round
   if constexpr (SPLIT) {
-    // unit u = ((head, tile), split), no pace keeping (the members walk different key ranges)
-    const int per_head = a.n_qtiles * a.n_split;
-    const int u = gr * a.members + member;
-    h = u / per_head;
-    const int v = u - h * per_head;
-    qt = h < a.n_q_heads ? v / a.n_split : a.n_qtiles;
-    sp = v % a.n_split;
-    if (h >= a.n_q_heads) h = 0;
-  } else if (gr < n_full_gr) {
-    h = gr % a.n_q_heads;
-    qt = a.n_rem + (a.n_full - 1 - gr / a.n_q_heads) * a.members + (a.members - 1 - member);
-  } else {  // packed rounds: unit u = (head, tile below n_rem), tiles descending inside a head
-    const int u = (gr - n_full_gr) * a.members + member;
-    h = u / a.n_rem;
-    qt = h < a.n_q_heads ? a.n_rem - 1 - u % a.n_rem : a.n_qtiles;
-    if (h >= a.n_q_heads) h = 0;
+    none = u >= n_pieces;
+    if constexpr (BATCH) {
+      if (!none) {
+        // the last request that begins at or before piece u (64 of them at a time)
+        int r = -1;
+        for (int r0 = 0; r0 < a0.n_req; r0 += 64) {
+          const int x = r0 + lane;
+          const int first = a0.plan[x < a0.n_req ? x : a0.n_req].first;
+          const int n = __popcll(__ballot(x < a0.n_req && first <= u));
+          r += n;
+          if (n < 64) break;
+        }
+        // (a skipped request begins where the next one does: the last one found has the piece)
+        u -= __builtin_amdgcn_readfirstlane(a0.plan[r].first);
+        none = !batch_view(a0, r, a_req);
+      }
+    }
+    if constexpr (!BATCH) u += a0.first_piece;
+    int e = u;
+    whole = u < a.n_whole;
+    if (!whole && !none) {
+      const int v = u - a.n_whole, n = a.n_units - a.n_whole;
+      sp = v / n;
+      e = a.n_whole + v - sp * n;
+      slot = v;
+    }
+    if (none) e = 0;
+    unit_of(a, e, g, h, qt);
+  } else {
+    if (gr < n_full_gr) {
+      h = gr % a.n_q_heads;
+      qt = a.n_rem + (a.n_full - 1 - gr / a.n_q_heads) * a.members + (a.members - 1 - member);
+    } else {  // packed rounds: unit u = (head, tile below n_rem), tiles descending inside a head
+      const int v = (gr - n_full_gr) * a.members + member;
+      h = v / a.n_rem;
+      qt = a.n_rem - 1 - v % a.n_rem;
+      if (h >= a.n_q_heads) { h = 0; none = true; }
+    }
+    g = h / a.group;
   }
+  // This wave's rows: query block t of the tile, 32 rows from block row il0; with packed heads the one query block,
+  // the rows from its first live one, and head h + th (whose bit in an entry's mask is th)
+  const int pack = SPLIT ? a.pack : 1;
+  int t = wv >> 1, th = 0, il0 = (wv & 1) << 5;
+  if (SPLIT && pack > 1) {
+    t = 0;
+    th = pack == 4 ? wv : wv >> 1;
+    il0 = a.row_pad + (pack == 4 ? 0 : il0);
+  }
+  const int mbit = SPLIT && pack > 1 ? th : t;
+  const bool head_ok = !SPLIT || (h - g * a.group) + th < a.group;
+  const int hw = head_ok ? h + th : h;             // this wave's head
+  const int il = il0 + (lane & 31) < 64 ? il0 + (lane & 31) : 63;   // row inside the query block (rows behind it: not stored)
   const int64_t n_k = a.n_k;
-  const int g = h / a.group;
   const uint32_t expected = (uint32_t)(rnd + 1) * (uint32_t)a.members;
   // marks key segments seg_done - 1, ..., s_new done for this member, then holds the workgroup
   // back (wave 0 polls, the others meet it at the step barrier) until the whole group is done
@@ -328,22 +442,25 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
     }
     seg_done = s_new + 1;
   };
-  if (qt >= a.n_qtiles) {  // no tile for this member in this round
+  if (!SPLIT && none) {
     enter_segment(-1, false);
     continue;
   }
+  if (!none) {
   const int64_t row0 = (int64_t)qt * (64 * NQB);
-  const int64_t row = row0 + 64 * t + il;
+  const int64_t row = row0 + 64 * t + il0 + (lane & 31);
   const int m0 = (int)(a.q_start / 64) + qt * NQB;  // absolute index of query block t = 0
-  const bool wave_valid = row0 + 64 * t + ((wv & 1) << 5) < a.q_len;
+  const bool wave_valid = head_ok && row0 + 64 * t + il0 < a.q_len;
   const int64_t rows_in_tile = (a.q_len - row0) < 64 * NQB ? (a.q_len - row0) : 64 * NQB;
   const int64_t last_pos = a.same_pos ? n_k - 1 : a.q_start + row0 + rows_in_tile - 1;
 
-  const uint32_t* bmA = a.bm_a + (int64_t)h * a.bm_stride;
+  const uint32_t* bmA = a.bm_a + (int64_t)hw * a.bm_stride;
   const int seg_shift = __builtin_amdgcn_readfirstlane((int)bmA[a.bm_words - 1]);  // sparser list, longer sync segments
-  const uint32_t* ent_h = a.ent + (int64_t)h * a.ent_stride;
+  const uint32_t* ent_h = a.ent + (int64_t)(SPLIT ? g * a.n_hs + (h - g * a.group) / pack : h) * a.ent_stride;
   const int32_t* vidx_h = a.v_idx ? a.v_idx + (int64_t)h * a.v_budget : nullptr;
-  const int vcnt = a.v_idx ? __builtin_amdgcn_readfirstlane(a.v_cnt[h]) : 0;
+  // selected columns of head h, with packed heads those of head h + i in lane i
+  const int vcnt_l = a.v_idx ? (SPLIT ? a.v_cnt[h + (lane < pack && h - g * a.group + lane < a.group ? lane : 0)] : a.v_cnt[h]) : 0;
+  const int vcnt = __builtin_amdgcn_readfirstlane(vcnt_l);
   const int n_vt = (vcnt + 63) >> 6;
   const int cc_last = m0 + NQB - 1;  // entry cc stands for key block m0 + (NQB - 1) - cc >= 0
 
@@ -364,7 +481,7 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
     }
     int64_t rc = row - a.row_pad;  // the caller's row (clamped: padding and tail rows load a valid one)
     rc = rc < 0 ? 0 : (rc < a.q_rows ? rc : a.q_rows - 1);
-    const __bf16* qp = qb + rc * a.q_stride_tok + (int64_t)h * a.q_stride_head + 8 * hh;
+    const __bf16* qp = qb + rc * a.q_stride_tok + (int64_t)hw * a.q_stride_head + 8 * hh;
 #pragma unroll
     for (int st = 0; st < DSTEPS; ++st) qreg[st] = *(const bf16x8*)(qp + 16 * st);
     q_var = var;
@@ -403,8 +520,9 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
   // n_split-th vertical tile; the first entry is found by bisection (the list ascends in cc and
   // ends in sentinels).
   int cc_end = cc_last, ei0 = 0;
-  const int vstep = SPLIT ? a.n_split : 1;
-  if constexpr (SPLIT) {
+  const int vstep = SPLIT && !whole ? a.n_split : 1;
+  int vlin = sp - vstep;
+  if (SPLIT && !whole) {
     const int per = (cc_last + a.n_split) / a.n_split;  // ceil((cc_last + 1) / n_split)
     const int cc_lo = sp * per;
     cc_end = cc_lo + per - 1 < cc_last ? cc_lo + per - 1 : cc_last;
@@ -436,7 +554,19 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
         enter_segment(-1, false);  // the slash walk is over
       }
     }
-    if (k2 == 1) {
+    if (k2 == 1 && SPLIT && pack > 1) {
+      // the tiles of the packed heads one after the other: idx = (head, tile of its columns).  The one query block of
+      // the launch ends at the last key, so that no tile lies behind it
+      vlin += vstep;
+      int x = vlin, hd = 0;
+      for (; hd < pack && h - g * a.group + hd < a.group; ++hd) {
+        const int nt = (int)(__builtin_amdgcn_readlane(vcnt_l, hd) + 63) >> 6;
+        if (x < nt) break;
+        x -= nt;
+      }
+      if (hd < pack && h - g * a.group + hd < a.group) { i2 = (hd << kHeadShift) | x; m2 = 1 << hd; }
+      else { k2 = 2; i2 = 0; }
+    } else if (k2 == 1) {
       const int vt = i2 + vstep;
       bool more = vt < n_vt;
       if (more) more = (int64_t)__builtin_amdgcn_readfirstlane(vidx_h[64 * vt]) <= last_pos;
@@ -452,6 +582,10 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
     if (kind == 0) {
       int64_t j = (int64_t)(m0 - (idx - (NQB - 1))) * 64 + r;
       return j < n_k ? j : n_k - 1;
+    }
+    if (SPLIT && pack > 1) {
+      const int hd = idx >> kHeadShift, pos = 64 * (idx & ((1 << kHeadShift) - 1)) + r;
+      return pos < __builtin_amdgcn_readlane(vcnt_l, hd) ? (int64_t)vidx_h[(int64_t)hd * a.v_budget + pos] : 0;
     }
     int pos = 64 * idx + r;
     return pos < vcnt ? (int64_t)vidx_h[pos] : 0;
@@ -861,14 +995,20 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
     diag = false;
     bool usable = false;  // vertical tile: this lane's key can be used by some row of the block
     if (__builtin_expect(cur_kind == 0, 1)) {
-      part = part && ((cur_mask >> t) & 1);
+      part = part && ((cur_mask >> mbit) & 1);
       diag = cur_idx - (NQB - 1) + t == 0;  // block diagonal 0 of (query block t, this key block)
     } else if (!last) {
-      const int pos = 64 * cur_idx + lane;
+      int pos = 64 * cur_idx + lane, n_cols = vcnt;
+      if (SPLIT && pack > 1) {
+        const int hd = cur_idx >> kHeadShift;
+        pos = 64 * (cur_idx & ((1 << kHeadShift) - 1)) + lane;
+        n_cols = __builtin_amdgcn_readlane(vcnt_l, hd);
+        part = part && hd == th;
+      }
       const int j = vidx_s[buf * 64 + lane];
       const int ad = (m0 + t) - (j >> 6);
       int need = 64;
-      if (pos < vcnt && ad >= 0 && !bm_test(bmA, ad)) need = ad == 0 ? (j & 63) : 0;
+      if (pos < n_cols && ad >= 0 && !bm_test(bmA, ad)) need = ad == 0 ? (j & 63) : 0;
       need_s[wv * 64 + lane] = (uint8_t)need;
       usable = need < 64;
       part = part && __ballot(usable) != 0;
@@ -978,12 +1118,14 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
   // ---- normalise and store ------------------------------------------------------------------
   const float l_tot = l_run + __shfl_xor(l_run, 32);
   const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
-  if constexpr (SPLIT) {
-    // this split's share of the row: accumulators and row sum relative to the reference m_o
+  if (SPLIT && !whole) {
+    // this piece's share of the row: accumulators and row sum relative to the reference m_o
     const int64_t ro = row - a.row_pad;
-    if (ro >= 0 && ro < a.q_rows) {
-      const int64_t pr = ((int64_t)sp * a.n_q_heads + h) * a.q_rows + ro;
-      float* op = a.part_o + pr * D;
+    if (head_ok && ro >= 0 && ro < a.q_rows) {
+      const bool more = slot >= a.n_first_slots;
+      const int64_t pr = (int64_t)(more ? slot - a.n_first_slots : slot) * kTileRows + 32 * wv + (lane & 31);
+      float* op = (more ? a.more_o : a.part_o) + pr * D;
+      float* mlp = (more ? a.more_ml : a.part_ml) + pr * 2;
 #pragma unroll
       for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -994,14 +1136,14 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
           *(f32x4*)(op + 32 * db + 8 * vq + 4 * hh) = o4;
         }
       if (hh == 0) {
-        a.part_ml[2 * pr] = m_o;
-        a.part_ml[2 * pr + 1] = l_tot;
+        mlp[0] = m_o;
+        mlp[1] = l_tot;
       }
     }
   } else
-  if (row >= a.row_pad && row < a.q_len) {
+  if (head_ok && row >= a.row_pad && row < a.q_len) {
     const int64_t ro = row - a.row_pad;
-    __bf16* op = a.out + ro * a.o_stride_tok + (int64_t)h * a.o_stride_head;
+    __bf16* op = a.out + ro * a.o_stride_tok + (int64_t)hw * a.o_stride_head;
 #pragma unroll
     for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -1012,11 +1154,44 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
         *(bf16x4*)(op + 32 * db + 8 * vq + 4 * hh) = __builtin_convertvector(o4, bf16x4);
       }
     if (a.lse && hh == 0)
-      a.lse[(int64_t)h * a.q_rows + ro] =
+      a.lse[(int64_t)hw * a.q_rows + ro] =
           l_tot > 0.f ? (m_o + __builtin_amdgcn_logf(l_tot)) * kLn2 : -INFINITY;
   }
   enter_segment(-1, false);  // (a tile whose walk ended early has marked nothing yet)
-  __syncthreads();           // the LDS tiles are reused by the next round
+  }  // !none
+  if constexpr (SPLIT) {
+    if (n_pieces <= (int)gridDim.x) break;
+    int* const next_s = (int*)vidx_s;
+    if (tid < 64) {
+      int at = __builtin_amdgcn_readfirstlane((int)q_next), from = grp;
+      auto left_in = [&](int x) -> int {   // pieces of queue x: whole runs of `members`, and the run that the last piece ends in
+        const int runs = n_pieces / a0.members, tail = n_pieces - runs * a0.members;
+        return ((runs - x + 7) >> 3) * a0.members + ((runs & 7) == x ? tail : 0);
+      };
+      while (at >= left_in(from)) {
+        // the own queue is empty: the one with the most left.  A queue only ever grows emptier, so this ends
+        const int x = lane & 7;
+        const int seen = (int)__hip_atomic_load(&a0.queue[x * kQueueStride], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + a0.members;
+        int best = left_in(x) - seen > 0 ? ((left_in(x) - seen) << 3) | x : 0;
+#pragma unroll
+        for (int d = 1; d < 8; d <<= 1) { const int y = __shfl_xor(best, d); best = y > best ? y : best; }
+        best = __builtin_amdgcn_readfirstlane(best);
+        if (best == 0) { at = -1; break; }
+        from = best & 7;
+        uint32_t got = 0;
+        if (lane == 0) got = atomicAdd(&a0.queue[from * kQueueStride], 1u);
+        at = (int)__builtin_amdgcn_readfirstlane(got) + a0.members;
+      }
+      if (tid == 0) { next_s[0] = at; next_s[1] = from; }
+    }
+    __syncthreads();   // (also: the LDS tiles are reused by the next piece)
+    q_pos = __builtin_amdgcn_readfirstlane(next_s[0]);
+    q_grp = __builtin_amdgcn_readfirstlane(next_s[1]);
+    __syncthreads();   // the next piece writes column indices there
+    if (q_pos < 0) break;
+  } else {
+    __syncthreads();   // the LDS tiles are reused by the next round
+  }
   }  // rounds
 }
 
@@ -1026,10 +1201,12 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
 // and, when o is not a multiple of 64, floor(o/64) + 1: these set the bitmap A.  The entry
 // list then holds every cc for which A has a bit in [cc - (NQB-1), cc], with the per-query-
 // block mask, in ascending order, followed by sentinels up to the end of the row.
-// With req != null the launch builds one list per (request, head), blockIdx.y = r * n_heads + h:
+// With packed heads (pack > 1) a list is that of a tile of `pack` heads with one query block: the union of their
+// diagonals a, as cc = a + NQB - 1, with a mask bit per head that has the diagonal.
+// With req != null the launch builds one list per (request, head), blockIdx.y = 1 + r * n_heads + h:
 // offsets, their count, the number of key blocks and "dense" (no offsets given) come from the
-// request; a request outside the bounds the workspace was sized for, or shorter than min_q_len, gets no
-// list (the attention kernel skips it).  The workgroup of the first list also clears the n_zero words at `zero` (the
+// request; a request that the attention kernel skips gets no list, and where it packs heads only as many as it
+// has tiles.  The first workgroup of a batch writes its plan (write_plan), the lists follow.  The workgroup of the first list also clears the n_zero words at `zero` (the
 // attention launch's counters).
 //
 // A sparse list is one workgroup's (blockIdx.x = 0) and bound by latency, not bytes (6,096 offsets
@@ -1041,33 +1218,137 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
 // is cut into kBlDensePart entries per workgroup.
 // ---------------------------------------------------------------------------------------------
 constexpr int kBlThreads = 1024;
-constexpr int kBlWin = 4096;        // bitmap words in LDS at a time (8.4M keys)
+constexpr int kBlWin = 4096;        // bitmap words in LDS at a time (8.4M keys; shared by packed heads)
 constexpr int kBlDensePart = 4096;  // entries of a dense list per workgroup
+struct ListArgs {
+  const int32_t* s_idx;
+  const int32_t* s_cnt;
+  int32_t s_budget, dense, n_blk, n_words, ent_stride;
+  uint32_t* bm_a;
+  uint32_t* ent;
+  int32_t n_heads, group, pack;
+  uint32_t* zero;
+  int32_t n_zero;
+  // a batch
+  const vs_request* req;
+  BatchPlan* plan;
+  int32_t n_req, skip_single, pieces;
+  int64_t max_q_len, max_n_k;
+};
+// Steps (64-key blocks, columns at twice their number: they take the masked path) that a tile of the request walks, for the
+// plan only: a list is taken to scatter.
+__device__ __forceinline__ int64_t batch_steps(const vs_request& rq, const BatchShape& b) {
+  const int64_t n_blk = (rq.q_start + rq.q_len + kBlock - 1) / kBlock;
+  if (b.dense) return n_blk;
+  const int64_t listed = 2 * (int64_t)rq.s_cnt[0] + 1;
+  return (listed < n_blk ? listed : n_blk) + 2 * b.pack * ((rq.v_cnt[0] + 63) / 64);
+}
+// Ranges per unit so that all pieces of a batch come out about equally long and there are a.pieces of them: the requests
+// differ in length, and a workgroup takes the next piece when it is done with one.  Rounded down, so that the split units
+// have at most a.pieces pieces (slots of partial results).
+__device__ void write_plan(const ListArgs& a, int64_t* scan) {
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  constexpr int NW = kBlThreads / 64;
+  auto look = [&](int r, BatchShape& b, int64_t& steps) -> bool {
+    const vs_request rq = a.req[r];
+    if (!batch_shape(rq, a.group, a.n_heads / a.group, a.max_q_len, a.max_n_k, a.skip_single, b)) return false;
+    steps = batch_steps(rq, b);
+    return true;
+  };
+  BatchShape b;
+  int64_t steps = 0, sum = 0;
+  bool taken = false;   // of the request this thread looked at last (the only one of up to kBlThreads requests)
+  for (int r = tid; r < a.n_req; r += kBlThreads) {
+    taken = look(r, b, steps);
+    if (taken) sum += b.n_units * steps;
+  }
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) sum += __shfl_xor((long long)sum, d);
+  if (lane == 0) scan[wv] = sum;
+  __syncthreads();
+  int64_t total = 0;
+  for (int w = 0; w < NW; ++w) total += scan[w];
+  __syncthreads();
+  // (about three pieces per workgroup slot, one where they would come out short)
+  const int64_t target = total < (int64_t)kBatchSlots * kShortSteps && a.pieces > kBatchSlots ? kBatchSlots : a.pieces;
+  int64_t before = 0;   // pieces, and slots in the high half
+  for (int r0 = 0; r0 < a.n_req; r0 += kBlThreads) {
+    const int r = r0 + tid;
+    int n_split = 0;
+    int64_t mine = 0;
+    if (a.n_req > kBlThreads) taken = r < a.n_req && look(r, b, steps);
+    if (taken) {
+      int64_t n = steps * target / total;
+      if (n > steps / kMinSteps) n = steps / kMinSteps;
+      n_split = n < 1 ? 1 : (n > kMaxSplit ? kMaxSplit : (int)n);
+      const int64_t pieces = (int64_t)b.n_units * n_split;
+      mine = pieces | (n_split > 1 ? pieces << 32 : 0);
+    }
+    int64_t inc = mine;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const int64_t y = __shfl_up((long long)inc, d);
+      if (lane >= d) inc += y;
+    }
+    if (lane == 63) scan[wv] = inc;
+    __syncthreads();
+    int64_t all = 0;
+    for (int w = 0; w < NW; ++w) {
+      if (w < wv) inc += scan[w];
+      all += scan[w];
+    }
+    inc += before - mine;
+    if (r < a.n_req) {
+      a.plan[r].first = (int32_t)inc;
+      a.plan[r].n_split = n_split;
+      a.plan[r].slot = (int32_t)(inc >> 32);
+    }
+    before += all;
+    __syncthreads();
+  }
+  if (tid == 0) {
+    a.plan[a.n_req].first = (int32_t)before;
+    a.plan[a.n_req].n_split = 0;
+    a.plan[a.n_req].slot = (int32_t)(before >> 32);
+  }
+}
 template <int NQB>
-__global__ __launch_bounds__(kBlThreads) void k_build_blocklist(const int32_t* s_idx, const int32_t* s_cnt,
-                                                                int32_t s_budget, int dense, int n_blk,
-                                                                int n_words, int ent_stride, uint32_t* bm_a,
-                                                                uint32_t* ent, const vs_request* req, int n_heads,
-                                                                int64_t min_q_len, int64_t max_q_len,
-                                                                int64_t max_n_k, uint32_t* zero, int n_zero) {
+__global__ __launch_bounds__(kBlThreads) void k_build_blocklist(const ListArgs a) {
   constexpr int NW = kBlThreads / 64;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int part = blockIdx.x, list = blockIdx.y;
-  int h = list;
-  uint32_t* const A = bm_a + (int64_t)list * n_words;
-  uint32_t* const E = ent + (int64_t)list * ent_stride;
+  const int part = blockIdx.x, list = (int)blockIdx.y - (a.req ? 1 : 0);   // a batch: the first workgroup is the plan's
+  const int n_words = a.n_words, ent_stride = a.ent_stride;
+  int x0 = list, dense = a.dense, n_blk = a.n_blk, pack = a.pack, n_hs = (a.group + pack - 1) / pack;
+  const int32_t* s_idx = a.s_idx;
+  const int32_t* s_cnt = a.s_cnt;
+  uint32_t* bm_a = a.bm_a;
+  uint32_t* const E = a.ent + (int64_t)list * ent_stride;
   if (part == 0 && list == 0)
-    for (int x = tid; x < n_zero; x += kBlThreads) zero[x] = 0u;
-  if (req) {
-    const vs_request rq = req[list / n_heads];
-    h = list % n_heads;
-    if (rq.q_len < min_q_len || rq.q_len > max_q_len || rq.q_start < 0 || rq.q_start + rq.q_len > max_n_k) return;
-    dense = rq.s_idx == nullptr;
-    if (!dense && !rq.s_cnt) return;
+    for (int x = tid; x < a.n_zero; x += kBlThreads) a.zero[x] = 0u;
+  if (a.req) {
+    __shared__ int64_t scan[NW];
+    if (list < 0) {
+      write_plan(a, scan);
+      return;
+    }
+    const int r = list / a.n_heads;
+    x0 = list - r * a.n_heads;
+    const vs_request rq = a.req[r];
+    BatchShape b;
+    if (!batch_shape(rq, a.group, a.n_heads / a.group, a.max_q_len, a.max_n_k, a.skip_single, b)) return;
+    pack = b.pack;
+    n_hs = b.n_hs;
+    dense = b.dense;
     s_idx = rq.s_idx; s_cnt = rq.s_cnt;
     n_blk = (int)((rq.q_start + rq.q_len + kBlock - 1) / kBlock);
+    bm_a += (int64_t)r * a.n_heads * n_words;
+    if (x0 >= a.n_heads / a.group * n_hs) return;
   }
+  // the first head of list x0, and how many heads it has
+  const int grp = dense && !a.req ? 0 : x0 / n_hs, h0 = dense && !a.req ? 0 : grp * a.group + (x0 - grp * n_hs) * pack;
+  const int n_in = grp * a.group + a.group - h0 < pack ? grp * a.group + a.group - h0 : pack;
+  uint32_t* const A = bm_a + (int64_t)h0 * n_words;
   // The last two words of the bitmap row lie beyond every diagonal.  The last one tells the attention
   // kernel how sparse the list is: sync segments of this head are 2^shift times the base size, so
   // that a segment holds about as many listed key blocks as it would in a dense list.
@@ -1078,6 +1359,14 @@ __global__ __launch_bounds__(kBlThreads) void k_build_blocklist(const int32_t* s
     A[n_words - 1] = (uint32_t)shift;
     A[n_words - 2] = n_list;  // length of the list: the head's share of the work (k_attn_schedule)
   };
+  if (dense && pack > 1) {
+    for (int i = part * kBlDensePart + tid; i < ent_stride && (i < (part + 1) * kBlDensePart || (int)gridDim.x == part + 1);
+         i += kBlThreads)
+      E[i] = i < n_blk ? ((uint32_t)(i + NQB - 1) << 4) | 15u : kEntSentinel;
+    // (no bitmap: a dense walk has no columns that ask it)
+    if (part == 0 && tid == 0) write_tail((uint32_t)n_blk);
+    return;
+  }
   if (dense) {
     const int n_list = n_blk + NQB - 1, all = (1 << NQB) - 1;
     for (int i = part * kBlDensePart + tid; i < ent_stride && (i < (part + 1) * kBlDensePart || (int)gridDim.x == part + 1);
@@ -1104,9 +1393,62 @@ __global__ __launch_bounds__(kBlThreads) void k_build_blocklist(const int32_t* s
 
   __shared__ uint32_t aw[kBlWin + 2];   // aw[1 + w]: bitmap word w0 + w; aw[0]: the word before the window
   __shared__ uint32_t wsum[NW];
-  const int cnt = s_cnt[h];
-  const int32_t* const so = s_idx + (int64_t)h * s_budget;
-  uint32_t running = 0, before = 0;
+  uint32_t running = 0;
+  if (pack > 1) {
+    // one bitmap of `win` words per head in LDS
+    const int win = kBlWin / 4;
+    for (int w0 = 0; w0 < n_words - 2; w0 += win) {
+      const int nw = n_words - 2 - w0 < win ? n_words - 2 - w0 : win;
+      for (int w = tid; w < 4 * win; w += kBlThreads) aw[w] = 0u;
+      __syncthreads();
+      for (int p = 0; p < n_in; ++p) {
+        const int cnt = s_cnt[h0 + p];
+        const int32_t* const so = s_idx + (int64_t)(h0 + p) * a.s_budget;
+        for (int i = tid; i < cnt; i += kBlThreads)
+          list_bits(so[i], i > 0 ? so[i - 1] : -1, n_blk, [&](int ad) {
+            const int x = (ad >> 5) - w0;
+            if (x >= 0 && x < nw) atomicOr(&aw[p * win + x], 1u << (ad & 31));
+          });
+      }
+      __syncthreads();
+      for (int p = 0; p < n_in; ++p)
+        for (int w = tid; w < nw; w += kBlThreads) A[(int64_t)p * n_words + w0 + w] = aw[p * win + w];
+      // (heads beyond n_in have no bits; words beyond nw neither, up to the next power of two that a wave reads)
+      const int wg = (((nw + 31) >> 5) + NW - 1) / NW, wlo = wv * wg * 32;
+      auto listed = [&](int w) -> uint32_t {
+        return w < nw ? aw[w] | aw[win + w] | aw[2 * win + w] | aw[3 * win + w] : 0u;
+      };
+      uint32_t c = 0;
+      for (int g = 0; g < wg; g += 2) c += g + (lane >> 5) < wg ? __popc(listed(wlo + 32 * g + lane)) : 0u;
+#pragma unroll
+      for (int d = 1; d < 64; d <<= 1) c += __shfl_xor(c, d);
+      if (lane == 0) wsum[wv] = c;
+      __syncthreads();
+      uint32_t pos = running, total = 0;
+      for (int x = 0; x < NW; ++x) {
+        if (x < wv) pos += wsum[x];
+        total += wsum[x];
+      }
+      for (int w = wlo; w < wlo + 32 * wg && w < nw; w += 2) {
+        const uint64_t m = (uint64_t)listed(w) | ((uint64_t)listed(w + 1) << 32);
+        const int ww = lane < 32 ? w : (w + 1 < nw ? w + 1 : w);
+        uint32_t mask = 0;
+#pragma unroll
+        for (int p = 0; p < 4; ++p) mask |= ((aw[p * win + ww] >> (lane & 31)) & 1u) << p;
+        if ((m >> lane) & 1ull)
+          E[pos + __popcll(m & ((1ull << lane) - 1ull))] = ((uint32_t)(32 * (w0 + w) + lane + NQB - 1) << 4) | mask;
+        pos += __popcll(m);
+      }
+      running += total;
+      __syncthreads();   // wsum and aw are rewritten by the next window
+    }
+    for (int i = running + tid; i < ent_stride; i += kBlThreads) E[i] = kEntSentinel;
+    if (tid < n_in) { A[(int64_t)tid * n_words + n_words - 1] = 0u; A[(int64_t)tid * n_words + n_words - 2] = running; }
+    return;
+  }
+  const int cnt = s_cnt[h0];
+  const int32_t* const so = s_idx + (int64_t)h0 * a.s_budget;
+  uint32_t before = 0;
   for (int w0 = 0; w0 < n_words - 2; w0 += kBlWin) {
     const int nw = n_words - 2 - w0 < kBlWin ? n_words - 2 - w0 : kBlWin;
     for (int w = tid; w <= nw; w += kBlThreads) aw[w] = w ? 0u : before;
@@ -1230,80 +1572,186 @@ static int attn_sync_blocks(const vs_params& p) {
 }
 static size_t attn_counter_bytes(const vs_params& p) {
   const int64_t n_blk = ceil_div(p.q_start + p.q_len, kBlock);
-  return align_up((size_t)8 * (size_t)ceil_div(n_blk, attn_sync_blocks(p)) * sizeof(uint32_t), 256);
+  const size_t queues = 8 * kQueueStride * sizeof(uint32_t);   // of the key-split kernel, in front
+  return queues + align_up((size_t)8 * (size_t)ceil_div(n_blk, attn_sync_blocks(p)) * sizeof(uint32_t), 256);
 }
-size_t attn_sync_bytes(const vs_params& p) {
-  // counters, then the schedule: 8 rows of at most Hq x (query tiles) group-rounds
+// the schedule: 8 rows of at most Hq x (query tiles) group-rounds
+static size_t attn_sched_bytes(const vs_params& p) {
   const size_t rounds = (size_t)p.n_q_heads * (size_t)ceil_div(p.q_len + p.q_start % kBlock, (int64_t)64 * kAttnQBlocks);
-  return attn_counter_bytes(p) + align_up(8 * rounds * sizeof(int32_t), 256);
+  return align_up(8 * rounds * sizeof(int32_t), 256);
 }
 
-// Key split of short chunks.  With few (query tile, head) units the persistent launch would
-// leave most of the chip idle, each unit walking the whole context alone; the walk is then cut
-// into n_split ranges.  The policy is fixed (512 workgroup slots: 256 compute units x 2), so
-// that workspace sizes do not depend on the device.
+// Key split of short chunks, and of what is left of longer ones when their units do not fill the chip evenly: a launch
+// has 512 workgroup slots (256 compute units x 2; fixed, so that workspace sizes do not depend on the device).
 static std::atomic<int> g_key_split{0};  // 0: automatic, 1: never, n: n ranges (still at least 16 key blocks each)
 void set_attn_key_split(int n) { g_key_split.store(n < 0 ? 0 : (n > 16 ? 16 : n), std::memory_order_relaxed); }
 // dense attention of one token with grouped queries: the heads of a KV group share a tile
 bool attn_packed_decode(const vs_params& p, bool dense) {
   return dense && p.q_len == 1 && p.n_q_heads > p.n_kv_heads && p.n_q_heads / p.n_kv_heads <= 64 * kAttnQBlocks;
 }
-int attn_split(const vs_params& p, bool dense) {
-  const int forced = g_key_split.load(std::memory_order_relaxed);
-  if (forced == 1) return 1;
-  const bool packed = attn_packed_decode(p, dense);
-  const int64_t units = packed ? p.n_kv_heads
-                               : ceil_div(p.q_len + p.q_start % kBlock, (int64_t)64 * kAttnQBlocks) * p.n_q_heads;
+// How a launch is cut: queue false = the pace-keeping kernel, one workgroup per whole unit.  Units rarely fill whole rounds
+// of the 512 slots: what is left over is cut so finely that it takes a fraction of a round (28 heads; before, at most 16
+// ranges and only below 256 units): 5,084 rows at 45K keys, 2.2 rounds, 4.06 -> 3.13 ms; 850 rows at 758K, 0.4 rounds in two
+// ranges, 10.5 -> 8.9; 8,192 rows at 400K, 3.5 rounds, 39.5 -> 35.9; 2,400 rows at 100K 4.94 -> 3.13.  A gain of less than 3 %
+// by the count below is left: full rounds keep pace, which is worth a few per cent at long contexts (launch_attention).
+struct AttnCut {
+  bool queue;
+  int32_t pack, n_hs, n_qtiles, n_units, n_whole, n_split;
+};
+static AttnCut attn_cut(const vs_params& p, bool dense, int forced) {
+  const bool one = attn_packed_decode(p, dense);
+  const int group = p.n_q_heads / p.n_kv_heads, row_pad = (int)(p.q_start % kBlock);
+  AttnCut c = {};
+  c.pack = one || forced == 1 ? 1 : heads_per_tile(p.q_len, row_pad, group);
+  c.n_hs = one ? 1 : (int)ceil_div(group, c.pack);
+  const int64_t n_qtiles = ceil_div(one ? group : p.q_len + row_pad, (int64_t)kTileRows);
+  const int64_t units = n_qtiles * p.n_kv_heads * c.n_hs;
   const int64_t n_blk = ceil_div(p.q_start + p.q_len, kBlock);
-  int64_t s = forced > 1 ? forced : 512 / units;
-  const int64_t cap = packed && forced == 0 ? 128 : 16;  // few units when the heads are packed: more ranges
-  if (s > cap) s = cap;
-  if (s > n_blk / 16) s = n_blk / 16;  // at least 16 key blocks per range
-  return s < 2 ? 1 : (int)s;
-}
-size_t attn_split_bytes(const vs_params& p, bool dense) {
-  const int s = attn_split(p, dense);
-  if (s == 1) return 0;
-  const size_t rows = (size_t)s * p.n_q_heads * (size_t)p.q_len;
-  return align_up(rows * p.head_dim * sizeof(float), 256) + align_up(rows * 2 * sizeof(float), 256);
-}
-
-// out = sum_s O_s 2^(m_s - M) / sum_s l_s 2^(m_s - M), M = max_s m_s; one wave per (row, head),
-// splits folded in ascending order (fixed, so the result is run-to-run identical).
-template <int D, bool BATCH = false>
-__global__ __launch_bounds__(256) void k_attn_combine(const AttnArgs a0) {
-  const int lane = threadIdx.x & 63;
-  const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int h = blockIdx.y;
-  AttnArgs a = a0;
-  if constexpr (BATCH) {
-    if (!batch_view(a0, blockIdx.z, a)) return;
-    if (h >= a.n_q_heads) return;
+  c.n_split = 1;
+  if (forced == 1 || units > kMaxQueueUnits) return c;
+  c.n_qtiles = (int32_t)n_qtiles;
+  c.n_units = (int32_t)units;
+  c.n_whole = 0;
+  if (forced > 1) {
+    c.n_split = (int)(forced < n_blk / 16 ? forced : n_blk / 16);
+    c.queue = c.n_split > 1;
+    if (!c.queue) { c.pack = 1; c.n_hs = group; c.n_split = 1; }
+    return c;
   }
-  if (row >= a.q_rows) return;
-  float M = -INFINITY;
-  for (int sp = 0; sp < a.n_split; ++sp)
-    M = fmaxf(M, a.part_ml[2 * (((int64_t)sp * a.n_q_heads + h) * a.q_rows + row)]);
-  float L = 0.f, acc[D / 64];
-#pragma unroll
-  for (int e = 0; e < D / 64; ++e) acc[e] = 0.f;
-  if (M != -INFINITY) {
-    for (int sp = 0; sp < a.n_split; ++sp) {
-      const int64_t pr = ((int64_t)sp * a.n_q_heads + h) * a.q_rows + row;
-      const float m = a.part_ml[2 * pr];
-      if (m == -INFINITY) continue;
-      const float w = __builtin_amdgcn_exp2f(m - M);
-      L += a.part_ml[2 * pr + 1] * w;
-#pragma unroll
-      for (int e = 0; e < D / 64; ++e) acc[e] += a.part_o[pr * D + 64 * e + lane] * w;
+  // Steps of a whole walk: all key blocks, with index sets too (so that the cut is the same as without them, and with
+  // everything selected the results are)
+  const double steps = (double)n_blk;
+  // Rounds of 512 pieces, in steps.  A piece costs kPieceSteps beside its walk; writing and folding partial results
+  // costs about eight steps per 512 pieces and the second launch three.
+  const int64_t slots = 512;
+  double best = -1.0;
+  for (int drop = 0; drop < 3; ++drop) {
+    int64_t whole = units / slots * slots;
+    if (drop == 1) whole = whole >= slots ? whole - slots : 0;
+    if (drop == 2) whole = 0;
+    const int64_t rest = units - whole;
+    for (int64_t n = 1; n <= kMaxSplit; ++n) {
+      if (n > 1 && (rest == 0 || rest * n > kMaxPieces || steps / (double)n < kMinSteps)) break;
+      const int64_t pieces = rest * n;
+      double cost = (double)(whole / slots) * (steps + kPieceSteps) +
+                    (double)ceil_div(pieces, slots) * (steps / (double)n + kPieceSteps);
+      if (n > 1) cost += 3.0 + 8.0 * (double)pieces / (double)slots;
+      if (best < 0 || cost < best) {
+        best = cost;
+        c.n_whole = (int32_t)whole;
+        c.n_split = (int32_t)n;
+      }
     }
   }
-  const float inv = L > 0.f ? 1.0f / L : 0.f;
-  __bf16* op = a.out + row * a.o_stride_tok + (int64_t)h * a.o_stride_head;
+  if (c.n_split == 1) c.n_whole = c.n_units;
+  c.queue = units <= slots || best < 0.97 * (double)ceil_div(units, slots) * (steps + kPieceSteps);
+  if (!c.queue) { c.pack = 1; c.n_hs = group; c.n_split = 1; }
+  return c;
+}
+static AttnCut attn_cut(const vs_params& p, bool dense) { return attn_cut(p, dense, g_key_split.load(std::memory_order_relaxed)); }
+// Partial results of `ranges` ranges.  Those of the first kOptSplit ranges (as many as the option can ask for) have a place
+// whose size follows the option; those of the further ones, which only the automatic choice makes, one that does not.
+static size_t part_bytes(const vs_params& p, const AttnCut& c, int ranges) {
+  if (!c.queue || c.n_split == 1 || ranges < 1) return 0;
+  const size_t rows = (size_t)(c.n_units - c.n_whole) * ranges * kTileRows;
+  return align_up(rows * p.head_dim * sizeof(float), 256) + align_up(rows * 2 * sizeof(float), 256);
+}
+static int first_ranges(const AttnCut& c) { return c.n_split < kOptSplit ? c.n_split : kOptSplit; }
+size_t attn_split_bytes(const vs_params& p, bool dense) {
+  const AttnCut c = attn_cut(p, dense);
+  return part_bytes(p, c, first_ranges(c));
+}
+// counters, schedule, partial results beyond the first kOptSplit ranges
+size_t attn_sync_bytes(const vs_params& p, bool dense) {
+  const AttnCut c = attn_cut(p, dense, 0);
+  return attn_counter_bytes(p) + attn_sched_bytes(p) + part_bytes(p, c, c.n_split - kOptSplit);
+}
+
+// out = sum_s O_s 2^(m_s - M) / sum_s l_s 2^(m_s - M), M = max_s m_s; D / 4 lanes per row of a tile,
+// pieces folded in ascending order (fixed, so the result is run-to-run identical).
+template <int D, bool BATCH>
+constexpr int combine_rows() { return 1024 / D * (BATCH ? 4 : 1); }   // rows per workgroup (a batch: the plan is read first)
+template <int D, bool BATCH = false>
+__global__ __launch_bounds__(256) void k_attn_combine(const AttnArgs a0) {
+  constexpr int LR = D / 4;            // lanes per row
+  constexpr int WPU = kTileRows / combine_rows<D, BATCH>();  // workgroups per unit
+  int e = blockIdx.x / WPU;
+  const int d = 4 * (threadIdx.x % LR);
+  AttnArgs a = a0;
+  if constexpr (BATCH) {
+    const int lane = threadIdx.x & 63;
+    // the first request whose split units reach beyond e
+    int r = 0;
+    for (int before = 0;; r += 64) {
+      if (r >= a0.n_req) return;
+      const int x = r + lane < a0.n_req ? r + lane : a0.n_req - 1;
+      const BatchPlan p0 = a0.plan[x], p1 = a0.plan[x + 1];
+      int n = r + lane < a0.n_req && p0.n_split > 1 ? (p1.first - p0.first) / p0.n_split : 0;
 #pragma unroll
-  for (int e = 0; e < D / 64; ++e) op[64 * e + lane] = (__bf16)(acc[e] * inv);
-  if (a.lse && lane == 0)
-    a.lse[(int64_t)h * a.q_rows + row] = L > 0.f ? (M + __builtin_amdgcn_logf(L)) * kLn2 : -INFINITY;
+      for (int s = 1; s < 64; s <<= 1) {
+        const int y = __shfl_up(n, s);
+        if (lane >= s) n += y;
+      }
+      const uint64_t beyond = __ballot(before + n > e);
+      if (beyond) {
+        const int at = __builtin_ctzll(beyond);
+        e -= at > 0 ? before + __builtin_amdgcn_readlane(n, at - 1) : before;
+        r += at;
+        break;
+      }
+      before += __builtin_amdgcn_readlane(n, 63);
+    }
+    if (!batch_view(a0, __builtin_amdgcn_readfirstlane(r), a)) return;
+    e = __builtin_amdgcn_readfirstlane(e);
+  }
+  const int n_fold = a.n_units - a.n_whole;
+  if (e >= n_fold) return;
+  int g, h, qt;
+  unit_of(a, a.n_whole + e, g, h, qt);
+  for (int pass = 0; pass < combine_rows<D, BATCH>(); pass += 1024 / D) {
+  // (the row of the tile as k_attention deals them out)
+  const int lrow = (blockIdx.x % WPU) * combine_rows<D, BATCH>() + pass + threadIdx.x / LR;
+  const int wv = lrow >> 5;
+  int t = wv >> 1, th = 0, il0 = (wv & 1) << 5;
+  if (a.pack > 1) {
+    t = 0;
+    th = a.pack == 4 ? wv : wv >> 1;
+    il0 = a.row_pad + (a.pack == 4 ? 0 : il0);
+  }
+  const int64_t row = (int64_t)qt * kTileRows + 64 * t + il0 + (lrow & 31) - a.row_pad;
+  if (row < 0 || row >= a.q_rows || h - g * a.group + th >= a.group) continue;
+  const int hw = h + th;
+  const int64_t at = (int64_t)e * kTileRows + lrow, step = (int64_t)n_fold * kTileRows;
+  const int n_first = BATCH || a.n_split < kOptSplit ? a.n_split : kOptSplit, n_more = a.n_split - n_first;
+  float M = -INFINITY;
+  auto highest = [&](const float* ml, int n) {
+#pragma unroll 4
+    for (int sp = 0; sp < n; ++sp) M = fmaxf(M, ml[2 * (at + step * sp)]);
+  };
+  highest(a.part_ml, n_first);
+  if (!BATCH) highest(a.more_ml, n_more);
+  const float M0 = M == -INFINITY ? 0.f : M;
+  float L = 0.f;
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  auto fold = [&](const float* po, const float* ml, int n) {
+#pragma unroll 4
+    for (int sp = 0; sp < n; ++sp) {
+      const float w = __builtin_amdgcn_exp2f(ml[2 * (at + step * sp)] - M0);   // a piece without live keys: 0, and zeros in its slot
+      const f32x4 o = *(const f32x4*)(po + (at + step * sp) * D + d);
+      L += ml[2 * (at + step * sp) + 1] * w;
+#pragma unroll
+      for (int x = 0; x < 4; ++x) acc[x] += o[x] * w;
+    }
+  };
+  fold(a.part_o, a.part_ml, n_first);
+  if (!BATCH) fold(a.more_o, a.more_ml, n_more);
+  const float inv = L > 0.f ? 1.0f / L : 0.f;
+#pragma unroll
+  for (int x = 0; x < 4; ++x) acc[x] *= inv;
+  *(bf16x4*)(a.out + row * a.o_stride_tok + (int64_t)hw * a.o_stride_head + d) = __builtin_convertvector(acc, bf16x4);
+  if (a.lse && d == 0)
+    a.lse[(int64_t)hw * a.q_rows + row] = L > 0.f ? (M + __builtin_amdgcn_logf(L)) * kLn2 : -INFINITY;
+  }
 }
 
 // Which group takes which group-round.  Heads differ in the length of their block lists (by a
@@ -1388,18 +1836,26 @@ __global__ __launch_bounds__(1024) void k_attn_schedule(const AttnArgs a, int32_
   }
 }
 
-// One list per head (one for all heads when dense); sync_ws: the attention launch's counters, cleared
-// on the way where that launch keeps pace (null: none to clear).
+// One list per head, or per tile of packed heads (one for all heads when dense); attn: for the attention launch with the
+// counters at sync_ws, which are cleared on the way (null: for k_count_tiles, which packs nothing and has none to clear).
 hipError_t launch_build_blocklist(const vs_params& p, const int32_t* s_idx, const int32_t* s_cnt,
                                   bool dense, const BlockList& bl, void* sync_ws, hipStream_t st) {
   const int64_t n_k = p.q_start + p.q_len;
-  const int n_blk = (int)ceil_div(n_k, kBlock);
-  const int n_zero = sync_ws && attn_split(p, dense) == 1 ? (int)(attn_counter_bytes(p) / sizeof(uint32_t)) : 0;
+  AttnCut c = {};
+  if (sync_ws) c = attn_cut(p, dense);
+  ListArgs a = {};
+  a.s_idx = s_idx; a.s_cnt = s_cnt; a.s_budget = p.slash_budget;
+  a.dense = dense;
+  a.n_blk = (int)ceil_div(n_k, kBlock);
+  a.n_words = (int)bl.words; a.ent_stride = (int)bl.ent_stride;
+  a.bm_a = bl.bm_a; a.ent = bl.ent;
+  a.n_heads = p.n_q_heads; a.group = p.n_q_heads / p.n_kv_heads;
+  a.pack = c.queue ? c.pack : 1;
+  a.zero = (uint32_t*)sync_ws;
+  a.n_zero = sync_ws ? (int)(attn_counter_bytes(p) / sizeof(uint32_t)) : 0;
   const unsigned parts = dense ? (unsigned)ceil_div(bl.ent_stride, kBlDensePart) : 1u;
-  hipLaunchKernelGGL((k_build_blocklist<kAttnQBlocks>), dim3(parts, (unsigned)bl.heads), dim3(kBlThreads), 0, st, s_idx,
-                     s_cnt, p.slash_budget, dense ? 1 : 0, n_blk, (int)bl.words, (int)bl.ent_stride, bl.bm_a, bl.ent,
-                     (const vs_request*)nullptr, 1, (int64_t)0, (int64_t)0, (int64_t)0, (uint32_t*)sync_ws,
-                     n_zero);
+  const unsigned lists = dense ? 1u : (unsigned)(p.n_kv_heads * ceil_div(a.group, a.pack));
+  hipLaunchKernelGGL((k_build_blocklist<kAttnQBlocks>), dim3(parts, lists), dim3(kBlThreads), 0, st, a);
   return hipGetLastError();
 }
 
@@ -1484,6 +1940,9 @@ hipError_t launch_attention(const vs_params& p, const void* q, const DcaArgs* dc
   }
   a.n_qtiles = (int)ceil_div(a.q_len, 64 * NQB);
   a.scale_log2 = p.softmax_scale * kLog2e;
+  const AttnCut cut = attn_cut(p, dense);
+  a.pack = cut.pack; a.n_hs = cut.n_hs;
+  a.n_units = cut.n_units; a.n_whole = cut.n_whole;
   // two workgroups fit a compute unit; one persistent workgroup per slot, in 8 groups
   int n_cu = 0;
   {
@@ -1492,48 +1951,67 @@ hipError_t launch_attention(const vs_params& p, const void* q, const DcaArgs* dc
   }
   int members = ((4 / kAttnQBlocks) * n_cu) / 8;   // resident workgroups per XCD
   if (members < 1) members = 1;
-  a.n_split = attn_split(p, dense);
-  a.part_o = a.part_ml = nullptr;
-  if (a.n_split > 1) {
+  a.n_split = cut.n_split;
+  a.part_o = a.part_ml = a.more_o = a.more_ml = nullptr;
+  if (cut.queue && a.n_split > 1) {
     if (!split_ws) return hipErrorInvalidValue;
-    const size_t rows = (size_t)a.n_split * p.n_q_heads * (size_t)p.q_len;  // (packed decode: Hkv x G rows, the same)
+    const size_t rows = (size_t)(a.n_units - a.n_whole) * first_ranges(cut) * kTileRows;
     a.part_o = (float*)split_ws;
     a.part_ml = (float*)((char*)split_ws + align_up(rows * p.head_dim * sizeof(float), 256));
+    if (cut.n_split > kOptSplit) {
+      const size_t more_rows = (size_t)(a.n_units - a.n_whole) * (cut.n_split - kOptSplit) * kTileRows;
+      a.more_o = (float*)((char*)sync_ws + attn_counter_bytes(p) + attn_sched_bytes(p));
+      a.more_ml = (float*)((char*)a.more_o + align_up(more_rows * p.head_dim * sizeof(float), 256));
+    }
   }
-  const int64_t units = (int64_t)a.n_qtiles * a.n_q_heads * a.n_split;
-  if (units < 8 * (int64_t)members) members = (int)ceil_div(units, 8);  // small launches: no idle workgroups
-  a.members = members;
-  a.n_wg = 8 * members;
-  a.n_full = a.n_qtiles / members;
-  a.n_rem = a.n_qtiles - a.n_full * members;
+  a.n_first_slots = (a.n_units - a.n_whole) * first_ranges(cut);
+  a.queue = (uint32_t*)sync_ws;
   a.sync_blocks = attn_sync_blocks(p);
   a.sync_shift = 0;
   while ((1 << (a.sync_shift + 1)) <= a.sync_blocks) ++a.sync_shift;
   a.n_sync = (int)ceil_div(ceil_div(p.q_start + p.q_len, kBlock), a.sync_blocks);
-  a.arrive = (uint32_t*)sync_ws;
-  a.n_gr = a.n_full * a.n_q_heads + (int)ceil_div((int64_t)a.n_rem * a.n_q_heads, a.members);
+  a.arrive = (uint32_t*)sync_ws + 8 * kQueueStride;
   int32_t* const sched = (int32_t*)((char*)sync_ws + attn_counter_bytes(p));
   a.sched = sched;
-  if (a.n_split == 1) hipLaunchKernelGGL(k_attn_schedule, dim3(1), dim3(1024), 0, st, a, sched,
-                                        g_sched_in_turn.load(std::memory_order_relaxed));
-  const dim3 grid((unsigned)a.n_wg), block(128 * NQB);
-  const bool split = a.n_split > 1;
 #define VS_ATTN_LAUNCH(DD, DCA_, SPLIT_) \
-  hipLaunchKernelGGL((k_attention<DD, NQB, DCA_, SPLIT_>), grid, block, attn_lds_bytes<DD>(), st, a)
-  if (p.head_dim == 128) {
-    if (dca && split) VS_ATTN_LAUNCH(128, true, true);
-    else if (dca) VS_ATTN_LAUNCH(128, true, false);
-    else if (split) VS_ATTN_LAUNCH(128, false, true);
-    else VS_ATTN_LAUNCH(128, false, false);
-  } else {
-    if (dca && split) VS_ATTN_LAUNCH(64, true, true);
-    else if (dca) VS_ATTN_LAUNCH(64, true, false);
-    else if (split) VS_ATTN_LAUNCH(64, false, true);
-    else VS_ATTN_LAUNCH(64, false, false);
+  hipLaunchKernelGGL((k_attention<DD, NQB, DCA_, SPLIT_>), dim3((unsigned)a.n_wg), dim3(128 * NQB), attn_lds_bytes<DD>(), st, a)
+  // `units` whole units keeping pace
+  auto keep_pace = [&](int64_t units) {
+    a.members = members;
+    if (units < 8 * (int64_t)members) a.members = (int)ceil_div(units, 8);  // small launches: no idle workgroups
+    a.n_wg = 8 * a.members;
+    a.n_full = a.n_qtiles / a.members;
+    a.n_rem = a.n_qtiles - a.n_full * a.members;
+    const int64_t rounds = (int64_t)a.n_full * a.n_q_heads + ceil_div((int64_t)a.n_rem * a.n_q_heads, a.members);
+    a.n_gr = (int)(ceil_div(units, a.members) < rounds ? ceil_div(units, a.members) : rounds);
+    hipLaunchKernelGGL(k_attn_schedule, dim3(1), dim3(1024), 0, st, a, sched, g_sched_in_turn.load(std::memory_order_relaxed));
+    if (p.head_dim == 128) { if (dca) VS_ATTN_LAUNCH(128, true, false); else VS_ATTN_LAUNCH(128, false, false); }
+    else { if (dca) VS_ATTN_LAUNCH(64, true, false); else VS_ATTN_LAUNCH(64, false, false); }
+  };
+  a.first_piece = 0;
+  if (!cut.queue) {
+    keep_pace((int64_t)a.n_qtiles * a.n_q_heads);
+    return hipGetLastError();
+  }
+  // Long walks keep pace while they are whole, in a launch of their own (where the group of an XCD is as large as a run of
+  // units): 8,192 rows at 400K keys 35.9 ms against 37.3 in one launch, 9,500 clustered ones at 300K 12.8 against 14.0.
+  // Below 256K keys the caches hold what the members of a group are apart, and one launch fills its own gaps: 2,400 rows at
+  // 100K keys 3.44 ms against 3.52, 5,426 clustered ones at 33K 2.31 against 2.46.
+  if (a.n_split > 1 && a.n_whole > 0 && members == kRun && ceil_div(a.n_k, kBlock) >= kPaceBlocks) {
+    keep_pace(a.n_whole);
+    a.first_piece = a.n_whole;
+  }
+  {
+    const int64_t pieces = a.n_whole - a.first_piece + (int64_t)(a.n_units - a.n_whole) * a.n_split;
+    a.members = pieces < 8 * (int64_t)members ? (int)ceil_div(pieces, 8) : members;
+    a.n_wg = 8 * a.members;
+    a.n_full = a.n_rem = a.n_gr = 0;
+    if (p.head_dim == 128) { if (dca) VS_ATTN_LAUNCH(128, true, true); else VS_ATTN_LAUNCH(128, false, true); }
+    else { if (dca) VS_ATTN_LAUNCH(64, true, true); else VS_ATTN_LAUNCH(64, false, true); }
   }
 #undef VS_ATTN_LAUNCH
-  if (split) {
-    const dim3 cgrid((unsigned)ceil_div(a.q_rows, 4), (unsigned)a.n_q_heads);
+  if (a.n_split > 1) {
+    const dim3 cgrid((unsigned)((int64_t)(a.n_units - a.n_whole) * (kTileRows / (1024 / p.head_dim))));
     if (p.head_dim == 128) hipLaunchKernelGGL(k_attn_combine<128>, cgrid, dim3(256), 0, st, a);
     else hipLaunchKernelGGL(k_attn_combine<64>, cgrid, dim3(256), 0, st, a);
   }
@@ -1541,32 +2019,27 @@ hipError_t launch_attention(const vs_params& p, const void* q, const DcaArgs* dc
 }
 
 // ---- several requests per launch ----------------------------------------------------------------
-// p.q_len is the longest request, p.q_start + p.q_len the most keys any request sees.  The number
-// of key ranges is one for the whole batch.  Requests differ in what they cost (and those of a single token leave
-// their slots empty), so there are about four units per workgroup: 8 requests of 1 to 64 rows at 262,144 keys take
-// 1.74 ms, with one unit per workgroup 3.1 ms.
-static int batch_rows_cap(const vs_params& p) {
-  const int G = p.n_q_heads / p.n_kv_heads;
-  return (int)(p.q_len > G ? p.q_len : G);   // a packed single-token request has G rows per KV head
+// p.q_len is the longest request, p.q_start + p.q_len the most keys any request sees.  The host knows only these bounds;
+// the plan is made on the device (write_plan).  About three pieces per workgroup slot: requests differ in what they cost,
+// and a slot takes the next piece when it is done with one: 8 requests of 1 to 64 rows at 262,144 keys 870 us, with one range count
+// for all and fixed places 1,850.
+static int batch_pieces(const vs_params& p, int n_req) {
+  const int64_t group = p.n_q_heads / p.n_kv_heads;
+  const int64_t rows = p.q_len + kBlock - 1 > group ? p.q_len + kBlock - 1 : group;   // (single tokens: heads as rows)
+  const int64_t units = (int64_t)n_req * p.n_q_heads * ceil_div(rows, (int64_t)kTileRows);
+  const int64_t n_blk = ceil_div(p.q_start + p.q_len, kBlock) + 8 * ceil_div(p.vertical_budget, 64);
+  int64_t n = n_blk / kMinSteps;
+  n = n < 1 ? 1 : (n > kMaxSplit ? kMaxSplit : n);
+  return (int)(units * n < kBatchPieces ? units * n : kBatchPieces);
 }
-static int batch_tiles(const vs_params& p) { return (int)ceil_div(p.q_len + kBlock - 1, (int64_t)64 * kAttnQBlocks); }
-int attn_batch_split(const vs_params& p, int n_req) {
-  // (a single-token request whose heads are packed into rows turns its G head slots into G times as
-  // many key ranges, so the count of unit slots is the same for every kind of request)
-  const int64_t units = (int64_t)n_req * p.n_q_heads * batch_tiles(p);
-  const int64_t n_blk = ceil_div(p.q_start + p.q_len, kBlock);
-  int64_t s = 2048 / units;
-  const int64_t cap = 16;
-  if (s > cap) s = cap;
-  if (s > n_blk / 16) s = n_blk / 16;
-  return s < 1 ? 1 : (int)s;
-}
+static size_t plan_bytes(int n_req) { return align_up((size_t)(n_req + 1) * sizeof(BatchPlan), 256); }
 size_t attn_batch_bytes(const vs_params& p, int n_req) {
   const int64_t n_k = p.q_start + p.q_len;
   const size_t lists = (size_t)n_req * p.n_q_heads;
-  const size_t rows = (size_t)n_req * attn_batch_split(p, n_req) * p.n_q_heads * (size_t)batch_rows_cap(p);
+  const size_t rows = (size_t)batch_pieces(p, n_req) * kTileRows;
   return align_up(lists * (size_t)bitmap_words(n_k) * 4, 256) + align_up(lists * (size_t)entry_stride(n_k) * 4, 256) +
-         align_up(rows * p.head_dim * sizeof(float), 256) + align_up(rows * 2 * sizeof(float), 256) + 256;
+         align_up(rows * p.head_dim * sizeof(float), 256) + align_up(rows * 2 * sizeof(float), 256) +
+         align_up(8 * kQueueStride * sizeof(uint32_t), 256) + plan_bytes(n_req);
 }
 
 hipError_t launch_attention_batch(const vs_params& p, const vs_request* req, int n_req, bool skip_single, void* ws,
@@ -1575,31 +2048,27 @@ hipError_t launch_attention_batch(const vs_params& p, const vs_request* req, int
   const int64_t n_k = p.q_start + p.q_len;
   const size_t lists = (size_t)n_req * p.n_q_heads;
   const int64_t words = bitmap_words(n_k), ent_stride = entry_stride(n_k);
+  const int pieces = batch_pieces(p, n_req);
   char* w = (char*)ws;
-  uint32_t* bm_a = (uint32_t*)w;
-  w += align_up(lists * (size_t)words * 4, 256);
-  uint32_t* ent = (uint32_t*)w;
-  w += align_up(lists * (size_t)ent_stride * 4, 256);
+  auto take = [&](size_t bytes) { char* x = w; w += align_up(bytes, 256); return (void*)x; };
   AttnArgs a = {};
-  a.n_split = attn_batch_split(p, n_req);
-  a.rows_cap = batch_rows_cap(p);
-  const size_t rows = (size_t)n_req * a.n_split * p.n_q_heads * (size_t)a.rows_cap;
-  a.part_o = (float*)w;
-  w += align_up(rows * p.head_dim * sizeof(float), 256);
-  a.part_ml = (float*)w;
-  w += align_up(rows * 2 * sizeof(float), 256);
-  a.arrive = (uint32_t*)w;   // unused by the key-split kernel; one valid word
+  a.bm_a = (uint32_t*)take(lists * (size_t)words * 4);
+  a.ent = (uint32_t*)take(lists * (size_t)ent_stride * 4);
+  a.part_o = (float*)take((size_t)pieces * kTileRows * p.head_dim * sizeof(float));
+  a.part_ml = (float*)take((size_t)pieces * kTileRows * 2 * sizeof(float));
+  a.queue = (uint32_t*)take(8 * kQueueStride * sizeof(uint32_t));
+  BatchPlan* const plan = (BatchPlan*)take(plan_bytes(n_req));
+  a.plan = plan;
+  a.arrive = a.queue;   // unused by the key-split kernel; one valid word
   a.n_sync = 1; a.sync_blocks = 1 << 30; a.sync_shift = 30; a.sched = nullptr; a.n_gr = 0;
   a.q_stride_tok = p.q_stride_tok; a.q_stride_head = p.q_stride_head;
   a.k_stride_tok = p.k_stride_tok; a.k_stride_head = p.k_stride_head;
   a.v_stride_tok = p.v_stride_tok; a.v_stride_head = p.v_stride_head;
   a.o_stride_tok = p.o_stride_tok; a.o_stride_head = p.o_stride_head;
-  a.bm_a = bm_a; a.ent = ent;
   a.bm_stride = words; a.bm_words = (int32_t)words;
   a.ent_stride = ent_stride; a.ent_len = ent_stride;
   a.v_budget = p.vertical_budget;
   a.n_q_heads = p.n_q_heads; a.n_kv_heads = p.n_kv_heads; a.group = p.n_q_heads / p.n_kv_heads;
-  a.n_qtiles = batch_tiles(p);
   a.n_k = n_k;
   a.scale_log2 = p.softmax_scale * kLog2e;
   a.req = req; a.n_req = n_req; a.head_dim = p.head_dim;
@@ -1608,16 +2077,20 @@ hipError_t launch_attention_batch(const vs_params& p, const vs_request* req, int
   int n_cu = 0;
   hipError_t e = attn_device_setup(&n_cu);
   if (e != hipSuccess) return e;
-  const int64_t units = (int64_t)n_req * a.n_q_heads * a.n_qtiles * a.n_split;
   int members = ((4 / kAttnQBlocks) * n_cu) / 8;   // resident workgroups per XCD
   if (members < 1) members = 1;
-  if (units < 8 * (int64_t)members) members = (int)ceil_div(units, 8);
   a.members = members; a.n_wg = 8 * members; a.n_full = 0; a.n_rem = 0;
-  hipLaunchKernelGGL((k_build_blocklist<NQB>), dim3(1, (unsigned)lists), dim3(kBlThreads), 0, st, (const int32_t*)nullptr,
-                     (const int32_t*)nullptr, p.slash_budget, 0, 0, (int)words, (int)ent_stride, bm_a, ent, req,
-                     (int)p.n_q_heads, (int64_t)(skip_single ? 2 : 1), (int64_t)p.q_len, n_k, (uint32_t*)nullptr, 0);
+  ListArgs l = {};
+  l.s_budget = p.slash_budget;
+  l.n_words = (int)words; l.ent_stride = (int)ent_stride;
+  l.bm_a = (uint32_t*)a.bm_a; l.ent = (uint32_t*)a.ent;
+  l.n_heads = p.n_q_heads; l.group = a.group; l.pack = 1;
+  l.zero = a.queue; l.n_zero = 8 * kQueueStride;
+  l.req = req; l.plan = plan; l.n_req = n_req; l.skip_single = skip_single; l.pieces = pieces;
+  l.max_q_len = p.q_len; l.max_n_k = n_k;
+  hipLaunchKernelGGL((k_build_blocklist<NQB>), dim3(1, (unsigned)lists + 1), dim3(kBlThreads), 0, st, l);
   const dim3 grid((unsigned)a.n_wg), block(128 * NQB);
-  const dim3 cgrid((unsigned)ceil_div(a.rows_cap, 4), (unsigned)a.n_q_heads, (unsigned)n_req);
+  const dim3 cgrid((unsigned)(ceil_div(pieces, 2) * (kTileRows / (4096 / p.head_dim))));   // split units: two pieces or more
   if (p.head_dim == 128) {
     hipLaunchKernelGGL((k_attention<128, NQB, false, true, true>), grid, block, attn_lds_bytes<128>(), st, a);
     hipLaunchKernelGGL((k_attn_combine<128, true>), cgrid, dim3(256), 0, st, a);

@@ -1,0 +1,89 @@
+"""The ways the tile kernel cuts a launch into units and pieces: heads that share a tile (rows of one query block, at every
+place in it and at 32 / 33 rows, where two or four heads fit), whole units next to cut ones (with and without pace
+keeping), and plans over batches of more requests than a wave, and than a workgroup, looks at in one go.  Against the fp64
+oracle, at the largest sizes on a sample of rows."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2501_15383_amd as vs
+from gpu_util import assert_attn_close, chunk_of, dev
+from helpers import rand_bf16
+from test_gpu_attention import _rand_sets, _t
+from test_gpu_batch import _check, _make_requests, _run_batch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("hq,hkv,d", [(7, 1, 128), (6, 3, 64), (5, 1, 64), (3, 3, 128)])
+@pytest.mark.parametrize("c,place", [(2, 0), (31, 33), (32, 32), (32, 33), (33, 31), (33, 0), (63, 1), (64, 0)])
+@pytest.mark.parametrize("blocks", [1, 40, 70])   # key blocks before the chunk's: one range, a few, a second batch of entries
+def test_heads_that_share_a_tile(hq, hkv, d, c, place, blocks):
+    s = 64 * blocks + place
+    rng = np.random.default_rng(3000 + s + c)
+    q = rand_bf16(rng, (c, hq, d)); k = rand_bf16(rng, (s + c, hkv, d)); v = rand_bf16(rng, (s + c, hkv, d))
+    pb = oracle.Problem(hq, hkv, d, c, s, 1.0 / np.sqrt(d), vertical_budget=160, slash_budget=90, keep_first_cols=0, keep_local_band=0)
+    ref = oracle.dense_attention(pb, q, k, v)
+    got = vs.dense_causal_prefill(chunk_of(pb), dev(q), dev(k), dev(v), want_lse=True)
+    torch.cuda.synchronize()
+    assert_attn_close(*got, *ref, f"dense {hq}/{hkv} C={c} s={s}")
+    for nv, ns in ((150, 6), (65, 0), (0, 20)):   # no diagonal, no column: rows without any key among them
+        sets = _rand_sets(rng, pb, nv, ns)
+        for h in range(0, hq, 2):   # heads of a tile with lists of different lengths
+            keep = int(sets[1][h]) // 2
+            sets[0][h, keep:] = -1; sets[1][h] = keep
+        ref = oracle.sparse_attention(pb, q, k, v, *sets)
+        got = vs.sparse_attn_prefill(chunk_of(pb), dev(q), dev(k), dev(v), *[_t(x) for x in sets], want_lse=True)
+        torch.cuda.synchronize()
+        assert_attn_close(*got, *ref, f"sparse {hq}/{hkv} C={c} s={s} {nv} columns {ns} offsets")
+
+
+@pytest.mark.parametrize("c,s", [(66 * 128 - 5, 70), (66 * 128 - 5, 4100 * 64 + 1)])   # 528 units: 512 whole, 16 cut
+def test_whole_units_and_cut_ones(c, s):
+    hq, hkv, d = 8, 1, 64
+    rng = np.random.default_rng(3100)
+    q = rand_bf16(rng, (c, hq, d)); k = rand_bf16(rng, (s + c, hkv, d)); v = rand_bf16(rng, (s + c, hkv, d))
+    pb = oracle.Problem(hq, hkv, d, c, s, 1.0 / np.sqrt(d), vertical_budget=300, slash_budget=400)
+    out, lse = vs.dense_causal_prefill(chunk_of(pb), dev(q), dev(k), dev(v), want_lse=True)
+    sets = _rand_sets(rng, pb, 290, 300, force_cols=[0], force_offs=range(64))
+    out_s, lse_s = vs.sparse_attn_prefill(chunk_of(pb), dev(q), dev(k), dev(v), *[_t(x) for x in sets], want_lse=True)
+    torch.cuda.synchronize()
+    # rows of the first, of the last whole and of the cut tiles
+    for rows in ([0, 57, 58, 191], [c - 1, c - 128, c // 2]):
+        at = torch.tensor(rows, device="cuda")
+        ref = oracle.dense_attention(pb, q, k, v, rows=rows)
+        assert_attn_close(out[at], lse[:, at], *ref, f"dense C={c} s={s} rows {rows}")
+        ref = oracle.sparse_attention(pb, q, k, v, *sets, rows=rows)
+        assert_attn_close(out_s[at], lse_s[:, at], *ref, f"sparse C={c} s={s} rows {rows}")
+    # all rows against the kernel that cuts nothing: both within the rounding of bf16 probabilities and outputs
+    vs.set_option(vs.VS_OPT_ATTN_KEY_SPLIT, 1)
+    try:
+        p, lp = vs.dense_causal_prefill(chunk_of(pb), dev(q), dev(k), dev(v), want_lse=True)
+        ps, lps = vs.sparse_attn_prefill(chunk_of(pb), dev(q), dev(k), dev(v), *[_t(x) for x in sets], want_lse=True)
+        torch.cuda.synchronize()
+    finally:
+        vs.set_option(vs.VS_OPT_ATTN_KEY_SPLIT, 0)
+    for a, b, la, lb in ((out, p, lse, lp), (out_s, ps, lse_s, lps)):
+        a, b = a.float(), b.float()
+        assert ((a - b).norm(dim=2) <= 2e-2 * b.norm(dim=2)).all() and (la - lb).abs().max().item() < 1e-4
+
+
+@pytest.mark.parametrize("n_req", [70, 1030])
+def test_plans_over_many_requests(n_req):
+    hq, hkv, d, bv, bs = 4, 2, 64, 40, 90
+    rng = np.random.default_rng(3200 + n_req)
+    specs = [(int(rng.integers(2, 5)), int(rng.integers(0, 150)), bool(i % 3 == 0)) for i in range(n_req)]
+    specs[n_req // 2] = (130, 9000, False)   # one that is cut, between short ones
+    specs[-1] = (40, 5000, True)
+    reqs = _make_requests(rng, hq, hkv, d, specs, bv, bs)
+    skipped = n_req // 2 + 1
+
+    def poison(table):
+        table[skipped, 2] = 0   # no values: skipped, between two that are taken
+    a = _run_batch(reqs, hq, hkv, d, bv, bs, poison=poison)
+    b = _run_batch(reqs, hq, hkv, d, bv, bs, poison=poison)
+    for x, y in zip(a, b):
+        assert torch.equal(x["out"].view(torch.int16), y["out"].view(torch.int16)) and torch.equal(x["lse"], y["lse"])
+    assert (a[skipped]["out"].float() == -3.0).all() and (a[skipped]["lse"] == 7.0).all()
+    _check(reqs, a, skip=(skipped,))
