@@ -3,21 +3,12 @@
 // tokens of each chunk).  For the W' <= 64 window rows of every head: causal softmax rows
 // over all n_k keys, summed along columns (vscore) and along diagonals pos - j (sscore).
 //
-// Two sweeps over the K cache, both tiled the same way: a workgroup owns one KV head and a
-// contiguous range of keys; a wave is (query head of that KV group, half of the window rows),
-// so every K tile is fetched from HBM once per sweep for all heads of the group and staged
-// in LDS (two buffers, one barrier per tile).
-//   sweep A  per-row running (max, sum) over the range -> partials -> k_estimate_combine -> lse
-//   sweep B  P = exp2(S * scale*log2e - lse2).  Column sums: the wave of the upper half hands
-//            its sums to the wave of the lower half through LDS, which stores them (a column
-//            belongs to exactly one workgroup).  Diagonal sums of every 32 x 32 block come
-//            from lane rotations and are collected in an LDS strip private to the wave; the
-//            two strips of a head are added to the zero-filled global array at the end (at
-//            most two workgroups touch one offset, and x + y is commutative), so scores are
-//            run-to-run identical.
-// bf16 MFMA (32x32x16) with fp32 accumulation; sweep A uses the K Q^T orientation (a lane
-// owns one query), sweep B the Q K^T orientation (a lane owns one key).  Both sweeps are
-// bound by the exponential (one per score, quarter rate), not by memory.
+// Two sweeps over the K cache (each reads it once for all heads of a KV group):
+//   sweep A  per-row running (max, sum) over a range of keys -> partials -> k_estimate_combine -> lse
+//   sweep B  P = exp2(S * scale*log2e - lse2), summed along columns and diagonals; run-to-run identical
+// bf16 MFMA (32x32x16) with fp32 accumulation; sweep A uses the K Q^T orientation (a lane owns one query), sweep B the Q K^T
+// orientation (a lane owns one key).  k_est_sums / k_est_scores are the sweeps of ordinary calls, k_estimate those of Dual
+// Chunk Attention, whose rotations change from tile to tile.
 #include <type_traits>
 
 #include "vs_common.h"
@@ -49,8 +40,15 @@ struct EstArgs {
   float scale_log2;
 };
 
-template <int D, int NH, int PASS, bool DCA>
-__global__ __launch_bounds__(128 * NH, DCA ? 1 : 4) void k_estimate(const EstArgs a) {
+// The sweeps of Dual Chunk Attention: a workgroup owns one KV head and a contiguous range of keys; a wave is (query head of that
+// KV group, half of the window rows), so every K tile is fetched from HBM once per sweep for all heads of the group and staged
+// in LDS (two buffers, one barrier per tile).  Sweep B: the wave of the upper half hands its column sums to the wave of the lower
+// half through LDS, which stores them (a column belongs to exactly one workgroup).  Diagonal sums of every 32 x 32 block come
+// from lane rotations and are collected in an LDS strip private to the wave; the two strips of a head are added to the
+// zero-filled global array at the end (at most two workgroups touch one offset, and x + y is commutative).
+template <int D, int NH, int PASS>
+__global__ __launch_bounds__(128 * NH, 1) void k_estimate(const EstArgs a) {
+  constexpr bool DCA = true;
   constexpr int NW = 2 * NH, NT = 64 * NW, KS = D + 8, DCH = D / 8, DSTEPS = D / 16;
   constexpr int KPT = (64 * DCH + NT - 1) / NT;
   constexpr int STRIP = kEstRange + 64;
@@ -343,6 +341,268 @@ __global__ __launch_bounds__(128 * NH, DCA ? 1 : 4) void k_estimate(const EstArg
   }
 }
 
+// ---- the two sweeps, one rotation of the queries (everything but Dual Chunk Attention) ------------------------------------
+// A wave holds the K rows of 64 keys in registers, as MFMA operands straight from memory, and takes the query heads of the KV
+// group one after the other; the window rows of all of them wait in LDS.  So K is read once per sweep, nothing is staged and
+// there is no barrier on the way.
+// Bound: issue cycles.  On this chip the cycles of the vector instructions and those of the matrix products add up (counters:
+// 61 % + 39 % of sweep A, 76 % + 33 % of sweep B), whatever the order they are issued in: the next block's product interleaved
+// with this one's exponentials by hand, two or three waves per SIMD and more registers, was 5 to 20 % slower.  Per 64 scores there
+// are 16 cycles of MFMA, in sweep A fma, exp, add and half a max, in sweep B half a lane swap, fma, exp and five more (column
+// sum, diagonals).  1M keys, 28 query / 4 KV heads of 128: sweep A 590 us, sweep B 740, 1.38 ms with everything; with the K tiles
+// in LDS, a barrier per tile, 32 rows per wave, the diagonals turned by LDS lane exchanges and a pass that cleared the scores
+// 640 + 950, 1.63.  Small calls are cut finer: 8,192 keys 77 us -> 45.
+constexpr int kEstWaves = 16;    // waves per workgroup (4 where it takes one or two heads): four per SIMD, 128 registers
+
+struct EstShape {
+  int32_t heads;     // query heads per workgroup
+  int32_t n_hb;      // workgroups per (key range, KV head)
+  int32_t waves;     // per workgroup
+  int32_t tiles;     // 64-key tiles per wave
+  int32_t n_blocks;  // workgroups along the keys
+};
+
+// what a workgroup of either sweep is: its KV head, heads, and the tiles of its waves.  The n_hb workgroups of one (key range,
+// KV head) are placed on one XCD (blockIdx b and b + 8), so that the second finds the K rows in that XCD's L2.
+struct EstPlace {
+  int g, h0, n_h, blk;
+  bool ok;
+};
+__device__ __forceinline__ EstPlace est_place(const EstArgs& a, const EstShape& z) {
+  EstPlace p;
+  const int b = blockIdx.x, unit = (b / (8 * z.n_hb)) * 8 + (b & 7), hb = (b >> 3) % z.n_hb;
+  p.ok = unit < z.n_blocks * a.n_kv_heads;
+  p.blk = unit % z.n_blocks;
+  p.g = unit / z.n_blocks;
+  p.h0 = p.g * a.group + hb * z.heads;
+  p.n_h = a.group - hb * z.heads < z.heads ? a.group - hb * z.heads : z.heads;
+  return p;
+}
+// window rows of n_h heads into LDS: row r of head x at (64 x + r) D, its 16-byte piece c in slot c ^ ((r / R) % DCH)
+template <int D>
+__device__ __forceinline__ void est_load_q(const EstArgs& a, const EstPlace& p, __bf16* qs) {
+  constexpr int DCH = D / 8, R = 128 / D;
+  for (int x = threadIdx.x; x < p.n_h * 64 * DCH; x += blockDim.x) {
+    const int c = x % DCH, r = (x / DCH) & 63, hd = x / (64 * DCH);
+    const int rw = r < a.wp ? r : a.wp - 1;
+    const __bf16* qp = a.q + (a.q_len - a.wp + rw) * a.q_stride_tok + (int64_t)(p.h0 + hd) * a.q_stride_head + 8 * c;
+    *(u32x4*)&qs[(64 * hd + r) * D + ((c ^ ((r / R) % DCH)) * 8)] = *(const u32x4*)qp;
+  }
+}
+// K rows j0 .. j0 + 63 as MFMA operands: lane (row 32 jb + lane % 32, 8 elements from 16 st + 8 hh)
+template <int D>
+__device__ __forceinline__ void est_load_k(const EstArgs& a, int g, int64_t j0, int lane, bf16x8 (&kf)[2][D / 16]) {
+#pragma unroll
+  for (int jb = 0; jb < 2; ++jb) {
+    int64_t j = j0 + 32 * jb + (lane & 31);
+    if (j > a.n_k - 1) j = a.n_k - 1;
+    const __bf16* kp = a.k + (int64_t)g * a.k_stride_head + j * a.k_stride_tok + 8 * (lane >> 5);
+#pragma unroll
+    for (int st = 0; st < D / 16; ++st) kf[jb][st] = *(const bf16x8*)(kp + 16 * st);
+  }
+}
+
+// mul(st, operand) for the MFMA steps of window rows 32 x .. 32 x + 31 of the workgroup's heads
+template <int D, typename Mul>
+__device__ __forceinline__ void est_product(const __bf16* qs, int x, int lane, Mul&& mul) {
+  constexpr int DCH = D / 8, R = 128 / D;
+  const __bf16* const qr = qs + (32 * x + (lane & 31)) * D;
+  const int sw = (lane >> 5) ^ (((lane & 31) / R) % DCH);
+#pragma unroll
+  for (int st = 0; st < D / 16; ++st) {
+    mul(st, *(const bf16x8*)(qr + ((2 * st) ^ sw) * 8));
+    if (st & 1) __builtin_amdgcn_sched_barrier(0);   // two operands at a time: the registers are full of K
+  }
+}
+
+// Sweep A: (max, sum) of every window row over the workgroup's keys.  K Q^T: a lane owns a query row (32 x + lane % 32 of row
+// block x) and half of the keys; its state lies in LDS between the tiles.
+template <int D>
+__global__ __launch_bounds__(64 * kEstWaves) void k_est_sums(const EstArgs a, const EstShape z, const int tiles_b) {
+  constexpr int DSTEPS = D / 16;
+  extern __shared__ __attribute__((aligned(16))) unsigned char est_lds[];
+  __bf16* const qs = (__bf16*)est_lds;
+  float2* const state = (float2*)(qs + z.heads * 64 * D);   // [wave][row block][64]
+  const EstPlace p = est_place(a, z);
+  if (!p.ok) return;
+  const int tid = threadIdx.x, lane = tid & 63, hh = lane >> 5;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  est_load_q<D>(a, p, qs);
+  float2* const mine = state + wv * 2 * z.heads * 64 + lane;
+  for (int x = 0; x < 2 * p.n_h; ++x) mine[64 * x] = make_float2(-INFINITY, 0.f);
+  __syncthreads();
+  const int n_tiles = (int)((a.n_k + 63) >> 6);
+  const int t0 = (p.blk * z.waves + wv) * z.tiles, t1 = t0 + z.tiles < n_tiles ? t0 + z.tiles : n_tiles;
+  for (int t = t0; t < t1; ++t) {
+    const int64_t j0 = 64 * (int64_t)t;
+    bf16x8 kf[2][DSTEPS];
+    est_load_k<D>(a, p.g, j0, lane, kf);
+    // sweep B adds two parts to the offsets of a wave's first tile, and to those behind the last one: cleared here
+    auto clear = [&](int tile) {
+      const int64_t o = a.p0 + 63 - 64 * (int64_t)tile - lane;
+      if (o >= 0 && o < a.n_k)
+        for (int x = 0; x < p.n_h; ++x) a.sscore[(int64_t)(p.h0 + x) * a.n_k + o] = 0.f;
+    };
+    if (t % tiles_b == 0) clear(t);
+    if (t == n_tiles - 1) clear(n_tiles);
+    const bool causal = j0 + 63 > a.p0;   // some (row, key) of this tile is acausal
+    for (int x = 0; x < 2 * p.n_h; ++x) {
+      f32x16 s[2];
+#pragma unroll
+      for (int jb = 0; jb < 2; ++jb)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) s[jb][e] = 0.f;
+      const float2 st = mine[64 * x];
+      est_product<D>(qs, x, lane, [&](int k, bf16x8 qf) {
+        s[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[0][k], qf, s[0], 0, 0, 0);
+        s[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[1][k], qf, s[1], 0, 0, 0);
+      });
+      if (causal) {
+        // element e of jb is key 32 jb + 8 (e/4) + 4 hh + (e%4); it is masked for row r iff j - p0 > r
+        const int dr = 32 * (x & 1) + (lane & 31) - (int)(j0 - a.p0) - 4 * hh;
+#pragma unroll
+        for (int jb = 0; jb < 2; ++jb)
+#pragma unroll
+          for (int e = 0; e < 16; ++e)
+            if (32 * jb + 8 * (e >> 2) + (e & 3) > dr) s[jb][e] = -INFINITY;
+      }
+      float mx = fmaxf(s[0][0], s[1][0]);
+#pragma unroll
+      for (int e = 1; e < 16; ++e) mx = fmaxf(fmaxf(mx, s[0][e]), s[1][e]);
+      const float m_new = fmaxf(st.x, mx * a.scale_log2);
+      const float m_use = (m_new == -INFINITY) ? 0.f : m_new;
+      float acc0 = st.y * __builtin_amdgcn_exp2f(st.x - m_use), acc1 = 0.f;
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        acc0 += __builtin_amdgcn_exp2f(__builtin_fmaf(s[0][e], a.scale_log2, -m_use));
+        acc1 += __builtin_amdgcn_exp2f(__builtin_fmaf(s[1][e], a.scale_log2, -m_use));
+      }
+      mine[64 * x] = make_float2(m_new, acc0 + acc1);
+    }
+  }
+  __syncthreads();
+  // the waves and key halves of a row folded in a fixed order: one partial per (head, workgroup, row)
+  for (int x = tid; x < 64 * p.n_h; x += blockDim.x) {
+    const int rb = x >> 5, r = x & 31;
+    const float2* const col = state + rb * 64 + r;
+    float M = -INFINITY, L = 0.f;
+    for (int w = 0; w < z.waves; ++w) M = fmaxf(M, fmaxf(col[w * 2 * z.heads * 64].x, col[w * 2 * z.heads * 64 + 32].x));
+    const float Mu = (M == -INFINITY) ? 0.f : M;
+    for (int w = 0; w < z.waves; ++w) {
+      const float2 u = col[w * 2 * z.heads * 64], v = col[w * 2 * z.heads * 64 + 32];
+      L += u.y * __builtin_amdgcn_exp2f(u.x - Mu) + v.y * __builtin_amdgcn_exp2f(v.x - Mu);
+    }
+    float* const pp = a.part + (((int64_t)(p.h0 + (rb >> 1)) * a.n_ranges + p.blk) * 64 + (x & 63)) * 2;
+    pp[0] = M;
+    pp[1] = L;
+  }
+}
+
+// Sweep B: P = exp2(S scale_log2 - lse2), summed along columns and diagonals.  Q K^T, and the two blocks of 32 keys swapped
+// by half-waves: a register then is one window row, its 64 lanes the tile's 64 keys.  A column sum is a plain sum over the
+// registers.  A diagonal moves on by one lane from row to row, so its sum is an add with a lane rotation per row:
+//   acc <- rotate(acc, 1) + P[q],   q = 0 .. 63
+// after which lane f holds the offset p0 + 63 - (j0 + f), all in one register.  What lies right of the tile's own diagonal
+// (lanes > q) wraps around and belongs to the next tile's offsets; it is summed by itself and waits in LDS for the next tile
+// of the wave.  (One sum over everything and a subtraction would be a select less, but off by a rounding of the larger part.)  Offsets at the seam of two waves get their two parts by atomic adds (cleared by
+// sweep A; x + y is commutative, so scores are run-to-run identical).
+template <int D>
+__global__ __launch_bounds__(64 * kEstWaves) void k_est_scores(const EstArgs a, const EstShape z) {
+  constexpr int DSTEPS = D / 16;
+  extern __shared__ __attribute__((aligned(16))) unsigned char est_lds[];
+  __bf16* const qs = (__bf16*)est_lds;
+  const EstPlace p = est_place(a, z);
+  if (!p.ok) return;
+  const int tid = threadIdx.x, lane = tid & 63, hh = lane >> 5;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  float* const carry = (float*)(qs + z.heads * 64 * D) + wv * z.heads * 64 + lane;   // [wave][head][64]
+  est_load_q<D>(a, p, qs);
+  __syncthreads();
+  const int n_tiles = (int)((a.n_k + 63) >> 6);
+  const int t0 = (p.blk * z.waves + wv) * z.tiles, t1 = t0 + z.tiles < n_tiles ? t0 + z.tiles : n_tiles;
+  float c = a.scale_log2;
+  asm("" : "+v"(c));   // (one scalar operand per instruction, and that is the row's lse2)
+  auto rotate = [](float v) -> float {   // lane f takes lane f - 1's value
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x13C, 0xF, 0xF, false));
+  };
+  for (int t = t0; t < t1; ++t) {
+    const int64_t j0 = 64 * (int64_t)t;
+    bf16x8 kf[2][DSTEPS];
+    est_load_k<D>(a, p.g, j0, lane, kf);
+    const int64_t o = a.p0 + 63 - j0 - lane;
+    const bool causal = j0 + 63 > a.p0;
+    for (int x = 0; x < p.n_h; ++x) {
+      const int h = __builtin_amdgcn_readfirstlane(p.h0 + x);
+      float col[2] = {0.f, 0.f}, own = 0.f, over = 0.f;
+      uint64_t right = ~1ull;   // lanes > q; opaque, or the compiler keeps 64 of them in scalar registers
+      asm("" : "+s"(right));
+      // (the scalar cache: the rows are the same in every lane)
+      typedef const __attribute__((address_space(4))) float* const_ptr;
+      const const_ptr lse = (const_ptr)(a.lse2 + (int64_t)h * 64);
+#pragma clang loop unroll(disable)
+      for (int half = 0; half < 2; ++half) {
+        f32x16 s[2];
+#pragma unroll
+        for (int jb = 0; jb < 2; ++jb)
+#pragma unroll
+          for (int e = 0; e < 16; ++e) s[jb][e] = 0.f;
+        est_product<D>(qs, 2 * x + half, lane, [&](int k, bf16x8 qf) {
+          s[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf, kf[0][k], s[0], 0, 0, 0);
+          s[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf, kf[1][k], s[1], 0, 0, 0);
+        });
+        if (causal) {
+          // element e is row 32 half + 8 (e/4) + 4 hh + (e%4), the lane key 32 jb + lane % 32; masked iff j - p0 > row
+          const int dj = (int)(j0 - a.p0) + (lane & 31) - 4 * hh - 32 * half;
+#pragma unroll
+          for (int jb = 0; jb < 2; ++jb)
+#pragma unroll
+            for (int e = 0; e < 16; ++e)
+              if (dj + 32 * jb > 8 * (e >> 2) + (e & 3)) s[jb][e] = -INFINITY;
+        }
+#pragma unroll
+        for (int e4 = 0; e4 < 4; ++e4) {
+          // rows 8 e4 + 0..3 of the half in s[0], rows 8 e4 + 4..7 in s[1] after the swap
+#pragma unroll
+          for (int e = 4 * e4; e < 4 * e4 + 4; ++e) {
+            const float x0 = s[0][e], x1 = s[1][e];
+            const auto w = __builtin_amdgcn_permlane32_swap(__float_as_uint(x0), __float_as_uint(x1), false, false);
+            const uint32_t w0 = w[0], w1 = w[1];
+            s[0][e] = __uint_as_float(w0);
+            s[1][e] = __uint_as_float(w1);
+          }
+#pragma unroll
+          for (int k = 0; k < 2; ++k)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              const int q = 32 * half + 8 * e4 + 4 * k + e;
+              const float pr = __builtin_amdgcn_exp2f(__builtin_fmaf(s[k][4 * e4 + e], c, -lse[q]));
+              const bool next = __builtin_amdgcn_inverse_ballot_w64(right);
+              col[q & 1] += pr;
+              own = rotate(own) + (next ? 0.f : pr);
+              over = rotate(over) + (next ? pr : 0.f);
+              right <<= 1;
+            }
+        }
+      }
+      float* const so = a.sscore + (int64_t)h * a.n_k + o;
+      const bool in = o >= 0 && o < a.n_k;
+      if (t == t0) {
+        if (in) atomicAdd(so, own);
+      } else {
+        own += carry[64 * x];
+        if (in) *so = own;
+      }
+      carry[64 * x] = over;
+      if (j0 + lane < a.n_k) a.vscore[(int64_t)h * a.n_k + j0 + lane] = col[0] + col[1];
+    }
+  }
+  if (t0 < t1) {
+    const int64_t o = a.p0 + 63 - 64 * (int64_t)t1 - lane;
+    if (o >= 0 && o < a.n_k)
+      for (int x = 0; x < p.n_h; ++x) atomicAdd(&a.sscore[(int64_t)(p.h0 + x) * a.n_k + o], carry[64 * x]);
+  }
+}
+
 // lse2[h][r] = M + log2(L) over all range partials; rows >= W' get +inf (their P is 0).
 // 16 groups of 64 threads each fold every 16th range, then group 0 folds the 16 results: a
 // fixed order, so the result is run-to-run identical.
@@ -382,26 +642,57 @@ static int pick_waves(int group) {
   return 8;
 }
 
+// The cut of a sweep: as many heads per workgroup as leave enough waves for the chip (256 compute units), at most `most`, and several
+// rounds of workgroups, so that the last one is short.
+static EstShape est_shape(const vs_params& p, int most, int rounds) {
+  const int group = p.n_q_heads / p.n_kv_heads;
+  const int64_t n_tiles = ceil_div(p.q_start + p.q_len, 64), waves = 256 * kEstWaves;
+  EstShape z;
+  z.n_hb = (int32_t)ceil_div(group, most);
+  while (z.n_hb < group && n_tiles * p.n_kv_heads * z.n_hb < waves * 3 / 4) ++z.n_hb;
+  z.heads = (int32_t)ceil_div(group, z.n_hb);
+  z.n_hb = (int32_t)ceil_div(group, z.heads);
+  z.waves = z.heads > 2 ? kEstWaves : 4;
+  const int64_t tiles = n_tiles * p.n_kv_heads * z.n_hb / (waves * rounds);
+  z.tiles = (int32_t)(tiles < 1 ? 1 : tiles);
+  z.n_blocks = (int32_t)ceil_div(n_tiles, (int64_t)z.tiles * z.waves);
+  return z;
+}
+static EstShape est_shape_a(const vs_params& p) { return est_shape(p, 4, 2); }   // (its state takes LDS as well)
+static EstShape est_shape_b(const vs_params& p) { return est_shape(p, 7, 2); }
+
 size_t estimate_ws_bytes(const vs_params& p) {
   const int64_t n_k = p.q_start + p.q_len;
-  const int64_t n_ranges = ceil_div(n_k, kEstRange);
+  int64_t n_ranges = ceil_div(n_k, kEstRange);   // of a Dual Chunk Attention call
+  if (est_shape_a(p).n_blocks > n_ranges) n_ranges = est_shape_a(p).n_blocks;
   return align_up((size_t)p.n_q_heads * n_ranges * 64 * 2 * sizeof(float), 256) +
          align_up((size_t)p.n_q_heads * 64 * sizeof(float), 256);
 }
 
 template <int D, int NH>
-static hipError_t launch_est(EstArgs a, int hb, hipStream_t st) {
+static hipError_t launch_est_dca(EstArgs a, int hb, hipStream_t st) {
   a.n_hb = hb;
   const dim3 grid((unsigned)(ceil_div((int64_t)a.n_ranges * a.n_kv_heads, 8) * 8 * hb));
-  if (a.dca_chunk > 0) {
-    hipLaunchKernelGGL((k_estimate<D, NH, 0, true>), grid, dim3(128 * NH), 0, st, a);
-    hipLaunchKernelGGL(k_estimate_combine, dim3(a.n_q_heads), dim3(1024), 0, st, a);
-    hipLaunchKernelGGL((k_estimate<D, NH, 1, true>), grid, dim3(128 * NH), 0, st, a);
-    return hipGetLastError();
-  }
-  hipLaunchKernelGGL((k_estimate<D, NH, 0, false>), grid, dim3(128 * NH), 0, st, a);
+  hipLaunchKernelGGL((k_estimate<D, NH, 0>), grid, dim3(128 * NH), 0, st, a);
   hipLaunchKernelGGL(k_estimate_combine, dim3(a.n_q_heads), dim3(1024), 0, st, a);
-  hipLaunchKernelGGL((k_estimate<D, NH, 1, false>), grid, dim3(128 * NH), 0, st, a);
+  hipLaunchKernelGGL((k_estimate<D, NH, 1>), grid, dim3(128 * NH), 0, st, a);
+  return hipGetLastError();
+}
+
+template <int D>
+static hipError_t launch_est(const vs_params& p, const EstArgs& a, hipStream_t st) {
+  static DeviceOnce once;
+  const hipError_t e = once.run([] {   // more than 64 KiB of LDS per workgroup
+    const hipError_t r = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_est_sums<D>), hipFuncAttributeMaxDynamicSharedMemorySize, 160 << 10);
+    return r != hipSuccess ? r : hipFuncSetAttribute(reinterpret_cast<const void*>(&k_est_scores<D>), hipFuncAttributeMaxDynamicSharedMemorySize, 160 << 10);
+  });
+  if (e != hipSuccess) return e;
+  const EstShape za = est_shape_a(p), zb = est_shape_b(p);
+  auto grid = [&](const EstShape& z) { return dim3((unsigned)(ceil_div((int64_t)z.n_blocks * a.n_kv_heads, 8) * 8 * z.n_hb)); };
+  const size_t q_bytes = 64 * D * sizeof(__bf16);
+  hipLaunchKernelGGL(k_est_sums<D>, grid(za), dim3(64 * za.waves), za.heads * (q_bytes + (size_t)za.waves * 2 * 64 * sizeof(float2)), st, a, za, zb.tiles);
+  hipLaunchKernelGGL(k_estimate_combine, dim3(a.n_q_heads), dim3(1024), 0, st, a);
+  hipLaunchKernelGGL(k_est_scores<D>, grid(zb), dim3(64 * zb.waves), zb.heads * (q_bytes + (size_t)zb.waves * 64 * sizeof(float)), st, a, zb);
   return hipGetLastError();
 }
 
@@ -419,19 +710,24 @@ hipError_t launch_estimate(const vs_params& p, const void* q, const DcaArgs* dca
   a.n_q_heads = p.n_q_heads; a.n_kv_heads = p.n_kv_heads; a.group = p.n_q_heads / p.n_kv_heads;
   a.wp = (int32_t)(p.last_q < p.q_len ? p.last_q : p.q_len);
   a.q_len = p.q_len; a.n_k = p.q_start + p.q_len; a.p0 = a.n_k - a.wp;
-  a.n_ranges = (int32_t)ceil_div(a.n_k, kEstRange);
+  a.n_ranges = dca ? (int32_t)ceil_div(a.n_k, kEstRange) : est_shape_a(p).n_blocks;
+  a.n_hb = 1;
   a.scale_log2 = p.softmax_scale * kLog2e;
   a.part = (float*)ws;
   a.lse2 = (float*)((char*)ws + align_up((size_t)p.n_q_heads * a.n_ranges * 64 * 2 * sizeof(float), 256));
+  if (!dca) {
+    if (p.head_dim == 128) return launch_est<128>(p, a, st);
+    return launch_est<64>(p, a, st);
+  }
   const int64_t n_sc = (int64_t)p.n_q_heads * a.n_k;
   hipLaunchKernelGGL(k_fill_zero, dim3((unsigned)(n_sc / 1024 < 1 ? 1 : (n_sc / 1024 > 8192 ? 8192 : n_sc / 1024))),
                      dim3(256), 0, st, sscore, n_sc);
-  // large groups are split over two workgroups: two of them fit a compute unit, and the DCA
-  // instantiation needs the registers (the two are placed on one XCD, see the kernel)
+  // large groups are split over two workgroups: the three rotations need the registers (the two are placed on one XCD,
+  // see the kernel)
   const int nw = pick_waves(a.group > 4 ? (a.group + 1) / 2 : a.group);
   const int hb = (int)ceil_div(a.group, nw);
 #define VS_EST_CASE(DD, WW) \
-  if (p.head_dim == DD && nw == WW) return launch_est<DD, WW>(a, hb, st);
+  if (p.head_dim == DD && nw == WW) return launch_est_dca<DD, WW>(a, hb, st);
   VS_EST_CASE(128, 1) VS_EST_CASE(128, 2) VS_EST_CASE(128, 4) VS_EST_CASE(128, 5)
   VS_EST_CASE(128, 7) VS_EST_CASE(128, 8)
   VS_EST_CASE(64, 1) VS_EST_CASE(64, 2) VS_EST_CASE(64, 4) VS_EST_CASE(64, 5)

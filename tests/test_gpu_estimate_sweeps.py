@@ -1,0 +1,43 @@
+"""The two sweeps of the estimate at the edges of their cut: one tile of keys, ragged last tiles, windows shorter than 64 rows
+(whose last offsets lie behind the last tile), groups of one head to more than a workgroup takes, several tiles per wave (their
+seams add two parts).  Against the fp64 oracle: element-wise at the rule of the other estimate tests, and 1e-5 of the norm
+(sums of up to 64 fp32 exponentials, whose arguments carry a few 2^-24 of scores below 32)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2501_15383_amd as vs
+from gpu_util import chunk_of, dev, f64
+from helpers import rand_bf16
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(hq, hkv, d, c, s, seed):
+    rng = np.random.default_rng(seed)
+    q = rand_bf16(rng, (c, hq, d)); k = rand_bf16(rng, (s + c, hkv, d))
+    pb = oracle.Problem(hq, hkv, d, c, s, 1.0 / np.sqrt(d))
+    rvs, rss, rlse = oracle.estimate(pb, q, k)
+    ck = chunk_of(pb)
+    poison = lambda: torch.full((hq, s + c), float("nan"), device="cuda")  # noqa: E731  every score is written
+    vsc, ssc, lse = vs.estimate(ck, dev(q), dev(k), want_lse=True, vscore=poison(), sscore=poison())
+    again = vs.estimate(ck, dev(q), dev(k), want_lse=True, vscore=poison(), sscore=poison())
+    torch.cuda.synchronize()
+    assert torch.equal(vsc, again[0]) and torch.equal(ssc, again[1]) and torch.equal(lse, again[2])
+    for got, ref in ((vsc, rvs), (ssc, rss)):
+        got = f64(got)
+        np.testing.assert_allclose(got, ref, rtol=2e-4, atol=1e-7)
+        assert np.linalg.norm(got - ref) <= 1e-5 * np.linalg.norm(ref)
+    np.testing.assert_allclose(f64(lse).reshape(rlse.shape), rlse, rtol=2e-5, atol=2e-5)
+
+
+@pytest.mark.parametrize("c,s", [(1, 0), (1, 63), (1, 64), (5, 59), (63, 1), (64, 0), (64, 64), (65, 63), (100, 933), (3, 4094)])
+@pytest.mark.parametrize("hq,hkv,d", [(1, 1, 128), (7, 1, 128), (6, 2, 64), (9, 1, 64), (16, 2, 128)])
+def test_edges(hq, hkv, d, c, s):
+    _check(hq, hkv, d, c, s, 4000 + c + s)
+
+
+@pytest.mark.parametrize("hq,hkv,d,c,s", [(16, 8, 64, 77, 140001), (14, 2, 128, 64, 30000), (4, 4, 128, 20, 200000)])
+def test_several_tiles_and_workgroups(hq, hkv, d, c, s):
+    _check(hq, hkv, d, c, s, 4100)
