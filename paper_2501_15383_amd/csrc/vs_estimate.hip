@@ -9,6 +9,8 @@
 // bf16 MFMA (32x32x16) with fp32 accumulation; sweep A uses the K Q^T orientation (a lane owns one query), sweep B the Q K^T
 // orientation (a lane owns one key).  k_est_sums / k_est_scores are the sweeps of ordinary calls, k_estimate those of Dual
 // Chunk Attention, whose rotations change from tile to tile.
+#include <math.h>
+
 #include <type_traits>
 
 #include "vs_common.h"
@@ -352,7 +354,8 @@ __global__ __launch_bounds__(128 * NH, 1) void k_estimate(const EstArgs a) {
 // sum, diagonals).  1M keys, 28 query / 4 KV heads of 128: sweep A 590 us, sweep B 740, 1.38 ms with everything; with the K tiles
 // in LDS, a barrier per tile, 32 rows per wave, the diagonals turned by LDS lane exchanges and a pass that cleared the scores
 // 640 + 950, 1.63.  Small calls are cut finer: 8,192 keys 77 us -> 45.
-constexpr int kEstWaves = 16;    // waves per workgroup (4 where it takes one or two heads): four per SIMD, 128 registers
+constexpr int kEstWaves = 16;    // waves per workgroup at most, and per compute unit: four per SIMD, 128 registers
+constexpr int kEstLds = 160 << 10;
 
 struct EstShape {
   int32_t heads;     // query heads per workgroup
@@ -642,24 +645,43 @@ static int pick_waves(int group) {
   return 8;
 }
 
-// The cut of a sweep: as many heads per workgroup as leave enough waves for the chip (256 compute units), at most `most`, and several
-// rounds of workgroups, so that the last one is short.
-static EstShape est_shape(const vs_params& p, int most, int rounds) {
-  const int group = p.n_q_heads / p.n_kv_heads;
-  const int64_t n_tiles = ceil_div(p.q_start + p.q_len, 64), waves = 256 * kEstWaves;
-  EstShape z;
-  z.n_hb = (int32_t)ceil_div(group, most);
-  while (z.n_hb < group && n_tiles * p.n_kv_heads * z.n_hb < waves * 3 / 4) ++z.n_hb;
-  z.heads = (int32_t)ceil_div(group, z.n_hb);
-  z.n_hb = (int32_t)ceil_div(group, z.heads);
-  z.waves = z.heads > 2 ? kEstWaves : 4;
-  const int64_t tiles = n_tiles * p.n_kv_heads * z.n_hb / (waves * rounds);
-  z.tiles = (int32_t)(tiles < 1 ? 1 : tiles);
-  z.n_blocks = (int32_t)ceil_div(n_tiles, (int64_t)z.tiles * z.waves);
-  return z;
+// The cut of a sweep, by the time it should take, in units of one row block of a wave with 16 waves on the compute unit
+// (about 2.8 us): a tile costs 2 per head and 1.5 for its K rows, a workgroup its start and the window rows it puts into LDS,
+// and a row block is faster with fewer waves around.  Small calls are made of few rounds of workgroups, so the waves per
+// workgroup are whatever fills them.  28 / 4 heads, against at most 16 waves and always many heads per workgroup: 38,209 keys
+// 111 -> 85 us, 84,333 178 -> 146, 300,001 501 -> 420; 1M the same.  head_bytes: LDS per head and wave, beside the rows.
+static EstShape est_shape(const vs_params& p, int most, int head_bytes) {
+  const int group = p.n_q_heads / p.n_kv_heads, n_cu = 256;
+  const double n_tiles = (double)ceil_div(p.q_start + p.q_len, 64), units = n_tiles * p.n_kv_heads;
+  EstShape best = {};
+  double best_cost = -1.0;
+  const int hb0 = (group + most - 1) / most, hbs[4] = {hb0, hb0 + 1, hb0 + 2, group};
+  static constexpr int kWaves[] = {16, 14, 12, 10, 9, 8, 7, 6, 5, 4};
+  for (const int hb : hbs) {
+    if (hb > group) continue;
+    const int heads = (group + hb - 1) / hb, n_hb = (group + heads - 1) / heads;
+    for (const int waves : kWaves) {
+      const int lds = heads * (64 * p.head_dim * 2 + waves * head_bytes);
+      if (lds > kEstLds) continue;
+      const int by_lds = kEstLds / lds, by_waves = kEstWaves / waves, per_cu = by_lds < by_waves ? by_lds : by_waves;
+      for (int want = 1; want <= 3; ++want) {   // rounds
+        const double tiles = ceil(units * n_hb / ((double)waves * per_cu * n_cu * want));
+        const double blocks = ceil(n_tiles / (tiles * waves)), wgs = blocks * p.n_kv_heads * n_hb;
+        const double rounds = ceil(wgs / (n_cu * per_cu)), resident = rounds > 1 ? per_cu : ceil(wgs / n_cu);
+        const double rate = 0.3 + 0.7 * resident * waves / kEstWaves;
+        const double cost = rounds * (tiles * (2.0 * heads + 1.5) * rate + 1.5 + 0.2 * heads * kEstWaves / waves);
+        if (best_cost < 0 || cost < best_cost) {
+          best_cost = cost;
+          best.heads = heads; best.n_hb = n_hb; best.waves = waves;
+          best.tiles = (int32_t)tiles; best.n_blocks = (int32_t)blocks;
+        }
+      }
+    }
+  }
+  return best;
 }
-static EstShape est_shape_a(const vs_params& p) { return est_shape(p, 4, 2); }   // (its state takes LDS as well)
-static EstShape est_shape_b(const vs_params& p) { return est_shape(p, 7, 2); }
+static EstShape est_shape_a(const vs_params& p) { return est_shape(p, 4, 2 * 64 * sizeof(float2)); }
+static EstShape est_shape_b(const vs_params& p) { return est_shape(p, 7, 64 * sizeof(float)); }
 
 size_t estimate_ws_bytes(const vs_params& p) {
   const int64_t n_k = p.q_start + p.q_len;
@@ -683,8 +705,8 @@ template <int D>
 static hipError_t launch_est(const vs_params& p, const EstArgs& a, hipStream_t st) {
   static DeviceOnce once;
   const hipError_t e = once.run([] {   // more than 64 KiB of LDS per workgroup
-    const hipError_t r = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_est_sums<D>), hipFuncAttributeMaxDynamicSharedMemorySize, 160 << 10);
-    return r != hipSuccess ? r : hipFuncSetAttribute(reinterpret_cast<const void*>(&k_est_scores<D>), hipFuncAttributeMaxDynamicSharedMemorySize, 160 << 10);
+    const hipError_t r = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_est_sums<D>), hipFuncAttributeMaxDynamicSharedMemorySize, kEstLds);
+    return r != hipSuccess ? r : hipFuncSetAttribute(reinterpret_cast<const void*>(&k_est_scores<D>), hipFuncAttributeMaxDynamicSharedMemorySize, kEstLds);
   });
   if (e != hipSuccess) return e;
   const EstShape za = est_shape_a(p), zb = est_shape_b(p);
