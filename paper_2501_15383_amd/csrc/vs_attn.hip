@@ -245,7 +245,7 @@ __device__ __forceinline__ bool bm_test(const uint32_t* bm, int i) {
 // LDS bytes of one workgroup: K and V tiles (unpadded, chunk-swizzled), double-buffered, the
 // gathered column indices of a vertical tile, and per-wave mask thresholds.
 template <int D>
-constexpr int attn_lds_bytes() { return 4 * 64 * D * 2 + 2 * 64 * 4 + 4 * kAttnQBlocks * 64; }
+constexpr int attn_lds_bytes() { return 4 * 64 * D * 2 + 4 * 64 * 4 + 4 * kAttnQBlocks * 64; }
 
 // Direct global -> LDS copy, 16 bytes per lane: lane L's bytes land at lds_addr + 16 L
 // (lds_addr is wave-uniform and goes through M0).  Completion is tracked by vmcnt.
@@ -318,8 +318,8 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   __bf16* const Ks = (__bf16*)smem_raw;               // [2][TILE]
   __bf16* const Vs = Ks + 2 * TILE;                   // [2][TILE]
-  int32_t* const vidx_s = (int32_t*)(Vs + 2 * TILE);  // [2][64]
-  uint8_t* const need_s = (uint8_t*)(vidx_s + 2 * 64);  // [waves][64], private to each wave
+  int32_t* const vidx_s = (int32_t*)(Vs + 2 * TILE);  // [4][64]
+  uint8_t* const need_s = (uint8_t*)(vidx_s + 4 * 64);  // [waves][64], private to each wave
   static_assert(2 * (2 * NQB) * 64 <= 4 * kAttnQBlocks * 64, "need_s and dcak_s share the bytes after vidx_s");
   uint8_t* const dcak_s = need_s + 2 * NQB * 64;        // [waves][64], DCA pattern code of a tile's keys
   const uint32_t ks_addr = lds_address(Ks), vs_addr = lds_address(Vs);
@@ -517,8 +517,8 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
   // kind 0: slash tile, idx = cc, mask = query blocks that use it; kind 1: vertical tile,
   // idx = vt; kind 2: end.  Entries are fetched 64 at a time (one per lane), one batch ahead.
   // With a key split this workgroup walks the entries with cc in [cc_lo, cc_end] and every
-  // n_split-th vertical tile; the first entry is found by bisection (the list ascends in cc and
-  // ends in sentinels).
+  // n_split-th vertical tile; the first entry is searched for with 64 probes at a time (the list ascends
+  // in cc and ends in sentinels): three loads in a row for 16K entries, 14 by bisection.
   int cc_end = cc_last, ei0 = 0;
   const int vstep = SPLIT && !whole ? a.n_split : 1;
   int vlin = sp - vstep;
@@ -528,14 +528,21 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
     cc_end = cc_lo + per - 1 < cc_last ? cc_lo + per - 1 : cc_last;
     int lo = 0, hi = (int)a.ent_len - 1;  // the last entry is a sentinel: an answer always exists
     while (lo < hi) {
-      const int mid = (lo + hi) >> 1;
-      const int cm = (int)(__builtin_amdgcn_readfirstlane(ent_h[mid]) >> 4);
-      if (cm >= cc_lo) hi = mid; else lo = mid + 1;
+      const int step = (hi - lo + 63) >> 6, x = lo + lane * step;
+      const int below = __popcll(__ballot((int)(ent_h[x < hi ? x : hi] >> 4) < cc_lo));   // (never at hi)
+      if (below == 0) break;
+      hi = lo + below * step < hi ? lo + below * step : hi;
+      lo += (below - 1) * step + 1;
     }
     ei0 = lo;
   }
   uint32_t ecache = ent_h[(ei0 & ~63) + lane], ecache_nx = ent_h[(ei0 & ~63) + 64 + lane];
   int ei = ei0 - 1;
+  // Columns of vertical tiles go into a ring of four in LDS when the tile is found, two steps before its rows are copied:
+  // slot (ring + n) & 3 for the tile n steps from now, written by the first wave, read behind the barrier of the step.
+  // (Looked up when the rows were copied, K and then V, they cost two trips to memory in every such step: 4 sparse requests of
+  // up to 200 rows and 4,671 keys 152 -> 116 us, 109 rows at 3,336 keys 64 -> 50, both with the search below.)
+  int ring = -2;
   auto advance = [&](int& kind, int& idx, int& mask) {
     int k2 = kind, i2 = idx, m2 = 0;
     if (k2 == 0) {
@@ -564,12 +571,20 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
         if (x < nt) break;
         x -= nt;
       }
-      if (hd < pack && h - g * a.group + hd < a.group) { i2 = (hd << kHeadShift) | x; m2 = 1 << hd; }
-      else { k2 = 2; i2 = 0; }
+      if (hd < pack && h - g * a.group + hd < a.group) {
+        i2 = (hd << kHeadShift) | x; m2 = 1 << hd;
+        const int pos = 64 * x + lane;
+        const int col = pos < __builtin_amdgcn_readlane(vcnt_l, hd) ? vidx_h[(int64_t)hd * a.v_budget + pos] : 0;
+        if (wv == 0) vidx_s[((ring + 2) & 3) * 64 + lane] = col;
+      } else { k2 = 2; i2 = 0; }
     } else if (k2 == 1) {
       const int vt = i2 + vstep;
       bool more = vt < n_vt;
-      if (more) more = (int64_t)__builtin_amdgcn_readfirstlane(vidx_h[64 * vt]) <= last_pos;
+      if (more) {
+        const int col = 64 * vt + lane < vcnt ? vidx_h[64 * vt + lane] : 0;
+        more = (int64_t)__builtin_amdgcn_readfirstlane(col) <= last_pos;
+        if (wv == 0) vidx_s[((ring + 2) & 3) * 64 + lane] = col;
+      }
       if (more) i2 = vt; else { k2 = 2; i2 = 0; }
     }
     // the descriptor is uniform by construction; say so, so that it lives in scalar registers
@@ -577,18 +592,10 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
     idx = __builtin_amdgcn_readfirstlane(i2);
     mask = __builtin_amdgcn_readfirstlane(m2);
   };
-  // key index that tile row r comes from (general path)
-  auto src_row = [&](int kind, int idx, int r) -> int64_t {
-    if (kind == 0) {
-      int64_t j = (int64_t)(m0 - (idx - (NQB - 1))) * 64 + r;
-      return j < n_k ? j : n_k - 1;
-    }
-    if (SPLIT && pack > 1) {
-      const int hd = idx >> kHeadShift, pos = 64 * (idx & ((1 << kHeadShift) - 1)) + r;
-      return pos < __builtin_amdgcn_readlane(vcnt_l, hd) ? (int64_t)vidx_h[(int64_t)hd * a.v_budget + pos] : 0;
-    }
-    int pos = 64 * idx + r;
-    return pos < vcnt ? (int64_t)vidx_h[pos] : 0;
+  // key index that row r of a slash tile comes from (general path)
+  auto src_row = [&](int idx, int r) -> int64_t {
+    int64_t j = (int64_t)(m0 - (idx - (NQB - 1))) * 64 + r;
+    return j < n_k ? j : n_k - 1;
   };
 
   // ---- staging: global -> LDS copies, GPW groups of RPG rows per wave for K and for V --------
@@ -608,7 +615,7 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
     koff[e] = (uint32_t)((e * WAVES * RPG + r0) * a.k_stride_tok * 2 + kch * 16);
     voff[e] = (uint32_t)((e * WAVES * RPG + r0) * a.v_stride_tok * 2 + vch * 16);
   }
-  auto issue_k = [&](int kind, int idx, int buf) {
+  auto issue_k = [&](int kind, int idx, int buf, int slot) {
     const uint32_t kdst = ks_addr + (uint32_t)(buf * TILE * 2 + wv * 1024);
     bool fast = false;
     if (kind == 0) {
@@ -631,13 +638,12 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
     if (__builtin_expect(!fast, 0)) {
 #pragma unroll
       for (int e = 0; e < GPW; ++e) {
-        const int64_t j = src_row(kind, idx, e * WAVES * RPG + r0);
+        const int64_t j = kind == 1 ? (int64_t)vidx_s[slot * 64 + e * WAVES * RPG + r0] : src_row(idx, e * WAVES * RPG + r0);
         dma16_lane_ptr(kdst + e * WAVES * 1024, kbase + j * a.k_stride_tok + kch * 8);
       }
-      if (kind == 1 && tid < 64) vidx_s[buf * 64 + tid] = (int32_t)src_row(kind, idx, tid);
     }
   };
-  auto issue_v = [&](int kind, int idx, int buf) {
+  auto issue_v = [&](int kind, int idx, int buf, int slot) {
     const uint32_t vdst = vs_addr + (uint32_t)(buf * TILE * 2 + wv * 1024);
     bool fast = false;
     if (kind == 0) {
@@ -660,7 +666,7 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
     if (__builtin_expect(!fast, 0)) {
 #pragma unroll
       for (int e = 0; e < GPW; ++e) {
-        const int64_t j = src_row(kind, idx, e * WAVES * RPG + r0);
+        const int64_t j = kind == 1 ? (int64_t)vidx_s[slot * 64 + e * WAVES * RPG + r0] : src_row(idx, e * WAVES * RPG + r0);
         dma16_lane_ptr(vdst + e * WAVES * 1024, vbase + j * a.v_stride_tok + vch * 8);
       }
     }
@@ -948,9 +954,12 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
   advance(cur_kind, cur_idx, cur_mask);
   int nxt_kind = cur_kind, nxt_idx = cur_idx, nxt_mask = cur_mask;
   if (cur_kind != 2) {
-    issue_k(cur_kind, cur_idx, 0);
+    if (cur_kind == 1) __syncthreads();   // (a piece without a slash tile: its columns were found just now)
+    issue_k(cur_kind, cur_idx, 0, 0);
+    ring = -1;
     advance(nxt_kind, nxt_idx, nxt_mask);
   }
+  ring = 0;
   wait_copies();
   __syncthreads();
   int buf = 0;
@@ -1005,7 +1014,7 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
         n_cols = __builtin_amdgcn_readlane(vcnt_l, hd);
         part = part && hd == th;
       }
-      const int j = vidx_s[buf * 64 + lane];
+      const int j = vidx_s[(ring & 3) * 64 + lane];
       const int ad = (m0 + t) - (j >> 6);
       int need = 64;
       if (pos < n_cols && ad >= 0 && !bm_test(bmA, ad)) need = ad == 0 ? (j & 63) : 0;
@@ -1032,7 +1041,7 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
             dcak_s[wv * 64 + lane] = (uint8_t)lane;
           } else need_var = 2;
         } else {
-          const int j = vidx_s[buf * 64 + lane];
+          const int j = vidx_s[(ring & 3) * 64 + lane];
           const int cb = j >> 6;
           int code = 0;
           if (cb >= dca_cs) code = 100;
@@ -1059,8 +1068,8 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
   // copies of K(i + 1) and V(i) into the buffers that step i - 1 used last
   auto launch_copies = [&]() {
     if (!last) {
-      if (nxt_kind != 2) issue_k(nxt_kind, nxt_idx, buf ^ 1);
-      issue_v(cur_kind, cur_idx, buf);
+      if (nxt_kind != 2) issue_k(nxt_kind, nxt_idx, buf ^ 1, (ring + 1) & 3);
+      issue_v(cur_kind, cur_idx, buf, ring & 3);
     }
   };
   auto end_step = [&]() {
@@ -1073,6 +1082,7 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
     cur_kind = nxt_kind; cur_idx = nxt_idx; cur_mask = nxt_mask;
     nxt_kind = nn_kind; nxt_idx = nn_idx; nxt_mask = nn_mask;
     buf ^= 1;
+    ++ring;
   };
 
   for (;;) {
@@ -1085,7 +1095,7 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
       if (!DCA && !SPLIT && a.bm_stride == 0 && cur_kind == 0 && nxt_kind == 0 && cur_idx >= NQB) {
         while (cur_idx + 2 <= cc_end) {
           const int ci = cur_idx;
-          auto launch = [&]() { issue_k(0, ci + 1, buf ^ 1); issue_v(0, ci, buf); };
+          auto launch = [&]() { issue_k(0, ci + 1, buf ^ 1, 0); issue_v(0, ci, buf, 0); };
           fused(Ks + buf * TILE, Vs + (buf ^ 1) * TILE, launch);
           enter_segment((cc_last - (ci + 2)) >> (a.sync_shift + seg_shift), true);
           wait_copies();
