@@ -1,6 +1,6 @@
 """The two sweeps of the estimate at the edges of their cut: one tile of keys, ragged last tiles, windows shorter than 64 rows
 (whose last offsets lie behind the last tile), groups of one head to more than a workgroup takes, several tiles per wave (their
-seams add two parts).  Against the fp64 oracle: element-wise at the rule of the other estimate tests, and 1e-5 of the norm
+seams add two parts), rotations that change between and inside blocks.  Against the fp64 oracle: element-wise at the rule of the other estimate tests, and 1e-5 of the norm
 (sums of up to 64 fp32 exponentials, whose arguments carry a few 2^-24 of scores below 32)."""
 import numpy as np
 import pytest
@@ -14,15 +14,17 @@ from helpers import rand_bf16
 pytestmark = pytest.mark.gpu
 
 
-def _check(hq, hkv, d, c, s, seed):
+def _check(hq, hkv, d, c, s, seed, dca=None):
     rng = np.random.default_rng(seed)
     q = rand_bf16(rng, (c, hq, d)); k = rand_bf16(rng, (s + c, hkv, d))
+    succ, inter = (rand_bf16(rng, (c, hq, d)) for _ in range(2))   # unlike q: a wrong choice of rotation shows
     pb = oracle.Problem(hq, hkv, d, c, s, 1.0 / np.sqrt(d))
-    rvs, rss, rlse = oracle.estimate(pb, q, k)
+    rvs, rss, rlse = oracle.estimate(pb, q, k, dca=None if dca is None else oracle.Dca(dca[0], dca[1], succ, inter))
+    gd = None if dca is None else (dev(succ), dev(inter), dca[0], dca[1])
     ck = chunk_of(pb)
     poison = lambda: torch.full((hq, s + c), float("nan"), device="cuda")  # noqa: E731  every score is written
-    vsc, ssc, lse = vs.estimate(ck, dev(q), dev(k), want_lse=True, vscore=poison(), sscore=poison())
-    again = vs.estimate(ck, dev(q), dev(k), want_lse=True, vscore=poison(), sscore=poison())
+    vsc, ssc, lse = vs.estimate(ck, dev(q), dev(k), want_lse=True, vscore=poison(), sscore=poison(), dca=gd)
+    again = vs.estimate(ck, dev(q), dev(k), want_lse=True, vscore=poison(), sscore=poison(), dca=gd)
     torch.cuda.synchronize()
     assert torch.equal(vsc, again[0]) and torch.equal(ssc, again[1]) and torch.equal(lse, again[2])
     for got, ref in ((vsc, rvs), (ssc, rss)):
@@ -41,3 +43,21 @@ def test_edges(hq, hkv, d, c, s):
 @pytest.mark.parametrize("hq,hkv,d,c,s", [(16, 8, 64, 77, 140001), (14, 2, 128, 64, 30000), (4, 4, 128, 20, 200000)])
 def test_several_tiles_and_workgroups(hq, hkv, d, c, s):
     _check(hq, hkv, d, c, s, 4100)
+
+
+@pytest.mark.parametrize("c,s,dca", [
+    (64, 1000, (64, 0)),          # the smallest chunk: rows on both sides of a boundary, no window
+    (64, 1000, (128, 64)),
+    (40, 2000, (512, 512)),       # a window as long as the chunk
+    (64, 4064, (1024, 192)),      # rows on both sides; the window ends inside blocks
+    (64, 3000, (1024, 4096)),     # longer than the chunk
+    (3, 700, (4096, 64)),         # one chunk
+    (200, 30000, (8192, 1024)),
+])
+@pytest.mark.parametrize("hq,hkv,d", [(7, 1, 128), (6, 2, 64), (5, 5, 128)])
+def test_rotations(hq, hkv, d, c, s, dca):
+    _check(hq, hkv, d, c, s, 4200 + s, dca)
+
+
+def test_rotations_over_several_tiles_per_wave():
+    _check(8, 8, 64, 64, 120000, 4300, (32768, 2048))
