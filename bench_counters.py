@@ -164,8 +164,8 @@ def main():
     out += [f"  k_attention sparse launch   read {sparse_rd / 1e9:9.2f} GB   written {sparse_wr / 1e9:7.3f} GB",
             f"  k_attention dense launch    read {dense_rd / 1e9:9.2f} GB",
             f"  k_attention gather probe    read {gather_rd / 1e9:9.2f} GB   written {gather_wr / 1e9:7.3f} GB"]
-    for nm in ("k_estimate<128, 4, 0, false>", "k_estimate<128, 4, 1, false>", "k_sel_hist", "k_sel_count", "k_sel_write",
-               "k_fill_zero(", "k_estimate_combine", "k_build_blocklist"):
+    for nm in ("k_est_sums<128, false>", "k_est_scores<128, false>", "k_estimate_combine", "k_sel_sample", "k_sel_filter",
+               "k_sel_row<0>", "k_build_blocklist", "k_attn_schedule"):
         r_, w_ = pick(rd, nm), pick(wr, nm)
         out.append(f"  {nm:27s} read {(rd_bytes(r_[0]) if r_ else 0) / 1e9:9.3f} GB   written "
                    f"{(w_[0]['WRITE_SIZE'] * 1024 if w_ else 0) / 1e9:7.3f} GB")
@@ -174,12 +174,12 @@ def main():
             "touch-once minimum (Q, O, K, V) 2.62 GB; bytes copied into LDS 32 KiB per workgroup step",
             f"gather probe: {(gather_rd + gather_wr) / 1e9:.2f} GB per launch over {kt_gather_ms:.3f} ms = "
             f"{(gather_rd + gather_wr) / 1e9 / kt_gather_ms:.2f} TB/s on the HBM side"]
-    e0, e1 = pick(rd, "k_estimate<128, 4, 0, false>")[0], pick(rd, "k_estimate<128, 4, 1, false>")[0]
-    w1 = pick(wr, "k_estimate<128, 4, 1, false>")[0]["WRITE_SIZE"] * 1024
-    ta = [v for n, v in per.items() if "k_estimate<128, 4, 0, false>" in n][0]
-    tb = [v for n, v in per.items() if "k_estimate<128, 4, 1, false>" in n][0]
+    e0, e1 = pick(rd, "k_est_sums<128, false>")[0], pick(rd, "k_est_scores<128, false>")[0]
+    w1 = pick(wr, "k_est_scores<128, false>")[0]["WRITE_SIZE"] * 1024
+    ta = [v for n, v in per.items() if "k_est_sums<128, false>" in n][0]
+    tb = [v for n, v in per.items() if "k_est_scores<128, false>" in n][0]
     ta, tb = sum(ta) / len(ta), sum(tb) / len(tb)
-    out += [f"k_estimate sweep A: {rd_bytes(e0) / 1e9:.3f} GB read in {ta:.3f} ms = {rd_bytes(e0) / 1e9 / ta:.2f} TB/s; sweep B: "
+    out += [f"estimate sweep A: {rd_bytes(e0) / 1e9:.3f} GB read in {ta:.3f} ms = {rd_bytes(e0) / 1e9 / ta:.2f} TB/s; sweep B: "
             f"{rd_bytes(e1) / 1e9:.3f} GB read + {w1 / 1e9:.3f} GB written in {tb:.3f} ms = {(rd_bytes(e1) + w1) / 1e9 / tb:.2f} TB/s "
             "(K cache = 1.074 GB)", ""]
     # ---- 3. SQ counters, sparse / dense / gather launches
