@@ -391,8 +391,8 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
       e = a.n_whole + v - sp * n;
       slot = v;
     }
-    if (none) e = 0;
-    unit_of(a, e, g, h, qt);
+    g = h = qt = 0;
+    if (!none) unit_of(a, e, g, h, qt);
   } else {
     if (gr < n_full_gr) {
       h = gr % a.n_q_heads;

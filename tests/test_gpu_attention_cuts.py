@@ -87,3 +87,13 @@ def test_plans_over_many_requests(n_req):
         assert torch.equal(x["out"].view(torch.int16), y["out"].view(torch.int16)) and torch.equal(x["lse"], y["lse"])
     assert (a[skipped]["out"].float() == -3.0).all() and (a[skipped]["lse"] == 7.0).all()
     _check(reqs, a, skip=(skipped,))
+
+
+def test_a_batch_without_any_request_to_take():
+    hq, hkv, d, bv, bs = 4, 2, 64, 40, 90
+    reqs = _make_requests(np.random.default_rng(3300), hq, hkv, d, [(20, 300, False), (5, 100, True)], bv, bs)
+
+    def poison(table):
+        table[:, 0] = 0   # no queries
+    for g in _run_batch(reqs, hq, hkv, d, bv, bs, poison=poison):
+        assert (g["out"].float() == -3.0).all() and (g["lse"] == 7.0).all()
