@@ -2007,7 +2007,8 @@ hipError_t launch_attention(const vs_params& p, const void* q, const DcaArgs* dc
   // units): 8,192 rows at 400K keys 35.9 ms against 37.3 in one launch, 9,500 clustered ones at 300K 12.8 against 14.0.
   // Below 256K keys the caches hold what the members of a group are apart, and one launch fills its own gaps: 2,400 rows at
   // 100K keys 3.44 ms against 3.52, 5,426 clustered ones at 33K 2.31 against 2.46.
-  if (a.n_split > 1 && a.n_whole > 0 && members == kRun && ceil_div(a.n_k, kBlock) >= kPaceBlocks) {
+  // Not where heads share tiles: the pace-keeping kernel takes one head per unit, with one list per head.
+  if (a.n_split > 1 && a.n_whole > 0 && a.pack == 1 && members == kRun && ceil_div(a.n_k, kBlock) >= kPaceBlocks) {
     keep_pace(a.n_whole);
     a.first_piece = a.n_whole;
   }

@@ -69,6 +69,32 @@ def test_whole_units_and_cut_ones(c, s):
         assert ((a - b).norm(dim=2) <= 2e-2 * b.norm(dim=2)).all() and (la - lb).abs().max().item() < 1e-4
 
 
+# one KV head, 64 rows and as many keys as whole units keep pace from: 515 tiles of two heads, 512 of them whole and the last
+# three cut; and the same heads behind a start inside a block (two query blocks: no sharing, 1,030 units)
+@pytest.mark.parametrize("s", [4095 * 64, 4096 * 64 + 9])
+def test_whole_tiles_of_shared_heads_at_long_contexts(s):
+    hq, hkv, d, c = 1030, 1, 64, 64
+    rng = np.random.default_rng(3150)
+    q = rand_bf16(rng, (c, hq, d)); k = rand_bf16(rng, (s + c, hkv, d)); v = rand_bf16(rng, (s + c, hkv, d))
+    pb = oracle.Problem(hq, hkv, d, c, s, 1.0 / np.sqrt(d), vertical_budget=100, slash_budget=90)
+    heads = [0, 1, 255, 511, 512, 513, 700, 1022, 1023, 1024, 1029]   # both heads of a tile; whole and cut tiles
+    rows = [0, 31, 32, 63]
+    at = torch.tensor(rows, device="cuda")
+    few = oracle.Problem(7, 1, d, c, s, 1.0 / np.sqrt(d), vertical_budget=100, slash_budget=90)
+    sets = [x[np.arange(hq) % 7] for x in _rand_sets(rng, few, 90, 20, force_cols=[0], force_offs=range(64))]
+    for name, call, want in (
+            ("dense", lambda o: vs.dense_causal_prefill(chunk_of(pb), dev(q), dev(k), dev(v), want_lse=True, out=o),
+             lambda: oracle.dense_attention(pb, q, k, v, heads=heads, rows=rows)),
+            ("sparse", lambda o: vs.sparse_attn_prefill(chunk_of(pb), dev(q), dev(k), dev(v), *[_t(x) for x in sets],
+                                                        want_lse=True, out=o),
+             lambda: oracle.sparse_attention(pb, q, k, v, *sets, heads=heads, rows=rows))):
+        o = torch.full((c, hq, d), 7.0, dtype=torch.bfloat16, device="cuda")
+        out, lse = call(o)
+        torch.cuda.synchronize()
+        assert not (out == 7.0).all(dim=2).any(), f"{name}: rows that nobody wrote"
+        assert_attn_close(out[at][:, heads], lse[heads][:, at], *want(), f"{name}, {hq} heads, s={s}")
+
+
 @pytest.mark.parametrize("n_req", [70, 1030])
 def test_plans_over_many_requests(n_req):
     hq, hkv, d, bv, bs = 4, 2, 64, 40, 90
