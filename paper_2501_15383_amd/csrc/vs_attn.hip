@@ -1213,13 +1213,14 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
 // block mask, in ascending order, followed by sentinels up to the end of the row.
 // With packed heads (pack > 1) a list is that of a tile of `pack` heads with one query block: the union of their
 // diagonals a, as cc = a + NQB - 1, with a mask bit per head that has the diagonal.
-// With req != null the launch builds one list per (request, head), blockIdx.y = 1 + r * n_heads + h:
+// List x0 is blockIdx.x, the part of a dense list blockIdx.y (the x axis takes any number of heads, y 65,535 workgroups).
+// With req != null the launch builds one list per (request, head), blockIdx = (h, 1 + r):
 // offsets, their count, the number of key blocks and "dense" (no offsets given) come from the
 // request; a request that the attention kernel skips gets no list, and where it packs heads only as many as it
-// has tiles.  The first workgroup of a batch writes its plan (write_plan), the lists follow.  The workgroup of the first list also clears the n_zero words at `zero` (the
-// attention launch's counters).
+// has tiles.  The first workgroup of a batch writes its plan (write_plan), the lists follow.  The first workgroup also
+// clears the n_zero words at `zero` (the attention launch's counters).
 //
-// A sparse list is one workgroup's (blockIdx.x = 0) and bound by latency, not bytes (6,096 offsets
+// A sparse list is one workgroup's (part 0) and bound by latency, not bytes (6,096 offsets
 // in, 16K bits and up to 64 KB of entries out).  The bitmap is collected in LDS, kBlWin words at a
 // time: neighbouring offsets fall into the same few words, and the same OR-ing done with atomics in
 // global memory stood in line there (110-228 us for 28-40 heads at 256K-1M keys by where the
@@ -1327,23 +1328,21 @@ __global__ __launch_bounds__(kBlThreads) void k_build_blocklist(const ListArgs a
   constexpr int NW = kBlThreads / 64;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int part = blockIdx.x, list = (int)blockIdx.y - (a.req ? 1 : 0);   // a batch: the first workgroup is the plan's
+  const int part = a.req ? 0 : blockIdx.y, n_parts = a.req ? 1 : gridDim.y;
+  const int x0 = blockIdx.x, r = (int)blockIdx.y - 1;   // (r: of a batch, whose first workgroup is the plan's)
   const int n_words = a.n_words, ent_stride = a.ent_stride;
-  int x0 = list, dense = a.dense, n_blk = a.n_blk, pack = a.pack, n_hs = (a.group + pack - 1) / pack;
+  int dense = a.dense, n_blk = a.n_blk, pack = a.pack, n_hs = (a.group + pack - 1) / pack;
   const int32_t* s_idx = a.s_idx;
   const int32_t* s_cnt = a.s_cnt;
   uint32_t* bm_a = a.bm_a;
-  uint32_t* const E = a.ent + (int64_t)list * ent_stride;
-  if (part == 0 && list == 0)
+  if (blockIdx.x == 0 && blockIdx.y == 0)
     for (int x = tid; x < a.n_zero; x += kBlThreads) a.zero[x] = 0u;
   if (a.req) {
     __shared__ int64_t scan[NW];
-    if (list < 0) {
-      write_plan(a, scan);
+    if (r < 0) {
+      if (x0 == 0) write_plan(a, scan);
       return;
     }
-    const int r = list / a.n_heads;
-    x0 = list - r * a.n_heads;
     const vs_request rq = a.req[r];
     BatchShape b;
     if (!batch_shape(rq, a.group, a.n_heads / a.group, a.max_q_len, a.max_n_k, a.skip_single, b)) return;
@@ -1355,6 +1354,7 @@ __global__ __launch_bounds__(kBlThreads) void k_build_blocklist(const ListArgs a
     bm_a += (int64_t)r * a.n_heads * n_words;
     if (x0 >= a.n_heads / a.group * n_hs) return;
   }
+  uint32_t* const E = a.ent + ((a.req ? (int64_t)r * a.n_heads : 0) + x0) * ent_stride;
   // the first head of list x0, and how many heads it has
   const int grp = dense && !a.req ? 0 : x0 / n_hs, h0 = dense && !a.req ? 0 : grp * a.group + (x0 - grp * n_hs) * pack;
   const int n_in = grp * a.group + a.group - h0 < pack ? grp * a.group + a.group - h0 : pack;
@@ -1370,7 +1370,7 @@ __global__ __launch_bounds__(kBlThreads) void k_build_blocklist(const ListArgs a
     A[n_words - 2] = n_list;  // length of the list: the head's share of the work (k_attn_schedule)
   };
   if (dense && pack > 1) {
-    for (int i = part * kBlDensePart + tid; i < ent_stride && (i < (part + 1) * kBlDensePart || (int)gridDim.x == part + 1);
+    for (int i = part * kBlDensePart + tid; i < ent_stride && (i < (part + 1) * kBlDensePart || n_parts == part + 1);
          i += kBlThreads)
       E[i] = i < n_blk ? ((uint32_t)(i + NQB - 1) << 4) | 15u : kEntSentinel;
     // (no bitmap: a dense walk has no columns that ask it)
@@ -1379,7 +1379,7 @@ __global__ __launch_bounds__(kBlThreads) void k_build_blocklist(const ListArgs a
   }
   if (dense) {
     const int n_list = n_blk + NQB - 1, all = (1 << NQB) - 1;
-    for (int i = part * kBlDensePart + tid; i < ent_stride && (i < (part + 1) * kBlDensePart || (int)gridDim.x == part + 1);
+    for (int i = part * kBlDensePart + tid; i < ent_stride && (i < (part + 1) * kBlDensePart || n_parts == part + 1);
          i += kBlThreads) {
       uint32_t e = kEntSentinel;
       if (i < n_list) {   // mask bit t = diagonal i - (NQB - 1) + t exists
@@ -1865,7 +1865,7 @@ hipError_t launch_build_blocklist(const vs_params& p, const int32_t* s_idx, cons
   a.n_zero = sync_ws ? (int)(attn_counter_bytes(p) / sizeof(uint32_t)) : 0;
   const unsigned parts = dense ? (unsigned)ceil_div(bl.ent_stride, kBlDensePart) : 1u;
   const unsigned lists = dense ? 1u : (unsigned)(p.n_kv_heads * ceil_div(a.group, a.pack));
-  hipLaunchKernelGGL((k_build_blocklist<kAttnQBlocks>), dim3(parts, lists), dim3(kBlThreads), 0, st, a);
+  hipLaunchKernelGGL((k_build_blocklist<kAttnQBlocks>), dim3(lists, parts), dim3(kBlThreads), 0, st, a);
   return hipGetLastError();
 }
 
@@ -2099,7 +2099,8 @@ hipError_t launch_attention_batch(const vs_params& p, const vs_request* req, int
   l.zero = a.queue; l.n_zero = 8 * kQueueStride;
   l.req = req; l.plan = plan; l.n_req = n_req; l.skip_single = skip_single; l.pieces = pieces;
   l.max_q_len = p.q_len; l.max_n_k = n_k;
-  hipLaunchKernelGGL((k_build_blocklist<NQB>), dim3(1, (unsigned)lists + 1), dim3(kBlThreads), 0, st, l);
+  hipLaunchKernelGGL((k_build_blocklist<NQB>), dim3((unsigned)p.n_q_heads, (unsigned)n_req + 1), dim3(kBlThreads), 0, st, l);
+  if ((e = hipGetLastError()) != hipSuccess) return e;   // (what follows goes by the plan and the lists)
   const dim3 grid((unsigned)a.n_wg), block(128 * NQB);
   const dim3 cgrid((unsigned)(ceil_div(pieces, 2) * (kTileRows / (4096 / p.head_dim))));   // split units: two pieces or more
   if (p.head_dim == 128) {

@@ -115,6 +115,18 @@ def test_plans_over_many_requests(n_req):
     _check(reqs, a, skip=(skipped,))
 
 
+def test_more_lists_than_a_launch_takes_along_y():
+    hq, hkv, d, bv, bs, n_req = 24, 1, 64, 20, 70, 4096   # 98,304 lists (the y axis of a launch takes 65,535)
+    rng = np.random.default_rng(3250)
+    specs = [(int(rng.integers(1, 4)), int(rng.integers(0, 130)), i % 16 == 5) for i in range(n_req)]
+    reqs = _make_requests(rng, hq, hkv, d, specs, bv, bs)
+    got = _run_batch(reqs, hq, hkv, d, bv, bs)
+    lse = torch.cat([g["lse"].reshape(-1) for g in got])
+    assert not (lse == 7.0).any(), "rows that nobody wrote"
+    some = [0, 5, 2729, 2730, 2731, 4085, 4095] + rng.integers(0, n_req, 60).tolist()   # 65,536 / 24 = 2,730.7
+    _check([reqs[i] for i in some], [got[i] for i in some])
+
+
 def test_a_batch_without_any_request_to_take():
     hq, hkv, d, bv, bs = 4, 2, 64, 40, 90
     reqs = _make_requests(np.random.default_rng(3300), hq, hkv, d, [(20, 300, False), (5, 100, True)], bv, bs)
