@@ -117,8 +117,8 @@ int vs_select(const vs_params *p, const float *vscore, const float *sscore,
  * hand over: code under HIP graph capture, tight serving loops, harnesses that forbid
  * hipMalloc.  Same arguments, outputs and results as vs_select, minus the workspace:
  * the rows' candidate lists live in a device array inside the library, 12 MB on
- * every GPU the library runs on, for the life of the process (lists that do not fit
- * it are made per row, more slowly).  The call allocates and frees nothing and
+ * every GPU the library runs on, for the life of the process (where the lists do not
+ * fit it, the rows take other routes, more slowly).  The call allocates and frees nothing and
  * writes what it reads with its own kernels.  Limits: n_q_heads <= 128 (VS_ERR_TOO_LARGE beyond, checked
  * on the host before any device work).  All calls on one GPU share the array:
  * calls that may overlap in time on one GPU (two streams, two threads) race --

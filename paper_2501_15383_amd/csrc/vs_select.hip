@@ -19,6 +19,9 @@
 //               scores is the floor itself: the compaction then reads the row, as far as it has to.
 //   the row     where the sample missed, or the list does not fit, every digit and the compaction read the
 //               row again: exact in every case.
+// Long rows with large budgets (lists longer than sel_most_candidates) are cut into slices, one workgroup each, that read the
+// scores once per digit of 8 bits, once for the counts and once for the compaction (k_slice_*): the list would be one
+// workgroup's work.
 // Measured on one MI355X, 28 heads, budgets 1000 / 6096, against four digits, a count and a write pass over all
 // scores in seven launches: 8,192 scores per row 14 us (67), 32,768 21 us (70), 300,001 57 us (152), 1M 108 us
 // (345: filter 63 us = 3.7 TB/s, sample 16, rows 29); 4 heads, budgets 128 / 256, 1M: 50 us (98).
@@ -36,6 +39,13 @@ constexpr int kSelStep = 8;                    // scores per lane and step where
 constexpr int kSelOwnKeys = 48 * 1024;         // up to here a workgroup lists its own row's candidates: 31-35 us against
                                                // 36-38 us for the three launches at 28 heads, 22-25 us either way at 4
 constexpr int kSelBins = 2048;
+// control block of a row whose slices go through the digits together, in 32-bit words
+constexpr int kSliceMax = 64;                  // slices of a row at most
+constexpr int kWHist = 0;                      // [4][256] histogram of every digit
+constexpr int kWDone = 1024;                   // [4] workgroups done with the digit
+constexpr int kWState = 1028;                  // [5][2] (prefix, entries still to find) before digit 0..3 and after
+constexpr int kWCount = 1056;                  // [slices][2] keys > T, keys == T
+constexpr int kSliceRowWords = kWCount + 2 * kSliceMax;
 // workspace of a row: header, table of slices, candidates
 struct SelHeader {
   uint32_t floor_key;  // entries above it are candidates
@@ -68,6 +78,9 @@ struct SelArgs {
   uint32_t cap;
   int32_t n_slices;
   int32_t samples_v, samples_s;  // samples per thread for the rows of each kind
+  // rows in slices
+  uint32_t* ctl;       // [2 Hq][kSliceRowWords]
+  int64_t slice_len;   // a multiple of kSelStep * kSelThreads
 };
 
 // row = kind * Hq + h
@@ -610,6 +623,188 @@ __global__ __launch_bounds__(kSelFilterThreads) void k_sel_filter(const SelArgs 
   }
 }
 
+// ---- rows in slices ---------------------------------------------------------------------------
+constexpr int64_t kSliceStep = (int64_t)kSelStep * kSelThreads;
+
+// Forced entries, padding, the count, and a cleared control block.
+__global__ __launch_bounds__(256) void k_slice_init(const SelArgs a) {
+  const SelRow r = sel_row(a, blockIdx.x);
+  uint32_t* const ctl = a.ctl + (int64_t)blockIdx.x * kSliceRowWords;
+  const int tid = threadIdx.x;
+  for (int x = tid; x < kSliceRowWords; x += 256) ctl[x] = x == kWState + 1 ? r.kp : 0u;
+  for (int t = tid; t < r.row_len; t += 256) {
+    if (t < r.f) r.out[t] = t;
+    else if (t >= r.k) r.out[t] = -1;
+  }
+  if (tid == 0) (r.kind ? a.s_cnt : a.v_cnt)[r.h] = r.k;
+}
+
+// One digit of the radix select: threshold key T = kp-th largest key among the candidates.
+__global__ __launch_bounds__(kSelThreads) void k_slice_digit(const SelArgs a, const int pass) {
+  const SelRow r = sel_row(a, blockIdx.y);
+  uint32_t* const ctl = a.ctl + (int64_t)blockIdx.y * kSliceRowWords;
+  if (r.kp == 0) return;
+  const int64_t lo = (int64_t)r.f + (int64_t)blockIdx.x * a.slice_len;
+  const int64_t hi = lo + a.slice_len < a.n ? lo + a.slice_len : a.n;
+  const uint32_t prefix = ctl[kWState + 2 * pass], krem = ctl[kWState + 2 * pass + 1];
+  const int tid = threadIdx.x, lane = tid & 63;
+  // 16 copies of the 256-bin histogram, copy = lane % 16 in consecutive banks: the top digits of
+  // real scores crowd into a few bins, and 64 lanes adding to one address would serialise
+  __shared__ uint32_t hist16[256 * 16];
+  __shared__ uint32_t hist[256];
+  __shared__ bool last;
+  const int shift = 24 - 8 * pass;
+  const uint32_t himask = pass == 0 ? 0u : (0xFFFFFFFFu << (shift + 8));
+  for (int x = tid; x < 256 * 16; x += kSelThreads) hist16[x] = 0;
+  __syncthreads();
+  // kSelStep independent loads per thread in flight (the pass is latency-bound otherwise)
+  for (int64_t base = lo; base < hi; base += kSliceStep) {
+    uint32_t key[kSelStep];
+    bool ok[kSelStep];
+#pragma unroll
+    for (int e = 0; e < kSelStep; ++e) {
+      const int64_t i = base + (int64_t)e * kSelThreads + tid;
+      ok[e] = i < hi;
+      key[e] = order_key(r.sc[ok[e] ? i : hi - 1]);  // unconditional, so that the loads overlap
+    }
+#pragma unroll
+    for (int e = 0; e < kSelStep; ++e)
+      if (ok[e] && (key[e] & himask) == prefix)
+        atomicAdd(&hist16[(((key[e] >> shift) & 255u) << 4) | (lane & 15)], 1u);
+  }
+  __syncthreads();
+  uint32_t* const gh = ctl + kWHist + 256 * pass;
+  // The additions and the ticket are device-wide atomics, performed where all workgroups see
+  // them.  The additions return a value, and the wait for it is the wait for their completion;
+  // only then does the workgroup draw its ticket, so the one that draws the last ticket finds
+  // every addition done.  (No cache is involved: a fence would write back the whole L2.)
+  if (tid < 256) {
+    uint32_t c = 0;
+#pragma unroll
+    for (int x = 0; x < 16; ++x) c += hist16[(tid << 4) | x];
+    uint32_t old = 0;
+    if (c) old = __hip_atomic_fetch_add(&gh[tid], c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    asm volatile("s_waitcnt vmcnt(0)" : "+v"(old) : : "memory");
+  }
+  __syncthreads();
+  if (tid == 0)
+    last = __hip_atomic_fetch_add(&ctl[kWDone + pass], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
+  __syncthreads();
+  if (!last) return;
+  if (tid < 256) hist[tid] = __hip_atomic_load(&gh[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __syncthreads();
+  if (tid == 0) {
+    uint32_t cum = 0;
+    int b = 255;
+    for (; b > 0; --b) {
+      const uint32_t c = hist[b];
+      if (cum + c >= krem) break;
+      cum += c;
+    }
+    ctl[kWState + 2 * (pass + 1)] = prefix | ((uint32_t)b << shift);
+    ctl[kWState + 2 * (pass + 1) + 1] = krem - cum;
+  }
+}
+
+// Keys above and equal to the threshold in every slice.
+__global__ __launch_bounds__(kSelThreads) void k_slice_count(const SelArgs a) {
+  const SelRow r = sel_row(a, blockIdx.y);
+  uint32_t* const ctl = a.ctl + (int64_t)blockIdx.y * kSliceRowWords;
+  if (r.kp == 0) return;
+  const int64_t lo = (int64_t)r.f + (int64_t)blockIdx.x * a.slice_len;
+  const int64_t hi = lo + a.slice_len < a.n ? lo + a.slice_len : a.n;
+  const uint32_t T = ctl[kWState + 8];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  __shared__ uint32_t wtot[kSelWaves][2];
+  uint32_t tg = 0, te = 0;
+  for (int64_t base = lo; base < hi; base += kSliceStep) {
+    uint32_t key[kSelStep];
+#pragma unroll
+    for (int e = 0; e < kSelStep; ++e) {
+      const int64_t i = base + (int64_t)e * kSelThreads + tid;
+      key[e] = order_key(r.sc[i < hi ? i : hi - 1]);
+    }
+#pragma unroll
+    for (int e = 0; e < kSelStep; ++e) {
+      const bool in = base + (int64_t)e * kSelThreads + tid < hi;
+      tg += __popcll(__ballot(in && key[e] > T));
+      te += __popcll(__ballot(in && key[e] == T));
+    }
+  }
+  if (lane == 0) { wtot[wv][0] = tg; wtot[wv][1] = te; }
+  __syncthreads();
+  if (tid == 0) {
+    uint32_t g = 0, e = 0;
+    for (int w = 0; w < kSelWaves; ++w) { g += wtot[w][0]; e += wtot[w][1]; }
+    ctl[kWCount + 2 * blockIdx.x] = g;
+    ctl[kWCount + 2 * blockIdx.x + 1] = e;
+  }
+}
+
+// Ordered compaction of one slice.
+__global__ __launch_bounds__(kSelThreads) void k_slice_write(const SelArgs a) {
+  const SelRow r = sel_row(a, blockIdx.y);
+  const uint32_t* const ctl = a.ctl + (int64_t)blockIdx.y * kSliceRowWords;
+  const uint32_t kp = r.kp;
+  if (kp == 0) return;
+  const int f = r.f;
+  const int64_t lo = (int64_t)f + (int64_t)blockIdx.x * a.slice_len;
+  const int64_t hi = lo + a.slice_len < a.n ? lo + a.slice_len : a.n;
+  const uint32_t T = ctl[kWState + 8];
+  const uint32_t need_eq = ctl[kWState + 9];  // >= 1
+  int32_t* const out = r.out;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  __shared__ uint32_t wtot[2][kSelWaves][2];
+  uint32_t run_gt = 0, run_eq = 0;  // totals over everything before this slice, then before the step
+  for (int sl = 0; sl < (int)blockIdx.x; ++sl) {
+    run_gt += ctl[kWCount + 2 * sl];
+    run_eq += ctl[kWCount + 2 * sl + 1];
+  }
+  if (run_gt + (run_eq < need_eq ? run_eq : need_eq) >= kp) return;  // the row is complete already
+  const uint64_t lt_mask = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+  int par = 0;
+  for (int64_t base = lo; base < hi; base += kSliceStep, par ^= 1) {
+    uint64_t bg[kSelStep], be[kSelStep];
+    uint32_t tg = 0, te = 0, keys[kSelStep];
+#pragma unroll
+    for (int e = 0; e < kSelStep; ++e) {
+      const int64_t i = base + (int64_t)wv * (64 * kSelStep) + e * 64 + lane;
+      keys[e] = order_key(r.sc[i < hi ? i : hi - 1]);
+    }
+#pragma unroll
+    for (int e = 0; e < kSelStep; ++e) {
+      const int64_t i = base + (int64_t)wv * (64 * kSelStep) + e * 64 + lane;
+      const uint32_t key = keys[e];
+      bg[e] = __ballot(i < hi && key > T);
+      be[e] = __ballot(i < hi && key == T);
+      tg += __popcll(bg[e]);
+      te += __popcll(be[e]);
+    }
+    if (lane == 0) { wtot[par][wv][0] = tg; wtot[par][wv][1] = te; }
+    __syncthreads();
+    uint32_t gt_before = run_gt, eq_before = run_eq, cg = 0, ce = 0;
+    for (int w = 0; w < kSelWaves; ++w) {
+      const uint32_t g_ = wtot[par][w][0], e_ = wtot[par][w][1];
+      if (w < wv) { gt_before += g_; eq_before += e_; }
+      cg += g_; ce += e_;
+    }
+#pragma unroll
+    for (int e = 0; e < kSelStep; ++e) {
+      const int64_t i = base + (int64_t)wv * (64 * kSelStep) + e * 64 + lane;
+      const uint32_t gr = gt_before + __popcll(bg[e] & lt_mask);
+      const uint32_t er = eq_before + __popcll(be[e] & lt_mask);
+      const bool is_g = (bg[e] >> lane) & 1ull, is_e = (be[e] >> lane) & 1ull;
+      if (is_g) out[f + gr + (er < need_eq ? er : need_eq)] = (int32_t)i;
+      else if (is_e && er < need_eq) out[f + gr + er] = (int32_t)i;
+      gt_before += __popcll(bg[e]);
+      eq_before += __popcll(be[e]);
+    }
+    run_gt += cg;
+    run_eq += ce;
+    if (run_gt + (run_eq < need_eq ? run_eq : need_eq) >= kp) break;
+  }
+}
+
 // Entries that a row's list may get: what is to be expected from the sample and 4.5 sigma of it to spare.
 static int64_t sel_list_len(int64_t n, int32_t budget, int spt) {
   const float s = (float)(spt * kSelThreads), rank = sel_sample_rank((float)budget, (float)n, s);
@@ -621,12 +816,25 @@ static int64_t sel_list_len(int64_t n, int32_t budget, int spt) {
 static int sel_samples(int64_t n, int32_t budget) {
   return n <= kSelRegKeys ? 0 : (sel_list_len(n, budget, 8) <= kSelCand ? 8 : 16);
 }
+// The longest list that is worth making.  The row's one workgroup takes about 1.45 us per 1,000 candidates, and the slices
+// read the scores seven times.  Measured over 1 to 64 heads, 50,000 to 4M keys and 8,000 to 106,000 candidates, with lists
+// against in slices (us): break-even at 26,000 candidates for two rows of 50,000 keys (70), 33,000 for 56 (90), 39,000 for two
+// of 1M (88), 52,000 for eight of 1M (118), 74,000 for 56 of 300,001 (170); the line below stays under these.  (56 rows of 1M
+// keys, budgets 50,000 / 300,000: 835 with lists, 419 in slices.)
+static int64_t sel_most_candidates(int64_t n, int rows) {
+  const int64_t most = 24000 + (int64_t)((double)n * rows * 2.5e-3);
+  return most < 65536 ? most : 65536;
+}
 struct SelLayout {
   size_t slices, cand, total;
   int32_t n_slices;
   uint32_t cap;
   int samples_v, samples_s;
+  bool sliced;
 };
+static size_t sel_ctl_bytes(const vs_params& p) {
+  return align_up((size_t)2 * p.n_q_heads * kSliceRowWords * sizeof(uint32_t), 256);
+}
 static SelLayout sel_layout(const vs_params& p) {
   SelLayout l;
   const int64_t n = p.q_start + p.q_len;
@@ -638,26 +846,43 @@ static SelLayout sel_layout(const vs_params& p) {
   l.cap = (uint32_t)(cv > cs ? cv : cs);
   l.slices = align_up(rows * sizeof(SelHeader), 256);
   l.cand = l.slices + align_up(rows * (size_t)l.n_slices * sizeof(uint2), 256);
-  l.total = l.samples_v ? l.cand + align_up(rows * l.cap * sizeof(uint2), 256) : 256;
+  l.sliced = n > kSelOwnKeys && (int64_t)l.cap > sel_most_candidates(n, (int)rows);
+  // (rows of up to kSelOwnKeys list their own candidates in LDS)
+  l.total = n <= kSelOwnKeys ? 256 : (l.sliced ? sel_ctl_bytes(p) : l.cand + align_up(rows * l.cap * sizeof(uint2), 256));
   return l;
 }
 size_t select_ws_bytes(const vs_params& p) { return sel_layout(p).total; }
 
-// ws: ws_bytes bytes; fewer than select_ws_bytes(p), or none: every row lists its own candidates
+static hipError_t launch_slices(SelArgs a, void* ws, hipStream_t st) {
+  a.ctl = (uint32_t*)ws;
+  // whole steps of the workgroup, enough slices for about 2048 workgroups in all
+  const int rows = 2 * a.n_q_heads;
+  int64_t want = 2048 / rows;
+  want = want < 1 ? 1 : (want > kSliceMax ? kSliceMax : want);
+  a.slice_len = ceil_div(ceil_div(a.n, kSliceStep), want) * kSliceStep;
+  const dim3 grid((unsigned)ceil_div(a.n, a.slice_len), (unsigned)rows), block(kSelThreads);
+  hipLaunchKernelGGL(k_slice_init, dim3((unsigned)rows), dim3(256), 0, st, a);
+  for (int pass = 0; pass < 4; ++pass) hipLaunchKernelGGL(k_slice_digit, grid, block, 0, st, a, pass);
+  hipLaunchKernelGGL(k_slice_count, grid, block, 0, st, a);
+  hipLaunchKernelGGL(k_slice_write, grid, block, 0, st, a);
+  return hipGetLastError();
+}
+
+// ws: ws_bytes bytes.  With fewer than select_ws_bytes(p), which only the static entry point has, every row lists its own
+// candidates where the list fits the LDS; longer lists' rows go in slices (56 rows of 1M keys, 20,000 of them to choose: 371 us,
+// row by row 989).
 hipError_t launch_select(const vs_params& p, const float* vscore, const float* sscore,
                          const int32_t* v_budget_h, const int32_t* s_budget_h,
                          int32_t* v_idx, int32_t* v_cnt, int32_t* s_idx, int32_t* s_cnt, void* ws,
                          size_t ws_bytes, hipStream_t st) {
-  SelArgs a;
+  SelArgs a = {};
   a.vscore = vscore; a.sscore = sscore; a.n = p.q_start + p.q_len;
   a.n_q_heads = p.n_q_heads;
   a.v_budget = p.vertical_budget; a.s_budget = p.slash_budget;
   a.keep_v = p.keep_first_cols; a.keep_s = p.keep_local_band;
   a.v_budget_h = v_budget_h; a.s_budget_h = s_budget_h;
   a.v_idx = v_idx; a.v_cnt = v_cnt; a.s_idx = s_idx; a.s_cnt = s_cnt;
-  a.hdr = nullptr; a.slices = nullptr; a.cand = nullptr;
   const SelLayout l = sel_layout(p);
-  a.cap = 0;
   a.n_slices = l.n_slices; a.samples_v = l.samples_v; a.samples_s = l.samples_s;
   const dim3 rows(2u * (unsigned)p.n_q_heads), block(kSelThreads);
   if (a.n <= 8 * kSelThreads) {
@@ -666,6 +891,9 @@ hipError_t launch_select(const vs_params& p, const float* vscore, const float* s
     hipLaunchKernelGGL(k_sel_row<16>, rows, block, 0, st, a);
   } else if (a.n <= kSelRegKeys) {
     hipLaunchKernelGGL(k_sel_row<32>, rows, block, 0, st, a);
+  } else if (l.sliced || (a.n > kSelOwnKeys && ws_bytes < l.total && l.cap > kSelCand)) {
+    if (!ws || ws_bytes < sel_ctl_bytes(p)) return hipErrorInvalidValue;
+    return launch_slices(a, ws, st);
   } else {
     static DeviceOnce once;   // the opt-in to more than 64 KiB of LDS
     const hipError_t e = once.run([]() {
@@ -689,7 +917,8 @@ hipError_t launch_select(const vs_params& p, const float* vscore, const float* s
 
 // ---- the selection for callers that cannot allocate ------------------------------------------
 // vs_select_static: the headers, tables and candidate lists of the rows live in a file-scope device array instead of a
-// caller workspace, where they fit (28 heads at 1M keys take 7 MB); beyond that every row lists its own candidates.
+// caller workspace, where they fit (28 heads at 1M keys take 7 MB); beyond that every row lists its own candidates, or goes
+// in slices (launch_select).
 // Every device the library runs on holds its own copy of the array at its own address until the process ends; in host
 // code the array's name is only a handle, the address comes from hipGetSymbolAddress, once per device, with that
 // device current.  A call writes what it reads, so it never sees the contents the call before it left behind; calls

@@ -52,3 +52,18 @@ def test_select_equals_a_full_sort(n, kind):
         for sets in (vs.select(ck, vsc, ssc), vs.select_static(ck, vsc, ssc, vs.alloc_index_sets(ck, vsc.device))):
             for a, b, nm in zip(sets, want, ("v_idx", "v_cnt", "s_idx", "s_cnt")):
                 assert torch.equal(a, b), f"{nm}: n {n}, {kind}, budgets {bv} / {bs}"
+
+
+# (heads, keys, offsets kept): lists in the workspace that fit the LDS, that do not, and that are not made (slices); of the
+# static entry point, whose scratch holds 12 MB, the first as well, rows that list their own candidates, and slices
+@pytest.mark.parametrize("kind", ["spread", "ties", "sparse", "signed"])
+@pytest.mark.parametrize("hq,n,bs", [(3, 131071, 9000), (3, 131071, 20000), (3, 131071, 26000), (128, 100000, 6096),
+                                     (64, 100000, 16000), (2, 3000001, 40000)])
+def test_every_route_of_long_rows(hq, n, bs, kind):
+    g = torch.Generator(device="cuda:0").manual_seed(200 + n + bs)
+    vsc, ssc = _scores(kind, hq, n, g), _scores(kind, hq, n, g)
+    ck = vs.Chunk(hq, 1, 128, 64, n - 64, 0.1, vertical_budget=700, slash_budget=bs, keep_first_cols=1, keep_local_band=64)
+    want = (*_want(vsc, 700, 1), *_want(ssc, bs, 64))
+    for sets in (vs.select(ck, vsc, ssc), vs.select_static(ck, vsc, ssc, vs.alloc_index_sets(ck, vsc.device))):
+        for a, b, nm in zip(sets, want, ("v_idx", "v_cnt", "s_idx", "s_cnt")):
+            assert torch.equal(a, b), f"{nm}: {hq} heads, n {n}, {kind}, {bs} offsets"
