@@ -16,7 +16,9 @@
 //               kSelCand of them.  With a workspace the whole chip makes the lists, in one pass over the scores
 //               (k_sel_sample, k_sel_filter; bound by that read at 1M keys); for rows of up to kSelOwnKeys, and
 //               without a workspace, k_sel_row makes its row's own.  A threshold that falls on a crowd of equal
-//               scores is the floor itself: the compaction then reads the row, as far as it has to.
+//               scores is the floor itself: all candidates are wanted, and of the crowd its first entries, for which the row
+//               is read until it has them (28 heads, 1M keys of which 2,097 are not zero, 6,096 wanted: 485 us with the row
+//               read to its end, 125 so).
 //   the row     where the sample missed, or the list does not fit, every digit and the compaction read the
 //               row again: exact in every case.
 // Long rows with large budgets (lists longer than sel_most_candidates) are cut into slices, one workgroup each, that read the
@@ -388,8 +390,11 @@ __device__ __forceinline__ void sel_walk_row(const SelRow& r, int64_t n, Step&& 
   }
 }
 
-// The ordered compaction of a row whose threshold is known.
-__device__ __forceinline__ void sel_compact_row(SelShared& sh, const SelRow& r, int64_t n, uint32_t T, uint32_t need_eq) {
+// The ordered compaction of a row whose threshold is known, as far as the row has to be read: until it is complete or, where a
+// list holds the keys > T (`listed`), until the equal ones are (the smallest scores, if most of a row's are the same: a few
+// thousand entries).  Returns how many of the keys > T it has met.
+template <bool listed>
+__device__ __forceinline__ uint32_t sel_compact_row(SelShared& sh, const SelRow& r, int64_t n, uint32_t T, uint32_t need_eq) {
   uint32_t run_g = 0, run_e = 0;
   sel_walk_row(r, n, [&](const uint32_t (&key)[kSelStep], int32_t i0, int par) {
     uint32_t g = 0, q = 0;
@@ -404,8 +409,45 @@ __device__ __forceinline__ void sel_compact_row(SelShared& sh, const SelRow& r, 
     for (int e = 0; e < kSelStep; ++e) sel_emit(r, need_eq, key[e] > T, key[e] == T, i0 + 64 * e, gt, eq);
     run_g += all_g;
     run_e += all_e;
+    if (listed) return run_e < need_eq;
     return run_g + (run_e < need_eq ? run_e : need_eq) < r.kp;   // else the row is complete
   });
+  return run_g;
+}
+
+// The candidates of a row from number `from` of the order on, for a row all of whose candidates are wanted, behind `equal` other
+// entries.  1,024 slices at a time: their places in the order, then 16 lanes per slice.
+template <typename SliceOf>
+__device__ __forceinline__ void sel_copy_candidates(SelShared& sh, const uint2* cl, const SelRow& r, int n_slices, uint32_t from,
+                                                    uint32_t equal, SliceOf&& slice_of) {
+  static_assert(kSelBins == 2 * kSelThreads, "two words per thread");
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  uint32_t before = 0;   // candidates of the slices before this round's
+  for (int sb = 0; sb < n_slices; sb += kSelThreads) {
+    const uint2 mine = sb + tid < n_slices ? slice_of(sb + tid) : make_uint2(0u, 0u);
+    uint32_t inc = mine.y;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const uint32_t y = __shfl_up(inc, d);
+      if (lane >= d) inc += y;
+    }
+    __syncthreads();   // (the last readers of wsum and hist)
+    if (lane == 63) sh.wsum[wv] = inc;
+    __syncthreads();
+    uint32_t at = before + inc - mine.y;
+    for (int x = 0; x < kSelWaves; ++x) {
+      at += x < wv ? sh.wsum[x] : 0u;
+      before += sh.wsum[x];
+    }
+    sh.hist[tid] = at;
+    sh.hist[kSelThreads + tid] = mine.x;
+    __syncthreads();
+    for (int t = tid >> 4; t < kSelThreads; t += kSelThreads / 16) {
+      const uint32_t a = sh.hist[t], end = t + 1 < kSelThreads ? sh.hist[t + 1] : before, first = sh.hist[kSelThreads + t];
+      uint32_t i = (a < from ? from : a) + (tid & 15);
+      for (; i < end; i += 16) r.out[r.f + equal + i] = (int32_t)cl[first + (i - a)].y;
+    }
+  }
 }
 
 // A row read from memory for its range, once per digit and once more for the compaction.
@@ -427,7 +469,7 @@ __device__ __forceinline__ void sel_from_row(SelShared& sh, const SelRow& r, int
       return true;
     });
   }, r.kp, lo + 1u, hi, T, need_eq);
-  sel_compact_row(sh, r, n, T, need_eq);
+  sel_compact_row<false>(sh, r, n, T, need_eq);
 }
 
 // The floor of a row's candidates: one score from each of SPT x kSelThreads stretches of the row (at a place inside its
@@ -511,14 +553,17 @@ __global__ __launch_bounds__(kSelThreads) void k_sel_row(const SelArgs a) {
       __syncthreads();
     }
     const int m = (int)hd.count;
+    const uint2* const cand = a.cand + (int64_t)blockIdx.x * a.cap;
+    const uint2* const slices = a.slices + (int64_t)blockIdx.x * a.n_slices;
+    auto slice_of = [&](int s) { return slices[s]; };
     if (hd.count > room || hd.count + hd.equal < r.kp) {   // the sample missed
       sel_from_row(sh, r, a.n);
     } else if (hd.count < r.kp) {   // the threshold is the floor
-      sel_compact_row(sh, r, a.n, hd.floor_key, r.kp - hd.count);
+      const uint32_t equal = r.kp - hd.count, met = sel_compact_row<true>(sh, r, a.n, hd.floor_key, equal);
+      if (listed) sel_copy_candidates(sh, cand, r, a.n_slices, met, equal, slice_of);
+      else
+        for (int i = (int)met + tid; i < m; i += kSelThreads) r.out[r.f + equal + i] = (int32_t)cl[i].y;
     } else if (listed) {
-      const uint2* const cand = a.cand + (int64_t)blockIdx.x * a.cap;
-      const uint2* const slices = a.slices + (int64_t)blockIdx.x * a.n_slices;
-      auto slice_of = [&](int s) { return slices[s]; };
       if (m <= kSelCand) {
 #pragma unroll
         for (int e = 0; e < kSelCand / kSelThreads; ++e) {
