@@ -153,6 +153,8 @@ __device__ __forceinline__ void sel_range(SelShared& sh, uint32_t lo, uint32_t h
 // kp >= 1): keys above T, and need_eq of those equal to it, are the kp largest.  Digits of 11 bits from the top of the range
 // hi - lo, so that keys that share their exponent still spread over the bins (scores do: with digits of the
 // whole key a wave's 64 additions met in four bins, 65 to 250 clocks each); done as soon as a bin is taken whole.
+// Keys equal to lo are not counted, their bin has whatever the others leave of kp: a crowd of the smallest score (zeros) would
+// queue for it (32,768 scores, 2 in 1,000 of them not zero: 102 us counted, 25 so).
 // Called by the whole workgroup; every thread gets the result.
 template <typename ForEach>
 __device__ __forceinline__ void radix_kth(SelShared& sh, ForEach&& for_each, uint32_t kp, uint32_t lo, uint32_t hi, uint32_t& T,
@@ -170,11 +172,13 @@ __device__ __forceinline__ void radix_kth(SelShared& sh, ForEach&& for_each, uin
     __syncthreads();
     for_each([&](uint32_t key, bool valid) {
       const uint32_t d = key - lo;
-      if (valid && (first || (d >> shift) == prefix)) atomicAdd(&sh.hist[(d >> sh0) & dmask], 1u);
+      if (valid && d != 0u && (first || (d >> shift) == prefix)) atomicAdd(&sh.hist[(d >> sh0) & dmask], 1u);
     });
     __syncthreads();
     // bins from the top: thread t takes the bins 2047 - 2 t and 2046 - 2 t
-    const uint32_t c0 = sh.hist[kSelBins - 1 - 2 * tid], c1 = sh.hist[kSelBins - 2 - 2 * tid];
+    const uint32_t c0 = sh.hist[kSelBins - 1 - 2 * tid];
+    uint32_t c1 = sh.hist[kSelBins - 2 - 2 * tid];
+    if (tid == kSelThreads - 1 && prefix == 0) c1 = 0x7FFFFFFFu;   // the bin of lo: what the others leave
     uint32_t inc = c0 + c1;
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) {
@@ -507,7 +511,8 @@ __global__ __launch_bounds__(kSelThreads) void k_sel_row(const SelArgs a) {
   __shared__ SelShared sh;
   extern __shared__ __attribute__((aligned(16))) unsigned char sel_dyn[];
   const int tid = threadIdx.x;
-  const SelRow r = sel_row(a, blockIdx.x);
+  SelRow r = sel_row(a, blockIdx.x);
+  if (r.k == a.n) { r.f = r.k; r.kp = 0; }   // the row is wanted whole
   for (int t = tid; t < r.row_len; t += kSelThreads) {
     if (t < r.f) r.out[t] = t;
     else if (t >= r.k) r.out[t] = -1;
