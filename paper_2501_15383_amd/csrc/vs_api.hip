@@ -44,7 +44,7 @@ int check_ws(const void* ws, size_t have, size_t need) {
 }
 
 size_t sparse_ws_bytes(const vs_params& p, bool dense) {
-  const size_t own = blocklist_bytes(p, dense) + attn_sync_bytes(p, dense) + attn_split_bytes(p, dense);
+  const size_t own = blocklist_bytes(p, dense) + attn_sync_bytes(p) + attn_split_bytes(p, dense);
   // (a single token without DCA is the decode kernel's, with DCA the tile kernel's: room for either)
   if (p.q_len == 1 && decode_fits(p)) {
     const size_t dec = decode_bytes(p, 1, !dense);
@@ -311,7 +311,7 @@ int sparse_attn(const vs_params* p, const void* q, const vs_dca* dca, const void
   hipError_t e = launch_build_blocklist(*p, s_idx, s_cnt, false, bl, sync, st);
   if (e != hipSuccess) return VS_ERR_HIP;
   return hip_status(launch_attention(*p, q, dca ? &da : nullptr, k, v, v_idx, v_cnt, false, bl, out, lse, sync,
-                                     sync + attn_sync_bytes(*p, false), st));
+                                     sync + attn_sync_bytes(*p), st));
 }
 
 int dense_attn(const vs_params* p, const void* q, const vs_dca* dca, const void* k, const void* v,
@@ -334,7 +334,7 @@ int dense_attn(const vs_params* p, const void* q, const vs_dca* dca, const void*
   hipError_t e = launch_build_blocklist(*p, nullptr, nullptr, true, bl, sync, st);
   if (e != hipSuccess) return VS_ERR_HIP;
   return hip_status(launch_attention(*p, q, dca ? &da : nullptr, k, v, nullptr, nullptr, true, bl, out, lse, sync,
-                                     sync + attn_sync_bytes(*p, true), st));
+                                     sync + attn_sync_bytes(*p), st));
 }
 }  // namespace
 

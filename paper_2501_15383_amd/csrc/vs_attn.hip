@@ -67,10 +67,6 @@ struct AttnArgs {
   int32_t n_split, n_units, n_whole, first_piece;
   float* part_o;
   float* part_ml;
-  // where the slots from n_first_slots on lie
-  float* more_o;
-  float* more_ml;
-  int32_t n_first_slots;
   // SPLIT: query heads of one KV group that share a tile (1, 2 or 4).  Chunks whose rows lie in one query block leave
   // half of a tile's waves (three quarters: at most 32 rows) without rows; these waves take further heads.
   // n_hs: tiles per KV group = ceil(group / pack)
@@ -133,7 +129,6 @@ struct AttnArgs {
   int32_t skip_single;   // BATCH: single tokens are the decode kernel's
 };
 
-constexpr int kOptSplit = 16;                      // most ranges that VS_OPT_ATTN_KEY_SPLIT asks for
 constexpr int kMaxSplit = 128;                     // ranges of a unit at most
 constexpr int kMinSteps = 8;                       // steps of a range at least
 constexpr double kPieceSteps = 4.0;                // what a piece costs beside its walk, in steps
@@ -208,7 +203,6 @@ __device__ __forceinline__ bool batch_view(const AttnArgs& a0, int r, AttnArgs& 
   a.pack = b.pack; a.n_hs = b.n_hs; a.n_qtiles = b.n_qtiles; a.n_units = b.n_units;
   a.n_whole = a.n_split == 1 ? b.n_units : 0;
   a.first_piece = 0;
-  a.n_first_slots = INT32_MAX;
   if (b.same_pos) {
     a.q_stride_tok = a0.q_stride_head; a.q_stride_head = (int64_t)a0.group * a0.q_stride_head;
     a.o_stride_tok = a0.o_stride_head; a.o_stride_head = (int64_t)a0.group * a0.o_stride_head;
@@ -1132,10 +1126,9 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
     // this piece's share of the row: accumulators and row sum relative to the reference m_o
     const int64_t ro = row - a.row_pad;
     if (head_ok && ro >= 0 && ro < a.q_rows) {
-      const bool more = slot >= a.n_first_slots;
-      const int64_t pr = (int64_t)(more ? slot - a.n_first_slots : slot) * kTileRows + 32 * wv + (lane & 31);
-      float* op = (more ? a.more_o : a.part_o) + pr * D;
-      float* mlp = (more ? a.more_ml : a.part_ml) + pr * 2;
+      const int64_t pr = (int64_t)slot * kTileRows + 32 * wv + (lane & 31);
+      float* op = a.part_o + pr * D;
+      float* mlp = a.part_ml + pr * 2;
 #pragma unroll
       for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -1659,23 +1652,15 @@ static AttnCut attn_cut(const vs_params& p, bool dense, int forced) {
   return c;
 }
 static AttnCut attn_cut(const vs_params& p, bool dense) { return attn_cut(p, dense, g_key_split.load(std::memory_order_relaxed)); }
-// Partial results of `ranges` ranges.  Those of the first kOptSplit ranges (as many as the option can ask for) have a place
-// whose size follows the option; those of the further ones, which only the automatic choice makes, one that does not.
-static size_t part_bytes(const vs_params& p, const AttnCut& c, int ranges) {
-  if (!c.queue || c.n_split == 1 || ranges < 1) return 0;
-  const size_t rows = (size_t)(c.n_units - c.n_whole) * ranges * kTileRows;
-  return align_up(rows * p.head_dim * sizeof(float), 256) + align_up(rows * 2 * sizeof(float), 256);
-}
-static int first_ranges(const AttnCut& c) { return c.n_split < kOptSplit ? c.n_split : kOptSplit; }
+// Partial results of the cut units: a tile's rows for every range.
 size_t attn_split_bytes(const vs_params& p, bool dense) {
   const AttnCut c = attn_cut(p, dense);
-  return part_bytes(p, c, first_ranges(c));
+  if (!c.queue || c.n_split == 1) return 0;
+  const size_t rows = (size_t)(c.n_units - c.n_whole) * c.n_split * kTileRows;
+  return align_up(rows * p.head_dim * sizeof(float), 256) + align_up(rows * 2 * sizeof(float), 256);
 }
-// counters, schedule, partial results beyond the first kOptSplit ranges
-size_t attn_sync_bytes(const vs_params& p, bool dense) {
-  const AttnCut c = attn_cut(p, dense, 0);
-  return attn_counter_bytes(p) + attn_sched_bytes(p) + part_bytes(p, c, c.n_split - kOptSplit);
-}
+// counters, schedule
+size_t attn_sync_bytes(const vs_params& p) { return attn_counter_bytes(p) + attn_sched_bytes(p); }
 
 // out = sum_s O_s 2^(m_s - M) / sum_s l_s 2^(m_s - M), M = max_s m_s; D / 4 lanes per row of a tile,
 // pieces folded in ascending order (fixed, so the result is run-to-run identical).
@@ -1732,29 +1717,21 @@ __global__ __launch_bounds__(256) void k_attn_combine(const AttnArgs a0) {
   if (row < 0 || row >= a.q_rows || h - g * a.group + th >= a.group) continue;
   const int hw = h + th;
   const int64_t at = (int64_t)e * kTileRows + lrow, step = (int64_t)n_fold * kTileRows;
-  const int n_first = BATCH || a.n_split < kOptSplit ? a.n_split : kOptSplit, n_more = a.n_split - n_first;
   float M = -INFINITY;
-  auto highest = [&](const float* ml, int n) {
 #pragma unroll 4
-    for (int sp = 0; sp < n; ++sp) M = fmaxf(M, ml[2 * (at + step * sp)]);
-  };
-  highest(a.part_ml, n_first);
-  if (!BATCH) highest(a.more_ml, n_more);
+  for (int sp = 0; sp < a.n_split; ++sp) M = fmaxf(M, a.part_ml[2 * (at + step * sp)]);
   const float M0 = M == -INFINITY ? 0.f : M;
   float L = 0.f;
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  auto fold = [&](const float* po, const float* ml, int n) {
 #pragma unroll 4
-    for (int sp = 0; sp < n; ++sp) {
-      const float w = __builtin_amdgcn_exp2f(ml[2 * (at + step * sp)] - M0);   // a piece without live keys: 0, and zeros in its slot
-      const f32x4 o = *(const f32x4*)(po + (at + step * sp) * D + d);
-      L += ml[2 * (at + step * sp) + 1] * w;
+  for (int sp = 0; sp < a.n_split; ++sp) {
+    const float* const ml = a.part_ml + 2 * (at + step * sp);
+    const float w = __builtin_amdgcn_exp2f(ml[0] - M0);   // a piece without live keys: 0, and zeros in its slot
+    const f32x4 o = *(const f32x4*)(a.part_o + (at + step * sp) * D + d);
+    L += ml[1] * w;
 #pragma unroll
-      for (int x = 0; x < 4; ++x) acc[x] += o[x] * w;
-    }
-  };
-  fold(a.part_o, a.part_ml, n_first);
-  if (!BATCH) fold(a.more_o, a.more_ml, n_more);
+    for (int x = 0; x < 4; ++x) acc[x] += o[x] * w;
+  }
   const float inv = L > 0.f ? 1.0f / L : 0.f;
 #pragma unroll
   for (int x = 0; x < 4; ++x) acc[x] *= inv;
@@ -1962,19 +1939,13 @@ hipError_t launch_attention(const vs_params& p, const void* q, const DcaArgs* dc
   int members = ((4 / kAttnQBlocks) * n_cu) / 8;   // resident workgroups per XCD
   if (members < 1) members = 1;
   a.n_split = cut.n_split;
-  a.part_o = a.part_ml = a.more_o = a.more_ml = nullptr;
+  a.part_o = a.part_ml = nullptr;
   if (cut.queue && a.n_split > 1) {
     if (!split_ws) return hipErrorInvalidValue;
-    const size_t rows = (size_t)(a.n_units - a.n_whole) * first_ranges(cut) * kTileRows;
+    const size_t rows = (size_t)(a.n_units - a.n_whole) * a.n_split * kTileRows;
     a.part_o = (float*)split_ws;
     a.part_ml = (float*)((char*)split_ws + align_up(rows * p.head_dim * sizeof(float), 256));
-    if (cut.n_split > kOptSplit) {
-      const size_t more_rows = (size_t)(a.n_units - a.n_whole) * (cut.n_split - kOptSplit) * kTileRows;
-      a.more_o = (float*)((char*)sync_ws + attn_counter_bytes(p) + attn_sched_bytes(p));
-      a.more_ml = (float*)((char*)a.more_o + align_up(more_rows * p.head_dim * sizeof(float), 256));
-    }
   }
-  a.n_first_slots = (a.n_units - a.n_whole) * first_ranges(cut);
   a.queue = (uint32_t*)sync_ws;
   a.sync_blocks = attn_sync_blocks(p);
   a.sync_shift = 0;

@@ -116,7 +116,7 @@ struct DcaArgs {
   const void* q_inter;
   int64_t chunk, window;
 };
-// sync_ws: attn_sync_bytes(p, dense) bytes: counters, cleared by launch_build_blocklist, the schedule, more partials; split_ws:
+// sync_ws: attn_sync_bytes(p) bytes: counters, cleared by launch_build_blocklist, and the schedule; split_ws:
 // attn_split_bytes(p) bytes (may be null when that is 0); dca may be null
 hipError_t launch_attention(const vs_params& p, const void* q, const DcaArgs* dca, const void* k, const void* v,
                             const int32_t* v_idx, const int32_t* v_cnt, bool dense,
@@ -133,7 +133,7 @@ bool decode_fits(const vs_params& p);
 size_t decode_bytes(const vs_params& p, int n_req, bool lists);
 hipError_t launch_decode(const vs_params& p, const vs_request* one, const vs_request* req, int n_req, bool lists, void* ws,
                          hipStream_t st);
-size_t attn_sync_bytes(const vs_params& p, bool dense);
+size_t attn_sync_bytes(const vs_params& p);
 // key split of short chunks: bytes of partial results
 void set_attn_key_split(int n);
 void set_attn_schedule_in_turn(int on);

@@ -166,9 +166,16 @@ def test_options_and_the_workspaces_they_change():
         auto = vs.workspace_bytes(ck, vs.VS_WS_DENSE)
         vs.set_option(vs.VS_OPT_ATTN_KEY_SPLIT, 2)
         two = vs.workspace_bytes(ck, vs.VS_WS_DENSE)
-        # partial results: (D + 2) floats per row, head and range, each array rounded up to 256 bytes
-        assert two - unsplit == 2 * 4 * 64 * 128 * 4 + 2 * 4 * 64 * 2 * 4
-        assert auto - unsplit == 8 * (two - unsplit)          # 16 ranges chosen for 4 units
+        # partial results: (D + 2) floats per row of a tile and range (two tiles of 128 rows: two heads' 64 rows each), and
+        # nothing of them where nothing is split
+        assert two - unsplit == 2 * 2 * 128 * (128 + 2) * 4
+        assert auto - unsplit == 2 * 128 * 128 * (128 + 2) * 4   # 128 ranges of 8 key blocks chosen for the two tiles
+        one_block = vs.Chunk(4, 1, 128, 64, 0, 0.1, vertical_budget=8, slash_budget=70)   # no keys to split
+        vs.set_option(vs.VS_OPT_ATTN_KEY_SPLIT, 0)
+        short = vs.workspace_bytes(one_block, vs.VS_WS_DENSE)
+        vs.set_option(vs.VS_OPT_ATTN_KEY_SPLIT, 1)
+        assert vs.workspace_bytes(one_block, vs.VS_WS_DENSE) == short
+        assert unsplit < 32768   # block list of 1,025 key blocks, counters, schedule
         for bad in (-1, 17):
             with pytest.raises(vs.VsError):
                 vs.set_option(vs.VS_OPT_ATTN_KEY_SPLIT, bad)
