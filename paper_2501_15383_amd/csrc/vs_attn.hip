@@ -135,7 +135,8 @@ constexpr double kPieceSteps = 4.0;                // what a piece costs beside 
 constexpr int kBatchSlots = 512, kShortSteps = 64;  // a batch of fewer steps per slot is cut into one piece per slot: 2 requests
                                                     // of 64 rows at 46K keys 134 us -> 107
 constexpr int kMaxPieces = 2048, kBatchPieces = 1536;   // pieces with partial results: a call's, a batch's
-constexpr int kMaxQueueUnits = 4096;
+constexpr int kMaxQueueUnits = 4096;               // beyond it whole rounds are full enough; ranges that are asked for are made
+constexpr int64_t kMaxAskedUnits = 1 << 23;        // all the same (128 M pieces of 33 KB and more: no workspace holds them)
 constexpr int kPaceBlocks = 4096;                  // key blocks from which whole units keep pace (see launch_attention)
 constexpr int kRun = 64;                           // workgroup slots of an XCD: members of a pace-keeping group
 constexpr int kQueueStride = 16;                   // words between two queue counters: a cache line each
@@ -1611,7 +1612,7 @@ static AttnCut attn_cut(const vs_params& p, bool dense, int forced) {
   const int64_t units = n_qtiles * p.n_kv_heads * c.n_hs;
   const int64_t n_blk = ceil_div(p.q_start + p.q_len, kBlock);
   c.n_split = 1;
-  if (forced == 1 || units > kMaxQueueUnits) return c;
+  if (forced == 1 || units > (forced > 1 ? kMaxAskedUnits : kMaxQueueUnits)) return c;
   c.n_qtiles = (int32_t)n_qtiles;
   c.n_units = (int32_t)units;
   c.n_whole = 0;

@@ -196,12 +196,17 @@ def test_options_and_the_workspaces_they_change():
     small = vs.workspace_bytes(ck, vs.VS_WS_DENSE)
     vs.set_option(vs.VS_OPT_ATTN_KEY_SPLIT, 0)
     assert L.vs_dense_causal_prefill(C.byref(p), ok, ok, ok, ok, None, ok, small, None) == vs.VS_ERR_WORKSPACE
-    # a long chunk is never split
+    # a long chunk is not split by itself
     long_ck = vs.Chunk(28, 4, 128, 32768, 32768, 0.1, vertical_budget=8, slash_budget=70)
     vs.set_option(vs.VS_OPT_ATTN_KEY_SPLIT, 1)
     a = vs.workspace_bytes(long_ck, vs.VS_WS_DENSE)
     vs.set_option(vs.VS_OPT_ATTN_KEY_SPLIT, 0)
     assert vs.workspace_bytes(long_ck, vs.VS_WS_DENSE) == a
+    # ... unless ranges are asked for: two of each of its 256 x 28 tiles
+    vs.set_option(vs.VS_OPT_ATTN_KEY_SPLIT, 2)
+    two = vs.workspace_bytes(long_ck, vs.VS_WS_DENSE)
+    vs.set_option(vs.VS_OPT_ATTN_KEY_SPLIT, 0)
+    assert two - a == 2 * 256 * 28 * 128 * (128 + 2) * 4
     assert vs.workspace_bytes(long_ck, vs.VS_WS_SELECT) > 0
     L = vs.lib()
     ok = C.c_void_p(4096)

@@ -69,6 +69,30 @@ def test_whole_units_and_cut_ones(c, s):
         assert ((a - b).norm(dim=2) <= 2e-2 * b.norm(dim=2)).all() and (la - lb).abs().max().item() < 1e-4
 
 
+def test_ranges_that_are_asked_for_of_many_units():
+    hq, hkv, d, c, s = 1100, 10, 64, 512, 2048 + 33   # 5,500 units, 41 key blocks: two ranges of each
+    rng = np.random.default_rng(3120)
+    q = rand_bf16(rng, (c, hq, d)); k = rand_bf16(rng, (s + c, hkv, d)); v = rand_bf16(rng, (s + c, hkv, d))
+    pb = oracle.Problem(hq, hkv, d, c, s, 1.0 / np.sqrt(d))
+    got = []
+    for n in (0, 2):
+        vs.set_option(vs.VS_OPT_ATTN_KEY_SPLIT, n)
+        try:
+            got.append((vs.workspace_bytes(chunk_of(pb), vs.VS_WS_DENSE),
+                        *vs.dense_causal_prefill(chunk_of(pb), dev(q), dev(k), dev(v), want_lse=True)))
+            torch.cuda.synchronize()
+        finally:
+            vs.set_option(vs.VS_OPT_ATTN_KEY_SPLIT, 0)
+    assert got[1][0] - got[0][0] == 2 * 5500 * 128 * (d + 2) * 4
+    heads, rows = [0, 109, 110, 700, 1099], [0, 94, 95, 300, 511]
+    at = torch.tensor(rows, device="cuda")
+    ref = oracle.dense_attention(pb, q, k, v, heads=heads, rows=rows)
+    for _, out, lse in got:
+        assert_attn_close(out[at][:, heads], lse[heads][:, at], *ref, f"{hq} heads")
+    (_, a, la), (_, b, lb) = got
+    assert ((a.float() - b.float()).norm(dim=2) <= 2e-2 * b.float().norm(dim=2)).all() and (la - lb).abs().max().item() < 1e-4
+
+
 # one KV head, 64 rows and as many keys as whole units keep pace from: 515 tiles of two heads, 512 of them whole and the last
 # three cut; and the same heads behind a start inside a block (two query blocks: no sharing, 1,030 units)
 @pytest.mark.parametrize("s", [4095 * 64, 4096 * 64 + 9])
