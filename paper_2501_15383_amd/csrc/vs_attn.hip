@@ -146,10 +146,15 @@ constexpr int kTileRows = 64 * kAttnQBlocks;       // rows of a query tile, of a
 // block fill two of a tile's four waves (two SIMDs of four), at most 32 rows one; with the heads side by side all four work,
 // and K and V are copied once for them.  28 query / 4 KV heads: 64 rows at 1M keys 1,384 us -> 815 (with the finer cut and the
 // order of the pieces, see attn_cut), 4 rows at 50K keys 100 -> 46, 22 requests of up to 64 rows and 38K keys (40 heads)
-// 921 -> 308.  Heads without a group (or a second query block) have nothing to share.
-__host__ __device__ __forceinline__ int heads_per_tile(int64_t rows, int row_pad, int group) {
+// 921 -> 308.  Heads without a group (or a second query block) have nothing to share.  Gathered columns are not shared: a tile
+// walks those of its heads one after the other, so it takes as many heads as leave their steps (two per 64 columns, which
+// take the masked path) below the n_blk of the key blocks.  With four heads whatever the columns, 28 heads: 2 rows at 1,000
+// keys, as many columns, 120 us, 55 so; at 300 keys 77 and 42.
+__host__ __device__ __forceinline__ int heads_per_tile(int64_t rows, int row_pad, int group, int64_t n_blk, int64_t columns) {
   if (kAttnQBlocks != 2 || group < 2 || row_pad + rows > kBlock) return 1;
-  return rows <= 32 && group > 2 ? 4 : 2;
+  int n = rows <= 32 && group > 2 ? 4 : 2;
+  while (n > 1 && 2 * n * ((columns + 63) / 64) > n_blk) n >>= 1;
+  return n;
 }
 
 // What a request of a batch is to the launch: false for one outside the stated bounds or with a null pointer, which is
@@ -159,7 +164,7 @@ struct BatchShape {
   int32_t row_pad, pack, n_hs, n_qtiles, n_units;
 };
 __device__ __forceinline__ bool batch_shape(const vs_request& rq, int group, int n_kv_heads, int64_t max_q_len, int64_t max_n_k,
-                                            bool skip_single, BatchShape& b) {
+                                            int v_budget, bool skip_single, BatchShape& b) {
   if (!rq.q || !rq.k || !rq.v || !rq.out) return false;
   if (rq.q_len < 1 || rq.q_len > max_q_len || rq.q_start < 0 || rq.q_start + rq.q_len > max_n_k) return false;
   if (skip_single && rq.q_len == 1) return false;
@@ -168,7 +173,9 @@ __device__ __forceinline__ bool batch_shape(const vs_request& rq, int group, int
   b.row_pad = (int32_t)(rq.q_start % kBlock);
   // attention of one token: the G heads of a KV group are the rows of one tile
   b.same_pos = rq.q_len == 1 && group > 1 && b.dense;
-  b.pack = b.same_pos ? 1 : heads_per_tile(rq.q_len, b.row_pad, group);
+  const int64_t n_k = rq.q_start + rq.q_len;
+  b.pack = b.same_pos ? 1 : heads_per_tile(rq.q_len, b.row_pad, group, (n_k + kBlock - 1) / kBlock,
+                                           b.dense ? 0 : (v_budget < n_k ? v_budget : n_k));
   b.n_hs = b.same_pos ? 1 : (group + b.pack - 1) / b.pack;
   const int64_t rows = b.same_pos ? group : b.row_pad + rq.q_len;
   b.n_qtiles = (int32_t)((rows + kTileRows - 1) / kTileRows);
@@ -184,7 +191,7 @@ __device__ __forceinline__ bool batch_view(const AttnArgs& a0, int r, AttnArgs& 
   rq.s_idx = uniform64(rq.s_idx); rq.s_cnt = uniform64(rq.s_cnt);
   rq.q_start = uniform64(rq.q_start); rq.q_len = uniform64(rq.q_len);
   BatchShape b;
-  if (!batch_shape(rq, a0.group, a0.n_kv_heads, a0.max_q_len, a0.max_n_k, a0.skip_single, b)) return false;
+  if (!batch_shape(rq, a0.group, a0.n_kv_heads, a0.max_q_len, a0.max_n_k, a0.v_budget, a0.skip_single, b)) return false;
   a.q = (const __bf16*)rq.q; a.k = (const __bf16*)rq.k; a.v = (const __bf16*)rq.v;
   a.out = (__bf16*)rq.out; a.lse = rq.lse;
   a.v_idx = b.dense ? nullptr : rq.v_idx;
@@ -1237,7 +1244,7 @@ struct ListArgs {
   // a batch
   const vs_request* req;
   BatchPlan* plan;
-  int32_t n_req, skip_single, pieces;
+  int32_t n_req, skip_single, pieces, v_budget;
   int64_t max_q_len, max_n_k;
 };
 // Steps (64-key blocks, columns at twice their number: they take the masked path) that a tile of the request walks, for the
@@ -1256,7 +1263,7 @@ __device__ void write_plan(const ListArgs& a, int64_t* scan) {
   constexpr int NW = kBlThreads / 64;
   auto look = [&](int r, BatchShape& b, int64_t& steps) -> bool {
     const vs_request rq = a.req[r];
-    if (!batch_shape(rq, a.group, a.n_heads / a.group, a.max_q_len, a.max_n_k, a.skip_single, b)) return false;
+    if (!batch_shape(rq, a.group, a.n_heads / a.group, a.max_q_len, a.max_n_k, a.v_budget, a.skip_single, b)) return false;
     steps = batch_steps(rq, b);
     return true;
   };
@@ -1339,7 +1346,7 @@ __global__ __launch_bounds__(kBlThreads) void k_build_blocklist(const ListArgs a
     }
     const vs_request rq = a.req[r];
     BatchShape b;
-    if (!batch_shape(rq, a.group, a.n_heads / a.group, a.max_q_len, a.max_n_k, a.skip_single, b)) return;
+    if (!batch_shape(rq, a.group, a.n_heads / a.group, a.max_q_len, a.max_n_k, a.v_budget, a.skip_single, b)) return;
     pack = b.pack;
     n_hs = b.n_hs;
     dense = b.dense;
@@ -1605,12 +1612,13 @@ struct AttnCut {
 static AttnCut attn_cut(const vs_params& p, bool dense, int forced) {
   const bool one = attn_packed_decode(p, dense);
   const int group = p.n_q_heads / p.n_kv_heads, row_pad = (int)(p.q_start % kBlock);
+  const int64_t n_blk = ceil_div(p.q_start + p.q_len, kBlock);
   AttnCut c = {};
-  c.pack = one || forced == 1 ? 1 : heads_per_tile(p.q_len, row_pad, group);
+  const int64_t columns = dense ? 0 : (p.vertical_budget < p.q_start + p.q_len ? p.vertical_budget : p.q_start + p.q_len);
+  c.pack = one || forced == 1 ? 1 : heads_per_tile(p.q_len, row_pad, group, n_blk, columns);
   c.n_hs = one ? 1 : (int)ceil_div(group, c.pack);
   const int64_t n_qtiles = ceil_div(one ? group : p.q_len + row_pad, (int64_t)kTileRows);
   const int64_t units = n_qtiles * p.n_kv_heads * c.n_hs;
-  const int64_t n_blk = ceil_div(p.q_start + p.q_len, kBlock);
   c.n_split = 1;
   if (forced == 1 || units > (forced > 1 ? kMaxAskedUnits : kMaxQueueUnits)) return c;
   c.n_qtiles = (int32_t)n_qtiles;
@@ -2064,7 +2072,7 @@ hipError_t launch_attention_batch(const vs_params& p, const vs_request* req, int
   if (members < 1) members = 1;
   a.members = members; a.n_wg = 8 * members; a.n_full = 0; a.n_rem = 0;
   ListArgs l = {};
-  l.s_budget = p.slash_budget;
+  l.s_budget = p.slash_budget; l.v_budget = p.vertical_budget;
   l.n_words = (int)words; l.ent_stride = (int)ent_stride;
   l.bm_a = (uint32_t*)a.bm_a; l.ent = (uint32_t*)a.ent;
   l.n_heads = p.n_q_heads; l.group = a.group; l.pack = 1;

@@ -39,6 +39,11 @@ def test_heads_that_share_a_tile(hq, hkv, d, c, place, blocks):
         assert_attn_close(*got, *ref, f"sparse {hq}/{hkv} C={c} s={s} {nv} columns {ns} offsets")
 
 
+@pytest.mark.parametrize("blocks", [4, 11, 12, 22, 23])   # 160 columns: four heads of a tile from 24 blocks on, two from 12
+def test_heads_that_share_a_tile_as_the_columns_let_them(blocks):
+    test_heads_that_share_a_tile(7, 1, 128, 20, 5, blocks)
+
+
 @pytest.mark.parametrize("c,s", [(66 * 128 - 5, 70), (66 * 128 - 5, 4100 * 64 + 1)])   # 528 units: 512 whole, 16 cut
 def test_whole_units_and_cut_ones(c, s):
     hq, hkv, d = 8, 1, 64
