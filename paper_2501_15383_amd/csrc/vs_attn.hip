@@ -38,17 +38,32 @@
 //    its own instantiation.
 #include <atomic>
 #include <mutex>
+#include <type_traits>
 
 #include "vs_common.h"
 
 namespace vs {
 
 // Where the pieces of request r of a batch begin among those of all requests, the ranges each of its units is cut into
-// (0: the request is skipped), and its first slot of partial results.  Written by k_build_blocklist; entry n_req holds
-// the number of pieces.
+// (0: the request is skipped), its first slot of partial results, and its first unit among those that are cut.  Written by
+// k_build_blocklist; entry n_req holds the numbers of pieces, slots and cut units.
 struct BatchPlan {
-  int32_t first, n_split, slot;
+  int32_t first, n_split, slot, cut;
 };
+// The last request whose first piece (cut unit) is piece (cut unit) x or one before it: the one that has it, because a request
+// without any begins where the next one does.  64 probes at a time: one step for 64 requests, two for 4,096.
+template <int32_t BatchPlan::*Field>
+__device__ __forceinline__ int batch_find(const BatchPlan* plan, int n_req, int x) {
+  const int lane = threadIdx.x & 63;
+  int r = 0, left = n_req;
+  while (left > 1) {
+    const int step = (left + 63) >> 6, y = lane * step;
+    const int n = __popcll(__ballot(y < left && plan[r + (y < left ? y : 0)].*Field <= x));   // (the first one always)
+    r += (n - 1) * step;
+    left = left - (n - 1) * step < step ? left - (n - 1) * step : step;
+  }
+  return __builtin_amdgcn_readfirstlane(r);
+}
 
 struct AttnArgs {
   const __bf16* q;
@@ -370,16 +385,7 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
     none = u >= n_pieces;
     if constexpr (BATCH) {
       if (!none) {
-        // the last request that begins at or before piece u (64 of them at a time)
-        int r = -1;
-        for (int r0 = 0; r0 < a0.n_req; r0 += 64) {
-          const int x = r0 + lane;
-          const int first = a0.plan[x < a0.n_req ? x : a0.n_req].first;
-          const int n = __popcll(__ballot(x < a0.n_req && first <= u));
-          r += n;
-          if (n < 64) break;
-        }
-        // (a skipped request begins where the next one does: the last one found has the piece)
+        const int r = batch_find<&BatchPlan::first>(a0.plan, a0.n_req, u);
         u -= __builtin_amdgcn_readfirstlane(a0.plan[r].first);
         none = !batch_view(a0, r, a_req);
       }
@@ -1283,7 +1289,7 @@ __device__ void write_plan(const ListArgs& a, int64_t* scan) {
   __syncthreads();
   // (about three pieces per workgroup slot, one where they would come out short)
   const int64_t target = total < (int64_t)kBatchSlots * kShortSteps && a.pieces > kBatchSlots ? kBatchSlots : a.pieces;
-  int64_t before = 0;   // pieces, and slots in the high half
+  int64_t before = 0;   // pieces, from bit 32 on slots, from bit 48 on cut units (at most a.pieces of both)
   for (int r0 = 0; r0 < a.n_req; r0 += kBlThreads) {
     const int r = r0 + tid;
     int n_split = 0;
@@ -1294,7 +1300,7 @@ __device__ void write_plan(const ListArgs& a, int64_t* scan) {
       if (n > steps / kMinSteps) n = steps / kMinSteps;
       n_split = n < 1 ? 1 : (n > kMaxSplit ? kMaxSplit : (int)n);
       const int64_t pieces = (int64_t)b.n_units * n_split;
-      mine = pieces | (n_split > 1 ? pieces << 32 : 0);
+      mine = pieces | (n_split > 1 ? pieces << 32 | (int64_t)b.n_units << 48 : 0);
     }
     int64_t inc = mine;
 #pragma unroll
@@ -1313,7 +1319,8 @@ __device__ void write_plan(const ListArgs& a, int64_t* scan) {
     if (r < a.n_req) {
       a.plan[r].first = (int32_t)inc;
       a.plan[r].n_split = n_split;
-      a.plan[r].slot = (int32_t)(inc >> 32);
+      a.plan[r].slot = (int32_t)(inc >> 32) & 0xFFFF;
+      a.plan[r].cut = (int32_t)(inc >> 48);
     }
     before += all;
     __syncthreads();
@@ -1321,7 +1328,8 @@ __device__ void write_plan(const ListArgs& a, int64_t* scan) {
   if (tid == 0) {
     a.plan[a.n_req].first = (int32_t)before;
     a.plan[a.n_req].n_split = 0;
-    a.plan[a.n_req].slot = (int32_t)(before >> 32);
+    a.plan[a.n_req].slot = (int32_t)(before >> 32) & 0xFFFF;
+    a.plan[a.n_req].cut = (int32_t)(before >> 48);
   }
 }
 template <int NQB>
@@ -1673,48 +1681,37 @@ size_t attn_sync_bytes(const vs_params& p) { return attn_counter_bytes(p) + attn
 
 // out = sum_s O_s 2^(m_s - M) / sum_s l_s 2^(m_s - M), M = max_s m_s; D / 4 lanes per row of a tile,
 // pieces folded in ascending order (fixed, so the result is run-to-run identical).
-template <int D, bool BATCH>
-constexpr int combine_rows() { return 1024 / D * (BATCH ? 4 : 1); }   // rows per workgroup (a batch: the plan is read first)
+// One workgroup folds 1024 / D rows of a unit at a time; those of a batch, whose cut units only the device knows, take the next
+// ones until none are left (a grid for as many units as there may be: 26 us for 1,500 requests none of which was cut, 4 now),
+// and up to four of a unit in a row where there are more than workgroups, because finding them takes as long as folding a few
+// pieces.  Eight pieces at a time are on their way (four: 55 us for two requests of 64 rows and 40,000 keys in 128 ranges, 17
+// now; with few pieces four).
+template <int D>
+constexpr int combine_parts() { return kTileRows / (1024 / D); }   // per unit
+constexpr int kCombineGrid = 2048;   // workgroups for a batch at most
 template <int D, bool BATCH = false>
 __global__ __launch_bounds__(256) void k_attn_combine(const AttnArgs a0) {
   constexpr int LR = D / 4;            // lanes per row
-  constexpr int WPU = kTileRows / combine_rows<D, BATCH>();  // workgroups per unit
-  int e = blockIdx.x / WPU;
+  constexpr int WPU = combine_parts<D>();
   const int d = 4 * (threadIdx.x % LR);
+  const int n_tasks = (BATCH ? __builtin_amdgcn_readfirstlane(a0.plan[a0.n_req].cut) : a0.n_units - a0.n_whole) * WPU;
+  int run = 1;   // consecutive parts of a unit
+  while (BATCH && run < 4 && n_tasks > run * (int)gridDim.x) run *= 2;
+  for (int task = blockIdx.x * run; task < n_tasks; task += gridDim.x * run) {
+  int e = task / WPU;
   AttnArgs a = a0;
   if constexpr (BATCH) {
-    const int lane = threadIdx.x & 63;
-    // the first request whose split units reach beyond e
-    int r = 0;
-    for (int before = 0;; r += 64) {
-      if (r >= a0.n_req) return;
-      const int x = r + lane < a0.n_req ? r + lane : a0.n_req - 1;
-      const BatchPlan p0 = a0.plan[x], p1 = a0.plan[x + 1];
-      int n = r + lane < a0.n_req && p0.n_split > 1 ? (p1.first - p0.first) / p0.n_split : 0;
-#pragma unroll
-      for (int s = 1; s < 64; s <<= 1) {
-        const int y = __shfl_up(n, s);
-        if (lane >= s) n += y;
-      }
-      const uint64_t beyond = __ballot(before + n > e);
-      if (beyond) {
-        const int at = __builtin_ctzll(beyond);
-        e -= at > 0 ? before + __builtin_amdgcn_readlane(n, at - 1) : before;
-        r += at;
-        break;
-      }
-      before += __builtin_amdgcn_readlane(n, 63);
-    }
-    if (!batch_view(a0, __builtin_amdgcn_readfirstlane(r), a)) return;
-    e = __builtin_amdgcn_readfirstlane(e);
+    const int r = batch_find<&BatchPlan::cut>(a0.plan, a0.n_req, e);
+    e -= __builtin_amdgcn_readfirstlane(a0.plan[r].cut);
+    if (!batch_view(a0, r, a)) continue;
   }
   const int n_fold = a.n_units - a.n_whole;
-  if (e >= n_fold) return;
+  if (e >= n_fold) continue;
   int g, h, qt;
   unit_of(a, a.n_whole + e, g, h, qt);
-  for (int pass = 0; pass < combine_rows<D, BATCH>(); pass += 1024 / D) {
+  for (int part = task % WPU; part < task % WPU + run; ++part) {
   // (the row of the tile as k_attention deals them out)
-  const int lrow = (blockIdx.x % WPU) * combine_rows<D, BATCH>() + pass + threadIdx.x / LR;
+  const int lrow = part * (1024 / D) + threadIdx.x / LR;
   const int wv = lrow >> 5;
   int t = wv >> 1, th = 0, il0 = (wv & 1) << 5;
   if (a.pack > 1) {
@@ -1727,27 +1724,44 @@ __global__ __launch_bounds__(256) void k_attn_combine(const AttnArgs a0) {
   const int hw = h + th;
   const int64_t at = (int64_t)e * kTileRows + lrow, step = (int64_t)n_fold * kTileRows;
   float M = -INFINITY;
-#pragma unroll 4
+#pragma unroll 8
   for (int sp = 0; sp < a.n_split; ++sp) M = fmaxf(M, a.part_ml[2 * (at + step * sp)]);
   const float M0 = M == -INFINITY ? 0.f : M;
   float L = 0.f;
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll 4
-  for (int sp = 0; sp < a.n_split; ++sp) {
-    const float* const ml = a.part_ml + 2 * (at + step * sp);
-    const float w = __builtin_amdgcn_exp2f(ml[0] - M0);   // a piece without live keys: 0, and zeros in its slot
-    const f32x4 o = *(const f32x4*)(a.part_o + (at + step * sp) * D + d);
-    L += ml[1] * w;
+  auto fold = [&](auto pieces) {
+    constexpr int U = decltype(pieces)::value;
+    for (int s0 = 0; s0 < a.n_split; s0 += U) {
+      float m[U], l[U];
+      f32x4 o[U];
 #pragma unroll
-    for (int x = 0; x < 4; ++x) acc[x] += o[x] * w;
-  }
+      for (int u = 0; u < U; ++u) {
+        const int64_t x = at + step * (s0 + u < a.n_split ? s0 + u : a.n_split - 1);
+        m[u] = a.part_ml[2 * x];
+        l[u] = a.part_ml[2 * x + 1];
+        o[u] = *(const f32x4*)(a.part_o + x * D + d);
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        // (a piece without live keys: 0, and zeros in its slot)
+        const float w = s0 + u < a.n_split ? __builtin_amdgcn_exp2f(m[u] - M0) : 0.f;
+        L += l[u] * w;
+#pragma unroll
+        for (int x = 0; x < 4; ++x) acc[x] += o[u][x] * w;
+      }
+    }
+  };
+  if (a.n_split > 4) fold(std::integral_constant<int, 8>{});
+  else if (a.n_split > 2) fold(std::integral_constant<int, 4>{});
+  else fold(std::integral_constant<int, 2>{});
   const float inv = L > 0.f ? 1.0f / L : 0.f;
 #pragma unroll
   for (int x = 0; x < 4; ++x) acc[x] *= inv;
   *(bf16x4*)(a.out + row * a.o_stride_tok + (int64_t)hw * a.o_stride_head + d) = __builtin_convertvector(acc, bf16x4);
   if (a.lse && d == 0)
     a.lse[(int64_t)hw * a.q_rows + row] = L > 0.f ? (M + __builtin_amdgcn_logf(L)) * kLn2 : -INFINITY;
-  }
+  }  // parts
+  }  // tasks
 }
 
 // Which group takes which group-round.  Heads differ in the length of their block lists (by a
@@ -2002,7 +2016,7 @@ hipError_t launch_attention(const vs_params& p, const void* q, const DcaArgs* dc
   }
 #undef VS_ATTN_LAUNCH
   if (a.n_split > 1) {
-    const dim3 cgrid((unsigned)((int64_t)(a.n_units - a.n_whole) * (kTileRows / (1024 / p.head_dim))));
+    const dim3 cgrid((unsigned)((int64_t)(a.n_units - a.n_whole) * (p.head_dim == 128 ? combine_parts<128>() : combine_parts<64>())));
     if (p.head_dim == 128) hipLaunchKernelGGL(k_attn_combine<128>, cgrid, dim3(256), 0, st, a);
     else hipLaunchKernelGGL(k_attn_combine<64>, cgrid, dim3(256), 0, st, a);
   }
@@ -2082,7 +2096,8 @@ hipError_t launch_attention_batch(const vs_params& p, const vs_request* req, int
   hipLaunchKernelGGL((k_build_blocklist<NQB>), dim3((unsigned)p.n_q_heads, (unsigned)n_req + 1), dim3(kBlThreads), 0, st, l);
   if ((e = hipGetLastError()) != hipSuccess) return e;   // (what follows goes by the plan and the lists)
   const dim3 grid((unsigned)a.n_wg), block(128 * NQB);
-  const dim3 cgrid((unsigned)(ceil_div(pieces, 2) * (kTileRows / (4096 / p.head_dim))));   // split units: two pieces or more
+  const int64_t parts = ceil_div(pieces, 2) * (p.head_dim == 128 ? combine_parts<128>() : combine_parts<64>());   // cut units: two pieces or more
+  const dim3 cgrid((unsigned)(parts < kCombineGrid ? parts : kCombineGrid));
   if (p.head_dim == 128) {
     hipLaunchKernelGGL((k_attention<128, NQB, false, true, true>), grid, block, attn_lds_bytes<128>(), st, a);
     hipLaunchKernelGGL((k_attn_combine<128, true>), cgrid, dim3(256), 0, st, a);
