@@ -410,10 +410,23 @@ int vs_prefill_chunk_dca(const vs_params* p, const void* q_intra, const vs_dca* 
 }
 
 namespace {
+// Whether the single tokens of a batch are the decode kernel's.  Beside longer requests its three launches cost 15 to 25 us
+// whatever they find, and the tile kernel, which has work on all compute units anyway, reads the caches of a few tokens as fast.
+// Measured with and without them over 300 batches (us): 5 requests of up to 16 rows and 6,244 keys, 28 / 4 heads, 73 and 57;
+// 42 with 6,243 keys 126 and 109; 44 of 8,626 keys, 40 / 8 heads, 397 and 433; 8 of 262,144 keys, 28 / 4 heads, 1,278 and 1,336;
+// 200 sparse ones of up to 800 keys 298 and 411; 200 of 16 / 16 heads (nothing to share in a group) 186 and 147.  So: where the
+// caches may be large (512 MB), or the requests many.
+bool batch_decodes(const vs_params& p, int n_req) {
+  if (!decode_fits(p)) return false;
+  if (p.q_len == 1) return true;
+  if (p.n_q_heads == p.n_kv_heads) return false;
+  const int64_t caches = (int64_t)n_req * p.n_kv_heads;
+  return caches >= 256 || (double)caches * (double)(p.q_start + p.q_len) * p.head_dim * 4.0 >= 512.0 * (1 << 20);
+}
 // workspace of a batch: the decode kernel's part, then the tile kernel's
-size_t decode_part(const vs_params& p, int n_req) { return decode_fits(p) ? decode_bytes(p, n_req, true) : 0; }
+size_t decode_part(const vs_params& p, int n_req) { return batch_decodes(p, n_req) ? decode_bytes(p, n_req, true) : 0; }
 size_t batch_bytes(const vs_params& p, int n_req) {
-  return decode_part(p, n_req) + (decode_fits(p) && p.q_len == 1 ? 0 : attn_batch_bytes(p, n_req));
+  return decode_part(p, n_req) + (batch_decodes(p, n_req) && p.q_len == 1 ? 0 : attn_batch_bytes(p, n_req));
 }
 int check_batch(const vs_params* p, int32_t n_requests) {
   int rc = check_params(p, true);
@@ -436,9 +449,9 @@ int vs_attn_batch(const vs_params* p, const vs_request* requests, int32_t n_requ
   if (!requests || !aligned(requests, 8)) return VS_ERR_INVALID_ARG;
   rc = check_ws(ws, ws_bytes, batch_bytes(*p, n_requests));
   if (rc != VS_OK) return rc;
-  // single tokens by the decode kernel, the longer requests by the tile kernel (which skips the former)
+  // single tokens by the decode kernel, the longer requests by the tile kernel (which skips the former), or all by the latter
   hipStream_t st = (hipStream_t)stream;
-  const bool decode = decode_fits(*p);
+  const bool decode = batch_decodes(*p, n_requests);
   if (decode) {
     const hipError_t e = launch_decode(*p, nullptr, requests, n_requests, true, ws, st);
     if (e != hipSuccess || p->q_len == 1) return hip_status(e);

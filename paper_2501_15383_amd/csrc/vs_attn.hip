@@ -112,8 +112,8 @@ struct AttnArgs {
   int32_t row_pad;
   int64_t q_rows;
   int64_t n_k;  // keys visible to the chunk
-  // Dense attention of a single token with grouped queries that the decode kernel does not take (DCA, or more than
-  // 16 heads per group): the G query heads of a KV group are the rows of one tile (so K and V are read once per
+  // Dense attention of a single token with grouped queries that the decode kernel does not take (DCA, more than
+  // 16 heads per group, a token in a small batch of longer requests): the G query heads of a KV group are the rows of one tile (so K and V are read once per
   // group, not once per head); all rows then stand at the same position, pos_in_block keys into the diagonal block.
   int32_t same_pos, pos_in_block;
   float scale_log2;  // softmax_scale * log2(e)
