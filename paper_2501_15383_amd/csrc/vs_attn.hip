@@ -45,10 +45,10 @@
 namespace vs {
 
 // Where the pieces of request r of a batch begin among those of all requests, the ranges each of its units is cut into
-// (0: the request is skipped), its first slot of partial results, and its first unit among those that are cut.  Written by
+// (0: the request is skipped) and, from bit 16 on, the heads of a tile, its first slot of partial results, and its first unit among those that are cut.  Written by
 // k_build_blocklist; entry n_req holds the numbers of pieces, slots and cut units.
 struct BatchPlan {
-  int32_t first, n_split, slot, cut;
+  int32_t first, split_pack, slot, cut;
 };
 // The last request whose first piece (cut unit) is piece (cut unit) x or one before it: the one that has it, because a request
 // without any begins where the next one does.  64 probes at a time: one step for 64 requests, two for 4,096.
@@ -82,6 +82,7 @@ struct AttnArgs {
   int32_t n_split, n_units, n_whole, first_piece;
   float* part_o;
   float* part_ml;
+  int32_t first_slot;   // BATCH: of the request's partial results
   // SPLIT: query heads of one KV group that share a tile (1, 2 or 4).  Chunks whose rows lie in one query block leave
   // half of a tile's waves (three quarters: at most 32 rows) without rows; these waves take further heads.
   // n_hs: tiles per KV group = ceil(group / pack)
@@ -178,8 +179,13 @@ struct BatchShape {
   bool dense, same_pos;
   int32_t row_pad, pack, n_hs, n_qtiles, n_units;
 };
+__device__ __forceinline__ int batch_pack(const vs_request& rq, int group, int v_budget) {
+  const int64_t n_k = rq.q_start + rq.q_len;
+  return heads_per_tile(rq.q_len, (int)(rq.q_start % kBlock), group, (n_k + kBlock - 1) / kBlock,
+                        rq.s_idx == nullptr ? 0 : (v_budget < n_k ? v_budget : n_k));
+}
 __device__ __forceinline__ bool batch_shape(const vs_request& rq, int group, int n_kv_heads, int64_t max_q_len, int64_t max_n_k,
-                                            int v_budget, bool skip_single, BatchShape& b) {
+                                            bool skip_single, int pack, BatchShape& b) {
   if (!rq.q || !rq.k || !rq.v || !rq.out) return false;
   if (rq.q_len < 1 || rq.q_len > max_q_len || rq.q_start < 0 || rq.q_start + rq.q_len > max_n_k) return false;
   if (skip_single && rq.q_len == 1) return false;
@@ -188,9 +194,7 @@ __device__ __forceinline__ bool batch_shape(const vs_request& rq, int group, int
   b.row_pad = (int32_t)(rq.q_start % kBlock);
   // attention of one token: the G heads of a KV group are the rows of one tile
   b.same_pos = rq.q_len == 1 && group > 1 && b.dense;
-  const int64_t n_k = rq.q_start + rq.q_len;
-  b.pack = b.same_pos ? 1 : heads_per_tile(rq.q_len, b.row_pad, group, (n_k + kBlock - 1) / kBlock,
-                                           b.dense ? 0 : (v_budget < n_k ? v_budget : n_k));
+  b.pack = b.same_pos ? 1 : pack;
   b.n_hs = b.same_pos ? 1 : (group + b.pack - 1) / b.pack;
   const int64_t rows = b.same_pos ? group : b.row_pad + rq.q_len;
   b.n_qtiles = (int32_t)((rows + kTileRows - 1) / kTileRows);
@@ -205,8 +209,10 @@ __device__ __forceinline__ bool batch_view(const AttnArgs& a0, int r, AttnArgs& 
   rq.lse = uniform64(rq.lse); rq.v_idx = uniform64(rq.v_idx); rq.v_cnt = uniform64(rq.v_cnt);
   rq.s_idx = uniform64(rq.s_idx); rq.s_cnt = uniform64(rq.s_cnt);
   rq.q_start = uniform64(rq.q_start); rq.q_len = uniform64(rq.q_len);
+  const BatchPlan pl = a0.plan[r];
+  const int split_pack = __builtin_amdgcn_readfirstlane(pl.split_pack);
   BatchShape b;
-  if (!batch_shape(rq, a0.group, a0.n_kv_heads, a0.max_q_len, a0.max_n_k, a0.v_budget, a0.skip_single, b)) return false;
+  if (!batch_shape(rq, a0.group, a0.n_kv_heads, a0.max_q_len, a0.max_n_k, a0.skip_single, split_pack >> 16, b)) return false;
   a.q = (const __bf16*)rq.q; a.k = (const __bf16*)rq.k; a.v = (const __bf16*)rq.v;
   a.out = (__bf16*)rq.out; a.lse = rq.lse;
   a.v_idx = b.dense ? nullptr : rq.v_idx;
@@ -218,11 +224,8 @@ __device__ __forceinline__ bool batch_view(const AttnArgs& a0, int r, AttnArgs& 
   a.n_k = rq.q_start + rq.q_len;
   a.bm_a = a0.bm_a + (int64_t)r * a0.n_q_heads * a0.bm_stride;
   a.ent = a0.ent + (int64_t)r * a0.n_q_heads * a0.ent_stride;
-  const BatchPlan pl = a0.plan[r];
-  a.n_split = __builtin_amdgcn_readfirstlane(pl.n_split);
-  const int64_t slot = (int64_t)__builtin_amdgcn_readfirstlane(pl.slot) * kTileRows;
-  a.part_o = a0.part_o + slot * a0.head_dim;
-  a.part_ml = a0.part_ml + slot * 2;
+  a.n_split = split_pack & 0xFFFF;
+  a.first_slot = __builtin_amdgcn_readfirstlane(pl.slot);
   a.pack = b.pack; a.n_hs = b.n_hs; a.n_qtiles = b.n_qtiles; a.n_units = b.n_units;
   a.n_whole = a.n_split == 1 ? b.n_units : 0;
   a.first_piece = 0;
@@ -397,7 +400,7 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
       const int v = u - a.n_whole, n = a.n_units - a.n_whole;
       sp = v / n;
       e = a.n_whole + v - sp * n;
-      slot = v;
+      slot = BATCH ? v + a.first_slot : v;
     }
     g = h = qt = 0;
     if (!none) unit_of(a, e, g, h, qt);
@@ -456,7 +459,7 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
   }
   if (!none) {
   const int64_t row0 = (int64_t)qt * (64 * NQB);
-  const int64_t row = row0 + 64 * t + il0 + (lane & 31);
+  const int row = (int)row0 + 64 * t + il0 + (lane & 31);
   const int m0 = (int)(a.q_start / 64) + qt * NQB;  // absolute index of query block t = 0
   const bool wave_valid = head_ok && row0 + 64 * t + il0 < a.q_len;
   const int64_t rows_in_tile = (a.q_len - row0) < 64 * NQB ? (a.q_len - row0) : 64 * NQB;
@@ -487,9 +490,9 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
       if (var == 1) qb = a.q_succ;
       if (var == 2) qb = a.q_inter;
     }
-    int64_t rc = row - a.row_pad;  // the caller's row (clamped: padding and tail rows load a valid one)
-    rc = rc < 0 ? 0 : (rc < a.q_rows ? rc : a.q_rows - 1);
-    const __bf16* qp = qb + rc * a.q_stride_tok + (int64_t)hw * a.q_stride_head + 8 * hh;
+    int rc = row - a.row_pad;  // the caller's row (clamped: padding and tail rows load a valid one)
+    rc = rc < 0 ? 0 : (rc < (int)a.q_rows ? rc : (int)a.q_rows - 1);
+    const __bf16* qp = qb + (int64_t)rc * a.q_stride_tok + (int64_t)hw * a.q_stride_head + 8 * hh;
 #pragma unroll
     for (int st = 0; st < DSTEPS; ++st) qreg[st] = *(const bf16x8*)(qp + 16 * st);
     q_var = var;
@@ -1141,8 +1144,8 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
     const int64_t ro = row - a.row_pad;
     if (head_ok && ro >= 0 && ro < a.q_rows) {
       const int64_t pr = (int64_t)slot * kTileRows + 32 * wv + (lane & 31);
-      float* op = a.part_o + pr * D;
-      float* mlp = a.part_ml + pr * 2;
+      float* op = a0.part_o + pr * D;
+      float* mlp = a0.part_ml + pr * 2;
 #pragma unroll
       for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -1269,7 +1272,7 @@ __device__ void write_plan(const ListArgs& a, int64_t* scan) {
   constexpr int NW = kBlThreads / 64;
   auto look = [&](int r, BatchShape& b, int64_t& steps) -> bool {
     const vs_request rq = a.req[r];
-    if (!batch_shape(rq, a.group, a.n_heads / a.group, a.max_q_len, a.max_n_k, a.v_budget, a.skip_single, b)) return false;
+    if (!batch_shape(rq, a.group, a.n_heads / a.group, a.max_q_len, a.max_n_k, a.skip_single, batch_pack(rq, a.group, a.v_budget), b)) return false;
     steps = batch_steps(rq, b);
     return true;
   };
@@ -1318,7 +1321,7 @@ __device__ void write_plan(const ListArgs& a, int64_t* scan) {
     inc += before - mine;
     if (r < a.n_req) {
       a.plan[r].first = (int32_t)inc;
-      a.plan[r].n_split = n_split;
+      a.plan[r].split_pack = n_split | (taken ? b.pack << 16 : 0);
       a.plan[r].slot = (int32_t)(inc >> 32) & 0xFFFF;
       a.plan[r].cut = (int32_t)(inc >> 48);
     }
@@ -1327,7 +1330,7 @@ __device__ void write_plan(const ListArgs& a, int64_t* scan) {
   }
   if (tid == 0) {
     a.plan[a.n_req].first = (int32_t)before;
-    a.plan[a.n_req].n_split = 0;
+    a.plan[a.n_req].split_pack = 0;
     a.plan[a.n_req].slot = (int32_t)(before >> 32) & 0xFFFF;
     a.plan[a.n_req].cut = (int32_t)(before >> 48);
   }
@@ -1354,7 +1357,7 @@ __global__ __launch_bounds__(kBlThreads) void k_build_blocklist(const ListArgs a
     }
     const vs_request rq = a.req[r];
     BatchShape b;
-    if (!batch_shape(rq, a.group, a.n_heads / a.group, a.max_q_len, a.max_n_k, a.v_budget, a.skip_single, b)) return;
+    if (!batch_shape(rq, a.group, a.n_heads / a.group, a.max_q_len, a.max_n_k, a.skip_single, batch_pack(rq, a.group, a.v_budget), b)) return;
     pack = b.pack;
     n_hs = b.n_hs;
     dense = b.dense;
@@ -1722,7 +1725,7 @@ __global__ __launch_bounds__(256) void k_attn_combine(const AttnArgs a0) {
   const int64_t row = (int64_t)qt * kTileRows + 64 * t + il0 + (lrow & 31) - a.row_pad;
   if (row < 0 || row >= a.q_rows || h - g * a.group + th >= a.group) continue;
   const int hw = h + th;
-  const int64_t at = (int64_t)e * kTileRows + lrow, step = (int64_t)n_fold * kTileRows;
+  const int64_t at = (int64_t)(BATCH ? e + a.first_slot : e) * kTileRows + lrow, step = (int64_t)n_fold * kTileRows;
   float M = -INFINITY;
 #pragma unroll 8
   for (int sp = 0; sp < a.n_split; ++sp) M = fmaxf(M, a.part_ml[2 * (at + step * sp)]);
