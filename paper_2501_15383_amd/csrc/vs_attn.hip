@@ -348,6 +348,13 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave index, known uniform
   const int hh = lane >> 5;
 
+  // The arguments, for what comes after the walk: read from memory there.  (Read through a0 they are loaded once, in front of the
+  // rounds, and sit in vector registers' lanes during the walk: there are about a hundred scalar registers for twice as many values.)
+  auto late_args = []() -> const AttnArgs& {
+    uint64_t p = (uint64_t)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return *(const AttnArgs*)(const __attribute__((address_space(4))) AttnArgs*)p;
+  };
   // ---- persistent workgroup: one (query tile, head) per round ------------------------------
   // The `members` workgroups of a group take consecutive query tiles of ONE head, so they walk
   // the same entry list, shifted by two key blocks per tile, at the same pace; the arrive
@@ -1137,15 +1144,17 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
   }
 
   // ---- normalise and store ------------------------------------------------------------------
+  const AttnArgs& z0 = late_args();
+  const AttnArgs& z = BATCH ? a : z0;
   const float l_tot = l_run + __shfl_xor(l_run, 32);
   const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
   if (SPLIT && !whole) {
     // this piece's share of the row: accumulators and row sum relative to the reference m_o
-    const int64_t ro = row - a.row_pad;
-    if (head_ok && ro >= 0 && ro < a.q_rows) {
+    const int64_t ro = row - z.row_pad;
+    if (head_ok && ro >= 0 && ro < z.q_rows) {
       const int64_t pr = (int64_t)slot * kTileRows + 32 * wv + (lane & 31);
-      float* op = a0.part_o + pr * D;
-      float* mlp = a0.part_ml + pr * 2;
+      float* op = z0.part_o + pr * D;
+      float* mlp = z0.part_ml + pr * 2;
 #pragma unroll
       for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -1161,9 +1170,9 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
       }
     }
   } else
-  if (head_ok && row >= a.row_pad && row < a.q_len) {
-    const int64_t ro = row - a.row_pad;
-    __bf16* op = a.out + ro * a.o_stride_tok + (int64_t)hw * a.o_stride_head;
+  if (head_ok && row >= z.row_pad && row < z.q_len) {
+    const int64_t ro = row - z.row_pad;
+    __bf16* op = z.out + ro * z.o_stride_tok + (int64_t)hw * z.o_stride_head;
 #pragma unroll
     for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -1173,25 +1182,26 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
         for (int x = 0; x < 4; ++x) o4[x] = oacc[db][4 * vq + x] * inv;
         *(bf16x4*)(op + 32 * db + 8 * vq + 4 * hh) = __builtin_convertvector(o4, bf16x4);
       }
-    if (a.lse && hh == 0)
-      a.lse[(int64_t)hw * a.q_rows + ro] =
+    if (z.lse && hh == 0)
+      z.lse[(int64_t)hw * z.q_rows + ro] =
           l_tot > 0.f ? (m_o + __builtin_amdgcn_logf(l_tot)) * kLn2 : -INFINITY;
   }
   enter_segment(-1, false);  // (a tile whose walk ended early has marked nothing yet)
   }  // !none
   if constexpr (SPLIT) {
     if (n_pieces <= (int)gridDim.x) break;
+    const AttnArgs& z0 = late_args();
     int* const next_s = (int*)vidx_s;
     if (tid < 64) {
       int at = __builtin_amdgcn_readfirstlane((int)q_next), from = grp;
       auto left_in = [&](int x) -> int {   // pieces of queue x: whole runs of `members`, and the run that the last piece ends in
-        const int runs = n_pieces / a0.members, tail = n_pieces - runs * a0.members;
-        return ((runs - x + 7) >> 3) * a0.members + ((runs & 7) == x ? tail : 0);
+        const int runs = n_pieces / z0.members, tail = n_pieces - runs * z0.members;
+        return ((runs - x + 7) >> 3) * z0.members + ((runs & 7) == x ? tail : 0);
       };
       while (at >= left_in(from)) {
         // the own queue is empty: the one with the most left.  A queue only ever grows emptier, so this ends
         const int x = lane & 7;
-        const int seen = (int)__hip_atomic_load(&a0.queue[x * kQueueStride], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + a0.members;
+        const int seen = (int)__hip_atomic_load(&z0.queue[x * kQueueStride], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + z0.members;
         int best = left_in(x) - seen > 0 ? ((left_in(x) - seen) << 3) | x : 0;
 #pragma unroll
         for (int d = 1; d < 8; d <<= 1) { const int y = __shfl_xor(best, d); best = y > best ? y : best; }
@@ -1199,8 +1209,8 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
         if (best == 0) { at = -1; break; }
         from = best & 7;
         uint32_t got = 0;
-        if (lane == 0) got = atomicAdd(&a0.queue[from * kQueueStride], 1u);
-        at = (int)__builtin_amdgcn_readfirstlane(got) + a0.members;
+        if (lane == 0) got = atomicAdd(&z0.queue[from * kQueueStride], 1u);
+        at = (int)__builtin_amdgcn_readfirstlane(got) + z0.members;
       }
       if (tid == 0) { next_s[0] = at; next_s[1] = from; }
     }
