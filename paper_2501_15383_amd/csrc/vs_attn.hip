@@ -379,6 +379,11 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
   uint32_t q_next = 0;
   if constexpr (SPLIT) {
     u = ((q_pos / a0.members) * 8 + q_grp) * a0.members + q_pos % a0.members;
+    // (a batch, whose pieces the host cannot count: fewer than workgroups are dealt evenly over the XCDs, as launch_attention does)
+    if (BATCH && n_pieces < (int)gridDim.x) {
+      const int each = (n_pieces + 7) >> 3;
+      u = member < each ? grp * each + member : n_pieces;
+    }
     // the place after this one, requested now and read at the end of the piece
     if (n_pieces > (int)gridDim.x && tid == 0) q_next = atomicAdd(&a0.queue[grp * kQueueStride], 1u) + (uint32_t)a0.members;
   } else {
@@ -1274,9 +1279,23 @@ __device__ __forceinline__ int64_t batch_steps(const vs_request& rq, const Batch
   const int64_t listed = 2 * (int64_t)rq.s_cnt[0] + 1;
   return (listed < n_blk ? listed : n_blk) + 2 * b.pack * ((rq.v_cnt[0] + 63) / 64);
 }
+// Ranges that equally long units are best cut into: rounds of kBatchSlots pieces, as in attn_cut.
+__device__ int best_split(int64_t units, int64_t steps, int64_t most_pieces) {
+  int best = 1;
+  float best_cost = 0.f;
+  for (int n = 1; n <= kMaxSplit && n <= steps; ++n) {
+    const int64_t pieces = units * n;
+    if (n > 1 && pieces > most_pieces) break;
+    float cost = (float)((pieces + kBatchSlots - 1) / kBatchSlots) * ((float)steps / (float)n + (float)kPieceSteps);
+    if (n > 1) cost += 3.f + 8.f * (float)pieces / (float)kBatchSlots;
+    if (n == 1 || cost < best_cost) { best = n; best_cost = cost; }
+  }
+  return best;
+}
 // Ranges per unit so that all pieces of a batch come out about equally long and there are a.pieces of them: the requests
 // differ in length, and a workgroup takes the next piece when it is done with one.  Rounded down, so that the split units
-// have at most a.pieces pieces (slots of partial results).
+// have at most a.pieces pieces (slots of partial results).  The units of a single request are equally long: they are cut as
+// attn_cut would cut them all (2,500 rows at 20,000 keys, 20 heads: 400 units whole ONE1, in three ranges each ONE3).
 __device__ void write_plan(const ListArgs& a, int64_t* scan) {
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   constexpr int NW = kBlThreads / 64;
@@ -1310,6 +1329,7 @@ __device__ void write_plan(const ListArgs& a, int64_t* scan) {
     if (a.n_req > kBlThreads) taken = r < a.n_req && look(r, b, steps);
     if (taken) {
       int64_t n = steps * target / total;
+      if (a.n_req == 1) n = best_split(b.n_units, steps, a.pieces);
       if (n > steps / kMinSteps) n = steps / kMinSteps;
       n_split = n < 1 ? 1 : (n > kMaxSplit ? kMaxSplit : (int)n);
       const int64_t pieces = (int64_t)b.n_units * n_split;
