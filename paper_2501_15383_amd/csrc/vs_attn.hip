@@ -225,6 +225,7 @@ __device__ __forceinline__ bool batch_view(const AttnArgs& a0, int r, AttnArgs& 
   a.bm_a = a0.bm_a + (int64_t)r * a0.n_q_heads * a0.bm_stride;
   a.ent = a0.ent + (int64_t)r * a0.n_q_heads * a0.ent_stride;
   a.n_split = split_pack & 0xFFFF;
+  if (b.dense) a.ent_stride = a.bm_stride = 0;   // one list, the first head's
   a.first_slot = __builtin_amdgcn_readfirstlane(pl.slot);
   a.pack = b.pack; a.n_hs = b.n_hs; a.n_qtiles = b.n_qtiles; a.n_units = b.n_units;
   a.n_whole = a.n_split == 1 ? b.n_units : 0;
@@ -1256,13 +1257,14 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
 constexpr int kBlThreads = 1024;
 constexpr int kBlWin = 4096;        // bitmap words in LDS at a time (8.4M keys; shared by packed heads)
 constexpr int kBlDensePart = 4096;  // entries of a dense list per workgroup
+constexpr int kListGroups = 4096;   // workgroups for the lists of a batch, about
 struct ListArgs {
   const int32_t* s_idx;
   const int32_t* s_cnt;
   int32_t s_budget, dense, n_blk, n_words, ent_stride;
   uint32_t* bm_a;
   uint32_t* ent;
-  int32_t n_heads, group, pack;
+  int32_t n_lists, n_heads, group, pack;   // n_lists: of a call, or of a request at most
   uint32_t* zero;
   int32_t n_zero;
   // a batch
@@ -1295,7 +1297,7 @@ __device__ int best_split(int64_t units, int64_t steps, int64_t most_pieces) {
 // Ranges per unit so that all pieces of a batch come out about equally long and there are a.pieces of them: the requests
 // differ in length, and a workgroup takes the next piece when it is done with one.  Rounded down, so that the split units
 // have at most a.pieces pieces (slots of partial results).  The units of a single request are equally long: they are cut as
-// attn_cut would cut them all (2,500 rows at 20,000 keys, 20 heads: 400 units whole ONE1, in three ranges each ONE3).
+// attn_cut would cut them all (2,500 rows at 20,000 keys, 20 heads: 400 units whole 528 us, in three ranges each 613).
 __device__ void write_plan(const ListArgs& a, int64_t* scan) {
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   constexpr int NW = kBlThreads / 64;
@@ -1365,36 +1367,30 @@ __device__ void write_plan(const ListArgs& a, int64_t* scan) {
     a.plan[a.n_req].cut = (int32_t)(before >> 48);
   }
 }
+// List x0; false: nothing to be done for it or the ones behind it.
 template <int NQB>
-__global__ __launch_bounds__(kBlThreads) void k_build_blocklist(const ListArgs a) {
+__device__ __forceinline__ bool build_list(const ListArgs& a, int x0) {
   constexpr int NW = kBlThreads / 64;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int part = a.req ? 0 : blockIdx.y, n_parts = a.req ? 1 : gridDim.y;
-  const int x0 = blockIdx.x, r = (int)blockIdx.y - 1;   // (r: of a batch, whose first workgroup is the plan's)
+  const int r = (int)blockIdx.y - 1;   // (of a batch, whose first workgroup is the plan's)
   const int n_words = a.n_words, ent_stride = a.ent_stride;
   int dense = a.dense, n_blk = a.n_blk, pack = a.pack, n_hs = (a.group + pack - 1) / pack;
   const int32_t* s_idx = a.s_idx;
   const int32_t* s_cnt = a.s_cnt;
   uint32_t* bm_a = a.bm_a;
-  if (blockIdx.x == 0 && blockIdx.y == 0)
-    for (int x = tid; x < a.n_zero; x += kBlThreads) a.zero[x] = 0u;
   if (a.req) {
-    __shared__ int64_t scan[NW];
-    if (r < 0) {
-      if (x0 == 0) write_plan(a, scan);
-      return;
-    }
     const vs_request rq = a.req[r];
     BatchShape b;
-    if (!batch_shape(rq, a.group, a.n_heads / a.group, a.max_q_len, a.max_n_k, a.skip_single, batch_pack(rq, a.group, a.v_budget), b)) return;
+    if (!batch_shape(rq, a.group, a.n_heads / a.group, a.max_q_len, a.max_n_k, a.skip_single, batch_pack(rq, a.group, a.v_budget), b)) return false;
     pack = b.pack;
     n_hs = b.n_hs;
     dense = b.dense;
     s_idx = rq.s_idx; s_cnt = rq.s_cnt;
     n_blk = (int)((rq.q_start + rq.q_len + kBlock - 1) / kBlock);
     bm_a += (int64_t)r * a.n_heads * n_words;
-    if (x0 >= a.n_heads / a.group * n_hs) return;
+    if (x0 >= (b.dense ? 1 : a.n_heads / a.group * n_hs)) return false;   // (a dense request has one list for all heads)
   }
   uint32_t* const E = a.ent + ((a.req ? (int64_t)r * a.n_heads : 0) + x0) * ent_stride;
   // the first head of list x0, and how many heads it has
@@ -1417,7 +1413,7 @@ __global__ __launch_bounds__(kBlThreads) void k_build_blocklist(const ListArgs a
       E[i] = i < n_blk ? ((uint32_t)(i + NQB - 1) << 4) | 15u : kEntSentinel;
     // (no bitmap: a dense walk has no columns that ask it)
     if (part == 0 && tid == 0) write_tail((uint32_t)n_blk);
-    return;
+    return true;
   }
   if (dense) {
     const int n_list = n_blk + NQB - 1, all = (1 << NQB) - 1;
@@ -1439,9 +1435,9 @@ __global__ __launch_bounds__(kBlThreads) void k_build_blocklist(const ListArgs a
       }
       if (tid == 0) write_tail((uint32_t)n_list);
     }
-    return;
+    return true;
   }
-  if (part != 0) return;
+  if (part != 0) return false;
 
   __shared__ uint32_t aw[kBlWin + 2];   // aw[1 + w]: bitmap word w0 + w; aw[0]: the word before the window
   __shared__ uint32_t wsum[NW];
@@ -1496,7 +1492,7 @@ __global__ __launch_bounds__(kBlThreads) void k_build_blocklist(const ListArgs a
     }
     for (int i = running + tid; i < ent_stride; i += kBlThreads) E[i] = kEntSentinel;
     if (tid < n_in) { A[(int64_t)tid * n_words + n_words - 1] = 0u; A[(int64_t)tid * n_words + n_words - 2] = running; }
-    return;
+    return true;
   }
   const int cnt = s_cnt[h0];
   const int32_t* const so = s_idx + (int64_t)h0 * a.s_budget;
@@ -1556,6 +1552,21 @@ __global__ __launch_bounds__(kBlThreads) void k_build_blocklist(const ListArgs a
   }
   for (int i = running + tid; i < ent_stride; i += kBlThreads) E[i] = kEntSentinel;
   if (tid == 0) write_tail(running);
+  return true;
+}
+template <int NQB>
+__global__ __launch_bounds__(kBlThreads) void k_build_blocklist(const ListArgs a) {
+  if (blockIdx.x == 0 && blockIdx.y == 0)
+    for (int x = threadIdx.x; x < a.n_zero; x += kBlThreads) a.zero[x] = 0u;
+  if (a.req && blockIdx.y == 0) {
+    __shared__ int64_t scan[kBlThreads / 64];
+    if (blockIdx.x == 0) write_plan(a, scan);
+    return;
+  }
+  for (int x0 = blockIdx.x; x0 < a.n_lists; x0 += gridDim.x) {
+    if (!build_list<NQB>(a, x0)) return;   // (the same for all threads)
+    __syncthreads();   // its LDS is the next list's
+  }
 }
 
 // Issued-tile accounting, one workgroup per head: for every query block of the chunk, the
@@ -1898,6 +1909,7 @@ hipError_t launch_build_blocklist(const vs_params& p, const int32_t* s_idx, cons
   a.n_zero = sync_ws ? (int)(attn_counter_bytes(p) / sizeof(uint32_t)) : 0;
   const unsigned parts = dense ? (unsigned)ceil_div(bl.ent_stride, kBlDensePart) : 1u;
   const unsigned lists = dense ? 1u : (unsigned)(p.n_kv_heads * ceil_div(a.group, a.pack));
+  a.n_lists = (int)lists;
   hipLaunchKernelGGL((k_build_blocklist<kAttnQBlocks>), dim3(lists, parts), dim3(kBlThreads), 0, st, a);
   return hipGetLastError();
 }
@@ -2126,7 +2138,12 @@ hipError_t launch_attention_batch(const vs_params& p, const vs_request* req, int
   l.zero = a.queue; l.n_zero = 8 * kQueueStride;
   l.req = req; l.plan = plan; l.n_req = n_req; l.skip_single = skip_single; l.pieces = pieces;
   l.max_q_len = p.q_len; l.max_n_k = n_k;
-  hipLaunchKernelGGL((k_build_blocklist<NQB>), dim3((unsigned)p.n_q_heads, (unsigned)n_req + 1), dim3(kBlThreads), 0, st, l);
+  // (a few workgroups per request where they fill the chip: 24,000 of 1,024 threads that find nothing to do, for 1,500 dense
+  // requests of 16 heads, took 187 us, 48 so)
+  l.n_lists = p.n_q_heads;
+  const int each = (int)ceil_div(kListGroups, n_req);
+  hipLaunchKernelGGL((k_build_blocklist<NQB>), dim3((unsigned)(each < p.n_q_heads ? each : p.n_q_heads), (unsigned)n_req + 1),
+                     dim3(kBlThreads), 0, st, l);
   if ((e = hipGetLastError()) != hipSuccess) return e;   // (what follows goes by the plan and the lists)
   const dim3 grid((unsigned)a.n_wg), block(128 * NQB);
   const int64_t parts = ceil_div(pieces, 2) * (p.head_dim == 128 ? combine_parts<128>() : combine_parts<64>());   // cut units: two pieces or more
