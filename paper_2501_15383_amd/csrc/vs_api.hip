@@ -411,17 +411,16 @@ int vs_prefill_chunk_dca(const vs_params* p, const void* q_intra, const vs_dca* 
 
 namespace {
 // Whether the single tokens of a batch are the decode kernel's.  Beside longer requests its three launches cost 15 to 25 us
-// whatever they find, and the tile kernel, which has work on all compute units anyway, reads the caches of a few tokens as fast.
-// Measured with and without them over 300 batches (us): 5 requests of up to 16 rows and 6,244 keys, 28 / 4 heads, 73 and 57;
-// 42 with 6,243 keys 126 and 109; 44 of 8,626 keys, 40 / 8 heads, 397 and 433; 8 of 262,144 keys, 28 / 4 heads, 1,278 and 1,336;
-// 200 sparse ones of up to 800 keys 298 and 411; 200 of 16 / 16 heads (nothing to share in a group) 186 and 147.  So: where the
-// caches may be large (512 MB), or the requests many.
+// whatever they find, and the tile kernel reads small caches as fast.  Measured without and with them over 300 batches (us): 16
+// requests of up to 33 rows and 2,000 keys, 8 / 2 heads of 64 (16 MB of caches at most), 46 and 60; 16 / 16 heads, where a
+// group has nothing to share, 52 and 71; 14 of 3,215 keys with 2,000 gathered columns, 40 / 8 heads (184 MB), 187 and 135; 200
+// sparse ones of up to 800 keys, 28 / 4 heads, 411 and 298.  So: from 64 MB of caches on, or where the requests are many.
 bool batch_decodes(const vs_params& p, int n_req) {
   if (!decode_fits(p)) return false;
   if (p.q_len == 1) return true;
   if (p.n_q_heads == p.n_kv_heads) return false;
   const int64_t caches = (int64_t)n_req * p.n_kv_heads;
-  return caches >= 256 || (double)caches * (double)(p.q_start + p.q_len) * p.head_dim * 4.0 >= 512.0 * (1 << 20);
+  return caches >= 256 || (double)caches * (double)(p.q_start + p.q_len) * p.head_dim * 4.0 >= 64.0 * (1 << 20);
 }
 // workspace of a batch: the decode kernel's part, then the tile kernel's
 size_t decode_part(const vs_params& p, int n_req) { return batch_decodes(p, n_req) ? decode_bytes(p, n_req, true) : 0; }

@@ -164,7 +164,7 @@ constexpr int kTileRows = 64 * kAttnQBlocks;       // rows of a query tile, of a
 // order of the pieces, see attn_cut), 4 rows at 50K keys 100 -> 46, 22 requests of up to 64 rows and 38K keys (40 heads)
 // 921 -> 308.  Heads without a group (or a second query block) have nothing to share.  Gathered columns are not shared: a tile
 // walks those of its heads one after the other, so it takes as many heads as leave their steps (two per 64 columns, which
-// take the masked path) below the n_blk of the key blocks.  With four heads whatever the columns, 28 heads: 2 rows at 1,000
+// take the masked path) below the n_blk of the key blocks; ranges are counted by these.  With four heads whatever the columns, 28 heads: 2 rows at 1,000
 // keys, as many columns, 120 us, 55 so; at 300 keys 77 and 42.
 __host__ __device__ __forceinline__ int heads_per_tile(int64_t rows, int row_pad, int group, int64_t n_blk, int64_t columns) {
   if (kAttnQBlocks != 2 || group < 2 || row_pad + rows > kBlock) return 1;
@@ -179,10 +179,9 @@ struct BatchShape {
   bool dense, same_pos;
   int32_t row_pad, pack, n_hs, n_qtiles, n_units;
 };
-__device__ __forceinline__ int batch_pack(const vs_request& rq, int group, int v_budget) {
-  const int64_t n_k = rq.q_start + rq.q_len;
-  return heads_per_tile(rq.q_len, (int)(rq.q_start % kBlock), group, (n_k + kBlock - 1) / kBlock,
-                        rq.s_idx == nullptr ? 0 : (v_budget < n_k ? v_budget : n_k));
+// (whatever the columns: the plan counts their steps and cuts the tiles that have many)
+__device__ __forceinline__ int batch_pack(const vs_request& rq, int group) {
+  return heads_per_tile(rq.q_len, (int)(rq.q_start % kBlock), group, 1, 0);
 }
 __device__ __forceinline__ bool batch_shape(const vs_request& rq, int group, int n_kv_heads, int64_t max_q_len, int64_t max_n_k,
                                             bool skip_single, int pack, BatchShape& b) {
@@ -1270,7 +1269,7 @@ struct ListArgs {
   // a batch
   const vs_request* req;
   BatchPlan* plan;
-  int32_t n_req, skip_single, pieces, v_budget;
+  int32_t n_req, skip_single, pieces;
   int64_t max_q_len, max_n_k;
 };
 // Steps (64-key blocks, columns at twice their number: they take the masked path) that a tile of the request walks, for the
@@ -1303,7 +1302,7 @@ __device__ void write_plan(const ListArgs& a, int64_t* scan) {
   constexpr int NW = kBlThreads / 64;
   auto look = [&](int r, BatchShape& b, int64_t& steps) -> bool {
     const vs_request rq = a.req[r];
-    if (!batch_shape(rq, a.group, a.n_heads / a.group, a.max_q_len, a.max_n_k, a.skip_single, batch_pack(rq, a.group, a.v_budget), b)) return false;
+    if (!batch_shape(rq, a.group, a.n_heads / a.group, a.max_q_len, a.max_n_k, a.skip_single, batch_pack(rq, a.group), b)) return false;
     steps = batch_steps(rq, b);
     return true;
   };
@@ -1383,7 +1382,7 @@ __device__ __forceinline__ bool build_list(const ListArgs& a, int x0) {
   if (a.req) {
     const vs_request rq = a.req[r];
     BatchShape b;
-    if (!batch_shape(rq, a.group, a.n_heads / a.group, a.max_q_len, a.max_n_k, a.skip_single, batch_pack(rq, a.group, a.v_budget), b)) return false;
+    if (!batch_shape(rq, a.group, a.n_heads / a.group, a.max_q_len, a.max_n_k, a.skip_single, batch_pack(rq, a.group), b)) return false;
     pack = b.pack;
     n_hs = b.n_hs;
     dense = b.dense;
@@ -2131,7 +2130,7 @@ hipError_t launch_attention_batch(const vs_params& p, const vs_request* req, int
   if (members < 1) members = 1;
   a.members = members; a.n_wg = 8 * members; a.n_full = 0; a.n_rem = 0;
   ListArgs l = {};
-  l.s_budget = p.slash_budget; l.v_budget = p.vertical_budget;
+  l.s_budget = p.slash_budget;
   l.n_words = (int)words; l.ent_stride = (int)ent_stride;
   l.bm_a = (uint32_t*)a.bm_a; l.ent = (uint32_t*)a.ent;
   l.n_heads = p.n_q_heads; l.group = a.group; l.pack = 1;
