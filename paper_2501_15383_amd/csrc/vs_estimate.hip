@@ -443,31 +443,33 @@ __global__ __launch_bounds__(1024) void k_estimate_combine(const EstArgs a) {
 // and a row block is faster with fewer waves around.  Small calls are made of few rounds of workgroups, so the waves per
 // workgroup are whatever fills them.  28 / 4 heads, against at most 16 waves and always many heads per workgroup: 38,209 keys
 // 111 -> 85 us, 84,333 178 -> 146, 300,001 501 -> 420; 1M the same.  head_bytes: LDS per head and wave, beside the rows.
+// A workgroup of fewer heads than the group is tried at every count that leaves fewest for the last one (32 heads: shares of 4
+// come out even, 7 + 7 + 7 + 7 + 4 do not; 131,072 keys 258 -> 195 us).
 static EstShape est_shape(const vs_params& p, int most, int head_bytes, bool dca) {
   const int group = p.n_q_heads / p.n_kv_heads, n_cu = 256;
-  const double n_tiles = (double)ceil_div(p.q_start + p.q_len, 64), units = n_tiles * p.n_kv_heads;
+  const int64_t n_tiles = ceil_div(p.q_start + p.q_len, 64), units = n_tiles * p.n_kv_heads;
   EstShape best = {};
   double best_cost = -1.0;
-  const int hb0 = (group + most - 1) / most, hbs[4] = {hb0, hb0 + 1, hb0 + 2, group};
   static constexpr int kWaves[] = {16, 14, 12, 10, 9, 8, 7, 6, 5, 4};
-  for (const int hb : hbs) {
-    if (hb > group) continue;
-    const int heads = (group + hb - 1) / hb, n_hb = (group + heads - 1) / heads;
+  for (int heads = most < group ? most : group; heads >= 1; --heads) {
+    const int n_hb = (group + heads - 1) / heads;
+    if (heads > 1 && (group + heads - 2) / (heads - 1) == n_hb) continue;
     for (const int waves : kWaves) {
       const int lds = heads * ((dca ? 3 : 1) * 64 * p.head_dim * 2 + waves * head_bytes);
       if (lds > kEstLds - 64 || waves > est_waves(dca)) continue;
-      const int by_lds = kEstLds / lds, by_waves = kEstWaves / waves, per_cu = by_lds < by_waves ? by_lds : by_waves;
+      const int by_lds = kEstLds / lds, by_waves = est_waves(dca) / waves, per_cu = by_lds < by_waves ? by_lds : by_waves;
       for (int want = 1; want <= 3; ++want) {   // rounds
-        const double tiles = ceil(units * n_hb / ((double)waves * per_cu * n_cu * want));
-        const double blocks = ceil(n_tiles / (tiles * waves)), wgs = blocks * p.n_kv_heads * n_hb;
-        const double rounds = ceil(wgs / (n_cu * per_cu)), resident = rounds > 1 ? per_cu : ceil(wgs / n_cu);
-        const double rate = 0.3 + 0.7 * resident * waves / kEstWaves;
-        const double cost = rounds * (tiles * (2.0 * heads + 1.5) * rate + 1.5 + 0.2 * heads * kEstWaves / waves);
+        const int64_t tiles = ceil_div(units * n_hb, (int64_t)waves * per_cu * n_cu * want);
+        const int64_t blocks = ceil_div(n_tiles, tiles * waves), wgs = blocks * p.n_kv_heads * n_hb;
+        const int64_t rounds = ceil_div(wgs, n_cu * per_cu), resident = rounds > 1 ? per_cu : ceil_div(wgs, n_cu);
+        const double rate = 0.3 + 0.7 * (double)(resident * waves) / kEstWaves;
+        const double cost = (double)rounds * ((double)tiles * (2.0 * heads + 1.5) * rate + 1.5 + 0.2 * heads * kEstWaves / waves);
         if (best_cost < 0 || cost < best_cost) {
           best_cost = cost;
           best.heads = heads; best.n_hb = n_hb; best.waves = waves;
           best.tiles = (int32_t)tiles; best.n_blocks = (int32_t)blocks;
         }
+        if (tiles == 1) break;   // (no finer)
       }
     }
   }
