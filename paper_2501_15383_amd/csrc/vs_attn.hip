@@ -1688,10 +1688,11 @@ static AttnCut attn_cut(const vs_params& p, bool dense, int forced) {
   // costs about eight steps per 512 pieces and the second launch three.
   const int64_t slots = 512;
   double best = -1.0;
-  for (int drop = 0; drop < 3; ++drop) {
-    int64_t whole = units / slots * slots;
-    if (drop == 1) whole = whole >= slots ? whole - slots : 0;
-    if (drop == 2) whole = 0;
+  // whole rounds kept: all, all but one, none
+  const int64_t full = units / slots * slots, keep[3] = {full, full - slots, 0};
+  for (int x = 0; x < 3; ++x) {
+    const int64_t whole = keep[x];
+    if (x > 0 && (whole < 0 || whole == keep[x - 1])) continue;
     const int64_t rest = units - whole;
     for (int64_t n = 1; n <= kMaxSplit; ++n) {
       if (n > 1 && (rest == 0 || rest * n > kMaxPieces || steps / (double)n < kMinSteps)) break;

@@ -36,7 +36,7 @@ struct DecodeArgs {
   int64_t q_stride_head, k_stride_tok, k_stride_head, v_stride_tok, v_stride_head, o_stride_head;
   float scale_log2;
   int32_t v_budget, s_budget;
-  int64_t max_q_len, max_n_k;
+  int64_t max_n_k;
   // index sets: block-diagonal bitmap per (request, head), union list and its lengths per (request, KV head)
   uint32_t* bm;           // [n_req][Hq][words]
   uint2* ent;             // [n_req][Hkv][ent_stride] (diagonal, heads that have it)
@@ -660,7 +660,7 @@ hipError_t launch_decode(const vs_params& p, const vs_request* one, const vs_req
   a.v_stride_tok = p.v_stride_tok; a.v_stride_head = p.v_stride_head;
   a.scale_log2 = p.softmax_scale * kLog2e;
   a.v_budget = p.vertical_budget; a.s_budget = p.slash_budget;
-  a.max_q_len = p.q_len; a.max_n_k = p.q_start + p.q_len;
+  a.max_n_k = p.q_start + p.q_len;
   char* const w = (char*)ws;
   a.part_o = (float*)w;
   a.part_ml = (float*)(w + l.part_ml);
