@@ -74,6 +74,31 @@ def test_whole_units_and_cut_ones(c, s):
         assert ((a - b).norm(dim=2) <= 2e-2 * b.norm(dim=2)).all() and (la - lb).abs().max().item() < 1e-4
 
 
+# the same with Dual Chunk Attention: chunk boundaries inside the rows and the window's end inside key blocks, sampled around
+# both and in whole and cut tiles
+@pytest.mark.parametrize("c,s,chunk,window", [(66 * 128 - 5, 70, 3200, 320), (66 * 128 - 5, 4100 * 64 + 1, 4130 * 64, 576)])
+def test_whole_units_and_cut_ones_with_dca(c, s, chunk, window):
+    hq, hkv, d = 8, 1, 64
+    rng = np.random.default_rng(3110)
+    qs = [rand_bf16(rng, (c, hq, d)) for _ in range(3)]
+    k = rand_bf16(rng, (s + c, hkv, d)); v = rand_bf16(rng, (s + c, hkv, d))
+    pb = oracle.Problem(hq, hkv, d, c, s, 1.0 / np.sqrt(d), vertical_budget=300, slash_budget=400)
+    ref_dca = oracle.Dca(chunk, window, qs[1], qs[2])
+    gpu_dca = (dev(qs[1]), dev(qs[2]), chunk, window)
+    out, lse = vs.dense_causal_prefill(chunk_of(pb), dev(qs[0]), dev(k), dev(v), want_lse=True, dca=gpu_dca)
+    sets = _rand_sets(rng, pb, 290, 300, force_cols=[0], force_offs=range(64))
+    out_s, lse_s = vs.sparse_attn_prefill(chunk_of(pb), dev(qs[0]), dev(k), dev(v), *[_t(x) for x in sets], want_lse=True,
+                                          dca=gpu_dca)
+    torch.cuda.synchronize()
+    bound = chunk - s % chunk   # the first row of the next chunk
+    for rows in ([0, 57, 58, 191], [bound - 1, bound, bound + 40, bound + window], [c - 1, c - 128, c // 2]):
+        at = torch.tensor(rows, device="cuda")
+        ref = oracle.dense_attention(pb, qs[0], k, v, rows=rows, dca=ref_dca)
+        assert_attn_close(out[at], lse[:, at], *ref, f"dense dca C={c} s={s} rows {rows}")
+        ref = oracle.sparse_attention(pb, qs[0], k, v, *sets, rows=rows, dca=ref_dca)
+        assert_attn_close(out_s[at], lse_s[:, at], *ref, f"sparse dca C={c} s={s} rows {rows}")
+
+
 def test_ranges_that_are_asked_for_of_many_units():
     hq, hkv, d, c, s = 1100, 10, 64, 512, 2048 + 33   # 5,500 units, 41 key blocks: two ranges of each
     rng = np.random.default_rng(3120)

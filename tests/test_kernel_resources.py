@@ -4,7 +4,8 @@ The attention kernel runs two workgroups of four waves per compute unit, i.e. at
 vector registers per lane.  A change anywhere in its source can push an instantiation over
 that edge; the compiler then spills to scratch memory silently and the launch gets much
 slower (a Dual Chunk Attention launch went from 255 to 352 ms that way).  This test compiles
-csrc/vs_attn.hip to assembly and checks the resource lines of every instantiation."""
+csrc/vs_attn.hip to assembly and checks the resource lines of every instantiation.  The estimate, the
+selection and the decode kernel are written to register budgets too (waves per compute unit): theirs are checked below."""
 import os
 import re
 import subprocess
@@ -14,23 +15,31 @@ import pytest
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
-@pytest.fixture(scope="module")
-def resources(tmp_path_factory):
+def _compile(tmp_path_factory, name):
+    """(mangled name, its resources) of every kernel of csrc/<name>.hip"""
     from paper_2501_15383_amd import build
-    out = tmp_path_factory.mktemp("isa") / "vs_attn.s"
+    out = tmp_path_factory.mktemp("isa") / f"{name}.s"
     flags = [f for f in build.FLAGS if f not in ("-fPIC", "-Wall")]
     r = subprocess.run([build._hipcc()] + flags + ["-S", "--cuda-device-only", "-o", str(out),
-                                                    os.path.join(build.CSRC, "vs_attn.hip")],
+                                                    os.path.join(build.CSRC, f"{name}.hip")],
                        capture_output=True, text=True)
     assert r.returncode == 0, r.stderr[-2000:]
-    txt = out.read_text()
-    res = {}
-    for m in re.finditer(r"\.name:\s+(\S*k_attention\S*)\n(.*?)\.wavefront_size", txt, flags=re.S):
+    res = []
+    for m in re.finditer(r"\.name:\s+(\S*2vs\S*)\n(.*?)\.wavefront_size", out.read_text(), flags=re.S):
         body = m.group(2)
         get = lambda key: int(re.search(rf"\.{key}:\s+(\d+)", body).group(1))
-        t = re.search(r"k_attentionILi(\d+)ELi(\d+)ELb([01])ELb([01])ELb([01])", m.group(1))
-        res[tuple(int(x) for x in t.groups())] = dict(vgpr=get("vgpr_count"), spill=get("vgpr_spill_count"),
-                                                      scratch=get("private_segment_fixed_size"))
+        res.append((m.group(1), dict(vgpr=get("vgpr_count"), spill=get("vgpr_spill_count"),
+                                     scratch=get("private_segment_fixed_size"))))
+    return res
+
+
+@pytest.fixture(scope="module")
+def resources(tmp_path_factory):
+    res = {}
+    for name, r in _compile(tmp_path_factory, "vs_attn"):
+        t = re.search(r"k_attentionILi(\d+)ELi(\d+)ELb([01])ELb([01])ELb([01])", name)
+        if t:
+            res[tuple(int(x) for x in t.groups())] = r
     return res
 
 
@@ -53,3 +62,24 @@ def test_the_dca_kernels_spill_no_more_than_a_handful_of_registers(resources):
     for key, r in resources.items():
         if key[2]:
             assert r["spill"] <= 16 and r["scratch"] <= 128, (key, r)
+
+
+# (kernel, vector registers that its waves per compute unit allow, registers spilled today and a few): four waves per SIMD of
+# the estimate's sweeps have 128, three with Dual Chunk Attention 168 (whose patterns per pair are what spills at head_dim 128);
+# a selection row is one workgroup of 16 waves, 128; the decode kernel's four waves share a compute unit's LDS with nobody
+@pytest.mark.parametrize("source,budgets", [
+    ("vs_estimate", {"k_est_sumsILi128ELb0E": (128, 12), "k_est_scoresILi128ELb0E": (128, 0), "k_est_sumsILi64ELb0E": (128, 0),
+                     "k_est_scoresILi64ELb0E": (128, 0), "k_est_sumsILi128ELb1E": (168, 56), "k_est_scoresILi128ELb1E": (168, 32),
+                     "k_est_sumsILi64ELb1E": (168, 12), "k_est_scoresILi64ELb1E": (168, 0)}),
+    ("vs_select", {"k_sel_rowILi8E": (128, 0), "k_sel_rowILi16E": (128, 0), "k_sel_rowILi32E": (128, 16), "k_sel_rowILi0E": (128, 0),
+                   "k_sel_sample": (128, 0), "k_sel_filter": (128, 0), "k_slice_digit": (64, 0), "k_slice_count": (64, 0),
+                   "k_slice_write": (64, 0)}),
+    ("vs_decode", {"k_decodeILi128E": (256, 0), "k_decodeILi64E": (256, 0), "k_decode_lists": (64, 0)}),
+])
+def test_the_other_kernels_keep_their_register_budgets(tmp_path_factory, source, budgets):
+    res = _compile(tmp_path_factory, source)
+    for kernel, (vgpr, spill) in budgets.items():
+        found = [r for name, r in res if kernel in name]
+        assert len(found) == 1, (kernel, [n for n, _ in res])
+        assert found[0]["vgpr"] <= vgpr and found[0]["spill"] <= spill, (kernel, found[0])
+        assert spill or found[0]["scratch"] == 0, (kernel, found[0])
