@@ -212,6 +212,19 @@ def main():
                 f"   wave cycles in s_waitcnt {a['SQ_WAIT_INST_ANY'] / a['SQ_WAVE_CYCLES'] * 100:.1f}% (of which on LDS "
                 f"{a['SQ_WAIT_INST_LDS'] / a['SQ_WAVE_CYCLES'] * 100:.1f}%), waiting for anything {a['SQ_WAIT_ANY'] / a['SQ_WAVE_CYCLES'] * 100:.1f}%; "
                 f"LDS bank conflicts {a['SQ_LDS_BANK_CONFLICT']:.0f}, LDS data FIFO full {a['SQ_LDS_DATA_FIFO_FULL']:.0f}, command FIFO full {a['SQ_LDS_CMD_FIFO_FULL']:.0f} cycles"]
+    # ---- 4. the same for the sweeps of the estimate
+    out += ["", "## 4. SQ counters of the estimate's sweeps (the same runs)", ""]
+    for nm, ms in (("k_est_sums<128, false>", ta), ("k_est_scores<128, false>", tb)):
+        a = collections.defaultdict(float)
+        for run in ("sq1", "sq2", "sq3"):
+            for k, v in pick(dispatches(run, base), nm)[0].items():
+                a.setdefault(k, v)
+        cyc = a["GRBM_GUI_ACTIVE"] / 8
+        out.append(f"{nm}: {cyc / 1e6:.3f} M cycles over {ms:.3f} ms; MFMA busy {a['SQ_VALU_MFMA_BUSY_CYCLES'] / 1024 / cyc * 100:.0f}%, "
+                   f"VALU active {a['SQ_ACTIVE_INST_VALU'] * 4 / 1024 / cyc * 100:.0f}% (MFMA issue included) of the clocked cycles; per MFMA "
+                   f"{a['SQ_INSTS_VALU'] / a['SQ_INSTS_MFMA']:.1f} VALU (MFMA included), {a['SQ_INSTS_VALU_TRANS_F32'] / a['SQ_INSTS_MFMA']:.1f} "
+                   f"transcendental, {a['SQ_INSTS_LDS'] / a['SQ_INSTS_MFMA']:.2f} LDS, {a['SQ_INSTS_VMEM'] / a['SQ_INSTS_MFMA']:.2f} VMEM; "
+                   f"wave cycles waiting for anything {a['SQ_WAIT_ANY'] / a['SQ_WAVE_CYCLES'] * 100:.0f}%")
     os.makedirs(os.path.join(ROOT, "profiles"), exist_ok=True)
     open(os.path.join(ROOT, "profiles", "vs_kernels_7b_1m_last_chunk.txt"), "w").write("\n".join(out) + "\n")
     json.dump({"kernel": "k_attention", "workload": "7b_1m last chunk", "kernel_source_sha": bench.kernel_source_hash(),

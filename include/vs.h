@@ -163,9 +163,10 @@ int vs_prefill_chunk(const vs_params *p, const void *q, const void *k,
                      size_t ws_bytes, void *stream);
 
 /* Work accounting for a set of index sets: per head, the number of 64x64
- * (query block, key block) tiles the sparse kernel issues for this chunk
- * (slash tiles, then vertical tiles of up to 64 gathered columns).  This is the
- * unit in which the FLOPs "on computed blocks" are counted (section 5.3.1 quotes
+ * (query block, key block) tiles that its sets need in this chunk (slash tiles, then
+ * vertical tiles of up to 64 gathered columns).  The sparse kernel issues these and no
+ * others where a tile is one head's; short chunks whose heads share tiles, and single
+ * tokens, walk the union of the heads' lists.  This is the unit in which the FLOPs "on computed blocks" are counted (section 5.3.1 quotes
  * the kernel's FLOPs utilisation) and the cost that section 5.3.2 sizes chunks by.
  *   tiles: int64 [Hq][2] = {slash tiles, vertical tiles}. */
 int vs_count_tiles(const vs_params *p, const int32_t *v_idx, const int32_t *v_cnt,

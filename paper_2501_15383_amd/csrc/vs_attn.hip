@@ -1570,7 +1570,8 @@ __global__ __launch_bounds__(kBlThreads) void k_build_blocklist(const ListArgs a
 
 // Issued-tile accounting, one workgroup per head: for every query block of the chunk, the
 // number of slash tiles (computed diagonals a <= m) and of vertical tiles (groups of 64
-// gathered columns with at least one usable column).  Mirrors what k_attention executes.
+// gathered columns with at least one usable column).  This is the work that the head's own sets ask for, and what k_attention
+// executes where a tile is one head's; tiles that heads share, and single tokens, walk the union of their heads' lists.
 __global__ __launch_bounds__(256) void k_count_tiles(const int32_t* v_idx, const int32_t* v_cnt,
                                                     int32_t v_budget, const uint32_t* bm_a,
                                                     int n_words, int64_t q_start, int64_t q_len,
