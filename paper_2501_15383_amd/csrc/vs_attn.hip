@@ -38,7 +38,6 @@
 //    its own instantiation.
 #include <atomic>
 #include <mutex>
-#include <type_traits>
 
 #include "vs_common.h"
 
@@ -1263,7 +1262,7 @@ struct ListArgs {
   int32_t s_budget, dense, n_blk, n_words, ent_stride;
   uint32_t* bm_a;
   uint32_t* ent;
-  int32_t n_lists, n_heads, group, pack;   // n_lists: of a call, or of a request at most
+  int32_t n_heads, group, pack;
   uint32_t* zero;
   int32_t n_zero;
   // a batch
@@ -1367,19 +1366,19 @@ __device__ void write_plan(const ListArgs& a, int64_t* scan) {
   }
 }
 // List x0; false: nothing to be done for it or the ones behind it.
-template <int NQB>
+template <int NQB, bool BATCH>
 __device__ __forceinline__ bool build_list(const ListArgs& a, int x0) {
   constexpr int NW = kBlThreads / 64;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int part = a.req ? 0 : blockIdx.y, n_parts = a.req ? 1 : gridDim.y;
+  const int part = BATCH ? 0 : blockIdx.y, n_parts = BATCH ? 1 : gridDim.y;
   const int r = (int)blockIdx.y - 1;   // (of a batch, whose first workgroup is the plan's)
   const int n_words = a.n_words, ent_stride = a.ent_stride;
   int dense = a.dense, n_blk = a.n_blk, pack = a.pack, n_hs = (a.group + pack - 1) / pack;
   const int32_t* s_idx = a.s_idx;
   const int32_t* s_cnt = a.s_cnt;
   uint32_t* bm_a = a.bm_a;
-  if (a.req) {
+  if constexpr (BATCH) {
     const vs_request rq = a.req[r];
     BatchShape b;
     if (!batch_shape(rq, a.group, a.n_heads / a.group, a.max_q_len, a.max_n_k, a.skip_single, batch_pack(rq, a.group), b)) return false;
@@ -1391,9 +1390,9 @@ __device__ __forceinline__ bool build_list(const ListArgs& a, int x0) {
     bm_a += (int64_t)r * a.n_heads * n_words;
     if (x0 >= (b.dense ? 1 : a.n_heads / a.group * n_hs)) return false;   // (a dense request has one list for all heads)
   }
-  uint32_t* const E = a.ent + ((a.req ? (int64_t)r * a.n_heads : 0) + x0) * ent_stride;
+  uint32_t* const E = a.ent + ((BATCH ? (int64_t)r * a.n_heads : 0) + x0) * ent_stride;
   // the first head of list x0, and how many heads it has
-  const int grp = dense && !a.req ? 0 : x0 / n_hs, h0 = dense && !a.req ? 0 : grp * a.group + (x0 - grp * n_hs) * pack;
+  const int grp = dense && !BATCH ? 0 : x0 / n_hs, h0 = dense && !BATCH ? 0 : grp * a.group + (x0 - grp * n_hs) * pack;
   const int n_in = grp * a.group + a.group - h0 < pack ? grp * a.group + a.group - h0 : pack;
   uint32_t* const A = bm_a + (int64_t)h0 * n_words;
   // The last two words of the bitmap row lie beyond every diagonal.  The last one tells the attention
@@ -1553,18 +1552,22 @@ __device__ __forceinline__ bool build_list(const ListArgs& a, int x0) {
   if (tid == 0) write_tail(running);
   return true;
 }
-template <int NQB>
+template <int NQB, bool BATCH>
 __global__ __launch_bounds__(kBlThreads) void k_build_blocklist(const ListArgs a) {
   if (blockIdx.x == 0 && blockIdx.y == 0)
     for (int x = threadIdx.x; x < a.n_zero; x += kBlThreads) a.zero[x] = 0u;
-  if (a.req && blockIdx.y == 0) {
+  if constexpr (BATCH) {
     __shared__ int64_t scan[kBlThreads / 64];
-    if (blockIdx.x == 0) write_plan(a, scan);
-    return;
-  }
-  for (int x0 = blockIdx.x; x0 < a.n_lists; x0 += gridDim.x) {
-    if (!build_list<NQB>(a, x0)) return;   // (the same for all threads)
-    __syncthreads();   // its LDS is the next list's
+    if (blockIdx.y == 0) {
+      if (blockIdx.x == 0) write_plan(a, scan);
+      return;
+    }
+    for (int x0 = blockIdx.x; x0 < a.n_heads; x0 += gridDim.x) {
+      if (!build_list<NQB, true>(a, x0)) return;   // (the same for all threads)
+      __syncthreads();   // its LDS is the next list's
+    }
+  } else {
+    build_list<NQB, false>(a, blockIdx.x);
   }
 }
 
@@ -1729,8 +1732,8 @@ size_t attn_sync_bytes(const vs_params& p) { return attn_counter_bytes(p) + attn
 // One workgroup folds 1024 / D rows of a unit at a time; those of a batch, whose cut units only the device knows, take the next
 // ones until none are left (a grid for as many units as there may be: 26 us for 1,500 requests none of which was cut, 4 now),
 // and up to four of a unit in a row where there are more than workgroups, because finding them takes as long as folding a few
-// pieces.  Eight pieces at a time are on their way (four: 55 us for two requests of 64 rows and 40,000 keys in 128 ranges, 17
-// now; with few pieces four).
+// pieces.  Eight pieces at a time are on their way (four: 55 us for two requests of 64 rows and 40,000 keys in 128 ranges, 24
+// now).
 template <int D>
 constexpr int combine_parts() { return kTileRows / (1024 / D); }   // per unit
 constexpr int kCombineGrid = 2048;   // workgroups for a batch at most
@@ -1768,37 +1771,46 @@ __global__ __launch_bounds__(256) void k_attn_combine(const AttnArgs a0) {
   if (row < 0 || row >= a.q_rows || h - g * a.group + th >= a.group) continue;
   const int hw = h + th;
   const int64_t at = (int64_t)(BATCH ? e + a.first_slot : e) * kTileRows + lrow, step = (int64_t)n_fold * kTileRows;
+  constexpr int U = 8;
   float M = -INFINITY;
-#pragma unroll 8
-  for (int sp = 0; sp < a.n_split; ++sp) M = fmaxf(M, a.part_ml[2 * (at + step * sp)]);
+  int sp = 0;
+  for (; sp + U <= a.n_split; sp += U) {
+    float m[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) m[u] = a.part_ml[2 * (at + step * (sp + u))];
+#pragma unroll
+    for (int u = 0; u < U; ++u) M = fmaxf(M, m[u]);
+  }
+#pragma unroll 4
+  for (; sp < a.n_split; ++sp) M = fmaxf(M, a.part_ml[2 * (at + step * sp)]);
   const float M0 = M == -INFINITY ? 0.f : M;
   float L = 0.f;
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  auto fold = [&](auto pieces) {
-    constexpr int U = decltype(pieces)::value;
-    for (int s0 = 0; s0 < a.n_split; s0 += U) {
-      float m[U], l[U];
-      f32x4 o[U];
+  // (a piece without live keys: weight 0, and zeros in its slot)
+  auto fold = [&](float m, float l, f32x4 o) {
+    const float w = __builtin_amdgcn_exp2f(m - M0);
+    L += l * w;
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int64_t x = at + step * (s0 + u < a.n_split ? s0 + u : a.n_split - 1);
-        m[u] = a.part_ml[2 * x];
-        l[u] = a.part_ml[2 * x + 1];
-        o[u] = *(const f32x4*)(a.part_o + x * D + d);
-      }
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        // (a piece without live keys: 0, and zeros in its slot)
-        const float w = s0 + u < a.n_split ? __builtin_amdgcn_exp2f(m[u] - M0) : 0.f;
-        L += l[u] * w;
-#pragma unroll
-        for (int x = 0; x < 4; ++x) acc[x] += o[u][x] * w;
-      }
-    }
+    for (int x = 0; x < 4; ++x) acc[x] += o[x] * w;
   };
-  if (a.n_split > 4) fold(std::integral_constant<int, 8>{});
-  else if (a.n_split > 2) fold(std::integral_constant<int, 4>{});
-  else fold(std::integral_constant<int, 2>{});
+  for (sp = 0; sp + U <= a.n_split; sp += U) {
+    float m[U], l[U];
+    f32x4 o[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t x = at + step * (sp + u);
+      m[u] = a.part_ml[2 * x];
+      l[u] = a.part_ml[2 * x + 1];
+      o[u] = *(const f32x4*)(a.part_o + x * D + d);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) fold(m[u], l[u], o[u]);
+  }
+#pragma unroll 4
+  for (; sp < a.n_split; ++sp) {
+    const int64_t x = at + step * sp;
+    fold(a.part_ml[2 * x], a.part_ml[2 * x + 1], *(const f32x4*)(a.part_o + x * D + d));
+  }
   const float inv = L > 0.f ? 1.0f / L : 0.f;
 #pragma unroll
   for (int x = 0; x < 4; ++x) acc[x] *= inv;
@@ -1910,8 +1922,7 @@ hipError_t launch_build_blocklist(const vs_params& p, const int32_t* s_idx, cons
   a.n_zero = sync_ws ? (int)(attn_counter_bytes(p) / sizeof(uint32_t)) : 0;
   const unsigned parts = dense ? (unsigned)ceil_div(bl.ent_stride, kBlDensePart) : 1u;
   const unsigned lists = dense ? 1u : (unsigned)(p.n_kv_heads * ceil_div(a.group, a.pack));
-  a.n_lists = (int)lists;
-  hipLaunchKernelGGL((k_build_blocklist<kAttnQBlocks>), dim3(lists, parts), dim3(kBlThreads), 0, st, a);
+  hipLaunchKernelGGL((k_build_blocklist<kAttnQBlocks, false>), dim3(lists, parts), dim3(kBlThreads), 0, st, a);
   return hipGetLastError();
 }
 
@@ -2141,9 +2152,8 @@ hipError_t launch_attention_batch(const vs_params& p, const vs_request* req, int
   l.max_q_len = p.q_len; l.max_n_k = n_k;
   // (a few workgroups per request where they fill the chip: 24,000 of 1,024 threads that find nothing to do, for 1,500 dense
   // requests of 16 heads, took 187 us, 48 so)
-  l.n_lists = p.n_q_heads;
   const int each = (int)ceil_div(kListGroups, n_req);
-  hipLaunchKernelGGL((k_build_blocklist<NQB>), dim3((unsigned)(each < p.n_q_heads ? each : p.n_q_heads), (unsigned)n_req + 1),
+  hipLaunchKernelGGL((k_build_blocklist<NQB, true>), dim3((unsigned)(each < p.n_q_heads ? each : p.n_q_heads), (unsigned)n_req + 1),
                      dim3(kBlThreads), 0, st, l);
   if ((e = hipGetLastError()) != hipSuccess) return e;   // (what follows goes by the plan and the lists)
   const dim3 grid((unsigned)a.n_wg), block(128 * NQB);
