@@ -3,7 +3,8 @@
 // tokens of each chunk).  For the W' <= 64 window rows of every head: causal softmax rows
 // over all n_k keys, summed along columns (vscore) and along diagonals pos - j (sscore).
 //
-// Two sweeps over the K cache (each reads it once for all heads of a KV group):
+// Two sweeps over the K cache (read once for every workgroup's share of the heads of a KV group: up to four heads in sweep A,
+// seven in sweep B):
 //   sweep A  per-row running (max, sum) over a range of keys -> partials -> k_estimate_combine -> lse
 //   sweep B  P = exp2(S * scale*log2e - lse2), summed along columns and diagonals; run-to-run identical
 // bf16 MFMA (32x32x16) with fp32 accumulation; sweep A uses the K Q^T orientation (a lane owns one query), sweep B the Q K^T
@@ -40,15 +41,15 @@ struct EstArgs {
 };
 
 // A wave holds the K rows of 64 keys in registers, as MFMA operands straight from memory, and takes the query heads of the KV
-// group one after the other; the window rows of all of them wait in LDS.  So K is read once per sweep, nothing is staged and
-// there is no barrier on the way.
-// Bound: issue cycles.  On this chip the cycles of the vector instructions and those of the matrix products add up (counters:
-// 61 % + 39 % of sweep A, 76 % + 33 % of sweep B), whatever the order they are issued in: the next block's product interleaved
-// with this one's exponentials by hand, two or three waves per SIMD and more registers, was 5 to 20 % slower.  Per 64 scores there
-// are 16 cycles of MFMA, in sweep A fma, exp, add and half a max, in sweep B half a lane swap, fma, exp and five more (column
-// sum, diagonals).  1M keys, 28 query / 4 KV heads of 128: sweep A 590 us, sweep B 740, 1.38 ms with everything; with the K tiles
-// in LDS, a barrier per tile, 32 rows per wave, the diagonals turned by LDS lane exchanges and a pass that cleared the scores
-// 640 + 950, 1.63.  Small calls are cut finer: 8,192 keys 77 us -> 45.
+// group one after the other; the window rows of all of them wait in LDS.  Nothing is staged and there is no barrier on the way.
+// Bound: of sweep B the issue cycles (80 % vector instructions, matrix products included, 32 % MFMA busy at 1M keys, 28 query / 4
+// KV heads of 128); of sweep A these (50 % and 33 %) and its reads: the state of four heads fills the LDS, so K goes by twice
+// (2.24 GB for a cache of 1.07, 4.0 TB/s) and waves wait 43 % of their cycles.  The next block's product interleaved with this
+// one's exponentials by hand, two or three waves per SIMD and more registers, was 5 to 20 % slower.  Per 64 scores there are 16
+// cycles of MFMA, in sweep A fma, exp, add and half a max, in sweep B half a lane swap, fma, exp and five more (column sum,
+// diagonals).  1M keys: sweep A 533 to 590 us by box, sweep B 687 to 740, 1.24 to 1.38 ms with everything; with the K tiles in LDS,
+// a barrier per tile, 32 rows per wave, the diagonals turned by LDS lane exchanges and a pass that cleared the scores 640 +
+// 950, 1.63.  Small calls are cut finer: 8,192 keys 77 us -> 33.
 constexpr int kEstWaves = 16;    // waves per workgroup at most, and per compute unit: four per SIMD, 128 registers
 constexpr int est_waves(bool dca) { return dca ? 12 : kEstWaves; }   // (a block of several rotations needs the registers)
 constexpr int kEstLds = 160 << 10;
@@ -62,7 +63,8 @@ struct EstShape {
 };
 
 // what a workgroup of either sweep is: its KV head, heads, and the tiles of its waves.  The n_hb workgroups of one (key range,
-// KV head) are placed on one XCD (blockIdx b and b + 8), so that the second finds the K rows in that XCD's L2.
+// KV head) are placed on one XCD (blockIdx b and b + 8).  At long contexts the second does not find the K rows in that XCD's L2 all
+// the same (see above: its 32 workgroups have 4 MB of them on their way).
 struct EstPlace {
   int g, h0, n_h, blk;
   bool ok;
