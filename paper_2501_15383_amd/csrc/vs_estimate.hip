@@ -47,7 +47,7 @@ struct EstArgs {
 // (2.24 GB for a cache of 1.07, 4.0 TB/s) and waves wait 43 % of their cycles.  The next block's product interleaved with this
 // one's exponentials by hand, two or three waves per SIMD and more registers, was 5 to 20 % slower.  Per 64 scores there are 16
 // cycles of MFMA, in sweep A fma, exp, add and half a max, in sweep B half a lane swap, fma, exp and five more (column sum,
-// diagonals).  1M keys: sweep A 533 to 590 us by box, sweep B 687 to 740, 1.24 to 1.38 ms with everything; with the K tiles in LDS,
+// diagonals).  1M keys: sweep A 533 to 590 us by card, sweep B 687 to 740, 1.24 to 1.38 ms with everything; with the K tiles in LDS,
 // a barrier per tile, 32 rows per wave, the diagonals turned by LDS lane exchanges and a pass that cleared the scores 640 +
 // 950, 1.63.  Small calls are cut finer: 8,192 keys 77 us -> 33.
 constexpr int kEstWaves = 16;    // waves per workgroup at most, and per compute unit: four per SIMD, 128 registers
