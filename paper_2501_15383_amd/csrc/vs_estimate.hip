@@ -441,15 +441,19 @@ __global__ __launch_bounds__(1024) void k_estimate_combine(const EstArgs a) {
 }
 
 // The cut of a sweep, by the time it should take, in units of one row block of a wave with 16 waves on the compute unit
-// (about 2.8 us): a tile costs 2 per head and 1.5 for its K rows, a workgroup its start and the window rows it puts into LDS,
-// and a row block is faster with fewer waves around.  Small calls are made of few rounds of workgroups, so the waves per
-// workgroup are whatever fills them.  28 / 4 heads, against at most 16 waves and always many heads per workgroup: 38,209 keys
-// 111 -> 85 us, 84,333 178 -> 146, 300,001 501 -> 420; 1M the same.  head_bytes: LDS per head and wave, beside the rows.
-// A workgroup of fewer heads than the group is tried at every count that leaves fewest for the last one (32 heads: shares of 4
-// come out even, 7 + 7 + 7 + 7 + 4 do not; 131,072 keys 258 -> 195 us).
+// (about 2.8 us): a tile costs 2 per head and something for its K rows, a row block is faster with fewer waves around; a
+// workgroup costs its start and the window rows that it puts into LDS, a wave per head what it adds to its neighbours' offsets
+// (atomic additions), and every share of the heads its K rows once more.  With Dual Chunk Attention the start (up to three
+// rotations, patterns) weighs more.  The weights are fitted to all cuts of 130 calls (1 to 64 heads, 2,558 to 300,001 keys): the
+// chosen cuts are within 2.6 % of the best ones on average, 0.9 % with Dual Chunk Attention (with fewer terms 4.2 and 1.7, and
+// worst cases of 54 and 29 %).  Small calls are made of few rounds of workgroups, so the waves per workgroup are whatever fills
+// them.  28 / 4 heads, against at most 16 waves and always many heads per workgroup: 38,209 keys 111 -> 85 us, 84,333 178 -> 146,
+// 300,001 501 -> 420; 1M the same; DCA, 26,543 keys 173 -> 100.  head_bytes: LDS per head and wave, beside the rows.
+// Shares are those that leave fewest heads for the last one (of 32 heads 4 each, not 7, 7, 7, 7 and 4: 131,072 keys 258 -> 195 us).
 static EstShape est_shape(const vs_params& p, int most, int head_bytes, bool dca) {
   const int group = p.n_q_heads / p.n_kv_heads, n_cu = 256;
   const int64_t n_tiles = ceil_div(p.q_start + p.q_len, 64), units = n_tiles * p.n_kv_heads;
+  const double k_rows = dca ? 2.0 : 0.5, start = dca ? 4.0 : 1.5, fill = dca ? 0.2 : 0.3, seam = dca ? 1.5 : 2.0, again = dca ? 0.5e-3 : 2e-3;
   EstShape best = {};
   double best_cost = -1.0;
   static constexpr int kWaves[] = {16, 14, 12, 10, 9, 8, 7, 6, 5, 4};
@@ -464,8 +468,9 @@ static EstShape est_shape(const vs_params& p, int most, int head_bytes, bool dca
         const int64_t tiles = ceil_div(units * n_hb, (int64_t)waves * per_cu * n_cu * want);
         const int64_t blocks = ceil_div(n_tiles, tiles * waves), wgs = blocks * p.n_kv_heads * n_hb;
         const int64_t rounds = ceil_div(wgs, n_cu * per_cu), resident = rounds > 1 ? per_cu : ceil_div(wgs, n_cu);
-        const double rate = 0.3 + 0.7 * (double)(resident * waves) / kEstWaves;
-        const double cost = (double)rounds * ((double)tiles * (2.0 * heads + 1.5) * rate + 1.5 + 0.2 * heads * kEstWaves / waves);
+        const double rate = 0.2 + 0.8 * (double)(resident * waves) / kEstWaves;
+        const double cost = (double)rounds * ((double)tiles * (2.0 * heads + k_rows) * rate + start + fill * heads * kEstWaves / waves +
+                                              seam * heads) + again * (double)(n_hb * units);
         if (best_cost < 0 || cost < best_cost) {
           best_cost = cost;
           best.heads = heads; best.n_hb = n_hb; best.waves = waves;
