@@ -444,7 +444,7 @@ __global__ __launch_bounds__(1024) void k_estimate_combine(const EstArgs a) {
 // (about 2.8 us): a tile costs 2 per head and something for its K rows, a row block is faster with fewer waves around; a
 // workgroup costs its start and the window rows that it puts into LDS, a wave per head what it adds to its neighbours' offsets
 // (atomic additions), and every share of the heads its K rows once more.  With Dual Chunk Attention the start (up to three
-// rotations, patterns) weighs more.  The weights are fitted to all cuts of 130 calls (1 to 64 heads, 2,558 to 300,001 keys): the
+// rotations, patterns) weighs more.  The weights are fitted to all cuts of 193 calls (1 to 64 heads, 2,558 to 300,001 keys): the
 // chosen cuts are within 2.6 % of the best ones on average, 0.9 % with Dual Chunk Attention (with fewer terms 4.2 and 1.7, and
 // worst cases of 54 and 29 %).  Small calls are made of few rounds of workgroups, so the waves per workgroup are whatever fills
 // them.  28 / 4 heads, against at most 16 waves and always many heads per workgroup: 38,209 keys 111 -> 85 us, 84,333 178 -> 146,
