@@ -40,8 +40,8 @@ def _stale(target: str, deps: list[str]) -> bool:
 def build(force: bool = False, verbose: bool = False, extra_flags: list[str] | None = None,
           variant: str | None = None) -> str:
     """Compile and link libvs.so.  With `variant` the objects go to _build/<variant>/ and the library
-    to libvs_<variant>.so next to libvs.so (a build with other -D switches, e.g. the timing diagnostics
-    of vs_attn.hip; load it by setting VS_LIB_PATH)."""
+    to libvs_<variant>.so next to libvs.so (a build with other flags beside the one in
+    use; load it by setting VS_LIB_PATH)."""
     build_dir = os.path.join(BUILD, variant) if variant else BUILD
     lib = os.path.join(HERE, f"libvs_{variant}.so") if variant else LIB
     os.makedirs(build_dir, exist_ok=True)

@@ -304,17 +304,6 @@ __device__ __forceinline__ uint32_t lds_address(const void* p) {
   return (uint32_t)(size_t)(const __attribute__((address_space(3))) char*)p;
 }
 
-// Timing diagnostics (never defined in the library that ships; results are WRONG with any of them,
-// all accesses stay in bounds and every barrier that remains is reached by all waves):
-//   VS_X_NOVLDS     the V^T fragments of the fused step come from a register instead of LDS
-//                   (half of the LDS operand reads gone, same MFMA count)
-//   VS_X_NOCOPY     the global -> LDS copies of whole key blocks are skipped after the first two
-//   VS_X_SAMEBLK    every whole-block copy reads key block 0 or 1 of the head (always in the L2)
-//   VS_X_NOBARRIER  no workgroup barrier at the end of a step
-//   VS_X_TIGHT      dense list only: the steady-state steps run in a loop with no list reads, no
-//                   tile classification and no bookkeeping beyond the pace keeping (right results)
-// They split the time of a step into what the arithmetic stream, the operand reads, the copies
-// and the barrier cost.
 constexpr int kHeadShift = 27;   // vertical tile of packed heads: (head << kHeadShift) | tile of 64 columns (a head has at most 2^25)
 template <int D, int NQB, bool DCA, bool SPLIT, bool BATCH = false>
 __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
@@ -644,14 +633,7 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
       const int64_t j0 = (int64_t)(m0 - (idx - (NQB - 1))) * 64;
       if (__builtin_expect(j0 + 64 <= n_k, 1)) {  // whole block in range: uniform bases + one per-lane 32-bit offset
         fast = true;
-#ifdef VS_X_NOCOPY
-        if (ei > ei0 + 1) return;
-#endif
-#ifdef VS_X_SAMEBLK
-        const char* kt = (const char*)kbase + (j0 & 64) * a.k_stride_tok * 2;
-#else
         const char* kt = (const char*)kbase + j0 * a.k_stride_tok * 2;
-#endif
         if constexpr (GPW == 4) dma16x4(kdst, kt, koff[0], koff[1], koff[2], koff[3], WAVES * 1024);
         else if constexpr (GPW == 2) dma16x2(kdst, kt, koff[0], koff[1], WAVES * 1024);
         else dma16_lane_ptr(kdst, kt + koff[0]);
@@ -672,14 +654,7 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
       const int64_t j0 = (int64_t)(m0 - (idx - (NQB - 1))) * 64;
       if (__builtin_expect(j0 + 64 <= n_k, 1)) {
         fast = true;
-#ifdef VS_X_NOCOPY
-        if (ei > ei0 + 1) return;
-#endif
-#ifdef VS_X_SAMEBLK
-        const char* vt = (const char*)vbase + (j0 & 64) * a.v_stride_tok * 2;
-#else
         const char* vt = (const char*)vbase + j0 * a.v_stride_tok * 2;
-#endif
         if constexpr (GPW == 4) dma16x4(vdst, vt, voff[0], voff[1], voff[2], voff[3], WAVES * 1024);
         else if constexpr (GPW == 2) dma16x2(vdst, vt, voff[0], voff[1], WAVES * 1024);
         else dma16_lane_ptr(vdst, vt + voff[0]);
@@ -921,11 +896,7 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
     auto v_index = [&](int n) -> int { return n < NM + 3 * NBQ ? (n - NM) / 3 : n - NM - 2 * NBQ; };
     auto frag = [&](int n) -> bf16x8 {
       if (is_k(n)) return k_load(kb, k_index(n) / NM, k_index(n) % NM);
-#ifdef VS_X_NOVLDS
-      return qreg[v_index(n) % DSTEPS];
-#else
       return v_frag(vbp, v_index(n));
-#endif
     };
     bf16x8 fq[NB];
     f32x16 sa, sn;
@@ -1098,9 +1069,7 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
     int nn_kind = nxt_kind, nn_idx = nxt_idx, nn_mask = nxt_mask;
     if (nxt_kind != 2) advance(nn_kind, nn_idx, nn_mask);
     wait_copies();
-#ifndef VS_X_NOBARRIER
     __syncthreads();
-#endif
     cur_kind = nxt_kind; cur_idx = nxt_idx; cur_mask = nxt_mask;
     nxt_kind = nn_kind; nxt_idx = nn_idx; nxt_mask = nn_mask;
     buf ^= 1;
@@ -1111,26 +1080,6 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
     classify();
     // steady state: runs of steps in which this wave multiplies tile i and folds in tile i - 1
     while (__builtin_expect(pend && part && !(diag || vert || !have_max), 1)) {
-#ifdef VS_X_TIGHT
-      // timing diagnostic (dense list only: entry index = cc, every mask full): the steps of the walk with
-      // nothing but the fused arithmetic, the copies, the pace keeping and the barrier
-      if (!DCA && !SPLIT && a.bm_stride == 0 && cur_kind == 0 && nxt_kind == 0 && cur_idx >= NQB) {
-        while (cur_idx + 2 <= cc_end) {
-          const int ci = cur_idx;
-          auto launch = [&]() { issue_k(0, ci + 1, buf ^ 1, 0); issue_v(0, ci, buf, 0); };
-          fused(Ks + buf * TILE, Vs + (buf ^ 1) * TILE, launch);
-          enter_segment((cc_last - (ci + 2)) >> (a.sync_shift + seg_shift), true);
-          wait_copies();
-          __syncthreads();
-          ++cur_idx;
-          buf ^= 1;
-        }
-        nxt_idx = cur_idx + 1; nxt_mask = 3; cur_mask = 3;
-        ei = nxt_idx;
-        ecache = ent_h[(ei & ~63) + lane]; ecache_nx = ent_h[(ei & ~63) + 64 + lane];
-        classify();
-      }
-#endif
       if (__builtin_expect(!fused(kb, vbp, launch_copies), 0)) qk_exact(kb, diag, vert, apply_mask);
       end_step();
       classify();
