@@ -3,15 +3,16 @@
 // tokens of each chunk).  For the W' <= 64 window rows of every head: causal softmax rows
 // over all n_k keys, summed along columns (vscore) and along diagonals pos - j (sscore).
 //
-// Two sweeps over the K cache (read once for every workgroup's share of the heads of a KV group: up to four heads in sweep A,
-// seven in sweep B):
-//   sweep A  per-row running (max, sum) over a range of keys -> partials -> k_estimate_combine -> lse
+// Two sweeps over the K cache (read once for every workgroup's share of the heads of a KV group, up to seven):
+//   sweep A  per-row (reference, sum) over a range of keys -> partials -> k_estimate_combine -> lse
 //   sweep B  P = exp2(S * scale*log2e - lse2), summed along columns and diagonals; run-to-run identical
 // bf16 MFMA (32x32x16) with fp32 accumulation; sweep A uses the K Q^T orientation (a lane owns one query), sweep B the Q K^T
 // orientation (a lane owns one key).  With Dual Chunk Attention (template parameter DCA) the rotations of the window rows
-// that a workgroup's keys meet lie in LDS side by side, and a block of (32 rows, 64 keys) takes the one it needs; where the
-// pattern changes inside the block, the products of all that occur, and every pair keeps that of its own pattern.
-// (28 heads, 400,000 keys: 830 us; with sweeps of their own that staged K in LDS 1,176; 2,558 keys, 8 heads: 20 against 71.)
+// that a workgroup's keys meet lie in LDS side by side, and every lane reads its row in the rotation that the row meets the nearest
+// key of the tile in: rows on both sides of a chunk boundary still take one product.  Where the window ends inside the tile, a
+// second product has the rows in the rotation of the farthest key, and every pair keeps that of its own side.  (Before, a tile took
+// one product per rotation that any of 32 rows needed: 28 heads, 300,001 keys 640 us -> 424, with the window of rows across a
+// chunk boundary 1,224 -> 433; 2,558 keys 38 -> 29.)
 #include <math.h>
 
 #include "vs_common.h"
@@ -42,14 +43,15 @@ struct EstArgs {
 
 // A wave holds the K rows of 64 keys in registers, as MFMA operands straight from memory, and takes the query heads of the KV
 // group one after the other; the window rows of all of them wait in LDS.  Nothing is staged and there is no barrier on the way.
-// Bound: of sweep B the issue cycles (80 % vector instructions, matrix products included, 32 % MFMA busy at 1M keys, 28 query / 4
-// KV heads of 128); of sweep A these (50 % and 33 %) and its reads: the state of four heads fills the LDS, so K goes by twice
-// (2.24 GB for a cache of 1.07, 4.0 TB/s) and waves wait 43 % of their cycles.  The next block's product interleaved with this
-// one's exponentials by hand, two or three waves per SIMD and more registers, was 5 to 20 % slower.  Per 64 scores there are 16
-// cycles of MFMA, in sweep A fma, exp, add and half a max, in sweep B half a lane swap, fma, exp and five more (column sum,
-// diagonals).  1M keys: sweep A 533 to 590 us by card, sweep B 687 to 740, 1.24 to 1.38 ms with everything; with the K tiles in LDS,
-// a barrier per tile, 32 rows per wave, the diagonals turned by LDS lane exchanges and a pass that cleared the scores 640 +
-// 950, 1.63.  Small calls are cut finer: 8,192 keys 77 us -> 33.
+// Bound: issue cycles and, at long contexts, power: both sweeps run at 1.7 to 1.9 GHz.  Per 64 scores there are 16 cycles of MFMA and,
+// as measured one by one (cycles of a SIMD, from any number of waves): exp 8.3, a lane swap or a half of it 4.2, an add with a lane
+// shift 4.3, fma and add 2 each, MFMA issue 4.  Sweep A has exp, fma and add (vector instructions 69 % of the clocked cycles,
+// MFMA 51 %, they overlap), sweep B half a lane swap and one shifted add more (62 % and 34 %).  1M keys, 28 query / 4 KV heads of
+// 128: sweep A 624 -> 521 us (a running maximum took half an instruction per score, and its state two shares of heads: K went by
+// twice, 2.24 GB), sweep B 808 -> 680 (three vector instructions fewer per row, see there), 1.27 -> 1.09 ms with everything.  Without
+// the stores of sweep B, its lse loads, new K rows per tile or the lane shifts, one at a time, it would be 2 to 9 % faster.
+// The next block's product interleaved with this one's exponentials by hand, two or three waves per SIMD and more
+// registers, were 5 to 20 % slower.
 constexpr int kEstWaves = 16;    // waves per workgroup at most, and per compute unit: four per SIMD, 128 registers
 constexpr int est_waves(bool dca) { return dca ? 12 : kEstWaves; }   // (a block of several rotations needs the registers)
 constexpr int kEstLds = 160 << 10;
@@ -174,22 +176,31 @@ __device__ __forceinline__ void est_product(const __bf16* qs, int x, int lane, M
   }
 }
 
-// Sweep A: (max, sum) of every window row over the workgroup's keys.  K Q^T: a lane owns a query row (32 x + lane % 32 of row
-// block x) and half of the keys; its state lies in LDS between the tiles.
+// Sweep A: (reference, sum) of every window row over the workgroup's keys.  K Q^T: a lane owns a query row (32 half + lane % 32
+// of the head) and half of the keys.  A row's reference is the largest score of the wave's first tile, cut to the upper half of its
+// bits, and stays until a tile's sum of 32 probabilities goes past 2^8 (first tiles and such tiles take the exact way: the largest
+// score first).  So there is no maximum in the steady step, and the state of a head is 64 sums and 64 half-words, small enough
+// for seven heads beside their rows in LDS: K goes by once.
 template <int D, bool DCA>
 __global__ __launch_bounds__(64 * est_waves(DCA)) void k_est_sums(const EstArgs a, const EstShape z, const int tiles_b) {
   constexpr int DSTEPS = D / 16;
   extern __shared__ __attribute__((aligned(16))) unsigned char est_lds[];
   __bf16* const qs = (__bf16*)est_lds;
-  float2* const state = (float2*)(qs + (DCA ? 3 : 1) * z.heads * 64 * D);   // [wave][row block][64]
+  float* const sums = (float*)(qs + (DCA ? 3 : 1) * z.heads * 64 * D);         // [wave][head][64]
+  uint16_t* const refs = (uint16_t*)(sums + z.waves * z.heads * 64);           // the same, upper halves of floats
   const EstPlace p = est_place(a, z);
   if (!p.ok) return;
   const int tid = threadIdx.x, lane = tid & 63, hh = lane >> 5;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n_tiles = (int)((a.n_k + 63) >> 6);
   const int one_q = est_load_all_q<D, DCA>(a, z, p, n_tiles, qs);
-  float2* const mine = state + wv * 2 * z.heads * 64 + lane;
-  for (int x = 0; x < 2 * p.n_h; ++x) mine[64 * x] = make_float2(-INFINITY, 0.f);
+  float* const my_sum = sums + wv * z.heads * 64;
+  uint16_t* const my_ref = refs + wv * z.heads * 64;
+  auto ref_of = [](uint32_t w) { return __uint_as_float(w << 16); };
+  for (int x = 0; x < p.n_h; ++x) {
+    my_sum[64 * x + lane] = 0.f;
+    my_ref[64 * x + lane] = 0xFF80u;   // -inf
+  }
   __syncthreads();
   const int t0 = (p.blk * z.waves + wv) * z.tiles, t1 = t0 + z.tiles < n_tiles ? t0 + z.tiles : n_tiles;
   for (int t = t0; t < t1; ++t) {
@@ -207,76 +218,101 @@ __global__ __launch_bounds__(64 * est_waves(DCA)) void k_est_sums(const EstArgs 
     if (t % tiles_b == 0) clear(t);
     if (t == n_tiles - 1) clear(n_tiles);
     const bool causal = j0 + 63 > a.p0;   // some (row, key) of this tile is acausal
-    for (int x = 0; x < 2 * p.n_h; ++x) {
-      f32x16 s[2];
-      auto product = [&](int rot, f32x16 (&d)[2]) {
+    for (int x = 0; x < p.n_h; ++x) {
+      float part[2] = {0.f, 0.f};
+#pragma clang loop unroll(disable)
+      for (int half = 0; half < 2; ++half) {
+        part[0] = part[1];
+        f32x16 s[2];
+        auto product = [&](int rot, f32x16 (&d)[2]) {
 #pragma unroll
-        for (int jb = 0; jb < 2; ++jb)
+          for (int jb = 0; jb < 2; ++jb)
 #pragma unroll
-          for (int e = 0; e < 16; ++e) d[jb][e] = 0.f;
-        est_product<D>(qs + rot * one_q, x, lane, [&](int k, bf16x8 qf) {
-          d[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[0][k], qf, d[0], 0, 0, 0);
-          d[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[1][k], qf, d[1], 0, 0, 0);
-        });
-      };
-      const float2 st = mine[64 * x];
-      if constexpr (DCA) {
-        uint32_t need = __builtin_amdgcn_readfirstlane(dca.need(32 * (x & 1)));
-        product(__builtin_ctz(need), s);
-        for (need &= need - 1; need; need &= need - 1) {
-          const int rot = __builtin_ctz(need);
+            for (int e = 0; e < 16; ++e) d[jb][e] = 0.f;
+          est_product<D>(qs + rot * one_q, 2 * x + half, lane, [&](int k, bf16x8 qf) {
+            d[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[0][k], qf, d[0], 0, 0, 0);
+            d[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[1][k], qf, d[1], 0, 0, 0);
+          });
+        };
+        uint16_t* const ref = my_ref + 64 * x + 32 * half + (lane & 31);
+        const float m = ref_of(*ref);
+        if constexpr (DCA) {
+          const int row = 32 * half + (lane & 31), near = dca.of(row, 63), far = dca.of(row, 0);
+          product(near, s);
+          if (__builtin_amdgcn_ballot_w64(near != far)) {
+            // keys behind the window: those up to `past` (counted from the lane's first)
+            int past = (near != far ? row + dca.dist0 - dca.window : -64) - 4 * hh;
+            asm volatile("" : "+v"(past));
 #pragma unroll
-          for (int jb = 0; jb < 2; ++jb) {
-            f32x16 d;
+            for (int jb = 0; jb < 2; ++jb) {
+              f32x16 d;
 #pragma unroll
-            for (int e = 0; e < 16; ++e) d[e] = 0.f;
-            est_product<D>(qs + rot * one_q, x, lane, [&](int k, bf16x8 qf) {
-              d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[jb][k], qf, d, 0, 0, 0);
-            });
+              for (int e = 0; e < 16; ++e) d[e] = 0.f;
+              est_product<D>(qs + far * one_q, 2 * x + half, lane, [&](int k, bf16x8 qf) {
+                d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[jb][k], qf, d, 0, 0, 0);
+              });
+#pragma unroll
+              for (int e = 0; e < 16; ++e)
+                if (32 * jb + 8 * (e >> 2) + (e & 3) <= past) s[jb][e] = d[e];
+            }
+          }
+        } else {
+          product(0, s);
+        }
+        if (causal) {
+          // element e of jb is key 32 jb + 8 (e/4) + 4 hh + (e%4); it is masked for row r iff j - p0 > r
+          int dr = 32 * half + (lane & 31) - (int)(j0 - a.p0) - 4 * hh;
+          asm volatile("" : "+v"(dr));   // (32 comparisons here, not 32 masks held through the loop)
+#pragma unroll
+          for (int jb = 0; jb < 2; ++jb)
 #pragma unroll
             for (int e = 0; e < 16; ++e)
-              if (dca.of(32 * (x & 1) + (lane & 31), 32 * jb + 8 * (e >> 2) + 4 * hh + (e & 3)) == rot) s[jb][e] = d[e];
-          }
+              if (32 * jb + 8 * (e >> 2) + (e & 3) > dr) s[jb][e] = -INFINITY;
         }
-      } else {
-        product(0, s);
+        auto sum = [&](float m_use) -> float {
+          float acc0 = 0.f, acc1 = 0.f;
+#pragma unroll
+          for (int e = 0; e < 16; ++e) {
+            acc0 += __builtin_amdgcn_exp2f(__builtin_fmaf(s[0][e], a.scale_log2, -m_use));
+            acc1 += __builtin_amdgcn_exp2f(__builtin_fmaf(s[1][e], a.scale_log2, -m_use));
+          }
+          return acc0 + acc1;
+        };
+        bool exact = t == t0;
+        if (!exact) {
+          part[1] = sum(m);
+          exact = __builtin_amdgcn_ballot_w64(!(part[1] <= 256.f)) != 0;   // (a reference of -inf makes inf or NaN)
+        }
+        if (exact) {
+          float mx = fmaxf(s[0][0], s[1][0]);
+#pragma unroll
+          for (int e = 1; e < 16; ++e) mx = fmaxf(fmaxf(mx, s[0][e]), s[1][e]);
+          mx = fmaxf(mx, __shfl_xor(mx, 32));
+          // (-inf stays -inf; rows without a key so far take 0 in its place)
+          const uint32_t w = __float_as_uint(fmaxf(m, mx * a.scale_log2)) >> 16;
+          const float m_new = ref_of(w), m_use = m_new == -INFINITY ? 0.f : m_new;
+          if (lane < 32) {
+            float* const l = my_sum + 64 * x + 32 * half + lane;
+            *l *= __builtin_amdgcn_exp2f(m - m_use);
+            *ref = (uint16_t)w;
+          }
+          part[1] = sum(m_use);
+        }
       }
-      if (causal) {
-        // element e of jb is key 32 jb + 8 (e/4) + 4 hh + (e%4); it is masked for row r iff j - p0 > r
-        const int dr = 32 * (x & 1) + (lane & 31) - (int)(j0 - a.p0) - 4 * hh;
-#pragma unroll
-        for (int jb = 0; jb < 2; ++jb)
-#pragma unroll
-          for (int e = 0; e < 16; ++e)
-            if (32 * jb + 8 * (e >> 2) + (e & 3) > dr) s[jb][e] = -INFINITY;
-      }
-      float mx = fmaxf(s[0][0], s[1][0]);
-#pragma unroll
-      for (int e = 1; e < 16; ++e) mx = fmaxf(fmaxf(mx, s[0][e]), s[1][e]);
-      const float m_new = fmaxf(st.x, mx * a.scale_log2);
-      const float m_use = (m_new == -INFINITY) ? 0.f : m_new;
-      float acc0 = st.y * __builtin_amdgcn_exp2f(st.x - m_use), acc1 = 0.f;
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        acc0 += __builtin_amdgcn_exp2f(__builtin_fmaf(s[0][e], a.scale_log2, -m_use));
-        acc1 += __builtin_amdgcn_exp2f(__builtin_fmaf(s[1][e], a.scale_log2, -m_use));
-      }
-      mine[64 * x] = make_float2(m_new, acc0 + acc1);
+      // the key halves of a row added: lanes 0..31 get the rows of the first half, lanes 32..63 those of the second
+      const auto w = __builtin_amdgcn_permlane32_swap(__float_as_uint(part[0]), __float_as_uint(part[1]), false, false);
+      const uint32_t w0 = w[0], w1 = w[1];
+      my_sum[64 * x + lane] += __uint_as_float(w0) + __uint_as_float(w1);
     }
   }
   __syncthreads();
-  // the waves and key halves of a row folded in a fixed order: one partial per (head, workgroup, row)
+  // the waves folded in a fixed order: one partial per (head, workgroup, row)
   for (int x = tid; x < 64 * p.n_h; x += blockDim.x) {
-    const int rb = x >> 5, r = x & 31;
-    const float2* const col = state + rb * 64 + r;
     float M = -INFINITY, L = 0.f;
-    for (int w = 0; w < z.waves; ++w) M = fmaxf(M, fmaxf(col[w * 2 * z.heads * 64].x, col[w * 2 * z.heads * 64 + 32].x));
+    for (int w = 0; w < z.waves; ++w) M = fmaxf(M, ref_of(refs[w * z.heads * 64 + x]));
     const float Mu = (M == -INFINITY) ? 0.f : M;
-    for (int w = 0; w < z.waves; ++w) {
-      const float2 u = col[w * 2 * z.heads * 64], v = col[w * 2 * z.heads * 64 + 32];
-      L += u.y * __builtin_amdgcn_exp2f(u.x - Mu) + v.y * __builtin_amdgcn_exp2f(v.x - Mu);
-    }
-    float* const pp = a.part + (((int64_t)(p.h0 + (rb >> 1)) * a.n_ranges + p.blk) * 64 + (x & 63)) * 2;
+    for (int w = 0; w < z.waves; ++w) L += sums[w * z.heads * 64 + x] * __builtin_amdgcn_exp2f(ref_of(refs[w * z.heads * 64 + x]) - Mu);
+    float* const pp = a.part + (((int64_t)(p.h0 + (x >> 6)) * a.n_ranges + p.blk) * 64 + (x & 63)) * 2;
     pp[0] = M;
     pp[1] = L;
   }
@@ -285,12 +321,19 @@ __global__ __launch_bounds__(64 * est_waves(DCA)) void k_est_sums(const EstArgs 
 // Sweep B: P = exp2(S scale_log2 - lse2), summed along columns and diagonals.  Q K^T, and the two blocks of 32 keys swapped
 // by half-waves: a register then is one window row, its 64 lanes the tile's 64 keys.  A column sum is a plain sum over the
 // registers.  A diagonal moves on by one lane from row to row, so its sum is an add with a lane rotation per row:
-//   acc <- rotate(acc, 1) + P[q],   q = 0 .. 63
-// after which lane f holds the offset p0 + 63 - (j0 + f), all in one register.  What lies right of the tile's own diagonal
-// (lanes > q) wraps around and belongs to the next tile's offsets; it is summed by itself and waits in LDS for the next tile
-// of the wave.  (One sum over everything and a subtraction would be a select less, but off by a rounding of the larger part.)
+//   acc <- shift(acc, 1) + P[q],   q = 0 .. 63
+// after which lane f holds the offset p0 + 63 - (j0 + f), all in one register.  What leaves lane 63 on the way is complete as far as
+// this tile goes and belongs to the next tile's offsets: lane 63 stores it, row by row, into LDS, where it waits for the next
+// tile of the wave.  (A lane rotation with two sums, of the lanes up to q and of those past it, took three more vector
+// instructions per row; the stores are the LDS's work.)
 // Offsets at the seam of two waves get their two parts by atomic adds (cleared by sweep A; x + y is commutative, so scores are
 // run-to-run identical).
+typedef __attribute__((address_space(3))) float lds_float;
+// lane 63's four floats to LDS byte address `at` + 16 * slot (all lanes are active before and after)
+__device__ __forceinline__ void est_store_last(uint32_t at, f32x4 v, const int slot) {
+  asm volatile("s_mov_b64 exec, %2\n\tds_write_b128 %0, %1 offset:%3\n\ts_mov_b64 exec, -1"
+               :: "v"(at), "v"(v), "s"(1ull << 63), "n"(16 * slot));
+}
 template <int D, bool DCA>
 __global__ __launch_bounds__(64 * est_waves(DCA)) void k_est_scores(const EstArgs a, const EstShape z) {
   constexpr int DSTEPS = D / 16;
@@ -300,15 +343,15 @@ __global__ __launch_bounds__(64 * est_waves(DCA)) void k_est_scores(const EstArg
   if (!p.ok) return;
   const int tid = threadIdx.x, lane = tid & 63, hh = lane >> 5;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  float* const carry = (float*)(qs + (DCA ? 3 : 1) * z.heads * 64 * D) + wv * z.heads * 64 + lane;   // [wave][head][64]
+  float* const carry = (float*)(qs + (DCA ? 3 : 1) * z.heads * 64 * D) + wv * z.heads * 64;   // [wave][head][64]
   const int n_tiles = (int)((a.n_k + 63) >> 6);
   const int one_q = est_load_all_q<D, DCA>(a, z, p, n_tiles, qs);
   __syncthreads();
   const int t0 = (p.blk * z.waves + wv) * z.tiles, t1 = t0 + z.tiles < n_tiles ? t0 + z.tiles : n_tiles;
   float c = a.scale_log2;
   asm("" : "+v"(c));   // (one scalar operand per instruction, and that is the row's lse2)
-  auto rotate = [](float v) -> float {   // lane f takes lane f - 1's value
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x13C, 0xF, 0xF, false));
+  auto shift = [](float v) -> float {   // lane f takes lane f - 1's value, lane 0 a zero
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x138, 0xF, 0xF, true));
   };
   for (int t = t0; t < t1; ++t) {
     const int64_t j0 = 64 * (int64_t)t;
@@ -320,14 +363,21 @@ __global__ __launch_bounds__(64 * est_waves(DCA)) void k_est_scores(const EstArg
     const bool causal = j0 + 63 > a.p0;
     for (int x = 0; x < p.n_h; ++x) {
       const int h = __builtin_amdgcn_readfirstlane(p.h0 + x);
-      float col[2] = {0.f, 0.f}, own = 0.f, over = 0.f;
-      uint64_t right = ~1ull;   // lanes > q; opaque, or the compiler keeps 64 of them in scalar registers
-      asm("" : "+s"(right));
-      // (the scalar cache: the rows are the same in every lane)
-      typedef const __attribute__((address_space(4))) float* const_ptr;
-      const const_ptr lse = (const_ptr)(a.lse2 + (int64_t)h * 64);
+      float col[2] = {0.f, 0.f}, diag = 0.f;
+      // (volatile: the stores of lane 63 below are not the compiler's)
+      const float before = t == t0 ? 0.f : *(volatile float*)(carry + 64 * x + lane);
 #pragma clang loop unroll(disable)
       for (int half = 0; half < 2; ++half) {
+        // lse2 of the rows (the scalar cache: they are the same in every lane), on their way during the product; with Dual Chunk
+        // Attention the scalar registers are full and they are read behind it
+        f32x16 lse_lo, lse_hi;
+        auto load_lse = [&]() {
+          typedef const __attribute__((address_space(4))) f32x16* const_ptr;
+          const const_ptr lse = (const_ptr)(a.lse2 + (int64_t)h * 64 + 32 * half);
+          lse_lo = lse[0];
+          lse_hi = lse[1];
+        };
+        if constexpr (!DCA) load_lse();
         f32x16 s[2];
         auto product = [&](int rot, f32x16 (&d)[2]) {
 #pragma unroll
@@ -340,21 +390,26 @@ __global__ __launch_bounds__(64 * est_waves(DCA)) void k_est_scores(const EstArg
           });
         };
         if constexpr (DCA) {
-          uint32_t need = __builtin_amdgcn_readfirstlane(dca.need(32 * half));
-          product(__builtin_ctz(need), s);
-          for (need &= need - 1; need; need &= need - 1) {
-            const int rot = __builtin_ctz(need);
+          const int row = 32 * half + (lane & 31), near = dca.of(row, 63), far = dca.of(row, 0);
+          product(near, s);
+          if (__builtin_amdgcn_ballot_w64(near != far)) {
+            // rows for which a key lies behind the window: from `first` on (counted from the lane's first row; of the second 32 keys
+            // 32 later) and below `end`.  (Rows that meet the whole tile behind it are `far` in both products.)
+            const int rb = dca.row_bound, lo = dca.ck_rel == 0 ? rb : 0, own = 32 * half + 4 * hh;
+            int first = (lane & 31) + dca.window - dca.dist0 - own, end = (dca.ck_rel == 0 ? 64 : rb) - own;
+            asm volatile("" : "+v"(first), "+v"(end));
 #pragma unroll
             for (int jb = 0; jb < 2; ++jb) {
+              const int from = first + 32 * jb > lo - own ? first + 32 * jb : lo - own;
               f32x16 d;
 #pragma unroll
               for (int e = 0; e < 16; ++e) d[e] = 0.f;
-              est_product<D>(qs + rot * one_q, 2 * x + half, lane, [&](int k, bf16x8 qf) {
+              est_product<D>(qs + far * one_q, 2 * x + half, lane, [&](int k, bf16x8 qf) {
                 d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf, kf[jb][k], d, 0, 0, 0);
               });
 #pragma unroll
               for (int e = 0; e < 16; ++e)
-                if (dca.of(32 * half + 8 * (e >> 2) + 4 * hh + (e & 3), 32 * jb + (lane & 31)) == rot) s[jb][e] = d[e];
+                if (8 * (e >> 2) + (e & 3) >= from && 8 * (e >> 2) + (e & 3) < end) s[jb][e] = d[e];
             }
           }
         } else {
@@ -369,6 +424,8 @@ __global__ __launch_bounds__(64 * est_waves(DCA)) void k_est_scores(const EstArg
             for (int e = 0; e < 16; ++e)
               if (dj + 32 * jb > 8 * (e >> 2) + (e & 3)) s[jb][e] = -INFINITY;
         }
+        if constexpr (DCA) load_lse();
+        const uint32_t carry_at = (uint32_t)(uintptr_t)(lds_float*)(carry + 64 * x + 32 * (1 - half));
 #pragma unroll
         for (int e4 = 0; e4 < 4; ++e4) {
           // rows 8 e4 + 0..3 of the half in s[0], rows 8 e4 + 4..7 in s[1] after the swap
@@ -381,35 +438,34 @@ __global__ __launch_bounds__(64 * est_waves(DCA)) void k_est_scores(const EstArg
             s[1][e] = __uint_as_float(w1);
           }
 #pragma unroll
-          for (int k = 0; k < 2; ++k)
+          for (int k = 0; k < 2; ++k) {
+            f32x4 out;   // lane 63 before rows q .. q + 3: offsets p0 + q - 1 - (j0 + 63) and on, the next tile's lanes 63 - q and down
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-              const int q = 32 * half + 8 * e4 + 4 * k + e;
-              const float pr = __builtin_amdgcn_exp2f(__builtin_fmaf(s[k][4 * e4 + e], c, -lse[q]));
-              const bool next = __builtin_amdgcn_inverse_ballot_w64(right);
+              const int q = 8 * e4 + 4 * k + e;
+              const float pr = __builtin_amdgcn_exp2f(__builtin_fmaf(s[k][4 * e4 + e], c, -(q < 16 ? lse_lo : lse_hi)[q & 15]));
               col[q & 1] += pr;
-              own = rotate(own) + (next ? 0.f : pr);
-              over = rotate(over) + (next ? pr : 0.f);
-              right <<= 1;
+              out[3 - e] = diag;
+              diag = shift(diag) + pr;
             }
+            est_store_last(carry_at, out, 7 - 2 * e4 - k);
+          }
         }
       }
       float* const so = a.sscore + (int64_t)h * a.n_k + o;
       const bool in = o >= 0 && o < a.n_k;
       if (t == t0) {
-        if (in) atomicAdd(so, own);
+        if (in) atomicAdd(so, diag);
       } else {
-        own += carry[64 * x];
-        if (in) *so = own;
+        if (in) *so = diag + before;
       }
-      carry[64 * x] = over;
       if (j0 + lane < a.n_k) a.vscore[(int64_t)h * a.n_k + j0 + lane] = col[0] + col[1];
     }
   }
   if (t0 < t1) {
     const int64_t o = a.p0 + 63 - 64 * (int64_t)t1 - lane;
     if (o >= 0 && o < a.n_k)
-      for (int x = 0; x < p.n_h; ++x) atomicAdd(&a.sscore[(int64_t)(p.h0 + x) * a.n_k + o], carry[64 * x]);
+      for (int x = 0; x < p.n_h; ++x) atomicAdd(&a.sscore[(int64_t)(p.h0 + x) * a.n_k + o], *(volatile float*)(carry + 64 * x + lane));
   }
 }
 
@@ -441,34 +497,37 @@ __global__ __launch_bounds__(1024) void k_estimate_combine(const EstArgs a) {
 }
 
 // The cut of a sweep, by the time it should take, in units of one row block of a wave with 16 waves on the compute unit
-// (about 2.8 us): a tile costs 2 per head and something for its K rows, a row block is faster with fewer waves around; a
+// (about 2.5 us): a tile costs 2 per head and something for its K rows, a row block is faster with fewer waves around; a
 // workgroup costs its start and the window rows that it puts into LDS, a wave per head what it adds to its neighbours' offsets
 // (atomic additions), and every share of the heads its K rows once more.  With Dual Chunk Attention the start (up to three
-// rotations, patterns) weighs more.  The weights are fitted to all cuts of 193 calls (1 to 64 heads, 2,558 to 300,001 keys): the
-// chosen cuts are within 2.6 % of the best ones on average, 0.9 % with Dual Chunk Attention (with fewer terms 4.2 and 1.7, and
-// worst cases of 54 and 29 %).  Small calls are made of few rounds of workgroups, so the waves per workgroup are whatever fills
-// them.  28 / 4 heads, against at most 16 waves and always many heads per workgroup: 38,209 keys 111 -> 85 us, 84,333 178 -> 146,
-// 300,001 501 -> 420; 1M the same; DCA, 26,543 keys 173 -> 100.  head_bytes: LDS per head and wave, beside the rows.
-// Shares are those that leave fewest heads for the last one (of 32 heads 4 each, not 7, 7, 7, 7 and 4: 131,072 keys 258 -> 195 us).
+// rotations, patterns) weighs more.  Workgroups of one key range stay on one XCD (est_place), so rounds are those of the XCD that gets
+// most (20 heads on one KV head, 45,000 keys: 25 ranges of 10 shares had 40 workgroups on an XCD of 32 compute units, 105 us; 61 now).
+// The weights are fitted to all cuts of 189 calls (1 to 64 heads, 2,558 to 300,001 keys): the chosen cuts are within 0.9 % of the
+// best ones on average, 0.8 % with Dual Chunk Attention, the worst 10 and 12 % off.  Small calls are made of few rounds of workgroups,
+// so the waves per workgroup are whatever fills them.  head_bytes: LDS per head and wave, beside the rows.
+// Shares are those that leave fewest heads for the last one (of 32 heads 4 each, not 7, 7, 7, 7 and 4); with Dual Chunk Attention three
+// heads only where that leaves no more places empty than two (five heads 131,072 keys 346 us with two, 300 with three; of seven the
+// third share would have one).
 static EstShape est_shape(const vs_params& p, int most, int head_bytes, bool dca) {
   const int group = p.n_q_heads / p.n_kv_heads, n_cu = 256;
   const int64_t n_tiles = ceil_div(p.q_start + p.q_len, 64), units = n_tiles * p.n_kv_heads;
-  const double k_rows = dca ? 2.0 : 0.5, start = dca ? 4.0 : 1.5, fill = dca ? 0.2 : 0.3, seam = dca ? 1.5 : 2.0, again = dca ? 0.5e-3 : 2e-3;
+  const double busy = dca ? 0.2 : 0.1, k_rows = dca ? 1.5 : 4.0, start = dca ? 4.0 : 1.5, fill = 0.2, seam = dca ? 1.5 : 2.0, again = 0.5e-3;
   EstShape best = {};
   double best_cost = -1.0;
   static constexpr int kWaves[] = {16, 14, 12, 10, 9, 8, 7, 6, 5, 4};
   for (int heads = most < group ? most : group; heads >= 1; --heads) {
     const int n_hb = (group + heads - 1) / heads;
     if (heads > 1 && (group + heads - 2) / (heads - 1) == n_hb) continue;
+    if (dca && heads == 3 && n_hb * 3 > (group + 1) / 2 * 2) continue;
     for (const int waves : kWaves) {
       const int lds = heads * ((dca ? 3 : 1) * 64 * p.head_dim * 2 + waves * head_bytes);
       if (lds > kEstLds - 64 || waves > est_waves(dca)) continue;
       const int by_lds = kEstLds / lds, by_waves = est_waves(dca) / waves, per_cu = by_lds < by_waves ? by_lds : by_waves;
       for (int want = 1; want <= 3; ++want) {   // rounds
         const int64_t tiles = ceil_div(units * n_hb, (int64_t)waves * per_cu * n_cu * want);
-        const int64_t blocks = ceil_div(n_tiles, tiles * waves), wgs = blocks * p.n_kv_heads * n_hb;
+        const int64_t blocks = ceil_div(n_tiles, tiles * waves), wgs = 8 * ceil_div(blocks * p.n_kv_heads, 8) * n_hb;
         const int64_t rounds = ceil_div(wgs, n_cu * per_cu), resident = rounds > 1 ? per_cu : ceil_div(wgs, n_cu);
-        const double rate = 0.2 + 0.8 * (double)(resident * waves) / kEstWaves;
+        const double rate = busy + (1.0 - busy) * (double)(resident * waves) / kEstWaves;
         const double cost = (double)rounds * ((double)tiles * (2.0 * heads + k_rows) * rate + start + fill * heads * kEstWaves / waves +
                                               seam * heads) + again * (double)(n_hb * units);
         if (best_cost < 0 || cost < best_cost) {
@@ -482,8 +541,8 @@ static EstShape est_shape(const vs_params& p, int most, int head_bytes, bool dca
   }
   return best;
 }
-static EstShape est_shape_a(const vs_params& p, bool dca) { return est_shape(p, dca ? 2 : 4, 2 * 64 * sizeof(float2), dca); }
-static EstShape est_shape_b(const vs_params& p, bool dca) { return est_shape(p, dca ? 2 : 7, 64 * sizeof(float), dca); }
+static EstShape est_shape_a(const vs_params& p, bool dca) { return est_shape(p, dca ? 3 : 7, 64 * (sizeof(float) + sizeof(uint16_t)), dca); }
+static EstShape est_shape_b(const vs_params& p, bool dca) { return est_shape(p, dca ? 3 : 7, 64 * sizeof(float), dca); }
 
 size_t estimate_ws_bytes(const vs_params& p) {
   const int64_t n = est_shape_a(p, false).n_blocks, n_dca = est_shape_a(p, true).n_blocks;   // (the size serves either call)
@@ -505,7 +564,7 @@ static hipError_t launch_est(const vs_params& p, EstArgs a, void* ws, hipStream_
   a.lse2 = (float*)((char*)ws + align_up((size_t)p.n_q_heads * a.n_ranges * 64 * 2 * sizeof(float), 256));
   auto grid = [&](const EstShape& z) { return dim3((unsigned)(ceil_div((int64_t)z.n_blocks * a.n_kv_heads, 8) * 8 * z.n_hb)); };
   const size_t q_bytes = (DCA ? 3 : 1) * 64 * D * sizeof(__bf16);
-  hipLaunchKernelGGL((k_est_sums<D, DCA>), grid(za), dim3(64 * za.waves), za.heads * (q_bytes + (size_t)za.waves * 2 * 64 * sizeof(float2)), st, a, za, zb.tiles);
+  hipLaunchKernelGGL((k_est_sums<D, DCA>), grid(za), dim3(64 * za.waves), za.heads * (q_bytes + (size_t)za.waves * 64 * (sizeof(float) + sizeof(uint16_t))), st, a, za, zb.tiles);
   hipLaunchKernelGGL(k_estimate_combine, dim3(a.n_q_heads), dim3(1024), 0, st, a);
   hipLaunchKernelGGL((k_est_scores<D, DCA>), grid(zb), dim3(64 * zb.waves), zb.heads * (q_bytes + (size_t)zb.waves * 64 * sizeof(float)), st, a, zb);
   return hipGetLastError();

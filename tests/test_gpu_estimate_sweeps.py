@@ -8,15 +8,18 @@ import torch
 
 import oracle
 import paper_2501_15383_amd as vs
-from gpu_util import chunk_of, dev, f64
+from gpu_util import chunk_of, dev, f64, host_u16
 from helpers import rand_bf16
 
 pytestmark = pytest.mark.gpu
 
 
-def _check(hq, hkv, d, c, s, seed, dca=None):
+def _check(hq, hkv, d, c, s, seed, dca=None, ramp=None, norm=1e-5):
     rng = np.random.default_rng(seed)
     q = rand_bf16(rng, (c, hq, d)); k = rand_bf16(rng, (s + c, hkv, d))
+    if ramp is not None:   # keys whose length goes from ramp[0] to ramp[1] along the cache
+        kf = (k.astype(np.uint32) << 16).view(np.float32) * np.linspace(*ramp, s + c, dtype=np.float32)[:, None, None]
+        k = host_u16(torch.from_numpy(kf).bfloat16())
     succ, inter = (rand_bf16(rng, (c, hq, d)) for _ in range(2))   # unlike q: a wrong choice of rotation shows
     pb = oracle.Problem(hq, hkv, d, c, s, 1.0 / np.sqrt(d))
     rvs, rss, rlse = oracle.estimate(pb, q, k, dca=None if dca is None else oracle.Dca(dca[0], dca[1], succ, inter))
@@ -30,7 +33,7 @@ def _check(hq, hkv, d, c, s, seed, dca=None):
     for got, ref in ((vsc, rvs), (ssc, rss)):
         got = f64(got)
         np.testing.assert_allclose(got, ref, rtol=2e-4, atol=1e-7)
-        assert np.linalg.norm(got - ref) <= 1e-5 * np.linalg.norm(ref)
+        assert np.linalg.norm(got - ref) <= norm * np.linalg.norm(ref)
     np.testing.assert_allclose(f64(lse).reshape(rlse.shape), rlse, rtol=2e-5, atol=2e-5)
 
 
@@ -61,3 +64,13 @@ def test_rotations(hq, hkv, d, c, s, dca):
 
 def test_rotations_over_several_tiles_per_wave():
     _check(8, 8, 64, 64, 120000, 4300, (32768, 2048))
+
+
+@pytest.mark.parametrize("hq,hkv,d,c,s,dca", [(8, 8, 64, 64, 120000, None), (14, 2, 128, 40, 30000, None), (8, 8, 64, 64, 120000, (32768, 2048))])
+@pytest.mark.parametrize("ramp", [(0.05, 12.0), (12.0, 0.05)])
+def test_scores_that_outrun_the_reference_of_a_wave(hq, hkv, d, c, s, dca, ramp):
+    # Base-2 scores up to about 4.5 * 12 * log2(e) = 78 along a wave's tiles: references taken from a first tile are passed by far
+    # more than 2^8 and taken again (rising), or leave nothing of the later tiles (falling).  Arguments below 128 are off by up to 2^-18
+    # per rounding, of which there are three (the score, its product with the scale, the lse): 3 * 2^-18 * ln 2 = 8e-6 for a
+    # single probability that all weight lies on, and as much again for the sum that the lse comes from.
+    _check(hq, hkv, d, c, s, 4400, dca, ramp, norm=2e-5)
