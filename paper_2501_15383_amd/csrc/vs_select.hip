@@ -10,12 +10,13 @@
 //     lowest-index keys == T (ties go to the lower index).  Ranks come from wave ballots.
 // One workgroup finishes a row (k_sel_row), from one of three sources:
 //   registers   rows of up to kSelRegKeys scores are read once and stay in registers; a call is then
-//               this one launch, bound by the latency of its dozen barriers
+//               this one launch, bound by its vector instructions (of 32 scores per lane: loads and range 3.0 us, first
+//               digit 3, the pass that lists the threshold's bin 1.5, emission 2.5) and, of short rows, by its barriers
 //   candidates  longer rows are thinned out first.  A sample of 8,192 (16,384) scores per row gives a floor that
 //               about k + 4.5 sigma entries exceed, and only those entries are kept, in LDS if there are at most
 //               kSelCand of them.  With a workspace the whole chip makes the lists, in one pass over the scores
-//               (k_sel_sample, k_sel_filter; bound by that read at 1M keys); for rows of up to kSelOwnKeys, and
-//               without a workspace, k_sel_row makes its row's own.  A threshold that falls on a crowd of equal
+//               (k_sel_sample, k_sel_filter; bound by that read at 1M keys); without a workspace k_sel_row makes its
+//               row's own.  A threshold that falls on a crowd of equal
 //               scores is the floor itself: all candidates are wanted, and of the crowd its first entries, for which the row
 //               is read until it has them (28 heads, 1M keys of which 2,097 are not zero, 6,096 wanted: 485 us with the row
 //               read to its end, 125 so).
@@ -25,7 +26,7 @@
 // scores once per digit of 8 bits, once for the counts and once for the compaction (k_slice_*): the list would be one
 // workgroup's work.
 // Measured on one MI355X, 28 heads, budgets 1000 / 6096, against four digits, a count and a write pass over all
-// scores in seven launches: 8,192 scores per row 14 us (67), 32,768 21 us (70), 300,001 57 us (152), 1M 108 us
+// scores in seven launches: 8,192 scores per row 11 us (67), 32,768 19 us (70), 300,001 57 us (152), 1M 108 us
 // (345: filter 63 us = 3.7 TB/s, sample 16, rows 29); 4 heads, budgets 128 / 256, 1M: 50 us (98).
 #include "vs_common.h"
 
@@ -33,13 +34,12 @@ namespace vs {
 
 constexpr int kSelThreads = 1024;
 constexpr int kSelWaves = kSelThreads / 64;
-constexpr int kSelRegKeys = 32 * kSelThreads;  // longest row that stays in registers
+constexpr int kSelRegKeys = 48 * kSelThreads;  // longest row that stays in registers (128 of them; 44,000 scores, 28 heads: 25 us,
+                                               // 38 with the row's candidates in LDS; three launches 39 at 49,153)
 constexpr int kSelCand = 16384;                // longest list of candidates (128 KB of LDS)
 constexpr int kSelSlice = 2048;                // scores per wave of the filter (one slice each)
 constexpr int kSelFilterThreads = 256;
 constexpr int kSelStep = 8;                    // scores per lane and step where the row is read again and again
-constexpr int kSelOwnKeys = 48 * 1024;         // up to here a workgroup lists its own row's candidates: 31-35 us against
-                                               // 36-38 us for the three launches at 28 heads, 22-25 us either way at 4
 constexpr int kSelBins = 2048;
 // control block of a row whose slices go through the digits together, in 32-bit words
 constexpr int kSliceMax = 64;                  // slices of a row at most
@@ -122,12 +122,14 @@ __host__ __device__ inline float sel_sample_rank(float k, float n, float samples
 }
 
 struct SelShared {
-  uint32_t hist[kSelBins];
+  alignas(16) uint32_t hist[kSelBins];
   uint32_t wsum[kSelWaves];
   uint32_t digit, rest, in_bin;
   uint32_t wtot[2][kSelWaves][2];
   uint32_t wmin[kSelWaves], wmax[kSelWaves];
   int32_t first[kSelWaves + 1];
+  uint32_t few, few_T, few_need;   // keys of the last bin listed so far (in hist), and what they decide
+  uint32_t extra[kSelWaves];       // of a wave's keys in that bin, those taken
 };
 
 // smallest and largest of the threads' keys
@@ -150,65 +152,118 @@ __device__ __forceinline__ void sel_range(SelShared& sh, uint32_t lo, uint32_t h
 }
 
 // The kp-th largest of the keys that for_each(f) hands to f(key, valid) (valid keys lie in lo .. hi and number at least
-// kp >= 1): keys above T, and need_eq of those equal to it, are the kp largest.  Digits of 11 bits from the top of the range
+// kp >= 1): keys above T, and need_eq of those equal to it, are the kp largest; need_eq is 0 wherever every key equal to the
+// kp-th is wanted (T is the key below it then).  Digits of 11 bits from the top of the range
 // hi - lo, so that keys that share their exponent still spread over the bins (scores do: with digits of the
 // whole key a wave's 64 additions met in four bins, 65 to 250 clocks each); done as soon as a bin is taken whole.
 // Keys equal to lo are not counted, their bin has whatever the others leave of kp: a crowd of the smallest score (zeros) would
 // queue for it (32,768 scores, 2 in 1,000 of them not zero: 102 us counted, 25 so).
 // Called by the whole workgroup; every thread gets the result.
+constexpr uint32_t kSelAtLo = ~0u;
+struct SelDigits {
+  uint32_t prefix, krem, in_bin;   // digits so far (of key - lo), wanted keys of that bin, keys in it (kSelAtLo: krem keys equal to lo)
+  int shift;                       // bits below the prefix
+  bool first;
+};
+__device__ __forceinline__ SelDigits sel_digits(uint32_t kp, uint32_t lo, uint32_t hi) {
+  SelDigits d;
+  d.prefix = 0; d.krem = kp; d.in_bin = 0; d.first = true;
+  d.shift = 32 - __clz((int)(hi - lo) | 1);
+  return d;
+}
+template <typename ForEach>
+__device__ __forceinline__ void sel_digit(SelShared& sh, ForEach&& for_each, uint32_t lo, SelDigits& s) {
+  static_assert(kSelBins == 2 * kSelThreads, "two bins per thread");
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int width = s.shift < 11 ? s.shift : 11, sh0 = s.shift - width;
+  const uint32_t dmask = (1u << width) - 1u;
+  asm volatile("" : "+v"(lo));   // (key - lo is made again for every digit, not kept beside the keys)
+  sh.hist[tid] = 0;
+  sh.hist[kSelThreads + tid] = 0;
+  __syncthreads();
+  for_each([&](uint32_t key, bool valid) {
+    const uint32_t d = key - lo;
+    if (valid && d != 0u && (s.first || (d >> s.shift) == s.prefix)) atomicAdd(&sh.hist[(d >> sh0) & dmask], 1u);
+  });
+  __syncthreads();
+  // bins from the top: thread t takes the bins 2047 - 2 t and 2046 - 2 t
+  const uint32_t c0 = sh.hist[kSelBins - 1 - 2 * tid];
+  uint32_t c1 = sh.hist[kSelBins - 2 - 2 * tid];
+  const bool has_lo = tid == kSelThreads - 1 && s.prefix == 0;   // the bin of lo: what the others leave
+  const uint32_t but_lo = c1;
+  if (has_lo) c1 = 0x7FFFFFFFu;
+  uint32_t inc = c0 + c1;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint32_t y = __shfl_up(inc, d);
+    if (lane >= d) inc += y;
+  }
+  if (lane == 63) sh.wsum[wv] = inc;
+  __syncthreads();
+  uint32_t above = inc - c0 - c1;
+#pragma unroll
+  for (int x = 0; x < kSelWaves; ++x) above += x < wv ? sh.wsum[x] : 0u;
+  if (above < s.krem && s.krem <= above + c0 + c1) {
+    const bool second = above + c0 < s.krem;
+    sh.digit = (uint32_t)(kSelBins - 1 - 2 * tid - (second ? 1 : 0));
+    uint32_t rest = s.krem - above - (second ? c0 : 0u), in_bin = second ? c1 : c0;
+    if (has_lo && second && rest > but_lo) {   // the kp-th is lo itself
+      rest -= but_lo;
+      in_bin = kSelAtLo;
+    }
+    sh.rest = rest;
+    sh.in_bin = in_bin;
+  }
+  __syncthreads();
+  s.prefix = s.first ? sh.digit : (s.prefix << width) | sh.digit;
+  s.krem = sh.rest;
+  s.in_bin = sh.in_bin;
+  s.shift = sh0;
+  s.first = false;
+}
+// The krem-th largest of the c <= kSelFew keys in sh.hist, for every thread.  (They are compared with one another: the bin that
+// the first digit leaves of 6,000 to 48,000 scores has a few dozen, and a second and third digit took 1.2 us each.)
+constexpr uint32_t kSelFew = 64;
+__device__ __forceinline__ void sel_few(SelShared& sh, uint32_t c, uint32_t krem, uint32_t& T, uint32_t& need_eq) {
+  if (threadIdx.x < c) {
+    const uint32_t mine = sh.hist[threadIdx.x];
+    uint32_t above = 0, equal = 0;
+    for (uint32_t x = 0; x < c; x += 8) {   // eight at a time: one trip to the LDS
+      uint32_t y[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) y[e] = sh.hist[x + e];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        if (x + e >= c) y[e] = 0u;   // (no key of a list is 0)
+        above += y[e] > mine ? 1u : 0u;
+        equal += y[e] == mine ? 1u : 0u;
+      }
+    }
+    if (above < krem && krem <= above + equal) {   // (threads of equal keys write the same)
+      const bool all = krem == above + equal;
+      sh.few_T = mine - (all ? 1u : 0u);
+      sh.few_need = all ? 0u : krem - above;
+    }
+  }
+  __syncthreads();
+  T = sh.few_T;
+  need_eq = sh.few_need;
+}
 template <typename ForEach>
 __device__ __forceinline__ void radix_kth(SelShared& sh, ForEach&& for_each, uint32_t kp, uint32_t lo, uint32_t hi, uint32_t& T,
                                           uint32_t& need_eq) {
-  static_assert(kSelBins == 2 * kSelThreads, "two bins per thread");
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  uint32_t prefix = 0, krem = kp;             // digits so far (of key - lo)
-  int shift = 32 - __clz((int)(hi - lo) | 1);   // bits below the prefix
-  bool first = true;
-  while (shift > 0) {                         // uniform: at most three times
-    const int width = shift < 11 ? shift : 11, sh0 = shift - width;
-    const uint32_t dmask = (1u << width) - 1u;
-    sh.hist[tid] = 0;
-    sh.hist[kSelThreads + tid] = 0;
-    __syncthreads();
-    for_each([&](uint32_t key, bool valid) {
-      const uint32_t d = key - lo;
-      if (valid && d != 0u && (first || (d >> shift) == prefix)) atomicAdd(&sh.hist[(d >> sh0) & dmask], 1u);
-    });
-    __syncthreads();
-    // bins from the top: thread t takes the bins 2047 - 2 t and 2046 - 2 t
-    const uint32_t c0 = sh.hist[kSelBins - 1 - 2 * tid];
-    uint32_t c1 = sh.hist[kSelBins - 2 - 2 * tid];
-    if (tid == kSelThreads - 1 && prefix == 0) c1 = 0x7FFFFFFFu;   // the bin of lo: what the others leave
-    uint32_t inc = c0 + c1;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const uint32_t y = __shfl_up(inc, d);
-      if (lane >= d) inc += y;
-    }
-    if (lane == 63) sh.wsum[wv] = inc;
-    __syncthreads();
-    uint32_t above = inc - c0 - c1;
-#pragma unroll
-    for (int x = 0; x < kSelWaves; ++x) above += x < wv ? sh.wsum[x] : 0u;
-    if (above < krem && krem <= above + c0 + c1) {
-      const bool second = above + c0 < krem;
-      sh.digit = (uint32_t)(kSelBins - 1 - 2 * tid - (second ? 1 : 0));
-      sh.rest = krem - above - (second ? c0 : 0u);
-      sh.in_bin = second ? c1 : c0;
-    }
-    __syncthreads();
-    prefix = first ? sh.digit : (prefix << width) | sh.digit;
-    krem = sh.rest;
-    shift = sh0;
-    first = false;
-    if (krem == sh.in_bin && shift > 0) {   // the whole bin is wanted: everything above the key below it
-      T = lo + (prefix << shift) - 1u;
+  SelDigits s = sel_digits(kp, lo, hi);
+  while (s.shift > 0) {                       // uniform: at most three times
+    sel_digit(sh, for_each, lo, s);
+    if (s.in_bin == kSelAtLo) break;
+    if (s.krem == s.in_bin) {   // the whole bin is wanted: everything above the key below it
+      T = lo + (s.prefix << s.shift) - 1u;
       need_eq = 0;
       return;
     }
   }
-  T = lo + prefix;
-  need_eq = krem;
+  T = lo + s.prefix;
+  need_eq = s.krem;
 }
 
 // Emits one wave-wide group of 64 entries in order; gt / eq: entries above / equal to the threshold before it
@@ -222,6 +277,12 @@ __device__ __forceinline__ void sel_emit(const SelRow& r, uint32_t need_eq, bool
   else if (is_e && er < need_eq) r.out[r.f + gr + er] = index;
   gt += __popcll(bg);
   eq += __popcll(be);
+}
+// The same where all keys equal to the threshold are wanted (they count as above it): one ballot instead of two
+__device__ __forceinline__ void sel_emit(const SelRow& r, bool is_g, int32_t index, uint32_t& gt) {
+  const uint64_t b = __ballot(is_g);
+  if (is_g) r.out[r.f + gt + __builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u))] = index;
+  gt += __popcll(b);
 }
 // totals of the waves before this one (par: a parity, where a loop does this step after step)
 __device__ __forceinline__ void sel_wave_base(SelShared& sh, int par, uint32_t g, uint32_t e, uint32_t& gt, uint32_t& eq,
@@ -237,7 +298,11 @@ __device__ __forceinline__ void sel_wave_base(SelShared& sh, int par, uint32_t g
   }
 }
 
-// A row in registers: KPT scores per thread, a wave's scores contiguous (KPT groups of 64).
+// A row in registers: KPT scores per thread, a wave's scores contiguous (KPT groups of 64).  After the first digit a pass over the
+// scores lists the threshold's bin and counts every wave's scores above it; what a wave takes of the bin, and how many scores equal
+// to the threshold, follows from the list, so that nearly every wave emits against one threshold.  (With two more digits, a count
+// of both kinds and two ballots per group of 64, 28 heads, 20,000 scores took 24.3 us against 16.5, 32,768 23.8 against 18.9, 12,288
+// 15.2 against 12.8; shortest rows 10.8 against 9.0.)
 template <int KPT>
 __device__ __forceinline__ void sel_from_registers(SelShared& sh, const SelRow& r, int64_t n) {
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -249,6 +314,8 @@ __device__ __forceinline__ void sel_from_registers(SelShared& sh, const SelRow& 
     const uint32_t x = order_key(r.sc[i < n ? i : (int)n - 1]);   // unconditional, so that the loads overlap
     key[e] = i < n ? x : 0u;   // no finite score has key 0: neither counted nor emitted below
   }
+  if (threadIdx.x == 0) sh.few = 0;
+  if (threadIdx.x < kSelWaves) sh.extra[threadIdx.x] = 0;
   uint32_t lo = ~0u, hi = 0u, T, need_eq;
 #pragma unroll
   for (int e = 0; e < KPT; ++e) {
@@ -256,20 +323,72 @@ __device__ __forceinline__ void sel_from_registers(SelShared& sh, const SelRow& 
     hi = key[e] > hi ? key[e] : hi;
   }
   sel_range(sh, lo, hi, lo, hi);
-  radix_kth(sh, [&](auto&& f) {
+  ++lo;
+  auto for_each = [&](auto&& f) {
+    uint32_t none = 0u;
+    asm volatile("" : "+v"(none));   // (KPT lane masks held from pass to pass do not fit the scalar registers)
 #pragma unroll
-    for (int e = 0; e < KPT; ++e) f(key[e], key[e] != 0u);
-  }, r.kp, lo + 1u, hi, T, need_eq);
+    for (int e = 0; e < KPT; ++e) f(key[e], key[e] != none);
+  };
+  SelDigits s = sel_digits(r.kp, lo, hi);
+  bool few = false, whole = false;
+  while (s.shift > 0 && !few && !whole && s.in_bin != kSelAtLo) {
+    sel_digit(sh, for_each, lo, s);
+    whole = s.krem == s.in_bin;
+    few = !whole && s.shift > 0 && s.in_bin <= kSelFew;
+  }
   uint32_t g = 0, q = 0, gt = 0, eq = 0, ag, ae;
+  if (few) {
+    // one pass lists the keys of the threshold's bin and counts the wave's keys above it; the wave's share of the bin follows
+    uint32_t b0 = lo + (s.prefix << s.shift);
+    asm volatile("" : "+v"(b0));
+    const uint64_t b1 = (uint64_t)b0 + (1ull << s.shift) - 1u;
+    const uint32_t top = b1 < 0xFFFFFFFFull ? (uint32_t)b1 : 0xFFFFFFFFu;
 #pragma unroll
-  for (int e = 0; e < KPT; ++e) {
-    g += __popcll(__ballot(key[e] > T));
-    q += __popcll(__ballot(key[e] == T));
+    for (int e = 0; e < KPT; ++e) {
+      g += __popcll(__ballot(key[e] > top));
+      if (key[e] - b0 <= top - b0) {
+        const uint32_t at = atomicAdd(&sh.few, 1u);
+        sh.hist[at] = key[e];
+        sh.hist[kSelFew + at] = (uint32_t)wv;
+      }
+    }
+    __syncthreads();
+    sel_few(sh, s.in_bin, s.krem, T, need_eq);
+    if (need_eq == 0) {
+      if (threadIdx.x < s.in_bin && sh.hist[threadIdx.x] > T) atomicAdd(&sh.extra[sh.hist[kSelFew + threadIdx.x]], 1u);
+      __syncthreads();
+      g += sh.extra[wv];
+    }
+  } else {
+    T = whole ? lo + (s.prefix << s.shift) - 1u : lo + s.prefix;
+    need_eq = whole ? 0u : s.krem;
+  }
+  if (need_eq == 0) {
+    if (!few)
+#pragma unroll
+      for (int e = 0; e < KPT; ++e) g += __popcll(__ballot(key[e] > T));
+  } else {
+    g = 0;
+#pragma unroll
+    for (int e = 0; e < KPT; ++e) {
+      g += __popcll(__ballot(key[e] > T));
+      q += __popcll(__ballot(key[e] == T));
+    }
   }
   sel_wave_base(sh, 0, g, q, gt, eq, ag, ae);
-  asm volatile("" : "+v"(T));   // the lane masks are made again: 2 KPT of them do not fit the scalar registers
+  asm volatile("" : "+v"(T));   // the lane masks are made again: KPT of them do not fit the scalar registers
+  const uint32_t eq_s = __builtin_amdgcn_readfirstlane(eq), q_s = __builtin_amdgcn_readfirstlane(q), need_s = __builtin_amdgcn_readfirstlane(need_eq);
+  if (eq_s >= need_s || eq_s + q_s <= need_s) {
+    // of this wave's keys equal to T none is wanted, or all: they count as below or above the threshold
+    if (eq_s < need_s) --T;
+    gt += eq_s < need_s ? eq_s : need_s;
 #pragma unroll
-  for (int e = 0; e < KPT; ++e) sel_emit(r, need_eq, key[e] > T, key[e] == T, i0 + 64 * e, gt, eq);
+    for (int e = 0; e < KPT; ++e) sel_emit(r, key[e] > T, i0 + 64 * e, gt);
+  } else {
+#pragma unroll
+    for (int e = 0; e < KPT; ++e) sel_emit(r, need_eq, key[e] > T, key[e] == T, i0 + 64 * e, gt, eq);
+  }
 }
 
 // The m candidates of a row (keys above floor_key, with their indices), in n_slices slices: slice_of(s) = (first candidate,
@@ -352,6 +471,12 @@ __device__ __forceinline__ void sel_from_candidates(SelShared& sh, const uint2* 
     }
   };
   uint32_t g = 0, q = 0, gt = 0, eq = 0, ag, ae;
+  if (need_eq == 0) {   // no two kinds to tell apart
+    walk([&](bool is_g, bool, int32_t) { g += __popcll(__ballot(is_g)); });
+    sel_wave_base(sh, 0, g, q, gt, eq, ag, ae);
+    walk([&](bool is_g, bool, int32_t index) { sel_emit(r, is_g, index, gt); });
+    return;
+  }
   walk([&](bool is_g, bool is_e, int32_t) {
     g += __popcll(__ballot(is_g));
     q += __popcll(__ballot(is_e));
@@ -896,9 +1021,8 @@ static SelLayout sel_layout(const vs_params& p) {
   l.cap = (uint32_t)(cv > cs ? cv : cs);
   l.slices = align_up(rows * sizeof(SelHeader), 256);
   l.cand = l.slices + align_up(rows * (size_t)l.n_slices * sizeof(uint2), 256);
-  l.sliced = n > kSelOwnKeys && (int64_t)l.cap > sel_most_candidates(n, (int)rows);
-  // (rows of up to kSelOwnKeys list their own candidates in LDS)
-  l.total = n <= kSelOwnKeys ? 256 : (l.sliced ? sel_ctl_bytes(p) : l.cand + align_up(rows * l.cap * sizeof(uint2), 256));
+  l.sliced = n > kSelRegKeys && (int64_t)l.cap > sel_most_candidates(n, (int)rows);
+  l.total = n <= kSelRegKeys ? 256 : (l.sliced ? sel_ctl_bytes(p) : l.cand + align_up(rows * l.cap * sizeof(uint2), 256));
   return l;
 }
 size_t select_ws_bytes(const vs_params& p) { return sel_layout(p).total; }
@@ -935,13 +1059,14 @@ hipError_t launch_select(const vs_params& p, const float* vscore, const float* s
   const SelLayout l = sel_layout(p);
   a.n_slices = l.n_slices; a.samples_v = l.samples_v; a.samples_s = l.samples_s;
   const dim3 rows(2u * (unsigned)p.n_q_heads), block(kSelThreads);
-  if (a.n <= 8 * kSelThreads) {
-    hipLaunchKernelGGL(k_sel_row<8>, rows, block, 0, st, a);
-  } else if (a.n <= 16 * kSelThreads) {
-    hipLaunchKernelGGL(k_sel_row<16>, rows, block, 0, st, a);
-  } else if (a.n <= kSelRegKeys) {
-    hipLaunchKernelGGL(k_sel_row<32>, rows, block, 0, st, a);
-  } else if (l.sliced || (a.n > kSelOwnKeys && ws_bytes < l.total && l.cap > kSelCand)) {
+  const auto in_registers = [&](auto&& kernel, int kpt) {
+    if (a.n > (int64_t)kpt * kSelThreads) return false;
+    hipLaunchKernelGGL(kernel, rows, block, 0, st, a);
+    return true;
+  };
+  if (in_registers(k_sel_row<4>, 4) || in_registers(k_sel_row<8>, 8) || in_registers(k_sel_row<12>, 12) || in_registers(k_sel_row<16>, 16) ||
+      in_registers(k_sel_row<24>, 24) || in_registers(k_sel_row<32>, 32) || in_registers(k_sel_row<40>, 40) || in_registers(k_sel_row<48>, 48)) {
+  } else if (l.sliced || (a.n > kSelRegKeys && ws_bytes < l.total && l.cap > kSelCand)) {
     if (!ws || ws_bytes < sel_ctl_bytes(p)) return hipErrorInvalidValue;
     return launch_slices(a, ws, st);
   } else {
@@ -951,7 +1076,7 @@ hipError_t launch_select(const vs_params& p, const float* vscore, const float* s
                                  kSelCand * (int)sizeof(uint2));
     });
     if (e != hipSuccess) return e;
-    if (ws && ws_bytes >= l.total && a.n > kSelOwnKeys) {
+    if (ws && ws_bytes >= l.total && a.n > kSelRegKeys) {
       a.hdr = (SelHeader*)ws;
       a.slices = (uint2*)((char*)ws + l.slices);
       a.cand = (uint2*)((char*)ws + l.cand);

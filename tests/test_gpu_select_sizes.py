@@ -67,3 +67,21 @@ def test_every_route_of_long_rows(hq, n, bs, kind):
     for sets in (vs.select(ck, vsc, ssc), vs.select_static(ck, vsc, ssc, vs.alloc_index_sets(ck, vsc.device))):
         for a, b, nm in zip(sets, want, ("v_idx", "v_cnt", "s_idx", "s_cnt")):
             assert torch.equal(a, b), f"{nm}: {hq} heads, n {n}, {kind}, {bs} offsets"
+
+
+def _few(hq, n, g):
+    """Every score one to five times: thresholds fall on short lists, between equal scores of several waves and of one."""
+    dev = torch.device("cuda:0")
+    return torch.randint(1, n // 2 + 2, (hq, n), generator=g, device=dev).float() / n
+
+
+@pytest.mark.parametrize("n", [200, 4095, 4096, 4097, 8191, 12288, 12289, 16384, 24576, 24577, 32768, 40960, 40961, 49151, 49152])
+def test_rows_in_registers_at_every_length(n):
+    g = torch.Generator(device="cuda:0").manual_seed(300 + n)
+    hq = 4
+    for vsc, ssc in ((_few(hq, n, g), _few(hq, n, g)), (_scores("sparse", hq, n, g), _scores("ties", hq, n, g))):
+        for bv, bs, keep in ((2, 70, 64), (n // 7 + 2, n // 3 + 2, 64), (n - 1, n // 2, 0)):
+            ck = vs.Chunk(hq, 1, 128, 64, n - 64, 0.1, vertical_budget=bv, slash_budget=bs, keep_first_cols=1, keep_local_band=keep)
+            want = (*_want(vsc, bv, 1), *_want(ssc, bs, keep))
+            for a, b, nm in zip(vs.select(ck, vsc, ssc), want, ("v_idx", "v_cnt", "s_idx", "s_cnt")):
+                assert torch.equal(a, b), f"{nm}: n {n}, budgets {bv} / {bs}"
