@@ -42,8 +42,10 @@ struct DecodeArgs {
   uint2* ent;             // [n_req][Hkv][ent_stride] (diagonal, heads that have it)
   int2* len;              // [n_req][Hkv] (entries, entries + tiles of 64 gathered columns)
   int32_t words, ent_stride;
-  // shares: plan[0] = blocks in all, plan[1] = shares, plan[2 + r] = blocks before request r
+  // shares: plan[0] = blocks in all, plan[1] = shares, plan[2 + r] = blocks before request r; of one request without index sets the
+  // host knows them (one_T blocks, one_n shares; 0: the device finds them)
   int64_t* plan;
+  int64_t one_T, one_n;
   float* part_o;          // [share + (request, KV head)][G][D]
   float* part_ml;         // [share + (request, KV head)][G][2] (reference, sum)
 };
@@ -67,8 +69,12 @@ __device__ __forceinline__ bool decode_takes(const DecodeArgs& a, const vs_reque
 }
 __device__ __forceinline__ int decode_blocks(const vs_request& rq) { return (int)((rq.q_start + kBlock) / kBlock); }
 // share w of n covers blocks [w T / n, (w + 1) T / n)
-__device__ __forceinline__ int64_t share_start(int64_t w, int64_t n, int64_t T) { return w * T / n; }
-__device__ __forceinline__ int64_t share_of(int64_t block, int64_t n, int64_t T) { return ((block + 1) * n - 1) / T; }
+// (quotients of 64 bits, most of which fit 32: a fifth of the instructions)
+__device__ __forceinline__ int64_t short_div(int64_t x, int64_t y) {
+  return (uint64_t)(x | y) >> 32 ? x / y : (int64_t)((uint32_t)x / (uint32_t)y);
+}
+__device__ __forceinline__ int64_t share_start(int64_t w, int64_t n, int64_t T) { return short_div(w * T, n); }
+__device__ __forceinline__ int64_t share_of(int64_t block, int64_t n, int64_t T) { return short_div((block + 1) * n - 1, T); }
 
 template <int D>
 constexpr int decode_lds_bytes() { return kDecWaves * 2 * 2 * 32 * D * 2; }
@@ -113,9 +119,9 @@ __global__ __launch_bounds__(kDecThreads, 2) void k_decode(const DecodeArgs a) {
     for (int g = 0; g < a.n_kv_heads; ++g) n += a.len[(int64_t)r * a.n_kv_heads + g].y;
     return n;
   };
-  int64_t T = 0, first = 0;
+  int64_t T = a.one_T, first = 0;
   if (a.n_req == 1) {
-    T = blocks_of(0);
+    if (T == 0) T = blocks_of(0);
   } else {
     for (int r = tid; r < a.n_req; r += kDecThreads) T += blocks_of(r);
 #pragma unroll
@@ -127,8 +133,10 @@ __global__ __launch_bounds__(kDecThreads, 2) void k_decode(const DecodeArgs a) {
   }
   int64_t n_share = (T + kDecMinBlocks - 1) / kDecMinBlocks;
   if (n_share > (int64_t)gridDim.x) n_share = gridDim.x;
-  if (blockIdx.x == 0 && tid == 0) { a.plan[0] = T; a.plan[1] = n_share; }
-  if (a.n_req == 1) {
+  if (blockIdx.x == 0 && tid == 0 && a.one_T == 0) { a.plan[0] = T; a.plan[1] = n_share; }
+  if (a.one_T) {
+    if (blockIdx.x >= n_share) return;
+  } else if (a.n_req == 1) {
     if (blockIdx.x == 0 && tid == 0) a.plan[2] = 0;
     if (blockIdx.x >= n_share) return;
   } else if (blockIdx.x != 0 && blockIdx.x >= n_share) {
@@ -200,17 +208,13 @@ __global__ __launch_bounds__(kDecThreads, 2) void k_decode(const DecodeArgs a) {
     const bool whole = b0 == 0 && b1 == seg_len;
     const int h0 = g * a.group;
 
-    // ---- Q^T operand: lane (head h0 + col, k-group g4); heads beyond the group are zero ------------
+    // ---- Q^T operand: lane (head h0 + col, k-group g4); columns beyond the group repeat its first head and are not stored (zeros in
+    // their place had to wait for the loads before the first copies went out: 0.7 us) --------------------
     bf16x8 qreg[KS];
     {
       const __bf16* qp = (const __bf16*)rq.q + (int64_t)(h0 + (col < a.group ? col : 0)) * a.q_stride_head + 8 * g4;
 #pragma unroll
-      for (int st = 0; st < KS; ++st) {
-        qreg[st] = *(const bf16x8*)(qp + 32 * st);
-        if (col >= a.group)
-#pragma unroll
-          for (int x = 0; x < 8; ++x) qreg[st][x] = (__bf16)0.f;
-      }
+      for (int st = 0; st < KS; ++st) qreg[st] = *(const bf16x8*)(qp + 32 * st);
     }
     f32x4 oacc[DB];
 #pragma unroll
@@ -319,6 +323,10 @@ __global__ __launch_bounds__(kDecThreads, 2) void k_decode(const DecodeArgs a) {
     Chunk cur;
     cur.keys = cur.rows = 0u;
     if (c < c_end) cur = issue(c, 0);
+    // Q is waited for here, with the first copies: at its first use it would be waited for in every turn of the loop, and the next
+    // chunk's copies, which the compiler does not see, with it
+#pragma unroll
+    for (int st = 0; st < KS; ++st) asm volatile("" : "+v"(qreg[st]));
     for (int b = 0; c < c_end; c += kDecWaves, b ^= 1) {
       Chunk nxt;
       nxt.keys = nxt.rows = 0u;
@@ -457,16 +465,19 @@ __global__ __launch_bounds__(kDecThreads, 2) void k_decode(const DecodeArgs a) {
 }
 
 // out = sum_s O_s 2^(m_s - M) / sum_s l_s 2^(m_s - M) over the shares that a (request, KV head) lies in; one workgroup per
-// (query head, request), shares folded in a fixed order (run-to-run identical): wave w takes every fourth share, then
-// the waves are added in order.
-template <int D>
-__global__ __launch_bounds__(kDecThreads) void k_decode_combine(const DecodeArgs a) {
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+// (query head, request), shares folded in a fixed order (run-to-run identical): wave w takes every NW-th share, then
+// the waves are added in order.  Bound by latency: the partial results of 8 NW shares are all on their way before the references
+// are compared (four waves, and the references first: one token at 5,003 keys 14.1 us with its two launches, 12.1 so and with the
+// shares counted on the host).  Eight waves where a KV head lies in more than 32 shares, else four: 60 tokens of 40 heads, a share or
+// two each, 71 us with four, 75 with eight.
+template <int D, int NW>
+__global__ __launch_bounds__(64 * NW) void k_decode_combine(const DecodeArgs a) {
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int h = blockIdx.x, r = blockIdx.y, g = h / a.group, q = h - g * a.group;
   const vs_request rq = decode_request(a, r);
   if (!decode_takes(a, rq)) return;
-  const int64_t T = a.plan[0], n = a.plan[1];
-  int64_t from = a.plan[2 + r];
+  const int64_t T = a.one_T ? a.one_T : a.plan[0], n = a.one_T ? a.one_n : a.plan[1];
+  int64_t from = a.one_T ? 0 : a.plan[2 + r];
   int seg_len = decode_blocks(rq);
   if (rq.s_idx) {
     const int2* const len = a.len + (int64_t)r * a.n_kv_heads;
@@ -479,29 +490,33 @@ __global__ __launch_bounds__(kDecThreads) void k_decode_combine(const DecodeArgs
   if (s0 == s1) return;   // finished by its one share
   const int64_t row0 = ((int64_t)s0 + (int64_t)r * a.n_kv_heads + g) * a.group + q;   // row of share s: row0 + (s - s0) G
   const int cnt = s1 - s0 + 1;
-  float M = -INFINITY;
-  for (int s = lane; s < cnt; s += 64) M = fmaxf(M, a.part_ml[2 * (row0 + (int64_t)s * a.group)]);
+  constexpr int E = D / 64, U = 8;
+  float acc[E], L = 0.f, o[U][E], w[U], l[U];
+  auto fetch = [&](int sb) {   // shares sb, sb + NW, ...
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int s = sb + NW * u < cnt ? sb + NW * u : cnt - 1;
+      const int64_t row = row0 + (int64_t)s * a.group;
+      const float2 ml = *(const float2*)(a.part_ml + 2 * row);
+      w[u] = ml.x;
+      l[u] = ml.y;
+#pragma unroll
+      for (int e = 0; e < E; ++e) o[u][e] = a.part_o[row * D + 64 * e + lane];
+    }
+  };
+  float M = lane < cnt ? a.part_ml[2 * (row0 + (int64_t)lane * a.group)] : -INFINITY;
+  fetch(wv);
+  for (int s = 64 + lane; s < cnt; s += 64) M = fmaxf(M, a.part_ml[2 * (row0 + (int64_t)s * a.group)]);
 #pragma unroll
   for (int d = 1; d < 64; d <<= 1) M = fmaxf(M, __shfl_xor(M, d));
-  constexpr int E = D / 64, U = 8;
-  float acc[E], L = 0.f;
 #pragma unroll
   for (int e = 0; e < E; ++e) acc[e] = 0.f;
   if (M != -INFINITY) {
-    for (int sb = wv; sb < cnt; sb += kDecWaves * U) {
-      float o[U][E], w[U], l[U];
+    for (int sb = wv; sb < cnt; sb += NW * U) {
+      if (sb != wv) fetch(sb);
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const int s = sb + kDecWaves * u < cnt ? sb + kDecWaves * u : cnt - 1;
-        const int64_t row = row0 + (int64_t)s * a.group;
-        w[u] = a.part_ml[2 * row];
-        l[u] = a.part_ml[2 * row + 1];
-#pragma unroll
-        for (int e = 0; e < E; ++e) o[u][e] = a.part_o[row * D + 64 * e + lane];
-      }
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        if (sb + kDecWaves * u >= cnt || w[u] == -INFINITY) continue;
+        if (sb + NW * u >= cnt || w[u] == -INFINITY) continue;
         const float x = __builtin_amdgcn_exp2f(w[u] - M);
         L += l[u] * x;
 #pragma unroll
@@ -509,17 +524,17 @@ __global__ __launch_bounds__(kDecThreads) void k_decode_combine(const DecodeArgs
       }
     }
   }
-  __shared__ float acc_s[kDecWaves][D], l_s[kDecWaves];
+  __shared__ float acc_s[NW][D], l_s[NW];
 #pragma unroll
   for (int e = 0; e < E; ++e) acc_s[wv][64 * e + lane] = acc[e];
   if (lane == 0) l_s[wv] = L;
   __syncthreads();
   if (tid >= D) return;
-  float o = acc_s[0][tid];
+  float out = acc_s[0][tid];
   L = l_s[0];
 #pragma unroll
-  for (int w = 1; w < kDecWaves; ++w) { o += acc_s[w][tid]; L += l_s[w]; }
-  ((__bf16*)rq.out)[(int64_t)h * a.o_stride_head + tid] = (__bf16)(L > 0.f ? o / L : 0.f);
+  for (int x = 1; x < NW; ++x) { out += acc_s[x][tid]; L += l_s[x]; }
+  ((__bf16*)rq.out)[(int64_t)h * a.o_stride_head + tid] = (__bf16)(L > 0.f ? out / L : 0.f);
   if (rq.lse && tid == 0) rq.lse[h] = L > 0.f ? (M + __builtin_amdgcn_logf(L)) * kLn2 : -INFINITY;
 }
 
@@ -680,13 +695,21 @@ hipError_t launch_decode(const vs_params& p, const vs_request* one, const vs_req
   if (e != hipSuccess) return e;
   if (lists)
     hipLaunchKernelGGL(k_decode_lists, dim3((unsigned)p.n_kv_heads, (unsigned)n_req), dim3(kDecListThreads), 0, st, a);
+  if (one && !lists) {   // as k_decode counts them
+    a.one_T = ceil_div(one->q_start + one->q_len, (int64_t)kBlock) * p.n_kv_heads;
+    a.one_n = ceil_div(a.one_T, kDecMinBlocks);
+    if (a.one_n > l.shares) a.one_n = l.shares;
+  }
   const dim3 grid((unsigned)l.shares), cgrid((unsigned)p.n_q_heads, (unsigned)n_req);
+  const bool many = l.shares > 32 * (int64_t)n_req * p.n_kv_heads;
   if (p.head_dim == 128) {
     hipLaunchKernelGGL(k_decode<128>, grid, dim3(kDecThreads), decode_lds_bytes<128>(), st, a);
-    hipLaunchKernelGGL(k_decode_combine<128>, cgrid, dim3(kDecThreads), 0, st, a);
+    if (many) hipLaunchKernelGGL((k_decode_combine<128, 8>), cgrid, dim3(512), 0, st, a);
+    else hipLaunchKernelGGL((k_decode_combine<128, 4>), cgrid, dim3(256), 0, st, a);
   } else {
     hipLaunchKernelGGL(k_decode<64>, grid, dim3(kDecThreads), decode_lds_bytes<64>(), st, a);
-    hipLaunchKernelGGL(k_decode_combine<64>, cgrid, dim3(kDecThreads), 0, st, a);
+    if (many) hipLaunchKernelGGL((k_decode_combine<64, 8>), cgrid, dim3(512), 0, st, a);
+    else hipLaunchKernelGGL((k_decode_combine<64, 4>), cgrid, dim3(256), 0, st, a);
   }
   return hipGetLastError();
 }
