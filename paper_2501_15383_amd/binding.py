@@ -158,7 +158,7 @@ class Chunk:
         hq, hkv, d = self.n_q_heads, self.n_kv_heads, self.head_dim
 
         def st(t, heads):
-            return (t.stride(0), t.stride(1)) if t is not None else (heads * d, d)
+            return t.stride() if t is not None else (heads * d, d)
 
         qs, ks, vs_, os_ = st(q, hq), st(k, hkv), st(v, hkv), st(out, hq)
         return VsParams(hq, hkv, d, self.last_q, self.q_len, self.q_start, qs[0], qs[1], ks[0], ks[1],
@@ -167,11 +167,12 @@ class Chunk:
 
 
 def _ptr(t):
-    return C.c_void_p(t.data_ptr()) if t is not None else C.c_void_p(0)
+    return t.data_ptr() if t is not None else None
 
 
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    # the current stream's handle without the Stream object that torch.cuda.current_stream() makes
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _check(rc, where):
@@ -261,7 +262,7 @@ def select(ck: Chunk, vscore, sscore, sets=None):
     ws, n = _ws(ck, VS_WS_SELECT, dev)
     p = ck.params()
     _check(lib().vs_select(C.byref(p), _ptr(vscore), _ptr(sscore), _ptr(v_idx), _ptr(v_cnt), _ptr(s_idx),
-                           _ptr(s_cnt), _ptr(ws) if n else C.c_void_p(0), n, _stream()), "vs_select")
+                           _ptr(s_cnt), _ptr(ws) if n else None, n, _stream()), "vs_select")
     return v_idx, v_cnt, s_idx, s_cnt
 
 
@@ -291,7 +292,7 @@ def select_heads(ck: Chunk, vscore, sscore, v_budget_h, s_budget_h, sets=None):
     p = ck.params()
     _check(lib().vs_select_heads(C.byref(p), _ptr(vscore), _ptr(sscore), _ptr(v_budget_h), _ptr(s_budget_h),
                                  _ptr(v_idx), _ptr(v_cnt), _ptr(s_idx), _ptr(s_cnt),
-                                 _ptr(ws) if n else C.c_void_p(0), n, _stream()), "vs_select_heads")
+                                 _ptr(ws) if n else None, n, _stream()), "vs_select_heads")
     return v_idx, v_cnt, s_idx, s_cnt
 
 
@@ -344,9 +345,8 @@ def sparse_attn_prefill(ck: Chunk, q, k, v, v_idx, v_cnt, s_idx, s_cnt, want_lse
     if out is None:
         out = torch.empty((ck.q_len, ck.n_q_heads, ck.head_dim), dtype=torch.bfloat16, device=dev)
     lse = torch.empty((ck.n_q_heads, ck.q_len), dtype=torch.float32, device=dev) if want_lse else None
-    n = workspace_bytes(ck, VS_WS_SPARSE)
     if ws is None:
-        ws = torch.empty(max(n, 256), dtype=torch.uint8, device=dev)
+        ws = torch.empty(max(workspace_bytes(ck, VS_WS_SPARSE), 256), dtype=torch.uint8, device=dev)
     p = ck.params(q=q, k=k, v=v, out=out)
     if dca is not None:
         d = _dca_struct(ck, q, dca)
@@ -370,9 +370,8 @@ def dense_causal_prefill(ck: Chunk, q, k, v, want_lse=False, out=None, ws=None, 
     if out is None:
         out = torch.empty((ck.q_len, ck.n_q_heads, ck.head_dim), dtype=torch.bfloat16, device=dev)
     lse = torch.empty((ck.n_q_heads, ck.q_len), dtype=torch.float32, device=dev) if want_lse else None
-    n = workspace_bytes(ck, VS_WS_DENSE)
     if ws is None:
-        ws = torch.empty(max(n, 256), dtype=torch.uint8, device=dev)
+        ws = torch.empty(max(workspace_bytes(ck, VS_WS_DENSE), 256), dtype=torch.uint8, device=dev)
     p = ck.params(q=q, k=k, v=v, out=out)
     if dca is not None:
         d = _dca_struct(ck, q, dca)
@@ -396,9 +395,8 @@ def prefill_chunk(ck: Chunk, q, k, v, want_lse=False, out=None, ws=None, dca=Non
     if out is None:
         out = torch.empty((ck.q_len, ck.n_q_heads, ck.head_dim), dtype=torch.bfloat16, device=dev)
     lse = torch.empty((ck.n_q_heads, ck.q_len), dtype=torch.float32, device=dev) if want_lse else None
-    n = workspace_bytes(ck, VS_WS_CHUNK)
     if ws is None:
-        ws = torch.empty(max(n, 256), dtype=torch.uint8, device=dev)
+        ws = torch.empty(max(workspace_bytes(ck, VS_WS_CHUNK), 256), dtype=torch.uint8, device=dev)
     p = ck.params(q=q, k=k, v=v, out=out)
     if dca is not None:
         d = _dca_struct(ck, q, dca)
@@ -445,8 +443,8 @@ def attn_batch(ck: Chunk, table, n_requests, q, k, v, out, ws=None):
     """vs_attn_batch.  ck: the shared shape with q_len = the longest request and q_start + q_len = the most
     keys any request sees; table: from request_table; q / k / v / out: one request's tensors, for the strides."""
     p = ck.params(q=q, k=k, v=v, out=out)
-    n = int(lib().vs_batch_workspace_bytes(C.byref(p), int(n_requests)))
     if ws is None:
+        n = int(lib().vs_batch_workspace_bytes(C.byref(p), int(n_requests)))
         ws = torch.empty(max(n, 256), dtype=torch.uint8, device=table.device)
     _check(lib().vs_attn_batch(C.byref(p), _ptr(table), int(n_requests), _ptr(ws), ws.numel(), _stream()), "vs_attn_batch")
     return ws
