@@ -95,7 +95,7 @@ struct AttnArgs {
   int64_t q_stride_tok, q_stride_head, k_stride_tok, k_stride_head;
   int64_t v_stride_tok, v_stride_head, o_stride_tok, o_stride_head;
   const uint32_t* bm_a;  // block-diagonal bitmap per head
-  const uint32_t* ent;   // key-block entry list per head (see BlockList)
+  const uint32_t* ent;   // key-block entry list per head (see BlockList); null (SPLIT only): every block, no list is made
   int64_t bm_stride;     // words per head, 0 = one bitmap shared by all heads (dense)
   int32_t bm_words;      // words of one bitmap row; its last word holds the head's segment shift
   int64_t ent_stride;    // entries per head, 0 = one list shared by all heads (dense)
@@ -538,6 +538,7 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
     const int cc_lo = sp * per;
     cc_end = cc_lo + per - 1 < cc_last ? cc_lo + per - 1 : cc_last;
     int lo = 0, hi = (int)a.ent_len - 1;  // the last entry is a sentinel: an answer always exists
+    if (!BATCH && !a.ent) lo = hi = pack > 1 ? (cc_lo > NQB - 1 ? cc_lo - (NQB - 1) : 0) : cc_lo;
     while (lo < hi) {
       const int step = (hi - lo + 63) >> 6, x = lo + lane * step;
       const int below = __popcll(__ballot((int)(ent_h[x < hi ? x : hi] >> 4) < cc_lo));   // (never at hi)
@@ -547,7 +548,16 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
     }
     ei0 = lo;
   }
-  uint32_t ecache = ent_h[(ei0 & ~63) + lane], ecache_nx = ent_h[(ei0 & ~63) + 64 + lane];
+  // entries at .. at + 63, one per lane: of the list, or (see build_list) of all blocks, which ends with the walk and not with sentinels
+  auto entries = [&](int at) -> uint32_t {
+    if (SPLIT && !BATCH && !a.ent) {
+      const uint32_t i = (uint32_t)(at + lane);
+      if (pack > 1) return ((i + NQB - 1) << 4) | 15u;
+      return (i << 4) | (i < NQB - 1 ? ((1u << NQB) - 1u) & (((1u << NQB) - 1u) << (NQB - 1 - i)) : (1u << NQB) - 1u);
+    }
+    return ent_h[at + lane];
+  };
+  uint32_t ecache = entries(ei0 & ~63), ecache_nx = entries((ei0 & ~63) + 64);
   int ei = ei0 - 1;
   // Columns of vertical tiles go into a ring of four in LDS when the tile is found, two steps before its rows are copied:
   // slot (ring + n) & 3 for the tile n steps from now, written by the first wave, read behind the barrier of the step.
@@ -560,7 +570,7 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
       ++ei;
       if (__builtin_expect((ei & 63) == 0 && ei > ei0, 0)) {
         ecache = ecache_nx;
-        ecache_nx = ent_h[(ei & ~63) + 64 + lane];
+        ecache_nx = entries((ei & ~63) + 64);
       }
       const uint32_t e = __builtin_amdgcn_readlane(ecache, ei & 63);
       const int cc = (int)(e >> 4);
@@ -1681,8 +1691,9 @@ size_t attn_sync_bytes(const vs_params& p) { return attn_counter_bytes(p) + attn
 // One workgroup folds 1024 / D rows of a unit at a time; those of a batch, whose cut units only the device knows, take the next
 // ones until none are left (a grid for as many units as there may be: 26 us for 1,500 requests none of which was cut, 4 now),
 // and up to four of a unit in a row where there are more than workgroups, because finding them takes as long as folding a few
-// pieces.  Eight pieces at a time are on their way (four: 55 us for two requests of 64 rows and 40,000 keys in 128 ranges, 24
-// now).
+// pieces.  Bound by latency: a row's lanes read a reference and a sum each (all pieces' at once) while the first eight accumulators are
+// under way, and the weights go around by lane exchanges.  (Every lane reading all references, and after them everything again,
+// eight pieces at a time: 5 to 10 us for 40 to 60 pieces of a row, 3 to 6 so.)
 template <int D>
 constexpr int combine_parts() { return kTileRows / (1024 / D); }   // per unit
 constexpr int kCombineGrid = 2048;   // workgroups for a batch at most
@@ -1720,46 +1731,51 @@ __global__ __launch_bounds__(256) void k_attn_combine(const AttnArgs a0) {
   if (row < 0 || row >= a.q_rows || h - g * a.group + th >= a.group) continue;
   const int hw = h + th;
   const int64_t at = (int64_t)(BATCH ? e + a.first_slot : e) * kTileRows + lrow, step = (int64_t)n_fold * kTileRows;
-  constexpr int U = 8;
-  float M = -INFINITY;
-  int sp = 0;
-  for (; sp + U <= a.n_split; sp += U) {
-    float m[U];
+  constexpr int U = 8, NB = kMaxSplit / LR;   // pieces whose accumulators are under way together; references per lane
+  static_assert(LR % U == 0, "the pieces of a batch have their weights in one register");
+  f32x4 o[U];
+  auto fetch = [&](int sp) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) m[u] = a.part_ml[2 * (at + step * (sp + u))];
-#pragma unroll
-    for (int u = 0; u < U; ++u) M = fmaxf(M, m[u]);
-  }
-#pragma unroll 4
-  for (; sp < a.n_split; ++sp) M = fmaxf(M, a.part_ml[2 * (at + step * sp)]);
-  const float M0 = M == -INFINITY ? 0.f : M;
-  float L = 0.f;
-  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  // (a piece without live keys: weight 0, and zeros in its slot)
-  auto fold = [&](float m, float l, f32x4 o) {
-    const float w = __builtin_amdgcn_exp2f(m - M0);
-    L += l * w;
-#pragma unroll
-    for (int x = 0; x < 4; ++x) acc[x] += o[x] * w;
+    for (int u = 0; u < U; ++u) o[u] = *(const f32x4*)(a.part_o + (at + step * (sp + u < a.n_split ? sp + u : a.n_split - 1)) * D + d);
   };
-  for (sp = 0; sp + U <= a.n_split; sp += U) {
-    float m[U], l[U];
-    f32x4 o[U];
+  fetch(0);
+  // lane x of the row: pieces x, LR + x, ...
+  const int lr = threadIdx.x % LR, lane0 = (threadIdx.x & 63) - lr;
+  float m[NB], w[NB], M = -INFINITY, L = 0.f;
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int64_t x = at + step * (sp + u);
-      m[u] = a.part_ml[2 * x];
-      l[u] = a.part_ml[2 * x + 1];
-      o[u] = *(const f32x4*)(a.part_o + x * D + d);
+  for (int b = 0; b < NB; ++b) {
+    m[b] = -INFINITY;
+    w[b] = 0.f;
+    if (b * LR < a.n_split && b * LR + lr < a.n_split) {
+      const float2 ml = *(const float2*)(a.part_ml + 2 * (at + step * (b * LR + lr)));
+      m[b] = ml.x;
+      w[b] = ml.y;   // (the sum, until the weight is known)
     }
+    M = fmaxf(M, m[b]);
+  }
 #pragma unroll
-    for (int u = 0; u < U; ++u) fold(m[u], l[u], o[u]);
+  for (int x = 1; x < LR; x <<= 1) M = fmaxf(M, __shfl_xor(M, x));
+  const float M0 = M == -INFINITY ? 0.f : M;
+#pragma unroll
+  for (int b = 0; b < NB; ++b) {
+    const float l = w[b];
+    w[b] = __builtin_amdgcn_exp2f(m[b] - M0);   // (a piece without live keys: weight 0, and zeros in its slot)
+    L += l * w[b];
   }
-#pragma unroll 4
-  for (; sp < a.n_split; ++sp) {
-    const int64_t x = at + step * sp;
-    fold(a.part_ml[2 * x], a.part_ml[2 * x + 1], *(const f32x4*)(a.part_o + x * D + d));
-  }
+#pragma unroll
+  for (int x = 1; x < LR; x <<= 1) L += __shfl_xor(L, x);
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int b = 0; b < NB; ++b)
+    for (int sp = b * LR; sp < a.n_split && sp < (b + 1) * LR; sp += U) {
+      if (sp > 0) fetch(sp);
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const float wu = __shfl(w[b], lane0 + sp - b * LR + u);   // (0 behind the last piece)
+#pragma unroll
+        for (int x = 0; x < 4; ++x) acc[x] += o[u][x] * wu;
+      }
+    }
   const float inv = L > 0.f ? 1.0f / L : 0.f;
 #pragma unroll
   for (int x = 0; x < 4; ++x) acc[x] *= inv;
@@ -1852,29 +1868,6 @@ __global__ __launch_bounds__(1024) void k_attn_schedule(const AttnArgs a, int32_
   }
 }
 
-// One list per head, or per tile of packed heads (one for all heads when dense); attn: for the attention launch with the
-// counters at sync_ws, which are cleared on the way (null: for k_count_tiles, which packs nothing and has none to clear).
-hipError_t launch_build_blocklist(const vs_params& p, const int32_t* s_idx, const int32_t* s_cnt,
-                                  bool dense, const BlockList& bl, void* sync_ws, hipStream_t st) {
-  const int64_t n_k = p.q_start + p.q_len;
-  AttnCut c = {};
-  if (sync_ws) c = attn_cut(p, dense);
-  ListArgs a = {};
-  a.s_idx = s_idx; a.s_cnt = s_cnt; a.s_budget = p.slash_budget;
-  a.dense = dense;
-  a.n_blk = (int)ceil_div(n_k, kBlock);
-  a.n_words = (int)bl.words; a.ent_stride = (int)bl.ent_stride;
-  a.bm_a = bl.bm_a; a.ent = bl.ent;
-  a.n_heads = p.n_q_heads; a.group = p.n_q_heads / p.n_kv_heads;
-  a.pack = c.queue ? c.pack : 1;
-  a.zero = (uint32_t*)sync_ws;
-  a.n_zero = sync_ws ? (int)(attn_counter_bytes(p) / sizeof(uint32_t)) : 0;
-  const unsigned parts = dense ? (unsigned)ceil_div(bl.ent_stride, kBlDensePart) : 1u;
-  const unsigned lists = dense ? 1u : (unsigned)(p.n_kv_heads * ceil_div(a.group, a.pack));
-  hipLaunchKernelGGL((k_build_blocklist<kAttnQBlocks, false>), dim3(lists, parts), dim3(kBlThreads), 0, st, a);
-  return hipGetLastError();
-}
-
 // Per-device set-up, done once for each device a launch is made on (with that device current):
 // its number of compute units, and the opt-in of every attention instantiation to more than
 // 64 KiB of LDS per workgroup (a function attribute, held per device by the runtime).
@@ -1912,6 +1905,52 @@ static hipError_t attn_device_setup(int* n_cu_out) {
   }
   *n_cu_out = cu_of[dev];
   return hipSuccess;
+}
+
+// Resident workgroups per XCD: two fit a compute unit
+static int attn_members(int n_cu) {
+  const int members = ((4 / kAttnQBlocks) * n_cu) / 8;
+  return members < 1 ? 1 : members;
+}
+// Whole units of a cut launch that keep pace, in a launch of their own (see launch_attention).
+static bool attn_paced(const AttnCut& c, int64_t n_k, int members) {
+  return c.queue && c.n_split > 1 && c.n_whole > 0 && c.pack == 1 && members == kRun && ceil_div(n_k, kBlock) >= kPaceBlocks;
+}
+// Dense launches of no more pieces than workgroups need neither a list (every block is in it) nor cleared counters (nobody takes
+// a second piece): the list builder is not launched.  34 rows of 28 heads at 11,126 keys 34.5 us -> 31.3, the fold's share
+// of it included; rows of 2 to 391 at 600 to 50,000 keys gain 2 to 11 %.
+static bool attn_listless(const vs_params& p, bool dense, const AttnCut& c, int members) {
+  return dense && c.queue && !attn_paced(c, p.q_start + p.q_len, members) &&
+         c.n_whole + (int64_t)(c.n_units - c.n_whole) * c.n_split <= 8 * (int64_t)members;
+}
+
+// One list per head, or per tile of packed heads (one for all heads when dense); attn: for the attention launch with the
+// counters at sync_ws, which are cleared on the way (null: for k_count_tiles, which packs nothing and has none to clear).
+hipError_t launch_build_blocklist(const vs_params& p, const int32_t* s_idx, const int32_t* s_cnt,
+                                  bool dense, const BlockList& bl, void* sync_ws, hipStream_t st) {
+  const int64_t n_k = p.q_start + p.q_len;
+  AttnCut c = {};
+  if (sync_ws) {
+    c = attn_cut(p, dense);
+    int n_cu = 0;
+    const hipError_t e = attn_device_setup(&n_cu);
+    if (e != hipSuccess) return e;
+    if (attn_listless(p, dense, c, attn_members(n_cu))) return hipSuccess;
+  }
+  ListArgs a = {};
+  a.s_idx = s_idx; a.s_cnt = s_cnt; a.s_budget = p.slash_budget;
+  a.dense = dense;
+  a.n_blk = (int)ceil_div(n_k, kBlock);
+  a.n_words = (int)bl.words; a.ent_stride = (int)bl.ent_stride;
+  a.bm_a = bl.bm_a; a.ent = bl.ent;
+  a.n_heads = p.n_q_heads; a.group = p.n_q_heads / p.n_kv_heads;
+  a.pack = c.queue ? c.pack : 1;
+  a.zero = (uint32_t*)sync_ws;
+  a.n_zero = sync_ws ? (int)(attn_counter_bytes(p) / sizeof(uint32_t)) : 0;
+  const unsigned parts = dense ? (unsigned)ceil_div(bl.ent_stride, kBlDensePart) : 1u;
+  const unsigned lists = dense ? 1u : (unsigned)(p.n_kv_heads * ceil_div(a.group, a.pack));
+  hipLaunchKernelGGL((k_build_blocklist<kAttnQBlocks, false>), dim3(lists, parts), dim3(kBlThreads), 0, st, a);
+  return hipGetLastError();
 }
 
 hipError_t launch_attention(const vs_params& p, const void* q, const DcaArgs* dca, const void* k, const void* v,
@@ -1965,8 +2004,8 @@ hipError_t launch_attention(const vs_params& p, const void* q, const DcaArgs* dc
     const hipError_t e = attn_device_setup(&n_cu);
     if (e != hipSuccess) return e;
   }
-  int members = ((4 / kAttnQBlocks) * n_cu) / 8;   // resident workgroups per XCD
-  if (members < 1) members = 1;
+  const int members = attn_members(n_cu);
+  if (attn_listless(p, dense, cut, members)) a.ent = nullptr;
   a.n_split = cut.n_split;
   a.part_o = a.part_ml = nullptr;
   if (cut.queue && a.n_split > 1) {
@@ -2008,7 +2047,7 @@ hipError_t launch_attention(const vs_params& p, const void* q, const DcaArgs* dc
   // Below 256K keys the caches hold what the members of a group are apart, and one launch fills its own gaps: 2,400 rows at
   // 100K keys 3.44 ms against 3.52, 5,426 clustered ones at 33K 2.31 against 2.46.
   // Not where heads share tiles: the pace-keeping kernel takes one head per unit, with one list per head.
-  if (a.n_split > 1 && a.n_whole > 0 && a.pack == 1 && members == kRun && ceil_div(a.n_k, kBlock) >= kPaceBlocks) {
+  if (attn_paced(cut, a.n_k, members)) {
     keep_pace(a.n_whole);
     a.first_piece = a.n_whole;
   }
@@ -2088,8 +2127,7 @@ hipError_t launch_attention_batch(const vs_params& p, const vs_request* req, int
   int n_cu = 0;
   hipError_t e = attn_device_setup(&n_cu);
   if (e != hipSuccess) return e;
-  int members = ((4 / kAttnQBlocks) * n_cu) / 8;   // resident workgroups per XCD
-  if (members < 1) members = 1;
+  const int members = attn_members(n_cu);
   a.members = members; a.n_wg = 8 * members; a.n_full = 0; a.n_rem = 0;
   ListArgs l = {};
   l.s_budget = p.slash_budget;

@@ -44,6 +44,22 @@ def test_heads_that_share_a_tile_as_the_columns_let_them(blocks):
     test_heads_that_share_a_tile(7, 1, 128, 20, 5, blocks)
 
 
+# Dense calls of few pieces have no block list and no cleared counters: one, two and four heads per tile, one range and many, walks
+# of less and more than a batch of 64 entries, with a workspace of another call's bytes.
+@pytest.mark.parametrize("hq,hkv,d,c,s", [(4, 1, 64, 130, 64 * 130 + 5), (7, 1, 128, 65, 64 * 66), (8, 2, 128, 20, 64 * 129 + 3),
+                                          (6, 3, 64, 64, 64 * 63), (1, 1, 128, 300, 10), (5, 1, 128, 2, 61), (40, 8, 128, 129, 64 * 16 + 1)])
+def test_dense_calls_without_a_list(hq, hkv, d, c, s):
+    rng = np.random.default_rng(3050 + s + c)
+    q = rand_bf16(rng, (c, hq, d)); k = rand_bf16(rng, (s + c, hkv, d)); v = rand_bf16(rng, (s + c, hkv, d))
+    pb = oracle.Problem(hq, hkv, d, c, s, 1.0 / np.sqrt(d))
+    ck = chunk_of(pb)
+    for byte in (0, 0xA5):
+        ws = torch.full((max(256, vs.workspace_bytes(ck, vs.VS_WS_DENSE)),), byte, dtype=torch.uint8, device="cuda")
+        got = vs.dense_causal_prefill(ck, dev(q), dev(k), dev(v), want_lse=True, ws=ws)
+        torch.cuda.synchronize()
+        assert_attn_close(*got, *oracle.dense_attention(pb, q, k, v), f"dense {hq}/{hkv} C={c} s={s}")
+
+
 @pytest.mark.parametrize("c,s", [(66 * 128 - 5, 70), (66 * 128 - 5, 4100 * 64 + 1)])   # 528 units: 512 whole, 16 cut
 def test_whole_units_and_cut_ones(c, s):
     hq, hkv, d = 8, 1, 64
