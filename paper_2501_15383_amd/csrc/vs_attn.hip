@@ -1692,7 +1692,7 @@ size_t attn_sync_bytes(const vs_params& p) { return attn_counter_bytes(p) + attn
 // ones until none are left (a grid for as many units as there may be: 26 us for 1,500 requests none of which was cut, 4 now),
 // and up to four of a unit in a row where there are more than workgroups, because finding them takes as long as folding a few
 // pieces.  Bound by latency: a row's lanes read a reference and a sum each (all pieces' at once) while the first eight accumulators are
-// under way, and the weights go around by lane exchanges.  (Every lane reading all references, and after them everything again,
+// under way, and the weights go around through the LDS.  (Every lane reading all references, and after them everything again,
 // eight pieces at a time: 5 to 10 us for 40 to 60 pieces of a row, 3 to 6 so.)
 template <int D>
 constexpr int combine_parts() { return kTileRows / (1024 / D); }   // per unit
@@ -1701,6 +1701,7 @@ template <int D, bool BATCH = false>
 __global__ __launch_bounds__(256) void k_attn_combine(const AttnArgs a0) {
   constexpr int LR = D / 4;            // lanes per row
   constexpr int WPU = combine_parts<D>();
+  __shared__ __attribute__((aligned(16))) float w_s[256 / LR][kMaxSplit];
   const int d = 4 * (threadIdx.x % LR);
   const int n_tasks = (BATCH ? __builtin_amdgcn_readfirstlane(a0.plan[a0.n_req].cut) : a0.n_units - a0.n_whole) * WPU;
   int run = 1;   // consecutive parts of a unit
@@ -1730,26 +1731,27 @@ __global__ __launch_bounds__(256) void k_attn_combine(const AttnArgs a0) {
   const int64_t row = (int64_t)qt * kTileRows + 64 * t + il0 + (lrow & 31) - a.row_pad;
   if (row < 0 || row >= a.q_rows || h - g * a.group + th >= a.group) continue;
   const int hw = h + th;
-  const int64_t at = (int64_t)(BATCH ? e + a.first_slot : e) * kTileRows + lrow, step = (int64_t)n_fold * kTileRows;
+  const int64_t at = (int64_t)(BATCH ? e + a.first_slot : e) * kTileRows, step = (int64_t)n_fold * kTileRows;
   constexpr int U = 8, NB = kMaxSplit / LR;   // pieces whose accumulators are under way together; references per lane
-  static_assert(LR % U == 0, "the pieces of a batch have their weights in one register");
+  const float* const po = a.part_o + at * D + (lrow * D + d);   // (at: the same in every lane)
   f32x4 o[U];
   auto fetch = [&](int sp) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) o[u] = *(const f32x4*)(a.part_o + (at + step * (sp + u < a.n_split ? sp + u : a.n_split - 1)) * D + d);
+    for (int u = 0; u < U; ++u) o[u] = *(const f32x4*)(po + step * (sp + u < a.n_split ? sp + u : a.n_split - 1) * D);
   };
   fetch(0);
-  // lane x of the row: pieces x, LR + x, ...
-  const int lr = threadIdx.x % LR, lane0 = (threadIdx.x & 63) - lr;
-  float m[NB], w[NB], M = -INFINITY, L = 0.f;
+  // lane x of the row: pieces x, LR + x, ...; their weights wait in LDS (a row's lanes are of one wave)
+  const int lr = threadIdx.x % LR;
+  float* const ws = &w_s[threadIdx.x / LR][0];
+  float m[NB], l[NB], M = -INFINITY, L = 0.f;
 #pragma unroll
   for (int b = 0; b < NB; ++b) {
     m[b] = -INFINITY;
-    w[b] = 0.f;
+    l[b] = 0.f;
     if (b * LR < a.n_split && b * LR + lr < a.n_split) {
-      const float2 ml = *(const float2*)(a.part_ml + 2 * (at + step * (b * LR + lr)));
+      const float2 ml = *(const float2*)(a.part_ml + 2 * (at + lrow + step * (b * LR + lr)));
       m[b] = ml.x;
-      w[b] = ml.y;   // (the sum, until the weight is known)
+      l[b] = ml.y;
     }
     M = fmaxf(M, m[b]);
   }
@@ -1758,24 +1760,24 @@ __global__ __launch_bounds__(256) void k_attn_combine(const AttnArgs a0) {
   const float M0 = M == -INFINITY ? 0.f : M;
 #pragma unroll
   for (int b = 0; b < NB; ++b) {
-    const float l = w[b];
-    w[b] = __builtin_amdgcn_exp2f(m[b] - M0);   // (a piece without live keys: weight 0, and zeros in its slot)
-    L += l * w[b];
+    const float w = __builtin_amdgcn_exp2f(m[b] - M0);   // (a piece without live keys: weight 0, and zeros in its slot)
+    L += l[b] * w;
+    if (b * LR < a.n_split) ws[b * LR + lr] = w;         // (0 behind the last piece)
   }
 #pragma unroll
   for (int x = 1; x < LR; x <<= 1) L += __shfl_xor(L, x);
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma clang loop unroll(disable)
+  for (int sp = 0; sp < a.n_split; sp += U) {
+    if (sp > 0) fetch(sp);
 #pragma unroll
-  for (int b = 0; b < NB; ++b)
-    for (int sp = b * LR; sp < a.n_split && sp < (b + 1) * LR; sp += U) {
-      if (sp > 0) fetch(sp);
+    for (int u = 0; u < U; ++u) {
+      const float w = ws[sp + u];
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const float wu = __shfl(w[b], lane0 + sp - b * LR + u);   // (0 behind the last piece)
-#pragma unroll
-        for (int x = 0; x < 4; ++x) acc[x] += o[u][x] * wu;
-      }
+      for (int x = 0; x < 4; ++x) acc[x] += o[u][x] * w;
     }
+  }
   const float inv = L > 0.f ? 1.0f / L : 0.f;
 #pragma unroll
   for (int x = 0; x < 4; ++x) acc[x] *= inv;
