@@ -37,6 +37,7 @@ struct EstArgs {
   int32_t n_q_heads, n_kv_heads, group;
   int32_t wp;        // W'
   int32_t n_ranges;  // partials per head
+  int32_t fold;      // sweep B folds them itself (k_estimate_combine is not launched)
   int64_t q_len, n_k, p0;  // p0: position of window row 0
   float scale_log2;
 };
@@ -55,6 +56,7 @@ struct EstArgs {
 constexpr int kEstWaves = 16;    // waves per workgroup at most, and per compute unit: four per SIMD, 128 registers
 constexpr int est_waves(bool dca) { return dca ? 12 : kEstWaves; }   // (a block of several rotations needs the registers)
 constexpr int kEstLds = 160 << 10;
+constexpr int kEstFold = 16;     // ranges per wave that sweep B folds itself
 
 struct EstShape {
   int32_t heads;     // query heads per workgroup
@@ -328,6 +330,55 @@ __global__ __launch_bounds__(64 * est_waves(DCA)) void k_est_sums(const EstArgs 
 // instructions per row; the stores are the LDS's work.)
 // Offsets at the seam of two waves get their two parts by atomic adds (cleared by sweep A; x + y is commutative, so scores are
 // run-to-run identical).
+// (M, L) <- the partial (m, l) added
+__device__ __forceinline__ void est_fold(float& M, float& L, float m, float l) {
+  const float Mn = fmaxf(M, m);
+  const float Mu = (Mn == -INFINITY) ? 0.f : Mn;
+  L = L * __builtin_amdgcn_exp2f(M - Mu) + l * __builtin_amdgcn_exp2f(m - Mu);
+  M = Mn;
+}
+// lse2 of row r of head h from its folded partials (rows >= W' get +inf: their P is 0), and the caller's lse
+__device__ __forceinline__ void est_store_lse(const EstArgs& a, int h, int r, float M, float L, bool caller) {
+  const float l2 = M + __builtin_amdgcn_logf(L);
+  a.lse2[(int64_t)h * 64 + r] = r < a.wp ? l2 : INFINITY;
+  if (caller && a.lse_lastq && r < a.wp) a.lse_lastq[(int64_t)h * a.wp + r] = l2 * kLn2;
+}
+// The partials of a workgroup's heads folded by itself: waves / heads waves per head, every one a share of the ranges, and the
+// shares in order: the same numbers in every workgroup of the head, which all store them (scratch: 512 bytes per wave; ends with the
+// stores done and all waves past them).  A launch less, 4 to 5 us with its gap, for a trip to memory beside that of the window rows.
+__device__ __forceinline__ void est_fold_ranges(const EstArgs& a, const EstPlace& p, int waves, float2* scratch) {
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int shares = waves / p.n_h > 1 ? waves / p.n_h : 1, per = (a.n_ranges + shares - 1) / shares;
+  for (int x = wv; x < p.n_h * shares; x += waves) {   // (more heads than waves: one share each)
+    const int hd = x / shares, sh = x - hd * shares, r0 = sh * per, r1 = r0 + per < a.n_ranges ? r0 + per : a.n_ranges;
+    const float2* const pp = (const float2*)a.part + (int64_t)(p.h0 + hd) * a.n_ranges * 64 + lane;
+    float M = -INFINITY, L = 0.f;
+    constexpr int U = 8;
+#pragma clang loop unroll(disable)
+    for (int r = r0; r < r1; r += U) {
+      float2 v[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) v[u] = pp[64 * (r + u < r1 ? r + u : r1 - 1)];
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (r + u < r1) est_fold(M, L, v[u].x, v[u].y);
+    }
+    if (shares == 1) est_store_lse(a, p.h0 + hd, lane, M, L, p.blk == 0);
+    else scratch[64 * x + lane] = make_float2(M, L);
+  }
+  __syncthreads();
+  if (shares > 1 && wv < p.n_h) {
+    float M = -INFINITY, L = 0.f;
+    for (int sh = 0; sh < shares; ++sh) {
+      const float2 v = scratch[64 * (wv * shares + sh) + lane];
+      est_fold(M, L, v.x, v.y);
+    }
+    est_store_lse(a, p.h0 + wv, lane, M, L, p.blk == 0);
+  }
+  __threadfence_block();
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+}
 typedef __attribute__((address_space(3))) float lds_float;
 // lane 63's four floats to LDS byte address `at` + 16 * slot (all lanes are active before and after)
 __device__ __forceinline__ void est_store_last(uint32_t at, f32x4 v, const int slot) {
@@ -346,6 +397,11 @@ __global__ __launch_bounds__(64 * est_waves(DCA)) void k_est_scores(const EstArg
   float* const carry = (float*)(qs + (DCA ? 3 : 1) * z.heads * 64 * D) + wv * z.heads * 64;   // [wave][head][64]
   const int n_tiles = (int)((a.n_k + 63) >> 6);
   const int one_q = est_load_all_q<D, DCA>(a, z, p, n_tiles, qs);
+  const float* lse2 = a.lse2;
+  if (a.fold) {
+    est_fold_ranges(a, p, z.waves, (float2*)(qs + (DCA ? 3 : 1) * z.heads * 64 * D));   // (where the carries go later)
+    asm volatile("" : "+s"(lse2));   // (read through the scalar cache from here on, and not before)
+  }
   __syncthreads();
   const int t0 = (p.blk * z.waves + wv) * z.tiles, t1 = t0 + z.tiles < n_tiles ? t0 + z.tiles : n_tiles;
   float c = a.scale_log2;
@@ -373,7 +429,7 @@ __global__ __launch_bounds__(64 * est_waves(DCA)) void k_est_scores(const EstArg
         f32x16 lse_lo, lse_hi;
         auto load_lse = [&]() {
           typedef const __attribute__((address_space(4))) f32x16* const_ptr;
-          const const_ptr lse = (const_ptr)(a.lse2 + (int64_t)h * 64 + 32 * half);
+          const const_ptr lse = (const_ptr)(lse2 + (int64_t)h * 64 + 32 * half);
           lse_lo = lse[0];
           lse_hi = lse[1];
         };
@@ -474,26 +530,18 @@ __global__ __launch_bounds__(64 * est_waves(DCA)) void k_est_scores(const EstArg
 // fixed order, so the result is run-to-run identical.
 __global__ __launch_bounds__(1024) void k_estimate_combine(const EstArgs a) {
   const int h = blockIdx.x, r = threadIdx.x & 63, grp = threadIdx.x >> 6;
-  auto fold = [](float& M, float& L, float m, float l) {
-    const float Mn = fmaxf(M, m);
-    const float Mu = (Mn == -INFINITY) ? 0.f : Mn;
-    L = L * __builtin_amdgcn_exp2f(M - Mu) + l * __builtin_amdgcn_exp2f(m - Mu);
-    M = Mn;
-  };
   float M = -INFINITY, L = 0.f;
   for (int rg = grp; rg < a.n_ranges; rg += 16) {
     const float* pp = a.part + (((int64_t)h * a.n_ranges + rg) * 64 + r) * 2;
-    fold(M, L, pp[0], pp[1]);
+    est_fold(M, L, pp[0], pp[1]);
   }
   __shared__ float sm[16][64], sl[16][64];
   sm[grp][r] = M;
   sl[grp][r] = L;
   __syncthreads();
   if (grp != 0) return;
-  for (int g2 = 1; g2 < 16; ++g2) fold(M, L, sm[g2][r], sl[g2][r]);
-  const float l2 = M + __builtin_amdgcn_logf(L);
-  a.lse2[(int64_t)h * 64 + r] = r < a.wp ? l2 : INFINITY;
-  if (a.lse_lastq && r < a.wp) a.lse_lastq[(int64_t)h * a.wp + r] = l2 * kLn2;
+  for (int g2 = 1; g2 < 16; ++g2) est_fold(M, L, sm[g2][r], sl[g2][r]);
+  est_store_lse(a, h, r, M, L, true);
 }
 
 // The cut of a sweep, by the time it should take, in units of one row block of a wave with 16 waves on the compute unit
@@ -560,13 +608,18 @@ static hipError_t launch_est(const vs_params& p, EstArgs a, void* ws, hipStream_
   if (e != hipSuccess) return e;
   const EstShape za = est_shape_a(p, DCA), zb = est_shape_b(p, DCA);
   a.n_ranges = za.n_blocks;
+  // Sweep B folds up to 16 ranges per wave itself, in two trips to memory: 28 heads, 2,558 keys 23.0 us -> 20.6, 20,000 48.3 -> 46.7; 4 heads of
+  // 64, 8,192 keys 20.7 -> 15.6.  With seven heads per workgroup a wave has 30 and more, four trips: as long as the launch.
+  const int shares = zb.waves / zb.heads > 1 ? zb.waves / zb.heads : 1;
+  a.fold = a.n_ranges <= kEstFold * shares;
   a.part = (float*)ws;
   a.lse2 = (float*)((char*)ws + align_up((size_t)p.n_q_heads * a.n_ranges * 64 * 2 * sizeof(float), 256));
   auto grid = [&](const EstShape& z) { return dim3((unsigned)(ceil_div((int64_t)z.n_blocks * a.n_kv_heads, 8) * 8 * z.n_hb)); };
   const size_t q_bytes = (DCA ? 3 : 1) * 64 * D * sizeof(__bf16);
   hipLaunchKernelGGL((k_est_sums<D, DCA>), grid(za), dim3(64 * za.waves), za.heads * (q_bytes + (size_t)za.waves * 64 * (sizeof(float) + sizeof(uint16_t))), st, a, za, zb.tiles);
-  hipLaunchKernelGGL(k_estimate_combine, dim3(a.n_q_heads), dim3(1024), 0, st, a);
-  hipLaunchKernelGGL((k_est_scores<D, DCA>), grid(zb), dim3(64 * zb.waves), zb.heads * (q_bytes + (size_t)zb.waves * 64 * sizeof(float)), st, a, zb);
+  if (!a.fold) hipLaunchKernelGGL(k_estimate_combine, dim3(a.n_q_heads), dim3(1024), 0, st, a);
+  const size_t carry = (size_t)zb.heads * 64 * sizeof(float), fold = 64 * sizeof(float2);   // per wave
+  hipLaunchKernelGGL((k_est_scores<D, DCA>), grid(zb), dim3(64 * zb.waves), zb.heads * q_bytes + zb.waves * (carry > fold ? carry : fold), st, a, zb);
   return hipGetLastError();
 }
 
