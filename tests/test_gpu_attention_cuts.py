@@ -60,6 +60,24 @@ def test_dense_calls_without_a_list(hq, hkv, d, c, s):
         assert_attn_close(*got, *oracle.dense_attention(pb, q, k, v), f"dense {hq}/{hkv} C={c} s={s}")
 
 
+# Ranges of two and three key blocks, the last of them of one key, and lists shorter than the ranges that are cut from them.
+@pytest.mark.parametrize("hq,hkv,d", [(7, 1, 128), (4, 2, 64)])
+@pytest.mark.parametrize("c,n", [(3, 4 * 64 - 1), (3, 4 * 64), (33, 5 * 64 + 1), (65, 17 * 64), (140, 9 * 64 + 1)])
+def test_ranges_of_a_few_blocks(hq, hkv, d, c, n):
+    s = n - c
+    rng = np.random.default_rng(3080 + n + c)
+    q = rand_bf16(rng, (c, hq, d)); k = rand_bf16(rng, (n, hkv, d)); v = rand_bf16(rng, (n, hkv, d))
+    pb = oracle.Problem(hq, hkv, d, c, s, 1.0 / np.sqrt(d), vertical_budget=70, slash_budget=90, keep_first_cols=0, keep_local_band=0)
+    got = vs.dense_causal_prefill(chunk_of(pb), dev(q), dev(k), dev(v), want_lse=True)
+    torch.cuda.synchronize()
+    assert_attn_close(*got, *oracle.dense_attention(pb, q, k, v), f"dense {hq}/{hkv} C={c} n={n}")
+    for nv, ns in ((70, 3), (1, 0), (0, 1)):
+        sets = _rand_sets(rng, pb, min(nv, n), ns)
+        got = vs.sparse_attn_prefill(chunk_of(pb), dev(q), dev(k), dev(v), *[_t(x) for x in sets], want_lse=True)
+        torch.cuda.synchronize()
+        assert_attn_close(*got, *oracle.sparse_attention(pb, q, k, v, *sets), f"sparse {hq}/{hkv} C={c} n={n} {nv} columns {ns} offsets")
+
+
 @pytest.mark.parametrize("c,s", [(66 * 128 - 5, 70), (66 * 128 - 5, 4100 * 64 + 1)])   # 528 units: 512 whole, 16 cut
 def test_whole_units_and_cut_ones(c, s):
     hq, hkv, d = 8, 1, 64
