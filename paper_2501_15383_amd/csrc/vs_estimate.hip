@@ -179,17 +179,19 @@ __device__ __forceinline__ void est_product(const __bf16* qs, int x, int lane, M
 }
 
 // Sweep A: (reference, sum) of every window row over the workgroup's keys.  K Q^T: a lane owns a query row (32 half + lane % 32
-// of the head) and half of the keys.  A row's reference is the largest score of the wave's first tile, cut to the upper half of its
-// bits, and stays until a tile's sum of 32 probabilities goes past 2^8 (first tiles and such tiles take the exact way: the largest
-// score first).  So there is no maximum in the steady step, and the state of a head is 64 sums and 64 half-words, small enough
-// for seven heads beside their rows in LDS: K goes by once.
+// of the head) and half of the keys.  A row's reference is the largest score of the wave's first tile (base 2), an eighth of it
+// kept as a half-word, and stays until a tile's sum of 32 probabilities goes past 2^8 (first tiles and such tiles take the exact way:
+// the largest score first).  So there is no maximum in the steady step, and the state of a head is 64 sums and 64 half-words, small
+// enough for seven heads beside their rows in LDS: K goes by once.  An eighth, because a reference rounded to 11 bits is then within
+// 2^6 of scores up to 2^18, so that no probability overflows and none that counts is lost: there fp32 scores are off by 2^-6 themselves.
+// (The upper half of a float was off by up to 2^7 from 2^14 on: sums of infinity or nothing.)
 template <int D, bool DCA>
 __global__ __launch_bounds__(64 * est_waves(DCA)) void k_est_sums(const EstArgs a, const EstShape z, const int tiles_b) {
   constexpr int DSTEPS = D / 16;
   extern __shared__ __attribute__((aligned(16))) unsigned char est_lds[];
   __bf16* const qs = (__bf16*)est_lds;
   float* const sums = (float*)(qs + (DCA ? 3 : 1) * z.heads * 64 * D);         // [wave][head][64]
-  uint16_t* const refs = (uint16_t*)(sums + z.waves * z.heads * 64);           // the same, upper halves of floats
+  _Float16* const refs = (_Float16*)(sums + z.waves * z.heads * 64);           // the same, an eighth of each
   const EstPlace p = est_place(a, z);
   if (!p.ok) return;
   const int tid = threadIdx.x, lane = tid & 63, hh = lane >> 5;
@@ -197,11 +199,11 @@ __global__ __launch_bounds__(64 * est_waves(DCA)) void k_est_sums(const EstArgs 
   const int n_tiles = (int)((a.n_k + 63) >> 6);
   const int one_q = est_load_all_q<D, DCA>(a, z, p, n_tiles, qs);
   float* const my_sum = sums + wv * z.heads * 64;
-  uint16_t* const my_ref = refs + wv * z.heads * 64;
-  auto ref_of = [](uint32_t w) { return __uint_as_float(w << 16); };
+  _Float16* const my_ref = refs + wv * z.heads * 64;
+  auto ref_of = [](_Float16 w) { return 8.f * (float)w; };
   for (int x = 0; x < p.n_h; ++x) {
     my_sum[64 * x + lane] = 0.f;
-    my_ref[64 * x + lane] = 0xFF80u;   // -inf
+    my_ref[64 * x + lane] = (_Float16)-INFINITY;
   }
   __syncthreads();
   const int t0 = (p.blk * z.waves + wv) * z.tiles, t1 = t0 + z.tiles < n_tiles ? t0 + z.tiles : n_tiles;
@@ -236,7 +238,7 @@ __global__ __launch_bounds__(64 * est_waves(DCA)) void k_est_sums(const EstArgs 
             d[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[1][k], qf, d[1], 0, 0, 0);
           });
         };
-        uint16_t* const ref = my_ref + 64 * x + 32 * half + (lane & 31);
+        _Float16* const ref = my_ref + 64 * x + 32 * half + (lane & 31);
         const float m = ref_of(*ref);
         if constexpr (DCA) {
           const int row = 32 * half + (lane & 31), near = dca.of(row, 63), far = dca.of(row, 0);
@@ -291,12 +293,12 @@ __global__ __launch_bounds__(64 * est_waves(DCA)) void k_est_sums(const EstArgs 
           for (int e = 1; e < 16; ++e) mx = fmaxf(fmaxf(mx, s[0][e]), s[1][e]);
           mx = fmaxf(mx, __shfl_xor(mx, 32));
           // (-inf stays -inf; rows without a key so far take 0 in its place)
-          const uint32_t w = __float_as_uint(fmaxf(m, mx * a.scale_log2)) >> 16;
+          const _Float16 w = (_Float16)(0.125f * fmaxf(m, mx * a.scale_log2));
           const float m_new = ref_of(w), m_use = m_new == -INFINITY ? 0.f : m_new;
           if (lane < 32) {
             float* const l = my_sum + 64 * x + 32 * half + lane;
             *l *= __builtin_amdgcn_exp2f(m - m_use);
-            *ref = (uint16_t)w;
+            *ref = w;
           }
           part[1] = sum(m_use);
         }
@@ -589,7 +591,7 @@ static EstShape est_shape(const vs_params& p, int most, int head_bytes, bool dca
   }
   return best;
 }
-static EstShape est_shape_a(const vs_params& p, bool dca) { return est_shape(p, dca ? 3 : 7, 64 * (sizeof(float) + sizeof(uint16_t)), dca); }
+static EstShape est_shape_a(const vs_params& p, bool dca) { return est_shape(p, dca ? 3 : 7, 64 * (sizeof(float) + sizeof(_Float16)), dca); }
 static EstShape est_shape_b(const vs_params& p, bool dca) { return est_shape(p, dca ? 3 : 7, 64 * sizeof(float), dca); }
 
 size_t estimate_ws_bytes(const vs_params& p) {
@@ -616,7 +618,7 @@ static hipError_t launch_est(const vs_params& p, EstArgs a, void* ws, hipStream_
   a.lse2 = (float*)((char*)ws + align_up((size_t)p.n_q_heads * a.n_ranges * 64 * 2 * sizeof(float), 256));
   auto grid = [&](const EstShape& z) { return dim3((unsigned)(ceil_div((int64_t)z.n_blocks * a.n_kv_heads, 8) * 8 * z.n_hb)); };
   const size_t q_bytes = (DCA ? 3 : 1) * 64 * D * sizeof(__bf16);
-  hipLaunchKernelGGL((k_est_sums<D, DCA>), grid(za), dim3(64 * za.waves), za.heads * (q_bytes + (size_t)za.waves * 64 * (sizeof(float) + sizeof(uint16_t))), st, a, za, zb.tiles);
+  hipLaunchKernelGGL((k_est_sums<D, DCA>), grid(za), dim3(64 * za.waves), za.heads * (q_bytes + (size_t)za.waves * 64 * (sizeof(float) + sizeof(_Float16))), st, a, za, zb.tiles);
   if (!a.fold) hipLaunchKernelGGL(k_estimate_combine, dim3(a.n_q_heads), dim3(1024), 0, st, a);
   const size_t carry = (size_t)zb.heads * 64 * sizeof(float), fold = 64 * sizeof(float2);   // per wave
   hipLaunchKernelGGL((k_est_scores<D, DCA>), grid(zb), dim3(64 * zb.waves), zb.heads * q_bytes + zb.waves * (carry > fold ? carry : fold), st, a, zb);

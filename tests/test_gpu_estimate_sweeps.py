@@ -74,3 +74,23 @@ def test_scores_that_outrun_the_reference_of_a_wave(hq, hkv, d, c, s, dca, ramp)
     # per rounding, of which there are three (the score, its product with the scale, the lse): 3 * 2^-18 * ln 2 = 8e-6 for a
     # single probability that all weight lies on, and as much again for the sum that the lse comes from.
     _check(hq, hkv, d, c, s, 4400, dca, ramp, norm=2e-5)
+
+
+@pytest.mark.parametrize("hq,hkv,c,s", [(4, 2, 64, 2000), (8, 8, 40, 120000)])
+def test_scores_of_tens_of_thousands(hq, hkv, c, s):
+    # Base-2 scores of about -2^16 to 2^16, every second window row below zero throughout.  The products are whole numbers below 2^24,
+    # so that scores are exact but for their factor; what is left is the rounding of an lse below 2^17, 2^-8 each when it is made and
+    # when its maximum's product with the factor is: 2^-7 * ln 2 of a probability, and 2^-23 of the lse.
+    rng = np.random.default_rng(4500)
+    u = rng.choice([-64, 64], (1, 1, 64))
+    k = u + rng.integers(-60, 61, (s + c, hkv, 64))
+    q = u * np.where(np.arange(c) % 2, -1, 1)[:, None, None] + rng.integers(-60, 61, (c, hq, 64))
+    k, q = (host_u16(torch.from_numpy(x.astype(np.float32)).bfloat16()) for x in (k, q))
+    pb = oracle.Problem(hq, hkv, 64, c, s, 0.125)
+    rvs, rss, rlse = oracle.estimate(pb, q, k)
+    assert rlse.min() < -2.0 ** 13 and rlse.max() > 2.0 ** 15
+    vsc, ssc, lse = vs.estimate(chunk_of(pb), dev(q), dev(k), want_lse=True)
+    torch.cuda.synchronize()
+    np.testing.assert_allclose(f64(lse).reshape(rlse.shape), rlse, rtol=2.0 ** -21)
+    for got, ref in ((vsc, rvs), (ssc, rss)):
+        np.testing.assert_allclose(f64(got), ref, rtol=2.0 ** -6, atol=1e-7)
