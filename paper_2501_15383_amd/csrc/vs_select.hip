@@ -253,23 +253,12 @@ template <typename ForEach>
 __device__ __forceinline__ void radix_kth(SelShared& sh, ForEach&& for_each, uint32_t kp, uint32_t lo, uint32_t hi, uint32_t& T,
                                           uint32_t& need_eq) {
   SelDigits s = sel_digits(kp, lo, hi);
-  if (threadIdx.x == 0) sh.few = 0;
   while (s.shift > 0) {                       // uniform: at most three times
     sel_digit(sh, for_each, lo, s);
     if (s.in_bin == kSelAtLo) break;
     if (s.krem == s.in_bin) {   // the whole bin is wanted: everything above the key below it
       T = lo + (s.prefix << s.shift) - 1u;
       need_eq = 0;
-      return;
-    }
-    if (s.shift > 0 && s.in_bin <= kSelFew) {   // few keys left: one pass lists them, in place of a digit
-      // or two (28 heads, 300,001 scores 54.8 us -> 54.3, two runs differ by 0.1)
-      // (not the bin of lo, which counts as more: the list would have the keys equal to lo)
-      for_each([&](uint32_t key, bool valid) {
-        if (valid && ((key - lo) >> s.shift) == s.prefix) sh.hist[atomicAdd(&sh.few, 1u)] = key;
-      });
-      __syncthreads();
-      sel_few(sh, s.in_bin, s.krem, T, need_eq);
       return;
     }
   }

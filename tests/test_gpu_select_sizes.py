@@ -85,17 +85,3 @@ def test_rows_in_registers_at_every_length(n):
             want = (*_want(vsc, bv, 1), *_want(ssc, bs, keep))
             for a, b, nm in zip(vs.select(ck, vsc, ssc), want, ("v_idx", "v_cnt", "s_idx", "s_cnt")):
                 assert torch.equal(a, b), f"{nm}: n {n}, budgets {bv} / {bs}"
-
-
-@pytest.mark.parametrize("each", [1, 20, 64])
-@pytest.mark.parametrize("n,bv,bs", [(49153, 500, 5000), (200001, 1000, 12000)])
-def test_long_rows_whose_threshold_lies_among_few(n, bv, bs, each):
-    # every score about `each` times: the threshold's bin has up to and beyond the 64 keys that are listed, by row
-    g = torch.Generator(device="cuda:0").manual_seed(400 + n + each)
-    hq = 40
-    vsc, ssc = (torch.randint(1, n // each + 2, (hq, n), generator=g, device="cuda:0").float() / n for _ in range(2))
-    ck = vs.Chunk(hq, 1, 128, 64, n - 64, 0.1, vertical_budget=bv, slash_budget=bs, keep_first_cols=1, keep_local_band=64)
-    want = (*_want(vsc, bv, 1), *_want(ssc, bs, 64))
-    for sets in (vs.select(ck, vsc, ssc), vs.select_static(ck, vsc, ssc, vs.alloc_index_sets(ck, vsc.device))):
-        for a, b, nm in zip(sets, want, ("v_idx", "v_cnt", "s_idx", "s_cnt")):
-            assert torch.equal(a, b), f"{nm}: n {n}, budgets {bv} / {bs}, {each} of each"
