@@ -34,6 +34,7 @@ struct EstArgs {
   float* lse_lastq;  // optional, natural log
   float* part;       // [Hq][n_ranges][64][2]  (max, sum) in the base-2 scaled domain
   float* lse2;       // [Hq][64] base-2 scaled lse (+inf for rows >= W')
+  float* far;        // [Hq][n_ranges][waves][64]  references of sweep A past kEstNear (written and read only where there are any)
   int32_t n_q_heads, n_kv_heads, group;
   int32_t wp;        // W'
   int32_t n_ranges;  // partials per head
@@ -57,6 +58,7 @@ constexpr int kEstWaves = 16;    // waves per workgroup at most, and per compute
 constexpr int est_waves(bool dca) { return dca ? 12 : kEstWaves; }   // (a block of several rotations needs the registers)
 constexpr int kEstLds = 160 << 10;
 constexpr int kEstFold = 16;     // ranges per wave that sweep B folds itself
+constexpr float kEstNear = 131072.f;   // references of sweep A (base 2) that an eighth in a half-word stands for
 
 struct EstShape {
   int32_t heads;     // query heads per workgroup
@@ -183,8 +185,10 @@ __device__ __forceinline__ void est_product(const __bf16* qs, int x, int lane, M
 // kept as a half-word, and stays until a tile's sum of 32 probabilities goes past 2^8 (first tiles and such tiles take the exact way:
 // the largest score first).  So there is no maximum in the steady step, and the state of a head is 64 sums and 64 half-words, small
 // enough for seven heads beside their rows in LDS: K goes by once.  An eighth, because a reference rounded to 11 bits is then within
-// 2^6 of scores up to 2^18, so that no probability overflows and none that counts is lost: there fp32 scores are off by 2^-6 themselves.
-// (The upper half of a float was off by up to 2^7 from 2^14 on: sums of infinity or nothing.)
+// 2^5 of scores up to 2^17, so that no probability overflows and none that counts is lost.  (The upper half of a float was off by up
+// to 2^7 from 2^14 on: sums of infinity or nothing; and past 2^18 so is the eighth.)  A reference past 2^17 is kept whole, in
+// memory, and its half-word is a NaN: the sum against it is one too, and so the row takes the exact way in every tile, as a running
+// maximum: any score is as good as fp32 makes it.
 template <int D, bool DCA>
 __global__ __launch_bounds__(64 * est_waves(DCA)) void k_est_sums(const EstArgs a, const EstShape z, const int tiles_b) {
   constexpr int DSTEPS = D / 16;
@@ -201,6 +205,11 @@ __global__ __launch_bounds__(64 * est_waves(DCA)) void k_est_sums(const EstArgs 
   float* const my_sum = sums + wv * z.heads * 64;
   _Float16* const my_ref = refs + wv * z.heads * 64;
   auto ref_of = [](_Float16 w) { return 8.f * (float)w; };
+  auto far_of = [&](int x, int w) -> float* {   // of wave w: the rows of head x
+    return a.far + (((int64_t)(p.h0 + x) * z.n_blocks + p.blk) * z.waves + w) * 64;
+  };
+  __shared__ uint32_t far_s;   // a reference in memory
+  if (tid == 0) far_s = 0u;
   for (int x = 0; x < p.n_h; ++x) {
     my_sum[64 * x + lane] = 0.f;
     my_ref[64 * x + lane] = (_Float16)-INFINITY;
@@ -239,7 +248,7 @@ __global__ __launch_bounds__(64 * est_waves(DCA)) void k_est_sums(const EstArgs 
           });
         };
         _Float16* const ref = my_ref + 64 * x + 32 * half + (lane & 31);
-        const float m = ref_of(*ref);
+        float m = ref_of(*ref);
         if constexpr (DCA) {
           const int row = 32 * half + (lane & 31), near = dca.of(row, 63), far = dca.of(row, 0);
           product(near, s);
@@ -293,8 +302,22 @@ __global__ __launch_bounds__(64 * est_waves(DCA)) void k_est_sums(const EstArgs 
           for (int e = 1; e < 16; ++e) mx = fmaxf(fmaxf(mx, s[0][e]), s[1][e]);
           mx = fmaxf(mx, __shfl_xor(mx, 32));
           // (-inf stays -inf; rows without a key so far take 0 in its place)
-          const _Float16 w = (_Float16)(0.125f * fmaxf(m, mx * a.scale_log2));
-          const float m_new = ref_of(w), m_use = m_new == -INFINITY ? 0.f : m_new;
+          float top = fmaxf(m, mx * a.scale_log2);
+          _Float16 w = (_Float16)(0.125f * top);
+          float m_new = ref_of(w);
+          if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(fabsf(top) <= kEstNear) || m != m) != 0, 0)) {
+            int hd = x, row = 32 * half + (lane & 31);
+            asm volatile("" : "+s"(hd), "+v"(row));   // (the address is made here, not held through the loop)
+            float* const at = far_of(hd, wv) + row;
+            if (m != m) m = *at;   // (as the lane itself stored it: both of a row store the same)
+            top = fmaxf(m, top);
+            if (fabsf(top) > kEstNear && top != -INFINITY) {
+              *at = m_new = top;
+              w = (_Float16)NAN;
+              far_s = 1u;
+            }
+          }
+          const float m_use = m_new == -INFINITY ? 0.f : m_new;
           if (lane < 32) {
             float* const l = my_sum + 64 * x + 32 * half + lane;
             *l *= __builtin_amdgcn_exp2f(m - m_use);
@@ -313,9 +336,21 @@ __global__ __launch_bounds__(64 * est_waves(DCA)) void k_est_sums(const EstArgs 
   // the waves folded in a fixed order: one partial per (head, workgroup, row)
   for (int x = tid; x < 64 * p.n_h; x += blockDim.x) {
     float M = -INFINITY, L = 0.f;
-    for (int w = 0; w < z.waves; ++w) M = fmaxf(M, ref_of(refs[w * z.heads * 64 + x]));
-    const float Mu = (M == -INFINITY) ? 0.f : M;
-    for (int w = 0; w < z.waves; ++w) L += sums[w * z.heads * 64 + x] * __builtin_amdgcn_exp2f(ref_of(refs[w * z.heads * 64 + x]) - Mu);
+    if (__builtin_expect(far_s != 0u, 0)) {
+      auto ref_at = [&](int w) {
+        const float m = ref_of(refs[w * z.heads * 64 + x]);
+        return m != m ? far_of(x >> 6, w)[x & 63] : m;
+      };
+#pragma clang loop unroll(disable)
+      for (int w = 0; w < z.waves; ++w) M = fmaxf(M, ref_at(w));
+      const float Mu = (M == -INFINITY) ? 0.f : M;
+#pragma clang loop unroll(disable)
+      for (int w = 0; w < z.waves; ++w) L += sums[w * z.heads * 64 + x] * __builtin_amdgcn_exp2f(ref_at(w) - Mu);
+    } else {
+      for (int w = 0; w < z.waves; ++w) M = fmaxf(M, ref_of(refs[w * z.heads * 64 + x]));
+      const float Mu = (M == -INFINITY) ? 0.f : M;
+      for (int w = 0; w < z.waves; ++w) L += sums[w * z.heads * 64 + x] * __builtin_amdgcn_exp2f(ref_of(refs[w * z.heads * 64 + x]) - Mu);
+    }
     float* const pp = a.part + (((int64_t)(p.h0 + (x >> 6)) * a.n_ranges + p.blk) * 64 + (x & 63)) * 2;
     pp[0] = M;
     pp[1] = L;
@@ -595,9 +630,12 @@ static EstShape est_shape_a(const vs_params& p, bool dca) { return est_shape(p, 
 static EstShape est_shape_b(const vs_params& p, bool dca) { return est_shape(p, dca ? 3 : 7, 64 * sizeof(float), dca); }
 
 size_t estimate_ws_bytes(const vs_params& p) {
-  const int64_t n = est_shape_a(p, false).n_blocks, n_dca = est_shape_a(p, true).n_blocks;   // (the size serves either call)
-  return align_up((size_t)p.n_q_heads * (n > n_dca ? n : n_dca) * 64 * 2 * sizeof(float), 256) +
-         align_up((size_t)p.n_q_heads * 64 * sizeof(float), 256);
+  auto bytes = [&](const EstShape& z) {   // (partial, lse, far references)
+    const size_t rows = (size_t)p.n_q_heads * 64;
+    return rows * z.n_blocks * 2 * sizeof(float) + rows * sizeof(float) + rows * z.n_blocks * z.waves * sizeof(float);
+  };
+  const size_t n = bytes(est_shape_a(p, false)), n_dca = bytes(est_shape_a(p, true));   // (the size serves either call)
+  return n > n_dca ? n : n_dca;
 }
 
 template <int D, bool DCA>
@@ -615,7 +653,8 @@ static hipError_t launch_est(const vs_params& p, EstArgs a, void* ws, hipStream_
   const int shares = zb.waves / zb.heads > 1 ? zb.waves / zb.heads : 1;
   a.fold = a.n_ranges <= kEstFold * shares;
   a.part = (float*)ws;
-  a.lse2 = (float*)((char*)ws + align_up((size_t)p.n_q_heads * a.n_ranges * 64 * 2 * sizeof(float), 256));
+  a.lse2 = a.part + (size_t)p.n_q_heads * a.n_ranges * 64 * 2;   // (every part a multiple of 256 bytes)
+  a.far = a.lse2 + (size_t)p.n_q_heads * 64;
   auto grid = [&](const EstShape& z) { return dim3((unsigned)(ceil_div((int64_t)z.n_blocks * a.n_kv_heads, 8) * 8 * z.n_hb)); };
   const size_t q_bytes = (DCA ? 3 : 1) * 64 * D * sizeof(__bf16);
   hipLaunchKernelGGL((k_est_sums<D, DCA>), grid(za), dim3(64 * za.waves), za.heads * (q_bytes + (size_t)za.waves * 64 * (sizeof(float) + sizeof(_Float16))), st, a, za, zb.tiles);

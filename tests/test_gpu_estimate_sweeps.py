@@ -94,3 +94,38 @@ def test_scores_of_tens_of_thousands(hq, hkv, c, s):
     np.testing.assert_allclose(f64(lse).reshape(rlse.shape), rlse, rtol=2.0 ** -21)
     for got, ref in ((vsc, rvs), (ssc, rss)):
         np.testing.assert_allclose(f64(got), ref, rtol=2.0 ** -6, atol=1e-7)
+
+
+@pytest.mark.parametrize("scale", [0.68, 1.0, 2.9])   # the largest base-2 scores lie past 2^17, 2^18 and 2^20
+@pytest.mark.parametrize("every", [1, 2, 3])
+@pytest.mark.parametrize("hq,hkv,d,c,s,dca", [(4, 2, 64, 64, 2000, None), (8, 8, 64, 40, 120000, None), (7, 1, 128, 64, 9000, None),
+                                              (8, 8, 64, 40, 120000, (32768, 2048))])
+def test_scores_past_the_range_of_a_half_word(hq, hkv, d, c, s, dca, every, scale):
+    # As above, with factors that take the scores on; the keys of every 2nd or 3rd tile of 64 have only scores of a few
+    # thousandths of that, so that the largest score of a row goes up past 2^17, and of the rows below zero back from there, on the
+    # way through a wave's tiles.  Roundings as above: a probability is off by a factor of 2^(2^(b - 23)) for scores of 2^b.
+    rng = np.random.default_rng(4600)
+    u = rng.choice([-64, 64], (1, 1, 64))
+    far = (np.arange(s + c) // 64 % 3 % every == 0)[:, None, None]
+    k = np.zeros((s + c, hkv, d))
+    k[..., :64] = far * u + rng.integers(-60, 61, (s + c, hkv, 64)) * np.where(far, 1, 1 / 64)
+    qs = []
+    for _ in range(3 if dca else 1):
+        q = np.zeros((c, hq, d))
+        q[..., :64] = u * np.where(np.arange(c) % 2, -1, 1)[:, None, None] + rng.integers(-60, 61, (c, hq, 64))
+        qs.append(q)
+    k, *qs = (host_u16(torch.from_numpy(x.astype(np.float32)).bfloat16()) for x in (k, *qs))
+    pb = oracle.Problem(hq, hkv, d, c, s, scale)
+    rvs, rss, rlse = oracle.estimate(pb, qs[0], k, dca=oracle.Dca(*dca, *qs[1:]) if dca else None)
+    top = rlse.max() * np.log2(np.e)
+    assert top > 2.0 ** {0.68: 17, 1.0: 18, 2.9: 20}[scale]
+    ck = chunk_of(pb)
+    n = vs.workspace_bytes(ck, vs.VS_WS_ESTIMATE)
+    ws = torch.full((n + 4096,), 0xA5, dtype=torch.uint8, device="cuda")
+    vsc, ssc, lse = vs.estimate(ck, dev(qs[0]), dev(k), want_lse=True, ws=ws[:n], dca=(*map(dev, qs[1:]), *dca) if dca else None)
+    torch.cuda.synchronize()
+    assert bool((ws[n:] == 0xA5).all())
+    # (rows below zero may end near it: there the rounding is that of their own largest products)
+    np.testing.assert_allclose(f64(lse).reshape(rlse.shape), rlse, rtol=2.0 ** -21, atol=2.0 ** -10)
+    for got, ref in ((vsc, rvs), (ssc, rss)):
+        np.testing.assert_allclose(f64(got), ref, rtol=2.0 ** (np.floor(np.log2(top)) - 22), atol=1e-7)
