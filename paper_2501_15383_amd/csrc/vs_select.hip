@@ -34,13 +34,18 @@ namespace vs {
 
 constexpr int kSelThreads = 1024;
 constexpr int kSelWaves = kSelThreads / 64;
-constexpr int kSelRegKeys = 48 * kSelThreads;  // longest row that stays in registers (128 of them; 44,000 scores, 28 heads: 25 us,
-                                               // 38 with the row's candidates in LDS; three launches 39 at 49,153)
+constexpr int kSelRegKeys = 48 * kSelThreads;  // longest row that stays in registers (44,000 scores, 28 heads: 21 us, 35 with the
+                                               // row's candidates in LDS; three launches 39 at 49,153.  Scores of 2 to 25 values and
+                                               // budgets of hundreds take 28 to 39 so, 24 to 33 with candidates)
 constexpr int kSelCand = 16384;                // longest list of candidates (128 KB of LDS)
 constexpr int kSelSlice = 2048;                // scores per wave of the filter (one slice each)
 constexpr int kSelFilterThreads = 256;
 constexpr int kSelStep = 8;                    // scores per lane and step where the row is read again and again
 constexpr int kSelBins = 2048;
+// Counters per bin of rows in registers.  Lanes that share a bin queue for it, the longer the row the longer: 28 heads, of two values
+// 44,000 scores 74 us with one, 38 with four; 36,000 of an estimate 17.9 and 17.6; of up to 16 per lane four cost 0.15 us per row more to
+// clear and add up.  (Eight lie in too few banks: 20.8.)  A row in memory has its LDS full of candidates.
+constexpr int sel_copies(int kpt) { return kpt > 16 ? 4 : 1; }
 // control block of a row whose slices go through the digits together, in 32-bit words
 constexpr int kSliceMax = 64;                  // slices of a row at most
 constexpr int kWHist = 0;                      // [4][256] histogram of every digit
@@ -121,19 +126,22 @@ __host__ __device__ inline float sel_sample_rank(float k, float n, float samples
   return mu + 4.5f * sqrtf(mu) + 4.f;
 }
 
+// R: counters per bin (lane x adds to the (x % R)-th; a power of two)
+template <int R>
 struct SelShared {
-  alignas(16) uint32_t hist[kSelBins];
-  uint32_t wsum[kSelWaves];
+  alignas(16) uint32_t hist[R * kSelBins];
+  alignas(16) uint32_t wsum[kSelWaves];          // (read four words at a time: 0.35 us of a row's 7 to 10)
+  alignas(16) uint32_t wtot[2][kSelWaves][2];
+  alignas(16) uint32_t wmin[kSelWaves], wmax[kSelWaves];
   uint32_t digit, rest, in_bin;
-  uint32_t wtot[2][kSelWaves][2];
-  uint32_t wmin[kSelWaves], wmax[kSelWaves];
   int32_t first[kSelWaves + 1];
   uint32_t few, few_T, few_need;   // keys of the last bin listed so far (in hist), and what they decide
   uint32_t extra[kSelWaves];       // of a wave's keys in that bin, those taken
 };
 
 // smallest and largest of the threads' keys
-__device__ __forceinline__ void sel_range(SelShared& sh, uint32_t lo, uint32_t hi, uint32_t& all_lo, uint32_t& all_hi) {
+template <int R>
+__device__ __forceinline__ void sel_range(SelShared<R>& sh, uint32_t lo, uint32_t hi, uint32_t& all_lo, uint32_t& all_hi) {
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
 #pragma unroll
   for (int d = 1; d < 64; d <<= 1) {
@@ -171,24 +179,28 @@ __device__ __forceinline__ SelDigits sel_digits(uint32_t kp, uint32_t lo, uint32
   d.shift = 32 - __clz((int)(hi - lo) | 1);
   return d;
 }
-template <typename ForEach>
-__device__ __forceinline__ void sel_digit(SelShared& sh, ForEach&& for_each, uint32_t lo, SelDigits& s) {
+template <int R, typename ForEach>
+__device__ __forceinline__ void sel_digit(SelShared<R>& sh, ForEach&& for_each, uint32_t lo, SelDigits& s) {
   static_assert(kSelBins == 2 * kSelThreads, "two bins per thread");
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int width = s.shift < 11 ? s.shift : 11, sh0 = s.shift - width;
-  const uint32_t dmask = (1u << width) - 1u;
+  const uint32_t dmask = (1u << width) - 1u, copy = (uint32_t)lane & (R - 1);
   asm volatile("" : "+v"(lo));   // (key - lo is made again for every digit, not kept beside the keys)
-  sh.hist[tid] = 0;
-  sh.hist[kSelThreads + tid] = 0;
+#pragma unroll
+  for (int x = 0; x < 2 * R; ++x) sh.hist[x * kSelThreads + tid] = 0;
   __syncthreads();
   for_each([&](uint32_t key, bool valid) {
     const uint32_t d = key - lo;
-    if (valid && d != 0u && (s.first || (d >> s.shift) == s.prefix)) atomicAdd(&sh.hist[(d >> sh0) & dmask], 1u);
+    if (valid && d != 0u && (s.first || (d >> s.shift) == s.prefix)) atomicAdd(&sh.hist[R * ((d >> sh0) & dmask) + copy], 1u);
   });
   __syncthreads();
   // bins from the top: thread t takes the bins 2047 - 2 t and 2046 - 2 t
-  const uint32_t c0 = sh.hist[kSelBins - 1 - 2 * tid];
-  uint32_t c1 = sh.hist[kSelBins - 2 - 2 * tid];
+  uint32_t c0 = 0, c1 = 0;
+#pragma unroll
+  for (int x = 0; x < R; ++x) {
+    c0 += sh.hist[R * (kSelBins - 1 - 2 * tid) + x];
+    c1 += sh.hist[R * (kSelBins - 2 - 2 * tid) + x];
+  }
   const bool has_lo = tid == kSelThreads - 1 && s.prefix == 0;   // the bin of lo: what the others leave
   const uint32_t but_lo = c1;
   if (has_lo) c1 = 0x7FFFFFFFu;
@@ -224,7 +236,8 @@ __device__ __forceinline__ void sel_digit(SelShared& sh, ForEach&& for_each, uin
 // The krem-th largest of the c <= kSelFew keys in sh.hist, for every thread.  (They are compared with one another: the bin that
 // the first digit leaves of 6,000 to 48,000 scores has a few dozen, and a second and third digit took 1.2 us each.)
 constexpr uint32_t kSelFew = 64;
-__device__ __forceinline__ void sel_few(SelShared& sh, uint32_t c, uint32_t krem, uint32_t& T, uint32_t& need_eq) {
+template <int R>
+__device__ __forceinline__ void sel_few(SelShared<R>& sh, uint32_t c, uint32_t krem, uint32_t& T, uint32_t& need_eq) {
   if (threadIdx.x < c) {
     const uint32_t mine = sh.hist[threadIdx.x];
     uint32_t above = 0, equal = 0;
@@ -249,8 +262,8 @@ __device__ __forceinline__ void sel_few(SelShared& sh, uint32_t c, uint32_t krem
   T = sh.few_T;
   need_eq = sh.few_need;
 }
-template <typename ForEach>
-__device__ __forceinline__ void radix_kth(SelShared& sh, ForEach&& for_each, uint32_t kp, uint32_t lo, uint32_t hi, uint32_t& T,
+template <int R, typename ForEach>
+__device__ __forceinline__ void radix_kth(SelShared<R>& sh, ForEach&& for_each, uint32_t kp, uint32_t lo, uint32_t hi, uint32_t& T,
                                           uint32_t& need_eq) {
   SelDigits s = sel_digits(kp, lo, hi);
   while (s.shift > 0) {                       // uniform: at most three times
@@ -285,7 +298,8 @@ __device__ __forceinline__ void sel_emit(const SelRow& r, bool is_g, int32_t ind
   gt += __popcll(b);
 }
 // totals of the waves before this one (par: a parity, where a loop does this step after step)
-__device__ __forceinline__ void sel_wave_base(SelShared& sh, int par, uint32_t g, uint32_t e, uint32_t& gt, uint32_t& eq,
+template <int R>
+__device__ __forceinline__ void sel_wave_base(SelShared<R>& sh, int par, uint32_t g, uint32_t e, uint32_t& gt, uint32_t& eq,
                                               uint32_t& all_g, uint32_t& all_e) {
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   if (lane == 0) { sh.wtot[par][wv][0] = g; sh.wtot[par][wv][1] = e; }
@@ -303,10 +317,10 @@ __device__ __forceinline__ void sel_wave_base(SelShared& sh, int par, uint32_t g
 // to the threshold, follows from the list, so that nearly every wave emits against one threshold.  (With two more digits, a count
 // of both kinds and two ballots per group of 64, 28 heads, 20,000 scores took 24.3 us against 16.5, 32,768 23.8 against 18.9, 12,288
 // 15.2 against 12.8; shortest rows 10.8 against 9.0.)
-template <int KPT>
-__device__ __forceinline__ void sel_from_registers(SelShared& sh, const SelRow& r, int64_t n) {
+template <int KPT, int R>
+__device__ __forceinline__ void sel_from_registers(SelShared<R>& sh, const SelRow& r, int64_t n) {
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int i0 = r.f + wv * (64 * KPT) + lane;
+  int i0 = r.f + wv * (64 * KPT) + lane;
   uint32_t key[KPT];
 #pragma unroll
   for (int e = 0; e < KPT; ++e) {
@@ -326,18 +340,18 @@ __device__ __forceinline__ void sel_from_registers(SelShared& sh, const SelRow& 
   ++lo;
   auto for_each = [&](auto&& f) {
     uint32_t none = 0u;
-    asm volatile("" : "+v"(none));   // (KPT lane masks held from pass to pass do not fit the scalar registers)
+    if constexpr (KPT > 16) asm volatile("" : "+v"(none));   // (KPT lane masks held from pass to pass do not fit the scalar registers)
 #pragma unroll
     for (int e = 0; e < KPT; ++e) f(key[e], key[e] != none);
   };
   SelDigits s = sel_digits(r.kp, lo, hi);
   bool few = false, whole = false;
+  uint32_t g = 0, q = 0, gt = 0, eq = 0, ag, ae;
   while (s.shift > 0 && !few && !whole && s.in_bin != kSelAtLo) {
     sel_digit(sh, for_each, lo, s);
     whole = s.krem == s.in_bin;
     few = !whole && s.shift > 0 && s.in_bin <= kSelFew;
   }
-  uint32_t g = 0, q = 0, gt = 0, eq = 0, ag, ae;
   if (few) {
     // one pass lists the keys of the threshold's bin and counts the wave's keys above it; the wave's share of the bin follows
     uint32_t b0 = lo + (s.prefix << s.shift);
@@ -377,6 +391,7 @@ __device__ __forceinline__ void sel_from_registers(SelShared& sh, const SelRow& 
     }
   }
   sel_wave_base(sh, 0, g, q, gt, eq, ag, ae);
+  if constexpr (KPT > 32) asm volatile("" : "+v"(i0));   // (so are the indices: held from the loads on they were what spilled)
   asm volatile("" : "+v"(T));   // the lane masks are made again: KPT of them do not fit the scalar registers
   const uint32_t eq_s = __builtin_amdgcn_readfirstlane(eq), q_s = __builtin_amdgcn_readfirstlane(q), need_s = __builtin_amdgcn_readfirstlane(need_eq);
   if (eq_s >= need_s || eq_s + q_s <= need_s) {
@@ -395,8 +410,8 @@ __device__ __forceinline__ void sel_from_registers(SelShared& sh, const SelRow& 
 // candidates).  Slices lie there in any order; the entries of a slice ascend, and so do the slices' indices.  The ordered
 // compaction gives every wave consecutive slices that hold about an equal share of the candidates (the best offsets crowd near the
 // diagonal: with equal numbers of slices one wave had half of the 10,000 candidates of a 1M-key row, 45 us against 29).
-template <typename SliceOf>
-__device__ __forceinline__ void sel_from_candidates(SelShared& sh, const uint2* cl, const SelRow& r, int n_slices, int m,
+template <int R, typename SliceOf>
+__device__ __forceinline__ void sel_from_candidates(SelShared<R>& sh, const uint2* cl, const SelRow& r, int n_slices, int m,
                                                     uint32_t floor_key, SliceOf&& slice_of) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -522,8 +537,8 @@ __device__ __forceinline__ void sel_walk_row(const SelRow& r, int64_t n, Step&& 
 // The ordered compaction of a row whose threshold is known, as far as the row has to be read: until it is complete or, where a
 // list holds the keys > T (`listed`), until the equal ones are (the smallest scores, if most of a row's are the same: a few
 // thousand entries).  Returns how many of the keys > T it has met.
-template <bool listed>
-__device__ __forceinline__ uint32_t sel_compact_row(SelShared& sh, const SelRow& r, int64_t n, uint32_t T, uint32_t need_eq) {
+template <bool listed, int R>
+__device__ __forceinline__ uint32_t sel_compact_row(SelShared<R>& sh, const SelRow& r, int64_t n, uint32_t T, uint32_t need_eq) {
   uint32_t run_g = 0, run_e = 0;
   sel_walk_row(r, n, [&](const uint32_t (&key)[kSelStep], int32_t i0, int par) {
     uint32_t g = 0, q = 0;
@@ -546,8 +561,8 @@ __device__ __forceinline__ uint32_t sel_compact_row(SelShared& sh, const SelRow&
 
 // The candidates of a row from number `from` of the order on, for a row all of whose candidates are wanted, behind `equal` other
 // entries.  1,024 slices at a time: their places in the order, then 16 lanes per slice.
-template <typename SliceOf>
-__device__ __forceinline__ void sel_copy_candidates(SelShared& sh, const uint2* cl, const SelRow& r, int n_slices, uint32_t from,
+template <int R, typename SliceOf>
+__device__ __forceinline__ void sel_copy_candidates(SelShared<R>& sh, const uint2* cl, const SelRow& r, int n_slices, uint32_t from,
                                                     uint32_t equal, SliceOf&& slice_of) {
   static_assert(kSelBins == 2 * kSelThreads, "two words per thread");
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
@@ -580,7 +595,8 @@ __device__ __forceinline__ void sel_copy_candidates(SelShared& sh, const uint2* 
 }
 
 // A row read from memory for its range, once per digit and once more for the compaction.
-__device__ __forceinline__ void sel_from_row(SelShared& sh, const SelRow& r, int64_t n) {
+template <int R>
+__device__ __forceinline__ void sel_from_row(SelShared<R>& sh, const SelRow& r, int64_t n) {
   uint32_t lo = ~0u, hi = 0u, T, need_eq;
   sel_walk_row(r, n, [&](const uint32_t (&key)[kSelStep], int32_t, int) {
 #pragma unroll
@@ -603,8 +619,8 @@ __device__ __forceinline__ void sel_from_row(SelShared& sh, const SelRow& r, int
 
 // The floor of a row's candidates: one score from each of SPT x kSelThreads stretches of the row (at a place inside its
 // stretch that a hash of its number gives), and among these the one at sel_sample_rank.
-template <int SPT>
-__device__ __forceinline__ uint32_t sel_floor(SelShared& sh, const SelRow& r, int64_t n) {
+template <int SPT, int R>
+__device__ __forceinline__ uint32_t sel_floor(SelShared<R>& sh, const SelRow& r, int64_t n) {
   constexpr int S = SPT * kSelThreads;
   const int64_t m = n - r.f;   // more than 2 S entries
   const float rank = sel_sample_rank((float)r.kp, (float)m, (float)S);
@@ -633,7 +649,7 @@ __device__ __forceinline__ uint32_t sel_floor(SelShared& sh, const SelRow& r, in
 // KPT: scores per thread of a row in registers; 0: a long row.
 template <int KPT>
 __global__ __launch_bounds__(kSelThreads) void k_sel_row(const SelArgs a) {
-  __shared__ SelShared sh;
+  __shared__ SelShared<sel_copies(KPT)> sh;
   extern __shared__ __attribute__((aligned(16))) unsigned char sel_dyn[];
   const int tid = threadIdx.x;
   SelRow r = sel_row(a, blockIdx.x);
@@ -718,7 +734,7 @@ __global__ __launch_bounds__(kSelThreads) void k_sel_row(const SelArgs a) {
 
 // Headers of the rows with their floors: one workgroup per row.
 __global__ __launch_bounds__(kSelThreads) void k_sel_sample(const SelArgs a) {
-  __shared__ SelShared sh;
+  __shared__ SelShared<1> sh;
   const SelRow r = sel_row(a, blockIdx.x);
   SelHeader hd;
   hd.floor_key = ~0u;   // (all entries of the row are forced: no candidates)

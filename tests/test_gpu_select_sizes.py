@@ -85,3 +85,20 @@ def test_rows_in_registers_at_every_length(n):
             want = (*_want(vsc, bv, 1), *_want(ssc, bs, keep))
             for a, b, nm in zip(vs.select(ck, vsc, ssc), want, ("v_idx", "v_cnt", "s_idx", "s_cnt")):
                 assert torch.equal(a, b), f"{nm}: n {n}, budgets {bv} / {bs}"
+
+
+# Rows in registers from one counter per bin to four, and scores of a few values: every lane of a wave adds to the same bin, the
+# threshold falls on a crowd (of the largest value, of one in the middle, at the end of one), and crowds lie side by side or scattered.
+@pytest.mark.parametrize("n", [16384, 16385, 32769, 40961, 49152])
+@pytest.mark.parametrize("values", [2, 5, 50])
+def test_crowds_in_registers(n, values):
+    g = torch.Generator(device="cuda:0").manual_seed(400 + n + values)
+    hq = 4
+    crowd = lambda: torch.randint(0, values, (hq, n), generator=g, device="cuda").float() / 32 + 1  # noqa: E731
+    half = torch.where(torch.rand((hq, n), generator=g, device="cuda") < 0.5, 1.5, _scores("spread", hq, n, g) * n)
+    for vsc, ssc in ((crowd(), crowd().sort(1, descending=True).values), (half, -crowd())):
+        for bv, bs, keep in ((128, 256, 64), (n // 2, n // values, 0), (1000, n - n // values, 0)):
+            ck = vs.Chunk(hq, 1, 128, 64, n - 64, 0.1, vertical_budget=bv, slash_budget=bs, keep_first_cols=1, keep_local_band=keep)
+            want = (*_want(vsc, bv, 1), *_want(ssc, bs, keep))
+            for a, b, nm in zip(vs.select(ck, vsc, ssc), want, ("v_idx", "v_cnt", "s_idx", "s_cnt")):
+                assert torch.equal(a, b), f"{nm}: n {n}, {values} values, budgets {bv} / {bs}"
