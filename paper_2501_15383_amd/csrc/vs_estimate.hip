@@ -357,16 +357,6 @@ __global__ __launch_bounds__(64 * est_waves(DCA)) void k_est_sums(const EstArgs 
   }
 }
 
-// Sweep B: P = exp2(S scale_log2 - lse2), summed along columns and diagonals.  Q K^T, and the two blocks of 32 keys swapped
-// by half-waves: a register then is one window row, its 64 lanes the tile's 64 keys.  A column sum is a plain sum over the
-// registers.  A diagonal moves on by one lane from row to row, so its sum is an add with a lane rotation per row:
-//   acc <- shift(acc, 1) + P[q],   q = 0 .. 63
-// after which lane f holds the offset p0 + 63 - (j0 + f), all in one register.  What leaves lane 63 on the way is complete as far as
-// this tile goes and belongs to the next tile's offsets: lane 63 stores it, row by row, into LDS, where it waits for the next
-// tile of the wave.  (A lane rotation with two sums, of the lanes up to q and of those past it, took three more vector
-// instructions per row; the stores are the LDS's work.)
-// Offsets at the seam of two waves get their two parts by atomic adds (cleared by sweep A; x + y is commutative, so scores are
-// run-to-run identical).
 // (M, L) <- the partial (m, l) added
 __device__ __forceinline__ void est_fold(float& M, float& L, float m, float l) {
   const float Mn = fmaxf(M, m);
@@ -380,14 +370,15 @@ __device__ __forceinline__ void est_store_lse(const EstArgs& a, int h, int r, fl
   a.lse2[(int64_t)h * 64 + r] = r < a.wp ? l2 : INFINITY;
   if (caller && a.lse_lastq && r < a.wp) a.lse_lastq[(int64_t)h * a.wp + r] = l2 * kLn2;
 }
-// The partials of a workgroup's heads folded by itself: waves / heads waves per head, every one a share of the ranges, and the
-// shares in order: the same numbers in every workgroup of the head, which all store them (scratch: 512 bytes per wave; ends with the
-// stores done and all waves past them).  A launch less, 4 to 5 us with its gap, for a trip to memory beside that of the window rows.
+// The partials of a workgroup's heads folded by itself: waves / heads waves per head (two or more, see launch_est), every one a share
+// of the ranges, and the shares in order: the same numbers in every workgroup of the head, which all store them (scratch: 512 bytes
+// per wave; ends with the stores done and all waves past them).  A launch less, 4 to 5 us with its gap, for a trip to memory beside
+// that of the window rows.
 __device__ __forceinline__ void est_fold_ranges(const EstArgs& a, const EstPlace& p, int waves, float2* scratch) {
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int shares = waves / p.n_h > 1 ? waves / p.n_h : 1, per = (a.n_ranges + shares - 1) / shares;
-  for (int x = wv; x < p.n_h * shares; x += waves) {   // (more heads than waves: one share each)
-    const int hd = x / shares, sh = x - hd * shares, r0 = sh * per, r1 = r0 + per < a.n_ranges ? r0 + per : a.n_ranges;
+  const int shares = waves / p.n_h, per = (a.n_ranges + shares - 1) / shares;
+  if (wv < p.n_h * shares) {
+    const int hd = wv / shares, sh = wv - hd * shares, r0 = sh * per, r1 = r0 + per < a.n_ranges ? r0 + per : a.n_ranges;
     const float2* const pp = (const float2*)a.part + (int64_t)(p.h0 + hd) * a.n_ranges * 64 + lane;
     float M = -INFINITY, L = 0.f;
     constexpr int U = 8;
@@ -400,11 +391,10 @@ __device__ __forceinline__ void est_fold_ranges(const EstArgs& a, const EstPlace
       for (int u = 0; u < U; ++u)
         if (r + u < r1) est_fold(M, L, v[u].x, v[u].y);
     }
-    if (shares == 1) est_store_lse(a, p.h0 + hd, lane, M, L, p.blk == 0);
-    else scratch[64 * x + lane] = make_float2(M, L);
+    scratch[64 * wv + lane] = make_float2(M, L);
   }
   __syncthreads();
-  if (shares > 1 && wv < p.n_h) {
+  if (wv < p.n_h) {
     float M = -INFINITY, L = 0.f;
     for (int sh = 0; sh < shares; ++sh) {
       const float2 v = scratch[64 * (wv * shares + sh) + lane];
@@ -422,6 +412,16 @@ __device__ __forceinline__ void est_store_last(uint32_t at, f32x4 v, const int s
   asm volatile("s_mov_b64 exec, %2\n\tds_write_b128 %0, %1 offset:%3\n\ts_mov_b64 exec, -1"
                :: "v"(at), "v"(v), "s"(1ull << 63), "n"(16 * slot));
 }
+// Sweep B: P = exp2(S scale_log2 - lse2), summed along columns and diagonals.  Q K^T, and the two blocks of 32 keys swapped
+// by half-waves: a register then is one window row, its 64 lanes the tile's 64 keys.  A column sum is a plain sum over the
+// registers.  A diagonal moves on by one lane from row to row, so its sum is an add with a lane rotation per row:
+//   acc <- shift(acc, 1) + P[q],   q = 0 .. 63
+// after which lane f holds the offset p0 + 63 - (j0 + f), all in one register.  What leaves lane 63 on the way is complete as far as
+// this tile goes and belongs to the next tile's offsets: lane 63 stores it, row by row, into LDS, where it waits for the next
+// tile of the wave.  (A lane rotation with two sums, of the lanes up to q and of those past it, took three more vector
+// instructions per row; the stores are the LDS's work.)
+// Offsets at the seam of two waves get their two parts by atomic adds (cleared by sweep A; x + y is commutative, so scores are
+// run-to-run identical).
 template <int D, bool DCA>
 __global__ __launch_bounds__(64 * est_waves(DCA)) void k_est_scores(const EstArgs a, const EstShape z) {
   constexpr int DSTEPS = D / 16;
@@ -650,8 +650,9 @@ static hipError_t launch_est(const vs_params& p, EstArgs a, void* ws, hipStream_
   a.n_ranges = za.n_blocks;
   // Sweep B folds up to 16 ranges per wave itself, in two trips to memory: 28 heads, 2,558 keys 23.0 us -> 20.6, 20,000 48.3 -> 46.7; 4 heads of
   // 64, 8,192 keys 20.7 -> 15.6.  With seven heads per workgroup a wave has 30 and more, four trips: as long as the launch.
-  const int shares = zb.waves / zb.heads > 1 ? zb.waves / zb.heads : 1;
-  a.fold = a.n_ranges <= kEstFold * shares;
+  // Not where a head has no two waves of its own (never so few ranges, over 20,000 sizes and head shapes).
+  const int shares = zb.waves / zb.heads;
+  a.fold = shares > 1 && a.n_ranges <= kEstFold * shares;
   a.part = (float*)ws;
   a.lse2 = a.part + (size_t)p.n_q_heads * a.n_ranges * 64 * 2;   // (every part a multiple of 256 bytes)
   a.far = a.lse2 + (size_t)p.n_q_heads * 64;
