@@ -1081,28 +1081,29 @@ hipError_t launch_select(const vs_params& p, const float* vscore, const float* s
     return true;
   };
   if (in_registers(k_sel_row<4>, 4) || in_registers(k_sel_row<8>, 8) || in_registers(k_sel_row<12>, 12) || in_registers(k_sel_row<16>, 16) ||
-      in_registers(k_sel_row<24>, 24) || in_registers(k_sel_row<32>, 32) || in_registers(k_sel_row<40>, 40) || in_registers(k_sel_row<48>, 48)) {
-  } else if (l.sliced || (a.n > kSelRegKeys && ws_bytes < l.total && l.cap > kSelCand)) {
+      in_registers(k_sel_row<24>, 24) || in_registers(k_sel_row<32>, 32) || in_registers(k_sel_row<40>, 40) || in_registers(k_sel_row<48>, 48))
+    return hipGetLastError();
+  static_assert(kSelRegKeys == 48 * kSelThreads, "the rows from here on are long ones");
+  if (l.sliced || (ws_bytes < l.total && l.cap > kSelCand)) {
     if (!ws || ws_bytes < sel_ctl_bytes(p)) return hipErrorInvalidValue;
     return launch_slices(a, ws, st);
-  } else {
-    static DeviceOnce once;   // the opt-in to more than 64 KiB of LDS
-    const hipError_t e = once.run([]() {
-      return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_sel_row<0>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                 kSelCand * (int)sizeof(uint2));
-    });
-    if (e != hipSuccess) return e;
-    if (ws && ws_bytes >= l.total && a.n > kSelRegKeys) {
-      a.hdr = (SelHeader*)ws;
-      a.slices = (uint2*)((char*)ws + l.slices);
-      a.cand = (uint2*)((char*)ws + l.cand);
-      a.cap = l.cap;
-      hipLaunchKernelGGL(k_sel_sample, rows, block, 0, st, a);
-      hipLaunchKernelGGL(k_sel_filter, dim3((unsigned)ceil_div(l.n_slices, kSelFilterThreads / 64), rows.x),
-                         dim3(kSelFilterThreads), 0, st, a);
-    }
-    hipLaunchKernelGGL(k_sel_row<0>, rows, block, kSelCand * sizeof(uint2), st, a);
   }
+  static DeviceOnce once;   // the opt-in to more than 64 KiB of LDS
+  const hipError_t e = once.run([]() {
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_sel_row<0>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                               kSelCand * (int)sizeof(uint2));
+  });
+  if (e != hipSuccess) return e;
+  if (ws && ws_bytes >= l.total) {
+    a.hdr = (SelHeader*)ws;
+    a.slices = (uint2*)((char*)ws + l.slices);
+    a.cand = (uint2*)((char*)ws + l.cand);
+    a.cap = l.cap;
+    hipLaunchKernelGGL(k_sel_sample, rows, block, 0, st, a);
+    hipLaunchKernelGGL(k_sel_filter, dim3((unsigned)ceil_div(l.n_slices, kSelFilterThreads / 64), rows.x),
+                       dim3(kSelFilterThreads), 0, st, a);
+  }
+  hipLaunchKernelGGL(k_sel_row<0>, rows, block, kSelCand * sizeof(uint2), st, a);
   return hipGetLastError();
 }
 
