@@ -262,9 +262,10 @@ int vs_prefill_chunk_dca(const vs_params *p, const void *q_intra, const vs_dca *
  *               themselves stay on the device (no copy, no synchronisation).
  * A request outside these bounds, or with a null q / k / v / out, is skipped on the
  * device: its outputs are left untouched.  Results per request are those of
- * vs_dense_causal_prefill / vs_sparse_attn_prefill up to the rounding of the fp32
- * partial sums (the key walk of every unit may be cut into ranges, folded in a fixed
- * order: run-to-run identical).  Workspace: vs_batch_workspace_bytes(p, n_requests).
+ * vs_dense_causal_prefill / vs_sparse_attn_prefill up to the rounding of the bf16
+ * probabilities and the fp32 partial sums (the key walk of every unit may be cut into
+ * ranges, not always those of the single call, folded in a fixed order: run-to-run
+ * identical).  Workspace: vs_batch_workspace_bytes(p, n_requests).
  * Returns VS_ERR_UNSUPPORTED for p->q_len > 4096 or n_requests > 4096. */
 typedef struct vs_request {
   const void *q, *k, *v;
@@ -312,12 +313,13 @@ int vs_plan_chunks(int64_t n_ctx, int32_t n_chunks, int32_t model,
  *     before asking for them.
  *   VS_OPT_ATTN_KEY_SPLIT  chunks with few (query tile, head) units (a decode step, a short
  *     last chunk) have their key walk cut into ranges, one workgroup each, and a second
- *     kernel folds the partial results: 0 = automatic (up to 128 ranges of at least 8 key
- *     blocks, so that the pieces fill 512 workgroup slots evenly; of longer chunks only the
+ *     kernel folds the partial results: 0 = automatic (up to 128 ranges of at least 2 key
+ *     blocks, 8 in a batch, so that the pieces fill 512 workgroup slots evenly; of longer chunks only the
  *     units that whole rounds leave over are cut), 1 = never, 2..16 = that many ranges (at
  *     least 16 key blocks each).
- *     Results agree within the rounding of the fp32 partial sums.  Changes the workspace
- *     sizes like the option above.  Single tokens (no DCA, at most 16 query heads per KV
+ *     Results agree within the rounding of the bf16 probabilities (those of a range are
+ *     rounded relative to a reference of its own) and of the fp32 partial sums.  Changes the
+ *     workspace sizes like the option above: a short call may need more than a longer one.  Single tokens (no DCA, at most 16 query heads per KV
  *     head) and vs_attn_batch always share out their keys by themselves.
  *   VS_OPT_ATTN_ROUNDS_IN_TURN  0 (default): the rounds of the persistent attention launch are
  *     dealt to its eight workgroup groups by weight (length of each head's block list), the

@@ -1240,7 +1240,9 @@ __device__ __forceinline__ int64_t batch_steps(const vs_request& rq, const Batch
   const int64_t listed = 2 * (int64_t)rq.s_cnt[0] + 1;
   return (listed < n_blk ? listed : n_blk) + 2 * b.pack * ((rq.v_cnt[0] + 63) / 64);
 }
-// Ranges that equally long units are best cut into: rounds of kBatchSlots pieces, as in attn_cut.
+// Ranges that equally long units are best cut into: rounds of kBatchSlots pieces.  Not the cut of attn_cut: all units or none are cut,
+// in ranges of at least kMinBatchSteps (the caller sees to that), and the terms for a piece alone on its compute unit and for the serial
+// part of the fold, fitted to single calls, are not counted.
 __device__ int best_split(int64_t units, int64_t steps, int64_t most_pieces) {
   int best = 1;
   float best_cost = 0.f;
@@ -1255,8 +1257,8 @@ __device__ int best_split(int64_t units, int64_t steps, int64_t most_pieces) {
 }
 // Ranges per unit so that all pieces of a batch come out about equally long and there are a.pieces of them: the requests
 // differ in length, and a workgroup takes the next piece when it is done with one.  Rounded down, so that the split units
-// have at most a.pieces pieces (slots of partial results).  The units of a single request are equally long: they are cut as
-// attn_cut would cut them all (2,500 rows at 20,000 keys, 20 heads: 400 units whole 528 us, in three ranges each 613).
+// have at most a.pieces pieces (slots of partial results).  The units of a single request are equally long: best_split says
+// how they are cut (2,500 rows at 20,000 keys, 20 heads: 400 units whole 528 us, in three ranges each 613).
 __device__ void write_plan(const ListArgs& a, int64_t* scan) {
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   constexpr int NW = kBlThreads / 64;
