@@ -8,7 +8,7 @@ import torch
 
 import oracle
 import paper_2501_15383_amd as vs
-from gpu_util import assert_attn_close, chunk_of, dev
+from gpu_util import assert_attn_close, chunk_of, dev, f64
 from helpers import rand_bf16
 from test_gpu_attention import _rand_sets, _t
 from test_gpu_batch import _check, _make_requests, _run_batch
@@ -76,6 +76,31 @@ def test_ranges_of_a_few_blocks(hq, hkv, d, c, n):
         got = vs.sparse_attn_prefill(chunk_of(pb), dev(q), dev(k), dev(v), *[_t(x) for x in sets], want_lse=True)
         torch.cuda.synchronize()
         assert_attn_close(*got, *oracle.sparse_attention(pb, q, k, v, *sets), f"sparse {hq}/{hkv} C={c} n={n} {nv} columns {ns} offsets")
+
+
+# A call's ranges, however short, are as near to 64 bits as its walk in one piece: the probabilities of a range are rounded to bf16
+# relative to a reference of its own, by 2^-9 at most all the same.  Other roundings, so the two differ by about sqrt(2) of either's
+# error; the error itself is the same but for chance.  Squared errors of n independent values give their root mean to 1 / sqrt(2 n):
+# 0.3 % for the 532 rows of 128 of the smallest call, 3 % if all values of a row moved as one; 5 % are allowed.
+@pytest.mark.parametrize("hq,hkv,d,c,n", [(28, 4, 128, 138, 2869), (28, 4, 128, 214, 2337), (8, 2, 64, 234, 14394), (40, 8, 128, 35, 954),
+                                          (28, 4, 128, 19, 22035), (4, 1, 64, 191, 1866)])
+def test_ranges_lose_no_precision(hq, hkv, d, c, n):
+    rng = np.random.default_rng(3090 + n)
+    q = rand_bf16(rng, (c, hq, d)); k = rand_bf16(rng, (n, hkv, d)); v = rand_bf16(rng, (n, hkv, d))
+    pb = oracle.Problem(hq, hkv, d, c, n - c, 1.0 / np.sqrt(d))
+    ref = oracle.dense_attention(pb, q, k, v)[0].transpose(1, 0, 2)
+    err, size = [], []
+    for split in (0, 1):
+        try:
+            vs.set_option(vs.VS_OPT_ATTN_KEY_SPLIT, split)
+            size.append(vs.workspace_bytes(chunk_of(pb), vs.VS_WS_DENSE))
+            got = vs.dense_causal_prefill(chunk_of(pb), dev(q), dev(k), dev(v))[0]
+            torch.cuda.synchronize()
+        finally:
+            vs.set_option(vs.VS_OPT_ATTN_KEY_SPLIT, 0)
+        err.append(np.linalg.norm(f64(got) - ref) / np.linalg.norm(ref))
+    assert size[0] > size[1]   # (it was cut)
+    assert err[0] <= 1.05 * err[1], err
 
 
 @pytest.mark.parametrize("c,s", [(66 * 128 - 5, 70), (66 * 128 - 5, 4100 * 64 + 1)])   # 528 units: 512 whole, 16 cut
