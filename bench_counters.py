@@ -18,6 +18,10 @@ It runs nothing on the GPU.  The runs it reads (each in its own rocprofv3 proces
                  SQ_ACTIVE_INST_ANY SQ_ACTIVE_INST_SCA GRBM_GUI_ACTIVE --output-format csv
                  -d gpurun_out/prof/sq3 -- B --steps 1 --warmup 0
 
+Right before a run `python3 bench_counters.py --stamp gpurun_out/prof/<run>` notes in its folder the hash of the library's sources
+(the folder must be new).  Summaries are written only from runs of the present sources, one result file each: what an older
+run left in the folder would be taken for this one's.
+
 In every run the launches of k_attention<128, 2, false, false, false> come in this order: the sparse
 launch(es) of the timed steps, three dense launches, four launches of the gather probe.
 
@@ -33,6 +37,7 @@ run checks the expression.  WRITE_SIZE is in KiB and matches the copy one to one
 import collections
 import csv
 import glob
+import hashlib
 import json
 import os
 import sys
@@ -41,11 +46,41 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 ATT = "k_attention<128, 2, false, false, false>"
 
 
-def one(pattern):
-    f = glob.glob(pattern, recursive=True)
-    if not f:
-        raise SystemExit(f"missing rocprofv3 output: {pattern}")
+NOMINAL_GHZ = 2.4
+
+
+def sources_hash():
+    """sha256[:16] of every source of the library"""
+    h = hashlib.sha256()
+    from paper_2501_15383_amd import build
+    for f in [os.path.join(build.CSRC, x) for x in build.SOURCES] + build.HEADERS:
+        h.update(os.path.basename(f).encode() + b"\0" + open(f, "rb").read())
+    return h.hexdigest()[:16]
+
+
+def stamp(folder):
+    os.makedirs(folder)
+    with open(os.path.join(folder, "sources"), "w") as f:
+        f.write(sources_hash())
+
+
+def one(base, run, pattern):
+    """The one result file of a run, which has to be of the present sources."""
+    f = glob.glob(f"{base}/{run}/{pattern}", recursive=True)
+    if len(f) != 1:
+        raise SystemExit(f"{base}/{run}: {len(f)} files {pattern}, one is wanted")
+    at = f"{base}/{run}/sources"
+    if not os.path.exists(at) or open(at).read().strip() != sources_hash():
+        raise SystemExit(f"{base}/{run} is not of the present sources ({sources_hash()})")
     return f[0]
+
+
+def clock(cycles, ms, what):
+    """GHz; counters of one run over the time of another make sense only below the nominal clock."""
+    ghz = cycles / (ms * 1e-3) / 1e9
+    if ghz > 1.05 * NOMINAL_GHZ:
+        raise SystemExit(f"{what}: {cycles / 1e6:.3f} M cycles in {ms:.3f} ms are {ghz:.2f} GHz: not the same work")
+    return ghz
 
 
 def bench_line(log):
@@ -55,7 +90,7 @@ def bench_line(log):
 def dispatches(d, base):
     """per kernel dispatch, in dispatch order: (kernel name, {counter: value summed over instances})"""
     per = collections.OrderedDict()
-    for r in csv.DictReader(open(one(f"{base}/{d}/**/*counter_collection.csv"))):
+    for r in csv.DictReader(open(one(base, d, "**/*counter_collection.csv"))):
         k = (int(r["Dispatch_Id"]), r["Kernel_Name"])
         per.setdefault(k, collections.defaultdict(float))[r["Counter_Name"]] += float(r["Counter_Value"])
     return [(k[1], v) for k, v in sorted(per.items())]
@@ -80,7 +115,8 @@ def others(base):
          rocprofv3 --kernel-trace --stats --output-format csv -d gpurun_out/prof/kt_<name>
                    -- python3 bench.py <switches> --steps 3 --warmup 1 --no-cpu --no-extras"""
     out = ["# rocprofv3 kernel traces of the other workloads (one MI355X; raw outputs stay under gpurun_out/; written by",
-           "# bench_counters.py --others).  Each block: the command, the kernels of the library with their launch times over the",
+           f"# bench_counters.py --others; sources of the library: sha256[:16] = {sources_hash()}).  Each block: the command, the kernels",
+           "# of the library with their launch times over the",
            "# run, and the bench.py line of the same run.  A run is 1 warm-up + 3 timed chunk steps (+ 3 dense-kernel launches",
            "# where the workload is sparse), so the k_attention rows mix sparse and dense launches: min / max separate them.", ""]
     for name, sw in OTHERS:
@@ -90,7 +126,7 @@ def others(base):
                 f"command: rocprofv3 --kernel-trace --stats --output-format csv -d gpurun_out/prof/kt_{name} -- python3 bench.py "
                 f"{sw} --steps 3 --warmup 1 --no-cpu --no-extras"]
         per = collections.OrderedDict()
-        for r in csv.DictReader(open(one(f"{base}/kt_{name}/**/*_kernel_trace.csv"))):
+        for r in csv.DictReader(open(one(base, f"kt_{name}", "**/*_kernel_trace.csv"))):
             if "vs::" in r["Kernel_Name"]:
                 per.setdefault(r["Kernel_Name"], []).append((int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e6)
         out.append(f"{'kernel':62s} {'calls':>5s} {'avg ms':>10s} {'min ms':>10s} {'max ms':>10s}")
@@ -109,6 +145,8 @@ def others(base):
 
 
 def main():
+    if len(sys.argv) > 2 and sys.argv[1] == "--stamp":
+        return stamp(sys.argv[2])
     if len(sys.argv) > 1 and sys.argv[1] == "--others":
         return others(sys.argv[2] if len(sys.argv) > 2 else os.path.join(ROOT, "gpurun_out", "prof"))
     base = sys.argv[1] if len(sys.argv) > 1 else os.path.join(ROOT, "gpurun_out", "prof")
@@ -118,12 +156,13 @@ def main():
     out += ["# rocprofv3 summaries: vertical-slash sparse prefill, workload 7b_1m (last 32,768-token chunk of a 1,048,576-token",
             "# context, Hq 28 / Hkv 4 / D 128, W 64, Bv 1000, Bs 6096), one MI355X.  Written by bench_counters.py from the runs",
             "# its header lists (B = python3 bench.py --no-cpu --no-extras --gather-probe); raw outputs stay under gpurun_out/.",
-            f"# kernel sources: sha256[:16] of csrc/vs_attn.hip + csrc/vs_common.h = {bench.kernel_source_hash()}", ""]
+            f"# sources: sha256[:16] of all of the library = {sources_hash()} in every run; of csrc/vs_attn.hip + csrc/vs_common.h = "
+            f"{bench.kernel_source_hash()}", ""]
     # ---- 1. kernel trace
     out += ["## 1. kernel trace",
             "command: rocprofv3 --kernel-trace --stats --output-format csv -d gpurun_out/prof/kt -- B --steps 3 --warmup 1", ""]
     per = collections.OrderedDict()
-    rows = list(csv.DictReader(open(one(f"{base}/kt/**/*_kernel_trace.csv"))))
+    rows = list(csv.DictReader(open(one(base, "kt", "**/*_kernel_trace.csv"))))
     rows.sort(key=lambda r: int(r["Start_Timestamp"]))
     for r in rows:
         if "vs::" in r["Kernel_Name"]:
@@ -200,7 +239,7 @@ def main():
     for i, (nm, ms) in enumerate((("sparse", kt_sparse_ms), ("dense", kt_dense_ms), ("gather", kt_gather_ms))):
         a = agg[i]
         cyc = a["GRBM_GUI_ACTIVE"] / 8
-        out += [f"{nm}: GRBM_GUI_ACTIVE / 8 XCDs = {cyc / 1e6:.1f} M cycles over {ms:.2f} ms (kernel trace) -> clock {cyc / (ms * 1e-3) / 1e9:.2f} GHz "
+        out += [f"{nm}: GRBM_GUI_ACTIVE / 8 XCDs = {cyc / 1e6:.1f} M cycles over {ms:.2f} ms (kernel trace) -> clock {clock(cyc, ms, nm):.2f} GHz "
                 "(nominal 2.4; counter runs serialise the launch, the clock is indicative)",
                 f"   MFMA busy {a['SQ_VALU_MFMA_BUSY_CYCLES'] / 1024 / cyc * 100:.1f}% of the clocked cycles (32 cycles per MFMA on 1024 SIMDs); "
                 f"VALU active {a['SQ_ACTIVE_INST_VALU'] * 4 / 1024 / cyc * 100:.1f}% (MFMA issue included); "
@@ -220,7 +259,7 @@ def main():
             for k, v in pick(dispatches(run, base), nm)[0].items():
                 a.setdefault(k, v)
         cyc = a["GRBM_GUI_ACTIVE"] / 8
-        out.append(f"{nm}: {cyc / 1e6:.3f} M cycles over {ms:.3f} ms; MFMA busy {a['SQ_VALU_MFMA_BUSY_CYCLES'] / 1024 / cyc * 100:.0f}%, "
+        out.append(f"{nm}: {cyc / 1e6:.3f} M cycles over {ms:.3f} ms ({clock(cyc, ms, nm):.2f} GHz); MFMA busy {a['SQ_VALU_MFMA_BUSY_CYCLES'] / 1024 / cyc * 100:.0f}%, "
                    f"VALU active {a['SQ_ACTIVE_INST_VALU'] * 4 / 1024 / cyc * 100:.0f}% (MFMA issue included) of the clocked cycles; per MFMA "
                    f"{a['SQ_INSTS_VALU'] / a['SQ_INSTS_MFMA']:.1f} VALU (MFMA included), {a['SQ_INSTS_VALU_TRANS_F32'] / a['SQ_INSTS_MFMA']:.1f} "
                    f"transcendental, {a['SQ_INSTS_LDS'] / a['SQ_INSTS_MFMA']:.2f} LDS, {a['SQ_INSTS_VMEM'] / a['SQ_INSTS_MFMA']:.2f} VMEM; "

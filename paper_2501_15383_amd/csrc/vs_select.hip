@@ -26,16 +26,16 @@
 // scores once per digit of 8 bits, once for the counts and once for the compaction (k_slice_*): the list would be one
 // workgroup's work.
 // Measured on one MI355X, 28 heads, budgets 1000 / 6096, against four digits, a count and a write pass over all
-// scores in seven launches: 8,192 scores per row 11 us (67), 32,768 19 us (70), 300,001 57 us (152), 1M 108 us
-// (345: filter 63 us = 3.7 TB/s, sample 16, rows 29); 4 heads, budgets 128 / 256, 1M: 50 us (98).
+// scores in seven launches: 8,192 scores per row 8 us (67), 32,768 15 us (70), 300,001 55 us (152), 1M 107 us
+// (345: filter 64 us = 3.7 TB/s, sample 26, rows 28, under a profiler); 4 heads, budgets 128 / 256, 1M: 54 us (98).
 #include "vs_common.h"
 
 namespace vs {
 
 constexpr int kSelThreads = 1024;
 constexpr int kSelWaves = kSelThreads / 64;
-constexpr int kSelRegKeys = 48 * kSelThreads;  // longest row that stays in registers (44,000 scores, 28 heads: 21 us, 35 with the
-                                               // row's candidates in LDS; three launches 39 at 49,153.  Scores of 2 to 25 values and
+constexpr int kSelRegKeys = 48 * kSelThreads;  // longest row that stays in registers (44,000 scores, 28 heads: 20 us, 35 with the
+                                               // row's candidates in LDS; three launches 36 at 49,153.  Scores of 2 to 25 values and
                                                // budgets of hundreds take 28 to 39 so, 24 to 33 with candidates)
 constexpr int kSelCand = 16384;                // longest list of candidates (128 KB of LDS)
 constexpr int kSelSlice = 2048;                // scores per wave of the filter (one slice each)
@@ -315,8 +315,8 @@ __device__ __forceinline__ void sel_wave_base(SelShared<R>& sh, int par, uint32_
 // A row in registers: KPT scores per thread, a wave's scores contiguous (KPT groups of 64).  After the first digit a pass over the
 // scores lists the threshold's bin and counts every wave's scores above it; what a wave takes of the bin, and how many scores equal
 // to the threshold, follows from the list, so that nearly every wave emits against one threshold.  (With two more digits, a count
-// of both kinds and two ballots per group of 64, 28 heads, 20,000 scores took 24.3 us against 16.5, 32,768 23.8 against 18.9, 12,288
-// 15.2 against 12.8; shortest rows 10.8 against 9.0.)
+// of both kinds and two ballots per group of 64, one counter per bin and 8, 16 or 32 scores per lane, 28 heads, 20,000 scores took 21.0
+// us against 12.6, 32,768 20.9 against 15.4, 12,288 12.1 against 9.8, 4,096 8.4 against 6.9.)
 template <int KPT, int R>
 __device__ __forceinline__ void sel_from_registers(SelShared<R>& sh, const SelRow& r, int64_t n) {
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
