@@ -48,8 +48,8 @@ struct EstArgs {
 // Bound: issue cycles and, at long contexts, power: both sweeps run at 1.7 to 2.0 GHz.  Per 64 scores there are 16 cycles of MFMA and,
 // as measured one by one (cycles of a SIMD, from any number of waves): exp 8.3, a lane swap or a half of it 4.2, an add with a lane
 // shift 4.3, fma and add 2 each, MFMA issue 4.  Sweep A has exp, fma and add (vector instructions 71 % of the clocked cycles,
-// MFMA 51 %, they overlap), sweep B half a lane swap and one shifted add more (67 % and 37 %).  1M keys, 28 query / 4 KV heads of
-// 128, in kernel traces: sweep A 560 -> 477 us (a running maximum took half an instruction per score, and its state two shares of heads:
+// MFMA 51 %, they overlap), sweep B half a lane swap and one shifted add more (two thirds and 37 %).  1M keys, 28 query / 4 KV heads of
+// 128, in kernel traces: sweep A 560 -> 475 us (a running maximum took half an instruction per score, and its state two shares of heads:
 // K went by twice, 2.24 GB), sweep B 734 -> 619 (three vector instructions fewer per row, see there), 1.27 -> 1.09 ms with everything.  Without
 // the stores of sweep B, its lse loads, new K rows per tile or the lane shifts, one at a time, it would be 2 to 9 % faster.
 // The next block's product interleaved with this one's exponentials by hand, two or three waves per SIMD and more
