@@ -4,21 +4,21 @@
 It runs nothing on the GPU.  The runs it reads (each in its own rocprofv3 process; one MI355X;
 `B` = `python3 bench.py --no-cpu --no-extras --gather-probe`):
 
-  kt   rocprofv3 --kernel-trace --stats --output-format csv -d gpurun_out/prof/kt  -- B --steps 3 --warmup 1
+  kt   rocprofv3 --kernel-trace --stats --output-format csv -d PROF/kt  -- B --steps 3 --warmup 1
   rd   rocprofv3 --pmc TCC_EA0_RDREQ_32B_sum TCC_EA0_RDREQ_64B_sum TCC_EA0_RDREQ_128B_sum TCC_EA0_RDREQ_sum
-                 --output-format csv -d gpurun_out/prof/rd -- B --steps 1 --warmup 0 --calib-copy
-  wr   rocprofv3 --pmc WRITE_SIZE --output-format csv -d gpurun_out/prof/wr -- B --steps 1 --warmup 0 --calib-copy
+                 --output-format csv -d PROF/rd -- B --steps 1 --warmup 0 --calib-copy
+  wr   rocprofv3 --pmc WRITE_SIZE --output-format csv -d PROF/wr -- B --steps 1 --warmup 0 --calib-copy
   sq1  rocprofv3 --pmc SQ_VALU_MFMA_BUSY_CYCLES SQ_BUSY_CU_CYCLES SQ_INSTS_VALU SQ_INSTS_MFMA SQ_WAVE_CYCLES
                  SQ_WAIT_INST_ANY SQ_LDS_BANK_CONFLICT SQ_INSTS_LDS GRBM_GUI_ACTIVE --output-format csv
-                 -d gpurun_out/prof/sq1 -- B --steps 1 --warmup 0
+                 -d PROF/sq1 -- B --steps 1 --warmup 0
   sq2  rocprofv3 --pmc SQ_ACTIVE_INST_LDS SQ_INSTS_LDS_LOAD_BANDWIDTH SQ_ACTIVE_INST_VALU SQ_INSTS_VALU_TRANS_F32
                  SQ_ACTIVE_INST_VMEM SQ_WAIT_INST_LDS SQ_INSTS_VMEM GRBM_GUI_ACTIVE --output-format csv
-                 -d gpurun_out/prof/sq2 -- B --steps 1 --warmup 0
+                 -d PROF/sq2 -- B --steps 1 --warmup 0
   sq3  rocprofv3 --pmc SQ_LDS_IDX_ACTIVE SQ_LDS_DATA_FIFO_FULL SQ_LDS_CMD_FIFO_FULL SQ_WAIT_ANY SQ_INSTS_SALU
                  SQ_ACTIVE_INST_ANY SQ_ACTIVE_INST_SCA GRBM_GUI_ACTIVE --output-format csv
-                 -d gpurun_out/prof/sq3 -- B --steps 1 --warmup 0
+                 -d PROF/sq3 -- B --steps 1 --warmup 0
 
-Right before a run `python3 bench_counters.py --stamp gpurun_out/prof/<run>` notes in its folder the hash of the library's sources
+Right before a run `python3 bench_counters.py --stamp PROF/<run>` notes in its folder the hash of the library's sources
 (the folder must be new).  Summaries are written only from runs of the present sources, one result file each: what an older
 run left in the folder would be taken for this one's.
 
@@ -30,9 +30,9 @@ requests that are neither 32 nor 128 bytes long (the FETCH_SIZE expression of ro
 128-byte request as 64 bytes on this chip, so it is not used); the 1 GiB device copy of the same
 run checks the expression.  WRITE_SIZE is in KiB and matches the copy one to one.
 
-    python3 bench_counters.py [gpurun_out/prof]     writes profiles/vs_kernels_7b_1m_last_chunk.txt
+    python3 bench_counters.py [PROF]     writes profiles/vs_kernels_7b_1m_last_chunk.txt
                                                      and profiles/traffic_k_attention_7b_1m.json
-    python3 bench_counters.py --others [gpurun_out/prof]   writes profiles/vs_kernels_other_workloads.txt (see others())
+    python3 bench_counters.py --others [PROF]   writes profiles/vs_kernels_other_workloads.txt (see others())
 """
 import collections
 import csv
@@ -112,9 +112,9 @@ OTHERS = [("dense_7b_64k", "--workload dense_7b_64k"), ("7b_128k", "--workload 7
 
 def others(base):
     """profiles/vs_kernels_other_workloads.txt from the kernel traces kt_<name> of the other workloads:
-         rocprofv3 --kernel-trace --stats --output-format csv -d gpurun_out/prof/kt_<name>
+         rocprofv3 --kernel-trace --stats --output-format csv -d PROF/kt_<name>
                    -- python3 bench.py <switches> --steps 3 --warmup 1 --no-cpu --no-extras"""
-    out = ["# rocprofv3 kernel traces of the other workloads (one MI355X; raw outputs stay under gpurun_out/; written by",
+    out = ["# rocprofv3 kernel traces of the other workloads (one MI355X; raw outputs are not kept; written by",
            f"# bench_counters.py --others; sources of the library: sha256[:16] = {sources_hash()}).  Each block: the command, the kernels",
            "# of the library with their launch times over the",
            "# run, and the bench.py line of the same run.  A run is 1 warm-up + 3 timed chunk steps (+ 3 dense-kernel launches",
@@ -123,7 +123,7 @@ def others(base):
         if not glob.glob(f"{base}/kt_{name}/**/*_kernel_trace.csv", recursive=True):
             continue
         out += [f"## {name}",
-                f"command: rocprofv3 --kernel-trace --stats --output-format csv -d gpurun_out/prof/kt_{name} -- python3 bench.py "
+                f"command: rocprofv3 --kernel-trace --stats --output-format csv -d PROF/kt_{name} -- python3 bench.py "
                 f"{sw} --steps 3 --warmup 1 --no-cpu --no-extras"]
         per = collections.OrderedDict()
         for r in csv.DictReader(open(one(base, f"kt_{name}", "**/*_kernel_trace.csv"))):
@@ -148,19 +148,19 @@ def main():
     if len(sys.argv) > 2 and sys.argv[1] == "--stamp":
         return stamp(sys.argv[2])
     if len(sys.argv) > 1 and sys.argv[1] == "--others":
-        return others(sys.argv[2] if len(sys.argv) > 2 else os.path.join(ROOT, "gpurun_out", "prof"))
-    base = sys.argv[1] if len(sys.argv) > 1 else os.path.join(ROOT, "gpurun_out", "prof")
+        return others(sys.argv[2] if len(sys.argv) > 2 else "PROF")
+    base = sys.argv[1] if len(sys.argv) > 1 else "PROF"
     sys.path.insert(0, ROOT)
     import bench
     out = []
     out += ["# rocprofv3 summaries: vertical-slash sparse prefill, workload 7b_1m (last 32,768-token chunk of a 1,048,576-token",
             "# context, Hq 28 / Hkv 4 / D 128, W 64, Bv 1000, Bs 6096), one MI355X.  Written by bench_counters.py from the runs",
-            "# its header lists (B = python3 bench.py --no-cpu --no-extras --gather-probe); raw outputs stay under gpurun_out/.",
+            "# its header lists (B = python3 bench.py --no-cpu --no-extras --gather-probe); raw outputs are not kept.",
             f"# sources: sha256[:16] of all of the library = {sources_hash()} in every run; of csrc/vs_attn.hip + csrc/vs_common.h = "
             f"{bench.kernel_source_hash()}", ""]
     # ---- 1. kernel trace
     out += ["## 1. kernel trace",
-            "command: rocprofv3 --kernel-trace --stats --output-format csv -d gpurun_out/prof/kt -- B --steps 3 --warmup 1", ""]
+            "command: rocprofv3 --kernel-trace --stats --output-format csv -d PROF/kt -- B --steps 3 --warmup 1", ""]
     per = collections.OrderedDict()
     rows = list(csv.DictReader(open(one(base, "kt", "**/*_kernel_trace.csv"))))
     rows.sort(key=lambda r: int(r["Start_Timestamp"]))
@@ -191,8 +191,8 @@ def main():
     copy_w = max(c["WRITE_SIZE"] for c in pick(wr, "copyBuffer"))
     out += ["## 2. bytes between the L2 and the fabric (HBM side), per dispatch",
             "commands: rocprofv3 --pmc TCC_EA0_RDREQ_32B_sum TCC_EA0_RDREQ_64B_sum TCC_EA0_RDREQ_128B_sum TCC_EA0_RDREQ_sum "
-            "--output-format csv -d gpurun_out/prof/rd -- B --steps 1 --warmup 0 --calib-copy",
-            "          rocprofv3 --pmc WRITE_SIZE --output-format csv -d gpurun_out/prof/wr -- B --steps 1 --warmup 0 --calib-copy",
+            "--output-format csv -d PROF/rd -- B --steps 1 --warmup 0 --calib-copy",
+            "          rocprofv3 --pmc WRITE_SIZE --output-format csv -d PROF/wr -- B --steps 1 --warmup 0 --calib-copy",
             "read bytes = 32 n32 + 128 n128 + 64 (n - n32 - n128)",
             f"check: the 1 GiB device copy reads {rd_bytes(copy) / 2**30:.4f} GiB by this expression "
             f"(n128 = {copy['TCC_EA0_RDREQ_128B_sum']:.0f}, n32 = {copy['TCC_EA0_RDREQ_32B_sum']:.0f}, n = "
