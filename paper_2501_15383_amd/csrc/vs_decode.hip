@@ -8,6 +8,8 @@
 //    its own two buffers (the next 32 keys are on their way while these are multiplied), waits for its own copies
 //    only, and there is no barrier until the waves of the workgroup fold their results.  One workgroup of four waves
 //    fills the LDS of a compute unit: 64 to 128 KB of copies in flight.
+//  * Where there is much to read the waves take two neighbouring KV heads side by side, whose rows lie next to each other
+//    (kDecSideBlocks).
 //  * Work is cut into equal shares of 64-key blocks over all requests and KV heads (a share may start in the
 //    middle of one and end in the middle of another), so caches of different lengths leave no workgroup idle.  Every
 //    workgroup finds its share from the lengths alone.  Partial results are folded by k_decode_combine; a (request, KV
@@ -16,15 +18,15 @@
 //    heads whose own list has the diagonal: the scores of the others are -inf), then the gathered columns head by head.
 // Measured on one MI355X, 28 query / 4 KV heads, head_dim 128, against the tile kernel of vs_attn.hip with the heads as rows of
 // its 128-row tiles (copies of a step shared by four waves of which one multiplied, a barrier per step, one range count for a
-// whole batch): one token at 5,003 keys 39 -> 15 us, at 1M keys 510 -> 382 (5.7 TB/s of K and V); 24 tokens at 2K to 64K keys
-// 395 -> 228 (5.5 TB/s); 8 tokens with index sets at 262,144 keys 1,042 -> 776 (lists 252 -> 29 of it).
+// whole batch): one token at 5,003 keys 39 -> 15 us, at 1M keys 510 -> 363 (5.9 TB/s of K and V); 24 tokens at 2K to 64K keys
+// 395 -> 215 (5.8 TB/s); 8 tokens with index sets at 262,144 keys 1,042 -> 776 (lists 252 -> 29 of it).
 #include "vs_common.h"
 
 namespace vs {
 
 constexpr int kDecThreads = 256;
 constexpr int kDecWaves = kDecThreads / 64;
-constexpr int kDecMinBlocks = 2;     // 64-key blocks per share at least: one 32-key chunk for every wave
+constexpr int kDecMinBlocks = 2;     // 64-key blocks per share at least, of all its KV heads: one 32-key chunk for every wave
 constexpr int kDecListThreads = 1024;
 constexpr int kDecListWords = 14336; // bitmap words of all heads of a group in LDS at a time
 
@@ -33,6 +35,7 @@ struct DecodeArgs {
   const vs_request* req;
   int32_t n_req;
   int32_t n_q_heads, n_kv_heads, group;
+  int32_t side, n_seg;    // neighbouring KV heads that the waves of a workgroup take side by side (dec_layout), n_kv_heads / side
   int64_t q_stride_head, k_stride_tok, k_stride_head, v_stride_tok, v_stride_head, o_stride_head;
   float scale_log2;
   int32_t v_budget, s_budget;
@@ -42,12 +45,12 @@ struct DecodeArgs {
   uint2* ent;             // [n_req][Hkv][ent_stride] (diagonal, heads that have it)
   int2* len;              // [n_req][Hkv] (entries, entries + tiles of 64 gathered columns)
   int32_t words, ent_stride;
-  // shares: plan[0] = blocks in all, plan[1] = shares, plan[2 + r] = blocks before request r; of one request without index sets the
-  // host knows them (one_T blocks, one_n shares; 0: the device finds them)
+  // shares: plan[0] = units in all (a unit: 64 keys of `side` KV heads), plan[1] = shares, plan[2 + r] = units before request r; of one request without index sets the
+  // host knows them (one_T units, one_n shares; 0: the device finds them)
   int64_t* plan;
   int64_t one_T, one_n;
-  float* part_o;          // [share + (request, KV head)][G][D]
-  float* part_ml;         // [share + (request, KV head)][G][2] (reference, sum)
+  float* part_o;          // [share + (request, segment)][side G][D]
+  float* part_ml;         // [share + (request, segment)][side G][2] (reference, sum)
 };
 
 __device__ __forceinline__ vs_request decode_request(const DecodeArgs& a, int r) {
@@ -68,7 +71,14 @@ __device__ __forceinline__ bool decode_takes(const DecodeArgs& a, const vs_reque
   return rq.s_idx == nullptr || (rq.v_idx && rq.v_cnt && rq.s_cnt);
 }
 __device__ __forceinline__ int decode_blocks(const vs_request& rq) { return (int)((rq.q_start + kBlock) / kBlock); }
-// share w of n covers blocks [w T / n, (w + 1) T / n)
+// units of segment x (side neighbouring KV heads) of request r: as many as its longest head has
+__device__ __forceinline__ int decode_seg_len(const DecodeArgs& a, int r, int x) {
+  const int2* const len = a.len + (int64_t)r * a.n_kv_heads + x * a.side;
+  int n = len[0].y;
+  for (int e = 1; e < a.side; ++e) n = len[e].y > n ? len[e].y : n;
+  return n;
+}
+// share w of n covers units [w T / n, (w + 1) T / n)
 // (quotients of 64 bits, most of which fit 32: a fifth of the instructions)
 __device__ __forceinline__ int64_t short_div(int64_t x, int64_t y) {
   return (uint64_t)(x | y) >> 32 ? x / y : (int64_t)((uint32_t)x / (uint32_t)y);
@@ -89,8 +99,8 @@ __device__ __forceinline__ void dec_dma_lane(uint32_t lds_addr, const void* ptr)
                :: "s"(__builtin_amdgcn_readfirstlane(lds_addr)), "v"(ptr) : "memory");
 }
 
-template <int D>
-__global__ __launch_bounds__(kDecThreads, 2) void k_decode(const DecodeArgs a) {
+template <int D, int SIDE>
+__device__ __forceinline__ void decode_body(const DecodeArgs& a) {
   constexpr int DCH = D / 8;         // 16-byte pieces per row
   constexpr int KS = D / 32;         // MFMA steps of K Q^T
   constexpr int DB = D / 16;         // 16-row blocks of O^T
@@ -114,9 +124,9 @@ __global__ __launch_bounds__(kDecThreads, 2) void k_decode(const DecodeArgs a) {
   auto blocks_of = [&](int r) -> int64_t {
     const vs_request rq = a.req ? a.req[r] : a.one;
     if (!decode_takes(a, rq)) return 0;
-    if (!rq.s_idx) return (int64_t)decode_blocks(rq) * a.n_kv_heads;
+    if (!rq.s_idx) return (int64_t)decode_blocks(rq) * a.n_seg;
     int64_t n = 0;
-    for (int g = 0; g < a.n_kv_heads; ++g) n += a.len[(int64_t)r * a.n_kv_heads + g].y;
+    for (int x = 0; x < a.n_seg; ++x) n += decode_seg_len(a, r, x);
     return n;
   };
   int64_t T = a.one_T, first = 0;
@@ -131,7 +141,8 @@ __global__ __launch_bounds__(kDecThreads, 2) void k_decode(const DecodeArgs a) {
     T = 0;
     for (int w = 0; w < kDecWaves; ++w) T += scan_s[w];
   }
-  int64_t n_share = (T + kDecMinBlocks - 1) / kDecMinBlocks;
+  constexpr int min_units = kDecMinBlocks / SIDE;
+  int64_t n_share = (T + min_units - 1) / min_units;
   if (n_share > (int64_t)gridDim.x) n_share = gridDim.x;
   if (blockIdx.x == 0 && tid == 0 && a.one_T == 0) { a.plan[0] = T; a.plan[1] = n_share; }
   if (a.one_T) {
@@ -178,34 +189,44 @@ __global__ __launch_bounds__(kDecThreads, 2) void k_decode(const DecodeArgs a) {
   // the piece of its row that the lane fetches (the slot, swizzled): copy e of a tile holds rows e RPG + lr
   const int vpc = lc ^ ((((lr / R) & 3) << 2) & (DCH - 1));
   auto k_piece = [&](int e) -> int { return lc ^ (((e * RPG + lr) / R) % DCH); };
+  // this wave's KV head in a segment, its place among the waves of that head, and their number
+  const int sub = wv % SIDE, w_of = wv / SIDE;
+  constexpr int w_n = kDecWaves / SIDE;
   int64_t left = u_end - u_begin;
-  int g = 0;
+  int sg = 0;
   bool fresh = true;   // the request's fields are to be read
   vs_request rq;
   int64_t blk = first;
   while (left > 0) {
     if (fresh) {
       rq = decode_request(a, r);
-      g = 0;
+      sg = 0;
       if (!decode_takes(a, rq)) { ++r; continue; }
       fresh = false;
     }
     const bool sparse = rq.s_idx != nullptr;
     const int64_t n_k = rq.q_start + 1;
-    int n_ent = decode_blocks(rq), seg_len = n_ent;
+    const int g = sg * SIDE + sub;   // this wave's KV head
+    int n_ent = decode_blocks(rq), own_len = n_ent, seg_len = n_ent;
     if (sparse) {
       const int2 l2 = a.len[(int64_t)r * a.n_kv_heads + g];
       n_ent = __builtin_amdgcn_readfirstlane(l2.x);
-      seg_len = __builtin_amdgcn_readfirstlane(l2.y);
+      own_len = __builtin_amdgcn_readfirstlane(l2.y);
+      seg_len = __builtin_amdgcn_readfirstlane(decode_seg_len(a, r, sg));
     }
-    if (blk >= seg_len) {   // the share starts in a later KV head of this request
+    if (blk >= seg_len) {   // the share starts in a later segment of this request
       blk -= seg_len;
-      if (++g == a.n_kv_heads) { ++r; fresh = true; }
+      if (++sg == a.n_seg) { ++r; fresh = true; }
       continue;
     }
     const int64_t take64 = seg_len - blk < left ? seg_len - blk : left;
-    const int b0 = (int)blk, b1 = (int)(blk + take64);
-    const bool whole = b0 == 0 && b1 == seg_len;
+    const bool whole = blk == 0 && take64 == seg_len;
+    // the same part of the head's own walk (lists of neighbouring heads differ in length)
+    int b0 = (int)blk, b1 = (int)(blk + take64);
+    if (own_len != seg_len) {
+      b0 = (int)short_div((int64_t)b0 * own_len, seg_len);
+      b1 = (int)short_div((int64_t)b1 * own_len, seg_len);
+    }
     const int h0 = g * a.group;
 
     // ---- Q^T operand: lane (head h0 + col, k-group g4); columns beyond the group repeat its first head and are not stored (zeros in
@@ -228,7 +249,7 @@ __global__ __launch_bounds__(kDecThreads, 2) void k_decode(const DecodeArgs a) {
     const int pos_in_block = (int)(rq.q_start % kBlock);
 
     // chunk c: 32 keys.  Dense: keys 32 c ...; with index sets entry c / 2 of the union list, then the columns.
-    int c = 2 * b0 + wv;
+    int c = 2 * b0 + w_of;
     int c_end = 2 * b1;
     if (!sparse && c_end > (int)((n_k + 31) / 32)) c_end = (int)((n_k + 31) / 32);
     const int cnt_cache = sparse ? rq.v_cnt[h0 + (lane < a.group ? lane : 0)] : 0;   // columns of head h0 + lane
@@ -327,11 +348,11 @@ __global__ __launch_bounds__(kDecThreads, 2) void k_decode(const DecodeArgs a) {
     // chunk's copies, which the compiler does not see, with it
 #pragma unroll
     for (int st = 0; st < KS; ++st) asm volatile("" : "+v"(qreg[st]));
-    for (int b = 0; c < c_end; c += kDecWaves, b ^= 1) {
+    for (int b = 0; c < c_end; c += w_n, b ^= 1) {
       Chunk nxt;
       nxt.keys = nxt.rows = 0u;
-      if (c + kDecWaves < c_end) {
-        nxt = issue(c + kDecWaves, b ^ 1);
+      if (c + w_n < c_end) {
+        nxt = issue(c + w_n, b ^ 1);
         // this chunk's copies are done when at most the next chunk's are outstanding
         if constexpr (NC == 8) asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
         else asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
@@ -412,9 +433,9 @@ __global__ __launch_bounds__(kDecThreads, 2) void k_decode(const DecodeArgs a) {
     l_run += __shfl_xor(l_run, 32);
     if (g4 == 0) { ml_s[wv][col][0] = m_run; ml_s[wv][col][1] = l_run; }
     __syncthreads();   // (all tiles are done with as well: the LDS takes the accumulators)
-    float M = ml_s[0][col][0];
+    float M = ml_s[sub][col][0];
 #pragma unroll
-    for (int w = 1; w < kDecWaves; ++w) M = fmaxf(M, ml_s[w][col][0]);
+    for (int w = 1; w < w_n; ++w) M = fmaxf(M, ml_s[sub + SIDE * w][col][0]);
     const float own = m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run - M);
     float* const fold = (float*)dec_lds;   // [wave][16 heads][D + 4]
 #pragma unroll
@@ -425,46 +446,54 @@ __global__ __launch_bounds__(kDecThreads, 2) void k_decode(const DecodeArgs a) {
       *(f32x4*)&fold[(wv * 16 + col) * (D + 4) + 16 * db + 4 * g4] = o4;
     }
     __syncthreads();
-    const int64_t slot = (int64_t)blockIdx.x + (int64_t)r * a.n_kv_heads + g;
-    for (int x = tid; x < a.group * (D / 4); x += kDecThreads) {
-      const int q = x / (D / 4), d = 4 * (x % (D / 4));
-      f32x4 o = *(const f32x4*)&fold[q * (D + 4) + d];
+    const int64_t slot = ((int64_t)blockIdx.x + (int64_t)r * a.n_seg + sg) * SIDE * a.group;
+    for (int x = tid; x < SIDE * a.group * (D / 4); x += kDecThreads) {
+      // query head qs of the segment: row q of the waves w0, w0 + side, ...
+      const int qs = x / (D / 4), w0 = SIDE > 1 ? qs / a.group : 0, q = qs - w0 * a.group, d = 4 * (x % (D / 4));
+      f32x4 o = *(const f32x4*)&fold[(w0 * 16 + q) * (D + 4) + d];
+      float Mq = ml_s[w0][q][0];
 #pragma unroll
-      for (int w = 1; w < kDecWaves; ++w) {
-        const f32x4 y = *(const f32x4*)&fold[(w * 16 + q) * (D + 4) + d];
+      for (int w = 1; w < w_n; ++w) {
+        const f32x4 y = *(const f32x4*)&fold[((w0 + SIDE * w) * 16 + q) * (D + 4) + d];
 #pragma unroll
         for (int e = 0; e < 4; ++e) o[e] += y[e];
+        Mq = fmaxf(Mq, ml_s[w0 + SIDE * w][q][0]);
       }
-      float Mq = ml_s[0][q][0];
-#pragma unroll
-      for (int w = 1; w < kDecWaves; ++w) Mq = fmaxf(Mq, ml_s[w][q][0]);
       float L = 0.f;
       if (Mq != -INFINITY)
 #pragma unroll
-        for (int w = 0; w < kDecWaves; ++w)
-          L += ml_s[w][q][0] == -INFINITY ? 0.f : ml_s[w][q][1] * __builtin_amdgcn_exp2f(ml_s[w][q][0] - Mq);
+        for (int w = 0; w < w_n; ++w) {
+          const float* const ml = ml_s[w0 + SIDE * w][q];
+          L += ml[0] == -INFINITY ? 0.f : ml[1] * __builtin_amdgcn_exp2f(ml[0] - Mq);
+        }
       if (whole) {
         const float inv = L > 0.f ? 1.0f / L : 0.f;
 #pragma unroll
         for (int e = 0; e < 4; ++e) o[e] *= inv;
-        *(bf16x4*)((__bf16*)rq.out + (int64_t)(h0 + q) * a.o_stride_head + d) = __builtin_convertvector(o, bf16x4);
-        if (rq.lse && d == 0) rq.lse[h0 + q] = L > 0.f ? (Mq + __builtin_amdgcn_logf(L)) * kLn2 : -INFINITY;
+        const int h = sg * SIDE * a.group + qs;
+        *(bf16x4*)((__bf16*)rq.out + (int64_t)h * a.o_stride_head + d) = __builtin_convertvector(o, bf16x4);
+        if (rq.lse && d == 0) rq.lse[h] = L > 0.f ? (Mq + __builtin_amdgcn_logf(L)) * kLn2 : -INFINITY;
       } else {
-        *(f32x4*)&a.part_o[(slot * a.group + q) * D + d] = o;
+        *(f32x4*)&a.part_o[(slot + qs) * D + d] = o;
         if (d == 0) {
-          a.part_ml[(slot * a.group + q) * 2] = Mq;
-          a.part_ml[(slot * a.group + q) * 2 + 1] = L;
+          a.part_ml[(slot + qs) * 2] = Mq;
+          a.part_ml[(slot + qs) * 2 + 1] = L;
         }
       }
     }
     __syncthreads();   // the LDS is reused by the next piece
     left -= take64;
     blk = 0;
-    if (++g == a.n_kv_heads) { ++r; fresh = true; }
+    if (++sg == a.n_seg) { ++r; fresh = true; }
   }
 }
 
-// out = sum_s O_s 2^(m_s - M) / sum_s l_s 2^(m_s - M) over the shares that a (request, KV head) lies in; one workgroup per
+template <int D>
+__global__ __launch_bounds__(kDecThreads, 2) void k_decode(const DecodeArgs a) { decode_body<D, 1>(a); }
+// two neighbouring KV heads side by side
+__global__ __launch_bounds__(kDecThreads, 2) void k_decode_pairs(const DecodeArgs a) { decode_body<128, 2>(a); }
+
+// out = sum_s O_s 2^(m_s - M) / sum_s l_s 2^(m_s - M) over the shares that a (request, segment of KV heads) lies in; one workgroup per
 // (query head, request), shares folded in a fixed order (run-to-run identical): wave w takes every NW-th share, then
 // the waves are added in order.  Bound by latency: the partial results of 8 NW shares are all on their way before the references
 // are compared (four waves, and the references first: one token at 5,003 keys 14.1 us with its two launches, 12.1 so and with the
@@ -473,22 +502,21 @@ __global__ __launch_bounds__(kDecThreads, 2) void k_decode(const DecodeArgs a) {
 template <int D, int NW>
 __global__ __launch_bounds__(64 * NW) void k_decode_combine(const DecodeArgs a) {
   const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int h = blockIdx.x, r = blockIdx.y, g = h / a.group, q = h - g * a.group;
+  const int h = blockIdx.x, r = blockIdx.y, rows = a.side * a.group, sg = h / rows, q = h - sg * rows;
   const vs_request rq = decode_request(a, r);
   if (!decode_takes(a, rq)) return;
   const int64_t T = a.one_T ? a.one_T : a.plan[0], n = a.one_T ? a.one_n : a.plan[1];
   int64_t from = a.one_T ? 0 : a.plan[2 + r];
   int seg_len = decode_blocks(rq);
   if (rq.s_idx) {
-    const int2* const len = a.len + (int64_t)r * a.n_kv_heads;
-    for (int x = 0; x < g; ++x) from += len[x].y;
-    seg_len = len[g].y;
+    for (int x = 0; x < sg; ++x) from += decode_seg_len(a, r, x);
+    seg_len = decode_seg_len(a, r, sg);
   } else {
-    from += (int64_t)g * seg_len;
+    from += (int64_t)sg * seg_len;
   }
   const int s0 = (int)share_of(from, n, T), s1 = (int)share_of(from + seg_len - 1, n, T);
   if (s0 == s1) return;   // finished by its one share
-  const int64_t row0 = ((int64_t)s0 + (int64_t)r * a.n_kv_heads + g) * a.group + q;   // row of share s: row0 + (s - s0) G
+  const int64_t row0 = ((int64_t)s0 + (int64_t)r * a.n_seg + sg) * rows + q;   // row of share s: row0 + (s - s0) rows
   const int cnt = s1 - s0 + 1;
   constexpr int E = D / 64, U = 8;
   float acc[E], L = 0.f, o[U][E], w[U], l[U];
@@ -496,7 +524,7 @@ __global__ __launch_bounds__(64 * NW) void k_decode_combine(const DecodeArgs a) 
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int s = sb + NW * u < cnt ? sb + NW * u : cnt - 1;
-      const int64_t row = row0 + (int64_t)s * a.group;
+      const int64_t row = row0 + (int64_t)s * rows;
       const float2 ml = *(const float2*)(a.part_ml + 2 * row);
       w[u] = ml.x;
       l[u] = ml.y;
@@ -504,9 +532,9 @@ __global__ __launch_bounds__(64 * NW) void k_decode_combine(const DecodeArgs a) 
       for (int e = 0; e < E; ++e) o[u][e] = a.part_o[row * D + 64 * e + lane];
     }
   };
-  float M = lane < cnt ? a.part_ml[2 * (row0 + (int64_t)lane * a.group)] : -INFINITY;
+  float M = lane < cnt ? a.part_ml[2 * (row0 + (int64_t)lane * rows)] : -INFINITY;
   fetch(wv);
-  for (int s = 64 + lane; s < cnt; s += 64) M = fmaxf(M, a.part_ml[2 * (row0 + (int64_t)s * a.group)]);
+  for (int s = 64 + lane; s < cnt; s += 64) M = fmaxf(M, a.part_ml[2 * (row0 + (int64_t)s * rows)]);
 #pragma unroll
   for (int d = 1; d < 64; d <<= 1) M = fmaxf(M, __shfl_xor(M, d));
 #pragma unroll
@@ -634,26 +662,34 @@ bool decode_fits(const vs_params& p) { return p.n_q_heads / p.n_kv_heads <= 16; 
 
 namespace {
 constexpr int kDecShares = 256;   // at most: one workgroup fills the LDS of a compute unit
+// From this many 64-key blocks on (of all requests and KV heads, as the host knows them) the waves of a workgroup take two neighbouring KV
+// heads side by side, rows of 256 bytes each: 512 bytes in one place are read faster than 256 (a bare copy loop of this shape 6.2 TB/s against
+// 5.5, with four heads no more).  28 / 4 heads of 128: one token at 1M keys 383 us -> 363, 300,000 keys 118.2 -> 115.0, 200,000 80.7 -> 79.2,
+// 100,000 45.0 -> 45.9 (so the line), 12,000 12.9 -> 15.2 (twice the partial results per head); 24 tokens at 2K to 64K keys 225 -> 214.
+// Heads of 64 (8 / 2, 300,000 keys): 36.5 -> 37.8, so not these.  With index sets the two walks drift apart and the time is the same.
+constexpr int64_t kDecSideBlocks = 8192;
 struct DecLayout {
   size_t part_ml, plan, len, ent, bm, total;
-  int32_t words, ent_stride, shares;
+  int32_t words, ent_stride, shares, side;
 };
 DecLayout dec_layout(const vs_params& p, int n_req, bool lists) {
   DecLayout l;
   const int64_t n_blk = ceil_div(p.q_start + p.q_len, (int64_t)kBlock);
-  const size_t G = (size_t)(p.n_q_heads / p.n_kv_heads), segs = (size_t)n_req * p.n_kv_heads;
-  const int64_t most = ceil_div((int64_t)segs * (n_blk + (lists ? (int64_t)G * ceil_div(p.vertical_budget, 64) : 0)), kDecMinBlocks);
+  l.side = p.head_dim == 128 && p.n_kv_heads % 2 == 0 && (int64_t)n_req * p.n_kv_heads * n_blk >= kDecSideBlocks ? 2 : 1;
+  const size_t G = (size_t)(p.n_q_heads / p.n_kv_heads), segs = (size_t)n_req * (p.n_kv_heads / l.side);
+  const int64_t most = ceil_div((int64_t)segs * (n_blk + (lists ? (int64_t)G * ceil_div(p.vertical_budget, 64) : 0)), kDecMinBlocks / l.side);
   l.shares = (int32_t)(most < kDecShares ? most : kDecShares);
   l.words = (int32_t)ceil_div(n_blk, 32);
   l.ent_stride = (int32_t)n_blk;
-  const size_t rows = ((size_t)l.shares + segs) * G;
+  const size_t rows = ((size_t)l.shares + segs) * l.side * G;
   size_t off = align_up(rows * p.head_dim * sizeof(float), 256);
   l.part_ml = off; off += align_up(rows * 2 * sizeof(float), 256);
   l.plan = off; off += align_up((2 + (size_t)n_req) * sizeof(int64_t), 256);
   l.len = l.ent = l.bm = off;
   if (lists) {
-    off += align_up(segs * sizeof(int2), 256);
-    l.ent = off; off += align_up(segs * (size_t)l.ent_stride * sizeof(uint2), 256);
+    const size_t heads = (size_t)n_req * p.n_kv_heads;
+    off += align_up(heads * sizeof(int2), 256);
+    l.ent = off; off += align_up(heads * (size_t)l.ent_stride * sizeof(uint2), 256);
     l.bm = off; off += align_up((size_t)n_req * p.n_q_heads * (size_t)l.words * sizeof(uint32_t), 256);
   }
   l.total = off;
@@ -670,6 +706,7 @@ hipError_t launch_decode(const vs_params& p, const vs_request* one, const vs_req
   if (one) a.one = *one;
   a.req = req; a.n_req = n_req;
   a.n_q_heads = p.n_q_heads; a.n_kv_heads = p.n_kv_heads; a.group = p.n_q_heads / p.n_kv_heads;
+  a.side = l.side; a.n_seg = p.n_kv_heads / l.side;
   a.q_stride_head = p.q_stride_head; a.o_stride_head = p.o_stride_head;
   a.k_stride_tok = p.k_stride_tok; a.k_stride_head = p.k_stride_head;
   a.v_stride_tok = p.v_stride_tok; a.v_stride_head = p.v_stride_head;
@@ -686,24 +723,28 @@ hipError_t launch_decode(const vs_params& p, const vs_request* one, const vs_req
   a.words = l.words; a.ent_stride = l.ent_stride;
   static DeviceOnce once;   // the opt-in to more than 64 KiB of LDS
   const hipError_t e = once.run([]() {
-    const hipError_t e1 = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_decode<128>),
-                                              hipFuncAttributeMaxDynamicSharedMemorySize, decode_lds_bytes<128>());
-    if (e1 != hipSuccess) return e1;
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_decode<64>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                               decode_lds_bytes<64>());
+    const void* const fns[3] = {reinterpret_cast<const void*>(&k_decode<128>), reinterpret_cast<const void*>(&k_decode_pairs),
+                                reinterpret_cast<const void*>(&k_decode<64>)};
+    for (int i = 0; i < 3; ++i) {
+      const hipError_t e1 = hipFuncSetAttribute(fns[i], hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                i < 2 ? decode_lds_bytes<128>() : decode_lds_bytes<64>());
+      if (e1 != hipSuccess) return e1;
+    }
+    return hipSuccess;
   });
   if (e != hipSuccess) return e;
   if (lists)
     hipLaunchKernelGGL(k_decode_lists, dim3((unsigned)p.n_kv_heads, (unsigned)n_req), dim3(kDecListThreads), 0, st, a);
   if (one && !lists) {   // as k_decode counts them
-    a.one_T = ceil_div(one->q_start + one->q_len, (int64_t)kBlock) * p.n_kv_heads;
-    a.one_n = ceil_div(a.one_T, kDecMinBlocks);
+    a.one_T = ceil_div(one->q_start + one->q_len, (int64_t)kBlock) * a.n_seg;
+    a.one_n = ceil_div(a.one_T, kDecMinBlocks / a.side);
     if (a.one_n > l.shares) a.one_n = l.shares;
   }
   const dim3 grid((unsigned)l.shares), cgrid((unsigned)p.n_q_heads, (unsigned)n_req);
-  const bool many = l.shares > 32 * (int64_t)n_req * p.n_kv_heads;
+  const bool many = l.shares > 32 * (int64_t)n_req * a.n_seg;
   if (p.head_dim == 128) {
-    hipLaunchKernelGGL(k_decode<128>, grid, dim3(kDecThreads), decode_lds_bytes<128>(), st, a);
+    if (l.side == 2) hipLaunchKernelGGL(k_decode_pairs, grid, dim3(kDecThreads), decode_lds_bytes<128>(), st, a);
+    else hipLaunchKernelGGL(k_decode<128>, grid, dim3(kDecThreads), decode_lds_bytes<128>(), st, a);
     if (many) hipLaunchKernelGGL((k_decode_combine<128, 8>), cgrid, dim3(512), 0, st, a);
     else hipLaunchKernelGGL((k_decode_combine<128, 4>), cgrid, dim3(256), 0, st, a);
   } else {

@@ -73,3 +73,37 @@ def test_shares_over_many_requests(n_req):
             continue
         ref = oracle.dense_attention(pb, q, k, v) if sets is None else oracle.sparse_attention(pb, q, k, v, *sets)
         assert_attn_close(g["out"], g["lse"], *ref, f"request {i} of {n_req}, s={pb.q_start}")
+
+
+@pytest.mark.parametrize("hq,hkv,s", [(14, 2, 262143), (24, 8, 65599), (21, 3, 180000)])
+def test_long_token_of_neighbouring_heads(hq, hkv, s):
+    """8,192 blocks and more: two KV heads side by side where their number is even."""
+    rng = np.random.default_rng(2200 + hkv)
+    pb, q, k, v, _ = _problem(rng, hq, hkv, 128, s, 1, 1, "dense")
+    got = vs.dense_causal_prefill(chunk_of(pb), dev(q), dev(k), dev(v), want_lse=True)
+    torch.cuda.synchronize()
+    assert_attn_close(*got, *oracle.dense_attention(pb, q, k, v), f"{hq}/{hkv} s={s}")
+
+
+def test_neighbouring_heads_of_many_requests():
+    """A table whose bounds take the path of neighbouring heads: dense and sparse tokens, the heads' lists of different lengths (and
+    without any line), shares that hold several requests."""
+    hq, hkv, d, bv, bs, n_req = 6, 2, 128, 40, 30, 300
+    rng = np.random.default_rng(2300)
+    reqs, gpu = [], []
+    for i in range(n_req):
+        s = int(rng.choice([0, 5, 63, 64, 200, 940]))
+        pb, q, k, v, sets = _problem(rng, hq, hkv, d, s, bv, bs, ("dense", "both", "none", "both")[i % 4])
+        if sets is not None and i % 4 == 3:   # the second KV head keeps a line of each kind, or only a column
+            sets = tuple(x.copy() for x in sets)
+            sets[1][3:] = np.minimum(sets[1][3:], 1)
+            sets[3][3:] = np.minimum(sets[3][3:], i // 4 % 2)
+        reqs.append((pb, q, k, v, sets))
+        gpu.append(dict(q=dev(q), k=dev(k), v=dev(v), q_start=s, out=torch.full((1, hq, d), -3.0, dtype=torch.bfloat16, device="cuda"),
+                        lse=torch.full((hq, 1), 7.0, device="cuda"), sets=None if sets is None else tuple(_t(x) for x in sets)))
+    ck = vs.Chunk(hq, hkv, d, 1, 940, 1.0 / np.sqrt(d), vertical_budget=bv, slash_budget=bs)
+    vs.attn_batch(ck, vs.request_table(gpu, "cuda"), n_req, gpu[0]["q"], gpu[0]["k"], gpu[0]["v"], gpu[0]["out"])
+    torch.cuda.synchronize()
+    for i, ((pb, q, k, v, sets), g) in enumerate(zip(reqs, gpu)):
+        ref = oracle.dense_attention(pb, q, k, v) if sets is None else oracle.sparse_attention(pb, q, k, v, *sets)
+        assert_attn_close(g["out"], g["lse"], *ref, f"request {i}, s={pb.q_start}")
