@@ -64,6 +64,12 @@ __device__ __forceinline__ int batch_find(const BatchPlan* plan, int n_req, int 
   return __builtin_amdgcn_readfirstlane(r);
 }
 
+// A piece of an uneven cut (own_cut): its unit, range and number of ranges, slot of partial results, and the key-block distances
+// [cc_lo, cc_hi] that it walks.
+struct OwnPiece {
+  int32_t unit, sp, n_sp, slot, cc_lo, cc_hi, pad[2];
+};
+
 struct AttnArgs {
   const __bf16* q;
   // Dual Chunk Attention (template parameter DCA): the chunk's queries rotated for the
@@ -81,6 +87,12 @@ struct AttnArgs {
   int32_t n_split, n_units, n_whole, first_piece;
   float* part_o;
   float* part_ml;
+  // Uneven cut of the cut units (own_cut; 0: the even one above): slots of partial results, steps that a unit's columns count for, and
+  // what k_attn_pieces leaves: the number of pieces (0: the even cut stays), the pieces, ranges and first slot of every cut unit
+  int32_t own_slots, col_steps;
+  int32_t* own_n;
+  OwnPiece* own_pieces;
+  int2* own_units;
   int32_t first_slot;   // BATCH: of the request's partial results
   // SPLIT: query heads of one KV group that share a tile (1, 2 or 4).  Chunks whose rows lie in one query block leave
   // half of a tile's waves (three quarters: at most 32 rows) without rows; these waves take further heads.
@@ -259,6 +271,86 @@ __device__ __forceinline__ void unit_of(const AttnArgs& a, int e, int& g, int& h
   h0 = g * a.group + (hs - g * a.n_hs) * a.pack;
 }
 
+// Cut units that follow one another in that order and belong to one list (a run, or what runs leave of a head): segments.
+__host__ __device__ __forceinline__ int cut_segment_of(int e, int n_qtiles, int lists) {
+  const int n_run = n_qtiles / kRun, n_rem = n_qtiles - n_run * kRun, lead = n_run * lists * kRun;
+  return e < lead ? e / kRun : n_run * lists + (n_rem ? (e - lead) / n_rem : 0);
+}
+// segment x of the cut units: its list, first unit and units (0: behind the last one)
+__device__ __forceinline__ void cut_segment(const AttnArgs& a, int x, int& list, int& e0, int& cnt) {
+  const int lists = a.n_q_heads / a.group * a.n_hs, n_run = a.n_qtiles / kRun, n_rem = a.n_qtiles - n_run * kRun;
+  const int runs = n_run * lists, s = cut_segment_of(a.n_whole, a.n_qtiles, lists) + x;
+  list = s < runs ? s % lists : s - runs;
+  e0 = s < runs ? s * kRun : runs * kRun + (s - runs) * n_rem;
+  const int end = e0 < a.n_units ? e0 + (s < runs ? kRun : n_rem) : e0;
+  e0 = e0 < a.n_whole ? a.n_whole : e0;
+  cnt = end - e0;
+}
+// Ranges by the lists' own lengths.  Heads differ in them (scattered slashes by a tenth, clustered ones by a factor of two), and with one
+// range count for all a launch of one round waits for the heads with the longest lists.  Lane x of the calling wave (all lanes) gets the
+// ranges n of each of the cnt units of segment x and the segment's first slot of partial results; pieces, most: of all, most ranges
+// of a unit.  n follows the length, for up to four rounds of 512 pieces; most = 0 where the even cut is to stay: lists equally long
+// (so that with everything selected the results are those of dense calls), or a gain of less than 5 % by this count.
+// 28 heads, clustered slashes, even -> uneven: 200 rows at 500K keys 1,588 us -> 1,080, 333 at 100K 656 -> 518, 1,000 at 300K 2,584 ->
+// 1,958, 2,000 at 150K 2,811 -> 2,390; lists that differ by a tenth or less within 1 %.
+constexpr int kOwnRounds = 4, kOwnSegments = 64;
+__device__ __forceinline__ void own_cut(const AttnArgs& a, int lane, int& n, int& cnt, int& slot, int& pieces, int& most) {
+  int list, e0;
+  cut_segment(a, lane, list, e0, cnt);
+  int len = 0;
+  if (cnt > 0) {
+    const int h0 = list / a.n_hs * a.group + list % a.n_hs * a.pack;
+    len = (int)a.bm_a[(int64_t)h0 * a.bm_stride + a.bm_words - 2] + a.col_steps;
+    len = len > 1 ? len : 1;
+  }
+  int mx = len, mn = cnt > 0 ? len : 1 << 30;
+  float total = (float)cnt * (float)len;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const int x = __shfl_xor(mx, d), y = __shfl_xor(mn, d);
+    mx = x > mx ? x : mx;
+    mn = y < mn ? y : mn;
+    total += __shfl_xor(total, d);
+  }
+  n = 0;
+  pieces = most = slot = 0;
+  if (mx == mn) return;
+  const int n_cut = a.n_units - a.n_whole;
+  // a piece's time beside its walk, writing and folding it: as attn_cut counts them
+  auto beside = [](int p) -> float {
+    return (float)kPieceSteps * (float)((p + kBatchSlots - 1) / kBatchSlots) + 8.f * (float)p / (float)kBatchSlots;
+  };
+  const float share = total / (float)kBatchSlots;
+  float best = 0.95f * ((float)mx / (float)a.n_split + beside(n_cut * a.n_split));
+  for (int r = 1; r <= kOwnRounds && r * kBatchSlots <= a.own_slots; ++r) {
+    if (r * kBatchSlots <= n_cut) continue;
+    // (one each and the rest by length, rounded down: never more than the slots)
+    int m = 1 + (int)((float)len * ((float)(r * kBatchSlots - n_cut) / total));
+    m = m > kMaxSplit ? kMaxSplit : m;
+    m = m > 1 + len / 8 ? 1 + len / 8 : m;
+    float longest = cnt > 0 ? (float)len / (float)m : 0.f;
+    int p = cnt * m;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      longest = fmaxf(longest, __shfl_xor(longest, d));
+      p += __shfl_xor(p, d);
+    }
+    const float c = fminf((float)((p + kBatchSlots - 1) / kBatchSlots) * longest, share + 0.5f * longest) + beside(p);
+    if (fmaxf(c, longest) < best) { best = fmaxf(c, longest); n = m; }
+  }
+  if (__builtin_amdgcn_readfirstlane(n) == 0) { n = 0; return; }
+  most = cnt > 0 ? n : 1;
+  int end = cnt * n;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const int x = __shfl_xor(most, d), y = __shfl_up(end, d);
+    most = x > most ? x : most;
+    end += lane >= d ? y : 0;
+  }
+  slot = end - cnt * n;
+  pieces = __builtin_amdgcn_readlane(end, 63);
+  most = __builtin_amdgcn_readfirstlane(most);
+}
 __device__ __forceinline__ bool bm_test(const uint32_t* bm, int i) {
   return (bm[i >> 5] >> (i & 31)) & 1u;
 }
@@ -363,14 +455,18 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
   int n_pieces = 0;
   if constexpr (BATCH) n_pieces = __builtin_amdgcn_readfirstlane(a0.plan[a0.n_req].first);
   else if constexpr (SPLIT) n_pieces = a0.n_whole - a0.first_piece + (a0.n_units - a0.n_whole) * a0.n_split;
+  if (SPLIT && !BATCH && a0.own_slots > 0) {
+    const int own = __builtin_amdgcn_readfirstlane(*a0.own_n);
+    if (own > 0) n_pieces = a0.n_whole - a0.first_piece + own;
+  }
   int q_grp = grp, q_pos = member;   // SPLIT: the queue and the place in it of the next piece
   for (int rnd = 0; SPLIT || rnd < n_gr; ++rnd) {
   int gr = 0, u = 0;
   uint32_t q_next = 0;
   if constexpr (SPLIT) {
     u = ((q_pos / a0.members) * 8 + q_grp) * a0.members + q_pos % a0.members;
-    // (a batch, whose pieces the host cannot count: fewer than workgroups are dealt evenly over the XCDs, as launch_attention does)
-    if (BATCH && n_pieces < (int)gridDim.x) {
+    // (pieces that the host cannot count: fewer than workgroups are dealt evenly over the XCDs, as launch_attention does)
+    if ((BATCH || a0.own_slots > 0) && n_pieces < (int)gridDim.x) {
       const int each = (n_pieces + 7) >> 3;
       u = member < each ? grp * each + member : n_pieces;
     }
@@ -384,7 +480,7 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
   AttnArgs a_req;
   if constexpr (BATCH) a_req = a0;
   const AttnArgs& a = BATCH ? a_req : a0;
-  int g, h, qt, sp = 0, slot = 0;
+  int g, h, qt, sp = 0, slot = 0, n_sp = 1, cc_lo = -1, cc_hi = 0;
   bool whole = true, none = false;   // none: no tile for this workgroup in this round
   if constexpr (SPLIT) {
     none = u >= n_pieces;
@@ -400,9 +496,21 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
     whole = u < a.n_whole;
     if (!whole && !none) {
       const int v = u - a.n_whole, n = a.n_units - a.n_whole;
-      sp = v / n;
-      e = a.n_whole + v - sp * n;
-      slot = BATCH ? v + a.first_slot : v;
+      if (!BATCH && a.own_slots > 0 && __builtin_amdgcn_readfirstlane(*a.own_n) > 0) {
+        const OwnPiece* const o = a.own_pieces + v;
+        e = __builtin_amdgcn_readfirstlane(o->unit);
+        sp = __builtin_amdgcn_readfirstlane(o->sp);
+        n_sp = __builtin_amdgcn_readfirstlane(o->n_sp);
+        slot = __builtin_amdgcn_readfirstlane(o->slot);
+        cc_lo = __builtin_amdgcn_readfirstlane(o->cc_lo);
+        cc_hi = __builtin_amdgcn_readfirstlane(o->cc_hi);
+      } else {
+        n_sp = a.n_split;
+        sp = v / n;
+        e = a.n_whole + v - sp * n;
+        slot = BATCH ? v + a.first_slot : v;
+      }
+      whole = n_sp == 1;
     }
     g = h = qt = 0;
     if (!none) unit_of(a, e, g, h, qt);
@@ -529,16 +637,19 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
   // ---- tile iterator (uniform over the workgroup, kept in scalar registers) -----------------
   // kind 0: slash tile, idx = cc, mask = query blocks that use it; kind 1: vertical tile,
   // idx = vt; kind 2: end.  Entries are fetched 64 at a time (one per lane), one batch ahead.
-  // With a key split this workgroup walks the entries with cc in [cc_lo, cc_end] and every
-  // n_split-th vertical tile; the first entry is searched for with 64 probes at a time (the list ascends
+  // With a key split this workgroup walks the entries with cc in [cc_lo, cc_end] (of n_sp ranges of equal distances, or an uneven
+  // cut's) and every n_sp-th vertical tile; the first entry is searched for with 64 probes at a time (the list ascends
   // in cc and ends in sentinels): three loads in a row for 16K entries, 14 by bisection.
   int cc_end = cc_last, ei0 = 0;
-  const int vstep = SPLIT && !whole ? a.n_split : 1;
+  const int vstep = SPLIT && !whole ? n_sp : 1;
   int vlin = sp - vstep;
   if (SPLIT && !whole) {
-    const int per = (cc_last + a.n_split) / a.n_split;  // ceil((cc_last + 1) / n_split)
-    const int cc_lo = sp * per;
-    cc_end = cc_lo + per - 1 < cc_last ? cc_lo + per - 1 : cc_last;
+    if (cc_lo < 0) {
+      const int per = (cc_last + n_sp) / n_sp;  // ceil((cc_last + 1) / n_sp)
+      cc_lo = sp * per;
+      cc_hi = cc_lo + per - 1 < cc_last ? cc_lo + per - 1 : cc_last;
+    }
+    cc_end = cc_hi;
     int lo = 0, hi = (int)a.ent_len - 1;  // the last entry is a sentinel: an answer always exists
     if (!BATCH && !a.ent) lo = hi = pack > 1 ? (cc_lo > NQB - 1 ? cc_lo - (NQB - 1) : 0) : cc_lo;
     while (lo < hi) {
@@ -1626,6 +1737,11 @@ bool attn_packed_decode(const vs_params& p, bool dense) {
 struct AttnCut {
   bool queue;
   int32_t pack, n_hs, n_qtiles, n_units, n_whole, n_split;
+  int32_t own_slots;   // slots for ranges by the lists' lengths (own_cut; 0: even ranges only)
+  int64_t slots() const {
+    const int64_t even = n_split > 1 ? (int64_t)(n_units - n_whole) * n_split : 0;
+    return even > own_slots ? even : own_slots;
+  }
 };
 static AttnCut attn_cut(const vs_params& p, bool dense, int forced) {
   const bool one = attn_packed_decode(p, dense);
@@ -1680,15 +1796,31 @@ static AttnCut attn_cut(const vs_params& p, bool dense, int forced) {
   if (c.n_split == 1) c.n_whole = c.n_units;
   c.queue = units <= slots || best < 0.97 * (double)ceil_div(units, slots) * (steps + kPieceSteps);
   if (!c.queue) { c.pack = 1; c.n_hs = group; c.n_split = 1; }
+  // Uneven ranges where pieces are long enough for a launch that finds them (5 us; a range of 64 blocks takes 120, less where lists are
+  // short); whole units below a round, which need the fold then as well, from 1,024 blocks on.  Not with one query tile: even ranges
+  // of the heads of a KV group lie at the same keys, which the XCD's L2 reads once for them (64 rows at 1M keys, lists that differ by 8 %:
+  // 2,024 us, 2,101 uneven).  Nor where the even cut has several rounds: a slot takes the next piece when it is done, and the far
+  // pieces, which come last, are the short ones (11,109 clustered rows at 500K keys 16.9 ms, 17.2 uneven).
+  if (c.queue && !dense && n_qtiles > 1 && n_blk >= 64 * (int64_t)c.n_split && (c.n_split > 1 || n_blk >= 1024) &&
+      (c.n_units - (c.n_split > 1 ? c.n_whole : 0)) * (int64_t)c.n_split <= slots) {
+    if (c.n_split == 1) c.n_whole = 0;   // (units fit a round)
+    const int lists = p.n_kv_heads * c.n_hs;
+    if (cut_segment_of(c.n_units - 1, c.n_qtiles, lists) - cut_segment_of(c.n_whole, c.n_qtiles, lists) < kOwnSegments) {
+      const int64_t rounds = ceil_div(8 * (int64_t)(c.n_units - c.n_whole), slots);   // about eight pieces of a unit
+      c.own_slots = (int32_t)(slots * (rounds < kOwnRounds ? rounds : kOwnRounds));
+    } else if (c.n_split == 1) {
+      c.n_whole = c.n_units;
+    }
+  }
   return c;
 }
 static AttnCut attn_cut(const vs_params& p, bool dense) { return attn_cut(p, dense, g_key_split.load(std::memory_order_relaxed)); }
 // Partial results of the cut units: a tile's rows for every range.
 size_t attn_split_bytes(const vs_params& p, bool dense) {
   const AttnCut c = attn_cut(p, dense);
-  if (!c.queue || c.n_split == 1) return 0;
-  const size_t rows = (size_t)(c.n_units - c.n_whole) * c.n_split * kTileRows;
-  return align_up(rows * p.head_dim * sizeof(float), 256) + align_up(rows * 2 * sizeof(float), 256);
+  if (!c.queue || c.slots() == 0) return 0;
+  const size_t rows = (size_t)c.slots() * kTileRows, own = c.own_slots ? 256 + kMaxPieces * (sizeof(int2) + sizeof(OwnPiece)) : 0;
+  return align_up(rows * p.head_dim * sizeof(float), 256) + align_up(rows * 2 * sizeof(float), 256) + own;
 }
 // counters, schedule
 size_t attn_sync_bytes(const vs_params& p) { return attn_counter_bytes(p) + attn_sched_bytes(p); }
@@ -1725,6 +1857,16 @@ __global__ __launch_bounds__(256) void k_attn_combine(const AttnArgs a0) {
   if (e >= n_fold) continue;
   int g, h, qt;
   unit_of(a, a.n_whole + e, g, h, qt);
+  int n_sp = a.n_split, slot0 = BATCH ? e + a.first_slot : e, slot_step = n_fold;
+  if (!BATCH && a.own_slots > 0) {
+    if (__builtin_amdgcn_readfirstlane(*a.own_n) > 0) {
+      const int2 own = a.own_units[e];
+      n_sp = __builtin_amdgcn_readfirstlane(own.x);
+      slot0 = __builtin_amdgcn_readfirstlane(own.y);
+      slot_step = 1;
+    }
+    if (n_sp == 1) continue;   // (its walk was whole)
+  }
   for (int part = task % WPU; part < task % WPU + run; ++part) {
   // (the row of the tile as k_attention deals them out)
   const int lrow = part * (1024 / D) + threadIdx.x / LR;
@@ -1738,13 +1880,13 @@ __global__ __launch_bounds__(256) void k_attn_combine(const AttnArgs a0) {
   const int64_t row = (int64_t)qt * kTileRows + 64 * t + il0 + (lrow & 31) - a.row_pad;
   if (row < 0 || row >= a.q_rows || h - g * a.group + th >= a.group) continue;
   const int hw = h + th;
-  const int64_t at = (int64_t)(BATCH ? e + a.first_slot : e) * kTileRows, step = (int64_t)n_fold * kTileRows;
+  const int64_t at = (int64_t)slot0 * kTileRows, step = (int64_t)slot_step * kTileRows;
   constexpr int U = 8, NB = kMaxSplit / LR;   // pieces whose accumulators are under way together; references per lane
   const float* const po = a.part_o + at * D + (lrow * D + d);   // (at: the same in every lane)
   f32x4 o[U];
   auto fetch = [&](int sp) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) o[u] = *(const f32x4*)(po + step * (sp + u < a.n_split ? sp + u : a.n_split - 1) * D);
+    for (int u = 0; u < U; ++u) o[u] = *(const f32x4*)(po + step * (sp + u < n_sp ? sp + u : n_sp - 1) * D);
   };
   fetch(0);
   // lane x of the row: pieces x, LR + x, ...; their weights wait in LDS (a row's lanes are of one wave)
@@ -1755,7 +1897,7 @@ __global__ __launch_bounds__(256) void k_attn_combine(const AttnArgs a0) {
   for (int b = 0; b < NB; ++b) {
     m[b] = -INFINITY;
     l[b] = 0.f;
-    if (b * LR < a.n_split && b * LR + lr < a.n_split) {
+    if (b * LR < n_sp && b * LR + lr < n_sp) {
       const float2 ml = *(const float2*)(a.part_ml + 2 * (at + lrow + step * (b * LR + lr)));
       m[b] = ml.x;
       l[b] = ml.y;
@@ -1769,14 +1911,14 @@ __global__ __launch_bounds__(256) void k_attn_combine(const AttnArgs a0) {
   for (int b = 0; b < NB; ++b) {
     const float w = __builtin_amdgcn_exp2f(m[b] - M0);   // (a piece without live keys: weight 0, and zeros in its slot)
     L += l[b] * w;
-    if (b * LR < a.n_split) ws[b * LR + lr] = w;         // (0 behind the last piece)
+    if (b * LR < n_sp) ws[b * LR + lr] = w;         // (0 behind the last piece)
   }
 #pragma unroll
   for (int x = 1; x < LR; x <<= 1) L += __shfl_xor(L, x);
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma clang loop unroll(disable)
-  for (int sp = 0; sp < a.n_split; sp += U) {
+  for (int sp = 0; sp < n_sp; sp += U) {
     if (sp > 0) fetch(sp);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -1793,6 +1935,71 @@ __global__ __launch_bounds__(256) void k_attn_combine(const AttnArgs a0) {
     a.lse[(int64_t)hw * a.q_rows + row] = L > 0.f ? (M + __builtin_amdgcn_logf(L)) * kLn2 : -INFINITY;
   }  // parts
   }  // tasks
+}
+
+// The pieces of an uneven cut (own_cut), one workgroup.  They lie in `most` slices, one after the other: in slice z those of the segments
+// in turn whose range falls into it, f(z) = z n / most of a unit's ranges lie before it.  So pieces that are walked at the same time read
+// the same part of the cache, as with the even cut.  A range holds as many entries as the others of its unit: of equal distances
+// the near ones have twice the entries of the far ones where slashes are clustered.  (In the attention kernel itself, 2 us of every
+// workgroup, the code spilled 31 registers of the walk.)
+__global__ __launch_bounds__(1024) void k_attn_pieces(const AttnArgs a) {
+  __shared__ int32_t n_s[kOwnSegments], cnt_s[kOwnSegments], e0_s[kOwnSegments], slot_s[kOwnSegments], pieces_s, most_s;
+  __shared__ int32_t reach_s[kMaxPieces], table[kMaxPieces];   // of a cut unit: entries up to its last block; of a piece: unit, range
+  const int tid = threadIdx.x, lists = a.n_q_heads / a.group * a.n_hs, seg0 = cut_segment_of(a.n_whole, a.n_qtiles, lists);
+  if (tid < 64) {
+    int n, cnt, slot, pieces, most, list, e0;
+    own_cut(a, tid, n, cnt, slot, pieces, most);
+    cut_segment(a, tid, list, e0, cnt);
+    n_s[tid] = n; cnt_s[tid] = cnt; e0_s[tid] = e0; slot_s[tid] = slot;
+    if (tid == 0) { pieces_s = pieces; most_s = most; *a.own_n = pieces; }
+  }
+  __syncthreads();
+  const int pieces = pieces_s, most = most_s, n_cut = a.n_units - a.n_whole;
+  if (pieces == 0) return;
+  const int n_seg = cut_segment_of(a.n_units - 1, a.n_qtiles, lists) - seg0 + 1;
+  auto list_of = [&](int e, int& cc_last) -> const uint32_t* {
+    int g, h, qt;
+    unit_of(a, e, g, h, qt);
+    cc_last = (int)(a.q_start / 64) + qt * kAttnQBlocks + kAttnQBlocks - 1;
+    return a.ent + (int64_t)(g * a.n_hs + (h - g * a.group) / a.pack) * a.ent_stride;
+  };
+  for (int j = tid; j < n_cut; j += 1024) {
+    const int e = a.n_whole + j, x = cut_segment_of(e, a.n_qtiles, lists) - seg0;
+    a.own_units[j] = make_int2(n_s[x], slot_s[x] + (e - e0_s[x]) * n_s[x]);
+    int cc_last;
+    const uint32_t* const ent = list_of(e, cc_last);
+    int lo = 0, hi = (int)a.ent_len - 1;   // the last entry is a sentinel
+    while (lo < hi) {
+      const int mid = (lo + hi) >> 1;
+      if ((int)(ent[mid] >> 4) <= cc_last) lo = mid + 1;
+      else hi = mid;
+    }
+    reach_s[j] = lo;
+  }
+  auto before = [&](int z, int n) -> int { return (z * n * ((65535 + most) / most)) >> 16; };   // (exact for at most 128 ranges)
+  for (int t = tid; t < n_seg * most; t += 1024) {
+    const int sp = t / n_seg, x = t - sp * n_seg, n = n_s[x];
+    if (sp >= n) continue;
+    int z = sp * most / n;
+    while (before(z + 1, n) <= sp) ++z;
+    while (before(z, n) > sp) --z;
+    int at = 0;
+    for (int y = 0; y < n_seg; ++y) at += cnt_s[y] * (y < x ? before(z + 1, n_s[y]) : before(z, n_s[y]));
+    for (int i = 0; i < cnt_s[x]; ++i) table[at + i] = (e0_s[x] - a.n_whole + i) | sp << 16;
+  }
+  __syncthreads();
+  for (int v = tid; v < pieces; v += 1024) {
+    const int j = table[v] & 0xFFFF, sp = table[v] >> 16, e = a.n_whole + j, x = cut_segment_of(e, a.n_qtiles, lists) - seg0, n = n_s[x];
+    int cc_last;
+    const uint32_t* const ent = list_of(e, cc_last);
+    const int all = reach_s[j], each = (all + n - 1) / n, from = sp * each, to = from + each < all ? from + each : all;
+    OwnPiece o = {};
+    o.unit = e; o.sp = sp; o.n_sp = n;
+    o.slot = slot_s[x] + (e - e0_s[x]) * n + sp;
+    o.cc_lo = from < to ? (int)(ent[from] >> 4) : 0;
+    o.cc_hi = from < to ? (int)(ent[to - 1] >> 4) : -1;
+    a.own_pieces[v] = o;
+  }
 }
 
 // Which group takes which group-round.  Heads differ in the length of their block lists (by a
@@ -2017,11 +2224,17 @@ hipError_t launch_attention(const vs_params& p, const void* q, const DcaArgs* dc
   if (attn_listless(p, dense, cut, members)) a.ent = nullptr;
   a.n_split = cut.n_split;
   a.part_o = a.part_ml = nullptr;
-  if (cut.queue && a.n_split > 1) {
+  a.own_slots = cut.own_slots;
+  a.own_n = nullptr; a.own_units = nullptr; a.own_pieces = nullptr;
+  a.col_steps = 2 * cut.pack * (int)ceil_div(p.vertical_budget < a.n_k ? p.vertical_budget : a.n_k, 64);
+  if (cut.queue && cut.slots() > 0) {
     if (!split_ws) return hipErrorInvalidValue;
-    const size_t rows = (size_t)(a.n_units - a.n_whole) * a.n_split * kTileRows;
+    const size_t rows = (size_t)cut.slots() * kTileRows;
     a.part_o = (float*)split_ws;
     a.part_ml = (float*)((char*)split_ws + align_up(rows * p.head_dim * sizeof(float), 256));
+    a.own_n = (int32_t*)((char*)a.part_ml + align_up(rows * 2 * sizeof(float), 256));
+    a.own_units = (int2*)(a.own_n + 64);
+    a.own_pieces = (OwnPiece*)(a.own_units + kMaxPieces);
   }
   a.queue = (uint32_t*)sync_ws;
   a.sync_blocks = attn_sync_blocks(p);
@@ -2062,14 +2275,15 @@ hipError_t launch_attention(const vs_params& p, const void* q, const DcaArgs* dc
   }
   {
     const int64_t pieces = a.n_whole - a.first_piece + (int64_t)(a.n_units - a.n_whole) * a.n_split;
-    a.members = pieces < 8 * (int64_t)members ? (int)ceil_div(pieces, 8) : members;
+    a.members = pieces < 8 * (int64_t)members && !a.own_slots ? (int)ceil_div(pieces, 8) : members;
     a.n_wg = 8 * a.members;
     a.n_full = a.n_rem = a.n_gr = 0;
+    if (a.own_slots) hipLaunchKernelGGL(k_attn_pieces, dim3(1), dim3(1024), 0, st, a);
     if (p.head_dim == 128) { if (dca) VS_ATTN_LAUNCH(128, true, true); else VS_ATTN_LAUNCH(128, false, true); }
     else { if (dca) VS_ATTN_LAUNCH(64, true, true); else VS_ATTN_LAUNCH(64, false, true); }
   }
 #undef VS_ATTN_LAUNCH
-  if (a.n_split > 1) {
+  if (a.n_split > 1 || a.own_slots) {
     const dim3 cgrid((unsigned)((int64_t)(a.n_units - a.n_whole) * (p.head_dim == 128 ? combine_parts<128>() : combine_parts<64>())));
     if (p.head_dim == 128) hipLaunchKernelGGL(k_attn_combine<128>, cgrid, dim3(256), 0, st, a);
     else hipLaunchKernelGGL(k_attn_combine<64>, cgrid, dim3(256), 0, st, a);

@@ -182,6 +182,48 @@ def test_ranges_that_are_asked_for_of_many_units():
     assert ((a.float() - b.float()).norm(dim=2) <= 2e-2 * b.float().norm(dim=2)).all() and (la - lb).abs().max().item() < 1e-4
 
 
+# heads whose lists differ by a factor of ten, and one with everything selected: ranges by the lists' own lengths (k_attn_pieces), of
+# units in several ranges (128 units), of units that are whole with even ranges (448), and of 528 of which 512 are whole units in front
+@pytest.mark.parametrize("hq,hkv,c,s,chunk", [(32, 2, 450, 20007, 0), (32, 2, 1792, 66000, 0), (8, 1, 65 * 128 - 9, 50009, 0),
+                                              (32, 2, 450, 20007, 6400)])
+def test_ranges_by_the_lists_own_lengths(hq, hkv, c, s, chunk):
+    d, n = 64, s + c
+    rng = np.random.default_rng(3130)
+    qs = [rand_bf16(rng, (c, hq, d)) for _ in range(3 if chunk else 1)]
+    k = rand_bf16(rng, (n, hkv, d)); v = rand_bf16(rng, (n, hkv, d))
+    pb = oracle.Problem(hq, hkv, d, c, s, 1.0 / np.sqrt(d), vertical_budget=100, slash_budget=2000)
+    vi = np.full((hq, 100), -1, np.int32); si = np.full((hq, 2000), -1, np.int32)
+    vc = rng.integers(1, 101, hq).astype(np.int32); sc = np.zeros(hq, np.int32)
+    for h in range(hq):
+        vi[h, :vc[h]] = np.sort(np.concatenate([[0], 1 + rng.choice(n - 1, vc[h] - 1, replace=False)]))
+        far = n // 16 if h % 4 == 1 else n   # (clustered)
+        offs = np.union1d(np.arange(64), rng.choice(far, 1900 if h % 4 == 2 else 20 + 5 * h, replace=False))
+        if h == 3: offs = np.minimum(np.arange(0, n + 63, 64), n - 1)   # every diagonal
+        sc[h] = len(offs)
+        si[h, :sc[h]] = offs
+    dca = (dev(qs[1]), dev(qs[2]), chunk, 640) if chunk else None
+    args = (chunk_of(pb), dev(qs[0]), dev(k), dev(v), *[_t(x) for x in (vi, vc, si, sc)])
+    size = vs.workspace_bytes(chunk_of(pb), vs.VS_WS_SPARSE)
+    out, lse = vs.sparse_attn_prefill(*args, want_lse=True, dca=dca)
+    again, lse_again = vs.sparse_attn_prefill(*args, want_lse=True, dca=dca)
+    vs.set_option(vs.VS_OPT_ATTN_KEY_SPLIT, 1)
+    try:
+        assert size > vs.workspace_bytes(chunk_of(pb), vs.VS_WS_SPARSE)   # (it was cut)
+        one, lse_one = vs.sparse_attn_prefill(*args, want_lse=True, dca=dca)
+    finally:
+        vs.set_option(vs.VS_OPT_ATTN_KEY_SPLIT, 0)
+    torch.cuda.synchronize()
+    assert torch.equal(out, again) and torch.equal(lse, lse_again)
+    # both within the rounding of bf16 probabilities and outputs
+    a, b = out.float(), one.float()
+    assert ((a - b).norm(dim=2) <= 2e-2 * b.norm(dim=2)).all() and (lse - lse_one).abs().max().item() < 1e-4
+    rows, heads = [0, 127, 128, c // 2, c - 1], [0, 1, 2, 3, hq - 1]
+    at = torch.tensor(rows, device="cuda")
+    ref = oracle.sparse_attention(pb, qs[0], k, v, vi, vc, si, sc, heads=heads, rows=rows,
+                                  **(dict(dca=oracle.Dca(chunk, 640, qs[1], qs[2])) if chunk else {}))
+    assert_attn_close(out[at][:, heads], lse[heads][:, at], *ref, f"C={c} s={s}")
+
+
 # one KV head, 64 rows and as many keys as whole units keep pace from: 515 tiles of two heads, 512 of them whole and the last
 # three cut; and the same heads behind a start inside a block (two query blocks: no sharing, 1,030 units)
 @pytest.mark.parametrize("s", [4095 * 64, 4096 * 64 + 9])
