@@ -1316,16 +1316,15 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
 // has tiles.  The first workgroup of a batch writes its plan (write_plan), the lists follow.  The first workgroup also
 // clears the n_zero words at `zero` (the attention launch's counters).
 //
-// A sparse list is one workgroup's (part 0) and bound by latency, not bytes (6,096 offsets
-// in, 16K bits and up to 64 KB of entries out).  The bitmap is collected in LDS, kBlWin words at a
-// time: neighbouring offsets fall into the same few words, and the same OR-ing done with atomics in
-// global memory stood in line there (110-228 us for 28-40 heads at 256K-1M keys by where the
-// offsets crowd, against 12-15 us now).  Entries are then written a 64-bit word pair at a time with
-// a lane per bit, so that the stores of a wave are contiguous.  A dense list needs no collecting and
+// A sparse list is one workgroup's (part 0) and bound by latency and instructions, not bytes (6,096 offsets of a head
+// in, 16K bits and up to 64 KB of entries out).  Diagonals are collected as bytes in LDS (collect_flags): 28 heads, 20,000 keys
+// 8 us -> 6, four heads per list, 300,000 keys, 30 -> 14, the lists of 32 requests 36 -> 22.  Entries are written 64 diagonals at a time
+// with a lane per diagonal, so that the stores of a wave are contiguous.  A dense list needs no collecting and
 // is cut into kBlDensePart entries per workgroup.
 // ---------------------------------------------------------------------------------------------
 constexpr int kBlThreads = 1024;
-constexpr int kBlWin = 4096;        // bitmap words in LDS at a time (8.4M keys; shared by packed heads)
+constexpr int kBlWin = 16384 + 64;  // diagonals of packed heads in LDS at a time (1M keys and what a bitmap has behind them; of one head
+                                    // four times as many)
 constexpr int kBlDensePart = 4096;  // entries of a dense list per workgroup
 constexpr int kListGroups = 4096;   // workgroups for the lists of a batch, about
 struct ListArgs {
@@ -1511,119 +1510,69 @@ __device__ __forceinline__ bool build_list(const ListArgs& a, int x0) {
   }
   if (part != 0) return false;
 
-  __shared__ uint32_t aw[kBlWin + 2];   // aw[1 + w]: bitmap word w0 + w; aw[0]: the word before the window
+  // A byte per diagonal of the window (of four heads side by side with pack > 1), which begins with the last diagonal before it; behind
+  // it what lies outside.  Every wave has consecutive groups of 64 diagonals, a lane per diagonal.
+  static_assert(NQB == 2, "an entry has the diagonals of two query blocks");
+  __shared__ __attribute__((aligned(16))) uint8_t flags[4 * (kBlWin + 64)];
   __shared__ uint32_t wsum[NW];
-  uint32_t running = 0;
-  if (pack > 1) {
-    // one bitmap of `win` words per head in LDS
-    const int win = kBlWin / 4;
-    for (int w0 = 0; w0 < n_words - 2; w0 += win) {
-      const int nw = n_words - 2 - w0 < win ? n_words - 2 - w0 : win;
-      for (int w = tid; w < 4 * win; w += kBlThreads) aw[w] = 0u;
-      __syncthreads();
-      for (int p = 0; p < n_in; ++p) {
-        const int cnt = s_cnt[h0 + p];
-        const int32_t* const so = s_idx + (int64_t)(h0 + p) * a.s_budget;
-        for (int i = tid; i < cnt; i += kBlThreads)
-          list_bits(so[i], i > 0 ? so[i - 1] : -1, n_blk, [&](int ad) {
-            const int x = (ad >> 5) - w0;
-            if (x >= 0 && x < nw) atomicOr(&aw[p * win + x], 1u << (ad & 31));
-          });
-      }
-      __syncthreads();
-      for (int p = 0; p < n_in; ++p)
-        for (int w = tid; w < nw; w += kBlThreads) A[(int64_t)p * n_words + w0 + w] = aw[p * win + w];
-      // (heads beyond n_in have no bits; words beyond nw neither, up to the next power of two that a wave reads)
-      const int wg = (((nw + 31) >> 5) + NW - 1) / NW, wlo = wv * wg * 32;
-      auto listed = [&](int w) -> uint32_t {
-        return w < nw ? aw[w] | aw[win + w] | aw[2 * win + w] | aw[3 * win + w] : 0u;
-      };
-      uint32_t c = 0;
-      for (int g = 0; g < wg; g += 2) c += g + (lane >> 5) < wg ? __popc(listed(wlo + 32 * g + lane)) : 0u;
-#pragma unroll
-      for (int d = 1; d < 64; d <<= 1) c += __shfl_xor(c, d);
-      if (lane == 0) wsum[wv] = c;
-      __syncthreads();
-      uint32_t pos = running, total = 0;
-      for (int x = 0; x < NW; ++x) {
-        if (x < wv) pos += wsum[x];
-        total += wsum[x];
-      }
-      for (int w = wlo; w < wlo + 32 * wg && w < nw; w += 2) {
-        const uint64_t m = (uint64_t)listed(w) | ((uint64_t)listed(w + 1) << 32);
-        const int ww = lane < 32 ? w : (w + 1 < nw ? w + 1 : w);
-        uint32_t mask = 0;
-#pragma unroll
-        for (int p = 0; p < 4; ++p) mask |= ((aw[p * win + ww] >> (lane & 31)) & 1u) << p;
-        if ((m >> lane) & 1ull)
-          E[pos + __popcll(m & ((1ull << lane) - 1ull))] = ((uint32_t)(32 * (w0 + w) + lane + NQB - 1) << 4) | mask;
-        pos += __popcll(m);
-      }
-      running += total;
-      __syncthreads();   // wsum and aw are rewritten by the next window
-    }
-    for (int i = running + tid; i < ent_stride; i += kBlThreads) E[i] = kEntSentinel;
-    if (tid < n_in) { A[(int64_t)tid * n_words + n_words - 1] = 0u; A[(int64_t)tid * n_words + n_words - 2] = running; }
-    return true;
-  }
-  const int cnt = s_cnt[h0];
-  const int32_t* const so = s_idx + (int64_t)h0 * a.s_budget;
-  uint32_t before = 0;
-  for (int w0 = 0; w0 < n_words - 2; w0 += kBlWin) {
-    const int nw = n_words - 2 - w0 < kBlWin ? n_words - 2 - w0 : kBlWin;
-    for (int w = tid; w <= nw; w += kBlThreads) aw[w] = w ? 0u : before;
+  uint32_t running = 0, before = 0;
+  const int shift = pack > 1 ? 2 : 0, win = pack > 1 ? kBlWin : 4 * kBlWin;
+  for (int b0 = 0; b0 < 32 * (n_words - 2); b0 += win) {
+    const int bits = 32 * (n_words - 2) - b0, n_grp = ((bits < win ? bits : win) + 63) >> 6;
+    for (int x = tid; x <= n_grp << (2 + shift); x += kBlThreads) ((u32x4*)flags)[x] = u32x4{x ? 0u : before, 0u, 0u, 0u};
     __syncthreads();
-    for (int i = tid; i < cnt; i += kBlThreads)
-      list_bits(so[i], i > 0 ? so[i - 1] : -1, n_blk, [&](int ad) {
-        const int x = (ad >> 5) - w0;
-        if (x >= 0 && x < nw) atomicOr(&aw[1 + x], 1u << (ad & 31));
-      });
+    uint8_t* const f = flags + (1 << shift);
+    const int n_in_win = n_blk - b0 < win ? (n_blk > b0 ? n_blk - b0 : 0) : win;
+    if (pack > 1) collect_flags<kBlThreads, 16>(f, shift, b0, n_in_win, win, s_idx + (int64_t)h0 * a.s_budget, s_cnt + h0, a.s_budget, n_in);
+    else collect_flags<kBlThreads, 8>(f, 0, b0, n_in_win, win, s_idx + (int64_t)h0 * a.s_budget, s_cnt + h0, a.s_budget, 1);
     __syncthreads();
-    for (int w = tid; w < nw; w += kBlThreads) A[w0 + w] = aw[1 + w];
-    before = aw[nw];
-    // a wave's words: wg groups of 32 words, starting at word wlo
-    const int wg = (((nw + 31) >> 5) + NW - 1) / NW, wlo = wv * wg * 32;
-    auto listed = [&](int w) -> uint32_t {  // entries cc = 32 (w0 + w) .. + 31 of the list
-      if (w >= nw) return 0u;
-      const uint32_t cur = aw[1 + w], prev = aw[w];
-      uint32_t u = cur;
-#pragma unroll
-      for (int sft = 1; sft < NQB; ++sft) u |= (cur << sft) | (prev >> (32 - sft));
-      return u;
+    // the mask of a diagonal's entry: the heads that have it, or, of one head, bit t: diagonal b0 + x - 1 + t
+    auto mask_of = [&](int x) -> uint32_t {
+      if (pack > 1) return (((const uint32_t*)f)[x] * 0x01020408u >> 24) & 15u;   // (bytes of 0 and 1 to bits)
+      return (uint32_t)flags[x] | (uint32_t)flags[x + 1] << 1;
     };
+    const int each = (n_grp + NW - 1) / NW, g0 = wv * each, g1 = g0 + each < n_grp ? g0 + each : n_grp;
     uint32_t c = 0;
-    for (int g = 0; g < wg; g += 2) c += g + (lane >> 5) < wg ? __popc(listed(wlo + 32 * g + lane)) : 0u;
+#pragma unroll 4
+    for (int grp = g0; grp < g1; ++grp) {
+      const uint32_t mask = mask_of(64 * grp + lane);
+      c += __popcll(__ballot(mask != 0u));
+      // the bitmaps: lanes 2 p, 2 p + 1 write the words of head p
+      uint64_t bits_p = __ballot((mask >> (pack > 1 ? 0 : 1)) & 1u);
+      if (pack > 1)
 #pragma unroll
-    for (int d = 1; d < 64; d <<= 1) c += __shfl_xor(c, d);
+        for (int p = 1; p < 4; ++p) {
+          const uint64_t b = __ballot((mask >> p) & 1u);
+          bits_p = (lane >> 1) == p ? b : bits_p;
+        }
+      const int w = (b0 >> 5) + 2 * grp + (lane & 1);
+      if (lane < 2 * n_in && w < n_words - 2) A[(int64_t)(lane >> 1) * n_words + w] = (uint32_t)(bits_p >> (32 * (lane & 1)));
+    }
     if (lane == 0) wsum[wv] = c;
+    before = pack > 1 ? 0u : flags[win];
     __syncthreads();
-    uint32_t pos = running, total = 0;
+    uint32_t pos = running;
     for (int x = 0; x < NW; ++x) {
       if (x < wv) pos += wsum[x];
-      total += wsum[x];
+      running += wsum[x];
     }
-    for (int w = wlo; w < wlo + 32 * wg && w < nw; w += 2) {
-      // (uniform: the same LDS words in every lane)
-      const uint64_t m = (uint64_t)listed(w) | ((uint64_t)listed(w + 1) << 32);
-      const uint64_t cur = (uint64_t)aw[1 + w] | (w + 1 < nw ? (uint64_t)aw[2 + w] << 32 : 0ull);
-      const uint32_t prev = aw[w];
-      uint32_t mask = 0;   // mask bit t = A bit (bit index - (NQB - 1) + t)
-#pragma unroll
-      for (int t = 0; t < NQB; ++t) {
-        constexpr int kTop = NQB - 1;
-        const int sh = kTop - t;
-        const uint64_t x = sh ? (cur << sh) | (prev >> (32 - sh)) : cur;
-        mask |= (uint32_t)((x >> lane) & 1ull) << t;
-      }
-      if ((m >> lane) & 1ull)
-        E[pos + __popcll(m & ((1ull << lane) - 1ull))] = ((uint32_t)(32 * (w0 + w) + lane) << 4) | mask;
+#pragma unroll 4
+    for (int grp = g0; grp < g1; ++grp) {
+      const uint32_t mask = mask_of(64 * grp + lane);
+      const uint64_t m = __ballot(mask != 0u);
+      if (mask)
+        E[pos + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u))] =
+            (uint32_t)(b0 + 64 * grp + lane + (pack > 1 ? NQB - 1 : 0)) << 4 | mask;
       pos += __popcll(m);
     }
-    running += total;
-    __syncthreads();   // wsum and aw are rewritten by the next window
+    __syncthreads();   // wsum and flags are rewritten by the next window
   }
   for (int i = running + tid; i < ent_stride; i += kBlThreads) E[i] = kEntSentinel;
-  if (tid == 0) write_tail(running);
+  if (pack > 1) {
+    if (tid < n_in) { A[(int64_t)tid * n_words + n_words - 1] = 0u; A[(int64_t)tid * n_words + n_words - 2] = running; }
+  } else if (tid == 0) {
+    write_tail(running);
+  }
   return true;
 }
 template <int NQB, bool BATCH>

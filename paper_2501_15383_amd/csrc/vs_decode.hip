@@ -28,7 +28,7 @@ constexpr int kDecThreads = 256;
 constexpr int kDecWaves = kDecThreads / 64;
 constexpr int kDecMinBlocks = 2;     // 64-key blocks per share at least, of all its KV heads: one 32-key chunk for every wave
 constexpr int kDecListThreads = 1024;
-constexpr int kDecListWords = 14336; // bitmap words of all heads of a group in LDS at a time
+constexpr int kDecListBytes = 128 << 10;   // a byte per diagonal and head in LDS at a time: 1M keys of up to 8 heads
 
 struct DecodeArgs {
   vs_request one;         // the request of a call without a table (req null)
@@ -567,67 +567,53 @@ __global__ __launch_bounds__(64 * NW) void k_decode_combine(const DecodeArgs a) 
 }
 
 // Bitmaps of the heads of a KV group and the union of their block lists, one workgroup per (KV head, request), for single
-// tokens with index sets.  Bits are collected in LDS (see k_build_blocklist), a window of all heads' words at a time;
-// entries are written 64 at a time with a lane per bit.
+// tokens with index sets.  Diagonals are collected as bytes in LDS (see collect_flags), 8 or 16 heads side by side, a window at a time;
+// every wave has consecutive groups of 64 diagonals, a lane per diagonal.
 __global__ __launch_bounds__(kDecListThreads) void k_decode_lists(const DecodeArgs a) {
   constexpr int NW = kDecListThreads / 64;
-  __shared__ uint32_t bits[kDecListWords];   // [head][win]
+  __shared__ __attribute__((aligned(16))) uint8_t flags[kDecListBytes + 16];
   __shared__ uint32_t wsum[NW];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = blockIdx.x, r = blockIdx.y, G = a.group;
   const vs_request rq = decode_request(a, r);
   if (!decode_takes(a, rq) || !rq.s_idx) return;
-  const int n_blk = decode_blocks(rq), n_words = (n_blk + 31) / 32;
-  const int win = kDecListWords / G & ~1;
+  const int n_blk = decode_blocks(rq), n_words = (n_blk + 31) / 32, shift = G > 8 ? 4 : 3, win = kDecListBytes >> shift;
   uint2* const E = a.ent + ((int64_t)r * a.n_kv_heads + g) * a.ent_stride;
   uint32_t* const B = a.bm + ((int64_t)r * a.n_q_heads + (int64_t)g * G) * a.words;
+  const int64_t h0 = (int64_t)g * G;
   uint32_t running = 0;
-  for (int w0 = 0; w0 < n_words; w0 += win) {
-    const int nw = n_words - w0 < win ? n_words - w0 : win;
-    for (int x = tid; x < G * win; x += kDecListThreads) bits[x] = 0;
+  for (int b0 = 0; b0 < n_blk; b0 += win) {
+    const int n = n_blk - b0 < win ? n_blk - b0 : win, n_grp = (n + 63) >> 6;
+    for (int x = tid; x < n_grp << (2 + shift); x += kDecListThreads) ((u32x4*)flags)[x] = u32x4{0u, 0u, 0u, 0u};
     __syncthreads();
-    // (all heads' offsets on their way at once; what a line adds is set by the first of its neighbours, see list_bits)
-    for (int j0 = 0; j0 < G; j0 += 4) {
-      const int32_t* so[4];
-      int cnt[4], most = 0;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int h = g * G + (j0 + e < G ? j0 + e : j0);
-        so[e] = rq.s_idx + (int64_t)h * a.s_budget;
-        cnt[e] = j0 + e < G ? rq.s_cnt[h] : 0;
-        most = cnt[e] > most ? cnt[e] : most;
-      }
-      for (int i = tid; i < most; i += kDecListThreads) {
-        int o[4], before[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          o[e] = i < cnt[e] ? so[e][i] : 0;
-          before[e] = i < cnt[e] && i > 0 ? so[e][i - 1] : -1;
-        }
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (i < cnt[e])
-            list_bits(o[e], before[e], n_blk, [&](int ad) {
-              const int x = (ad >> 5) - w0;
-              if (x >= 0 && x < nw) atomicOr(&bits[(j0 + e) * win + x], 1u << (ad & 31));
-            });
-      }
-    }
+    collect_flags<kDecListThreads, 16>(flags, shift, b0, n, win, rq.s_idx + h0 * a.s_budget, rq.s_cnt + h0, a.s_budget, G);
     __syncthreads();
-    for (int j = 0; j < G; ++j)
-      for (int w = tid; w < nw; w += kDecListThreads) B[(int64_t)j * a.words + w0 + w] = bits[j * win + w];
-    auto any = [&](int w) -> uint32_t {
-      uint32_t u = 0;
-      if (w < nw)
-        for (int j = 0; j < G; ++j) u |= bits[j * win + w];
-      return u;
+    // heads that have diagonal b0 + x: bytes of 0 and 1 to bits
+    auto heads_of = [&](int x) -> uint32_t {
+      auto four = [](uint32_t v) -> uint32_t { return (v * 0x01020408u >> 24) & 15u; };
+      if (shift == 3) {
+        const uint2 v = ((const uint2*)flags)[x];
+        return four(v.x) | four(v.y) << 4;
+      }
+      const u32x4 v = ((const u32x4*)flags)[x];
+      return four(v[0]) | four(v[1]) << 4 | four(v[2]) << 8 | four(v[3]) << 12;
     };
-    const int wg = (((nw + 31) >> 5) + NW - 1) / NW, wlo = wv * wg * 32;   // groups of 32 words per wave
+    const int each = (n_grp + NW - 1) / NW, g0 = wv * each, g1 = g0 + each < n_grp ? g0 + each : n_grp;
     uint32_t c = 0;
-    for (int x = 0; x < wg; x += 2) c += x + (lane >> 5) < wg ? __popc(any(wlo + 32 * x + lane)) : 0u;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) c += __shfl_xor(c, d);
+#pragma unroll 4
+    for (int grp = g0; grp < g1; ++grp) {
+      const uint32_t heads = heads_of(64 * grp + lane);
+      c += __popcll(__ballot(heads != 0u));
+      // the bitmaps: lanes 2 j, 2 j + 1 write the words of head j
+      uint64_t bits = 0;
+      for (int j = 0; j < G; ++j) {
+        const uint64_t b = __ballot((heads >> j) & 1u);
+        bits = (lane >> 1) == j ? b : bits;
+      }
+      const int w = (b0 >> 5) + 2 * grp + (lane & 1);
+      if (lane < 2 * G && w < n_words) B[(int64_t)(lane >> 1) * a.words + w] = (uint32_t)(bits >> (32 * (lane & 1)));
+    }
     if (lane == 0) wsum[wv] = c;
     __syncthreads();
     uint32_t pos = running;
@@ -635,18 +621,16 @@ __global__ __launch_bounds__(kDecListThreads) void k_decode_lists(const DecodeAr
       if (x < wv) pos += wsum[x];
       running += wsum[x];
     }
-    for (int w = wlo; w < wlo + 32 * wg && w < nw; w += 2) {
-      const int wl = w + (lane >> 5);   // this lane's word and bit
-      uint32_t heads = 0;
-      if (wl < nw)
-        for (int j = 0; j < G; ++j) heads |= ((bits[j * win + wl] >> (lane & 31)) & 1u) << j;
-      const uint64_t m = __ballot(heads != 0);
+#pragma unroll 4
+    for (int grp = g0; grp < g1; ++grp) {
+      const uint32_t heads = heads_of(64 * grp + lane);
+      const uint64_t m = __ballot(heads != 0u);
       if (heads)
         E[pos + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u))] =
-            make_uint2((uint32_t)(32 * (w0 + w) + lane), heads);
+            make_uint2((uint32_t)(b0 + 64 * grp + lane), heads);
       pos += __popcll(m);
     }
-    __syncthreads();   // wsum and bits are rewritten by the next window
+    __syncthreads();   // wsum and flags are rewritten by the next window
   }
   if (tid == 0) {
     int tiles = 0;

@@ -158,6 +158,40 @@ def test_whole_units_and_cut_ones_with_dca(c, s, chunk, window):
         assert_attn_close(out_s[at], lse_s[:, at], *ref, f"sparse dca C={c} s={s} rows {rows}")
 
 
+# block lists of more diagonals than their builders hold at a time: 16 heads of a token (8,192), packed heads (16,448), one head (65,792)
+@pytest.mark.parametrize("hq,c,win", [(16, 1, 8192), (7, 1, 16384), (4, 2, 16448), (2, 70, 65792)])
+def test_lists_of_several_windows(hq, c, win):
+    d, n = 64, 64 * win + 1000
+    gen = torch.Generator(device="cuda").manual_seed(3140)
+    q = torch.randn((c, hq, d), generator=gen, device="cuda", dtype=torch.bfloat16)
+    k = torch.randn((n, 1, d), generator=gen, device="cuda", dtype=torch.bfloat16)
+    v = torch.randn((n, 1, d), generator=gen, device="cuda", dtype=torch.bfloat16)
+    rng = np.random.default_rng(3141)
+    ck = vs.Chunk(hq, 1, d, c, n - c, 0.125, vertical_budget=40, slash_budget=1500)
+    vi = np.full((hq, 40), -1, np.int32); si = np.full((hq, 1500), -1, np.int32)
+    vc = np.full(hq, 40, np.int32); sc = np.zeros(hq, np.int32)
+    for h in range(hq):
+        vi[h] = np.sort(rng.choice(n - c, 40, replace=False))
+        edge = 64 * win - 64 * (h % 3) + np.arange(-1, 2 + 100 * (h % 2))   # both sides of the window's end
+        offs = np.unique(np.concatenate([np.arange(3), edge, [n - 1], rng.choice(n, 40 * (1 + h), replace=False)]))
+        sc[h] = len(offs); si[h, :sc[h]] = offs
+    out = vs.sparse_attn_prefill(ck, q, k, v, *[_t(x) for x in (vi, vc, si, sc)])
+    out = out[0] if isinstance(out, (tuple, list)) else out
+    for h in range(hq):
+        offs = torch.as_tensor(si[h, :sc[h]], device="cuda").long()
+        ad = torch.cat([offs // 64, (offs + 63) // 64]).unique()
+        for r in {0, c // 2, c - 1}:
+            pos = n - c + r
+            blocks = pos // 64 - ad[ad <= pos // 64]
+            keys = (64 * blocks[:, None] + torch.arange(64, device="cuda")).flatten()
+            keys = torch.cat([keys, torch.as_tensor(vi[h], device="cuda").long()]).unique()
+            keys = keys[keys <= pos]
+            p = torch.softmax((k[keys, 0].float() @ q[r, h].float()) * 0.125, 0)
+            ref = p @ v[keys, 0].float()
+            # as everywhere: probabilities and outputs are rounded to bf16
+            assert (out[r, h].float() - ref).norm() <= 2e-2 * ref.norm(), (h, r)
+
+
 def test_ranges_that_are_asked_for_of_many_units():
     hq, hkv, d, c, s = 1100, 10, 64, 512, 2048 + 33   # 5,500 units, 41 key blocks: two ranges of each
     rng = np.random.default_rng(3120)
