@@ -87,9 +87,9 @@ struct AttnArgs {
   int32_t n_split, n_units, n_whole, first_piece;
   float* part_o;
   float* part_ml;
-  // Uneven cut of the cut units (own_cut; 0: the even one above): slots of partial results, steps that a unit's columns count for, and
+  // Uneven cut of the cut units (own_cut; 0: the even one above): slots of partial results, and
   // what k_attn_pieces leaves: the number of pieces (0: the even cut stays), the pieces, ranges and first slot of every cut unit
-  int32_t own_slots, col_steps;
+  int32_t own_slots;
   int32_t* own_n;
   OwnPiece* own_pieces;
   int2* own_units;
@@ -109,7 +109,7 @@ struct AttnArgs {
   const uint32_t* bm_a;  // block-diagonal bitmap per head
   const uint32_t* ent;   // key-block entry list per head (see BlockList); null (SPLIT only): every block, no list is made
   int64_t bm_stride;     // words per head, 0 = one bitmap shared by all heads (dense)
-  int32_t bm_words;      // words of one bitmap row; its last word holds the head's segment shift
+  int32_t bm_words;      // words of one bitmap row; its last two words: see build_list
   int64_t ent_stride;    // entries per head, 0 = one list shared by all heads (dense)
   int64_t ent_len;       // entries of one list (sentinel padding included)
   const int32_t* v_idx;  // null: no vertical phase
@@ -169,6 +169,8 @@ constexpr int64_t kMaxAskedUnits = 1 << 23;        // all the same (128 M pieces
 constexpr int kPaceBlocks = 4096;                  // key blocks from which whole units keep pace (see launch_attention)
 constexpr int kRun = 64;                           // workgroup slots of an XCD: members of a pace-keeping group
 constexpr int kQueueStride = 16;                   // words between two queue counters: a cache line each
+constexpr int kListBits = 28;                      // of a bitmap row's word that holds the length of the list (see build_list)
+constexpr uint32_t kListMask = (1u << kListBits) - 1u;
 constexpr int kTileRows = 64 * kAttnQBlocks;       // rows of a query tile, of a slot of partial results
 
 // Query heads that share a tile, from the rows of the launch and the first one's place in its 64-block.  Rows of one query
@@ -300,7 +302,8 @@ __device__ __forceinline__ void own_cut(const AttnArgs& a, int lane, int& n, int
   int len = 0;
   if (cnt > 0) {
     const int h0 = list / a.n_hs * a.group + list % a.n_hs * a.pack;
-    len = (int)a.bm_a[(int64_t)h0 * a.bm_stride + a.bm_words - 2] + a.col_steps;
+    const uint32_t* const tail = a.bm_a + (int64_t)h0 * a.bm_stride + a.bm_words - 2;
+    len = (int)(tail[0] & kListMask) + 2 * (int)((tail[1] + 63) >> 6);   // (a gathered tile takes as long as two: the masked path)
     len = len > 1 ? len : 1;
   }
   int mx = len, mn = cnt > 0 ? len : 1 << 30;
@@ -576,11 +579,11 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
   const int64_t last_pos = a.same_pos ? n_k - 1 : a.q_start + row0 + rows_in_tile - 1;
 
   const uint32_t* bmA = a.bm_a + (int64_t)hw * a.bm_stride;
-  const int seg_shift = __builtin_amdgcn_readfirstlane((int)bmA[a.bm_words - 1]);  // sparser list, longer sync segments
+  const int seg_shift = __builtin_amdgcn_readfirstlane((int)(bmA[a.bm_words - 2] >> kListBits));  // sparser list, longer sync segments
   const uint32_t* ent_h = a.ent + (int64_t)(SPLIT ? g * a.n_hs + (h - g * a.group) / pack : h) * a.ent_stride;
   const int32_t* vidx_h = a.v_idx ? a.v_idx + (int64_t)h * a.v_budget : nullptr;
-  // selected columns of head h, with packed heads those of head h + i in lane i
-  const int vcnt_l = a.v_idx ? (SPLIT ? a.v_cnt[h + (lane < pack && h - g * a.group + lane < a.group ? lane : 0)] : a.v_cnt[h]) : 0;
+  // columns to gather of head h, with packed heads those of head h + i in lane i
+  const int vcnt_l = a.v_idx ? (int)a.bm_a[(int64_t)(SPLIT ? h + (lane < pack && h - g * a.group + lane < a.group ? lane : 0) : h) * a.bm_stride + a.bm_words - 1] : 0;
   const int vcnt = __builtin_amdgcn_readfirstlane(vcnt_l);
   const int n_vt = (vcnt + 63) >> 6;
   const int cc_last = m0 + NQB - 1;  // entry cc stands for key block m0 + (NQB - 1) - cc >= 0
@@ -1330,6 +1333,7 @@ constexpr int kListGroups = 4096;   // workgroups for the lists of a batch, abou
 struct ListArgs {
   const int32_t* s_idx;
   const int32_t* s_cnt;
+  const int32_t* v_cnt;   // null: nobody gathers columns
   int32_t s_budget, dense, n_blk, n_words, ent_stride;
   uint32_t* bm_a;
   uint32_t* ent;
@@ -1450,6 +1454,7 @@ __device__ __forceinline__ bool build_list(const ListArgs& a, int x0) {
   int dense = a.dense, n_blk = a.n_blk, pack = a.pack, n_hs = (a.group + pack - 1) / pack;
   const int32_t* s_idx = a.s_idx;
   const int32_t* s_cnt = a.s_cnt;
+  const int32_t* v_cnt = a.v_cnt;
   uint32_t* bm_a = a.bm_a;
   if constexpr (BATCH) {
     const vs_request rq = a.req[r];
@@ -1458,7 +1463,7 @@ __device__ __forceinline__ bool build_list(const ListArgs& a, int x0) {
     pack = b.pack;
     n_hs = b.n_hs;
     dense = b.dense;
-    s_idx = rq.s_idx; s_cnt = rq.s_cnt;
+    s_idx = rq.s_idx; s_cnt = rq.s_cnt; v_cnt = rq.v_cnt;
     n_blk = (int)((rq.q_start + rq.q_len + kBlock - 1) / kBlock);
     bm_a += (int64_t)r * a.n_heads * n_words;
     if (x0 >= (b.dense ? 1 : a.n_heads / a.group * n_hs)) return false;   // (a dense request has one list for all heads)
@@ -1468,22 +1473,23 @@ __device__ __forceinline__ bool build_list(const ListArgs& a, int x0) {
   const int grp = dense && !BATCH ? 0 : x0 / n_hs, h0 = dense && !BATCH ? 0 : grp * a.group + (x0 - grp * n_hs) * pack;
   const int n_in = grp * a.group + a.group - h0 < pack ? grp * a.group + a.group - h0 : pack;
   uint32_t* const A = bm_a + (int64_t)h0 * n_words;
-  // The last two words of the bitmap row lie beyond every diagonal.  The last one tells the attention
-  // kernel how sparse the list is: sync segments of this head are 2^shift times the base size, so
-  // that a segment holds about as many listed key blocks as it would in a dense list.
-  auto write_tail = [&](uint32_t n_list) {
-    const uint32_t n_ent = n_list > 0 ? n_list : 1u;
-    int shift = 0;
-    while (shift < 4 && ((uint32_t)n_blk >> (shift + 1)) >= n_ent) ++shift;
-    A[n_words - 1] = (uint32_t)shift;
-    A[n_words - 2] = n_list;  // length of the list: the head's share of the work (k_attn_schedule)
+  // The last two words of the bitmap row lie beyond every diagonal.  One holds the length of the list (the head's share of the work) and,
+  // from bit kListBits on, how sparse it is: sync segments of this head are 2^shift times the base size, so that a segment holds about
+  // as many listed key blocks as it would in a dense list.  The other holds the columns to gather: none where the head has every
+  // diagonal (6,096 scattered offsets give all of them up to some 64K keys), because all their rows are walked.  28 heads, 4,096 rows
+  // from the first on 296 us -> 250, 5,000 of 12,000 keys 827 -> 775; 32 requests of up to 64 rows and 20,000 keys 353 -> 285.
+  const uint32_t cols = v_cnt ? (uint32_t)v_cnt[h0 + (tid < n_in ? tid : 0)] : 0u;   // (on its way from here; thread p writes head p's tail)
+  auto write_tail = [&](int p, uint32_t n_list, int shift, bool full) {
+    uint32_t* const row = A + (int64_t)p * n_words;
+    row[n_words - 1] = full ? 0u : cols;
+    row[n_words - 2] = n_list | (uint32_t)shift << kListBits;
   };
   if (dense && pack > 1) {
     for (int i = part * kBlDensePart + tid; i < ent_stride && (i < (part + 1) * kBlDensePart || n_parts == part + 1);
          i += kBlThreads)
       E[i] = i < n_blk ? ((uint32_t)(i + NQB - 1) << 4) | 15u : kEntSentinel;
     // (no bitmap: a dense walk has no columns that ask it)
-    if (part == 0 && tid == 0) write_tail((uint32_t)n_blk);
+    if (part == 0 && tid == 0) write_tail(0, (uint32_t)n_blk, 0, true);
     return true;
   }
   if (dense) {
@@ -1504,7 +1510,7 @@ __device__ __forceinline__ bool build_list(const ListArgs& a, int x0) {
         const int lo = w * 32;
         A[w] = lo + 32 <= n_blk ? ~0u : (lo < n_blk ? (1u << (n_blk - lo)) - 1u : 0u);
       }
-      if (tid == 0) write_tail((uint32_t)n_list);
+      if (tid == 0) write_tail(0, (uint32_t)n_list, 0, true);
     }
     return true;
   }
@@ -1514,8 +1520,9 @@ __device__ __forceinline__ bool build_list(const ListArgs& a, int x0) {
   // it what lies outside.  Every wave has consecutive groups of 64 diagonals, a lane per diagonal.
   static_assert(NQB == 2, "an entry has the diagonals of two query blocks");
   __shared__ __attribute__((aligned(16))) uint8_t flags[4 * (kBlWin + 64)];
-  __shared__ uint32_t wsum[NW];
-  uint32_t running = 0, before = 0;
+  __shared__ uint32_t wsum[NW], missing_s;   // (a bit per head that lacks a diagonal)
+  uint32_t running = 0, before = 0, missing = 0;
+  if (tid == 0) missing_s = 0u;
   const int shift = pack > 1 ? 2 : 0, win = pack > 1 ? kBlWin : 4 * kBlWin;
   for (int b0 = 0; b0 < 32 * (n_words - 2); b0 += win) {
     const int bits = 32 * (n_words - 2) - b0, n_grp = ((bits < win ? bits : win) + 63) >> 6;
@@ -1523,8 +1530,7 @@ __device__ __forceinline__ bool build_list(const ListArgs& a, int x0) {
     __syncthreads();
     uint8_t* const f = flags + (1 << shift);
     const int n_in_win = n_blk - b0 < win ? (n_blk > b0 ? n_blk - b0 : 0) : win;
-    if (pack > 1) collect_flags<kBlThreads, 16>(f, shift, b0, n_in_win, win, s_idx + (int64_t)h0 * a.s_budget, s_cnt + h0, a.s_budget, n_in);
-    else collect_flags<kBlThreads, 8>(f, 0, b0, n_in_win, win, s_idx + (int64_t)h0 * a.s_budget, s_cnt + h0, a.s_budget, 1);
+    collect_flags<kBlThreads, 8>(f, shift, b0, n_in_win, win, s_idx + (int64_t)h0 * a.s_budget, s_cnt + h0, a.s_budget, n_in);
     __syncthreads();
     // the mask of a diagonal's entry: the heads that have it, or, of one head, bit t: diagonal b0 + x - 1 + t
     auto mask_of = [&](int x) -> uint32_t {
@@ -1533,10 +1539,10 @@ __device__ __forceinline__ bool build_list(const ListArgs& a, int x0) {
     };
     const int each = (n_grp + NW - 1) / NW, g0 = wv * each, g1 = g0 + each < n_grp ? g0 + each : n_grp;
     uint32_t c = 0;
-#pragma unroll 4
     for (int grp = g0; grp < g1; ++grp) {
       const uint32_t mask = mask_of(64 * grp + lane);
       c += __popcll(__ballot(mask != 0u));
+      if (b0 + 64 * grp + lane < n_blk) missing |= ~mask;
       // the bitmaps: lanes 2 p, 2 p + 1 write the words of head p
       uint64_t bits_p = __ballot((mask >> (pack > 1 ? 0 : 1)) & 1u);
       if (pack > 1)
@@ -1549,6 +1555,10 @@ __device__ __forceinline__ bool build_list(const ListArgs& a, int x0) {
       if (lane < 2 * n_in && w < n_words - 2) A[(int64_t)(lane >> 1) * n_words + w] = (uint32_t)(bits_p >> (32 * (lane & 1)));
     }
     if (lane == 0) wsum[wv] = c;
+    uint32_t lacks = 0;
+#pragma unroll
+    for (int p = 0; p < 4; ++p) lacks |= __ballot((missing >> p) & 1u) ? 1u << p : 0u;
+    if (lane == 0) atomicOr(&missing_s, lacks);
     before = pack > 1 ? 0u : flags[win];
     __syncthreads();
     uint32_t pos = running;
@@ -1556,7 +1566,6 @@ __device__ __forceinline__ bool build_list(const ListArgs& a, int x0) {
       if (x < wv) pos += wsum[x];
       running += wsum[x];
     }
-#pragma unroll 4
     for (int grp = g0; grp < g1; ++grp) {
       const uint32_t mask = mask_of(64 * grp + lane);
       const uint64_t m = __ballot(mask != 0u);
@@ -1569,9 +1578,11 @@ __device__ __forceinline__ bool build_list(const ListArgs& a, int x0) {
   }
   for (int i = running + tid; i < ent_stride; i += kBlThreads) E[i] = kEntSentinel;
   if (pack > 1) {
-    if (tid < n_in) { A[(int64_t)tid * n_words + n_words - 1] = 0u; A[(int64_t)tid * n_words + n_words - 2] = running; }
+    if (tid < n_in) write_tail(tid, running, 0, !(missing_s >> tid & 1u));
   } else if (tid == 0) {
-    write_tail(running);
+    int sft = 0;
+    while (sft < 4 && ((uint32_t)n_blk >> (sft + 1)) >= (running > 0 ? running : 1u)) ++sft;
+    write_tail(0, running, sft, !(missing_s & 2u));   // (bit 1 of an entry's mask is its own diagonal)
   }
   return true;
 }
@@ -1974,7 +1985,7 @@ __global__ __launch_bounds__(1024) void k_attn_schedule(const AttnArgs a, int32_
   }
   if (tid < 64) {
     uint64_t sum = 0;
-    for (int h = tid; h < a.n_q_heads; h += 64) sum += a.bm_a[(int64_t)h * a.bm_stride + a.bm_words - 2];
+    for (int h = tid; h < a.n_q_heads; h += 64) sum += a.bm_a[(int64_t)h * a.bm_stride + a.bm_words - 2] & kListMask;
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) sum += __shfl_xor((unsigned long long)sum, d);
     if (tid == 0) avg_ent = (float)((double)sum / a.n_q_heads);
@@ -1986,7 +1997,7 @@ __global__ __launch_bounds__(1024) void k_attn_schedule(const AttnArgs a, int32_
     float ent, reach;
     if (gr < n_full_gr) {
       const int h = gr % a.n_q_heads, c = a.n_full - 1 - gr / a.n_q_heads;
-      ent = (float)a.bm_a[(int64_t)h * a.bm_stride + a.bm_words - 2];
+      ent = (float)(a.bm_a[(int64_t)h * a.bm_stride + a.bm_words - 2] & kListMask);
       reach = (float)(mb + 2 * (a.n_rem + c * a.members + a.members / 2) + 2);  // key blocks before the chunk's middle tile
     } else {
       ent = avg_ent;  // leftover tiles of several heads
@@ -2092,7 +2103,7 @@ static bool attn_listless(const vs_params& p, bool dense, const AttnCut& c, int 
 // One list per head, or per tile of packed heads (one for all heads when dense); attn: for the attention launch with the
 // counters at sync_ws, which are cleared on the way (null: for k_count_tiles, which packs nothing and has none to clear).
 hipError_t launch_build_blocklist(const vs_params& p, const int32_t* s_idx, const int32_t* s_cnt,
-                                  bool dense, const BlockList& bl, void* sync_ws, hipStream_t st) {
+                                  const int32_t* v_cnt, bool dense, const BlockList& bl, void* sync_ws, hipStream_t st) {
   const int64_t n_k = p.q_start + p.q_len;
   AttnCut c = {};
   if (sync_ws) {
@@ -2103,7 +2114,7 @@ hipError_t launch_build_blocklist(const vs_params& p, const int32_t* s_idx, cons
     if (attn_listless(p, dense, c, attn_members(n_cu))) return hipSuccess;
   }
   ListArgs a = {};
-  a.s_idx = s_idx; a.s_cnt = s_cnt; a.s_budget = p.slash_budget;
+  a.s_idx = s_idx; a.s_cnt = s_cnt; a.v_cnt = v_cnt; a.s_budget = p.slash_budget;
   a.dense = dense;
   a.n_blk = (int)ceil_div(n_k, kBlock);
   a.n_words = (int)bl.words; a.ent_stride = (int)bl.ent_stride;
@@ -2175,7 +2186,6 @@ hipError_t launch_attention(const vs_params& p, const void* q, const DcaArgs* dc
   a.part_o = a.part_ml = nullptr;
   a.own_slots = cut.own_slots;
   a.own_n = nullptr; a.own_units = nullptr; a.own_pieces = nullptr;
-  a.col_steps = 2 * cut.pack * (int)ceil_div(p.vertical_budget < a.n_k ? p.vertical_budget : a.n_k, 64);
   if (cut.queue && cut.slots() > 0) {
     if (!split_ws) return hipErrorInvalidValue;
     const size_t rows = (size_t)cut.slots() * kTileRows;

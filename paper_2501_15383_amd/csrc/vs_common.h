@@ -76,6 +76,16 @@ __device__ __forceinline__ void collect_flags(uint8_t* flags, int shift, int b0,
                                               const int32_t* s_cnt, int budget, int n_lists) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int cnts = s_cnt[lane < n_lists ? lane : 0];
+  auto put = [&](int offset, bool in, int list) {
+    const uint32_t x = (uint32_t)((offset >> 6) - b0), y = (uint32_t)(((offset + 63) >> 6) - b0);
+    flags[((in && x < (uint32_t)n ? x : (uint32_t)n_win) << shift) + list] = 1;
+    flags[((in && y < (uint32_t)n ? y : (uint32_t)n_win) << shift) + list] = 1;
+  };
+  if (n_lists == 1 && budget <= THREADS) {   // (the loop below is 0.8 us of instructions for it)
+    const int o = s_idx[tid < budget ? tid : budget - 1];
+    if (tid < __builtin_amdgcn_readfirstlane(cnts)) put(o, true, 0);
+    return;
+  }
   int p = 0, at = 0, most;   // list and place in it of the next group: the lists in turn
   do {
     int o[U], list[U], from[U];
@@ -93,10 +103,7 @@ __device__ __forceinline__ void collect_flags(uint8_t* flags, int shift, int b0,
     for (int u = 0; u < U; ++u) {
       const int cnt = __builtin_amdgcn_readlane(cnts, list[u]);
       if (from[u] >= cnt) continue;
-      const uint32_t x = (uint32_t)((o[u] >> 6) - b0), y = (uint32_t)(((o[u] + 63) >> 6) - b0);
-      const bool in = from[u] + tid < cnt;
-      flags[((in && x < (uint32_t)n ? x : (uint32_t)n_win) << shift) + list[u]] = 1;
-      flags[((in && y < (uint32_t)n ? y : (uint32_t)n_win) << shift) + list[u]] = 1;
+      put(o[u], from[u] + tid < cnt, list[u]);
     }
   } while (__ballot(most > at));
 }
@@ -129,7 +136,7 @@ static inline BlockList blocklist_layout(const vs_params& p, bool dense, void* w
 
 // ---- launchers (defined in the .hip files; all enqueue on `st`, return hipError_t) ------
 hipError_t launch_build_blocklist(const vs_params& p, const int32_t* s_idx, const int32_t* s_cnt,
-                                  bool dense, const BlockList& bl, void* sync_ws, hipStream_t st);
+                                  const int32_t* v_cnt, bool dense, const BlockList& bl, void* sync_ws, hipStream_t st);
 // Dual Chunk Attention: the two other rotations of the chunk's queries (same strides as q),
 // chunk length and local window in tokens (multiples of 64)
 struct DcaArgs {

@@ -43,7 +43,7 @@ struct DecodeArgs {
   // index sets: block-diagonal bitmap per (request, head), union list and its lengths per (request, KV head)
   uint32_t* bm;           // [n_req][Hq][words]
   uint2* ent;             // [n_req][Hkv][ent_stride] (diagonal, heads that have it)
-  int2* len;              // [n_req][Hkv] (entries, entries + tiles of 64 gathered columns)
+  int4* len;              // [n_req][Hkv] (entries, entries + tiles of 64 gathered columns, heads that have every diagonal)
   int32_t words, ent_stride;
   // shares: plan[0] = units in all (a unit: 64 keys of `side` KV heads), plan[1] = shares, plan[2 + r] = units before request r; of one request without index sets the
   // host knows them (one_T units, one_n shares; 0: the device finds them)
@@ -73,7 +73,7 @@ __device__ __forceinline__ bool decode_takes(const DecodeArgs& a, const vs_reque
 __device__ __forceinline__ int decode_blocks(const vs_request& rq) { return (int)((rq.q_start + kBlock) / kBlock); }
 // units of segment x (side neighbouring KV heads) of request r: as many as its longest head has
 __device__ __forceinline__ int decode_seg_len(const DecodeArgs& a, int r, int x) {
-  const int2* const len = a.len + (int64_t)r * a.n_kv_heads + x * a.side;
+  const int4* const len = a.len + (int64_t)r * a.n_kv_heads + x * a.side;
   int n = len[0].y;
   for (int e = 1; e < a.side; ++e) n = len[e].y > n ? len[e].y : n;
   return n;
@@ -207,11 +207,12 @@ __device__ __forceinline__ void decode_body(const DecodeArgs& a) {
     const bool sparse = rq.s_idx != nullptr;
     const int64_t n_k = rq.q_start + 1;
     const int g = sg * SIDE + sub;   // this wave's KV head
-    int n_ent = decode_blocks(rq), own_len = n_ent, seg_len = n_ent;
+    int n_ent = decode_blocks(rq), own_len = n_ent, seg_len = n_ent, full = 0;
     if (sparse) {
-      const int2 l2 = a.len[(int64_t)r * a.n_kv_heads + g];
+      const int4 l2 = a.len[(int64_t)r * a.n_kv_heads + g];
       n_ent = __builtin_amdgcn_readfirstlane(l2.x);
       own_len = __builtin_amdgcn_readfirstlane(l2.y);
+      full = l2.z;
       seg_len = __builtin_amdgcn_readfirstlane(decode_seg_len(a, r, sg));
     }
     if (blk >= seg_len) {   // the share starts in a later segment of this request
@@ -252,7 +253,8 @@ __device__ __forceinline__ void decode_body(const DecodeArgs& a) {
     int c = 2 * b0 + w_of;
     int c_end = 2 * b1;
     if (!sparse && c_end > (int)((n_k + 31) / 32)) c_end = (int)((n_k + 31) / 32);
-    const int cnt_cache = sparse ? rq.v_cnt[h0 + (lane < a.group ? lane : 0)] : 0;   // columns of head h0 + lane
+    // columns to gather of head h0 + lane: none where it has every diagonal
+    const int cnt_cache = sparse && !(full >> (lane & 15) & 1) ? rq.v_cnt[h0 + (lane < a.group ? lane : 0)] : 0;
     uint2 ecache = make_uint2(0u, 0u);
     int ebase = -64;
     // what the next chunk is: its live keys (bit k: key k) and live rows (bit q), both uniform
@@ -572,7 +574,7 @@ __global__ __launch_bounds__(64 * NW) void k_decode_combine(const DecodeArgs a) 
 __global__ __launch_bounds__(kDecListThreads) void k_decode_lists(const DecodeArgs a) {
   constexpr int NW = kDecListThreads / 64;
   __shared__ __attribute__((aligned(16))) uint8_t flags[kDecListBytes + 16];
-  __shared__ uint32_t wsum[NW];
+  __shared__ uint32_t wsum[NW], missing_s;   // (a bit per head that lacks a diagonal)
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = blockIdx.x, r = blockIdx.y, G = a.group;
@@ -582,7 +584,8 @@ __global__ __launch_bounds__(kDecListThreads) void k_decode_lists(const DecodeAr
   uint2* const E = a.ent + ((int64_t)r * a.n_kv_heads + g) * a.ent_stride;
   uint32_t* const B = a.bm + ((int64_t)r * a.n_q_heads + (int64_t)g * G) * a.words;
   const int64_t h0 = (int64_t)g * G;
-  uint32_t running = 0;
+  uint32_t running = 0, missing = 0;
+  if (tid == 0) missing_s = 0u;
   for (int b0 = 0; b0 < n_blk; b0 += win) {
     const int n = n_blk - b0 < win ? n_blk - b0 : win, n_grp = (n + 63) >> 6;
     for (int x = tid; x < n_grp << (2 + shift); x += kDecListThreads) ((u32x4*)flags)[x] = u32x4{0u, 0u, 0u, 0u};
@@ -601,10 +604,10 @@ __global__ __launch_bounds__(kDecListThreads) void k_decode_lists(const DecodeAr
     };
     const int each = (n_grp + NW - 1) / NW, g0 = wv * each, g1 = g0 + each < n_grp ? g0 + each : n_grp;
     uint32_t c = 0;
-#pragma unroll 4
     for (int grp = g0; grp < g1; ++grp) {
       const uint32_t heads = heads_of(64 * grp + lane);
       c += __popcll(__ballot(heads != 0u));
+      if (b0 + 64 * grp + lane < n_blk) missing |= ~heads;
       // the bitmaps: lanes 2 j, 2 j + 1 write the words of head j
       uint64_t bits = 0;
       for (int j = 0; j < G; ++j) {
@@ -615,13 +618,15 @@ __global__ __launch_bounds__(kDecListThreads) void k_decode_lists(const DecodeAr
       if (lane < 2 * G && w < n_words) B[(int64_t)(lane >> 1) * a.words + w] = (uint32_t)(bits >> (32 * (lane & 1)));
     }
     if (lane == 0) wsum[wv] = c;
+    uint32_t lacks = 0;
+    for (int j = 0; j < G; ++j) lacks |= __ballot((missing >> j) & 1u) ? 1u << j : 0u;
+    if (lane == 0) atomicOr(&missing_s, lacks);
     __syncthreads();
     uint32_t pos = running;
     for (int x = 0; x < NW; ++x) {
       if (x < wv) pos += wsum[x];
       running += wsum[x];
     }
-#pragma unroll 4
     for (int grp = g0; grp < g1; ++grp) {
       const uint32_t heads = heads_of(64 * grp + lane);
       const uint64_t m = __ballot(heads != 0u);
@@ -634,9 +639,9 @@ __global__ __launch_bounds__(kDecListThreads) void k_decode_lists(const DecodeAr
   }
   if (tid == 0) {
     int tiles = 0;
-    for (int j = 0; j < G; ++j) tiles += (rq.v_cnt[g * G + j] + 63) >> 6;
+    for (int j = 0; j < G; ++j) tiles += missing_s >> j & 1u ? (rq.v_cnt[g * G + j] + 63) >> 6 : 0;
     const int units = (int)running + tiles;   // (at least one: a token without any key gets its 0 / -inf too)
-    a.len[(int64_t)r * a.n_kv_heads + g] = make_int2((int)running, units > 0 ? units : 1);
+    a.len[(int64_t)r * a.n_kv_heads + g] = make_int4((int)running, units > 0 ? units : 1, (int)~missing_s, 0);
   }
 }
 
@@ -672,7 +677,7 @@ DecLayout dec_layout(const vs_params& p, int n_req, bool lists) {
   l.len = l.ent = l.bm = off;
   if (lists) {
     const size_t heads = (size_t)n_req * p.n_kv_heads;
-    off += align_up(heads * sizeof(int2), 256);
+    off += align_up(heads * sizeof(int4), 256);
     l.ent = off; off += align_up(heads * (size_t)l.ent_stride * sizeof(uint2), 256);
     l.bm = off; off += align_up((size_t)n_req * p.n_q_heads * (size_t)l.words * sizeof(uint32_t), 256);
   }
@@ -701,7 +706,7 @@ hipError_t launch_decode(const vs_params& p, const vs_request* one, const vs_req
   a.part_o = (float*)w;
   a.part_ml = (float*)(w + l.part_ml);
   a.plan = (int64_t*)(w + l.plan);
-  a.len = (int2*)(w + l.len);
+  a.len = (int4*)(w + l.len);
   a.ent = (uint2*)(w + l.ent);
   a.bm = (uint32_t*)(w + l.bm);
   a.words = l.words; a.ent_stride = l.ent_stride;

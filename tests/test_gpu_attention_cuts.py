@@ -169,13 +169,48 @@ def test_lists_of_several_windows(hq, c, win):
     rng = np.random.default_rng(3141)
     ck = vs.Chunk(hq, 1, d, c, n - c, 0.125, vertical_budget=40, slash_budget=1500)
     vi = np.full((hq, 40), -1, np.int32); si = np.full((hq, 1500), -1, np.int32)
-    vc = np.full(hq, 40, np.int32); sc = np.zeros(hq, np.int32)
+    sc = np.zeros(hq, np.int32)
     for h in range(hq):
         vi[h] = np.sort(rng.choice(n - c, 40, replace=False))
         edge = 64 * win - 64 * (h % 3) + np.arange(-1, 2 + 100 * (h % 2))   # both sides of the window's end
         offs = np.unique(np.concatenate([np.arange(3), edge, [n - 1], rng.choice(n, 40 * (1 + h), replace=False)]))
         sc[h] = len(offs); si[h, :sc[h]] = offs
-    out = vs.sparse_attn_prefill(ck, q, k, v, *[_t(x) for x in (vi, vc, si, sc)])
+    _check_by_gathering(ck, q, k, v, vi, si, sc)
+
+
+# heads that have every diagonal, whose columns nobody gathers, beside heads that lack one diagonal (the first, one inside, the last) and
+# have columns in its key block: single tokens, packed heads, tiles of two query blocks
+@pytest.mark.parametrize("hq,c,n", [(3, 1, 1000), (7, 1, 64), (4, 2, 1000), (5, 40, 2048), (3, 130, 1000), (2, 300, 4999)])
+def test_columns_of_heads_that_have_every_diagonal(hq, c, n):
+    d, n_blk = 64, (n + 63) // 64
+    gen = torch.Generator(device="cuda").manual_seed(3150)
+    q, k, v = (torch.randn(s, generator=gen, device="cuda", dtype=torch.bfloat16) for s in ((c, hq, d), (n, 1, d), (n, 1, d)))
+    rng = np.random.default_rng(3151)
+    ck = vs.Chunk(hq, 1, d, c, n - c, 0.125, vertical_budget=70, slash_budget=n_blk)
+    vi = np.full((hq, 70), -1, np.int32); si = np.full((hq, n_blk), -1, np.int32)
+    sc = np.zeros(hq, np.int32)
+    for h in range(hq):
+        n_col = min(70, n)
+        vi[h, :n_col] = np.sort(rng.choice(n, n_col, replace=False))
+        offs = 64 * np.arange(n_blk)
+        if h % 4: offs = np.delete(offs, [0, n_blk // 2, n_blk - 1][h % 4 - 1])
+        sc[h] = len(offs); si[h, :sc[h]] = offs
+    _check_by_gathering(ck, q, k, v, vi, si, sc)
+    if c > 1: return
+    # the same token in a batch beside one without index sets
+    sets = [_t(x) for x in (vi, (vi >= 0).sum(1).astype(np.int32), si, sc)]
+    outs = [torch.empty_like(q) for _ in range(2)]
+    reqs = [dict(q=q, k=k, v=v, out=outs[x], q_start=n - c, lse=None, sets=tuple(sets) if x == 0 else None) for x in range(2)]
+    vs.attn_batch(ck, vs.request_table(reqs, q.device), 2, q, k, v, outs[0])
+    one = vs.sparse_attn_prefill(ck, q, k, v, *sets)
+    torch.cuda.synchronize()
+    assert (outs[0].float() - (one[0] if isinstance(one, tuple) else one).float()).norm() <= 2e-2 * outs[0].float().norm()
+
+
+def _check_by_gathering(ck, q, k, v, vi, si, sc):
+    """Outputs of one KV head against fp32 softmax over the keys that the sets name, gathered."""
+    (c, hq, _), n = q.shape, k.shape[0]
+    out = vs.sparse_attn_prefill(ck, q, k, v, *[_t(x) for x in (vi, (vi >= 0).sum(1).astype(np.int32), si, sc)])
     out = out[0] if isinstance(out, (tuple, list)) else out
     for h in range(hq):
         offs = torch.as_tensor(si[h, :sc[h]], device="cuda").long()
@@ -184,7 +219,7 @@ def test_lists_of_several_windows(hq, c, win):
             pos = n - c + r
             blocks = pos // 64 - ad[ad <= pos // 64]
             keys = (64 * blocks[:, None] + torch.arange(64, device="cuda")).flatten()
-            keys = torch.cat([keys, torch.as_tensor(vi[h], device="cuda").long()]).unique()
+            keys = torch.cat([keys, torch.as_tensor(vi[h][vi[h] >= 0], device="cuda").long()]).unique()
             keys = keys[keys <= pos]
             p = torch.softmax((k[keys, 0].float() @ q[r, h].float()) * 0.125, 0)
             ref = p @ v[keys, 0].float()
