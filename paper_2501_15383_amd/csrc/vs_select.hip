@@ -13,8 +13,8 @@
 //               this one launch, bound by its vector instructions (of 32 scores per lane: loads and range 3.0 us, first
 //               digit 3, the pass that lists the threshold's bin 1.5, emission 2.5) and, of short rows, by its barriers
 //   candidates  longer rows are thinned out first.  A sample of 8,192 (16,384) scores per row gives a floor that
-//               about k + 4.5 sigma entries exceed, and only those entries are kept, in LDS if there are at most
-//               kSelCand of them.  With a workspace the whole chip makes the lists, in one pass over the scores
+//               about k + 4.5 sigma entries exceed, and only those entries are kept, in registers (without a workspace: in LDS) if there
+//               are at most kSelCand of them.  With a workspace the whole chip makes the lists, in one pass over the scores
 //               (k_sel_sample, k_sel_filter; bound by that read at 1M keys); without a workspace k_sel_row makes its
 //               row's own.  A threshold that falls on a crowd of equal
 //               scores is the floor itself: all candidates are wanted, and of the crowd its first entries, for which the row
@@ -26,8 +26,8 @@
 // scores once per digit of 8 bits, once for the counts and once for the compaction (k_slice_*): the list would be one
 // workgroup's work.
 // Measured on one MI355X, 28 heads, budgets 1000 / 6096, against four digits, a count and a write pass over all
-// scores in seven launches: 8,192 scores per row 8 us (67), 32,768 15 us (70), 300,001 55 us (152), 1M 107 us
-// (345: filter 64 us = 3.7 TB/s, sample 26, rows 28, under a profiler); 4 heads, budgets 128 / 256, 1M: 54 us (98).
+// scores in seven launches: 8,192 scores per row 8 us (67), 32,768 15 us (70), 300,001 47 us (152), 1M 90 us
+// (345: filter 59 us = 4 TB/s, sample 17, rows 16, under a profiler); 4 heads, budgets 128 / 256, 300,000: 24 us.
 #include "vs_common.h"
 
 namespace vs {
@@ -317,17 +317,10 @@ __device__ __forceinline__ void sel_wave_base(SelShared<R>& sh, int par, uint32_
 // to the threshold, follows from the list, so that nearly every wave emits against one threshold.  (With two more digits, a count
 // of both kinds and two ballots per group of 64, one counter per bin and 8, 16 or 32 scores per lane, 28 heads, 20,000 scores took 21.0
 // us against 12.6, 32,768 20.9 against 15.4, 12,288 12.1 against 9.8, 4,096 8.4 against 6.9.)
-template <int KPT, int R>
-__device__ __forceinline__ void sel_from_registers(SelShared<R>& sh, const SelRow& r, int64_t n) {
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  int i0 = r.f + wv * (64 * KPT) + lane;
-  uint32_t key[KPT];
-#pragma unroll
-  for (int e = 0; e < KPT; ++e) {
-    const int i = i0 + 64 * e;
-    const uint32_t x = order_key(r.sc[i < n ? i : (int)n - 1]);   // unconditional, so that the loads overlap
-    key[e] = i < n ? x : 0u;   // no finite score has key 0: neither counted nor emitted below
-  }
+// index(e): that of the lane's score e; settle: see RowIndex
+template <int KPT, int R, typename Index>
+__device__ __forceinline__ void sel_keys(SelShared<R>& sh, const SelRow& r, uint32_t (&key)[KPT], Index&& index) {
+  const int wv = threadIdx.x >> 6;
   if (threadIdx.x == 0) sh.few = 0;
   if (threadIdx.x < kSelWaves) sh.extra[threadIdx.x] = 0;
   uint32_t lo = ~0u, hi = 0u, T, need_eq;
@@ -391,7 +384,7 @@ __device__ __forceinline__ void sel_from_registers(SelShared<R>& sh, const SelRo
     }
   }
   sel_wave_base(sh, 0, g, q, gt, eq, ag, ae);
-  if constexpr (KPT > 32) asm volatile("" : "+v"(i0));   // (so are the indices: held from the loads on they were what spilled)
+  index.settle();
   asm volatile("" : "+v"(T));   // the lane masks are made again: KPT of them do not fit the scalar registers
   const uint32_t eq_s = __builtin_amdgcn_readfirstlane(eq), q_s = __builtin_amdgcn_readfirstlane(q), need_s = __builtin_amdgcn_readfirstlane(need_eq);
   if (eq_s >= need_s || eq_s + q_s <= need_s) {
@@ -399,11 +392,85 @@ __device__ __forceinline__ void sel_from_registers(SelShared<R>& sh, const SelRo
     if (eq_s < need_s) --T;
     gt += eq_s < need_s ? eq_s : need_s;
 #pragma unroll
-    for (int e = 0; e < KPT; ++e) sel_emit(r, key[e] > T, i0 + 64 * e, gt);
+    for (int e = 0; e < KPT; ++e) sel_emit(r, key[e] > T, index(e), gt);
   } else {
 #pragma unroll
-    for (int e = 0; e < KPT; ++e) sel_emit(r, need_eq, key[e] > T, key[e] == T, i0 + 64 * e, gt, eq);
+    for (int e = 0; e < KPT; ++e) sel_emit(r, need_eq, key[e] > T, key[e] == T, index(e), gt, eq);
   }
+}
+
+template <int KPT>
+struct RowIndex {
+  int i0;
+  __device__ __forceinline__ void settle() {
+    if constexpr (KPT > 32) asm volatile("" : "+v"(i0));   // (the indices are made again: held from the loads on they were what spilled)
+  }
+  __device__ __forceinline__ int operator()(int e) const { return i0 + 64 * e; }
+};
+template <int KPT, int R>
+__device__ __forceinline__ void sel_from_registers(SelShared<R>& sh, const SelRow& r, int64_t n) {
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  RowIndex<KPT> index = {r.f + wv * (64 * KPT) + lane};
+  uint32_t key[KPT];
+#pragma unroll
+  for (int e = 0; e < KPT; ++e) {
+    const int i = index(e);
+    const uint32_t x = order_key(r.sc[i < n ? i : (int)n - 1]);   // unconditional, so that the loads overlap
+    key[e] = i < n ? x : 0u;   // no finite score has key 0: neither counted nor emitted below
+  }
+  sel_keys<KPT>(sh, r, key, index);
+}
+// The m <= 1,024 KPT candidates of a row whose at most kSelBins slices lie anywhere in its list (the filter's), into registers in the
+// order of their indices: the slices' places from a sum over their lengths, a candidate's slice by bisection in LDS, all of a lane's
+// at once.  (Copied to LDS as they lay there and brought in order 64 at a time by bisection over lanes, for the count and again
+// for the compaction, three digits: 28 heads, 50,000 scores 35.5 us, 24.4 so, 300,001
+// 54.8 and 46.5, 1M 103 and 90.)
+template <int KPT>
+struct ListIndex {
+  int at[KPT];
+  __device__ __forceinline__ void settle() {}
+  __device__ __forceinline__ int operator()(int e) const { return at[e]; }
+};
+template <int KPT, int R>
+__device__ __forceinline__ void sel_from_list(SelShared<R>& sh, uint32_t (&place)[kSelBins], const uint2* cand, const uint2* slices,
+                                              const SelRow& r, int n_slices, int m) {
+  static_assert(kSelBins == 2 * kSelThreads, "two slices per thread");
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const uint2 none = make_uint2(0u, 0u), s0 = 2 * tid < n_slices ? slices[2 * tid] : none, s1 = 2 * tid + 1 < n_slices ? slices[2 * tid + 1] : none;
+  uint32_t inc = s0.y + s1.y;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint32_t y = __shfl_up(inc, d);
+    if (lane >= d) inc += y;
+  }
+  if (lane == 63) sh.wsum[wv] = inc;
+  __syncthreads();
+  uint32_t at = inc - s0.y - s1.y;
+#pragma unroll
+  for (int x = 0; x < kSelWaves; ++x) at += x < wv ? sh.wsum[x] : 0u;
+  sh.hist[2 * tid] = at;
+  sh.hist[2 * tid + 1] = at + s0.y;
+  place[2 * tid] = s0.x - at;
+  place[2 * tid + 1] = s1.x - at - s0.y;
+  __syncthreads();
+  const int first = wv * (64 * KPT) + lane;
+  int j[KPT];
+#pragma unroll
+  for (int e = 0; e < KPT; ++e) j[e] = 0;
+  for (int d = n_slices > 1 ? 1 << (31 - __clz(n_slices - 1)) : 0; d >= 1; d >>= 1)
+#pragma unroll
+    for (int e = 0; e < KPT; ++e)
+      if (sh.hist[j[e] + d] <= (uint32_t)(first + 64 * e)) j[e] += d;   // (places behind the last slice are m)
+  ListIndex<KPT> index;
+  uint32_t key[KPT];
+#pragma unroll
+  for (int e = 0; e < KPT; ++e) {
+    const int i = first + 64 * e;
+    const uint2 c = cand[i < m ? (uint32_t)i + place[j[e]] : 0u];
+    key[e] = i < m ? c.x : 0u;
+    index.at[e] = (int)c.y;
+  }
+  sel_keys<KPT>(sh, r, key, index);
 }
 
 // The m candidates of a row (keys above floor_key, with their indices), in n_slices slices: slice_of(s) = (first candidate,
@@ -664,6 +731,7 @@ __global__ __launch_bounds__(kSelThreads) void k_sel_row(const SelArgs a) {
     sel_from_registers<KPT>(sh, r, a.n);
   } else {
     uint2* const cl = (uint2*)sel_dyn;
+    __shared__ uint32_t place[kSelBins];
     const int samples = r.kind ? a.samples_s : a.samples_v;
     const bool listed = a.hdr != nullptr;   // the filter made the list
     uint32_t room = listed ? a.cap : (uint32_t)kSelCand;
@@ -710,14 +778,11 @@ __global__ __launch_bounds__(kSelThreads) void k_sel_row(const SelArgs a) {
       else
         for (int i = (int)met + tid; i < m; i += kSelThreads) r.out[r.f + equal + i] = (int32_t)cl[i].y;
     } else if (listed) {
-      if (m <= kSelCand) {
-#pragma unroll
-        for (int e = 0; e < kSelCand / kSelThreads; ++e) {
-          const int i = e * kSelThreads + tid;
-          if (i < m) cl[i] = cand[i];
-        }
-        __syncthreads();
-        sel_from_candidates(sh, cl, r, a.n_slices, m, hd.floor_key, slice_of);
+      if (m <= kSelCand && a.n_slices <= kSelBins) {
+        static_assert(kSelCand == 16 * kSelThreads, "the longest list in registers");
+        if (m <= 8 * kSelThreads) sel_from_list<8>(sh, place, cand, slices, r, a.n_slices, m);
+        else if (m <= 12 * kSelThreads) sel_from_list<12>(sh, place, cand, slices, r, a.n_slices, m);
+        else sel_from_list<16>(sh, place, cand, slices, r, a.n_slices, m);
       } else {
         sel_from_candidates(sh, cand, r, a.n_slices, m, hd.floor_key, slice_of);
       }
@@ -1103,7 +1168,7 @@ hipError_t launch_select(const vs_params& p, const float* vscore, const float* s
     hipLaunchKernelGGL(k_sel_filter, dim3((unsigned)ceil_div(l.n_slices, kSelFilterThreads / 64), rows.x),
                        dim3(kSelFilterThreads), 0, st, a);
   }
-  hipLaunchKernelGGL(k_sel_row<0>, rows, block, kSelCand * sizeof(uint2), st, a);
+  hipLaunchKernelGGL(k_sel_row<0>, rows, block, a.hdr ? 0 : kSelCand * sizeof(uint2), st, a);
   return hipGetLastError();
 }
 

@@ -54,6 +54,19 @@ def test_select_equals_a_full_sort(n, kind):
                 assert torch.equal(a, b), f"{nm}: n {n}, {kind}, budgets {bv} / {bs}"
 
 
+# lists in registers: 8, 12 and 16 candidates per lane, numbers of slices (2,048 scores behind the forced ones) around a power of two, the
+# most that are placed at once (2,048) and one more
+@pytest.mark.parametrize("kind", ["spread", "ties", "crowded"])
+@pytest.mark.parametrize("bs", [300, 6500, 9500, 13000])
+@pytest.mark.parametrize("n", [32 * 2048 + 64, 32 * 2048 + 65, 64 * 2048 + 63, 2048 * 2048 + 64, 2048 * 2048 + 65])
+def test_lists_in_registers(n, bs, kind):
+    g = torch.Generator(device="cuda:0").manual_seed(200 + n)
+    vsc, ssc = _scores(kind, 2, n, g), _scores(kind, 2, n, g)
+    ck = vs.Chunk(2, 1, 128, 64, n - 64, 0.1, vertical_budget=1000, slash_budget=bs, keep_first_cols=1, keep_local_band=64)
+    for a, b in zip(vs.select(ck, vsc, ssc), (*_want(vsc, 1000, 1), *_want(ssc, bs, 64))):
+        assert torch.equal(a, b), f"n {n}, {kind}, {bs} offsets"
+
+
 # (heads, keys, offsets kept): lists in the workspace that fit the LDS, that do not, and that are not made (slices); of the
 # static entry point, whose scratch holds 12 MB, the first as well, rows that list their own candidates, and slices
 @pytest.mark.parametrize("kind", ["spread", "ties", "sparse", "signed"])
