@@ -26,8 +26,8 @@
 // scores once per digit of 8 bits, once for the counts and once for the compaction (k_slice_*): the list would be one
 // workgroup's work.
 // Measured on one MI355X, 28 heads, budgets 1000 / 6096, against four digits, a count and a write pass over all
-// scores in seven launches: 8,192 scores per row 8 us (67), 32,768 15 us (70), 300,001 47 us (152), 1M 90 us
-// (345: filter 59 us = 4 TB/s, sample 17, rows 16, under a profiler); 4 heads, budgets 128 / 256, 300,000: 24 us.
+// scores in seven launches: 8,192 scores per row 8 us (67), 32,768 15 us (70), 300,001 44 us (152), 1M 88 us
+// (345: filter 57 us = 4.1 TB/s, sample 17, rows 16, under a profiler); 4 heads, budgets 128 / 256, 300,000: 24 us.
 #include "vs_common.h"
 
 namespace vs {
@@ -811,7 +811,8 @@ __global__ __launch_bounds__(kSelThreads) void k_sel_sample(const SelArgs a) {
 
 // The candidates of a row's slices: the scores are read once, counted, given room in the row's list by one atomic
 // addition per workgroup (so the slices lie there in the order of arrival; k_sel_row goes by the table) and written in order,
-// a slice per wave.
+// a slice per wave.  Four consecutive scores per lane and load, counted in the lane: with one per lane and load and two population
+// counts per 64 scores, 28 heads, 300,001 scores 17.4 us, 15.7 so, 1M 61 and 57 (4.1 TB/s).
 __global__ __launch_bounds__(kSelFilterThreads) void k_sel_filter(const SelArgs a) {
   const SelRow r = sel_row(a, blockIdx.y);
   SelHeader* const hd = a.hdr + blockIdx.y;
@@ -824,15 +825,21 @@ __global__ __launch_bounds__(kSelFilterThreads) void k_sel_filter(const SelArgs 
   const int slice = blockIdx.x * NW + wv;
   const int64_t s0 = r.f + (int64_t)slice * kSelSlice;
   __shared__ uint32_t wcnt[NW][2], base_s;
+  // entry 4 e + f: 256 e + 4 lane + f of the slice (rows start at any word)
   int32_t x[PER];
+  typedef int32_t i32x4 __attribute__((ext_vector_type(4), aligned(4)));
   if (s0 + kSelSlice <= a.n) {   // a whole slice: one address
     const int32_t* const p = (const int32_t*)r.sc + s0;
 #pragma unroll
-    for (int e = 0; e < PER; ++e) x[e] = p[lane + 64 * e];
+    for (int e = 0; e < PER / 4; ++e) {
+      const i32x4 v = *(const i32x4*)(p + 256 * e + 4 * lane);
+#pragma unroll
+      for (int f = 0; f < 4; ++f) x[4 * e + f] = v[f];
+    }
   } else {
 #pragma unroll
     for (int e = 0; e < PER; ++e) {
-      const int64_t i = s0 + lane + 64 * e;
+      const int64_t i = s0 + 256 * (e / 4) + 4 * lane + e % 4;
       const int32_t b = ((const int32_t*)r.sc)[i < a.n ? i : a.n - 1];
       x[e] = i < a.n ? b : (int32_t)0xFFFFFFFF;   // behind the row: the image is the least one
     }
@@ -841,12 +848,17 @@ __global__ __launch_bounds__(kSelFilterThreads) void k_sel_filter(const SelArgs 
 #pragma unroll
     for (int e = 0; e < PER; ++e) x[e] ^= (x[e] >> 31) & 0x7FFFFFFF;
   }
-  uint32_t c = 0, q = 0;
+  uint32_t c = 0, q = 0;   // of the lane first: entries above the floor, and at or above it
 #pragma unroll
   for (int e = 0; e < PER; ++e) {
-    c += __popcll(__ballot(x[e] > floor_x));
-    q += __popcll(__ballot(x[e] == floor_x));
+    c += x[e] > floor_x ? 1u : 0u;
+    q += x[e] >= floor_x ? 1u : 0u;
   }
+  uint32_t both = c | q << 16;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) both += __shfl_xor(both, d);
+  c = __builtin_amdgcn_readfirstlane(both & 0xFFFFu);
+  q = __builtin_amdgcn_readfirstlane(both >> 16) - c;
   if (lane == 0) { wcnt[wv][0] = c; wcnt[wv][1] = q; }
   __syncthreads();
   uint32_t before = 0, total = 0, equal = 0;
@@ -868,13 +880,21 @@ __global__ __launch_bounds__(kSelFilterThreads) void k_sel_filter(const SelArgs 
   uint32_t pos = 0;
   asm volatile("" : "+s"(floor_x));   // the lane masks are made again rather than kept
 #pragma unroll
-  for (int e = 0; e < PER; ++e) {
-    const uint64_t b = __ballot(x[e] > floor_x);
-    if (b) {
-      if (x[e] > floor_x)
-        out[pos + __builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u))] =
-            make_uint2((uint32_t)x[e] ^ 0x80000000u, (uint32_t)(s0 + lane + 64 * e));
-      pos += __popcll(b);
+  for (int e = 0; e < PER / 4; ++e) {
+    uint64_t b[4];
+    uint32_t at = pos;
+#pragma unroll
+    for (int f = 0; f < 4; ++f) {
+      b[f] = __ballot(x[4 * e + f] > floor_x);
+      at = __builtin_amdgcn_mbcnt_hi((uint32_t)(b[f] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b[f], at));
+    }
+#pragma unroll
+    for (int f = 0; f < 4; ++f) {
+      if (x[4 * e + f] > floor_x) {
+        out[at] = make_uint2((uint32_t)x[4 * e + f] ^ 0x80000000u, (uint32_t)(s0 + 256 * e + 4 * lane + f));
+        ++at;
+      }
+      pos += __popcll(b[f]);
     }
   }
 }
