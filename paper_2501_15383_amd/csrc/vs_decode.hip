@@ -19,7 +19,7 @@
 // Measured on one MI355X, 28 query / 4 KV heads, head_dim 128, against the tile kernel of vs_attn.hip with the heads as rows of
 // its 128-row tiles (copies of a step shared by four waves of which one multiplied, a barrier per step, one range count for a
 // whole batch): one token at 5,003 keys 39 -> 15 us, at 1M keys 510 -> 363 (5.9 TB/s of K and V); 24 tokens at 2K to 64K keys
-// 395 -> 215 (5.8 TB/s); 8 tokens with index sets at 262,144 keys 1,042 -> 776 (lists 252 -> 29 of it).
+// 395 -> 215 (5.8 TB/s); 8 tokens with index sets at 262,144 keys 1,042 -> 770 (lists 252 -> 17 of it).
 #include "vs_common.h"
 
 namespace vs {
@@ -72,10 +72,11 @@ __device__ __forceinline__ bool decode_takes(const DecodeArgs& a, const vs_reque
 }
 __device__ __forceinline__ int decode_blocks(const vs_request& rq) { return (int)((rq.q_start + kBlock) / kBlock); }
 // units of segment x (side neighbouring KV heads) of request r: as many as its longest head has
+template <int SIDE>
 __device__ __forceinline__ int decode_seg_len(const DecodeArgs& a, int r, int x) {
-  const int4* const len = a.len + (int64_t)r * a.n_kv_heads + x * a.side;
+  const int4* const len = a.len + (int64_t)r * a.n_kv_heads + x * SIDE;
   int n = len[0].y;
-  for (int e = 1; e < a.side; ++e) n = len[e].y > n ? len[e].y : n;
+  for (int e = 1; e < SIDE; ++e) n = len[e].y > n ? len[e].y : n;
   return n;
 }
 // share w of n covers units [w T / n, (w + 1) T / n)
@@ -126,7 +127,7 @@ __device__ __forceinline__ void decode_body(const DecodeArgs& a) {
     if (!decode_takes(a, rq)) return 0;
     if (!rq.s_idx) return (int64_t)decode_blocks(rq) * a.n_seg;
     int64_t n = 0;
-    for (int x = 0; x < a.n_seg; ++x) n += decode_seg_len(a, r, x);
+    for (int x = 0; x < a.n_seg; ++x) n += decode_seg_len<SIDE>(a, r, x);
     return n;
   };
   int64_t T = a.one_T, first = 0;
@@ -213,7 +214,7 @@ __device__ __forceinline__ void decode_body(const DecodeArgs& a) {
       n_ent = __builtin_amdgcn_readfirstlane(l2.x);
       own_len = __builtin_amdgcn_readfirstlane(l2.y);
       full = l2.z;
-      seg_len = __builtin_amdgcn_readfirstlane(decode_seg_len(a, r, sg));
+      seg_len = __builtin_amdgcn_readfirstlane(decode_seg_len<SIDE>(a, r, sg));
     }
     if (blk >= seg_len) {   // the share starts in a later segment of this request
       blk -= seg_len;
@@ -224,7 +225,7 @@ __device__ __forceinline__ void decode_body(const DecodeArgs& a) {
     const bool whole = blk == 0 && take64 == seg_len;
     // the same part of the head's own walk (lists of neighbouring heads differ in length)
     int b0 = (int)blk, b1 = (int)(blk + take64);
-    if (own_len != seg_len) {
+    if (SIDE > 1 && own_len != seg_len) {
       b0 = (int)short_div((int64_t)b0 * own_len, seg_len);
       b1 = (int)short_div((int64_t)b1 * own_len, seg_len);
     }
@@ -501,18 +502,18 @@ __global__ __launch_bounds__(kDecThreads, 2) void k_decode_pairs(const DecodeArg
 // are compared (four waves, and the references first: one token at 5,003 keys 14.1 us with its two launches, 12.1 so and with the
 // shares counted on the host).  Eight waves where a KV head lies in more than 32 shares, else four: 60 tokens of 40 heads, a share or
 // two each, 71 us with four, 75 with eight.
-template <int D, int NW>
+template <int D, int NW, int SIDE>
 __global__ __launch_bounds__(64 * NW) void k_decode_combine(const DecodeArgs a) {
   const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int h = blockIdx.x, r = blockIdx.y, rows = a.side * a.group, sg = h / rows, q = h - sg * rows;
+  const int h = blockIdx.x, r = blockIdx.y, rows = SIDE * a.group, sg = h / rows, q = h - sg * rows;
   const vs_request rq = decode_request(a, r);
   if (!decode_takes(a, rq)) return;
   const int64_t T = a.one_T ? a.one_T : a.plan[0], n = a.one_T ? a.one_n : a.plan[1];
   int64_t from = a.one_T ? 0 : a.plan[2 + r];
   int seg_len = decode_blocks(rq);
   if (rq.s_idx) {
-    for (int x = 0; x < sg; ++x) from += decode_seg_len(a, r, x);
-    seg_len = decode_seg_len(a, r, sg);
+    for (int x = 0; x < sg; ++x) from += decode_seg_len<SIDE>(a, r, x);
+    seg_len = decode_seg_len<SIDE>(a, r, sg);
   } else {
     from += (int64_t)sg * seg_len;
   }
@@ -731,15 +732,19 @@ hipError_t launch_decode(const vs_params& p, const vs_request* one, const vs_req
   }
   const dim3 grid((unsigned)l.shares), cgrid((unsigned)p.n_q_heads, (unsigned)n_req);
   const bool many = l.shares > 32 * (int64_t)n_req * a.n_seg;
-  if (p.head_dim == 128) {
-    if (l.side == 2) hipLaunchKernelGGL(k_decode_pairs, grid, dim3(kDecThreads), decode_lds_bytes<128>(), st, a);
-    else hipLaunchKernelGGL(k_decode<128>, grid, dim3(kDecThreads), decode_lds_bytes<128>(), st, a);
-    if (many) hipLaunchKernelGGL((k_decode_combine<128, 8>), cgrid, dim3(512), 0, st, a);
-    else hipLaunchKernelGGL((k_decode_combine<128, 4>), cgrid, dim3(256), 0, st, a);
+  const auto fold = [&](auto&& four, auto&& eight) {
+    if (many) hipLaunchKernelGGL(eight, cgrid, dim3(512), 0, st, a);
+    else hipLaunchKernelGGL(four, cgrid, dim3(256), 0, st, a);
+  };
+  if (l.side == 2) {
+    hipLaunchKernelGGL(k_decode_pairs, grid, dim3(kDecThreads), decode_lds_bytes<128>(), st, a);
+    fold(k_decode_combine<128, 4, 2>, k_decode_combine<128, 8, 2>);
+  } else if (p.head_dim == 128) {
+    hipLaunchKernelGGL(k_decode<128>, grid, dim3(kDecThreads), decode_lds_bytes<128>(), st, a);
+    fold(k_decode_combine<128, 4, 1>, k_decode_combine<128, 8, 1>);
   } else {
     hipLaunchKernelGGL(k_decode<64>, grid, dim3(kDecThreads), decode_lds_bytes<64>(), st, a);
-    if (many) hipLaunchKernelGGL((k_decode_combine<64, 8>), cgrid, dim3(512), 0, st, a);
-    else hipLaunchKernelGGL((k_decode_combine<64, 4>), cgrid, dim3(256), 0, st, a);
+    fold(k_decode_combine<64, 4, 1>, k_decode_combine<64, 8, 1>);
   }
   return hipGetLastError();
 }
