@@ -87,17 +87,12 @@ struct AttnArgs {
   int32_t n_split, n_units, n_whole, first_piece;
   float* part_o;
   float* part_ml;
-  // Uneven cut of the cut units (own_cut; 0: the even one above): slots of partial results, and
-  // what k_attn_pieces leaves: the number of pieces (0: the even cut stays), the pieces, ranges and first slot of every cut unit
-  int32_t own_slots;
-  int32_t* own_n;
-  OwnPiece* own_pieces;
-  int2* own_units;
   int32_t first_slot;   // BATCH: of the request's partial results
   // SPLIT: query heads of one KV group that share a tile (1, 2 or 4).  Chunks whose rows lie in one query block leave
   // half of a tile's waves (three quarters: at most 32 rows) without rows; these waves take further heads.
   // n_hs: tiles per KV group = ceil(group / pack)
   int32_t pack, n_hs;
+  int32_t own_slots;    // slots of partial results for an uneven cut of the cut units (own_cut; 0: the even one above)
   // SPLIT: eight queues of pieces, one per XCD (kQueueStride words apart; zero at the start of the launch)
   uint32_t* queue;
   const __bf16* k;
@@ -154,6 +149,11 @@ struct AttnArgs {
   int32_t n_req, head_dim;
   int64_t max_q_len, max_n_k;
   int32_t skip_single;   // BATCH: single tokens are the decode kernel's
+  // What k_attn_pieces leaves of an uneven cut: the number of pieces (0: the even cut stays), the pieces, ranges and first slot of every
+  // cut unit.  (Behind everything else: a short kernel waits for each line of its arguments.)
+  int32_t* own_n;
+  OwnPiece* own_pieces;
+  int2* own_units;
 };
 
 constexpr int kMaxSplit = 128;                     // ranges of a unit at most
@@ -483,7 +483,7 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
   AttnArgs a_req;
   if constexpr (BATCH) a_req = a0;
   const AttnArgs& a = BATCH ? a_req : a0;
-  int g, h, qt, sp = 0, slot = 0, n_sp = 1, cc_lo = -1, cc_hi = 0;
+  int g, h, qt, sp = 0, slot = 0, n_sp = 1, own = -1;   // own: piece of an uneven cut
   bool whole = true, none = false;   // none: no tile for this workgroup in this round
   if constexpr (SPLIT) {
     none = u >= n_pieces;
@@ -500,13 +500,12 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
     if (!whole && !none) {
       const int v = u - a.n_whole, n = a.n_units - a.n_whole;
       if (!BATCH && a.own_slots > 0 && __builtin_amdgcn_readfirstlane(*a.own_n) > 0) {
+        own = v;
         const OwnPiece* const o = a.own_pieces + v;
         e = __builtin_amdgcn_readfirstlane(o->unit);
         sp = __builtin_amdgcn_readfirstlane(o->sp);
         n_sp = __builtin_amdgcn_readfirstlane(o->n_sp);
         slot = __builtin_amdgcn_readfirstlane(o->slot);
-        cc_lo = __builtin_amdgcn_readfirstlane(o->cc_lo);
-        cc_hi = __builtin_amdgcn_readfirstlane(o->cc_hi);
       } else {
         n_sp = a.n_split;
         sp = v / n;
@@ -647,12 +646,13 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
   const int vstep = SPLIT && !whole ? n_sp : 1;
   int vlin = sp - vstep;
   if (SPLIT && !whole) {
-    if (cc_lo < 0) {
-      const int per = (cc_last + n_sp) / n_sp;  // ceil((cc_last + 1) / n_sp)
-      cc_lo = sp * per;
-      cc_hi = cc_lo + per - 1 < cc_last ? cc_lo + per - 1 : cc_last;
+    const int per = (cc_last + n_sp) / n_sp;  // ceil((cc_last + 1) / n_sp)
+    int cc_lo = sp * per;
+    cc_end = cc_lo + per - 1 < cc_last ? cc_lo + per - 1 : cc_last;
+    if (!BATCH && own >= 0) {
+      cc_lo = __builtin_amdgcn_readfirstlane(a.own_pieces[own].cc_lo);
+      cc_end = __builtin_amdgcn_readfirstlane(a.own_pieces[own].cc_hi);
     }
-    cc_end = cc_hi;
     int lo = 0, hi = (int)a.ent_len - 1;  // the last entry is a sentinel: an answer always exists
     if (!BATCH && !a.ent) lo = hi = pack > 1 ? (cc_lo > NQB - 1 ? cc_lo - (NQB - 1) : 0) : cc_lo;
     while (lo < hi) {
