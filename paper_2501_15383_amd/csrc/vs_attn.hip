@@ -92,7 +92,6 @@ struct AttnArgs {
   // half of a tile's waves (three quarters: at most 32 rows) without rows; these waves take further heads.
   // n_hs: tiles per KV group = ceil(group / pack)
   int32_t pack, n_hs;
-  int32_t own_slots;    // slots of partial results for an uneven cut of the cut units (own_cut; 0: the even one above)
   // SPLIT: eight queues of pieces, one per XCD (kQueueStride words apart; zero at the start of the launch)
   uint32_t* queue;
   const __bf16* k;
@@ -149,8 +148,10 @@ struct AttnArgs {
   int32_t n_req, head_dim;
   int64_t max_q_len, max_n_k;
   int32_t skip_single;   // BATCH: single tokens are the decode kernel's
-  // What k_attn_pieces leaves of an uneven cut: the number of pieces (0: the even cut stays), the pieces, ranges and first slot of every
-  // cut unit.  (Behind everything else: a short kernel waits for each line of its arguments.)
+  // OWN: slots of partial results for an uneven cut of the cut units (own_cut), and what k_attn_pieces leaves of it: the number of pieces
+  // (0: the even cut stays), the pieces, ranges and first slot of every cut unit.  (Behind everything else: a short kernel waits
+  // for each line of its arguments.)
+  int32_t own_slots;
   int32_t* own_n;
   OwnPiece* own_pieces;
   int2* own_units;
@@ -402,9 +403,12 @@ __device__ __forceinline__ uint32_t lds_address(const void* p) {
 }
 
 constexpr int kHeadShift = 27;   // vertical tile of packed heads: (head << kHeadShift) | tile of 64 columns (a head has at most 2^25)
-template <int D, int NQB, bool DCA, bool SPLIT, bool BATCH = false>
-__global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
+// OWN: the cut units may have ranges by the lengths of their lists.  (Instantiations of their own: with this decided in the others, dense
+// calls of 20 to 500 rows took 0.15 to 0.5 us of 12 to 24 more.)
+template <int D, int NQB, bool DCA, bool SPLIT, bool BATCH, bool OWN>
+__device__ __forceinline__ void attention_body(const AttnArgs& a0) {
   static_assert(!BATCH || (SPLIT && !DCA), "several requests per launch ride on the key-split kernel");
+  static_assert(!OWN || (SPLIT && !BATCH), "uneven ranges are those of cut units of a single call");
   constexpr int DCH = D / 8;           // 16-byte chunks per row
   constexpr int DSTEPS = D / 16;       // MFMA k-steps of QK^T
   constexpr int DB = D / 32;           // 32-row blocks of O^T
@@ -458,7 +462,7 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
   int n_pieces = 0;
   if constexpr (BATCH) n_pieces = __builtin_amdgcn_readfirstlane(a0.plan[a0.n_req].first);
   else if constexpr (SPLIT) n_pieces = a0.n_whole - a0.first_piece + (a0.n_units - a0.n_whole) * a0.n_split;
-  if (SPLIT && !BATCH && a0.own_slots > 0) {
+  if constexpr (OWN) {
     const int own = __builtin_amdgcn_readfirstlane(*a0.own_n);
     if (own > 0) n_pieces = a0.n_whole - a0.first_piece + own;
   }
@@ -469,7 +473,7 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
   if constexpr (SPLIT) {
     u = ((q_pos / a0.members) * 8 + q_grp) * a0.members + q_pos % a0.members;
     // (pieces that the host cannot count: fewer than workgroups are dealt evenly over the XCDs, as launch_attention does)
-    if ((BATCH || a0.own_slots > 0) && n_pieces < (int)gridDim.x) {
+    if ((BATCH || OWN) && n_pieces < (int)gridDim.x) {
       const int each = (n_pieces + 7) >> 3;
       u = member < each ? grp * each + member : n_pieces;
     }
@@ -499,7 +503,7 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
     whole = u < a.n_whole;
     if (!whole && !none) {
       const int v = u - a.n_whole, n = a.n_units - a.n_whole;
-      if (!BATCH && a.own_slots > 0 && __builtin_amdgcn_readfirstlane(*a.own_n) > 0) {
+      if (OWN && __builtin_amdgcn_readfirstlane(*a.own_n) > 0) {
         own = v;
         const OwnPiece* const o = a.own_pieces + v;
         e = __builtin_amdgcn_readfirstlane(o->unit);
@@ -507,12 +511,12 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
         n_sp = __builtin_amdgcn_readfirstlane(o->n_sp);
         slot = __builtin_amdgcn_readfirstlane(o->slot);
       } else {
-        n_sp = a.n_split;
+        if (OWN) n_sp = a.n_split;
         sp = v / n;
         e = a.n_whole + v - sp * n;
         slot = BATCH ? v + a.first_slot : v;
       }
-      whole = n_sp == 1;
+      if (OWN) whole = n_sp == 1;
     }
     g = h = qt = 0;
     if (!none) unit_of(a, e, g, h, qt);
@@ -639,17 +643,17 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
   // ---- tile iterator (uniform over the workgroup, kept in scalar registers) -----------------
   // kind 0: slash tile, idx = cc, mask = query blocks that use it; kind 1: vertical tile,
   // idx = vt; kind 2: end.  Entries are fetched 64 at a time (one per lane), one batch ahead.
-  // With a key split this workgroup walks the entries with cc in [cc_lo, cc_end] (of n_sp ranges of equal distances, or an uneven
-  // cut's) and every n_sp-th vertical tile; the first entry is searched for with 64 probes at a time (the list ascends
+  // With a key split this workgroup walks the entries with cc in [cc_lo, cc_end] (of `ranges` of equal distances, or an uneven
+  // cut's) and every `ranges`-th vertical tile; the first entry is searched for with 64 probes at a time (the list ascends
   // in cc and ends in sentinels): three loads in a row for 16K entries, 14 by bisection.
   int cc_end = cc_last, ei0 = 0;
-  const int vstep = SPLIT && !whole ? n_sp : 1;
+  const int ranges = OWN ? n_sp : a.n_split, vstep = SPLIT && !whole ? ranges : 1;
   int vlin = sp - vstep;
   if (SPLIT && !whole) {
-    const int per = (cc_last + n_sp) / n_sp;  // ceil((cc_last + 1) / n_sp)
+    const int per = (cc_last + ranges) / ranges;  // ceil((cc_last + 1) / ranges)
     int cc_lo = sp * per;
     cc_end = cc_lo + per - 1 < cc_last ? cc_lo + per - 1 : cc_last;
-    if (!BATCH && own >= 0) {
+    if (OWN && own >= 0) {
       cc_lo = __builtin_amdgcn_readfirstlane(a.own_pieces[own].cc_lo);
       cc_end = __builtin_amdgcn_readfirstlane(a.own_pieces[own].cc_hi);
     }
@@ -1303,6 +1307,10 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a0) {
   }
   }  // rounds
 }
+template <int D, int NQB, bool DCA, bool SPLIT, bool BATCH = false>
+__global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a) { attention_body<D, NQB, DCA, SPLIT, BATCH, false>(a); }
+template <int D, int NQB, bool DCA>
+__global__ __launch_bounds__(128 * NQB, 2) void k_attention_own(const AttnArgs a) { attention_body<D, NQB, DCA, true, false, true>(a); }
 
 // ---------------------------------------------------------------------------------------------
 // Block list of one head from its selected slash offsets.
@@ -1796,7 +1804,7 @@ size_t attn_sync_bytes(const vs_params& p) { return attn_counter_bytes(p) + attn
 template <int D>
 constexpr int combine_parts() { return kTileRows / (1024 / D); }   // per unit
 constexpr int kCombineGrid = 2048;   // workgroups for a batch at most
-template <int D, bool BATCH = false>
+template <int D, bool BATCH = false, bool OWN = false>
 __global__ __launch_bounds__(256) void k_attn_combine(const AttnArgs a0) {
   constexpr int LR = D / 4;            // lanes per row
   constexpr int WPU = combine_parts<D>();
@@ -1818,7 +1826,7 @@ __global__ __launch_bounds__(256) void k_attn_combine(const AttnArgs a0) {
   int g, h, qt;
   unit_of(a, a.n_whole + e, g, h, qt);
   int n_sp = a.n_split, slot0 = BATCH ? e + a.first_slot : e, slot_step = n_fold;
-  if (!BATCH && a.own_slots > 0) {
+  if constexpr (OWN) {
     if (__builtin_amdgcn_readfirstlane(*a.own_n) > 0) {
       const int2 own = a.own_units[e];
       n_sp = __builtin_amdgcn_readfirstlane(own.x);
@@ -2062,7 +2070,7 @@ static hipError_t attn_device_setup(int* n_cu_out) {
     e = hipDeviceGetAttribute(&cu, hipDeviceAttributeMultiprocessorCount, dev);
     if (e != hipSuccess) return e;
     if (cu < 1) return hipErrorInvalidDevice;
-    const void* fns[10] = {reinterpret_cast<const void*>(&k_attention<128, NQB, false, false>),
+    const void* fns[14] = {reinterpret_cast<const void*>(&k_attention<128, NQB, false, false>),
                           reinterpret_cast<const void*>(&k_attention<64, NQB, false, false>),
                           reinterpret_cast<const void*>(&k_attention<128, NQB, true, false>),
                           reinterpret_cast<const void*>(&k_attention<64, NQB, true, false>),
@@ -2071,8 +2079,12 @@ static hipError_t attn_device_setup(int* n_cu_out) {
                           reinterpret_cast<const void*>(&k_attention<128, NQB, true, true>),
                           reinterpret_cast<const void*>(&k_attention<64, NQB, true, true>),
                           reinterpret_cast<const void*>(&k_attention<128, NQB, false, true, true>),
-                          reinterpret_cast<const void*>(&k_attention<64, NQB, false, true, true>)};
-    for (int i = 0; i < 10; ++i) {
+                          reinterpret_cast<const void*>(&k_attention<64, NQB, false, true, true>),
+                          reinterpret_cast<const void*>(&k_attention_own<128, NQB, false>),
+                          reinterpret_cast<const void*>(&k_attention_own<64, NQB, false>),
+                          reinterpret_cast<const void*>(&k_attention_own<128, NQB, true>),
+                          reinterpret_cast<const void*>(&k_attention_own<64, NQB, true>)};
+    for (int i = 0; i < 14; ++i) {
       e = hipFuncSetAttribute(fns[i], hipFuncAttributeMaxDynamicSharedMemorySize,
                               i % 2 == 0 ? attn_lds_bytes<128>() : attn_lds_bytes<64>());
       if (e != hipSuccess) return e;
@@ -2237,15 +2249,28 @@ hipError_t launch_attention(const vs_params& p, const void* q, const DcaArgs* dc
     a.members = pieces < 8 * (int64_t)members && !a.own_slots ? (int)ceil_div(pieces, 8) : members;
     a.n_wg = 8 * a.members;
     a.n_full = a.n_rem = a.n_gr = 0;
-    if (a.own_slots) hipLaunchKernelGGL(k_attn_pieces, dim3(1), dim3(1024), 0, st, a);
-    if (p.head_dim == 128) { if (dca) VS_ATTN_LAUNCH(128, true, true); else VS_ATTN_LAUNCH(128, false, true); }
-    else { if (dca) VS_ATTN_LAUNCH(64, true, true); else VS_ATTN_LAUNCH(64, false, true); }
+    if (a.own_slots) {
+      hipLaunchKernelGGL(k_attn_pieces, dim3(1), dim3(1024), 0, st, a);
+      const dim3 grid((unsigned)a.n_wg), block(128 * NQB);
+      if (p.head_dim == 128) {
+        if (dca) hipLaunchKernelGGL((k_attention_own<128, NQB, true>), grid, block, attn_lds_bytes<128>(), st, a);
+        else hipLaunchKernelGGL((k_attention_own<128, NQB, false>), grid, block, attn_lds_bytes<128>(), st, a);
+      } else {
+        if (dca) hipLaunchKernelGGL((k_attention_own<64, NQB, true>), grid, block, attn_lds_bytes<64>(), st, a);
+        else hipLaunchKernelGGL((k_attention_own<64, NQB, false>), grid, block, attn_lds_bytes<64>(), st, a);
+      }
+    } else if (p.head_dim == 128) {
+      if (dca) VS_ATTN_LAUNCH(128, true, true); else VS_ATTN_LAUNCH(128, false, true);
+    } else {
+      if (dca) VS_ATTN_LAUNCH(64, true, true); else VS_ATTN_LAUNCH(64, false, true);
+    }
   }
 #undef VS_ATTN_LAUNCH
   if (a.n_split > 1 || a.own_slots) {
     const dim3 cgrid((unsigned)((int64_t)(a.n_units - a.n_whole) * (p.head_dim == 128 ? combine_parts<128>() : combine_parts<64>())));
-    if (p.head_dim == 128) hipLaunchKernelGGL(k_attn_combine<128>, cgrid, dim3(256), 0, st, a);
-    else hipLaunchKernelGGL(k_attn_combine<64>, cgrid, dim3(256), 0, st, a);
+    const auto fold = [&](auto&& kernel) { hipLaunchKernelGGL(kernel, cgrid, dim3(256), 0, st, a); };
+    if (a.own_slots) { if (p.head_dim == 128) fold(k_attn_combine<128, false, true>); else fold(k_attn_combine<64, false, true>); }
+    else { if (p.head_dim == 128) fold(k_attn_combine<128>); else fold(k_attn_combine<64>); }
   }
   return hipGetLastError();
 }
