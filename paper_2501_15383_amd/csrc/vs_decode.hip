@@ -20,6 +20,8 @@
 // its 128-row tiles (copies of a step shared by four waves of which one multiplied, a barrier per step, one range count for a
 // whole batch): one token at 5,003 keys 39 -> 15 us, at 1M keys 510 -> 363 (5.9 TB/s of K and V); 24 tokens at 2K to 64K keys
 // 395 -> 215 (5.8 TB/s); 8 tokens with index sets at 262,144 keys 1,042 -> 770 (lists 252 -> 17 of it).
+#include <type_traits>
+
 #include "vs_common.h"
 
 namespace vs {
@@ -35,7 +37,6 @@ struct DecodeArgs {
   const vs_request* req;
   int32_t n_req;
   int32_t n_q_heads, n_kv_heads, group;
-  int32_t side, n_seg;    // neighbouring KV heads that the waves of a workgroup take side by side (dec_layout), n_kv_heads / side
   int64_t q_stride_head, k_stride_tok, k_stride_head, v_stride_tok, v_stride_head, o_stride_head;
   float scale_log2;
   int32_t v_budget, s_budget;
@@ -45,12 +46,12 @@ struct DecodeArgs {
   uint2* ent;             // [n_req][Hkv][ent_stride] (diagonal, heads that have it)
   int4* len;              // [n_req][Hkv] (entries, entries + tiles of 64 gathered columns, heads that have every diagonal)
   int32_t words, ent_stride;
-  // shares: plan[0] = units in all (a unit: 64 keys of `side` KV heads), plan[1] = shares, plan[2 + r] = units before request r; of one request without index sets the
+  // shares: plan[0] = units in all (a unit: 64 keys of the KV heads that go side by side), plan[1] = shares, plan[2 + r] = units before request r; of one request without index sets the
   // host knows them (one_T units, one_n shares; 0: the device finds them)
   int64_t* plan;
   int64_t one_T, one_n;
-  float* part_o;          // [share + (request, segment)][side G][D]
-  float* part_ml;         // [share + (request, segment)][side G][2] (reference, sum)
+  float* part_o;          // [share + (request, segment)][heads of a segment][D]
+  float* part_ml;         // [share + (request, segment)][heads of a segment][2] (reference, sum)
 };
 
 __device__ __forceinline__ vs_request decode_request(const DecodeArgs& a, int r) {
@@ -100,7 +101,10 @@ __device__ __forceinline__ void dec_dma_lane(uint32_t lds_addr, const void* ptr)
                :: "s"(__builtin_amdgcn_readfirstlane(lds_addr)), "v"(ptr) : "memory");
 }
 
-template <int D, int SIDE>
+// ONE: a single request without index sets (no table, no lists; the host has counted its units).  In a kernel of its own, because a short
+// token waits for its instructions: 5,003 keys 11.40 us where the kernel of all requests had 3,756 instructions, 11.55 with
+// 3,770 of them, 9.9 with the 1,893 of this one.
+template <int D, int SIDE, bool ONE>
 __device__ __forceinline__ void decode_body(const DecodeArgs& a) {
   constexpr int DCH = D / 8;         // 16-byte pieces per row
   constexpr int KS = D / 32;         // MFMA steps of K Q^T
@@ -125,14 +129,15 @@ __device__ __forceinline__ void decode_body(const DecodeArgs& a) {
   auto blocks_of = [&](int r) -> int64_t {
     const vs_request rq = a.req ? a.req[r] : a.one;
     if (!decode_takes(a, rq)) return 0;
-    if (!rq.s_idx) return (int64_t)decode_blocks(rq) * a.n_seg;
+    if (!rq.s_idx) return (int64_t)decode_blocks(rq) * (a.n_kv_heads / SIDE);
     int64_t n = 0;
-    for (int x = 0; x < a.n_seg; ++x) n += decode_seg_len<SIDE>(a, r, x);
+    for (int x = 0; x < a.n_kv_heads / SIDE; ++x) n += decode_seg_len<SIDE>(a, r, x);
     return n;
   };
-  int64_t T = a.one_T, first = 0;
-  if (a.n_req == 1) {
-    if (T == 0) T = blocks_of(0);
+  int64_t T = ONE ? a.one_T : 0, first = 0;
+  if (ONE) {
+  } else if (a.n_req == 1) {
+    T = blocks_of(0);
   } else {
     for (int r = tid; r < a.n_req; r += kDecThreads) T += blocks_of(r);
 #pragma unroll
@@ -145,8 +150,8 @@ __device__ __forceinline__ void decode_body(const DecodeArgs& a) {
   constexpr int min_units = kDecMinBlocks / SIDE;
   int64_t n_share = (T + min_units - 1) / min_units;
   if (n_share > (int64_t)gridDim.x) n_share = gridDim.x;
-  if (blockIdx.x == 0 && tid == 0 && a.one_T == 0) { a.plan[0] = T; a.plan[1] = n_share; }
-  if (a.one_T) {
+  if (!ONE && blockIdx.x == 0 && tid == 0) { a.plan[0] = T; a.plan[1] = n_share; }
+  if (ONE) {
     if (blockIdx.x >= n_share) return;
   } else if (a.n_req == 1) {
     if (blockIdx.x == 0 && tid == 0) a.plan[2] = 0;
@@ -157,7 +162,7 @@ __device__ __forceinline__ void decode_body(const DecodeArgs& a) {
   const int64_t u_begin = n_share ? share_start(blockIdx.x, n_share, T) : 0, u_end = n_share ? share_start(blockIdx.x + 1, n_share, T) : 0;
   int r = 0;
   first = u_begin;
-  if (a.n_req > 1) {
+  if (!ONE && a.n_req > 1) {
     int64_t before = 0;
     for (int rb = 0; rb < a.n_req; rb += kDecThreads) {
       const int64_t mine = rb + tid < a.n_req ? blocks_of(rb + tid) : 0;
@@ -199,26 +204,28 @@ __device__ __forceinline__ void decode_body(const DecodeArgs& a) {
   vs_request rq;
   int64_t blk = first;
   while (left > 0) {
-    if (fresh) {
+    if (ONE) {
+      rq = a.one;
+    } else if (fresh) {
       rq = decode_request(a, r);
       sg = 0;
       if (!decode_takes(a, rq)) { ++r; continue; }
       fresh = false;
     }
-    const bool sparse = rq.s_idx != nullptr;
+    const bool with_sets = !ONE && rq.s_idx != nullptr;
     const int64_t n_k = rq.q_start + 1;
     const int g = sg * SIDE + sub;   // this wave's KV head
     int n_ent = decode_blocks(rq), own_len = n_ent, seg_len = n_ent, full = 0;
-    if (sparse) {
+    if (with_sets) {
       const int4 l2 = a.len[(int64_t)r * a.n_kv_heads + g];
       n_ent = __builtin_amdgcn_readfirstlane(l2.x);
-      own_len = __builtin_amdgcn_readfirstlane(l2.y);
+      seg_len = own_len = __builtin_amdgcn_readfirstlane(l2.y);
       full = l2.z;
-      seg_len = __builtin_amdgcn_readfirstlane(decode_seg_len<SIDE>(a, r, sg));
+      if constexpr (SIDE > 1) seg_len = __builtin_amdgcn_readfirstlane(decode_seg_len<SIDE>(a, r, sg));
     }
     if (blk >= seg_len) {   // the share starts in a later segment of this request
       blk -= seg_len;
-      if (++sg == a.n_seg) { ++r; fresh = true; }
+      if (++sg == a.n_kv_heads / SIDE && !ONE) { ++r; fresh = true; }
       continue;
     }
     const int64_t take64 = seg_len - blk < left ? seg_len - blk : left;
@@ -231,6 +238,9 @@ __device__ __forceinline__ void decode_body(const DecodeArgs& a) {
     }
     const int h0 = g * a.group;
 
+    // The piece, with and without index sets: a request without them does not wait for the instructions of the others.
+    const auto walk = [&](auto sets) __attribute__((always_inline)) {
+    constexpr bool sparse = decltype(sets)::value;
     // ---- Q^T operand: lane (head h0 + col, k-group g4); columns beyond the group repeat its first head and are not stored (zeros in
     // their place had to wait for the loads before the first copies went out: 0.7 us) --------------------
     bf16x8 qreg[KS];
@@ -449,7 +459,7 @@ __device__ __forceinline__ void decode_body(const DecodeArgs& a) {
       *(f32x4*)&fold[(wv * 16 + col) * (D + 4) + 16 * db + 4 * g4] = o4;
     }
     __syncthreads();
-    const int64_t slot = ((int64_t)blockIdx.x + (int64_t)r * a.n_seg + sg) * SIDE * a.group;
+    const int64_t slot = ((int64_t)blockIdx.x + (int64_t)r * (a.n_kv_heads / SIDE) + sg) * SIDE * a.group;
     for (int x = tid; x < SIDE * a.group * (D / 4); x += kDecThreads) {
       // query head qs of the segment: row q of the waves w0, w0 + side, ...
       const int qs = x / (D / 4), w0 = SIDE > 1 ? qs / a.group : 0, q = qs - w0 * a.group, d = 4 * (x % (D / 4));
@@ -484,17 +494,22 @@ __device__ __forceinline__ void decode_body(const DecodeArgs& a) {
         }
       }
     }
+    };
+    if (with_sets) walk(std::true_type{});
+    else walk(std::false_type{});
     __syncthreads();   // the LDS is reused by the next piece
     left -= take64;
     blk = 0;
-    if (++sg == a.n_seg) { ++r; fresh = true; }
+    if (++sg == a.n_kv_heads / SIDE && !ONE) { ++r; fresh = true; }
   }
 }
 
 template <int D>
-__global__ __launch_bounds__(kDecThreads, 2) void k_decode(const DecodeArgs a) { decode_body<D, 1>(a); }
+__global__ __launch_bounds__(kDecThreads, 2) void k_decode(const DecodeArgs a) { decode_body<D, 1, false>(a); }
 // two neighbouring KV heads side by side
-__global__ __launch_bounds__(kDecThreads, 2) void k_decode_pairs(const DecodeArgs a) { decode_body<128, 2>(a); }
+__global__ __launch_bounds__(kDecThreads, 2) void k_decode_pairs(const DecodeArgs a) { decode_body<128, 2, false>(a); }
+template <int D, int SIDE>
+__global__ __launch_bounds__(kDecThreads, 2) void k_decode_one(const DecodeArgs a) { decode_body<D, SIDE, true>(a); }
 
 // out = sum_s O_s 2^(m_s - M) / sum_s l_s 2^(m_s - M) over the shares that a (request, segment of KV heads) lies in; one workgroup per
 // (query head, request), shares folded in a fixed order (run-to-run identical): wave w takes every NW-th share, then
@@ -519,7 +534,7 @@ __global__ __launch_bounds__(64 * NW) void k_decode_combine(const DecodeArgs a) 
   }
   const int s0 = (int)share_of(from, n, T), s1 = (int)share_of(from + seg_len - 1, n, T);
   if (s0 == s1) return;   // finished by its one share
-  const int64_t row0 = ((int64_t)s0 + (int64_t)r * a.n_seg + sg) * rows + q;   // row of share s: row0 + (s - s0) rows
+  const int64_t row0 = ((int64_t)s0 + (int64_t)r * (a.n_kv_heads / SIDE) + sg) * rows + q;   // row of share s: row0 + (s - s0) rows
   const int cnt = s1 - s0 + 1;
   constexpr int E = D / 64, U = 8;
   float acc[E], L = 0.f, o[U][E], w[U], l[U];
@@ -696,7 +711,7 @@ hipError_t launch_decode(const vs_params& p, const vs_request* one, const vs_req
   if (one) a.one = *one;
   a.req = req; a.n_req = n_req;
   a.n_q_heads = p.n_q_heads; a.n_kv_heads = p.n_kv_heads; a.group = p.n_q_heads / p.n_kv_heads;
-  a.side = l.side; a.n_seg = p.n_kv_heads / l.side;
+  const int n_seg = p.n_kv_heads / l.side;
   a.q_stride_head = p.q_stride_head; a.o_stride_head = p.o_stride_head;
   a.k_stride_tok = p.k_stride_tok; a.k_stride_head = p.k_stride_head;
   a.v_stride_tok = p.v_stride_tok; a.v_stride_head = p.v_stride_head;
@@ -713,11 +728,12 @@ hipError_t launch_decode(const vs_params& p, const vs_request* one, const vs_req
   a.words = l.words; a.ent_stride = l.ent_stride;
   static DeviceOnce once;   // the opt-in to more than 64 KiB of LDS
   const hipError_t e = once.run([]() {
-    const void* const fns[3] = {reinterpret_cast<const void*>(&k_decode<128>), reinterpret_cast<const void*>(&k_decode_pairs),
-                                reinterpret_cast<const void*>(&k_decode<64>)};
-    for (int i = 0; i < 3; ++i) {
+    const void* const fns[6] = {reinterpret_cast<const void*>(&k_decode<128>), reinterpret_cast<const void*>(&k_decode_pairs),
+                                reinterpret_cast<const void*>(&k_decode_one<128, 1>), reinterpret_cast<const void*>(&k_decode_one<128, 2>),
+                                reinterpret_cast<const void*>(&k_decode<64>), reinterpret_cast<const void*>(&k_decode_one<64, 1>)};
+    for (int i = 0; i < 6; ++i) {
       const hipError_t e1 = hipFuncSetAttribute(fns[i], hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                i < 2 ? decode_lds_bytes<128>() : decode_lds_bytes<64>());
+                                                i < 4 ? decode_lds_bytes<128>() : decode_lds_bytes<64>());
       if (e1 != hipSuccess) return e1;
     }
     return hipSuccess;
@@ -726,24 +742,25 @@ hipError_t launch_decode(const vs_params& p, const vs_request* one, const vs_req
   if (lists)
     hipLaunchKernelGGL(k_decode_lists, dim3((unsigned)p.n_kv_heads, (unsigned)n_req), dim3(kDecListThreads), 0, st, a);
   if (one && !lists) {   // as k_decode counts them
-    a.one_T = ceil_div(one->q_start + one->q_len, (int64_t)kBlock) * a.n_seg;
-    a.one_n = ceil_div(a.one_T, kDecMinBlocks / a.side);
+    a.one_T = ceil_div(one->q_start + one->q_len, (int64_t)kBlock) * n_seg;
+    a.one_n = ceil_div(a.one_T, kDecMinBlocks / l.side);
     if (a.one_n > l.shares) a.one_n = l.shares;
   }
   const dim3 grid((unsigned)l.shares), cgrid((unsigned)p.n_q_heads, (unsigned)n_req);
-  const bool many = l.shares > 32 * (int64_t)n_req * a.n_seg;
+  const bool many = l.shares > 32 * (int64_t)n_req * n_seg;
   const auto fold = [&](auto&& four, auto&& eight) {
     if (many) hipLaunchKernelGGL(eight, cgrid, dim3(512), 0, st, a);
     else hipLaunchKernelGGL(four, cgrid, dim3(256), 0, st, a);
   };
+  const auto walk = [&](auto&& kernel, int lds) { hipLaunchKernelGGL(kernel, grid, dim3(kDecThreads), lds, st, a); };
   if (l.side == 2) {
-    hipLaunchKernelGGL(k_decode_pairs, grid, dim3(kDecThreads), decode_lds_bytes<128>(), st, a);
+    if (a.one_T) walk(k_decode_one<128, 2>, decode_lds_bytes<128>()); else walk(k_decode_pairs, decode_lds_bytes<128>());
     fold(k_decode_combine<128, 4, 2>, k_decode_combine<128, 8, 2>);
   } else if (p.head_dim == 128) {
-    hipLaunchKernelGGL(k_decode<128>, grid, dim3(kDecThreads), decode_lds_bytes<128>(), st, a);
+    if (a.one_T) walk(k_decode_one<128, 1>, decode_lds_bytes<128>()); else walk(k_decode<128>, decode_lds_bytes<128>());
     fold(k_decode_combine<128, 4, 1>, k_decode_combine<128, 8, 1>);
   } else {
-    hipLaunchKernelGGL(k_decode<64>, grid, dim3(kDecThreads), decode_lds_bytes<64>(), st, a);
+    if (a.one_T) walk(k_decode_one<64, 1>, decode_lds_bytes<64>()); else walk(k_decode<64>, decode_lds_bytes<64>());
     fold(k_decode_combine<64, 4, 1>, k_decode_combine<64, 8, 1>);
   }
   return hipGetLastError();

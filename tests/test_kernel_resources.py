@@ -76,7 +76,8 @@ def test_the_dca_kernels_spill_no_more_than_a_handful_of_registers(resources):
     ("vs_select", {**{f"k_sel_rowILi{kpt}E": (128, 0) for kpt in (0, 4, 8, 12, 16, 24, 32, 40, 48)},
                    "k_sel_sample": (128, 0), "k_sel_filter": (128, 0), "k_slice_digit": (64, 0), "k_slice_count": (64, 0),
                    "k_slice_write": (64, 0)}),
-    ("vs_decode", {"k_decodeILi128E": (256, 0), "k_decodeILi64E": (256, 0), "k_decode_lists": (64, 0)}),
+    ("vs_decode", {"k_decodeILi128E": (256, 0), "k_decodeILi64E": (256, 0), "k_decode_lists": (64, 0), "k_decode_pairs": (256, 0),
+                   "k_decode_oneILi128ELi1E": (256, 0), "k_decode_oneILi128ELi2E": (256, 0), "k_decode_oneILi64ELi1E": (256, 0)}),
 ])
 def test_the_other_kernels_keep_their_register_budgets(tmp_path_factory, source, budgets):
     res = _compile(tmp_path_factory, source)
