@@ -671,7 +671,8 @@ constexpr int kDecShares = 256;   // at most: one workgroup fills the LDS of a c
 // heads side by side, rows of 256 bytes each: 512 bytes in one place are read faster than 256 (a bare copy loop of this shape 6.2 TB/s against
 // 5.5, with four heads no more).  28 / 4 heads of 128: one token at 1M keys 383 us -> 363, 300,000 keys 118.2 -> 115.0, 200,000 80.7 -> 79.2,
 // 100,000 45.0 -> 45.9 (so the line), 12,000 12.9 -> 15.2 (twice the partial results per head); 24 tokens at 2K to 64K keys 225 -> 214.
-// Heads of 64 (8 / 2, 300,000 keys): 36.5 -> 37.8, so not these.  With index sets the two walks drift apart and the time is the same.
+// Only where the rows of neighbouring heads lie next to each other: in caches of [KV heads][keys][128] 140,000 keys 48.1 -> 50.9, 1M 377 ->
+// 387, 24 tokens 208 -> 212.  Heads of 64 (8 / 2, 300,000 keys): 36.5 -> 37.8, so not these.  With index sets the two walks drift apart and the time is the same.
 constexpr int64_t kDecSideBlocks = 8192;
 struct DecLayout {
   size_t part_ml, plan, len, ent, bm, total;
@@ -680,7 +681,8 @@ struct DecLayout {
 DecLayout dec_layout(const vs_params& p, int n_req, bool lists) {
   DecLayout l;
   const int64_t n_blk = ceil_div(p.q_start + p.q_len, (int64_t)kBlock);
-  l.side = p.head_dim == 128 && p.n_kv_heads % 2 == 0 && (int64_t)n_req * p.n_kv_heads * n_blk >= kDecSideBlocks ? 2 : 1;
+  const bool side_by_side = p.k_stride_head == p.head_dim && p.v_stride_head == p.head_dim;
+  l.side = p.head_dim == 128 && p.n_kv_heads % 2 == 0 && side_by_side && (int64_t)n_req * p.n_kv_heads * n_blk >= kDecSideBlocks ? 2 : 1;
   const size_t G = (size_t)(p.n_q_heads / p.n_kv_heads), segs = (size_t)n_req * (p.n_kv_heads / l.side);
   const int64_t most = ceil_div((int64_t)segs * (n_blk + (lists ? (int64_t)G * ceil_div(p.vertical_budget, 64) : 0)), kDecMinBlocks / l.side);
   l.shares = (int32_t)(most < kDecShares ? most : kDecShares);

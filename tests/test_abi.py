@@ -214,6 +214,20 @@ def test_options_and_the_workspaces_they_change():
     assert L.vs_select(C.byref(p), ok, ok, ok, ok, ok, ok, None, 0, None) == vs.VS_ERR_WORKSPACE
 
 
+def test_neighbouring_kv_heads_go_side_by_side_only_where_their_rows_touch():
+    """The workspace of a table of long tokens holds the partial results of two KV heads per share where the caches are
+    [keys][KV heads][128], of one where they are [KV heads][keys][128]."""
+    L, n = vs.lib(), 300000
+    p = vs.Chunk(28, 4, 128, 1, n - 1, 0.1).params()
+    touching = L.vs_batch_workspace_bytes(C.byref(p), 1)
+    for t in "kv":
+        q = vs.Chunk(28, 4, 128, 1, n - 1, 0.1).params()
+        setattr(q, t + "_stride_tok", 128)
+        setattr(q, t + "_stride_head", 128 * n)
+        # 256 shares and two pairs, or 256 shares and four heads
+        assert touching - L.vs_batch_workspace_bytes(C.byref(q), 1) == (258 * 14 - 260 * 7) * (128 + 2) * 4, t
+
+
 def test_static_select_checks_its_capacity_on_the_host():
     """vs_select_static holds 128 query heads; more is refused before any device work."""
     L = vs.lib()

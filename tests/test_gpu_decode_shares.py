@@ -80,9 +80,14 @@ def test_long_token_of_neighbouring_heads(hq, hkv, s):
     """8,192 blocks and more: two KV heads side by side where their number is even."""
     rng = np.random.default_rng(2200 + hkv)
     pb, q, k, v, _ = _problem(rng, hq, hkv, 128, s, 1, 1, "dense")
-    got = vs.dense_causal_prefill(chunk_of(pb), dev(q), dev(k), dev(v), want_lse=True)
-    torch.cuda.synchronize()
-    assert_attn_close(*got, *oracle.dense_attention(pb, q, k, v), f"{hq}/{hkv} s={s}")
+    kd, vd = dev(k), dev(v)
+    ref = oracle.dense_attention(pb, q, k, v)
+    for major in (False, True):   # caches of [keys][KV heads][128], and of [KV heads][keys][128], whose heads go by themselves
+        if major:
+            kd, vd = (x.permute(1, 0, 2).contiguous().permute(1, 0, 2) for x in (kd, vd))
+        got = vs.dense_causal_prefill(chunk_of(pb), dev(q), kd, vd, want_lse=True)
+        torch.cuda.synchronize()
+        assert_attn_close(*got, *ref, f"{hq}/{hkv} s={s} major={major}")
 
 
 def test_neighbouring_heads_of_many_requests():
