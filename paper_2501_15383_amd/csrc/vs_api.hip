@@ -47,7 +47,7 @@ size_t sparse_ws_bytes(const vs_params& p, bool dense) {
   const size_t own = blocklist_bytes(p, dense) + attn_sync_bytes(p) + attn_split_bytes(p, dense);
   // (a single token without DCA is the decode kernel's, with DCA the tile kernel's: room for either)
   if (p.q_len == 1 && decode_fits(p)) {
-    const size_t dec = decode_bytes(p, 1, !dense);
+    const size_t dec = decode_bytes(p, 1, false, !dense);
     return own > dec ? own : dec;
   }
   return own;
@@ -423,7 +423,7 @@ bool batch_decodes(const vs_params& p, int n_req) {
   return caches >= 256 || (double)caches * (double)(p.q_start + p.q_len) * p.head_dim * 4.0 >= 64.0 * (1 << 20);
 }
 // workspace of a batch: the decode kernel's part, then the tile kernel's
-size_t decode_part(const vs_params& p, int n_req) { return batch_decodes(p, n_req) ? decode_bytes(p, n_req, true) : 0; }
+size_t decode_part(const vs_params& p, int n_req) { return batch_decodes(p, n_req) ? decode_bytes(p, n_req, true, true) : 0; }
 size_t batch_bytes(const vs_params& p, int n_req) {
   return decode_part(p, n_req) + (batch_decodes(p, n_req) && p.q_len == 1 ? 0 : attn_batch_bytes(p, n_req));
 }

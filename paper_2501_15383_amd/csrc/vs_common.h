@@ -158,7 +158,7 @@ hipError_t launch_attention_batch(const vs_params& p, const vs_request* req, int
                                   hipStream_t st);
 // single tokens, one request (`one`, by value; lists: it has index sets) or those of a table (req, device; lists = true)
 bool decode_fits(const vs_params& p);
-size_t decode_bytes(const vs_params& p, int n_req, bool lists);
+size_t decode_bytes(const vs_params& p, int n_req, bool table, bool lists);
 hipError_t launch_decode(const vs_params& p, const vs_request* one, const vs_request* req, int n_req, bool lists, void* ws,
                          hipStream_t st);
 size_t attn_sync_bytes(const vs_params& p);

@@ -32,6 +32,19 @@ constexpr int kDecMinBlocks = 2;     // 64-key blocks per share at least, of all
 constexpr int kDecListThreads = 1024;
 constexpr int kDecListBytes = 128 << 10;   // a byte per diagonal and head in LDS at a time: 1M keys of up to 8 heads
 
+// From this many 64-key blocks on (of all requests and KV heads) the waves of a workgroup take two neighbouring KV heads side by side, rows of
+// 256 bytes each: 512 bytes in one place are read faster than 256 (a bare copy loop of this shape 6.2 TB/s against 5.5, with four
+// heads no more), but a head has twice the partial results.  28 / 4 heads of 128, by themselves and side by side: one token at 12,000 keys
+// 9.7 us and 12.0, 100,000 35.9 and 37.9, 140,000 (8,752 blocks) 50.1 and 50.6, 200,000 79.7 and 77.8, 1M 381 and 361; 40 / 8 heads, 60,000
+// keys (7,504) 41.3 and 41.0, 70,000 (8,752) 49.8 and 48.3; tables of 30 tokens of up to 3,000 keys 25.3 and 25.5, 8 of 20,000 (10,016) 64.2
+// and 62.9, 24 at 2K to 64K keys 223 and 212.
+// Only where the rows of neighbouring heads lie next to each other: in caches of [KV heads][keys][128] 140,000 keys 48.1 -> 50.9, 1M 377 ->
+// 387, 24 tokens 208 -> 212.  Heads of 64 (8 / 2, 300,000 keys): 36.5 -> 37.8, so not these.  With index sets the two walks drift
+// apart: one token at 600,000 keys 209 -> 221, 64 of 16 heads per group at 60,000 938 -> 980.  So: a single token without index sets by
+// its length; a table whose bounds are as large by its requests' own lengths, on the device, where none has index sets (a request of
+// 12,000 keys under a bound of 262,144 13.4 -> 15.2 by the bounds alone).
+constexpr int64_t kDecSideBlocks = 8192;
+
 struct DecodeArgs {
   vs_request one;         // the request of a call without a table (req null)
   const vs_request* req;
@@ -72,13 +85,41 @@ __device__ __forceinline__ bool decode_takes(const DecodeArgs& a, const vs_reque
   return rq.s_idx == nullptr || (rq.v_idx && rq.v_cnt && rq.s_cnt);
 }
 __device__ __forceinline__ int decode_blocks(const vs_request& rq) { return (int)((rq.q_start + kBlock) / kBlock); }
-// units of segment x (side neighbouring KV heads) of request r: as many as its longest head has
-template <int SIDE>
-__device__ __forceinline__ int decode_seg_len(const DecodeArgs& a, int r, int x) {
-  const int4* const len = a.len + (int64_t)r * a.n_kv_heads + x * SIDE;
-  int n = len[0].y;
-  for (int e = 1; e < SIDE; ++e) n = len[e].y > n ? len[e].y : n;
+// units of request r with every KV head by itself
+__device__ __forceinline__ int64_t decode_units(const DecodeArgs& a, int r, const vs_request& rq) {
+  if (!decode_takes(a, rq)) return 0;
+  if (!rq.s_idx) return (int64_t)decode_blocks(rq) * a.n_kv_heads;
+  int64_t n = 0;
+  for (int g = 0; g < a.n_kv_heads; ++g) n += a.len[(int64_t)r * a.n_kv_heads + g].y;
   return n;
+}
+// Those of all requests, and of request tid (mine).  DENSE: -1 - their number where a request has index sets.  Called by a whole workgroup.
+template <bool DENSE>
+__device__ __forceinline__ int64_t decode_total(const DecodeArgs& a, int64_t& mine) {
+  __shared__ int64_t sum_s[kDecWaves];
+  constexpr int kSets = 52;   // from this bit on: requests with index sets (4,096 requests of far fewer than 2^40 units each)
+  const int tid = threadIdx.x;
+  auto of = [&](int r) -> int64_t {
+    const vs_request rq = a.req ? a.req[r] : a.one;
+    const int64_t n = decode_units(a, r, rq);
+    return DENSE && n && rq.s_idx ? n + (1ll << kSets) : n;
+  };
+  int64_t T = mine = 0;
+  if (a.n_req == 1) {
+    T = of(0);
+  } else {
+    if (tid < a.n_req) T = mine = of(tid);
+    for (int r = tid + kDecThreads; r < a.n_req; r += kDecThreads) T += of(r);
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) T += __shfl_xor((long long)T, d);
+    if ((tid & 63) == 0) sum_s[tid >> 6] = T;
+    __syncthreads();
+    T = 0;
+    for (int w = 0; w < kDecWaves; ++w) T += sum_s[w];
+  }
+  if (!DENSE || T >> kSets == 0) return T;
+  mine &= (1ll << kSets) - 1;
+  return -1 - (T & ((1ll << kSets) - 1));
 }
 // share w of n covers units [w T / n, (w + 1) T / n)
 // (quotients of 64 bits, most of which fit 32: a fifth of the instructions)
@@ -104,8 +145,9 @@ __device__ __forceinline__ void dec_dma_lane(uint32_t lds_addr, const void* ptr)
 // ONE: a single request without index sets (no table, no lists; the host has counted its units).  In a kernel of its own, because a short
 // token waits for its instructions: 5,003 keys 11.40 us where the kernel of all requests had 3,756 instructions, 11.55 with
 // 3,770 of them, 9.9 with the 1,893 of this one.
+// T: units of all requests, mine: of request tid with every KV head by itself.  SIDE > 1: nobody has index sets.
 template <int D, int SIDE, bool ONE>
-__device__ __forceinline__ void decode_body(const DecodeArgs& a) {
+__device__ __forceinline__ void decode_body(const DecodeArgs& a, int64_t T, int64_t mine0) {
   constexpr int DCH = D / 8;         // 16-byte pieces per row
   constexpr int KS = D / 32;         // MFMA steps of K Q^T
   constexpr int DB = D / 16;         // 16-row blocks of O^T
@@ -126,31 +168,15 @@ __device__ __forceinline__ void decode_body(const DecodeArgs& a) {
   const uint32_t buf_addr = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)(const __attribute__((address_space(3))) char*)buf);
 
   // ---- this workgroup's share ------------------------------------------------------------------
-  auto blocks_of = [&](int r) -> int64_t {
+  auto units_of = [&](int r) -> int64_t {
     const vs_request rq = a.req ? a.req[r] : a.one;
-    if (!decode_takes(a, rq)) return 0;
-    if (!rq.s_idx) return (int64_t)decode_blocks(rq) * (a.n_kv_heads / SIDE);
-    int64_t n = 0;
-    for (int x = 0; x < a.n_kv_heads / SIDE; ++x) n += decode_seg_len<SIDE>(a, r, x);
-    return n;
+    return decode_units(a, r, rq) / SIDE;
   };
-  int64_t T = ONE ? a.one_T : 0, first = 0;
-  if (ONE) {
-  } else if (a.n_req == 1) {
-    T = blocks_of(0);
-  } else {
-    for (int r = tid; r < a.n_req; r += kDecThreads) T += blocks_of(r);
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) T += __shfl_xor((long long)T, d);
-    if (lane == 0) scan_s[wv] = T;
-    __syncthreads();
-    T = 0;
-    for (int w = 0; w < kDecWaves; ++w) T += scan_s[w];
-  }
+  int64_t first = 0;
   constexpr int min_units = kDecMinBlocks / SIDE;
   int64_t n_share = (T + min_units - 1) / min_units;
   if (n_share > (int64_t)gridDim.x) n_share = gridDim.x;
-  if (!ONE && blockIdx.x == 0 && tid == 0) { a.plan[0] = T; a.plan[1] = n_share; }
+  if (!ONE && blockIdx.x == 0 && tid == 0) { a.plan[0] = T; a.plan[1] = n_share | (int64_t)SIDE << 32; }
   if (ONE) {
     if (blockIdx.x >= n_share) return;
   } else if (a.n_req == 1) {
@@ -165,7 +191,7 @@ __device__ __forceinline__ void decode_body(const DecodeArgs& a) {
   if (!ONE && a.n_req > 1) {
     int64_t before = 0;
     for (int rb = 0; rb < a.n_req; rb += kDecThreads) {
-      const int64_t mine = rb + tid < a.n_req ? blocks_of(rb + tid) : 0;
+      const int64_t mine = rb == 0 ? mine0 / SIDE : (rb + tid < a.n_req ? units_of(rb + tid) : 0);
       int64_t inc = mine;
 #pragma unroll
       for (int d = 1; d < 64; d <<= 1) {
@@ -212,16 +238,15 @@ __device__ __forceinline__ void decode_body(const DecodeArgs& a) {
       if (!decode_takes(a, rq)) { ++r; continue; }
       fresh = false;
     }
-    const bool with_sets = !ONE && rq.s_idx != nullptr;
+    const bool with_sets = !ONE && SIDE == 1 && rq.s_idx != nullptr;
     const int64_t n_k = rq.q_start + 1;
     const int g = sg * SIDE + sub;   // this wave's KV head
-    int n_ent = decode_blocks(rq), own_len = n_ent, seg_len = n_ent, full = 0;
+    int n_ent = decode_blocks(rq), seg_len = n_ent, full = 0;
     if (with_sets) {
       const int4 l2 = a.len[(int64_t)r * a.n_kv_heads + g];
       n_ent = __builtin_amdgcn_readfirstlane(l2.x);
-      seg_len = own_len = __builtin_amdgcn_readfirstlane(l2.y);
+      seg_len = __builtin_amdgcn_readfirstlane(l2.y);
       full = l2.z;
-      if constexpr (SIDE > 1) seg_len = __builtin_amdgcn_readfirstlane(decode_seg_len<SIDE>(a, r, sg));
     }
     if (blk >= seg_len) {   // the share starts in a later segment of this request
       blk -= seg_len;
@@ -230,12 +255,7 @@ __device__ __forceinline__ void decode_body(const DecodeArgs& a) {
     }
     const int64_t take64 = seg_len - blk < left ? seg_len - blk : left;
     const bool whole = blk == 0 && take64 == seg_len;
-    // the same part of the head's own walk (lists of neighbouring heads differ in length)
-    int b0 = (int)blk, b1 = (int)(blk + take64);
-    if (SIDE > 1 && own_len != seg_len) {
-      b0 = (int)short_div((int64_t)b0 * own_len, seg_len);
-      b1 = (int)short_div((int64_t)b1 * own_len, seg_len);
-    }
+    const int b0 = (int)blk, b1 = (int)(blk + take64);
     const int h0 = g * a.group;
 
     // The piece, with and without index sets: a request without them does not wait for the instructions of the others.
@@ -505,11 +525,20 @@ __device__ __forceinline__ void decode_body(const DecodeArgs& a) {
 }
 
 template <int D>
-__global__ __launch_bounds__(kDecThreads, 2) void k_decode(const DecodeArgs a) { decode_body<D, 1, false>(a); }
-// two neighbouring KV heads side by side
-__global__ __launch_bounds__(kDecThreads, 2) void k_decode_pairs(const DecodeArgs a) { decode_body<128, 2, false>(a); }
+__global__ __launch_bounds__(kDecThreads, 2) void k_decode(const DecodeArgs a) {
+  int64_t mine;
+  const int64_t T = decode_total<false>(a, mine);
+  decode_body<D, 1, false>(a, T, mine);
+}
+// A table whose bounds allow two neighbouring KV heads side by side: whether that pays, its requests say (see kDecSideBlocks).
+__global__ __launch_bounds__(kDecThreads, 2) void k_decode_pairs(const DecodeArgs a) {
+  int64_t mine;
+  const int64_t T = decode_total<true>(a, mine);
+  if (T >= kDecSideBlocks) decode_body<128, 2, false>(a, T / 2, mine);
+  else decode_body<128, 1, false>(a, T < 0 ? -1 - T : T, mine);
+}
 template <int D, int SIDE>
-__global__ __launch_bounds__(kDecThreads, 2) void k_decode_one(const DecodeArgs a) { decode_body<D, SIDE, true>(a); }
+__global__ __launch_bounds__(kDecThreads, 2) void k_decode_one(const DecodeArgs a) { decode_body<D, SIDE, true>(a, a.one_T, 0); }
 
 // out = sum_s O_s 2^(m_s - M) / sum_s l_s 2^(m_s - M) over the shares that a (request, segment of KV heads) lies in; one workgroup per
 // (query head, request), shares folded in a fixed order (run-to-run identical): wave w takes every NW-th share, then
@@ -517,24 +546,28 @@ __global__ __launch_bounds__(kDecThreads, 2) void k_decode_one(const DecodeArgs 
 // are compared (four waves, and the references first: one token at 5,003 keys 14.1 us with its two launches, 12.1 so and with the
 // shares counted on the host).  Eight waves where a KV head lies in more than 32 shares, else four: 60 tokens of 40 heads, a share or
 // two each, 71 us with four, 75 with eight.
+// SIDE: KV heads side by side; 0: as the walk's plan says.
 template <int D, int NW, int SIDE>
 __global__ __launch_bounds__(64 * NW) void k_decode_combine(const DecodeArgs a) {
   const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int h = blockIdx.x, r = blockIdx.y, rows = SIDE * a.group, sg = h / rows, q = h - sg * rows;
+  const int h = blockIdx.x, r = blockIdx.y;
   const vs_request rq = decode_request(a, r);
   if (!decode_takes(a, rq)) return;
-  const int64_t T = a.one_T ? a.one_T : a.plan[0], n = a.one_T ? a.one_n : a.plan[1];
+  const int64_t T = a.one_T ? a.one_T : a.plan[0], planned = a.one_T ? 0 : a.plan[1], n = a.one_T ? a.one_n : planned & 0xFFFFFFFF;
+  const int side = SIDE ? SIDE : __builtin_amdgcn_readfirstlane((int)(planned >> 32));
+  const int rows = side * a.group, sg = h / rows, q = h - sg * rows;
   int64_t from = a.one_T ? 0 : a.plan[2 + r];
   int seg_len = decode_blocks(rq);
   if (rq.s_idx) {
-    for (int x = 0; x < sg; ++x) from += decode_seg_len<SIDE>(a, r, x);
-    seg_len = decode_seg_len<SIDE>(a, r, sg);
+    const int4* const len = a.len + (int64_t)r * a.n_kv_heads;   // (one KV head by itself)
+    for (int x = 0; x < sg; ++x) from += len[x].y;
+    seg_len = len[sg].y;
   } else {
     from += (int64_t)sg * seg_len;
   }
   const int s0 = (int)share_of(from, n, T), s1 = (int)share_of(from + seg_len - 1, n, T);
   if (s0 == s1) return;   // finished by its one share
-  const int64_t row0 = ((int64_t)s0 + (int64_t)r * (a.n_kv_heads / SIDE) + sg) * rows + q;   // row of share s: row0 + (s - s0) rows
+  const int64_t row0 = ((int64_t)s0 + (int64_t)r * (a.n_kv_heads / side) + sg) * rows + q;   // row of share s: row0 + (s - s0) rows
   const int cnt = s1 - s0 + 1;
   constexpr int E = D / 64, U = 8;
   float acc[E], L = 0.f, o[U][E], w[U], l[U];
@@ -667,22 +700,17 @@ bool decode_fits(const vs_params& p) { return p.n_q_heads / p.n_kv_heads <= 16; 
 
 namespace {
 constexpr int kDecShares = 256;   // at most: one workgroup fills the LDS of a compute unit
-// From this many 64-key blocks on (of all requests and KV heads, as the host knows them) the waves of a workgroup take two neighbouring KV
-// heads side by side, rows of 256 bytes each: 512 bytes in one place are read faster than 256 (a bare copy loop of this shape 6.2 TB/s against
-// 5.5, with four heads no more).  28 / 4 heads of 128: one token at 1M keys 383 us -> 363, 300,000 keys 118.2 -> 115.0, 200,000 80.7 -> 79.2,
-// 100,000 45.0 -> 45.9 (so the line), 12,000 12.9 -> 15.2 (twice the partial results per head); 24 tokens at 2K to 64K keys 225 -> 214.
-// Only where the rows of neighbouring heads lie next to each other: in caches of [KV heads][keys][128] 140,000 keys 48.1 -> 50.9, 1M 377 ->
-// 387, 24 tokens 208 -> 212.  Heads of 64 (8 / 2, 300,000 keys): 36.5 -> 37.8, so not these.  With index sets the two walks drift apart and the time is the same.
-constexpr int64_t kDecSideBlocks = 8192;
 struct DecLayout {
   size_t part_ml, plan, len, ent, bm, total;
-  int32_t words, ent_stride, shares, side;
+  int32_t words, ent_stride, shares;
+  int32_t side;   // KV heads side by side, of a table at most
 };
-DecLayout dec_layout(const vs_params& p, int n_req, bool lists) {
+// table: requests from a table, with or without index sets; lists: with
+DecLayout dec_layout(const vs_params& p, int n_req, bool table, bool lists) {
   DecLayout l;
   const int64_t n_blk = ceil_div(p.q_start + p.q_len, (int64_t)kBlock);
   const bool side_by_side = p.k_stride_head == p.head_dim && p.v_stride_head == p.head_dim;
-  l.side = p.head_dim == 128 && p.n_kv_heads % 2 == 0 && side_by_side && (int64_t)n_req * p.n_kv_heads * n_blk >= kDecSideBlocks ? 2 : 1;
+  l.side = (table || !lists) && p.head_dim == 128 && p.n_kv_heads % 2 == 0 && side_by_side && (int64_t)n_req * p.n_kv_heads * n_blk >= kDecSideBlocks ? 2 : 1;
   const size_t G = (size_t)(p.n_q_heads / p.n_kv_heads), segs = (size_t)n_req * (p.n_kv_heads / l.side);
   const int64_t most = ceil_div((int64_t)segs * (n_blk + (lists ? (int64_t)G * ceil_div(p.vertical_budget, 64) : 0)), kDecMinBlocks / l.side);
   l.shares = (int32_t)(most < kDecShares ? most : kDecShares);
@@ -704,11 +732,11 @@ DecLayout dec_layout(const vs_params& p, int n_req, bool lists) {
 }
 }  // namespace
 
-size_t decode_bytes(const vs_params& p, int n_req, bool lists) { return dec_layout(p, n_req, lists).total; }
+size_t decode_bytes(const vs_params& p, int n_req, bool table, bool lists) { return dec_layout(p, n_req, table, lists).total; }
 
 hipError_t launch_decode(const vs_params& p, const vs_request* one, const vs_request* req, int n_req, bool lists, void* ws,
                          hipStream_t st) {
-  const DecLayout l = dec_layout(p, n_req, lists);
+  const DecLayout l = dec_layout(p, n_req, req != nullptr, lists);
   DecodeArgs a = {};
   if (one) a.one = *one;
   a.req = req; a.n_req = n_req;
@@ -757,7 +785,8 @@ hipError_t launch_decode(const vs_params& p, const vs_request* one, const vs_req
   const auto walk = [&](auto&& kernel, int lds) { hipLaunchKernelGGL(kernel, grid, dim3(kDecThreads), lds, st, a); };
   if (l.side == 2) {
     if (a.one_T) walk(k_decode_one<128, 2>, decode_lds_bytes<128>()); else walk(k_decode_pairs, decode_lds_bytes<128>());
-    fold(k_decode_combine<128, 4, 2>, k_decode_combine<128, 8, 2>);
+    if (a.one_T) fold(k_decode_combine<128, 4, 2>, k_decode_combine<128, 8, 2>);
+    else fold(k_decode_combine<128, 4, 0>, k_decode_combine<128, 8, 0>);
   } else if (p.head_dim == 128) {
     if (a.one_T) walk(k_decode_one<128, 1>, decode_lds_bytes<128>()); else walk(k_decode<128>, decode_lds_bytes<128>());
     fold(k_decode_combine<128, 4, 1>, k_decode_combine<128, 8, 1>);

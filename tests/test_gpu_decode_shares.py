@@ -112,3 +112,26 @@ def test_neighbouring_heads_of_many_requests():
     for i, ((pb, q, k, v, sets), g) in enumerate(zip(reqs, gpu)):
         ref = oracle.dense_attention(pb, q, k, v) if sets is None else oracle.sparse_attention(pb, q, k, v, *sets)
         assert_attn_close(g["out"], g["lse"], *ref, f"request {i}, s={pb.q_start}")
+
+
+@pytest.mark.parametrize("lens,mode", [([12000], "dense"), ([3000, 12000, 70, 5000, 64, 1, 900, 2500], "dense"), ([12000, 3000], "both"),
+                                       ([70000, 61000], "both")])
+def test_bounds_beyond_the_requests(lens, mode):
+    """What a table's tokens are is decided by their lengths and index sets, not by the table's bounds: the same bits (where
+    the fold has as many waves: it goes by the bounds)."""
+    hq, hkv, d, bv, bs = 14, 2, 128, 100, 300
+    rng = np.random.default_rng(2400)
+    gpu = []
+    for i, n in enumerate(lens):
+        pb, q, k, v, sets = _problem(rng, hq, hkv, d, n - 1, bv, bs, "both" if mode == "both" and i == 0 else "dense")
+        gpu.append(dict(q=dev(q), k=dev(k), v=dev(v), q_start=n - 1, out=torch.zeros((1, hq, d), dtype=torch.bfloat16, device="cuda"),
+                        lse=torch.zeros((hq, 1), device="cuda"), sets=None if sets is None else tuple(_t(x) for x in sets)))
+    got = []
+    table = vs.request_table(gpu, "cuda")
+    for bound in (max(lens), 1 << 20):
+        ck = vs.Chunk(hq, hkv, d, 1, bound - 1, 1.0 / np.sqrt(d), vertical_budget=bv, slash_budget=bs)
+        vs.attn_batch(ck, table, len(lens), gpu[0]["q"], gpu[0]["k"], gpu[0]["v"], gpu[0]["out"])
+        torch.cuda.synchronize()
+        got.append([(g["out"].clone(), g["lse"].clone()) for g in gpu])
+    for a, b in zip(*got):
+        assert torch.equal(a[0].view(torch.int16), b[0].view(torch.int16)) and torch.equal(a[1], b[1])
