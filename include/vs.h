@@ -77,7 +77,13 @@ typedef struct vs_params {
 
 /* Bytes of workspace the call named by `which` needs for these parameters
  * (0 on invalid parameters).  Host function; touches no device.  The workspace
- * must be 256-byte aligned.  VS_WS_CHUNK covers vs_prefill_chunk. */
+ * must be 256-byte aligned.  VS_WS_CHUNK covers vs_prefill_chunk.
+ * Most of what short sparse calls ask for is room for partial results of ranges
+ * that follow the heads' own lists: 28 heads of 128, 2,000 rows at 150,000 keys
+ * VS_WS_SPARSE 137 MB (0.3 without), VS_WS_CHUNK 171 (41).  A sparse, chunk or
+ * batch call that is given less, but all that it needs without such ranges (and,
+ * single tokens, without KV heads side by side), takes it and is slower; with less
+ * than that it returns VS_ERR_WORKSPACE. */
 size_t vs_workspace_bytes(const vs_params *p, int which);
 
 /* Host: static, NUL-terminated description of a status code. */

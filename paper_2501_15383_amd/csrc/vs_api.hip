@@ -43,11 +43,12 @@ int check_ws(const void* ws, size_t have, size_t need) {
   return VS_OK;
 }
 
-size_t sparse_ws_bytes(const vs_params& p, bool dense) {
-  const size_t own = blocklist_bytes(p, dense) + attn_sync_bytes(p) + attn_split_bytes(p, dense);
+// (least: the smallest workspace that a call takes, with which it is slower)
+size_t sparse_ws_bytes(const vs_params& p, bool dense, bool least = false) {
+  const size_t own = blocklist_bytes(p, dense) + attn_sync_bytes(p) + attn_split_bytes(p, dense, least);
   // (a single token without DCA is the decode kernel's, with DCA the tile kernel's: room for either)
   if (p.q_len == 1 && decode_fits(p)) {
-    const size_t dec = decode_bytes(p, 1, false, !dense);
+    const size_t dec = decode_bytes(p, 1, false, !dense, least);
     return own > dec ? own : dec;
   }
   return own;
@@ -57,7 +58,7 @@ size_t sparse_ws_bytes(const vs_params& p, bool dense) {
 struct ChunkWs {
   size_t vscore, sscore, v_idx, s_idx, v_cnt, s_cnt, sub, total;
 };
-ChunkWs chunk_layout(const vs_params& p) {
+ChunkWs chunk_layout(const vs_params& p, bool least = false) {
   const size_t n_k = (size_t)(p.q_start + p.q_len), hq = (size_t)p.n_q_heads;
   ChunkWs w;
   size_t off = 0;
@@ -69,7 +70,7 @@ ChunkWs chunk_layout(const vs_params& p) {
   w.v_cnt = take(hq * sizeof(int32_t));
   w.s_cnt = take(hq * sizeof(int32_t));
   w.sub = off;
-  const size_t a = estimate_ws_bytes(p), b = select_ws_bytes(p), c = sparse_ws_bytes(p, false);
+  const size_t a = estimate_ws_bytes(p), b = select_ws_bytes(p), c = sparse_ws_bytes(p, false, least);
   off += a > b ? (a > c ? a : c) : (b > c ? b : c);
   w.total = off;
   return w;
@@ -299,19 +300,22 @@ int sparse_attn(const vs_params* p, const void* q, const vs_dca* dca, const void
   if (dca && (rc = check_dca(dca, &da)) != VS_OK) return rc;
   if (!q || !k || !v || !out || !v_idx || !v_cnt || !s_idx || !s_cnt) return VS_ERR_INVALID_ARG;
   if (!aligned(q, 16) || !aligned(k, 16) || !aligned(v, 16) || !aligned(out, 16)) return VS_ERR_INVALID_ARG;
-  rc = check_ws(ws, ws_bytes, sparse_ws_bytes(*p, false));
+  size_t need = sparse_ws_bytes(*p, false);
+  const bool least = ws_bytes < need;
+  if (least) need = sparse_ws_bytes(*p, false, true);
+  rc = check_ws(ws, ws_bytes, need);
   if (rc != VS_OK) return rc;
   hipStream_t st = (hipStream_t)stream;
   if (!dca && p->q_len == 1 && decode_fits(*p)) {
     const vs_request one = {q, k, v, out, lse, v_idx, v_cnt, s_idx, s_cnt, p->q_start, p->q_len};
-    return hip_status(launch_decode(*p, &one, nullptr, 1, true, ws, st));
+    return hip_status(launch_decode(*p, &one, nullptr, 1, true, least, ws, st));
   }
   const BlockList bl = blocklist_layout(*p, false, ws);
   char* sync = (char*)ws + blocklist_bytes(*p, false);
   hipError_t e = launch_build_blocklist(*p, s_idx, s_cnt, v_cnt, false, bl, sync, st);
   if (e != hipSuccess) return VS_ERR_HIP;
   return hip_status(launch_attention(*p, q, dca ? &da : nullptr, k, v, v_idx, v_cnt, false, bl, out, lse, sync,
-                                     sync + attn_sync_bytes(*p), st));
+                                     sync + attn_sync_bytes(*p), least, st));
 }
 
 int dense_attn(const vs_params* p, const void* q, const vs_dca* dca, const void* k, const void* v,
@@ -322,19 +326,22 @@ int dense_attn(const vs_params* p, const void* q, const vs_dca* dca, const void*
   if (dca && (rc = check_dca(dca, &da)) != VS_OK) return rc;
   if (!q || !k || !v || !out) return VS_ERR_INVALID_ARG;
   if (!aligned(q, 16) || !aligned(k, 16) || !aligned(v, 16) || !aligned(out, 16)) return VS_ERR_INVALID_ARG;
-  rc = check_ws(ws, ws_bytes, sparse_ws_bytes(*p, true));
+  size_t need = sparse_ws_bytes(*p, true);
+  const bool least = ws_bytes < need;
+  if (least) need = sparse_ws_bytes(*p, true, true);
+  rc = check_ws(ws, ws_bytes, need);
   if (rc != VS_OK) return rc;
   hipStream_t st = (hipStream_t)stream;
   if (!dca && p->q_len == 1 && decode_fits(*p)) {
     const vs_request one = {q, k, v, out, lse, nullptr, nullptr, nullptr, nullptr, p->q_start, p->q_len};
-    return hip_status(launch_decode(*p, &one, nullptr, 1, false, ws, st));
+    return hip_status(launch_decode(*p, &one, nullptr, 1, false, least, ws, st));
   }
   const BlockList bl = blocklist_layout(*p, true, ws);
   char* sync = (char*)ws + blocklist_bytes(*p, true);
   hipError_t e = launch_build_blocklist(*p, nullptr, nullptr, nullptr, true, bl, sync, st);
   if (e != hipSuccess) return VS_ERR_HIP;
   return hip_status(launch_attention(*p, q, dca ? &da : nullptr, k, v, nullptr, nullptr, true, bl, out, lse, sync,
-                                     sync + attn_sync_bytes(*p), st));
+                                     sync + attn_sync_bytes(*p), least, st));
 }
 }  // namespace
 
@@ -377,7 +384,8 @@ int prefill_chunk_any(const vs_params* p, const void* q, const vs_dca* dca, cons
   DcaArgs scratch_da;
   if (dca && (rc = check_dca(dca, &scratch_da)) != VS_OK) return rc;
   if (sel && (rc = check_dca(sel, &scratch_da)) != VS_OK) return rc;
-  const ChunkWs w = chunk_layout(*p);
+  ChunkWs w = chunk_layout(*p);
+  if (ws_bytes < w.total) w = chunk_layout(*p, true);
   rc = check_ws(ws, ws_bytes, w.total);
   if (rc != VS_OK) return rc;
   char* b = (char*)ws;
@@ -423,9 +431,9 @@ bool batch_decodes(const vs_params& p, int n_req) {
   return caches >= 256 || (double)caches * (double)(p.q_start + p.q_len) * p.head_dim * 4.0 >= 64.0 * (1 << 20);
 }
 // workspace of a batch: the decode kernel's part, then the tile kernel's
-size_t decode_part(const vs_params& p, int n_req) { return batch_decodes(p, n_req) ? decode_bytes(p, n_req, true, true) : 0; }
-size_t batch_bytes(const vs_params& p, int n_req) {
-  return decode_part(p, n_req) + (batch_decodes(p, n_req) && p.q_len == 1 ? 0 : attn_batch_bytes(p, n_req));
+size_t decode_part(const vs_params& p, int n_req, bool least) { return batch_decodes(p, n_req) ? decode_bytes(p, n_req, true, true, least) : 0; }
+size_t batch_bytes(const vs_params& p, int n_req, bool least = false) {
+  return decode_part(p, n_req, least) + (batch_decodes(p, n_req) && p.q_len == 1 ? 0 : attn_batch_bytes(p, n_req));
 }
 int check_batch(const vs_params* p, int32_t n_requests) {
   int rc = check_params(p, true);
@@ -446,16 +454,19 @@ int vs_attn_batch(const vs_params* p, const vs_request* requests, int32_t n_requ
   int rc = check_batch(p, n_requests);
   if (rc != VS_OK) return rc;
   if (!requests || !aligned(requests, 8)) return VS_ERR_INVALID_ARG;
-  rc = check_ws(ws, ws_bytes, batch_bytes(*p, n_requests));
+  size_t need = batch_bytes(*p, n_requests);
+  const bool least = ws_bytes < need;
+  if (least) need = batch_bytes(*p, n_requests, true);
+  rc = check_ws(ws, ws_bytes, need);
   if (rc != VS_OK) return rc;
   // single tokens by the decode kernel, the longer requests by the tile kernel (which skips the former), or all by the latter
   hipStream_t st = (hipStream_t)stream;
   const bool decode = batch_decodes(*p, n_requests);
   if (decode) {
-    const hipError_t e = launch_decode(*p, nullptr, requests, n_requests, true, ws, st);
+    const hipError_t e = launch_decode(*p, nullptr, requests, n_requests, true, least, ws, st);
     if (e != hipSuccess || p->q_len == 1) return hip_status(e);
   }
-  return hip_status(launch_attention_batch(*p, requests, n_requests, decode, (char*)ws + decode_part(*p, n_requests), st));
+  return hip_status(launch_attention_batch(*p, requests, n_requests, decode, (char*)ws + decode_part(*p, n_requests, least), st));
 }
 
 int vs_count_tiles(const vs_params* p, const int32_t* v_idx, const int32_t* v_cnt,

@@ -1711,7 +1711,7 @@ struct AttnCut {
     return even > own_slots ? even : own_slots;
   }
 };
-static AttnCut attn_cut(const vs_params& p, bool dense, int forced) {
+static AttnCut attn_cut_as(const vs_params& p, bool dense, int forced) {
   const bool one = attn_packed_decode(p, dense);
   const int group = p.n_q_heads / p.n_kv_heads, row_pad = (int)(p.q_start % kBlock);
   const int64_t n_blk = ceil_div(p.q_start + p.q_len, kBlock);
@@ -1782,10 +1782,19 @@ static AttnCut attn_cut(const vs_params& p, bool dense, int forced) {
   }
   return c;
 }
-static AttnCut attn_cut(const vs_params& p, bool dense) { return attn_cut(p, dense, g_key_split.load(std::memory_order_relaxed)); }
+// least: without uneven ranges, whose partial results are most of a short sparse call's workspace (28 heads of 128, 2,000 rows at 150,000
+// keys: 137 MB of it, 0.3 without)
+static AttnCut attn_cut(const vs_params& p, bool dense, bool least = false) {
+  AttnCut c = attn_cut_as(p, dense, g_key_split.load(std::memory_order_relaxed));
+  if (least && c.own_slots) {
+    c.own_slots = 0;
+    if (c.n_split == 1) c.n_whole = c.n_units;
+  }
+  return c;
+}
 // Partial results of the cut units: a tile's rows for every range.
-size_t attn_split_bytes(const vs_params& p, bool dense) {
-  const AttnCut c = attn_cut(p, dense);
+size_t attn_split_bytes(const vs_params& p, bool dense, bool least) {
+  const AttnCut c = attn_cut(p, dense, least);
   if (!c.queue || c.slots() == 0) return 0;
   const size_t rows = (size_t)c.slots() * kTileRows, own = c.own_slots ? 256 + kMaxPieces * (sizeof(int2) + sizeof(OwnPiece)) : 0;
   return align_up(rows * p.head_dim * sizeof(float), 256) + align_up(rows * 2 * sizeof(float), 256) + own;
@@ -2143,7 +2152,7 @@ hipError_t launch_build_blocklist(const vs_params& p, const int32_t* s_idx, cons
 
 hipError_t launch_attention(const vs_params& p, const void* q, const DcaArgs* dca, const void* k, const void* v,
                             const int32_t* v_idx, const int32_t* v_cnt, bool dense,
-                            const BlockList& bl, void* out, float* lse, void* sync_ws, void* split_ws,
+                            const BlockList& bl, void* out, float* lse, void* sync_ws, void* split_ws, bool least,
                             hipStream_t st) {
   constexpr int NQB = kAttnQBlocks;
   if (!sync_ws) return hipErrorInvalidValue;
@@ -2183,7 +2192,7 @@ hipError_t launch_attention(const vs_params& p, const void* q, const DcaArgs* dc
   }
   a.n_qtiles = (int)ceil_div(a.q_len, 64 * NQB);
   a.scale_log2 = p.softmax_scale * kLog2e;
-  const AttnCut cut = attn_cut(p, dense);
+  const AttnCut cut = attn_cut(p, dense, least);
   a.pack = cut.pack; a.n_hs = cut.n_hs;
   a.n_units = cut.n_units; a.n_whole = cut.n_whole;
   // two workgroups fit a compute unit; one persistent workgroup per slot, in 8 groups

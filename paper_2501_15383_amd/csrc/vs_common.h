@@ -148,7 +148,7 @@ struct DcaArgs {
 // attn_split_bytes(p) bytes (may be null when that is 0); dca may be null
 hipError_t launch_attention(const vs_params& p, const void* q, const DcaArgs* dca, const void* k, const void* v,
                             const int32_t* v_idx, const int32_t* v_cnt, bool dense,
-                            const BlockList& bl, void* out, float* lse, void* sync_ws, void* split_ws,
+                            const BlockList& bl, void* out, float* lse, void* sync_ws, void* split_ws, bool least,
                             hipStream_t st);
 // several requests in one launch (short chunks, decode steps): p.q_len = the longest request,
 // p.q_start + p.q_len = the most keys any request sees; req is a device array
@@ -158,14 +158,15 @@ hipError_t launch_attention_batch(const vs_params& p, const vs_request* req, int
                                   hipStream_t st);
 // single tokens, one request (`one`, by value; lists: it has index sets) or those of a table (req, device; lists = true)
 bool decode_fits(const vs_params& p);
-size_t decode_bytes(const vs_params& p, int n_req, bool table, bool lists);
-hipError_t launch_decode(const vs_params& p, const vs_request* one, const vs_request* req, int n_req, bool lists, void* ws,
+// (least: the smallest workspace, with which it is slower)
+size_t decode_bytes(const vs_params& p, int n_req, bool table, bool lists, bool least);
+hipError_t launch_decode(const vs_params& p, const vs_request* one, const vs_request* req, int n_req, bool lists, bool least, void* ws,
                          hipStream_t st);
 size_t attn_sync_bytes(const vs_params& p);
 // key split of short chunks: bytes of partial results
 void set_attn_key_split(int n);
 void set_attn_schedule_in_turn(int on);
-size_t attn_split_bytes(const vs_params& p, bool dense);
+size_t attn_split_bytes(const vs_params& p, bool dense, bool least);
 void set_attn_segment_blocks(int blocks);
 hipError_t launch_count_tiles(const vs_params& p, const int32_t* v_idx, const int32_t* v_cnt,
                               const BlockList& bl, int64_t* tiles, hipStream_t st);

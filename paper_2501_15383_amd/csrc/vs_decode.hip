@@ -57,7 +57,8 @@ struct DecodeArgs {
   // index sets: block-diagonal bitmap per (request, head), union list and its lengths per (request, KV head)
   uint32_t* bm;           // [n_req][Hq][words]
   uint2* ent;             // [n_req][Hkv][ent_stride] (diagonal, heads that have it)
-  int4* len;              // [n_req][Hkv] (entries, entries + tiles of 64 gathered columns, heads that have every diagonal)
+  void* len;              // [n_req][Hkv] (entries, entries + tiles of 64 gathered columns, heads that have every diagonal): int4, or int2 in a
+                          // workspace without room for the third, in which the columns of every head are gathered (template parameter Len)
   int32_t words, ent_stride;
   // shares: plan[0] = units in all (a unit: 64 keys of the KV heads that go side by side), plan[1] = shares, plan[2 + r] = units before request r; of one request without index sets the
   // host knows them (one_T units, one_n shares; 0: the device finds them)
@@ -86,22 +87,23 @@ __device__ __forceinline__ bool decode_takes(const DecodeArgs& a, const vs_reque
 }
 __device__ __forceinline__ int decode_blocks(const vs_request& rq) { return (int)((rq.q_start + kBlock) / kBlock); }
 // units of request r with every KV head by itself
+template <typename Len>
 __device__ __forceinline__ int64_t decode_units(const DecodeArgs& a, int r, const vs_request& rq) {
   if (!decode_takes(a, rq)) return 0;
   if (!rq.s_idx) return (int64_t)decode_blocks(rq) * a.n_kv_heads;
   int64_t n = 0;
-  for (int g = 0; g < a.n_kv_heads; ++g) n += a.len[(int64_t)r * a.n_kv_heads + g].y;
+  for (int g = 0; g < a.n_kv_heads; ++g) n += ((const Len*)a.len)[(int64_t)r * a.n_kv_heads + g].y;
   return n;
 }
 // Those of all requests, and of request tid (mine).  DENSE: -1 - their number where a request has index sets.  Called by a whole workgroup.
-template <bool DENSE>
+template <bool DENSE, typename Len>
 __device__ __forceinline__ int64_t decode_total(const DecodeArgs& a, int64_t& mine) {
   __shared__ int64_t sum_s[kDecWaves];
   constexpr int kSets = 52;   // from this bit on: requests with index sets (4,096 requests of far fewer than 2^40 units each)
   const int tid = threadIdx.x;
   auto of = [&](int r) -> int64_t {
     const vs_request rq = a.req ? a.req[r] : a.one;
-    const int64_t n = decode_units(a, r, rq);
+    const int64_t n = decode_units<Len>(a, r, rq);
     return DENSE && n && rq.s_idx ? n + (1ll << kSets) : n;
   };
   int64_t T = mine = 0;
@@ -146,7 +148,7 @@ __device__ __forceinline__ void dec_dma_lane(uint32_t lds_addr, const void* ptr)
 // token waits for its instructions: 5,003 keys 11.40 us where the kernel of all requests had 3,756 instructions, 11.55 with
 // 3,770 of them, 9.9 with the 1,893 of this one.
 // T: units of all requests, mine: of request tid with every KV head by itself.  SIDE > 1: nobody has index sets.
-template <int D, int SIDE, bool ONE>
+template <int D, int SIDE, bool ONE, typename Len>
 __device__ __forceinline__ void decode_body(const DecodeArgs& a, int64_t T, int64_t mine0) {
   constexpr int DCH = D / 8;         // 16-byte pieces per row
   constexpr int KS = D / 32;         // MFMA steps of K Q^T
@@ -170,7 +172,7 @@ __device__ __forceinline__ void decode_body(const DecodeArgs& a, int64_t T, int6
   // ---- this workgroup's share ------------------------------------------------------------------
   auto units_of = [&](int r) -> int64_t {
     const vs_request rq = a.req ? a.req[r] : a.one;
-    return decode_units(a, r, rq) / SIDE;
+    return decode_units<Len>(a, r, rq) / SIDE;
   };
   int64_t first = 0;
   constexpr int min_units = kDecMinBlocks / SIDE;
@@ -243,10 +245,10 @@ __device__ __forceinline__ void decode_body(const DecodeArgs& a, int64_t T, int6
     const int g = sg * SIDE + sub;   // this wave's KV head
     int n_ent = decode_blocks(rq), seg_len = n_ent, full = 0;
     if (with_sets) {
-      const int4 l2 = a.len[(int64_t)r * a.n_kv_heads + g];
+      const Len l2 = ((const Len*)a.len)[(int64_t)r * a.n_kv_heads + g];
       n_ent = __builtin_amdgcn_readfirstlane(l2.x);
       seg_len = __builtin_amdgcn_readfirstlane(l2.y);
-      full = l2.z;
+      if constexpr (sizeof(Len) > 8) full = l2.z;
     }
     if (blk >= seg_len) {   // the share starts in a later segment of this request
       blk -= seg_len;
@@ -524,21 +526,25 @@ __device__ __forceinline__ void decode_body(const DecodeArgs& a, int64_t T, int6
   }
 }
 
-template <int D>
-__global__ __launch_bounds__(kDecThreads, 2) void k_decode(const DecodeArgs a) {
+template <int D, typename Len>
+__device__ __forceinline__ void decode_apart(const DecodeArgs& a) {
   int64_t mine;
-  const int64_t T = decode_total<false>(a, mine);
-  decode_body<D, 1, false>(a, T, mine);
+  const int64_t T = decode_total<false, Len>(a, mine);
+  decode_body<D, 1, false, Len>(a, T, mine);
 }
+template <int D>
+__global__ __launch_bounds__(kDecThreads, 2) void k_decode(const DecodeArgs a) { decode_apart<D, int4>(a); }
+template <int D>
+__global__ __launch_bounds__(kDecThreads, 2) void k_decode_least(const DecodeArgs a) { decode_apart<D, int2>(a); }
 // A table whose bounds allow two neighbouring KV heads side by side: whether that pays, its requests say (see kDecSideBlocks).
 __global__ __launch_bounds__(kDecThreads, 2) void k_decode_pairs(const DecodeArgs a) {
   int64_t mine;
-  const int64_t T = decode_total<true>(a, mine);
-  if (T >= kDecSideBlocks) decode_body<128, 2, false>(a, T / 2, mine);
-  else decode_body<128, 1, false>(a, T < 0 ? -1 - T : T, mine);
+  const int64_t T = decode_total<true, int4>(a, mine);
+  if (T >= kDecSideBlocks) decode_body<128, 2, false, int4>(a, T / 2, mine);
+  else decode_body<128, 1, false, int4>(a, T < 0 ? -1 - T : T, mine);
 }
 template <int D, int SIDE>
-__global__ __launch_bounds__(kDecThreads, 2) void k_decode_one(const DecodeArgs a) { decode_body<D, SIDE, true>(a, a.one_T, 0); }
+__global__ __launch_bounds__(kDecThreads, 2) void k_decode_one(const DecodeArgs a) { decode_body<D, SIDE, true, int4>(a, a.one_T, 0); }
 
 // out = sum_s O_s 2^(m_s - M) / sum_s l_s 2^(m_s - M) over the shares that a (request, segment of KV heads) lies in; one workgroup per
 // (query head, request), shares folded in a fixed order (run-to-run identical): wave w takes every NW-th share, then
@@ -547,7 +553,7 @@ __global__ __launch_bounds__(kDecThreads, 2) void k_decode_one(const DecodeArgs 
 // shares counted on the host).  Eight waves where a KV head lies in more than 32 shares, else four: 60 tokens of 40 heads, a share or
 // two each, 71 us with four, 75 with eight.
 // SIDE: KV heads side by side; 0: as the walk's plan says.
-template <int D, int NW, int SIDE>
+template <int D, int NW, int SIDE, typename Len = int4>
 __global__ __launch_bounds__(64 * NW) void k_decode_combine(const DecodeArgs a) {
   const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int h = blockIdx.x, r = blockIdx.y;
@@ -559,7 +565,7 @@ __global__ __launch_bounds__(64 * NW) void k_decode_combine(const DecodeArgs a) 
   int64_t from = a.one_T ? 0 : a.plan[2 + r];
   int seg_len = decode_blocks(rq);
   if (rq.s_idx) {
-    const int4* const len = a.len + (int64_t)r * a.n_kv_heads;   // (one KV head by itself)
+    const Len* const len = (const Len*)a.len + (int64_t)r * a.n_kv_heads;   // (one KV head by itself)
     for (int x = 0; x < sg; ++x) from += len[x].y;
     seg_len = len[sg].y;
   } else {
@@ -620,7 +626,8 @@ __global__ __launch_bounds__(64 * NW) void k_decode_combine(const DecodeArgs a) 
 // Bitmaps of the heads of a KV group and the union of their block lists, one workgroup per (KV head, request), for single
 // tokens with index sets.  Diagonals are collected as bytes in LDS (see collect_flags), 8 or 16 heads side by side, a window at a time;
 // every wave has consecutive groups of 64 diagonals, a lane per diagonal.
-__global__ __launch_bounds__(kDecListThreads) void k_decode_lists(const DecodeArgs a) {
+template <typename Len>
+__device__ __forceinline__ void decode_lists(const DecodeArgs& a) {
   constexpr int NW = kDecListThreads / 64;
   __shared__ __attribute__((aligned(16))) uint8_t flags[kDecListBytes + 16];
   __shared__ uint32_t wsum[NW], missing_s;   // (a bit per head that lacks a diagonal)
@@ -688,11 +695,17 @@ __global__ __launch_bounds__(kDecListThreads) void k_decode_lists(const DecodeAr
   }
   if (tid == 0) {
     int tiles = 0;
-    for (int j = 0; j < G; ++j) tiles += missing_s >> j & 1u ? (rq.v_cnt[g * G + j] + 63) >> 6 : 0;
+    for (int j = 0; j < G; ++j) tiles += sizeof(Len) == 8 || missing_s >> j & 1u ? (rq.v_cnt[g * G + j] + 63) >> 6 : 0;
     const int units = (int)running + tiles;   // (at least one: a token without any key gets its 0 / -inf too)
-    a.len[(int64_t)r * a.n_kv_heads + g] = make_int4((int)running, units > 0 ? units : 1, (int)~missing_s, 0);
+    Len l = {};
+    l.x = (int)running;
+    l.y = units > 0 ? units : 1;
+    if constexpr (sizeof(Len) > 8) l.z = (int)~missing_s;
+    ((Len*)a.len)[(int64_t)r * a.n_kv_heads + g] = l;
   }
 }
+__global__ __launch_bounds__(kDecListThreads) void k_decode_lists(const DecodeArgs a) { decode_lists<int4>(a); }
+__global__ __launch_bounds__(kDecListThreads) void k_decode_least_lists(const DecodeArgs a) { decode_lists<int2>(a); }
 
 // ---------------------------------------------------------------------------------------------------
 // the query heads of a KV group are the columns of one MFMA tile
@@ -705,12 +718,12 @@ struct DecLayout {
   int32_t words, ent_stride, shares;
   int32_t side;   // KV heads side by side, of a table at most
 };
-// table: requests from a table, with or without index sets; lists: with
-DecLayout dec_layout(const vs_params& p, int n_req, bool table, bool lists) {
+// table: requests from a table, with or without index sets; lists: with.  least: every KV head by itself, the columns of every head gathered
+DecLayout dec_layout(const vs_params& p, int n_req, bool table, bool lists, bool least) {
   DecLayout l;
   const int64_t n_blk = ceil_div(p.q_start + p.q_len, (int64_t)kBlock);
   const bool side_by_side = p.k_stride_head == p.head_dim && p.v_stride_head == p.head_dim;
-  l.side = (table || !lists) && p.head_dim == 128 && p.n_kv_heads % 2 == 0 && side_by_side && (int64_t)n_req * p.n_kv_heads * n_blk >= kDecSideBlocks ? 2 : 1;
+  l.side = !least && (table || !lists) && p.head_dim == 128 && p.n_kv_heads % 2 == 0 && side_by_side && (int64_t)n_req * p.n_kv_heads * n_blk >= kDecSideBlocks ? 2 : 1;
   const size_t G = (size_t)(p.n_q_heads / p.n_kv_heads), segs = (size_t)n_req * (p.n_kv_heads / l.side);
   const int64_t most = ceil_div((int64_t)segs * (n_blk + (lists ? (int64_t)G * ceil_div(p.vertical_budget, 64) : 0)), kDecMinBlocks / l.side);
   l.shares = (int32_t)(most < kDecShares ? most : kDecShares);
@@ -723,7 +736,7 @@ DecLayout dec_layout(const vs_params& p, int n_req, bool table, bool lists) {
   l.len = l.ent = l.bm = off;
   if (lists) {
     const size_t heads = (size_t)n_req * p.n_kv_heads;
-    off += align_up(heads * sizeof(int4), 256);
+    off += align_up(heads * (least ? sizeof(int2) : sizeof(int4)), 256);
     l.ent = off; off += align_up(heads * (size_t)l.ent_stride * sizeof(uint2), 256);
     l.bm = off; off += align_up((size_t)n_req * p.n_q_heads * (size_t)l.words * sizeof(uint32_t), 256);
   }
@@ -732,11 +745,11 @@ DecLayout dec_layout(const vs_params& p, int n_req, bool table, bool lists) {
 }
 }  // namespace
 
-size_t decode_bytes(const vs_params& p, int n_req, bool table, bool lists) { return dec_layout(p, n_req, table, lists).total; }
+size_t decode_bytes(const vs_params& p, int n_req, bool table, bool lists, bool least) { return dec_layout(p, n_req, table, lists, least).total; }
 
-hipError_t launch_decode(const vs_params& p, const vs_request* one, const vs_request* req, int n_req, bool lists, void* ws,
+hipError_t launch_decode(const vs_params& p, const vs_request* one, const vs_request* req, int n_req, bool lists, bool least, void* ws,
                          hipStream_t st) {
-  const DecLayout l = dec_layout(p, n_req, req != nullptr, lists);
+  const DecLayout l = dec_layout(p, n_req, req != nullptr, lists, least);
   DecodeArgs a = {};
   if (one) a.one = *one;
   a.req = req; a.n_req = n_req;
@@ -752,25 +765,29 @@ hipError_t launch_decode(const vs_params& p, const vs_request* one, const vs_req
   a.part_o = (float*)w;
   a.part_ml = (float*)(w + l.part_ml);
   a.plan = (int64_t*)(w + l.plan);
-  a.len = (int4*)(w + l.len);
+  a.len = w + l.len;
   a.ent = (uint2*)(w + l.ent);
   a.bm = (uint32_t*)(w + l.bm);
   a.words = l.words; a.ent_stride = l.ent_stride;
   static DeviceOnce once;   // the opt-in to more than 64 KiB of LDS
   const hipError_t e = once.run([]() {
-    const void* const fns[6] = {reinterpret_cast<const void*>(&k_decode<128>), reinterpret_cast<const void*>(&k_decode_pairs),
+    const void* const fns[8] = {reinterpret_cast<const void*>(&k_decode<128>), reinterpret_cast<const void*>(&k_decode_pairs),
                                 reinterpret_cast<const void*>(&k_decode_one<128, 1>), reinterpret_cast<const void*>(&k_decode_one<128, 2>),
-                                reinterpret_cast<const void*>(&k_decode<64>), reinterpret_cast<const void*>(&k_decode_one<64, 1>)};
-    for (int i = 0; i < 6; ++i) {
+                                reinterpret_cast<const void*>(&k_decode_least<128>), reinterpret_cast<const void*>(&k_decode<64>),
+                                reinterpret_cast<const void*>(&k_decode_one<64, 1>), reinterpret_cast<const void*>(&k_decode_least<64>)};
+    for (int i = 0; i < 8; ++i) {
       const hipError_t e1 = hipFuncSetAttribute(fns[i], hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                i < 4 ? decode_lds_bytes<128>() : decode_lds_bytes<64>());
+                                                i < 5 ? decode_lds_bytes<128>() : decode_lds_bytes<64>());
       if (e1 != hipSuccess) return e1;
     }
     return hipSuccess;
   });
   if (e != hipSuccess) return e;
-  if (lists)
-    hipLaunchKernelGGL(k_decode_lists, dim3((unsigned)p.n_kv_heads, (unsigned)n_req), dim3(kDecListThreads), 0, st, a);
+  if (lists) {
+    const dim3 lgrid((unsigned)p.n_kv_heads, (unsigned)n_req);
+    if (least) hipLaunchKernelGGL(k_decode_least_lists, lgrid, dim3(kDecListThreads), 0, st, a);
+    else hipLaunchKernelGGL(k_decode_lists, lgrid, dim3(kDecListThreads), 0, st, a);
+  }
   if (one && !lists) {   // as k_decode counts them
     a.one_T = ceil_div(one->q_start + one->q_len, (int64_t)kBlock) * n_seg;
     a.one_n = ceil_div(a.one_T, kDecMinBlocks / l.side);
@@ -783,15 +800,28 @@ hipError_t launch_decode(const vs_params& p, const vs_request* one, const vs_req
     else hipLaunchKernelGGL(four, cgrid, dim3(256), 0, st, a);
   };
   const auto walk = [&](auto&& kernel, int lds) { hipLaunchKernelGGL(kernel, grid, dim3(kDecThreads), lds, st, a); };
+  constexpr int lds128 = decode_lds_bytes<128>(), lds64 = decode_lds_bytes<64>();
   if (l.side == 2) {
-    if (a.one_T) walk(k_decode_one<128, 2>, decode_lds_bytes<128>()); else walk(k_decode_pairs, decode_lds_bytes<128>());
-    if (a.one_T) fold(k_decode_combine<128, 4, 2>, k_decode_combine<128, 8, 2>);
-    else fold(k_decode_combine<128, 4, 0>, k_decode_combine<128, 8, 0>);
+    if (a.one_T) {
+      walk(k_decode_one<128, 2>, lds128);
+      fold(k_decode_combine<128, 4, 2>, k_decode_combine<128, 8, 2>);
+    } else {
+      walk(k_decode_pairs, lds128);
+      fold(k_decode_combine<128, 4, 0>, k_decode_combine<128, 8, 0>);
+    }
+  } else if (least && !a.one_T) {
+    if (p.head_dim == 128) {
+      walk(k_decode_least<128>, lds128);
+      fold(k_decode_combine<128, 4, 1, int2>, k_decode_combine<128, 8, 1, int2>);
+    } else {
+      walk(k_decode_least<64>, lds64);
+      fold(k_decode_combine<64, 4, 1, int2>, k_decode_combine<64, 8, 1, int2>);
+    }
   } else if (p.head_dim == 128) {
-    if (a.one_T) walk(k_decode_one<128, 1>, decode_lds_bytes<128>()); else walk(k_decode<128>, decode_lds_bytes<128>());
+    if (a.one_T) walk(k_decode_one<128, 1>, lds128); else walk(k_decode<128>, lds128);
     fold(k_decode_combine<128, 4, 1>, k_decode_combine<128, 8, 1>);
   } else {
-    if (a.one_T) walk(k_decode_one<64, 1>, decode_lds_bytes<64>()); else walk(k_decode<64>, decode_lds_bytes<64>());
+    if (a.one_T) walk(k_decode_one<64, 1>, lds64); else walk(k_decode<64>, lds64);
     fold(k_decode_combine<64, 4, 1>, k_decode_combine<64, 8, 1>);
   }
   return hipGetLastError();

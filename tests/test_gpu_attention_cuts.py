@@ -251,6 +251,40 @@ def test_ranges_that_are_asked_for_of_many_units():
     assert ((a.float() - b.float()).norm(dim=2) <= 2e-2 * b.float().norm(dim=2)).all() and (la - lb).abs().max().item() < 1e-4
 
 
+def _guarded(n):
+    """A workspace of n bytes and the bytes behind it."""
+    buf = torch.full((n + 4096,), 0x5A, dtype=torch.uint8, device="cuda")
+    return buf[:n], buf[n:]
+
+
+def test_workspaces_without_room_for_uneven_ranges():
+    """448 units that are whole with even ranges: a workspace that holds nothing of partial results is taken (and not left), for a
+    sparse call and for a chunk; one byte less is refused."""
+    ck = vs.Chunk(32, 2, 64, 1792, 66000, 0.125, vertical_budget=100, slash_budget=500)
+    gen = torch.Generator(device="cuda").manual_seed(3160)
+    q, k, v = (torch.randn(s, generator=gen, device="cuda", dtype=torch.bfloat16) for s in ((1792, 32, 64), (ck.n_k, 2, 64), (ck.n_k, 2, 64)))
+    sets = vs.select(ck, *vs.estimate(ck, q, k)[:2])
+    calls = ((vs.VS_WS_SPARSE, lambda ws: vs.sparse_attn_prefill(ck, q, k, v, *sets, want_lse=True, ws=ws)),
+             (vs.VS_WS_CHUNK, lambda ws: vs.prefill_chunk(ck, q, k, v, want_lse=True, ws=ws)))
+    for which, call in calls:
+        full = vs.workspace_bytes(ck, which)
+        try:
+            vs.set_option(vs.VS_OPT_ATTN_KEY_SPLIT, 1)
+            least = vs.workspace_bytes(ck, which)
+            want = call(_guarded(least)[0])
+        finally:
+            vs.set_option(vs.VS_OPT_ATTN_KEY_SPLIT, 0)
+        assert full - least > 50e6
+        ws, behind = _guarded(least)
+        got = call(ws)
+        torch.cuda.synchronize()
+        assert torch.equal(got[0].view(torch.int16), want[0].view(torch.int16)) and torch.equal(got[1], want[1])
+        assert (behind == 0x5A).all()
+        with pytest.raises(vs.VsError) as e:
+            call(_guarded(least)[0][:-1])
+        assert e.value.status == vs.VS_ERR_WORKSPACE
+
+
 # heads whose lists differ by a factor of ten, and one with everything selected: ranges by the lists' own lengths (k_attn_pieces), of
 # units in several ranges (128 units), of units that are whole with even ranges (448), and of 528 of which 512 are whole units in front
 @pytest.mark.parametrize("hq,hkv,c,s,chunk", [(32, 2, 450, 20007, 0), (32, 2, 1792, 66000, 0), (8, 1, 65 * 128 - 9, 50009, 0),

@@ -1,6 +1,8 @@
 """Single tokens at the edges of the decode kernel: positions around the 32- and 64-key boundaries, group sizes from one
 head to a full MFMA tile, shares that end inside a KV head or span several requests, tokens without any line, and more
 requests than a workgroup has threads.  Against the fp64 oracle."""
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
@@ -135,3 +137,35 @@ def test_bounds_beyond_the_requests(lens, mode):
         got.append([(g["out"].clone(), g["lse"].clone()) for g in gpu])
     for a, b in zip(*got):
         assert torch.equal(a[0].view(torch.int16), b[0].view(torch.int16)) and torch.equal(a[1], b[1])
+
+
+def test_workspaces_without_room_for_neighbouring_heads():
+    """Three long tokens, one with index sets of heads that have every diagonal, in the workspace of heads by themselves."""
+    hq, hkv, d, bv, bs, n = 6, 2, 128, 100, 1400, 88000
+    rng = np.random.default_rng(2500)
+    gpu = []
+    for i in range(3):
+        pb, q, k, v, _ = _problem(rng, hq, hkv, d, n - 1 - 40 * i, bv, bs, "dense")
+        sets = None
+        if i == 1:
+            si = np.full((hq, bs), -1, np.int32)
+            si[:, :1375] = 64 * np.arange(1375)
+            si[2:4, 700:1375] = np.append(si[2:4, 701:1375], np.full((2, 1), -1), axis=1)   # two heads lack a diagonal
+            sets = (np.tile(np.arange(bv, dtype=np.int32) * 7, (hq, 1)), np.full(hq, bv, np.int32), si, (si >= 0).sum(1).astype(np.int32))
+        gpu.append(dict(q=dev(q), k=dev(k), v=dev(v), q_start=pb.q_start, out=torch.zeros((1, hq, d), dtype=torch.bfloat16, device="cuda"),
+                        lse=torch.zeros((hq, 1), device="cuda"), sets=None if sets is None else tuple(_t(x) for x in sets)))
+    ck = vs.Chunk(hq, hkv, d, 1, n - 1, 1.0 / np.sqrt(d), vertical_budget=bv, slash_budget=bs)
+    table = vs.request_table(gpu, "cuda")
+    apart = ck.params()
+    apart.k_stride_tok, apart.k_stride_head = d, d * n   # (heads by themselves)
+    least, full = (vs.lib().vs_batch_workspace_bytes(C.byref(p), 3) for p in (apart, ck.params()))
+    got = []
+    for size in (full, least):
+        buf = torch.full((size + 4096,), 0x5A, dtype=torch.uint8, device="cuda")
+        vs.attn_batch(ck, table, 3, gpu[0]["q"], gpu[0]["k"], gpu[0]["v"], gpu[0]["out"], ws=buf[:size])
+        torch.cuda.synchronize()
+        assert (buf[size:] == 0x5A).all()
+        got.append([(g["out"].clone().float(), g["lse"].clone()) for g in gpu])
+    assert least < full
+    for a, b in zip(*got):   # bf16 probabilities relative to other references, sums of other parts
+        assert (a[0] - b[0]).norm() <= 2e-2 * b[0].norm() and (a[1] - b[1]).abs().max() < 1e-4
