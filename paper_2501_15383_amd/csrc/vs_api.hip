@@ -314,7 +314,7 @@ int sparse_attn(const vs_params* p, const void* q, const vs_dca* dca, const void
   char* sync = (char*)ws + blocklist_bytes(*p, false);
   hipError_t e = launch_build_blocklist(*p, s_idx, s_cnt, v_cnt, false, bl, sync, st);
   if (e != hipSuccess) return VS_ERR_HIP;
-  return hip_status(launch_attention(*p, q, dca ? &da : nullptr, k, v, v_idx, v_cnt, false, bl, out, lse, sync,
+  return hip_status(launch_attention(*p, q, dca ? &da : nullptr, k, v, v_idx, false, bl, out, lse, sync,
                                      sync + attn_sync_bytes(*p), least, st));
 }
 
@@ -340,7 +340,7 @@ int dense_attn(const vs_params* p, const void* q, const vs_dca* dca, const void*
   char* sync = (char*)ws + blocklist_bytes(*p, true);
   hipError_t e = launch_build_blocklist(*p, nullptr, nullptr, nullptr, true, bl, sync, st);
   if (e != hipSuccess) return VS_ERR_HIP;
-  return hip_status(launch_attention(*p, q, dca ? &da : nullptr, k, v, nullptr, nullptr, true, bl, out, lse, sync,
+  return hip_status(launch_attention(*p, q, dca ? &da : nullptr, k, v, nullptr, true, bl, out, lse, sync,
                                      sync + attn_sync_bytes(*p), least, st));
 }
 }  // namespace

@@ -147,7 +147,7 @@ struct DcaArgs {
 // sync_ws: attn_sync_bytes(p) bytes: counters, cleared by launch_build_blocklist, and the schedule; split_ws:
 // attn_split_bytes(p) bytes (may be null when that is 0); dca may be null
 hipError_t launch_attention(const vs_params& p, const void* q, const DcaArgs* dca, const void* k, const void* v,
-                            const int32_t* v_idx, const int32_t* v_cnt, bool dense,
+                            const int32_t* v_idx, bool dense,
                             const BlockList& bl, void* out, float* lse, void* sync_ws, void* split_ws, bool least,
                             hipStream_t st);
 // several requests in one launch (short chunks, decode steps): p.q_len = the longest request,
