@@ -1336,6 +1336,10 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention_own(const AttnArgs a
 constexpr int kBlThreads = 1024;
 constexpr int kBlWin = 16384 + 64;  // diagonals of packed heads in LDS at a time (1M keys and what a bitmap has behind them; of one head
                                     // four times as many)
+// Groups of 64 diagonals of a single call's lists up to which their bitmaps are made by ballots.  In instantiations of their own, because
+// short calls wait for the instructions.  Calls of 4 heads with 256 offsets each, ballots and lanes: 2,500 keys 19.8 us and 20.2, 100,000
+// (25 groups of four heads) 35.6 and 36.0, 300,000 (74) 34.4 and 34.2, 1M (245) 39.9 and 36.9.
+constexpr int kBlBallots = 64;
 constexpr int kBlDensePart = 4096;  // entries of a dense list per workgroup
 constexpr int kListGroups = 4096;   // workgroups for the lists of a batch, about
 struct ListArgs {
@@ -1451,7 +1455,7 @@ __device__ void write_plan(const ListArgs& a, int64_t* scan) {
   }
 }
 // List x0; false: nothing to be done for it or the ones behind it.
-template <int NQB, bool BATCH>
+template <int NQB, bool BATCH, bool WIDE>
 __device__ __forceinline__ bool build_list(const ListArgs& a, int x0) {
   constexpr int NW = kBlThreads / 64;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -1524,50 +1528,96 @@ __device__ __forceinline__ bool build_list(const ListArgs& a, int x0) {
   }
   if (part != 0) return false;
 
-  // A byte per diagonal of the window (of four heads side by side with pack > 1), which begins with the last diagonal before it; behind
-  // it what lies outside.  Every wave has consecutive groups of 64 diagonals, a lane per diagonal.
+  // A byte per diagonal of the window (of four heads side by side with pack > 1) from f on; behind it what lies outside, in front of it the
+  // last diagonal before it.  Every wave has consecutive groups of 64 diagonals.  It writes their bitmaps and counts their entries,
+  // and then writes the entries with a lane per diagonal.  The former by ballots of a lane per diagonal too, or, WIDE, with eight
+  // diagonals of four heads, or 16 of one, per lane (see kBlBallots).
   static_assert(NQB == 2, "an entry has the diagonals of two query blocks");
-  __shared__ __attribute__((aligned(16))) uint8_t flags[4 * (kBlWin + 64)];
+  static_assert(kBlWin % 64 == 0, "whole groups");
+  __shared__ __attribute__((aligned(16))) uint8_t flags[16 + 4 * kBlWin + 16];
   __shared__ uint32_t wsum[NW], missing_s;   // (a bit per head that lacks a diagonal)
   uint32_t running = 0, before = 0, missing = 0;
   if (tid == 0) missing_s = 0u;
   const int shift = pack > 1 ? 2 : 0, win = pack > 1 ? kBlWin : 4 * kBlWin;
   for (int b0 = 0; b0 < 32 * (n_words - 2); b0 += win) {
     const int bits = 32 * (n_words - 2) - b0, n_grp = ((bits < win ? bits : win) + 63) >> 6;
-    for (int x = tid; x <= n_grp << (2 + shift); x += kBlThreads) ((u32x4*)flags)[x] = u32x4{x ? 0u : before, 0u, 0u, 0u};
+    uint8_t* const f = flags + 16;
+    for (int x = tid; x < n_grp << (2 + shift); x += kBlThreads) ((u32x4*)f)[x] = u32x4{0u, 0u, 0u, 0u};
+    if (tid == 0) f[-1] = (uint8_t)before;
     __syncthreads();
-    uint8_t* const f = flags + (1 << shift);
     const int n_in_win = n_blk - b0 < win ? (n_blk > b0 ? n_blk - b0 : 0) : win;
     collect_flags<kBlThreads, 8>(f, shift, b0, n_in_win, win, s_idx + (int64_t)h0 * a.s_budget, s_cnt + h0, a.s_budget, n_in);
     __syncthreads();
     // the mask of a diagonal's entry: the heads that have it, or, of one head, bit t: diagonal b0 + x - 1 + t
     auto mask_of = [&](int x) -> uint32_t {
       if (pack > 1) return (((const uint32_t*)f)[x] * 0x01020408u >> 24) & 15u;   // (bytes of 0 and 1 to bits)
-      return (uint32_t)flags[x] | (uint32_t)flags[x + 1] << 1;
+      return (uint32_t)f[x - 1] | (uint32_t)f[x] << 1;
     };
-    const int each = (n_grp + NW - 1) / NW, g0 = wv * each, g1 = g0 + each < n_grp ? g0 + each : n_grp;
+    const int each = (n_grp + NW - 1) / NW, g0 = wv * each < n_grp ? wv * each : n_grp, g1 = g0 + each < n_grp ? g0 + each : n_grp;
     uint32_t c = 0;
-    for (int grp = g0; grp < g1; ++grp) {
-      const uint32_t mask = mask_of(64 * grp + lane);
-      c += __popcll(__ballot(mask != 0u));
-      if (b0 + 64 * grp + lane < n_blk) missing |= ~mask;
-      // the bitmaps: lanes 2 p, 2 p + 1 write the words of head p
-      uint64_t bits_p = __ballot((mask >> (pack > 1 ? 0 : 1)) & 1u);
-      if (pack > 1)
+    if constexpr (!WIDE)
+      for (int grp = g0; grp < g1; ++grp) {
+        const uint32_t mask = mask_of(64 * grp + lane), own = pack > 1 ? mask : mask >> 1;
+        c += __popcll(__ballot(mask != 0u));
+        if (b0 + 64 * grp + lane < n_blk) missing |= ~own & (pack > 1 ? 15u : 1u);
+        // lanes 2 p, 2 p + 1 write the words of head p
+        uint64_t bits_p = __ballot(own & 1u);
+        if (pack > 1)
 #pragma unroll
-        for (int p = 1; p < 4; ++p) {
-          const uint64_t b = __ballot((mask >> p) & 1u);
-          bits_p = (lane >> 1) == p ? b : bits_p;
+          for (int p = 1; p < 4; ++p) {
+            const uint64_t b = __ballot((mask >> p) & 1u);
+            bits_p = (lane >> 1) == p ? b : bits_p;
+          }
+        const int w = (b0 >> 5) + 2 * grp + (lane & 1);
+        if (lane < 2 * n_in && w < n_words - 2) A[(int64_t)(lane >> 1) * n_words + w] = (uint32_t)(bits_p >> (32 * (lane & 1)));
+      }
+    auto add_up = [&](uint32_t mine) {   // mine: at most 16
+#pragma unroll
+      for (int b = 0; b < 5; ++b) c += (uint32_t)__popcll(__ballot((mine >> b) & 1u)) << b;
+    };
+    // diagonals from d on that exist, of n
+    auto existing = [&](int d, int n) -> uint32_t { return d + n <= n_blk ? (1u << n) - 1u : (d < n_blk ? (1u << (n_blk - d)) - 1u : 0u); };
+    if constexpr (!WIDE) {
+    } else if (pack > 1) {
+      for (int x0 = 8 * g0; x0 < 8 * g1; x0 += 64) {
+        const int x = x0 + lane;
+        uint32_t n = 0;
+        if (x < 8 * g1) {
+          const u32x4 lo = ((const u32x4*)f)[2 * x], hi = ((const u32x4*)f)[2 * x + 1];
+          const uint32_t v = lo[0] | lo[1] << 1 | lo[2] << 2 | lo[3] << 3 | hi[0] << 4 | hi[1] << 5 | hi[2] << 6 | hi[3] << 7;   // (a byte per head)
+          const uint32_t want = existing(b0 + 8 * x, 8);
+#pragma unroll
+          for (int p = 0; p < 4; ++p) {
+            const uint32_t v_p = (v >> (8 * p)) & 0xFFu;
+            if (p < n_in && b0 + 8 * x < 32 * (n_words - 2)) ((uint8_t*)(A + (int64_t)p * n_words))[(b0 >> 3) + x] = (uint8_t)v_p;
+            missing |= v_p != want ? 1u << p : 0u;
+          }
+          n = __popc((v | v >> 8 | v >> 16 | v >> 24) & 0xFFu);
         }
-      const int w = (b0 >> 5) + 2 * grp + (lane & 1);
-      if (lane < 2 * n_in && w < n_words - 2) A[(int64_t)(lane >> 1) * n_words + w] = (uint32_t)(bits_p >> (32 * (lane & 1)));
+        add_up(n);
+      }
+    } else {
+      for (int x0 = 4 * g0; x0 < 4 * g1; x0 += 64) {
+        const int x = x0 + lane;
+        uint32_t n = 0;
+        if (x < 4 * g1) {
+          const u32x4 q = ((const u32x4*)f)[x];
+          uint32_t v = 0;
+#pragma unroll
+          for (int y = 0; y < 4; ++y) v |= ((q[y] * 0x01020408u >> 24) & 15u) << (4 * y);
+          if (b0 + 16 * x < 32 * (n_words - 2)) ((uint16_t*)A)[(b0 >> 4) + x] = (uint16_t)v;
+          missing |= v != existing(b0 + 16 * x, 16) ? 1u : 0u;
+          n = __popc((v | v << 1 | f[16 * x - 1]) & 0xFFFFu);
+        }
+        add_up(n);
+      }
     }
     if (lane == 0) wsum[wv] = c;
     uint32_t lacks = 0;
 #pragma unroll
     for (int p = 0; p < 4; ++p) lacks |= __ballot((missing >> p) & 1u) ? 1u << p : 0u;
     if (lane == 0) atomicOr(&missing_s, lacks);
-    before = pack > 1 ? 0u : flags[win];
+    before = pack > 1 ? 0u : f[win - 1];
     __syncthreads();
     uint32_t pos = running;
     for (int x = 0; x < NW; ++x) {
@@ -1590,11 +1640,11 @@ __device__ __forceinline__ bool build_list(const ListArgs& a, int x0) {
   } else if (tid == 0) {
     int sft = 0;
     while (sft < 4 && ((uint32_t)n_blk >> (sft + 1)) >= (running > 0 ? running : 1u)) ++sft;
-    write_tail(0, running, sft, !(missing_s & 2u));   // (bit 1 of an entry's mask is its own diagonal)
+    write_tail(0, running, sft, missing_s == 0u);
   }
   return true;
 }
-template <int NQB, bool BATCH>
+template <int NQB, bool BATCH, bool WIDE = false>
 __global__ __launch_bounds__(kBlThreads) void k_build_blocklist(const ListArgs a) {
   if (blockIdx.x == 0 && blockIdx.y == 0)
     for (int x = threadIdx.x; x < a.n_zero; x += kBlThreads) a.zero[x] = 0u;
@@ -1605,11 +1655,11 @@ __global__ __launch_bounds__(kBlThreads) void k_build_blocklist(const ListArgs a
       return;
     }
     for (int x0 = blockIdx.x; x0 < a.n_heads; x0 += gridDim.x) {
-      if (!build_list<NQB, true>(a, x0)) return;   // (the same for all threads)
+      if (!build_list<NQB, true, WIDE>(a, x0)) return;   // (the same for all threads)
       __syncthreads();   // its LDS is the next list's
     }
   } else {
-    build_list<NQB, false>(a, blockIdx.x);
+    build_list<NQB, false, WIDE>(a, blockIdx.x);
   }
 }
 
@@ -2149,7 +2199,10 @@ hipError_t launch_build_blocklist(const vs_params& p, const int32_t* s_idx, cons
   a.n_zero = sync_ws ? (int)(attn_counter_bytes(p) / sizeof(uint32_t)) : 0;
   const unsigned parts = dense ? (unsigned)ceil_div(bl.ent_stride, kBlDensePart) : 1u;
   const unsigned lists = dense ? 1u : (unsigned)(p.n_kv_heads * ceil_div(a.group, a.pack));
-  hipLaunchKernelGGL((k_build_blocklist<kAttnQBlocks, false>), dim3(lists, parts), dim3(kBlThreads), 0, st, a);
+  if (!dense && a.n_blk > 64 * kBlBallots)
+    hipLaunchKernelGGL((k_build_blocklist<kAttnQBlocks, false, true>), dim3(lists, parts), dim3(kBlThreads), 0, st, a);
+  else
+    hipLaunchKernelGGL((k_build_blocklist<kAttnQBlocks, false>), dim3(lists, parts), dim3(kBlThreads), 0, st, a);
   return hipGetLastError();
 }
 

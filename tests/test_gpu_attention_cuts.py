@@ -178,6 +178,25 @@ def test_lists_of_several_windows(hq, c, win):
     _check_by_gathering(ck, q, k, v, vi, si, sc)
 
 
+# the two ways to make bitmaps: 4,096 diagonals and one more, of four heads and of one, an odd word and a part of one behind them
+@pytest.mark.parametrize("n", [64 * 4096, 64 * 4096 + 1, 64 * 4128 + 17])
+@pytest.mark.parametrize("hq,c", [(7, 2), (2, 70)])
+def test_lists_at_the_line_between_ballots_and_lanes(hq, c, n):
+    d = 64
+    gen = torch.Generator(device="cuda").manual_seed(3170)
+    q, k, v = (torch.randn(s, generator=gen, device="cuda", dtype=torch.bfloat16) for s in ((c, hq, d), (n, 1, d), (n, 1, d)))
+    rng = np.random.default_rng(3171)
+    ck = vs.Chunk(hq, 1, d, c, n - c, 0.125, vertical_budget=40, slash_budget=4500)
+    vi = np.full((hq, 40), -1, np.int32); si = np.full((hq, 4500), -1, np.int32)
+    sc = np.zeros(hq, np.int32)
+    for h in range(hq):
+        vi[h] = np.sort(rng.choice(n - c, 40, replace=False))
+        offs = 64 * np.arange((n + 63) // 64) if h % 3 == 1 else np.unique(np.concatenate([[0, n - 1], rng.choice(n, 30 * (1 + h), replace=False)]))
+        if h == 4: offs = offs[:-1]   # all but the last diagonal
+        sc[h] = len(offs); si[h, :sc[h]] = offs
+    _check_by_gathering(ck, q, k, v, vi, si, sc)
+
+
 # heads that have every diagonal, whose columns nobody gathers, beside heads that lack one diagonal (the first, one inside, the last) and
 # have columns in its key block: single tokens, packed heads, tiles of two query blocks
 @pytest.mark.parametrize("hq,c,n", [(3, 1, 1000), (7, 1, 64), (4, 2, 1000), (5, 40, 2048), (3, 130, 1000), (2, 300, 4999)])
