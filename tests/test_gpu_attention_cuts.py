@@ -304,17 +304,41 @@ def test_workspaces_without_room_for_uneven_ranges():
         assert e.value.status == vs.VS_ERR_WORKSPACE
 
 
+def _uneven_pieces(ws):
+    """What k_attn_pieces left in the workspace of a sparse call: the number of pieces of an uneven cut, 0 where the even one stayed.  Behind
+    it, at the end of the workspace, lie 256 bytes less one word, 2,048 units (8 bytes) and 2,048 pieces (32 bytes)."""
+    at = ws.numel() - 256 - 2048 * (8 + 32)
+    torch.cuda.synchronize()
+    return int(ws[at:at + 4].view(torch.int32).item())
+
+
+@pytest.mark.parametrize("differ", [0, 1])
+def test_lists_of_about_one_length_keep_even_ranges(differ):
+    hq, c, s = 32, 450, 20007
+    ck = vs.Chunk(hq, 2, 64, c, s, 0.125, vertical_budget=100, slash_budget=2000)
+    gen = torch.Generator(device="cuda").manual_seed(3180)
+    q, k, v = (torch.randn(x, generator=gen, device="cuda", dtype=torch.bfloat16) for x in ((c, hq, 64), (s + c, 2, 64), (s + c, 2, 64)))
+    si = np.full((hq, 2000), -1, np.int32); sc = np.full(hq, 150, np.int32)
+    for h in range(hq):
+        sc[h] -= differ * (h % 3)
+        si[h, :sc[h]] = 128 * np.arange(sc[h])
+    ws = torch.zeros(vs.workspace_bytes(ck, vs.VS_WS_SPARSE), dtype=torch.uint8, device="cuda")
+    vi = np.tile(np.arange(100, dtype=np.int32), (hq, 1))
+    vs.sparse_attn_prefill(ck, q, k, v, *[_t(x) for x in (vi, np.full(hq, 100, np.int32), si, sc)], ws=ws)
+    assert _uneven_pieces(ws) == 0
+
+
 # heads whose lists differ by a factor of ten, and one with everything selected: ranges by the lists' own lengths (k_attn_pieces), of
 # units in several ranges (128 units), of units that are whole with even ranges (448), and of 528 of which 512 are whole units in front
-@pytest.mark.parametrize("hq,hkv,c,s,chunk", [(32, 2, 450, 20007, 0), (32, 2, 1792, 66000, 0), (8, 1, 65 * 128 - 9, 50009, 0),
+@pytest.mark.parametrize("hq,hkv,c,s,chunk", [(32, 2, 450, 20007, 0), (32, 2, 1792, 66000, 0), (8, 1, 65 * 128 - 9, 140009, 0),
                                               (32, 2, 450, 20007, 6400)])
 def test_ranges_by_the_lists_own_lengths(hq, hkv, c, s, chunk):
     d, n = 64, s + c
     rng = np.random.default_rng(3130)
     qs = [rand_bf16(rng, (c, hq, d)) for _ in range(3 if chunk else 1)]
     k = rand_bf16(rng, (n, hkv, d)); v = rand_bf16(rng, (n, hkv, d))
-    pb = oracle.Problem(hq, hkv, d, c, s, 1.0 / np.sqrt(d), vertical_budget=100, slash_budget=2000)
-    vi = np.full((hq, 100), -1, np.int32); si = np.full((hq, 2000), -1, np.int32)
+    pb = oracle.Problem(hq, hkv, d, c, s, 1.0 / np.sqrt(d), vertical_budget=100, slash_budget=2500)
+    vi = np.full((hq, 100), -1, np.int32); si = np.full((hq, 2500), -1, np.int32)
     vc = rng.integers(1, 101, hq).astype(np.int32); sc = np.zeros(hq, np.int32)
     for h in range(hq):
         vi[h, :vc[h]] = np.sort(np.concatenate([[0], 1 + rng.choice(n - 1, vc[h] - 1, replace=False)]))
@@ -325,12 +349,15 @@ def test_ranges_by_the_lists_own_lengths(hq, hkv, c, s, chunk):
         si[h, :sc[h]] = offs
     dca = (dev(qs[1]), dev(qs[2]), chunk, 640) if chunk else None
     args = (chunk_of(pb), dev(qs[0]), dev(k), dev(v), *[_t(x) for x in (vi, vc, si, sc)])
-    size = vs.workspace_bytes(chunk_of(pb), vs.VS_WS_SPARSE)
-    out, lse = vs.sparse_attn_prefill(*args, want_lse=True, dca=dca)
+    ws = torch.zeros(vs.workspace_bytes(chunk_of(pb), vs.VS_WS_SPARSE), dtype=torch.uint8, device="cuda")
+    out, lse = vs.sparse_attn_prefill(*args, want_lse=True, dca=dca, ws=ws)
+    pieces = _uneven_pieces(ws)
+    # by length: more than one a unit, and not a multiple of the units as with the same number of ranges for all
+    n_cut = hq * ((c + s % 64 + 127) // 128) % 512
+    assert n_cut < pieces <= 2048 and pieces % n_cut, (pieces, n_cut)
     again, lse_again = vs.sparse_attn_prefill(*args, want_lse=True, dca=dca)
     vs.set_option(vs.VS_OPT_ATTN_KEY_SPLIT, 1)
     try:
-        assert size > vs.workspace_bytes(chunk_of(pb), vs.VS_WS_SPARSE)   # (it was cut)
         one, lse_one = vs.sparse_attn_prefill(*args, want_lse=True, dca=dca)
     finally:
         vs.set_option(vs.VS_OPT_ATTN_KEY_SPLIT, 0)

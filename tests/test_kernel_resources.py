@@ -67,8 +67,8 @@ def test_the_dca_kernels_spill_no_more_than_a_handful_of_registers(resources):
 # (kernel, vector registers that its waves per compute unit allow, registers it may spill): four waves per SIMD of
 # the estimate's sweeps have 128 (sweep A at head_dim 64 is held to 96, where small workgroups get a fifth wave: 7 heads of their
 # own, 100,000 keys 44 us, 49 with 98), three with Dual Chunk Attention 168 (sweep A at head_dim 128 spills one);
-# a selection row is one workgroup of 16 waves, 128, whatever the scores per lane; the decode kernel's four waves share a compute
-# unit's LDS with nobody
+# a selection row is one workgroup of 16 waves, 128, whatever the scores per lane, and so are a list and the pieces of an uneven cut;
+# the decode kernel's four waves share a compute unit's LDS with nobody
 @pytest.mark.parametrize("source,budgets", [
     ("vs_estimate", {"k_est_sumsILi128ELb0E": (128, 0), "k_est_scoresILi128ELb0E": (128, 0), "k_est_sumsILi64ELb0E": (96, 0),
                      "k_est_scoresILi64ELb0E": (128, 0), "k_est_sumsILi128ELb1E": (168, 2), "k_est_scoresILi128ELb1E": (168, 0),
@@ -76,8 +76,13 @@ def test_the_dca_kernels_spill_no_more_than_a_handful_of_registers(resources):
     ("vs_select", {**{f"k_sel_rowILi{kpt}E": (128, 0) for kpt in (0, 4, 8, 12, 16, 24, 32, 40, 48)},
                    "k_sel_sample": (128, 0), "k_sel_filter": (128, 0), "k_slice_digit": (64, 0), "k_slice_count": (64, 0),
                    "k_slice_write": (64, 0)}),
+    ("vs_attn", {"k_attention_ownILi128ELi2ELb0E": (256, 0), "k_attention_ownILi64ELi2ELb0E": (256, 0),
+                 "k_attention_ownILi128ELi2ELb1E": (256, 16), "k_attention_ownILi64ELi2ELb1E": (256, 16), "k_attn_pieces": (128, 0),
+                 **{f"k_attn_combineILi{d}ELb{b}ELb{o}E": (128, 0) for d in (64, 128) for b, o in ((0, 0), (0, 1), (1, 0))},
+                 **{f"k_build_blocklistILi2ELb{b}ELb{w}E": (128, 0) for b, w in ((0, 0), (0, 1), (1, 0))}}),
     ("vs_decode", {"k_decodeILi128E": (256, 0), "k_decodeILi64E": (256, 0), "k_decode_lists": (64, 0), "k_decode_pairs": (256, 0),
-                   "k_decode_oneILi128ELi1E": (256, 0), "k_decode_oneILi128ELi2E": (256, 0), "k_decode_oneILi64ELi1E": (256, 0)}),
+                   "k_decode_oneILi128ELi1E": (256, 0), "k_decode_oneILi128ELi2E": (256, 0), "k_decode_oneILi64ELi1E": (256, 0),
+                   "k_decode_leastILi128E": (256, 0), "k_decode_leastILi64E": (256, 0), "k_decode_least_lists": (64, 0)}),
 ])
 def test_the_other_kernels_keep_their_register_budgets(tmp_path_factory, source, budgets):
     res = _compile(tmp_path_factory, source)
