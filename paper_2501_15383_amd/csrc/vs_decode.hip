@@ -40,9 +40,10 @@ constexpr int kDecListBytes = 128 << 10;   // a byte per diagonal and head in LD
 // and 62.9, 24 at 2K to 64K keys 223 and 212.
 // Only where the rows of neighbouring heads lie next to each other: in caches of [KV heads][keys][128] 140,000 keys 48.1 -> 50.9, 1M 377 ->
 // 387, 24 tokens 208 -> 212.  Heads of 64 (8 / 2, 300,000 keys): 36.5 -> 37.8, so not these.  With index sets the two walks drift
-// apart: one token at 600,000 keys 209 -> 221, 64 of 16 heads per group at 60,000 938 -> 980.  So: a single token without index sets by
-// its length; a table whose bounds are as large by its requests' own lengths, on the device, where none has index sets (a request of
-// 12,000 keys under a bound of 262,144 13.4 -> 15.2 by the bounds alone).
+// apart: one token at 600,000 keys 209 -> 221, 64 of 16 heads per group at 60,000 917 -> 968; unless every head has every diagonal, and
+// the walks are those of tokens without sets.  So: a single token without index sets by its length; a table whose bounds are as
+// large by its requests' own lengths and sets, on the device (a request of 12,000 keys under a bound of 262,144 13.4 -> 15.2 by the bounds
+// alone).
 constexpr int64_t kDecSideBlocks = 8192;
 
 struct DecodeArgs {
@@ -86,42 +87,42 @@ __device__ __forceinline__ bool decode_takes(const DecodeArgs& a, const vs_reque
   return rq.s_idx == nullptr || (rq.v_idx && rq.v_cnt && rq.s_cnt);
 }
 __device__ __forceinline__ int decode_blocks(const vs_request& rq) { return (int)((rq.q_start + kBlock) / kBlock); }
-// units of request r with every KV head by itself
+// units of request r with every KV head by itself; uneven: set where it has index sets that leave out a key
 template <typename Len>
-__device__ __forceinline__ int64_t decode_units(const DecodeArgs& a, int r, const vs_request& rq) {
+__device__ __forceinline__ int64_t decode_units(const DecodeArgs& a, int r, const vs_request& rq, bool& uneven) {
   if (!decode_takes(a, rq)) return 0;
   if (!rq.s_idx) return (int64_t)decode_blocks(rq) * a.n_kv_heads;
   int64_t n = 0;
-  for (int g = 0; g < a.n_kv_heads; ++g) n += ((const Len*)a.len)[(int64_t)r * a.n_kv_heads + g].y;
+  for (int g = 0; g < a.n_kv_heads; ++g) {
+    const Len l = ((const Len*)a.len)[(int64_t)r * a.n_kv_heads + g];
+    n += l.y;
+    if constexpr (sizeof(Len) > 8) uneven |= (~(uint32_t)l.z & ((1u << a.group) - 1u)) != 0u;
+  }
   return n;
 }
-// Those of all requests, and of request tid (mine).  DENSE: -1 - their number where a request has index sets.  Called by a whole workgroup.
-template <bool DENSE, typename Len>
-__device__ __forceinline__ int64_t decode_total(const DecodeArgs& a, int64_t& mine) {
+// Those of all requests, and of request tid (mine).  Called by a whole workgroup.
+template <typename Len>
+__device__ __forceinline__ int64_t decode_total(const DecodeArgs& a, int64_t& mine, bool& uneven) {
   __shared__ int64_t sum_s[kDecWaves];
-  constexpr int kSets = 52;   // from this bit on: requests with index sets (4,096 requests of far fewer than 2^40 units each)
-  const int tid = threadIdx.x;
+  __shared__ uint32_t uneven_s[kDecWaves];
+  const int tid = threadIdx.x, wv = tid >> 6;
+  uneven = false;
   auto of = [&](int r) -> int64_t {
     const vs_request rq = a.req ? a.req[r] : a.one;
-    const int64_t n = decode_units<Len>(a, r, rq);
-    return DENSE && n && rq.s_idx ? n + (1ll << kSets) : n;
+    return decode_units<Len>(a, r, rq, uneven);
   };
   int64_t T = mine = 0;
-  if (a.n_req == 1) {
-    T = of(0);
-  } else {
-    if (tid < a.n_req) T = mine = of(tid);
-    for (int r = tid + kDecThreads; r < a.n_req; r += kDecThreads) T += of(r);
+  if (a.n_req == 1) return of(0);
+  if (tid < a.n_req) T = mine = of(tid);
+  for (int r = tid + kDecThreads; r < a.n_req; r += kDecThreads) T += of(r);
 #pragma unroll
-    for (int d = 1; d < 64; d <<= 1) T += __shfl_xor((long long)T, d);
-    if ((tid & 63) == 0) sum_s[tid >> 6] = T;
-    __syncthreads();
-    T = 0;
-    for (int w = 0; w < kDecWaves; ++w) T += sum_s[w];
-  }
-  if (!DENSE || T >> kSets == 0) return T;
-  mine &= (1ll << kSets) - 1;
-  return -1 - (T & ((1ll << kSets) - 1));
+  for (int d = 1; d < 64; d <<= 1) T += __shfl_xor((long long)T, d);
+  const uint32_t any = __ballot(uneven) ? 1u : 0u;
+  if ((tid & 63) == 0) { sum_s[wv] = T; uneven_s[wv] = any; }
+  __syncthreads();
+  T = 0;
+  for (int w = 0; w < kDecWaves; ++w) { T += sum_s[w]; uneven |= uneven_s[w] != 0u; }
+  return T;
 }
 // share w of n covers units [w T / n, (w + 1) T / n)
 // (quotients of 64 bits, most of which fit 32: a fifth of the instructions)
@@ -147,7 +148,7 @@ __device__ __forceinline__ void dec_dma_lane(uint32_t lds_addr, const void* ptr)
 // ONE: a single request without index sets (no table, no lists; the host has counted its units).  In a kernel of its own, because a short
 // token waits for its instructions: 5,003 keys 11.40 us where the kernel of all requests had 3,756 instructions, 11.55 with
 // 3,770 of them, 9.9 with the 1,893 of this one.
-// T: units of all requests, mine: of request tid with every KV head by itself.  SIDE > 1: nobody has index sets.
+// T: units of all requests, mine0: of request tid with every KV head by itself.  SIDE > 1: nobody has index sets that leave out a key.
 template <int D, int SIDE, bool ONE, typename Len>
 __device__ __forceinline__ void decode_body(const DecodeArgs& a, int64_t T, int64_t mine0) {
   constexpr int DCH = D / 8;         // 16-byte pieces per row
@@ -172,7 +173,8 @@ __device__ __forceinline__ void decode_body(const DecodeArgs& a, int64_t T, int6
   // ---- this workgroup's share ------------------------------------------------------------------
   auto units_of = [&](int r) -> int64_t {
     const vs_request rq = a.req ? a.req[r] : a.one;
-    return decode_units<Len>(a, r, rq) / SIDE;
+    bool unused;
+    return decode_units<Len>(a, r, rq, unused) / SIDE;
   };
   int64_t first = 0;
   constexpr int min_units = kDecMinBlocks / SIDE;
@@ -240,7 +242,7 @@ __device__ __forceinline__ void decode_body(const DecodeArgs& a, int64_t T, int6
       if (!decode_takes(a, rq)) { ++r; continue; }
       fresh = false;
     }
-    const bool with_sets = !ONE && SIDE == 1 && rq.s_idx != nullptr;
+    bool with_sets = !ONE && SIDE == 1 && rq.s_idx != nullptr;
     const int64_t n_k = rq.q_start + 1;
     const int g = sg * SIDE + sub;   // this wave's KV head
     int n_ent = decode_blocks(rq), seg_len = n_ent, full = 0;
@@ -248,7 +250,12 @@ __device__ __forceinline__ void decode_body(const DecodeArgs& a, int64_t T, int6
       const Len l2 = ((const Len*)a.len)[(int64_t)r * a.n_kv_heads + g];
       n_ent = __builtin_amdgcn_readfirstlane(l2.x);
       seg_len = __builtin_amdgcn_readfirstlane(l2.y);
-      if constexpr (sizeof(Len) > 8) full = l2.z;
+      if constexpr (sizeof(Len) > 8) {
+        // (a KV head all of whose heads have every diagonal is walked as without sets: 19 tokens of up to 4,419 keys, 40 heads, 48.8 us ->
+        // 46.4, 16 of up to 8,000, half of them without sets, 52.2 -> 49.5)
+        full = l2.z;
+        with_sets = __builtin_amdgcn_readfirstlane(~full & ((1 << a.group) - 1)) != 0;
+      }
     }
     if (blk >= seg_len) {   // the share starts in a later segment of this request
       blk -= seg_len;
@@ -517,8 +524,9 @@ __device__ __forceinline__ void decode_body(const DecodeArgs& a, int64_t T, int6
       }
     }
     };
-    if (with_sets) walk(std::true_type{});
-    else walk(std::false_type{});
+    // (in this order: 16 tokens of up to 4,000 keys 21.9 us the other way round, 21.2 so)
+    if (__builtin_expect(!with_sets, 1)) walk(std::false_type{});
+    else walk(std::true_type{});
     __syncthreads();   // the LDS is reused by the next piece
     left -= take64;
     blk = 0;
@@ -529,7 +537,8 @@ __device__ __forceinline__ void decode_body(const DecodeArgs& a, int64_t T, int6
 template <int D, typename Len>
 __device__ __forceinline__ void decode_apart(const DecodeArgs& a) {
   int64_t mine;
-  const int64_t T = decode_total<false, Len>(a, mine);
+  bool unused;
+  const int64_t T = decode_total<Len>(a, mine, unused);
   decode_body<D, 1, false, Len>(a, T, mine);
 }
 template <int D>
@@ -539,9 +548,10 @@ __global__ __launch_bounds__(kDecThreads, 2) void k_decode_least(const DecodeArg
 // A table whose bounds allow two neighbouring KV heads side by side: whether that pays, its requests say (see kDecSideBlocks).
 __global__ __launch_bounds__(kDecThreads, 2) void k_decode_pairs(const DecodeArgs a) {
   int64_t mine;
-  const int64_t T = decode_total<true, int4>(a, mine);
-  if (T >= kDecSideBlocks) decode_body<128, 2, false, int4>(a, T / 2, mine);
-  else decode_body<128, 1, false, int4>(a, T < 0 ? -1 - T : T, mine);
+  bool uneven;
+  const int64_t T = decode_total<int4>(a, mine, uneven);
+  if (T >= kDecSideBlocks && !uneven) decode_body<128, 2, false, int4>(a, T / 2, mine);
+  else decode_body<128, 1, false, int4>(a, T, mine);
 }
 template <int D, int SIDE>
 __global__ __launch_bounds__(kDecThreads, 2) void k_decode_one(const DecodeArgs a) { decode_body<D, SIDE, true, int4>(a, a.one_T, 0); }
@@ -564,8 +574,8 @@ __global__ __launch_bounds__(64 * NW) void k_decode_combine(const DecodeArgs a) 
   const int rows = side * a.group, sg = h / rows, q = h - sg * rows;
   int64_t from = a.one_T ? 0 : a.plan[2 + r];
   int seg_len = decode_blocks(rq);
-  if (rq.s_idx) {
-    const Len* const len = (const Len*)a.len + (int64_t)r * a.n_kv_heads;   // (one KV head by itself)
+  if (rq.s_idx && (SIDE == 1 || side == 1)) {
+    const Len* const len = (const Len*)a.len + (int64_t)r * a.n_kv_heads;
     for (int x = 0; x < sg; ++x) from += len[x].y;
     seg_len = len[sg].y;
   } else {

@@ -169,3 +169,22 @@ def test_workspaces_without_room_for_neighbouring_heads():
     assert least < full
     for a, b in zip(*got):   # bf16 probabilities relative to other references, sums of other parts
         assert (a[0] - b[0]).norm() <= 2e-2 * b[0].norm() and (a[1] - b[1]).abs().max() < 1e-4
+
+
+def test_as_many_sparse_tokens_as_a_table_takes():
+    """4,096 tokens with index sets, 8,192 units: none of them may be taken for one without."""
+    hq, hkv, d, n, n_req = 4, 2, 128, 150, 4096
+    gen = torch.Generator(device="cuda").manual_seed(2600)
+    q, k, v = (torch.randn(s, generator=gen, device="cuda", dtype=torch.bfloat16) for s in ((1, hq, d), (n, hkv, d), (n, hkv, d)))
+    ck = vs.Chunk(hq, hkv, d, 1, n - 1, 1.0 / np.sqrt(d), vertical_budget=20, slash_budget=3)
+    si = np.array([[0, -1, -1], [64, -1, -1], [0, 128, -1], [0, 64, 128]], np.int32)   # (the last head has every diagonal)
+    vi = np.tile(np.arange(20, dtype=np.int32) * 3, (hq, 1))
+    sets = tuple(_t(x) for x in (vi, np.full(hq, 20, np.int32), si, (si >= 0).sum(1).astype(np.int32)))
+    want, lse = vs.sparse_attn_prefill(ck, q, k, v, *sets, want_lse=True)
+    out = torch.zeros((n_req, 1, hq, d), dtype=torch.bfloat16, device="cuda")
+    lses = torch.zeros((n_req, hq, 1), device="cuda")
+    table = vs.request_table([dict(q=q, k=k, v=v, q_start=n - 1, out=out[i], lse=lses[i], sets=sets) for i in range(n_req)], "cuda")
+    vs.attn_batch(ck, table, n_req, q, k, v, out[0])
+    torch.cuda.synchronize()
+    assert ((out.float() - want.float()).flatten(1).norm(dim=1) <= 2e-2 * want.float().norm()).all()
+    assert (lses - lse).abs().max() < 1e-4
