@@ -33,6 +33,7 @@ run checks the expression.  WRITE_SIZE is in KiB and matches the copy one to one
     python3 bench_counters.py [PROF]     writes profiles/vs_kernels_7b_1m_last_chunk.txt
                                                      and profiles/traffic_k_attention_7b_1m.json
     python3 bench_counters.py --others [PROF]   writes profiles/vs_kernels_other_workloads.txt (see others())
+    python3 bench_counters.py --cases [PROF]    writes profiles/vs_kernels_cases.txt (see cases())
 """
 import collections
 import csv
@@ -144,11 +145,45 @@ def others(base):
     print("\n".join(out))
 
 
+# calls of perf/cases.py, by what they show: the decode kernels, ranges by the lists' lengths, a small chunk
+CASES = [("token", "c._dense(c.SHAPE_28, 1, 5003)"), ("token_1m", "c._dense(c.SHAPE_28, 1, c.MILLION)"),
+         ("tokens", "c._batch(c.SHAPE_28, 24, 65536, 'dense', 1, False)"),
+         ("tokens_sparse", "c._batch(c.SHAPE_28, 8, 262144, 'sparse', 1, True)"),
+         ("mixed", "c._batch(c.SHAPE_28, 8, 262144, 'mixed', 64, True)"),
+         ("clustered", "c._chunk(c.SHAPE_28, 333, 100000, local=True)"), ("small", "c._chunk(c.SHAPE_4, 1024, 4096)")]
+CASE_PROGRAM = ("import torch; from perf import cases as c; s = c.prepare({}, 1); "
+                "[c.run(s) for _ in range(20)]; torch.cuda.synchronize()")
+
+
+def cases(base):
+    """profiles/vs_kernels_cases.txt from the kernel traces case_<name> of the calls above:
+         rocprofv3 --kernel-trace --output-format csv -d PROF/case_<name> -- python3 -c PROGRAM"""
+    out = ["# rocprofv3 kernel traces of calls of perf/cases.py (one MI355X; raw outputs are not kept; written by",
+           f"# bench_counters.py --cases; sources of the library: sha256[:16] = {sources_hash()}).  Each block: the call, and the",
+           "# kernels of the library with their launch times over 20 passes (21 of a batch), in us.  command:",
+           "# rocprofv3 --kernel-trace --output-format csv -d PROF/case_NAME -- python3 -c",
+           f"#   \"{CASE_PROGRAM.format('CALL')}\"", ""]
+    for name, call in CASES:
+        per = collections.OrderedDict()
+        for r in csv.DictReader(open(one(base, f"case_{name}", "**/*_kernel_trace.csv"))):
+            if "vs::" in r["Kernel_Name"]:
+                per.setdefault(r["Kernel_Name"], []).append((int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3)
+        out += [f"## {name}: {call}", f"{'kernel':62s} {'calls':>5s} {'avg us':>10s} {'min us':>10s} {'max us':>10s}"]
+        out += [f"{n[:62]:62s} {len(v):5d} {sum(v) / len(v):10.2f} {min(v):10.2f} {max(v):10.2f}" for n, v in per.items()]
+        out.append("")
+    open(os.path.join(ROOT, "profiles", "vs_kernels_cases.txt"), "w").write("\n".join(out))
+    print("\n".join(out))
+
+
 def main():
     if len(sys.argv) > 2 and sys.argv[1] == "--stamp":
         return stamp(sys.argv[2])
     if len(sys.argv) > 1 and sys.argv[1] == "--others":
         return others(sys.argv[2] if len(sys.argv) > 2 else "PROF")
+    if len(sys.argv) > 1 and sys.argv[1] == "--cases":
+        return cases(sys.argv[2] if len(sys.argv) > 2 else "PROF")
+    if len(sys.argv) > 2 and sys.argv[1] == "--case-program":   # for the command line of a run
+        return print(CASE_PROGRAM.format(dict(CASES)[sys.argv[2]]))
     base = sys.argv[1] if len(sys.argv) > 1 else "PROF"
     sys.path.insert(0, ROOT)
     import bench

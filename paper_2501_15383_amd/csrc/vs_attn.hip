@@ -35,7 +35,7 @@
 //    pattern; section 5.1) and SPLIT (short chunks, and what whole rounds leave of longer ones:
 //    the key walk cut into pieces that wait in queues, partial results folded by k_attn_combine;
 //    heads of a KV group share a tile where the rows leave half of it empty).  The plain kernel is
-//    its own instantiation.
+//    its own instantiation, and so is the one whose ranges may follow the lists' lengths (k_attention_own).
 #include <atomic>
 #include <mutex>
 
@@ -295,7 +295,11 @@ __device__ __forceinline__ void cut_segment(const AttnArgs& a, int x, int& list,
 // of a unit.  n follows the length, for up to four rounds of 512 pieces; most = 0 where the even cut is to stay: lists equally long
 // (so that with everything selected the results are those of dense calls), or a gain of less than 5 % by this count.
 // 28 heads, clustered slashes, even -> uneven: 200 rows at 500K keys 1,588 us -> 1,080, 333 at 100K 656 -> 518, 1,000 at 300K 2,584 ->
-// 1,958, 2,000 at 150K 2,811 -> 2,390; lists that differ by a tenth or less within 1 %.
+// 1,958, 2,000 at 150K 2,811 -> 2,390; lists that differ by a tenth or less within 1 %.  Finding the ranges takes 2.5 to 4.5 us, also where
+// the even cut then stays or was as good: 1,000 rows of 8 heads at 200K keys 336 -> 338, the attention alone 95.8 -> 98.2, of 100 rows of 4
+// heads at 300K with offsets side by side 30.2 -> 34.5; against 275 -> 203 for 300 clustered rows of those at 900K, 300 -> 206 for 2,000
+// of 8 heads at 200K.  (A gain of four steps asked for on top of the 5 % keeps the even cut in these, too: equal distances hide from the
+// count that all entries lie in one range.)
 constexpr int kOwnRounds = 4, kOwnSegments = 64;
 __device__ __forceinline__ void own_cut(const AttnArgs& a, int lane, int& n, int& cnt, int& slot, int& pieces, int& most) {
   int list, e0;

@@ -18,7 +18,7 @@
 //    heads whose own list has the diagonal: the scores of the others are -inf), then the gathered columns head by head.
 // Measured on one MI355X, 28 query / 4 KV heads, head_dim 128, against the tile kernel of vs_attn.hip with the heads as rows of
 // its 128-row tiles (copies of a step shared by four waves of which one multiplied, a barrier per step, one range count for a
-// whole batch): one token at 5,003 keys 39 -> 15 us, at 1M keys 510 -> 363 (5.9 TB/s of K and V); 24 tokens at 2K to 64K keys
+// whole batch): one token at 5,003 keys 39 -> 10 us, at 1M keys 510 -> 361 (5.9 TB/s of K and V); 24 tokens at 2K to 64K keys
 // 395 -> 215 (5.8 TB/s); 8 tokens with index sets at 262,144 keys 1,042 -> 770 (lists 252 -> 17 of it).
 #include <type_traits>
 

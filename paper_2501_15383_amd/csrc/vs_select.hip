@@ -44,7 +44,8 @@ constexpr int kSelStep = 8;                    // scores per lane and step where
 constexpr int kSelBins = 2048;
 // Counters per bin of rows in registers.  Lanes that share a bin queue for it, the longer the row the longer: 28 heads, of two values
 // 44,000 scores 74 us with one, 38 with four; 36,000 of an estimate 17.9 and 17.6; of up to 16 per lane four cost 0.15 us per row more to
-// clear and add up.  (Eight lie in too few banks: 20.8.)  A row in memory has its LDS full of candidates.
+// clear and add up.  (Eight lie in too few banks: 20.8.)  A row that lists its own candidates (without a workspace) has its
+// LDS full of them.
 constexpr int sel_copies(int kpt) { return kpt > 16 ? 4 : 1; }
 // control block of a row whose slices go through the digits together, in 32-bit words
 constexpr int kSliceMax = 64;                  // slices of a row at most
