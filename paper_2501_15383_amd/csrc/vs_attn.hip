@@ -295,8 +295,8 @@ __device__ __forceinline__ void cut_segment(const AttnArgs& a, int x, int& list,
 // of a unit.  n follows the length, for up to four rounds of 512 pieces; most = 0 where the even cut is to stay: lists equally long
 // (so that with everything selected the results are those of dense calls), or a gain of less than 5 % by this count.
 // 28 heads, clustered slashes, even -> uneven: 200 rows at 500K keys 1,588 us -> 1,080, 333 at 100K 656 -> 518, 1,000 at 300K 2,584 ->
-// 1,958, 2,000 at 150K 2,811 -> 2,390; lists that differ by a tenth or less within 1 %.  Finding the ranges takes 2.5 to 4.5 us, also where
-// the even cut then stays or was as good: 1,000 rows of 8 heads at 200K keys 336 -> 338, the attention alone 95.8 -> 98.2, of 100 rows of 4
+// 1,958, 2,000 at 150K 2,811 -> 2,390; lists that differ by a tenth or less within 1 %.  Finding the ranges takes 5 us where
+// the even cut stays, up to 11 where it does not, and 2.5 to 4.5 of a call's time where that gains nothing: 1,000 rows of 8 heads at 200K keys 336 -> 338, the attention alone 95.8 -> 98.2, of 100 rows of 4
 // heads at 300K with offsets side by side 30.2 -> 34.5; against 275 -> 203 for 300 clustered rows of those at 900K, 300 -> 206 for 2,000
 // of 8 heads at 200K.  (A gain of four steps asked for on top of the 5 % keeps the even cut in these, too: equal distances hide from the
 // count that all entries lie in one range.)
@@ -1818,8 +1818,8 @@ static AttnCut attn_cut_as(const vs_params& p, bool dense, int forced) {
   if (c.n_split == 1) c.n_whole = c.n_units;
   c.queue = units <= slots || best < 0.97 * (double)ceil_div(units, slots) * (steps + kPieceSteps);
   if (!c.queue) { c.pack = 1; c.n_hs = group; c.n_split = 1; }
-  // Uneven ranges where pieces are long enough for a launch that finds them (5 us; a range of 64 blocks takes 120, less where lists are
-  // short); whole units below a round, which need the fold then as well, from 1,024 blocks on.  Not with one query tile: even ranges
+  // Uneven ranges where pieces are long enough for a launch that finds them (5 to 11 us; a range of 64 blocks takes 120, less where lists
+  // are short); whole units below a round, which need the fold then as well, from 1,024 blocks on.  Not with one query tile: even ranges
   // of the heads of a KV group lie at the same keys, which the XCD's L2 reads once for them (64 rows at 1M keys, lists that differ by 8 %:
   // 2,024 us, 2,101 uneven).  Nor where the even cut has several rounds: a slot takes the next piece when it is done, and the far
   // pieces, which come last, are the short ones (11,109 clustered rows at 500K keys 16.9 ms, 17.2 uneven).
