@@ -312,9 +312,9 @@ int sparse_attn(const vs_params* p, const void* q, const vs_dca* dca, const void
   }
   const BlockList bl = blocklist_layout(*p, false, ws);
   char* sync = (char*)ws + blocklist_bytes(*p, false);
-  hipError_t e = launch_build_blocklist(*p, s_idx, s_cnt, v_cnt, false, bl, sync, st);
+  hipError_t e = launch_build_blocklist(*p, s_idx, s_cnt, v_cnt, false, dca != nullptr, bl, sync, st);
   if (e != hipSuccess) return VS_ERR_HIP;
-  return hip_status(launch_attention(*p, q, dca ? &da : nullptr, k, v, v_idx, false, bl, out, lse, sync,
+  return hip_status(launch_attention(*p, q, dca ? &da : nullptr, k, v, {v_idx, v_cnt, s_idx, s_cnt}, false, bl, out, lse, sync,
                                      sync + attn_sync_bytes(*p), least, st));
 }
 
@@ -338,9 +338,9 @@ int dense_attn(const vs_params* p, const void* q, const vs_dca* dca, const void*
   }
   const BlockList bl = blocklist_layout(*p, true, ws);
   char* sync = (char*)ws + blocklist_bytes(*p, true);
-  hipError_t e = launch_build_blocklist(*p, nullptr, nullptr, nullptr, true, bl, sync, st);
+  hipError_t e = launch_build_blocklist(*p, nullptr, nullptr, nullptr, true, dca != nullptr, bl, sync, st);
   if (e != hipSuccess) return VS_ERR_HIP;
-  return hip_status(launch_attention(*p, q, dca ? &da : nullptr, k, v, nullptr, true, bl, out, lse, sync,
+  return hip_status(launch_attention(*p, q, dca ? &da : nullptr, k, v, {}, true, bl, out, lse, sync,
                                      sync + attn_sync_bytes(*p), least, st));
 }
 }  // namespace
@@ -479,7 +479,7 @@ int vs_count_tiles(const vs_params* p, const int32_t* v_idx, const int32_t* v_cn
   if (rc != VS_OK) return rc;
   const BlockList bl = blocklist_layout(*p, false, ws);
   hipStream_t st = (hipStream_t)stream;
-  hipError_t e = launch_build_blocklist(*p, s_idx, s_cnt, nullptr, false, bl, nullptr, st);
+  hipError_t e = launch_build_blocklist(*p, s_idx, s_cnt, nullptr, false, false, bl, nullptr, st);
   if (e != hipSuccess) return VS_ERR_HIP;
   return hip_status(launch_count_tiles(*p, v_idx, v_cnt, bl, tiles, st));
 }

@@ -406,6 +406,10 @@ __device__ __forceinline__ uint32_t lds_address(const void* p) {
   return (uint32_t)(size_t)(const __attribute__((address_space(3))) char*)p;
 }
 
+}  // namespace vs
+#include "vs_attn_short.h"
+namespace vs {
+
 constexpr int kHeadShift = 27;   // vertical tile of packed heads: (head << kHeadShift) | tile of 64 columns (a head has at most 2^25)
 // OWN: the cut units may have ranges by the lengths of their lists.  (Instantiations of their own: with this decided in the others, dense
 // calls of 20 to 500 rows took 0.15 to 0.5 us of 12 to 24 more.)
@@ -1760,6 +1764,7 @@ struct AttnCut {
   bool queue;
   int32_t pack, n_hs, n_qtiles, n_units, n_whole, n_split;
   int32_t own_slots;   // slots for ranges by the lists' lengths (own_cut; 0: even ranges only)
+  double steps;        // what it should take, in steps (automatic cuts)
   int64_t slots() const {
     const int64_t even = n_split > 1 ? (int64_t)(n_units - n_whole) * n_split : 0;
     return even > own_slots ? even : own_slots;
@@ -1809,7 +1814,7 @@ static AttnCut attn_cut_as(const vs_params& p, bool dense, int forced) {
                     (2 * pieces <= slots ? kAloneRate : 1.0) * (double)ceil_div(pieces, slots) * (steps / (double)n + kPieceSteps);
       if (n > 1) cost += 3.0 + kFoldSteps * (double)n + 8.0 * (double)pieces / (double)slots;
       if (best < 0 || cost < best) {
-        best = cost;
+        best = c.steps = cost;
         c.n_whole = (int32_t)whole;
         c.n_split = (int32_t)n;
       }
@@ -2136,7 +2141,7 @@ static hipError_t attn_device_setup(int* n_cu_out) {
     e = hipDeviceGetAttribute(&cu, hipDeviceAttributeMultiprocessorCount, dev);
     if (e != hipSuccess) return e;
     if (cu < 1) return hipErrorInvalidDevice;
-    const void* fns[14] = {reinterpret_cast<const void*>(&k_attention<128, NQB, false, false>),
+    const void* fns[18] = {reinterpret_cast<const void*>(&k_attention<128, NQB, false, false>),
                           reinterpret_cast<const void*>(&k_attention<64, NQB, false, false>),
                           reinterpret_cast<const void*>(&k_attention<128, NQB, true, false>),
                           reinterpret_cast<const void*>(&k_attention<64, NQB, true, false>),
@@ -2149,10 +2154,15 @@ static hipError_t attn_device_setup(int* n_cu_out) {
                           reinterpret_cast<const void*>(&k_attention_own<128, NQB, false>),
                           reinterpret_cast<const void*>(&k_attention_own<64, NQB, false>),
                           reinterpret_cast<const void*>(&k_attention_own<128, NQB, true>),
-                          reinterpret_cast<const void*>(&k_attention_own<64, NQB, true>)};
-    for (int i = 0; i < 14; ++i) {
+                          reinterpret_cast<const void*>(&k_attention_own<64, NQB, true>),
+                          reinterpret_cast<const void*>(&k_attn_short<128, false>),
+                          reinterpret_cast<const void*>(&k_attn_short<64, false>),
+                          reinterpret_cast<const void*>(&k_attn_short<128, true>),
+                          reinterpret_cast<const void*>(&k_attn_short<64, true>)};
+    for (int i = 0; i < 18; ++i) {
       e = hipFuncSetAttribute(fns[i], hipFuncAttributeMaxDynamicSharedMemorySize,
-                              i % 2 == 0 ? attn_lds_bytes<128>() : attn_lds_bytes<64>());
+                              i < 14 ? (i % 2 == 0 ? attn_lds_bytes<128>() : attn_lds_bytes<64>())
+                                     : (i % 2 == 0 ? short_lds_bytes<128>() : short_lds_bytes<64>()));
       if (e != hipSuccess) return e;
     }
     cu_of[dev] = cu;
@@ -2178,10 +2188,35 @@ static bool attn_listless(const vs_params& p, bool dense, const AttnCut& c, int 
          c.n_whole + (int64_t)(c.n_units - c.n_whole) * c.n_split <= 8 * (int64_t)members;
 }
 
+// Ranges per unit of a call that k_attn_short takes (0: it does not): at most one workgroup per compute unit, and where it takes less
+// time than the ranges of `c`, by two sums fitted (in us) to both kernels over 120 dense calls of 2 to 3,000 rows and 512 to 32,000 keys
+// (they are off by 2.7 and 5 % on average, 10 and 13 at most, those of attn_cut by 5 and 7; what they choose is 0.2 % behind the
+// faster one, at most 1 % slower than before, and on average 16 % faster for heads of 64 and 10 for 128).  With index sets there is a
+// launch less besides (4.5 us), which the choice leaves out, so that everything selected goes the way of dense calls.
+constexpr int64_t kShortOffsets = 16384;   // that a workgroup looks through: more are k_build_blocklist's
+static int attn_short(const vs_params& p, bool dense, bool dca, const AttnCut& c) {
+  const int64_t n_k = p.q_start + p.q_len, n_blk = ceil_div(n_k, kBlock);
+  if (dca || !c.queue || c.own_slots || attn_packed_decode(p, dense) || n_blk > kShortBlocks || c.n_qtiles >= kRun || c.n_units > 256) return 0;
+  if (g_key_split.load(std::memory_order_relaxed) != 0 || (c.n_split > 1 && c.n_whole > 0)) return 0;
+  if (!dense && c.pack * (p.slash_budget < n_k ? p.slash_budget : n_k) > kShortOffsets) return 0;
+  const bool wide = p.head_dim == 128;
+  double least = wide ? 1.6 + 1.28 * c.steps : 3.8 + 1.03 * c.steps;
+  int best = 0;
+  for (int n = 1; n <= c.n_split && n * c.n_units <= 256; ++n) {   // (no more ranges than before: the workspace is as large)
+    const int64_t range = ceil_div(n_blk + 1, n);
+    if (range > kShortRange) continue;
+    const double full = n * c.n_units / 256.0, steps = (double)ceil_div(range, kShortSets);
+    double cost = wide ? 5.5 + (1.06 + 0.82 * full) * steps + 3.2 * full : 4.2 + (1.15 + 0.14 * full) * steps + 2.5 * full;
+    if (n > 1) cost += wide ? 4.7 : 4.2 + 0.09 * n;
+    if (cost < least) { best = n; least = cost; }
+  }
+  return best;
+}
+
 // One list per head, or per tile of packed heads (one for all heads when dense); attn: for the attention launch with the
 // counters at sync_ws, which are cleared on the way (null: for k_count_tiles, which packs nothing and has none to clear).
 hipError_t launch_build_blocklist(const vs_params& p, const int32_t* s_idx, const int32_t* s_cnt,
-                                  const int32_t* v_cnt, bool dense, const BlockList& bl, void* sync_ws, hipStream_t st) {
+                                  const int32_t* v_cnt, bool dense, bool dca, const BlockList& bl, void* sync_ws, hipStream_t st) {
   const int64_t n_k = p.q_start + p.q_len;
   AttnCut c = {};
   if (sync_ws) {
@@ -2189,7 +2224,7 @@ hipError_t launch_build_blocklist(const vs_params& p, const int32_t* s_idx, cons
     int n_cu = 0;
     const hipError_t e = attn_device_setup(&n_cu);
     if (e != hipSuccess) return e;
-    if (attn_listless(p, dense, c, attn_members(n_cu))) return hipSuccess;
+    if (attn_short(p, dense, dca, c) || attn_listless(p, dense, c, attn_members(n_cu))) return hipSuccess;
   }
   ListArgs a = {};
   a.s_idx = s_idx; a.s_cnt = s_cnt; a.v_cnt = v_cnt; a.s_budget = p.slash_budget;
@@ -2211,7 +2246,7 @@ hipError_t launch_build_blocklist(const vs_params& p, const int32_t* s_idx, cons
 }
 
 hipError_t launch_attention(const vs_params& p, const void* q, const DcaArgs* dca, const void* k, const void* v,
-                            const int32_t* v_idx, bool dense,
+                            const IndexSets& sets, bool dense,
                             const BlockList& bl, void* out, float* lse, void* sync_ws, void* split_ws, bool least,
                             hipStream_t st) {
   constexpr int NQB = kAttnQBlocks;
@@ -2232,7 +2267,7 @@ hipError_t launch_attention(const vs_params& p, const void* q, const DcaArgs* dc
   a.bm_words = (int32_t)bl.words;
   a.ent_stride = dense ? 0 : bl.ent_stride;
   a.ent_len = bl.ent_stride;
-  a.v_idx = dense ? nullptr : v_idx;
+  a.v_idx = dense ? nullptr : sets.v_idx;
   a.v_budget = p.vertical_budget;
   a.n_q_heads = p.n_q_heads; a.n_kv_heads = p.n_kv_heads; a.group = p.n_q_heads / p.n_kv_heads;
   a.row_pad = (int32_t)(p.q_start % kBlock);
@@ -2299,7 +2334,36 @@ hipError_t launch_attention(const vs_params& p, const void* q, const DcaArgs* dc
     if (p.head_dim == 128) { if (dca) VS_ATTN_LAUNCH(128, true, false); else VS_ATTN_LAUNCH(128, false, false); }
     else { if (dca) VS_ATTN_LAUNCH(64, true, false); else VS_ATTN_LAUNCH(64, false, false); }
   };
+  const auto fold = [&]() {
+    const dim3 cgrid((unsigned)((int64_t)(a.n_units - a.n_whole) * (p.head_dim == 128 ? combine_parts<128>() : combine_parts<64>())));
+    const auto go = [&](auto&& kernel) { hipLaunchKernelGGL(kernel, cgrid, dim3(256), 0, st, a); };
+    if (a.own_slots) { if (p.head_dim == 128) go(k_attn_combine<128, false, true>); else go(k_attn_combine<64, false, true>); }
+    else { if (p.head_dim == 128) go(k_attn_combine<128>); else go(k_attn_combine<64>); }
+  };
   a.first_piece = 0;
+  if (const int ranges = attn_short(p, dense, dca != nullptr, cut)) {
+    a.n_split = ranges;
+    a.n_whole = ranges > 1 ? 0 : a.n_units;
+    ShortArgs b;
+    b.q = a.q; b.k = a.k; b.v = a.v; b.out = a.out; b.lse = lse; b.part_o = a.part_o; b.part_ml = a.part_ml;
+    b.q_stride_head = a.q_stride_head; b.k_stride_head = a.k_stride_head; b.v_stride_head = a.v_stride_head; b.o_stride_head = a.o_stride_head;
+    b.q_stride_tok = (int32_t)a.q_stride_tok; b.k_stride_tok = (int32_t)a.k_stride_tok;
+    b.v_stride_tok = (int32_t)a.v_stride_tok; b.o_stride_tok = (int32_t)a.o_stride_tok;
+    b.n_units = a.n_units; b.n_qtiles = a.n_qtiles; b.n_hs = a.n_hs; b.n_split = a.n_split;
+    b.n_pieces = a.n_units * a.n_split; b.each = (int32_t)ceil_div(b.n_pieces, 8);
+    b.by_units = short_magic((uint32_t)b.n_units); b.by_qtiles = short_magic((uint32_t)b.n_qtiles);
+    b.by_hs = short_magic((uint32_t)b.n_hs); b.by_split = short_magic((uint32_t)b.n_split);
+    b.pack = a.pack; b.group = a.group; b.row_pad = a.row_pad; b.q_rows = (int32_t)a.q_rows; b.m_first = (int32_t)(a.q_start / kBlock);
+    b.n_k = (int32_t)a.n_k; b.scale_log2 = a.scale_log2;
+    b.v_idx = sets.v_idx; b.v_cnt = sets.v_cnt; b.s_idx = sets.s_idx; b.s_cnt = sets.s_cnt;
+    b.v_budget = p.vertical_budget; b.s_budget = p.slash_budget;
+    const dim3 grid((unsigned)(8 * b.each));
+    const auto go = [&](auto&& kernel, int lds) { hipLaunchKernelGGL(kernel, grid, dim3(kShortThreads), lds, st, b); };
+    if (p.head_dim == 128) { if (dense) go(k_attn_short<128, false>, short_lds_bytes<128>()); else go(k_attn_short<128, true>, short_lds_bytes<128>()); }
+    else { if (dense) go(k_attn_short<64, false>, short_lds_bytes<64>()); else go(k_attn_short<64, true>, short_lds_bytes<64>()); }
+    if (a.n_split > 1) fold();
+    return hipGetLastError();
+  }
   if (!cut.queue) {
     keep_pace((int64_t)a.n_qtiles * a.n_q_heads);
     return hipGetLastError();
@@ -2335,12 +2399,7 @@ hipError_t launch_attention(const vs_params& p, const void* q, const DcaArgs* dc
     }
   }
 #undef VS_ATTN_LAUNCH
-  if (a.n_split > 1 || a.own_slots) {
-    const dim3 cgrid((unsigned)((int64_t)(a.n_units - a.n_whole) * (p.head_dim == 128 ? combine_parts<128>() : combine_parts<64>())));
-    const auto fold = [&](auto&& kernel) { hipLaunchKernelGGL(kernel, cgrid, dim3(256), 0, st, a); };
-    if (a.own_slots) { if (p.head_dim == 128) fold(k_attn_combine<128, false, true>); else fold(k_attn_combine<64, false, true>); }
-    else { if (p.head_dim == 128) fold(k_attn_combine<128>); else fold(k_attn_combine<64>); }
-  }
+  if (a.n_split > 1 || a.own_slots) fold();
   return hipGetLastError();
 }
 

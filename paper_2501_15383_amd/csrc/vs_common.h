@@ -136,7 +136,7 @@ static inline BlockList blocklist_layout(const vs_params& p, bool dense, void* w
 
 // ---- launchers (defined in the .hip files; all enqueue on `st`, return hipError_t) ------
 hipError_t launch_build_blocklist(const vs_params& p, const int32_t* s_idx, const int32_t* s_cnt,
-                                  const int32_t* v_cnt, bool dense, const BlockList& bl, void* sync_ws, hipStream_t st);
+                                  const int32_t* v_cnt, bool dense, bool dca, const BlockList& bl, void* sync_ws, hipStream_t st);
 // Dual Chunk Attention: the two other rotations of the chunk's queries (same strides as q),
 // chunk length and local window in tokens (multiples of 64)
 struct DcaArgs {
@@ -144,10 +144,16 @@ struct DcaArgs {
   const void* q_inter;
   int64_t chunk, window;
 };
+struct IndexSets {   // (nulls when dense)
+  const int32_t* v_idx;
+  const int32_t* v_cnt;
+  const int32_t* s_idx;
+  const int32_t* s_cnt;
+};
 // sync_ws: attn_sync_bytes(p) bytes: counters, cleared by launch_build_blocklist, and the schedule; split_ws:
 // attn_split_bytes(p) bytes (may be null when that is 0); dca may be null
 hipError_t launch_attention(const vs_params& p, const void* q, const DcaArgs* dca, const void* k, const void* v,
-                            const int32_t* v_idx, bool dense,
+                            const IndexSets& sets, bool dense,
                             const BlockList& bl, void* out, float* lse, void* sync_ws, void* split_ws, bool least,
                             hipStream_t st);
 // several requests in one launch (short chunks, decode steps): p.q_len = the longest request,
