@@ -37,6 +37,7 @@
 //    heads of a KV group share a tile where the rows leave half of it empty).  The plain kernel is
 //    its own instantiation, and so is the one whose ranges may follow the lists' lengths (k_attention_own).
 #include <atomic>
+#include <cstddef>
 #include <mutex>
 
 #include "vs_common.h"
@@ -413,10 +414,13 @@ namespace vs {
 constexpr int kHeadShift = 27;   // vertical tile of packed heads: (head << kHeadShift) | tile of 64 columns (a head has at most 2^25)
 // OWN: the cut units may have ranges by the lengths of their lists.  (Instantiations of their own: with this decided in the others, dense
 // calls of 20 to 500 rows took 0.15 to 0.5 us of 12 to 24 more.)
-template <int D, int NQB, bool DCA, bool SPLIT, bool BATCH, bool OWN>
-__device__ __forceinline__ void attention_body(const AttnArgs& a0) {
+// TAIL: behind a pace-keeping walk in the same kernel, whose workgroups end at different times: the first piece, too, is taken from a
+// queue.  args_at: where the arguments lie among the kernel's.
+template <int D, int NQB, bool DCA, bool SPLIT, bool BATCH, bool OWN, bool TAIL = false>
+__device__ __forceinline__ void attention_body(const AttnArgs& a0, const size_t args_at = 0) {
   static_assert(!BATCH || (SPLIT && !DCA), "several requests per launch ride on the key-split kernel");
   static_assert(!OWN || (SPLIT && !BATCH), "uneven ranges are those of cut units of a single call");
+  static_assert(!TAIL || SPLIT, "pieces");
   constexpr int DCH = D / 8;           // 16-byte chunks per row
   constexpr int DSTEPS = D / 16;       // MFMA k-steps of QK^T
   constexpr int DB = D / 32;           // 32-row blocks of O^T
@@ -447,8 +451,8 @@ __device__ __forceinline__ void attention_body(const AttnArgs& a0) {
 
   // The arguments, for what comes after the walk: read from memory there.  (Read through a0 they are loaded once, in front of the
   // rounds, and sit in vector registers' lanes during the walk: there are about a hundred scalar registers for twice as many values.)
-  auto late_args = []() -> const AttnArgs& {
-    uint64_t p = (uint64_t)__builtin_amdgcn_kernarg_segment_ptr();
+  auto late_args = [&]() -> const AttnArgs& {
+    uint64_t p = (uint64_t)__builtin_amdgcn_kernarg_segment_ptr() + args_at;
     asm volatile("" : "+s"(p));
     return *(const AttnArgs*)(const __attribute__((address_space(4))) AttnArgs*)p;
   };
@@ -475,18 +479,54 @@ __device__ __forceinline__ void attention_body(const AttnArgs& a0) {
     if (own > 0) n_pieces = a0.n_whole - a0.first_piece + own;
   }
   int q_grp = grp, q_pos = member;   // SPLIT: the queue and the place in it of the next piece
+  // the next piece, after the one at `own_next` (of thread 0) in the own queue was asked for; q_pos = -1: there is none
+  auto next_piece = [&](uint32_t own_next) {
+    const AttnArgs& z0 = late_args();
+    const int lead = TAIL ? 0 : z0.members;   // of a queue, that go to whom they lie at
+    int* const next_s = (int*)vidx_s;
+    if (tid < 64) {
+      int at = __builtin_amdgcn_readfirstlane((int)own_next), from = grp;
+      auto left_in = [&](int x) -> int {   // pieces of queue x: whole runs of `members`, and the run that the last piece ends in
+        const int runs = n_pieces / z0.members, tail = n_pieces - runs * z0.members;
+        return ((runs - x + 7) >> 3) * z0.members + ((runs & 7) == x ? tail : 0);
+      };
+      while (at >= left_in(from)) {
+        // the own queue is empty: the one with the most left.  A queue only ever grows emptier, so this ends
+        const int x = lane & 7;
+        const int seen = (int)__hip_atomic_load(&z0.queue[x * kQueueStride], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + lead;
+        int best = left_in(x) - seen > 0 ? ((left_in(x) - seen) << 3) | x : 0;
+#pragma unroll
+        for (int d = 1; d < 8; d <<= 1) { const int y = __shfl_xor(best, d); best = y > best ? y : best; }
+        best = __builtin_amdgcn_readfirstlane(best);
+        if (best == 0) { at = -1; break; }
+        from = best & 7;
+        uint32_t got = 0;
+        if (lane == 0) got = atomicAdd(&z0.queue[from * kQueueStride], 1u);
+        at = (int)__builtin_amdgcn_readfirstlane(got) + lead;
+      }
+      if (tid == 0) { next_s[0] = at; next_s[1] = from; }
+    }
+    __syncthreads();   // (also: the LDS tiles are reused by the next piece)
+    q_pos = __builtin_amdgcn_readfirstlane(next_s[0]);
+    q_grp = __builtin_amdgcn_readfirstlane(next_s[1]);
+    __syncthreads();   // the next piece writes column indices there
+  };
+  if constexpr (TAIL) {
+    next_piece(tid == 0 ? atomicAdd(&a0.queue[grp * kQueueStride], 1u) : 0u);
+    if (q_pos < 0) return;
+  }
   for (int rnd = 0; SPLIT || rnd < n_gr; ++rnd) {
   int gr = 0, u = 0;
   uint32_t q_next = 0;
   if constexpr (SPLIT) {
     u = ((q_pos / a0.members) * 8 + q_grp) * a0.members + q_pos % a0.members;
     // (pieces that the host cannot count: fewer than workgroups are dealt evenly over the XCDs, as launch_attention does)
-    if ((BATCH || OWN) && n_pieces < (int)gridDim.x) {
+    if (!TAIL && (BATCH || OWN) && n_pieces < (int)gridDim.x) {
       const int each = (n_pieces + 7) >> 3;
       u = member < each ? grp * each + member : n_pieces;
     }
     // the place after this one, requested now and read at the end of the piece
-    if (n_pieces > (int)gridDim.x && tid == 0) q_next = atomicAdd(&a0.queue[grp * kQueueStride], 1u) + (uint32_t)a0.members;
+    if (!TAIL && n_pieces > (int)gridDim.x && tid == 0) q_next = atomicAdd(&a0.queue[grp * kQueueStride], 1u) + (uint32_t)a0.members;
   } else {
     gr = __builtin_amdgcn_readfirstlane(a0.sched[grp * n_gr + rnd]);
     if (gr < 0) break;
@@ -1280,35 +1320,11 @@ __device__ __forceinline__ void attention_body(const AttnArgs& a0) {
   enter_segment(-1, false);  // (a tile whose walk ended early has marked nothing yet)
   }  // !none
   if constexpr (SPLIT) {
-    if (n_pieces <= (int)gridDim.x) break;
-    const AttnArgs& z0 = late_args();
-    int* const next_s = (int*)vidx_s;
-    if (tid < 64) {
-      int at = __builtin_amdgcn_readfirstlane((int)q_next), from = grp;
-      auto left_in = [&](int x) -> int {   // pieces of queue x: whole runs of `members`, and the run that the last piece ends in
-        const int runs = n_pieces / z0.members, tail = n_pieces - runs * z0.members;
-        return ((runs - x + 7) >> 3) * z0.members + ((runs & 7) == x ? tail : 0);
-      };
-      while (at >= left_in(from)) {
-        // the own queue is empty: the one with the most left.  A queue only ever grows emptier, so this ends
-        const int x = lane & 7;
-        const int seen = (int)__hip_atomic_load(&z0.queue[x * kQueueStride], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + z0.members;
-        int best = left_in(x) - seen > 0 ? ((left_in(x) - seen) << 3) | x : 0;
-#pragma unroll
-        for (int d = 1; d < 8; d <<= 1) { const int y = __shfl_xor(best, d); best = y > best ? y : best; }
-        best = __builtin_amdgcn_readfirstlane(best);
-        if (best == 0) { at = -1; break; }
-        from = best & 7;
-        uint32_t got = 0;
-        if (lane == 0) got = atomicAdd(&z0.queue[from * kQueueStride], 1u);
-        at = (int)__builtin_amdgcn_readfirstlane(got) + z0.members;
-      }
-      if (tid == 0) { next_s[0] = at; next_s[1] = from; }
+    if (!TAIL && n_pieces <= (int)gridDim.x) break;
+    if constexpr (TAIL) {   // (asked for now: a piece that waits for its workgroup is one that another could have)
+      if (tid == 0) q_next = atomicAdd(&late_args().queue[grp * kQueueStride], 1u);
     }
-    __syncthreads();   // (also: the LDS tiles are reused by the next piece)
-    q_pos = __builtin_amdgcn_readfirstlane(next_s[0]);
-    q_grp = __builtin_amdgcn_readfirstlane(next_s[1]);
-    __syncthreads();   // the next piece writes column indices there
+    next_piece(q_next);
     if (q_pos < 0) break;
   } else {
     __syncthreads();   // the LDS tiles are reused by the next round
@@ -1317,6 +1333,18 @@ __device__ __forceinline__ void attention_body(const AttnArgs& a0) {
 }
 template <int D, int NQB, bool DCA, bool SPLIT, bool BATCH = false>
 __global__ __launch_bounds__(128 * NQB, 2) void k_attention(const AttnArgs a) { attention_body<D, NQB, DCA, SPLIT, BATCH, false>(a); }
+// Whole units that keep pace, and then the pieces of the others, near ones (the longest) first: in one kernel, so that the workgroups
+// whose rounds end early take more of them.  In two launches, the second as long as its longest piece, 28 heads: 11,109 clustered rows at
+// 500K keys (lists between 920 and 2,120 blocks: rounds of a group 5 % above the mean) 17.3 ms, 15.9 so; 3,000 at 600K 7.4 and 5.6.
+struct PacedArgs {
+  AttnArgs whole, cut;
+};
+template <int D, int NQB, bool DCA>
+__global__ __launch_bounds__(128 * NQB, 2) void k_attention_paced(const PacedArgs a) {
+  attention_body<D, NQB, DCA, false, false, false>(a.whole);
+  __syncthreads();
+  attention_body<D, NQB, DCA, true, false, false, true>(a.cut, offsetof(PacedArgs, cut));
+}
 template <int D, int NQB, bool DCA>
 __global__ __launch_bounds__(128 * NQB, 2) void k_attention_own(const AttnArgs a) { attention_body<D, NQB, DCA, true, false, true>(a); }
 
@@ -1770,7 +1798,7 @@ struct AttnCut {
     return even > own_slots ? even : own_slots;
   }
 };
-static AttnCut attn_cut_as(const vs_params& p, bool dense, int forced) {
+static AttnCut attn_cut_as(const vs_params& p, bool dense, bool least, int forced) {
   const bool one = attn_packed_decode(p, dense);
   const int group = p.n_q_heads / p.n_kv_heads, row_pad = (int)(p.q_start % kBlock);
   const int64_t n_blk = ceil_div(p.q_start + p.q_len, kBlock);
@@ -1823,6 +1851,17 @@ static AttnCut attn_cut_as(const vs_params& p, bool dense, int forced) {
   if (c.n_split == 1) c.n_whole = c.n_units;
   c.queue = units <= slots || best < 0.97 * (double)ceil_div(units, slots) * (steps + kPieceSteps);
   if (!c.queue) { c.pack = 1; c.n_hs = group; c.n_split = 1; }
+  // Long walks: what whole rounds leave over is cut finely, and taken by workgroups as they are done with their rounds, which end as
+  // differently as the heads' lists are long (see k_attention_paced).  28 heads, 512, 1,024 and 2,048 pieces at most: 8,192 rows at 400K keys
+  // 35.2 ms, 34.5, 34.1, with DCA 36.6, 35.8, 35.3; 6,822 rows at 858K (2.95 rounds) 50.2 whole, 48.7.  Full rounds stay as they are: with
+  // the last of four cut, 32,768 clustered rows of 8 heads of 64 at 600K keys 1,551 us -> 1,666.
+  if (!least && c.pack == 1 && n_blk >= kPaceBlocks && units > slots && units % slots != 0) {
+    c.queue = true;
+    c.n_whole = (int32_t)full;
+    const int64_t n = kMaxPieces / (units - full);
+    c.n_split = (int32_t)(n < kMaxSplit ? n : kMaxSplit);
+    return c;
+  }
   // Uneven ranges where pieces are long enough for a launch that finds them (5 to 11 us; a range of 64 blocks takes 120, less where lists
   // are short); whole units below a round, which need the fold then as well, from 1,024 blocks on.  Not with one query tile: even ranges
   // of the heads of a KV group lie at the same keys, which the XCD's L2 reads once for them (64 rows at 1M keys, lists that differ by 8 %:
@@ -1841,10 +1880,10 @@ static AttnCut attn_cut_as(const vs_params& p, bool dense, int forced) {
   }
   return c;
 }
-// least: without uneven ranges, whose partial results are most of a short sparse call's workspace (28 heads of 128, 2,000 rows at 150,000
-// keys: 137 MB of it, 0.3 without)
+// least: without uneven and without the finest ranges, whose partial results are most of the workspace (28 heads of 128: 2,000 rows at
+// 150,000 keys 137 MB of it, 0.3 without; 8,192 rows at 400,000 keys 134 MB and 35)
 static AttnCut attn_cut(const vs_params& p, bool dense, bool least = false) {
-  AttnCut c = attn_cut_as(p, dense, g_key_split.load(std::memory_order_relaxed));
+  AttnCut c = attn_cut_as(p, dense, least, g_key_split.load(std::memory_order_relaxed));
   if (least && c.own_slots) {
     c.own_slots = 0;
     if (c.n_split == 1) c.n_whole = c.n_units;
@@ -2141,7 +2180,7 @@ static hipError_t attn_device_setup(int* n_cu_out) {
     e = hipDeviceGetAttribute(&cu, hipDeviceAttributeMultiprocessorCount, dev);
     if (e != hipSuccess) return e;
     if (cu < 1) return hipErrorInvalidDevice;
-    const void* fns[18] = {reinterpret_cast<const void*>(&k_attention<128, NQB, false, false>),
+    const void* fns[22] = {reinterpret_cast<const void*>(&k_attention<128, NQB, false, false>),
                           reinterpret_cast<const void*>(&k_attention<64, NQB, false, false>),
                           reinterpret_cast<const void*>(&k_attention<128, NQB, true, false>),
                           reinterpret_cast<const void*>(&k_attention<64, NQB, true, false>),
@@ -2155,13 +2194,17 @@ static hipError_t attn_device_setup(int* n_cu_out) {
                           reinterpret_cast<const void*>(&k_attention_own<64, NQB, false>),
                           reinterpret_cast<const void*>(&k_attention_own<128, NQB, true>),
                           reinterpret_cast<const void*>(&k_attention_own<64, NQB, true>),
+                          reinterpret_cast<const void*>(&k_attention_paced<128, NQB, false>),
+                          reinterpret_cast<const void*>(&k_attention_paced<64, NQB, false>),
+                          reinterpret_cast<const void*>(&k_attention_paced<128, NQB, true>),
+                          reinterpret_cast<const void*>(&k_attention_paced<64, NQB, true>),
                           reinterpret_cast<const void*>(&k_attn_short<128, false>),
                           reinterpret_cast<const void*>(&k_attn_short<64, false>),
                           reinterpret_cast<const void*>(&k_attn_short<128, true>),
                           reinterpret_cast<const void*>(&k_attn_short<64, true>)};
-    for (int i = 0; i < 18; ++i) {
+    for (int i = 0; i < 22; ++i) {
       e = hipFuncSetAttribute(fns[i], hipFuncAttributeMaxDynamicSharedMemorySize,
-                              i < 14 ? (i % 2 == 0 ? attn_lds_bytes<128>() : attn_lds_bytes<64>())
+                              i < 18 ? (i % 2 == 0 ? attn_lds_bytes<128>() : attn_lds_bytes<64>())
                                      : (i % 2 == 0 ? short_lds_bytes<128>() : short_lds_bytes<64>()));
       if (e != hipSuccess) return e;
     }
@@ -2178,7 +2221,7 @@ static int attn_members(int n_cu) {
 }
 // Whole units of a cut launch that keep pace, in a launch of their own (see launch_attention).
 static bool attn_paced(const AttnCut& c, int64_t n_k, int members) {
-  return c.queue && c.n_split > 1 && c.n_whole > 0 && c.pack == 1 && members == kRun && ceil_div(n_k, kBlock) >= kPaceBlocks;
+  return c.queue && c.n_split > 1 && c.n_whole > 0 && !c.own_slots && c.pack == 1 && members == kRun && ceil_div(n_k, kBlock) >= kPaceBlocks;
 }
 // Dense launches of no more pieces than workgroups need neither a list (every block is in it) nor cleared counters (nobody takes
 // a second piece): the list builder is not launched.  34 rows of 28 heads at 11,126 keys 34.5 us -> 31.3, the fold's share
@@ -2321,7 +2364,7 @@ hipError_t launch_attention(const vs_params& p, const void* q, const DcaArgs* dc
   a.sched = sched;
 #define VS_ATTN_LAUNCH(DD, DCA_, SPLIT_) \
   hipLaunchKernelGGL((k_attention<DD, NQB, DCA_, SPLIT_>), dim3((unsigned)a.n_wg), dim3(128 * NQB), attn_lds_bytes<DD>(), st, a)
-  // `units` whole units keeping pace
+  // `units` whole units keeping pace: the arguments and the schedule
   auto keep_pace = [&](int64_t units) {
     a.members = members;
     if (units < 8 * (int64_t)members) a.members = (int)ceil_div(units, 8);  // small launches: no idle workgroups
@@ -2331,8 +2374,6 @@ hipError_t launch_attention(const vs_params& p, const void* q, const DcaArgs* dc
     const int64_t rounds = (int64_t)a.n_full * a.n_q_heads + ceil_div((int64_t)a.n_rem * a.n_q_heads, a.members);
     a.n_gr = (int)(ceil_div(units, a.members) < rounds ? ceil_div(units, a.members) : rounds);
     hipLaunchKernelGGL(k_attn_schedule, dim3(1), dim3(1024), 0, st, a, sched, g_sched_in_turn.load(std::memory_order_relaxed));
-    if (p.head_dim == 128) { if (dca) VS_ATTN_LAUNCH(128, true, false); else VS_ATTN_LAUNCH(128, false, false); }
-    else { if (dca) VS_ATTN_LAUNCH(64, true, false); else VS_ATTN_LAUNCH(64, false, false); }
   };
   const auto fold = [&]() {
     const dim3 cgrid((unsigned)((int64_t)(a.n_units - a.n_whole) * (p.head_dim == 128 ? combine_parts<128>() : combine_parts<64>())));
@@ -2366,37 +2407,48 @@ hipError_t launch_attention(const vs_params& p, const void* q, const DcaArgs* dc
   }
   if (!cut.queue) {
     keep_pace((int64_t)a.n_qtiles * a.n_q_heads);
+    if (p.head_dim == 128) { if (dca) VS_ATTN_LAUNCH(128, true, false); else VS_ATTN_LAUNCH(128, false, false); }
+    else { if (dca) VS_ATTN_LAUNCH(64, true, false); else VS_ATTN_LAUNCH(64, false, false); }
     return hipGetLastError();
   }
-  // Long walks keep pace while they are whole, in a launch of their own (where the group of an XCD is as large as a run of
-  // units): 8,192 rows at 400K keys 35.9 ms against 37.3 in one launch, 9,500 clustered ones at 300K 12.8 against 14.0.
-  // Below 256K keys the caches hold what the members of a group are apart, and one launch fills its own gaps: 2,400 rows at
-  // 100K keys 3.44 ms against 3.52, 5,426 clustered ones at 33K 2.31 against 2.46.
+  // Long walks keep pace while they are whole (where the group of an XCD is as large as a run of units): 8,192 rows at 400K keys
+  // 35.9 ms against 37.3 without, 9,500 clustered ones at 300K 12.8 against 14.0 (with the pieces in a launch of their own behind them,
+  // 34.1 and 11.6 in the same).  Below 256K keys the caches hold what the members of a group are apart, and whole units come out of the
+  // queues, too: 2,400 rows at 100K keys 3.44 ms against 3.52, 5,426 clustered ones at 33K 2.31 against 2.46.
   // Not where heads share tiles: the pace-keeping kernel takes one head per unit, with one list per head.
   if (attn_paced(cut, a.n_k, members)) {
+    PacedArgs b;
     keep_pace(a.n_whole);
+    b.whole = a;
     a.first_piece = a.n_whole;
-  }
-  {
-    const int64_t pieces = a.n_whole - a.first_piece + (int64_t)(a.n_units - a.n_whole) * a.n_split;
-    a.members = pieces < 8 * (int64_t)members && !a.own_slots ? (int)ceil_div(pieces, 8) : members;
-    a.n_wg = 8 * a.members;
+    a.members = members;
     a.n_full = a.n_rem = a.n_gr = 0;
-    if (a.own_slots) {
-      hipLaunchKernelGGL(k_attn_pieces, dim3(1), dim3(1024), 0, st, a);
-      const dim3 grid((unsigned)a.n_wg), block(128 * NQB);
-      if (p.head_dim == 128) {
-        if (dca) hipLaunchKernelGGL((k_attention_own<128, NQB, true>), grid, block, attn_lds_bytes<128>(), st, a);
-        else hipLaunchKernelGGL((k_attention_own<128, NQB, false>), grid, block, attn_lds_bytes<128>(), st, a);
-      } else {
-        if (dca) hipLaunchKernelGGL((k_attention_own<64, NQB, true>), grid, block, attn_lds_bytes<64>(), st, a);
-        else hipLaunchKernelGGL((k_attention_own<64, NQB, false>), grid, block, attn_lds_bytes<64>(), st, a);
-      }
-    } else if (p.head_dim == 128) {
-      if (dca) VS_ATTN_LAUNCH(128, true, true); else VS_ATTN_LAUNCH(128, false, true);
+    b.cut = a;
+    const dim3 grid((unsigned)a.n_wg), block(128 * NQB);
+    const auto go = [&](auto&& kernel, int lds) { hipLaunchKernelGGL(kernel, grid, block, lds, st, b); };
+    if (p.head_dim == 128) { if (dca) go(k_attention_paced<128, NQB, true>, attn_lds_bytes<128>()); else go(k_attention_paced<128, NQB, false>, attn_lds_bytes<128>()); }
+    else { if (dca) go(k_attention_paced<64, NQB, true>, attn_lds_bytes<64>()); else go(k_attention_paced<64, NQB, false>, attn_lds_bytes<64>()); }
+    fold();
+    return hipGetLastError();
+  }
+  const int64_t pieces = a.n_whole + (int64_t)(a.n_units - a.n_whole) * a.n_split;
+  a.members = pieces < 8 * (int64_t)members && !a.own_slots ? (int)ceil_div(pieces, 8) : members;
+  a.n_wg = 8 * a.members;
+  a.n_full = a.n_rem = a.n_gr = 0;
+  if (a.own_slots) {
+    hipLaunchKernelGGL(k_attn_pieces, dim3(1), dim3(1024), 0, st, a);
+    const dim3 grid((unsigned)a.n_wg), block(128 * NQB);
+    if (p.head_dim == 128) {
+      if (dca) hipLaunchKernelGGL((k_attention_own<128, NQB, true>), grid, block, attn_lds_bytes<128>(), st, a);
+      else hipLaunchKernelGGL((k_attention_own<128, NQB, false>), grid, block, attn_lds_bytes<128>(), st, a);
     } else {
-      if (dca) VS_ATTN_LAUNCH(64, true, true); else VS_ATTN_LAUNCH(64, false, true);
+      if (dca) hipLaunchKernelGGL((k_attention_own<64, NQB, true>), grid, block, attn_lds_bytes<64>(), st, a);
+      else hipLaunchKernelGGL((k_attention_own<64, NQB, false>), grid, block, attn_lds_bytes<64>(), st, a);
     }
+  } else if (p.head_dim == 128) {
+    if (dca) VS_ATTN_LAUNCH(128, true, true); else VS_ATTN_LAUNCH(128, false, true);
+  } else {
+    if (dca) VS_ATTN_LAUNCH(64, true, true); else VS_ATTN_LAUNCH(64, false, true);
   }
 #undef VS_ATTN_LAUNCH
   if (a.n_split > 1 || a.own_slots) fold();
