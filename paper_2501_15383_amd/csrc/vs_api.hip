@@ -70,7 +70,7 @@ ChunkWs chunk_layout(const vs_params& p, bool least = false) {
   w.v_cnt = take(hq * sizeof(int32_t));
   w.s_cnt = take(hq * sizeof(int32_t));
   w.sub = off;
-  const size_t a = estimate_ws_bytes(p), b = select_ws_bytes(p), c = sparse_ws_bytes(p, false, least);
+  const size_t a = estimate_ws_bytes(p), b = select_ws_bytes(p, least), c = sparse_ws_bytes(p, false, least);
   off += a > b ? (a > c ? a : c) : (b > c ? b : c);
   w.total = off;
   return w;
@@ -89,7 +89,7 @@ size_t vs_workspace_bytes(const vs_params* p, int which) {
   if (check_params(p, which == VS_WS_SELECT || which == VS_WS_SPARSE || which == VS_WS_CHUNK || which == VS_WS_COUNT_TILES) != VS_OK) return 0;
   switch (which) {
     case VS_WS_ESTIMATE: return estimate_ws_bytes(*p);
-    case VS_WS_SELECT: return select_ws_bytes(*p);
+    case VS_WS_SELECT: return select_ws_bytes(*p, false);
     case VS_WS_SPARSE: return sparse_ws_bytes(*p, false);
     case VS_WS_DENSE: return sparse_ws_bytes(*p, true);
     case VS_WS_CHUNK: return chunk_layout(*p).total;
@@ -225,7 +225,7 @@ int vs_select(const vs_params* p, const float* vscore, const float* sscore, int3
   int rc = check_params(p, true);
   if (rc != VS_OK) return rc;
   if (!vscore || !sscore || !v_idx || !v_cnt || !s_idx || !s_cnt) return VS_ERR_INVALID_ARG;
-  rc = check_ws(ws, ws_bytes, select_ws_bytes(*p));
+  rc = check_ws(ws, ws_bytes, select_ws_bytes(*p, true));
   if (rc != VS_OK) return rc;
   return hip_status(launch_select(*p, vscore, sscore, nullptr, nullptr, v_idx, v_cnt, s_idx, s_cnt, ws,
                                   ws_bytes, (hipStream_t)stream));
@@ -252,7 +252,7 @@ int vs_select_heads(const vs_params* p, const float* vscore, const float* sscore
   if (rc != VS_OK) return rc;
   if (!vscore || !sscore || !v_budget_h || !s_budget_h || !v_idx || !v_cnt || !s_idx || !s_cnt)
     return VS_ERR_INVALID_ARG;
-  rc = check_ws(ws, ws_bytes, select_ws_bytes(*p));
+  rc = check_ws(ws, ws_bytes, select_ws_bytes(*p, true));
   if (rc != VS_OK) return rc;
   return hip_status(launch_select(*p, vscore, sscore, v_budget_h, s_budget_h, v_idx, v_cnt, s_idx, s_cnt, ws,
                                   ws_bytes, (hipStream_t)stream));

@@ -181,8 +181,9 @@ size_t estimate_ws_bytes(const vs_params& p);
 hipError_t launch_estimate(const vs_params& p, const void* q, const DcaArgs* dca, const void* k, float* vscore,
                            float* sscore, float* lse_lastq, void* ws, hipStream_t st);
 
-size_t select_ws_bytes(const vs_params& p);
-// ws with fewer than select_ws_bytes(p) bytes: another route (slower for long rows); 4,736 bytes per row at least
+// (least: the smallest workspace that a call takes)
+size_t select_ws_bytes(const vs_params& p, bool least);
+// ws with fewer bytes than that: another route (slower for long rows); 4,736 bytes per row at least
 hipError_t launch_select(const vs_params& p, const float* vscore, const float* sscore,
                          const int32_t* v_budget_h, const int32_t* s_budget_h,
                          int32_t* v_idx, int32_t* v_cnt, int32_t* s_idx, int32_t* s_cnt,

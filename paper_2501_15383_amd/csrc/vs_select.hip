@@ -12,7 +12,7 @@
 //   registers   rows of up to kSelRegKeys scores are read once and stay in registers; a call is then
 //               this one launch, bound by its vector instructions (of 32 scores per lane: loads and range 3.0 us, first
 //               digit 3, the pass that lists the threshold's bin 1.5, emission 2.5) and, of short rows, by its barriers
-//   candidates  longer rows are thinned out first.  A sample of 8,192 (16,384) scores per row gives a floor that
+//   candidates  longer rows are thinned out first.  A sample of 4,096 (8,192, 16,384) scores per row gives a floor that
 //               about k + 4.5 sigma entries exceed, and only those entries are kept, in registers (without a workspace: in LDS) if there
 //               are at most kSelCand of them.  With a workspace the whole chip makes the lists, in one pass over the scores
 //               (k_sel_sample, k_sel_filter; bound by that read at 1M keys); without a workspace k_sel_row makes its
@@ -714,6 +714,11 @@ __device__ __forceinline__ uint32_t sel_floor(SelShared<R>& sh, const SelRow& r,
   return T;   // (the floor may lie just below the sample of that rank: everything above it is a candidate)
 }
 
+template <int R>
+__device__ __forceinline__ uint32_t sel_floor(SelShared<R>& sh, const SelRow& r, int64_t n, int samples) {
+  return samples == 4 ? sel_floor<4>(sh, r, n) : samples == 8 ? sel_floor<8>(sh, r, n) : sel_floor<16>(sh, r, n);
+}
+
 // KPT: scores per thread of a row in registers; 0: a long row.
 template <int KPT>
 __global__ __launch_bounds__(kSelThreads) void k_sel_row(const SelArgs a) {
@@ -740,7 +745,7 @@ __global__ __launch_bounds__(kSelThreads) void k_sel_row(const SelArgs a) {
     if (listed) {
       hd = a.hdr[blockIdx.x];
     } else {
-      hd.floor_key = samples == 8 ? sel_floor<8>(sh, r, a.n) : sel_floor<16>(sh, r, a.n);
+      hd.floor_key = sel_floor(sh, r, a.n, samples);
       hd.count = hd.equal = 0;
       sel_walk_row(r, a.n, [&](const uint32_t (&key)[kSelStep], int32_t i0, int par) {
         uint32_t g = 0, q = 0;
@@ -804,7 +809,7 @@ __global__ __launch_bounds__(kSelThreads) void k_sel_sample(const SelArgs a) {
   const SelRow r = sel_row(a, blockIdx.x);
   SelHeader hd;
   hd.floor_key = ~0u;   // (all entries of the row are forced: no candidates)
-  if (r.kp > 0) hd.floor_key = (r.kind ? a.samples_s : a.samples_v) == 8 ? sel_floor<8>(sh, r, a.n) : sel_floor<16>(sh, r, a.n);
+  if (r.kp > 0) hd.floor_key = sel_floor(sh, r, a.n, r.kind ? a.samples_s : a.samples_v);
   hd.count = hd.equal = 0;
   hd.pad = 0;
   if (threadIdx.x == 0) a.hdr[blockIdx.x] = hd;
@@ -1089,9 +1094,14 @@ static int64_t sel_list_len(int64_t n, int32_t budget, int spt) {
   const int64_t len = (int64_t)((rank + 4.5f * sqrtf(rank)) * ((float)n / s)) + 64;
   return len < n ? len : n;
 }
-// Samples per thread: the smaller number whose list fits the LDS, else the larger one; 0: the rows stay in registers.
-static int sel_samples(int64_t n, int32_t budget) {
-  return n <= kSelRegKeys ? 0 : (sel_list_len(n, budget, 8) <= kSelCand ? 8 : 16);
+// Samples per thread: the smallest number whose list fits the registers, else the largest; 0: the rows stay in registers.  The samples
+// of a row lie in a cache line each, which one compute unit fetches (8,192 of them a megabyte): half as many and a list a sixth longer,
+// 28 heads, 300,001 scores 44.2 us -> 40.8, four heads 23.6 -> 21.8, 1M 36.0 -> 31.1; a quarter as many 44.3, 21.1, 30.9.
+// least: no fewer than eight, with which the list is shorter.
+static int sel_samples(int64_t n, int32_t budget, bool least) {
+  if (n <= kSelRegKeys) return 0;
+  if (!least && sel_list_len(n, budget, 4) <= kSelCand) return 4;
+  return sel_list_len(n, budget, 8) <= kSelCand ? 8 : 16;
 }
 // The longest list that is worth making.  The row's one workgroup takes about 1.45 us per 1,000 candidates, and the slices
 // read the scores seven times.  Measured over 1 to 64 heads, 50,000 to 4M keys and 8,000 to 106,000 candidates, with lists
@@ -1112,12 +1122,12 @@ struct SelLayout {
 static size_t sel_ctl_bytes(const vs_params& p) {
   return align_up((size_t)2 * p.n_q_heads * kSliceRowWords * sizeof(uint32_t), 256);
 }
-static SelLayout sel_layout(const vs_params& p) {
+static SelLayout sel_layout(const vs_params& p, bool least) {
   SelLayout l;
   const int64_t n = p.q_start + p.q_len;
   const size_t rows = 2 * (size_t)p.n_q_heads;
-  l.samples_v = sel_samples(n, p.vertical_budget);
-  l.samples_s = sel_samples(n, p.slash_budget);
+  l.samples_v = sel_samples(n, p.vertical_budget, least);
+  l.samples_s = sel_samples(n, p.slash_budget, least);
   l.n_slices = (int32_t)ceil_div(n, kSelSlice);
   const int64_t cv = sel_list_len(n, p.vertical_budget, l.samples_v), cs = sel_list_len(n, p.slash_budget, l.samples_s);
   l.cap = (uint32_t)(cv > cs ? cv : cs);
@@ -1127,7 +1137,7 @@ static SelLayout sel_layout(const vs_params& p) {
   l.total = n <= kSelRegKeys ? 256 : (l.sliced ? sel_ctl_bytes(p) : l.cand + align_up(rows * l.cap * sizeof(uint2), 256));
   return l;
 }
-size_t select_ws_bytes(const vs_params& p) { return sel_layout(p).total; }
+size_t select_ws_bytes(const vs_params& p, bool least) { return sel_layout(p, least).total; }
 
 static hipError_t launch_slices(SelArgs a, void* ws, hipStream_t st) {
   a.ctl = (uint32_t*)ws;
@@ -1144,7 +1154,7 @@ static hipError_t launch_slices(SelArgs a, void* ws, hipStream_t st) {
   return hipGetLastError();
 }
 
-// ws: ws_bytes bytes.  With fewer than select_ws_bytes(p), which only the static entry point has, every row lists its own
+// ws: ws_bytes bytes.  With fewer than select_ws_bytes(p, true), which only the static entry point has, every row lists its own
 // candidates where the list fits the LDS; longer lists' rows go in slices (56 rows of 1M keys, 20,000 of them to choose: 371 us,
 // row by row 989).
 hipError_t launch_select(const vs_params& p, const float* vscore, const float* sscore,
@@ -1158,7 +1168,8 @@ hipError_t launch_select(const vs_params& p, const float* vscore, const float* s
   a.keep_v = p.keep_first_cols; a.keep_s = p.keep_local_band;
   a.v_budget_h = v_budget_h; a.s_budget_h = s_budget_h;
   a.v_idx = v_idx; a.v_cnt = v_cnt; a.s_idx = s_idx; a.s_cnt = s_cnt;
-  const SelLayout l = sel_layout(p);
+  SelLayout l = sel_layout(p, false);
+  if (ws_bytes < l.total) l = sel_layout(p, true);
   a.n_slices = l.n_slices; a.samples_v = l.samples_v; a.samples_s = l.samples_s;
   const dim3 rows(2u * (unsigned)p.n_q_heads), block(kSelThreads);
   const auto in_registers = [&](auto&& kernel, int kpt) {
