@@ -11,7 +11,8 @@ CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libvs.so")
 SOURCES = ["vs_api.hip", "vs_attn.hip", "vs_decode.hip", "vs_estimate.hip", "vs_select.hip"]
-HEADERS = [os.path.join(CSRC, "vs_common.h"), os.path.join(CSRC, "vs_attn_short.h"), os.path.join(HERE, "..", "include", "vs.h")]
+HEADERS = [os.path.join(CSRC, "vs_common.h"), os.path.join(CSRC, "vs_attn_short.h"),
+           os.path.join(CSRC, "vs_decode_walk.h"), os.path.join(HERE, "..", "include", "vs.h")]
 
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",

@@ -462,11 +462,12 @@ int vs_attn_batch(const vs_params* p, const vs_request* requests, int32_t n_requ
   // single tokens by the decode kernel, the longer requests by the tile kernel (which skips the former), or all by the latter
   hipStream_t st = (hipStream_t)stream;
   const bool decode = batch_decodes(*p, n_requests);
-  if (decode) {
+  const bool together = decode && !least && p->q_len > 1;
+  if (decode && !together) {
     const hipError_t e = launch_decode(*p, nullptr, requests, n_requests, true, least, ws, st);
     if (e != hipSuccess || p->q_len == 1) return hip_status(e);
   }
-  return hip_status(launch_attention_batch(*p, requests, n_requests, decode, (char*)ws + decode_part(*p, n_requests, least), st));
+  return hip_status(launch_attention_batch(*p, requests, n_requests, decode, together ? ws : nullptr, (char*)ws + decode_part(*p, n_requests, least), st));
 }
 
 int vs_count_tiles(const vs_params* p, const int32_t* v_idx, const int32_t* v_cnt,

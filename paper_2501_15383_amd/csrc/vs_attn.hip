@@ -41,6 +41,7 @@
 #include <mutex>
 
 #include "vs_common.h"
+#include "vs_decode_walk.h"
 
 namespace vs {
 
@@ -1345,6 +1346,30 @@ __global__ __launch_bounds__(128 * NQB, 2) void k_attention_paced(const PacedArg
   __syncthreads();
   attention_body<D, NQB, DCA, true, false, false, true>(a.cut, offsetof(PacedArgs, cut));
 }
+// A batch of single tokens and longer requests.  Tokens wait for memory, tiles for the matrix cores, so they share the compute units: the
+// first workgroups, one on each (b and b + 256 lie on the same), walk the tokens, in half the LDS that k_decode takes, before they take
+// pieces; the others take pieces from the start.  Six launches (two for lists, two walks, two folds) become three.  8 requests of 1 to 64 rows and
+// 262,144 keys, dense and sparse, 1,210 us -> 1,130 (tokens by themselves 387, 424 in half the LDS; pieces 840); 22 dense ones of up to 64 rows and 38K keys,
+// 40 heads, 419 -> 391, 34 of up to 16 rows and 1,100 keys 102 -> 81, 5 sparse ones of 51K keys 474 -> 411, 30 of up to 64 rows and 60K
+// keys, 8 heads of 64, 131 -> 104.
+struct MixedArgs {
+  DecodeArgs tokens;
+  AttnArgs rows;
+};
+template <int D, int NQB>
+__global__ __launch_bounds__(128 * NQB, 2) void k_attention_mixed(const MixedArgs a) {
+  static_assert(kDecThreads == 128 * NQB && decode_lds_bytes<D>() / 2 <= attn_lds_bytes<D>(), "one launch serves both");
+  const int n_wg = a.tokens.shares < (int)gridDim.x ? a.tokens.shares : (int)gridDim.x;
+  if ((int)blockIdx.x < n_wg) {
+    int64_t mine;
+    bool uneven;
+    const int64_t T = decode_total<int4>(a.tokens, mine, uneven);
+    if (D == 128 && a.tokens.side == 2 && T >= kDecSideBlocks && !uneven) decode_body<D, D == 128 ? 2 : 1, false, int4, true>(a.tokens, T / 2, mine, n_wg);
+    else decode_body<D, 1, false, int4, true>(a.tokens, T, mine, n_wg);
+    __syncthreads();
+  }
+  attention_body<D, NQB, false, true, true, false, true>(a.rows, offsetof(MixedArgs, rows));
+}
 template <int D, int NQB, bool DCA>
 __global__ __launch_bounds__(128 * NQB, 2) void k_attention_own(const AttnArgs a) { attention_body<D, NQB, DCA, true, false, true>(a); }
 
@@ -1490,9 +1515,10 @@ __device__ void write_plan(const ListArgs& a, int64_t* scan) {
     a.plan[a.n_req].cut = (int32_t)(before >> 48);
   }
 }
-// List x0; false: nothing to be done for it or the ones behind it.
+// List x0; false: nothing to be done for it or the ones behind it.  flags: kBlFlags bytes of LDS.
+constexpr int kBlFlags = 16 + 4 * kBlWin + 16;
 template <int NQB, bool BATCH, bool WIDE>
-__device__ __forceinline__ bool build_list(const ListArgs& a, int x0) {
+__device__ __forceinline__ bool build_list(const ListArgs& a, int x0, uint8_t* flags) {
   constexpr int NW = kBlThreads / 64;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1570,7 +1596,6 @@ __device__ __forceinline__ bool build_list(const ListArgs& a, int x0) {
   // diagonals of four heads, or 16 of one, per lane (see kBlBallots).
   static_assert(NQB == 2, "an entry has the diagonals of two query blocks");
   static_assert(kBlWin % 64 == 0, "whole groups");
-  __shared__ __attribute__((aligned(16))) uint8_t flags[16 + 4 * kBlWin + 16];
   __shared__ uint32_t wsum[NW], missing_s;   // (a bit per head that lacks a diagonal)
   uint32_t running = 0, before = 0, missing = 0;
   if (tid == 0) missing_s = 0u;
@@ -1680,8 +1705,8 @@ __device__ __forceinline__ bool build_list(const ListArgs& a, int x0) {
   }
   return true;
 }
-template <int NQB, bool BATCH, bool WIDE = false>
-__global__ __launch_bounds__(kBlThreads) void k_build_blocklist(const ListArgs a) {
+template <int NQB, bool BATCH, bool WIDE>
+__device__ __forceinline__ void build_lists(const ListArgs& a, uint8_t* flags) {
   if (blockIdx.x == 0 && blockIdx.y == 0)
     for (int x = threadIdx.x; x < a.n_zero; x += kBlThreads) a.zero[x] = 0u;
   if constexpr (BATCH) {
@@ -1691,11 +1716,36 @@ __global__ __launch_bounds__(kBlThreads) void k_build_blocklist(const ListArgs a
       return;
     }
     for (int x0 = blockIdx.x; x0 < a.n_heads; x0 += gridDim.x) {
-      if (!build_list<NQB, true, WIDE>(a, x0)) return;   // (the same for all threads)
+      if (!build_list<NQB, true, WIDE>(a, x0, flags)) return;   // (the same for all threads)
       __syncthreads();   // its LDS is the next list's
     }
   } else {
-    build_list<NQB, false, WIDE>(a, blockIdx.x);
+    build_list<NQB, false, WIDE>(a, blockIdx.x, flags);
+  }
+}
+template <int NQB, bool BATCH, bool WIDE = false>
+__global__ __launch_bounds__(kBlThreads) void k_build_blocklist(const ListArgs a) {
+  __shared__ __attribute__((aligned(16))) uint8_t flags[kBlFlags];
+  build_lists<NQB, BATCH, WIDE>(a, flags);
+}
+// The lists of a batch (20 of 1,200 us when they came one after the other), and behind them, blockIdx.y from 1 + n_req on, those of its single tokens.
+struct MixedListArgs {
+  ListArgs rows;
+  DecodeArgs tokens;
+};
+template <int NQB>
+__global__ __launch_bounds__(kBlThreads) void k_mixed_lists(const MixedListArgs a) {
+  static_assert(kBlThreads == kDecListThreads, "one launch serves both");
+  constexpr int kTokenBytes = 64 << 10;
+  __shared__ __attribute__((aligned(16))) uint8_t flags[kBlFlags > kTokenBytes + 16 ? kBlFlags : kTokenBytes + 16];
+  const int r = (int)blockIdx.y - 1 - a.rows.n_req;
+  if (r < 0) {
+    build_lists<NQB, true, false>(a.rows, flags);
+    return;
+  }
+  for (int g = blockIdx.x; g < a.tokens.n_kv_heads; g += gridDim.x) {
+    decode_lists<int4, kTokenBytes>(a.tokens, g, r, flags);
+    __syncthreads();   // its LDS is the next list's
   }
 }
 
@@ -1849,13 +1899,14 @@ static AttnCut attn_cut_as(const vs_params& p, bool dense, bool least, int force
     }
   }
   if (c.n_split == 1) c.n_whole = c.n_units;
+  const bool packed = c.pack > 1;   // (units are then of several heads)
   c.queue = units <= slots || best < 0.97 * (double)ceil_div(units, slots) * (steps + kPieceSteps);
   if (!c.queue) { c.pack = 1; c.n_hs = group; c.n_split = 1; }
   // Long walks: what whole rounds leave over is cut finely, and taken by workgroups as they are done with their rounds, which end as
   // differently as the heads' lists are long (see k_attention_paced).  28 heads, 512, 1,024 and 2,048 pieces at most: 8,192 rows at 400K keys
   // 35.2 ms, 34.5, 34.1, with DCA 36.6, 35.8, 35.3; 6,822 rows at 858K (2.95 rounds) 50.2 whole, 48.7.  Full rounds stay as they are: with
   // the last of four cut, 32,768 clustered rows of 8 heads of 64 at 600K keys 1,551 us -> 1,666.
-  if (!least && c.pack == 1 && n_blk >= kPaceBlocks && units > slots && units % slots != 0) {
+  if (!least && !packed && n_blk >= kPaceBlocks && units > slots && units % slots != 0) {
     c.queue = true;
     c.n_whole = (int32_t)full;
     const int64_t n = kMaxPieces / (units - full);
@@ -1911,16 +1962,17 @@ size_t attn_sync_bytes(const vs_params& p) { return attn_counter_bytes(p) + attn
 template <int D>
 constexpr int combine_parts() { return kTileRows / (1024 / D); }   // per unit
 constexpr int kCombineGrid = 2048;   // workgroups for a batch at most
-template <int D, bool BATCH = false, bool OWN = false>
-__global__ __launch_bounds__(256) void k_attn_combine(const AttnArgs a0) {
+// n_wg: workgroups that share in it
+template <int D, bool BATCH, bool OWN>
+__device__ __forceinline__ void attn_fold(const AttnArgs& a0, const int n_wg) {
   constexpr int LR = D / 4;            // lanes per row
   constexpr int WPU = combine_parts<D>();
   __shared__ __attribute__((aligned(16))) float w_s[256 / LR][kMaxSplit];
   const int d = 4 * (threadIdx.x % LR);
   const int n_tasks = (BATCH ? __builtin_amdgcn_readfirstlane(a0.plan[a0.n_req].cut) : a0.n_units - a0.n_whole) * WPU;
   int run = 1;   // consecutive parts of a unit
-  while (BATCH && run < 4 && n_tasks > run * (int)gridDim.x) run *= 2;
-  for (int task = blockIdx.x * run; task < n_tasks; task += gridDim.x * run) {
+  while (BATCH && run < 4 && n_tasks > run * n_wg) run *= 2;
+  for (int task = blockIdx.x * run; task < n_tasks; task += n_wg * run) {
   int e = task / WPU;
   AttnArgs a = a0;
   if constexpr (BATCH) {
@@ -2010,6 +2062,18 @@ __global__ __launch_bounds__(256) void k_attn_combine(const AttnArgs a0) {
     a.lse[(int64_t)hw * a.q_rows + row] = L > 0.f ? (M + __builtin_amdgcn_logf(L)) * kLn2 : -INFINITY;
   }  // parts
   }  // tasks
+}
+template <int D, bool BATCH = false, bool OWN = false>
+__global__ __launch_bounds__(256) void k_attn_combine(const AttnArgs a) { attn_fold<D, BATCH, OWN>(a, gridDim.x); }
+// The folds of a batch, the first n_rows workgroups those of its longer requests, then one per request and head those of its tokens.
+template <int D>
+__global__ __launch_bounds__(256) void k_mixed_combine(const MixedArgs a, const int n_rows) {
+  if ((int)blockIdx.x < n_rows) {
+    attn_fold<D, true, false>(a.rows, n_rows);
+    return;
+  }
+  const int x = (int)blockIdx.x - n_rows, r = x / a.tokens.n_q_heads;
+  decode_fold<D, 4, D == 128 ? 0 : 1, int4>(a.tokens, x - r * a.tokens.n_q_heads, r);
 }
 
 // The pieces of an uneven cut (own_cut), one workgroup.  They lie in `most` slices, one after the other: in slice z those of the segments
@@ -2180,7 +2244,7 @@ static hipError_t attn_device_setup(int* n_cu_out) {
     e = hipDeviceGetAttribute(&cu, hipDeviceAttributeMultiprocessorCount, dev);
     if (e != hipSuccess) return e;
     if (cu < 1) return hipErrorInvalidDevice;
-    const void* fns[22] = {reinterpret_cast<const void*>(&k_attention<128, NQB, false, false>),
+    const void* fns[24] = {reinterpret_cast<const void*>(&k_attention<128, NQB, false, false>),
                           reinterpret_cast<const void*>(&k_attention<64, NQB, false, false>),
                           reinterpret_cast<const void*>(&k_attention<128, NQB, true, false>),
                           reinterpret_cast<const void*>(&k_attention<64, NQB, true, false>),
@@ -2198,13 +2262,15 @@ static hipError_t attn_device_setup(int* n_cu_out) {
                           reinterpret_cast<const void*>(&k_attention_paced<64, NQB, false>),
                           reinterpret_cast<const void*>(&k_attention_paced<128, NQB, true>),
                           reinterpret_cast<const void*>(&k_attention_paced<64, NQB, true>),
+                          reinterpret_cast<const void*>(&k_attention_mixed<128, NQB>),
+                          reinterpret_cast<const void*>(&k_attention_mixed<64, NQB>),
                           reinterpret_cast<const void*>(&k_attn_short<128, false>),
                           reinterpret_cast<const void*>(&k_attn_short<64, false>),
                           reinterpret_cast<const void*>(&k_attn_short<128, true>),
                           reinterpret_cast<const void*>(&k_attn_short<64, true>)};
-    for (int i = 0; i < 22; ++i) {
+    for (int i = 0; i < 24; ++i) {
       e = hipFuncSetAttribute(fns[i], hipFuncAttributeMaxDynamicSharedMemorySize,
-                              i < 18 ? (i % 2 == 0 ? attn_lds_bytes<128>() : attn_lds_bytes<64>())
+                              i < 20 ? (i % 2 == 0 ? attn_lds_bytes<128>() : attn_lds_bytes<64>())
                                      : (i % 2 == 0 ? short_lds_bytes<128>() : short_lds_bytes<64>()));
       if (e != hipSuccess) return e;
     }
@@ -2479,7 +2545,7 @@ size_t attn_batch_bytes(const vs_params& p, int n_req) {
          align_up(8 * kQueueStride * sizeof(uint32_t), 256) + plan_bytes(n_req);
 }
 
-hipError_t launch_attention_batch(const vs_params& p, const vs_request* req, int n_req, bool skip_single, void* ws,
+hipError_t launch_attention_batch(const vs_params& p, const vs_request* req, int n_req, bool skip_single, void* tokens_ws, void* ws,
                                   hipStream_t st) {
   constexpr int NQB = kAttnQBlocks;
   const int64_t n_k = p.q_start + p.q_len;
@@ -2527,18 +2593,34 @@ hipError_t launch_attention_batch(const vs_params& p, const vs_request* req, int
   // (a few workgroups per request where they fill the chip: 24,000 of 1,024 threads that find nothing to do, for 1,500 dense
   // requests of 16 heads, took 187 us, 48 so)
   const int each = (int)ceil_div(kListGroups, n_req);
-  hipLaunchKernelGGL((k_build_blocklist<NQB, true>), dim3((unsigned)(each < p.n_q_heads ? each : p.n_q_heads), (unsigned)n_req + 1),
-                     dim3(kBlThreads), 0, st, l);
+  const unsigned lists_x = (unsigned)(each < p.n_q_heads ? each : p.n_q_heads);
+  MixedArgs m;
+  if (tokens_ws) {
+    m.tokens = decode_args(p, req, n_req, tokens_ws);
+    m.rows = a;
+    hipLaunchKernelGGL((k_mixed_lists<NQB>), dim3(lists_x, 2 * (unsigned)n_req + 1), dim3(kBlThreads), 0, st, MixedListArgs{l, m.tokens});
+  } else {
+    hipLaunchKernelGGL((k_build_blocklist<NQB, true>), dim3(lists_x, (unsigned)n_req + 1), dim3(kBlThreads), 0, st, l);
+  }
   if ((e = hipGetLastError()) != hipSuccess) return e;   // (what follows goes by the plan and the lists)
   const dim3 grid((unsigned)a.n_wg), block(128 * NQB);
   const int64_t parts = ceil_div(pieces, 2) * (p.head_dim == 128 ? combine_parts<128>() : combine_parts<64>());   // cut units: two pieces or more
-  const dim3 cgrid((unsigned)(parts < kCombineGrid ? parts : kCombineGrid));
-  if (p.head_dim == 128) {
+  const unsigned folds = (unsigned)(parts < kCombineGrid ? parts : kCombineGrid);
+  if (tokens_ws) {
+    const dim3 cgrid(folds + (unsigned)n_req * (unsigned)p.n_q_heads);
+    if (p.head_dim == 128) {
+      hipLaunchKernelGGL((k_attention_mixed<128, NQB>), grid, block, attn_lds_bytes<128>(), st, m);
+      hipLaunchKernelGGL(k_mixed_combine<128>, cgrid, dim3(256), 0, st, m, (int)folds);
+    } else {
+      hipLaunchKernelGGL((k_attention_mixed<64, NQB>), grid, block, attn_lds_bytes<64>(), st, m);
+      hipLaunchKernelGGL(k_mixed_combine<64>, cgrid, dim3(256), 0, st, m, (int)folds);
+    }
+  } else if (p.head_dim == 128) {
     hipLaunchKernelGGL((k_attention<128, NQB, false, true, true>), grid, block, attn_lds_bytes<128>(), st, a);
-    hipLaunchKernelGGL((k_attn_combine<128, true>), cgrid, dim3(256), 0, st, a);
+    hipLaunchKernelGGL((k_attn_combine<128, true>), dim3(folds), dim3(256), 0, st, a);
   } else {
     hipLaunchKernelGGL((k_attention<64, NQB, false, true, true>), grid, block, attn_lds_bytes<64>(), st, a);
-    hipLaunchKernelGGL((k_attn_combine<64, true>), cgrid, dim3(256), 0, st, a);
+    hipLaunchKernelGGL((k_attn_combine<64, true>), dim3(folds), dim3(256), 0, st, a);
   }
   return hipGetLastError();
 }

@@ -159,8 +159,8 @@ hipError_t launch_attention(const vs_params& p, const void* q, const DcaArgs* dc
 // several requests in one launch (short chunks, decode steps): p.q_len = the longest request,
 // p.q_start + p.q_len = the most keys any request sees; req is a device array
 size_t attn_batch_bytes(const vs_params& p, int n_req);
-// (skip_single: single tokens are another kernel's)
-hipError_t launch_attention_batch(const vs_params& p, const vs_request* req, int n_req, bool skip_single, void* ws,
+// (skip_single: single tokens are the decode walk's; with tokens_ws, decode_bytes(p, n_req, true, true, false) of them, this launch has it)
+hipError_t launch_attention_batch(const vs_params& p, const vs_request* req, int n_req, bool skip_single, void* tokens_ws, void* ws,
                                   hipStream_t st);
 // single tokens, one request (`one`, by value; lists: it has index sets) or those of a table (req, device; lists = true)
 bool decode_fits(const vs_params& p);
