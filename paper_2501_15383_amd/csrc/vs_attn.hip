@@ -480,13 +480,17 @@ __device__ __forceinline__ void attention_body(const AttnArgs& a0, const size_t 
     if (own > 0) n_pieces = a0.n_whole - a0.first_piece + own;
   }
   int q_grp = grp, q_pos = member;   // SPLIT: the queue and the place in it of the next piece
-  // the next piece, after the one at `own_next` (of thread 0) in the own queue was asked for; q_pos = -1: there is none
-  auto next_piece = [&](uint32_t own_next) {
+  // The next piece; q_pos = -1: there is none.  It is asked for when the one before it is done: asked for at the start of that, to have the
+  // answer at hand, it waited for its workgroup where others had nothing left to do (28 heads: 5,084 rows at 45K keys 3,219 us, 2,998 so,
+  // 8,000 dense ones at 20K 1,914 and 1,758; 34 requests of up to 16 rows 100 and 81).
+  auto next_piece = [&]() {
     const AttnArgs& z0 = late_args();
     const int lead = TAIL ? 0 : z0.members;   // of a queue, that go to whom they lie at
     int* const next_s = (int*)vidx_s;
     if (tid < 64) {
-      int at = __builtin_amdgcn_readfirstlane((int)own_next), from = grp;
+      uint32_t first = 0;
+      if (lane == 0) first = atomicAdd(&z0.queue[grp * kQueueStride], 1u);
+      int at = (int)__builtin_amdgcn_readfirstlane(first) + lead, from = grp;
       auto left_in = [&](int x) -> int {   // pieces of queue x: whole runs of `members`, and the run that the last piece ends in
         const int runs = n_pieces / z0.members, tail = n_pieces - runs * z0.members;
         return ((runs - x + 7) >> 3) * z0.members + ((runs & 7) == x ? tail : 0);
@@ -513,12 +517,11 @@ __device__ __forceinline__ void attention_body(const AttnArgs& a0, const size_t 
     __syncthreads();   // the next piece writes column indices there
   };
   if constexpr (TAIL) {
-    next_piece(tid == 0 ? atomicAdd(&a0.queue[grp * kQueueStride], 1u) : 0u);
+    next_piece();
     if (q_pos < 0) return;
   }
   for (int rnd = 0; SPLIT || rnd < n_gr; ++rnd) {
   int gr = 0, u = 0;
-  uint32_t q_next = 0;
   if constexpr (SPLIT) {
     u = ((q_pos / a0.members) * 8 + q_grp) * a0.members + q_pos % a0.members;
     // (pieces that the host cannot count: fewer than workgroups are dealt evenly over the XCDs, as launch_attention does)
@@ -526,8 +529,6 @@ __device__ __forceinline__ void attention_body(const AttnArgs& a0, const size_t 
       const int each = (n_pieces + 7) >> 3;
       u = member < each ? grp * each + member : n_pieces;
     }
-    // the place after this one, requested now and read at the end of the piece
-    if (!TAIL && n_pieces > (int)gridDim.x && tid == 0) q_next = atomicAdd(&a0.queue[grp * kQueueStride], 1u) + (uint32_t)a0.members;
   } else {
     gr = __builtin_amdgcn_readfirstlane(a0.sched[grp * n_gr + rnd]);
     if (gr < 0) break;
@@ -1322,10 +1323,7 @@ __device__ __forceinline__ void attention_body(const AttnArgs& a0, const size_t 
   }  // !none
   if constexpr (SPLIT) {
     if (!TAIL && n_pieces <= (int)gridDim.x) break;
-    if constexpr (TAIL) {   // (asked for now: a piece that waits for its workgroup is one that another could have)
-      if (tid == 0) q_next = atomicAdd(&late_args().queue[grp * kQueueStride], 1u);
-    }
-    next_piece(q_next);
+    next_piece();
     if (q_pos < 0) break;
   } else {
     __syncthreads();   // the LDS tiles are reused by the next round
@@ -1902,14 +1900,20 @@ static AttnCut attn_cut_as(const vs_params& p, bool dense, bool least, int force
   const bool packed = c.pack > 1;   // (units are then of several heads)
   c.queue = units <= slots || best < 0.97 * (double)ceil_div(units, slots) * (steps + kPieceSteps);
   if (!c.queue) { c.pack = 1; c.n_hs = group; c.n_split = 1; }
-  // Long walks: what whole rounds leave over is cut finely, and taken by workgroups as they are done with their rounds, which end as
-  // differently as the heads' lists are long (see k_attention_paced).  28 heads, 512, 1,024 and 2,048 pieces at most: 8,192 rows at 400K keys
-  // 35.2 ms, 34.5, 34.1, with DCA 36.6, 35.8, 35.3; 6,822 rows at 858K (2.95 rounds) 50.2 whole, 48.7.  Full rounds stay as they are: with
-  // the last of four cut, 32,768 clustered rows of 8 heads of 64 at 600K keys 1,551 us -> 1,666.
-  if (!least && !packed && n_blk >= kPaceBlocks && units > slots && units % slots != 0) {
+  // What whole rounds leave over is cut finely, also where the count above would not: a workgroup takes the next piece when it is done
+  // with one, and whole units end as differently as lists are long and rows far from the first key.  Long walks, 28 heads, 512, 1,024 and
+  // 2,048 pieces at most: 8,192 rows at 400K keys 35.2 ms, 34.5, 34.1, with DCA 36.6, 35.8, 35.3; 6,822 rows at 858K (2.95 rounds) 50.2 whole,
+  // 48.7.  Shorter ones: 13,307 rows at 31K keys 4,850 us whole, 4,300; 4,096 clustered ones at 8,192 521 and 430; 3,128 of 40
+  // heads at 63K in a few ranges 4,116, 4,043.  Below 1,024 key blocks the ranges that the count makes are as good (40 calls: 2 % either way), and smaller.
+  // Full rounds stay as they are: with the last of four cut, 32,768 clustered rows of 8 heads of 64 at 600K keys 1,551 us -> 1,666.  And so
+  // do ranges of one round below kPaceBlocks, which with index sets go by the lists' lengths.
+  const bool one_round = c.n_split > 1 && (c.n_units - c.n_whole) * (int64_t)c.n_split <= slots && n_blk >= 64 * (int64_t)c.n_split;
+  if (!least && !packed && n_blk >= 64 && units > slots && units % slots != 0 &&
+      (c.n_split == 1 || n_blk >= kPaceBlocks || (n_blk >= 1024 && !one_round))) {
+    int64_t n = kMaxPieces / (units - full);
+    n = n < n_blk / 16 ? n : n_blk / 16;
     c.queue = true;
     c.n_whole = (int32_t)full;
-    const int64_t n = kMaxPieces / (units - full);
     c.n_split = (int32_t)(n < kMaxSplit ? n : kMaxSplit);
     return c;
   }
