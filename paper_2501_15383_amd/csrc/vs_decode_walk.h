@@ -46,9 +46,10 @@ struct DecodeArgs {
   // host knows them (one_T units, one_n shares; 0: the device finds them)
   int64_t* plan;
   int64_t one_T, one_n;
-  int32_t shares, side;   // most of them; KV heads side by side at most
   float* part_o;          // [share + (request, segment)][heads of a segment][D]
   float* part_ml;         // [share + (request, segment)][heads of a segment][2] (reference, sum)
+  // (behind what a short token waits for)
+  int32_t shares, side;   // most of them; KV heads side by side at most
 };
 
 __device__ __forceinline__ vs_request decode_request(const DecodeArgs& a, int r) {
