@@ -168,7 +168,7 @@ constexpr double kFoldSteps = 0.022;               // folding a row's piece, in 
 constexpr int kBatchSlots = 512, kShortSteps = 64;  // a batch of fewer steps per slot is cut into one piece per slot: 2 requests
                                                     // of 64 rows at 46K keys 134 us -> 107
 constexpr int kMaxPieces = 2048, kBatchPieces = 1536;   // pieces with partial results: a call's, a batch's
-constexpr int kMaxQueueUnits = 4096;               // beyond it whole rounds are full enough; ranges that are asked for are made
+constexpr int kMaxQueueUnits = 4096;               // beyond it only what whole rounds leave over is cut; ranges that are asked for are made
 constexpr int64_t kMaxAskedUnits = 1 << 23;        // all the same (128 M pieces of 33 KB and more: no workspace holds them)
 constexpr int kPaceBlocks = 4096;                  // key blocks from which whole units keep pace (see launch_attention)
 constexpr int kRun = 64;                           // workgroup slots of an XCD: members of a pace-keeping group
@@ -1857,6 +1857,34 @@ static AttnCut attn_cut_as(const vs_params& p, bool dense, bool least, int force
   const int64_t n_qtiles = ceil_div(one ? group : p.q_len + row_pad, (int64_t)kTileRows);
   const int64_t units = n_qtiles * p.n_kv_heads * c.n_hs;
   c.n_split = 1;
+  const int64_t slots = 512;
+  // What whole rounds leave over in up to kMaxPieces ranges, of full rounds the last one: a workgroup takes the next piece when it is done with
+  // one, and whole units end as differently as lists are long, rows far from the first key and XCDs fast (workgroups of full rounds
+  // ended 2 to 2.5 % before the last one on average).  32,768 rows, full rounds whole and so: 28 heads at 1M keys 225.9 ms and 221.4; 40 heads at
+  // 262,144 146.7 and 142.3; 16,384 rows of 28 at 16,384 dense 2,165 us and 1,766, clustered at 50K 7,562 and 7,046.  Heads of 64 keep full
+  // rounds that keep pace (8 heads, 32,768 clustered rows at 600K keys 1,486 us, 1,574 so; dense at 300K 21.8 ms and 21.6).  Full rounds of more
+  // than kMaxQueueUnits units stay whole below kPaceBlocks, where 136 MB of partial results would be as much as the caches, and
+  // come out of the queues: 28 heads at 65,536 dense 20.98 ms keeping pace, 20.33 so (19.57 with the last round cut), clustered 16.21 and 15.12.
+  const auto cut_rest = [&](int64_t rest) {
+    int64_t n = kMaxPieces / rest;
+    n = n < n_blk / 16 ? n : n_blk / 16;
+    c.queue = true;
+    c.n_qtiles = (int32_t)n_qtiles;
+    c.n_units = (int32_t)units;
+    c.n_whole = (int32_t)(units - rest);
+    c.n_split = (int32_t)(n < kMaxSplit ? n : kMaxSplit);
+  };
+  const bool fine = forced == 0 && !least && c.pack == 1 && n_blk >= 64 && units > slots && units < kMaxAskedUnits;
+  if (fine && (units > kMaxQueueUnits || (units % slots == 0 && (p.head_dim == 128 || n_blk < kPaceBlocks)))) {
+    if (units % slots != 0 || units <= kMaxQueueUnits || n_blk >= kPaceBlocks) {
+      cut_rest(units % slots ? units % slots : slots);
+    } else {
+      c.queue = true;
+      c.n_qtiles = (int32_t)n_qtiles;
+      c.n_units = c.n_whole = (int32_t)units;
+    }
+    return c;
+  }
   if (forced == 1 || units > (forced > 1 ? kMaxAskedUnits : kMaxQueueUnits)) return c;
   c.n_qtiles = (int32_t)n_qtiles;
   c.n_units = (int32_t)units;
@@ -1875,7 +1903,6 @@ static AttnCut attn_cut_as(const vs_params& p, bool dense, bool least, int force
   // steps where that is the least: short calls wait for their longest piece.  With eight at least, 12 rows of 28 heads at 956
   // keys 27.1 us -> 16.2 with two, 8 rows at 19,695 31.5 -> 28.5, 185 rows of 8 heads at 9,060 27.5 -> 25.1, 32 rows at 2,048 with
   // index sets 58.4 -> 52.3; over 100 calls of 2 to 3,000 rows below 60,000 keys 4.7 % less, the slowest 2.7 % more.
-  const int64_t slots = 512;
   double best = -1.0;
   // whole rounds kept: all, all but one, none
   const int64_t full = units / slots * slots, keep[3] = {full, full - slots, 0};
@@ -1897,24 +1924,16 @@ static AttnCut attn_cut_as(const vs_params& p, bool dense, bool least, int force
     }
   }
   if (c.n_split == 1) c.n_whole = c.n_units;
-  const bool packed = c.pack > 1;   // (units are then of several heads)
   c.queue = units <= slots || best < 0.97 * (double)ceil_div(units, slots) * (steps + kPieceSteps);
   if (!c.queue) { c.pack = 1; c.n_hs = group; c.n_split = 1; }
-  // What whole rounds leave over is cut finely, also where the count above would not: a workgroup takes the next piece when it is done
-  // with one, and whole units end as differently as lists are long and rows far from the first key.  Long walks, 28 heads, 512, 1,024 and
-  // 2,048 pieces at most: 8,192 rows at 400K keys 35.2 ms, 34.5, 34.1, with DCA 36.6, 35.8, 35.3; 6,822 rows at 858K (2.95 rounds) 50.2 whole,
-  // 48.7.  Shorter ones: 13,307 rows at 31K keys 4,850 us whole, 4,300; 4,096 clustered ones at 8,192 521 and 430; 3,128 of 40
-  // heads at 63K in a few ranges 4,116, 4,043.  Below 1,024 key blocks the ranges that the count makes are as good (40 calls: 2 % either way), and smaller.
-  // Full rounds stay as they are: with the last of four cut, 32,768 clustered rows of 8 heads of 64 at 600K keys 1,551 us -> 1,666.  And so
-  // do ranges of one round below kPaceBlocks, which with index sets go by the lists' lengths.
+  // Partial rounds, too, are cut finely where the count above would not.  Long walks, 28 heads, 512, 1,024 and 2,048 pieces at most: 8,192 rows
+  // at 400K keys 35.2 ms, 34.5, 34.1, with DCA 36.6, 35.8, 35.3; 6,822 rows at 858K (2.95 rounds) 50.2 whole, 48.7.  Shorter ones: 13,307 rows
+  // at 31K keys 4,850 us whole, 4,300; 4,096 clustered ones at 8,192 521 and 430; 3,128 of 40 heads at 63K in a few ranges 4,116, 4,043.
+  // Below 1,024 key blocks the ranges that the count makes are as good (40 calls: 2 % either way), and smaller; and ranges of one
+  // round below kPaceBlocks go, with index sets, by the lists' lengths.
   const bool one_round = c.n_split > 1 && (c.n_units - c.n_whole) * (int64_t)c.n_split <= slots && n_blk >= 64 * (int64_t)c.n_split;
-  if (!least && !packed && n_blk >= 64 && units > slots && units % slots != 0 &&
-      (c.n_split == 1 || n_blk >= kPaceBlocks || (n_blk >= 1024 && !one_round))) {
-    int64_t n = kMaxPieces / (units - full);
-    n = n < n_blk / 16 ? n : n_blk / 16;
-    c.queue = true;
-    c.n_whole = (int32_t)full;
-    c.n_split = (int32_t)(n < kMaxSplit ? n : kMaxSplit);
+  if (fine && units % slots != 0 && (c.n_split == 1 || n_blk >= kPaceBlocks || (n_blk >= 1024 && !one_round))) {
+    cut_rest(units % slots);
     return c;
   }
   // Uneven ranges where pieces are long enough for a launch that finds them (5 to 11 us; a range of 64 blocks takes 120, less where lists

@@ -10,10 +10,12 @@ pytestmark = pytest.mark.gpu
 
 
 # units beyond whole rounds of 512: 20 (many ranges each), 504 (a few), 8 of a second head size, rows that start inside a block; and, too
-# short to keep pace, 488
+# short to keep pace, 488; of full rounds the last, of more than 4,096 units what is over (64); 4,608 in full rounds, which stay whole
 @pytest.mark.parametrize("hq,hkv,d,c,n,dca", [(28, 4, 128, 2400, 264000, False), (28, 4, 128, 2432, 262144 + 2433, True),
                                               (8, 2, 64, 8320, 300001, False), (8, 1, 64, 8300, 264007, True), (127, 1, 64, 1000, 262200, False),
-                                              (8, 2, 64, 15950, 16384, False), (8, 2, 128, 15950, 16385, True)])
+                                              (8, 2, 64, 15950, 16384, False), (8, 2, 128, 15950, 16385, True),
+                                              (16, 2, 128, 8192, 8192, False), (16, 4, 64, 8192, 9024, True), (64, 1, 64, 8320, 8391, False),
+                                              (72, 1, 64, 8192, 8256, True)])
 def test_pieces_behind_whole_units(hq, hkv, d, c, n, dca):
     gen = torch.Generator(device="cuda").manual_seed(5200 + c)
     rnd = lambda *size: torch.randn(size, generator=gen, device="cuda").to(torch.bfloat16)  # noqa: E731
@@ -52,6 +54,9 @@ def test_pieces_behind_whole_units(hq, hkv, d, c, n, dca):
     again = call()
     torch.cuda.synchronize()
     assert torch.equal(got[0].view(torch.int16), again[0].view(torch.int16)) and torch.equal(got[1], again[1])
+    if full == uncut:   # (no pieces: the workspace is as small as it can be)
+        assert hq == 72
+        return
     # the smallest workspace that is taken (what a call needed when its pieces were fewer)
     lo, hi = uncut // 256 - 1, full // 256
     while hi - lo > 1:
