@@ -170,7 +170,7 @@ constexpr int kBatchSlots = 512, kShortSteps = 64;  // a batch of fewer steps pe
 constexpr int kMaxPieces = 2048, kBatchPieces = 1536;   // pieces with partial results: a call's, a batch's
 constexpr int kMaxQueueUnits = 4096;               // beyond it only what whole rounds leave over is cut; ranges that are asked for are made
 constexpr int64_t kMaxAskedUnits = 1 << 23;        // all the same (128 M pieces of 33 KB and more: no workspace holds them)
-constexpr int kPaceBlocks = 4096;                  // key blocks from which whole units keep pace (see launch_attention)
+constexpr int kPaceBlocks = 4096;                  // key blocks from which whole units of heads of 128 keep pace (see launch_attention)
 constexpr int kRun = 64;                           // workgroup slots of an XCD: members of a pace-keeping group
 constexpr int kQueueStride = 16;                   // words between two queue counters: a cache line each
 constexpr int kListBits = 28;                      // of a bitmap row's word that holds the length of the list (see build_list)
@@ -1858,13 +1858,13 @@ static AttnCut attn_cut_as(const vs_params& p, bool dense, bool least, int force
   const int64_t units = n_qtiles * p.n_kv_heads * c.n_hs;
   c.n_split = 1;
   const int64_t slots = 512;
+  const bool long_walk = p.head_dim == 128 && n_blk >= kPaceBlocks;   // whole units keep pace
   // What whole rounds leave over in up to kMaxPieces ranges, of full rounds the last one: a workgroup takes the next piece when it is done with
   // one, and whole units end as differently as lists are long, rows far from the first key and XCDs fast (workgroups of full rounds
   // ended 2 to 2.5 % before the last one on average).  32,768 rows, full rounds whole and so: 28 heads at 1M keys 225.9 ms and 221.4; 40 heads at
-  // 262,144 146.7 and 142.3; 16,384 rows of 28 at 16,384 dense 2,165 us and 1,766, clustered at 50K 7,562 and 7,046.  Heads of 64 keep full
-  // rounds that keep pace (8 heads, 32,768 clustered rows at 600K keys 1,486 us, 1,574 so; dense at 300K 21.8 ms and 21.6).  Full rounds of more
-  // than kMaxQueueUnits units stay whole below kPaceBlocks, where 136 MB of partial results would be as much as the caches, and
-  // come out of the queues: 28 heads at 65,536 dense 20.98 ms keeping pace, 20.33 so (19.57 with the last round cut), clustered 16.21 and 15.12.
+  // 262,144 146.7 and 142.3; 16,384 rows of 28 at 16,384 dense 2,165 us and 1,766, clustered at 50K 7,562 and 7,046.  Full rounds of more than
+  // kMaxQueueUnits units that do not keep pace stay whole, where 136 MB of partial results would be as much as the caches, and come out of
+  // the queues: 28 heads at 65,536 dense 20.98 ms keeping pace, 20.33 so (19.57 with the last round cut), clustered 16.21 and 15.12.
   const auto cut_rest = [&](int64_t rest) {
     int64_t n = kMaxPieces / rest;
     n = n < n_blk / 16 ? n : n_blk / 16;
@@ -1875,8 +1875,8 @@ static AttnCut attn_cut_as(const vs_params& p, bool dense, bool least, int force
     c.n_split = (int32_t)(n < kMaxSplit ? n : kMaxSplit);
   };
   const bool fine = forced == 0 && !least && c.pack == 1 && n_blk >= 64 && units > slots && units < kMaxAskedUnits;
-  if (fine && (units > kMaxQueueUnits || (units % slots == 0 && (p.head_dim == 128 || n_blk < kPaceBlocks)))) {
-    if (units % slots != 0 || units <= kMaxQueueUnits || n_blk >= kPaceBlocks) {
+  if (fine && (units > kMaxQueueUnits || units % slots == 0)) {
+    if (units % slots != 0 || units <= kMaxQueueUnits || long_walk) {
       cut_rest(units % slots ? units % slots : slots);
     } else {
       c.queue = true;
@@ -1930,9 +1930,9 @@ static AttnCut attn_cut_as(const vs_params& p, bool dense, bool least, int force
   // at 400K keys 35.2 ms, 34.5, 34.1, with DCA 36.6, 35.8, 35.3; 6,822 rows at 858K (2.95 rounds) 50.2 whole, 48.7.  Shorter ones: 13,307 rows
   // at 31K keys 4,850 us whole, 4,300; 4,096 clustered ones at 8,192 521 and 430; 3,128 of 40 heads at 63K in a few ranges 4,116, 4,043.
   // Below 1,024 key blocks the ranges that the count makes are as good (40 calls: 2 % either way), and smaller; and ranges of one
-  // round below kPaceBlocks go, with index sets, by the lists' lengths.
+  // round that do not keep pace go, with index sets, by the lists' lengths.
   const bool one_round = c.n_split > 1 && (c.n_units - c.n_whole) * (int64_t)c.n_split <= slots && n_blk >= 64 * (int64_t)c.n_split;
-  if (fine && units % slots != 0 && (c.n_split == 1 || n_blk >= kPaceBlocks || (n_blk >= 1024 && !one_round))) {
+  if (fine && units % slots != 0 && (c.n_split == 1 || long_walk || (n_blk >= 1024 && !one_round))) {
     cut_rest(units % slots);
     return c;
   }
@@ -2267,34 +2267,32 @@ static hipError_t attn_device_setup(int* n_cu_out) {
     e = hipDeviceGetAttribute(&cu, hipDeviceAttributeMultiprocessorCount, dev);
     if (e != hipSuccess) return e;
     if (cu < 1) return hipErrorInvalidDevice;
-    const void* fns[24] = {reinterpret_cast<const void*>(&k_attention<128, NQB, false, false>),
-                          reinterpret_cast<const void*>(&k_attention<64, NQB, false, false>),
-                          reinterpret_cast<const void*>(&k_attention<128, NQB, true, false>),
-                          reinterpret_cast<const void*>(&k_attention<64, NQB, true, false>),
-                          reinterpret_cast<const void*>(&k_attention<128, NQB, false, true>),
-                          reinterpret_cast<const void*>(&k_attention<64, NQB, false, true>),
-                          reinterpret_cast<const void*>(&k_attention<128, NQB, true, true>),
-                          reinterpret_cast<const void*>(&k_attention<64, NQB, true, true>),
-                          reinterpret_cast<const void*>(&k_attention<128, NQB, false, true, true>),
-                          reinterpret_cast<const void*>(&k_attention<64, NQB, false, true, true>),
-                          reinterpret_cast<const void*>(&k_attention_own<128, NQB, false>),
-                          reinterpret_cast<const void*>(&k_attention_own<64, NQB, false>),
-                          reinterpret_cast<const void*>(&k_attention_own<128, NQB, true>),
-                          reinterpret_cast<const void*>(&k_attention_own<64, NQB, true>),
-                          reinterpret_cast<const void*>(&k_attention_paced<128, NQB, false>),
-                          reinterpret_cast<const void*>(&k_attention_paced<64, NQB, false>),
-                          reinterpret_cast<const void*>(&k_attention_paced<128, NQB, true>),
-                          reinterpret_cast<const void*>(&k_attention_paced<64, NQB, true>),
-                          reinterpret_cast<const void*>(&k_attention_mixed<128, NQB>),
-                          reinterpret_cast<const void*>(&k_attention_mixed<64, NQB>),
-                          reinterpret_cast<const void*>(&k_attn_short<128, false>),
-                          reinterpret_cast<const void*>(&k_attn_short<64, false>),
-                          reinterpret_cast<const void*>(&k_attn_short<128, true>),
-                          reinterpret_cast<const void*>(&k_attn_short<64, true>)};
-    for (int i = 0; i < 24; ++i) {
-      e = hipFuncSetAttribute(fns[i], hipFuncAttributeMaxDynamicSharedMemorySize,
-                              i < 20 ? (i % 2 == 0 ? attn_lds_bytes<128>() : attn_lds_bytes<64>())
-                                     : (i % 2 == 0 ? short_lds_bytes<128>() : short_lds_bytes<64>()));
+    constexpr int lds128 = attn_lds_bytes<128>(), lds64 = attn_lds_bytes<64>();
+    const struct { const void* kernel; int lds; } fns[] = {
+        {reinterpret_cast<const void*>(&k_attention<128, NQB, false, false>), lds128},
+        {reinterpret_cast<const void*>(&k_attention<64, NQB, false, false>), lds64},
+        {reinterpret_cast<const void*>(&k_attention<128, NQB, true, false>), lds128},
+        {reinterpret_cast<const void*>(&k_attention<64, NQB, true, false>), lds64},
+        {reinterpret_cast<const void*>(&k_attention<128, NQB, false, true>), lds128},
+        {reinterpret_cast<const void*>(&k_attention<64, NQB, false, true>), lds64},
+        {reinterpret_cast<const void*>(&k_attention<128, NQB, true, true>), lds128},
+        {reinterpret_cast<const void*>(&k_attention<64, NQB, true, true>), lds64},
+        {reinterpret_cast<const void*>(&k_attention<128, NQB, false, true, true>), lds128},
+        {reinterpret_cast<const void*>(&k_attention<64, NQB, false, true, true>), lds64},
+        {reinterpret_cast<const void*>(&k_attention_own<128, NQB, false>), lds128},
+        {reinterpret_cast<const void*>(&k_attention_own<64, NQB, false>), lds64},
+        {reinterpret_cast<const void*>(&k_attention_own<128, NQB, true>), lds128},
+        {reinterpret_cast<const void*>(&k_attention_own<64, NQB, true>), lds64},
+        {reinterpret_cast<const void*>(&k_attention_paced<128, NQB, false>), lds128},
+        {reinterpret_cast<const void*>(&k_attention_paced<128, NQB, true>), lds128},
+        {reinterpret_cast<const void*>(&k_attention_mixed<128, NQB>), lds128},
+        {reinterpret_cast<const void*>(&k_attention_mixed<64, NQB>), lds64},
+        {reinterpret_cast<const void*>(&k_attn_short<128, false>), short_lds_bytes<128>()},
+        {reinterpret_cast<const void*>(&k_attn_short<64, false>), short_lds_bytes<64>()},
+        {reinterpret_cast<const void*>(&k_attn_short<128, true>), short_lds_bytes<128>()},
+        {reinterpret_cast<const void*>(&k_attn_short<64, true>), short_lds_bytes<64>()}};
+    for (const auto& f : fns) {
+      e = hipFuncSetAttribute(f.kernel, hipFuncAttributeMaxDynamicSharedMemorySize, f.lds);
       if (e != hipSuccess) return e;
     }
     cu_of[dev] = cu;
@@ -2309,14 +2307,15 @@ static int attn_members(int n_cu) {
   return members < 1 ? 1 : members;
 }
 // Whole units of a cut launch that keep pace, in a launch of their own (see launch_attention).
-static bool attn_paced(const AttnCut& c, int64_t n_k, int members) {
-  return c.queue && c.n_split > 1 && c.n_whole > 0 && !c.own_slots && c.pack == 1 && members == kRun && ceil_div(n_k, kBlock) >= kPaceBlocks;
+static bool attn_paced(const AttnCut& c, const vs_params& p, int members) {
+  return c.queue && c.n_split > 1 && c.n_whole > 0 && !c.own_slots && c.pack == 1 && members == kRun && p.head_dim == 128 &&
+         ceil_div(p.q_start + p.q_len, kBlock) >= kPaceBlocks;
 }
 // Dense launches of no more pieces than workgroups need neither a list (every block is in it) nor cleared counters (nobody takes
 // a second piece): the list builder is not launched.  34 rows of 28 heads at 11,126 keys 34.5 us -> 31.3, the fold's share
 // of it included; rows of 2 to 391 at 600 to 50,000 keys gain 2 to 11 %.
 static bool attn_listless(const vs_params& p, bool dense, const AttnCut& c, int members) {
-  return dense && c.queue && !attn_paced(c, p.q_start + p.q_len, members) &&
+  return dense && c.queue && !attn_paced(c, p, members) &&
          c.n_whole + (int64_t)(c.n_units - c.n_whole) * c.n_split <= 8 * (int64_t)members;
 }
 
@@ -2504,8 +2503,10 @@ hipError_t launch_attention(const vs_params& p, const void* q, const DcaArgs* dc
   // 35.9 ms against 37.3 without, 9,500 clustered ones at 300K 12.8 against 14.0 (with the pieces in a launch of their own behind them,
   // 34.1 and 11.6 in the same).  Below 256K keys the caches hold what the members of a group are apart, and whole units come out of the
   // queues, too: 2,400 rows at 100K keys 3.44 ms against 3.52, 5,426 clustered ones at 33K 2.31 against 2.46.
+  // Nor heads of 64, whose blocks are half as large: 8 heads, 19,083 rows at 300K keys 3,953 us keeping pace, 3,719 without, 15,000 clustered ones at
+  // 500K 812 and 765, at 1M 1,175 and 1,111; 4 heads, 30,000 clustered rows at 700K 480 and 463; of 17 calls the most that was lost is 873 and 888.
   // Not where heads share tiles: the pace-keeping kernel takes one head per unit, with one list per head.
-  if (attn_paced(cut, a.n_k, members)) {
+  if (attn_paced(cut, p, members)) {
     PacedArgs b;
     keep_pace(a.n_whole);
     b.whole = a;
@@ -2514,9 +2515,8 @@ hipError_t launch_attention(const vs_params& p, const void* q, const DcaArgs* dc
     a.n_full = a.n_rem = a.n_gr = 0;
     b.cut = a;
     const dim3 grid((unsigned)a.n_wg), block(128 * NQB);
-    const auto go = [&](auto&& kernel, int lds) { hipLaunchKernelGGL(kernel, grid, block, lds, st, b); };
-    if (p.head_dim == 128) { if (dca) go(k_attention_paced<128, NQB, true>, attn_lds_bytes<128>()); else go(k_attention_paced<128, NQB, false>, attn_lds_bytes<128>()); }
-    else { if (dca) go(k_attention_paced<64, NQB, true>, attn_lds_bytes<64>()); else go(k_attention_paced<64, NQB, false>, attn_lds_bytes<64>()); }
+    if (dca) hipLaunchKernelGGL((k_attention_paced<128, NQB, true>), grid, block, attn_lds_bytes<128>(), st, b);
+    else hipLaunchKernelGGL((k_attention_paced<128, NQB, false>), grid, block, attn_lds_bytes<128>(), st, b);
     fold();
     return hipGetLastError();
   }
