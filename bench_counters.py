@@ -22,8 +22,9 @@ Right before a run `python3 bench_counters.py --stamp PROF/<run>` notes in its f
 (the folder must be new).  Summaries are written only from runs of the present sources, one result file each: what an older
 run left in the folder would be taken for this one's.
 
-In every run the launches of k_attention<128, 2, false, false, false> come in this order: the sparse
-launch(es) of the timed steps, three dense launches, four launches of the gather probe.
+In every run the launches of k_attention_paced<128, 2, false> come in this order: the sparse
+launch(es) of the timed steps, three dense launches, four launches of the gather probe.  Each is followed by the fold of
+the partial results, k_attn_combine, which the figures of the attention kernel leave out.
 
 Bytes fetched over the fabric are counted directly, 32 n32 + 64 n64 + 128 n128 with n64 the
 requests that are neither 32 nor 128 bytes long (the FETCH_SIZE expression of rocprofv3 counts a
@@ -44,7 +45,7 @@ import os
 import sys
 
 ROOT = os.path.dirname(os.path.abspath(__file__))
-ATT = "k_attention<128, 2, false, false, false>"
+ATT = "k_attention_paced<128, 2, false>"
 
 
 NOMINAL_GHZ = 2.4
@@ -214,7 +215,7 @@ def main():
             f"k_attention, dense launches (every block diagonal):              n={len(de)} avg {sum(de) / len(de):.3f} ms",
             f"k_attention, gather probe (forced band + the vertical set):      n={len(ga)} avg {sum(ga) / len(ga):.3f} ms",
             f"bench.py line of the same run: sparse_attention {d['phases_ms']['sparse_attention']:.3f} ms (events; block list + "
-            f"schedule + counter fill + k_attention), estimate {d['phases_ms']['estimate']:.3f} ms, select "
+            f"schedule + counter fill + k_attention + fold), estimate {d['phases_ms']['estimate']:.3f} ms, select "
             f"{d['phases_ms']['select']:.3f} ms, dense {d['dense_ms']:.3f} ms",
             f"issued 64x64 tiles: slash {d['tiles']['slash']}, vertical {d['tiles']['vertical']} (dense equivalent "
             f"{d['tiles']['dense_equivalent']}); effective {d['effective_tflops']:.1f} TFLOP/s = {d['pct_bf16_mfma_peak']:.1f}% of "
@@ -239,7 +240,7 @@ def main():
             f"  k_attention dense launch    read {dense_rd / 1e9:9.2f} GB",
             f"  k_attention gather probe    read {gather_rd / 1e9:9.2f} GB   written {gather_wr / 1e9:7.3f} GB"]
     for nm in ("k_est_sums<128, false>", "k_est_scores<128, false>", "k_estimate_combine", "k_sel_sample", "k_sel_filter",
-               "k_sel_row<0>", "k_build_blocklist", "k_attn_schedule"):
+               "k_sel_row<0>", "k_build_blocklist", "k_attn_schedule", "k_attn_combine"):
         r_, w_ = pick(rd, nm), pick(wr, nm)
         out.append(f"  {nm:27s} read {(rd_bytes(r_[0]) if r_ else 0) / 1e9:9.3f} GB   written "
                    f"{(w_[0]['WRITE_SIZE'] * 1024 if w_ else 0) / 1e9:7.3f} GB")

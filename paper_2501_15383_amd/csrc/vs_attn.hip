@@ -27,15 +27,19 @@
 //    stream with the exponentials, operands three LDS reads ahead.
 //  * the tile walk reads a per-head list of (key block, query-block mask) entries through
 //    a 64-entry lane cache and lives entirely in scalar registers.
-//  * persistent launch: two workgroups per compute unit in eight groups (one per XCD); a group
-//    works on consecutive query tiles of one head per round and keeps its members within a
-//    few sync segments of keys, so that K/V blocks are shared through the L2.  Which group
-//    takes which round is decided on the device from the lengths of the block lists.
+//  * persistent launch: two workgroups per compute unit in eight groups (one per XCD).  Where keys
+//    are many (heads of 128 from 256K keys on) a group works on consecutive query tiles of one
+//    head per round and keeps its members within a few sync segments of keys, so that K/V blocks
+//    are shared through the L2.  Which group takes which round is decided on the device from the
+//    lengths of the block lists.  Elsewhere the pieces of the launch wait in one queue per XCD.
 //  * template parameters: DCA (three rotations of the queries, chosen per (query, key)
 //    pattern; section 5.1) and SPLIT (short chunks, and what whole rounds leave of longer ones:
 //    the key walk cut into pieces that wait in queues, partial results folded by k_attn_combine;
 //    heads of a KV group share a tile where the rows leave half of it empty).  The plain kernel is
 //    its own instantiation, and so is the one whose ranges may follow the lists' lengths (k_attention_own).
+//    k_attention_paced keeps pace over the whole units and goes on with the pieces of the rest in the
+//    same launch; k_attention_mixed walks a batch's longer requests beside its single tokens.
+//  * calls of one round whose pieces walk few key blocks have a kernel of their own (vs_attn_short.h).
 #include <atomic>
 #include <cstddef>
 #include <mutex>
@@ -1831,11 +1835,12 @@ void set_attn_key_split(int n) { g_key_split.store(n < 0 ? 0 : (n > 16 ? 16 : n)
 bool attn_packed_decode(const vs_params& p, bool dense) {
   return dense && p.q_len == 1 && p.n_q_heads > p.n_kv_heads && p.n_q_heads / p.n_kv_heads <= 64 * kAttnQBlocks;
 }
-// How a launch is cut: queue false = the pace-keeping kernel, one workgroup per whole unit.  Units rarely fill whole rounds
+// How a launch is cut: queue false = the pace-keeping kernel, every unit whole (where that is asked for, and of few key blocks); else
+// pieces in queues, before which attn_paced lets whole units keep pace.  Units rarely fill whole rounds
 // of the 512 slots: what is left over is cut so finely that it takes a fraction of a round (28 heads; before, at most 16
 // ranges and only below 256 units): 5,084 rows at 45K keys, 2.2 rounds, 4.06 -> 3.13 ms; 850 rows at 758K, 0.4 rounds in two
-// ranges, 10.5 -> 8.9; 8,192 rows at 400K, 3.5 rounds, 39.5 -> 35.9; 2,400 rows at 100K 4.94 -> 3.13.  A gain of less than 3 %
-// by the count below is left: full rounds keep pace, which is worth a few per cent at long contexts (launch_attention).
+// ranges, 10.5 -> 8.9; 8,192 rows at 400K, 3.5 rounds, 39.5 -> 35.9; 2,400 rows at 100K 4.94 -> 3.13.  The count of rounds below
+// finds the ranges of launches below a round and of short walks; the rest of longer ones is cut as finely as partial results allow.
 struct AttnCut {
   bool queue;
   int32_t pack, n_hs, n_qtiles, n_units, n_whole, n_split;

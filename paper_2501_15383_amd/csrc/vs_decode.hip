@@ -7,7 +7,8 @@
 //    K and V are read once per group.  A wave works alone on 32 keys at a time: it copies the rows global -> LDS into
 //    its own two buffers (the next 32 keys are on their way while these are multiplied), waits for its own copies
 //    only, and there is no barrier until the waves of the workgroup fold their results.  One workgroup of four waves
-//    fills the LDS of a compute unit: 64 to 128 KB of copies in flight.
+//    fills the LDS of a compute unit: 64 to 128 KB of copies in flight.  (Beside the tiles of longer requests, in
+//    k_attention_mixed of vs_attn.hip, a wave has one buffer, for keys and values in turn, and a workgroup 64 KB.)
 //  * Where there is much to read the waves take two neighbouring KV heads side by side, whose rows lie next to each other
 //    (kDecSideBlocks).
 //  * Work is cut into equal shares of 64-key blocks over all requests and KV heads (a share may start in the
