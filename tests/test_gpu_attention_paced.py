@@ -9,11 +9,11 @@ import paper_2501_15383_amd as vs
 pytestmark = pytest.mark.gpu
 
 
-# units beyond whole rounds of 512: 20 (many ranges each), 504 (a few), 8 of a second head size, rows that start inside a block; and, too
-# short to keep pace, 488; of full rounds the last, of more than 4,096 units what is over (64); 4,608 in full rounds, which stay whole
+# units beyond whole rounds of 512: 20 (many ranges each), 504 (a few), 8 of heads of 64 (which keep no pace) and the last of their full rounds,
+# rows that start inside a block; and, too short to keep pace, 488; of full rounds the last, of more than 4,096 units what is over (64); 4,608 in full rounds, which stay whole
 @pytest.mark.parametrize("hq,hkv,d,c,n,dca", [(28, 4, 128, 2400, 264000, False), (28, 4, 128, 2432, 262144 + 2433, True),
                                               (8, 2, 64, 8320, 300001, False), (8, 1, 64, 8300, 264007, True), (127, 1, 64, 1000, 262200, False),
-                                              (8, 2, 64, 15950, 16384, False), (8, 2, 128, 15950, 16385, True),
+                                              (16, 2, 64, 8192, 262400, False), (8, 2, 64, 15950, 16384, False), (8, 2, 128, 15950, 16385, True),
                                               (16, 2, 128, 8192, 8192, False), (16, 4, 64, 8192, 9024, True), (64, 1, 64, 8320, 8391, False),
                                               (72, 1, 64, 8192, 8256, True)])
 def test_pieces_behind_whole_units(hq, hkv, d, c, n, dca):
