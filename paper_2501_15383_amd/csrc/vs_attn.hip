@@ -1900,8 +1900,8 @@ static AttnCut attn_cut_as(const vs_params& p, bool dense, bool least, int force
     if (!c.queue) { c.pack = 1; c.n_hs = group; c.n_split = 1; }
     return c;
   }
-  // Steps of a whole walk: all key blocks, with index sets too (so that the cut is the same as without them, and with
-  // everything selected the results are)
+  // Steps of a whole walk: all key blocks, with index sets too (so that the cut is the same as without them, and with every
+  // offset selected the results are, unless many columns put fewer heads into a tile)
   const double steps = (double)n_blk;
   // Rounds of 512 pieces, in steps.  A piece costs kPieceSteps beside its walk; writing and folding partial results
   // costs about eight steps per 512 pieces and kFoldSteps per piece of a row, and the second launch three.  Ranges of two
@@ -2295,7 +2295,9 @@ static hipError_t attn_device_setup(int* n_cu_out) {
         {reinterpret_cast<const void*>(&k_attn_short<128, false>), short_lds_bytes<128>()},
         {reinterpret_cast<const void*>(&k_attn_short<64, false>), short_lds_bytes<64>()},
         {reinterpret_cast<const void*>(&k_attn_short<128, true>), short_lds_bytes<128>()},
-        {reinterpret_cast<const void*>(&k_attn_short<64, true>), short_lds_bytes<64>()}};
+        {reinterpret_cast<const void*>(&k_attn_short<64, true>), short_lds_bytes<64>()},
+        {reinterpret_cast<const void*>(&k_attn_short<128, true, true>), short_lds_bytes<128>()},
+        {reinterpret_cast<const void*>(&k_attn_short<64, true, true>), short_lds_bytes<64>()}};
     for (const auto& f : fns) {
       e = hipFuncSetAttribute(f.kernel, hipFuncAttributeMaxDynamicSharedMemorySize, f.lds);
       if (e != hipSuccess) return e;
@@ -2324,17 +2326,26 @@ static bool attn_listless(const vs_params& p, bool dense, const AttnCut& c, int 
          c.n_whole + (int64_t)(c.n_units - c.n_whole) * c.n_split <= 8 * (int64_t)members;
 }
 
+// Offsets of a tile's heads that a workgroup looks through by itself; beyond, it reads the bitmaps of k_build_blocklist.  The launch against the offsets,
+// 28 heads of 128 and 16 to 32 rows: 16,384 offsets 31.7 us with lists and 27.2 without, 32,768 46.0 and 41.7, 64,000 43.4 and 43.2, 80,000 53.3 and 54.6, 131,072 71.5
+// and 76.8 (and 72.9 in k_attention with lists); 17,000 of 8 heads of 64 30.4 and 26.6.
+constexpr int64_t kShortOffsets = 65536;
+static bool attn_short_listed(const vs_params& p, const AttnCut& c) {
+  const int64_t n_k = p.q_start + p.q_len;
+  return c.pack * (p.slash_budget < n_k ? p.slash_budget : n_k) > kShortOffsets;
+}
 // Ranges per unit of a call that k_attn_short takes (0: it does not): at most one workgroup per compute unit, and where it takes less
 // time than the ranges of `c`, by two sums fitted (in us) to both kernels over 120 dense calls of 2 to 3,000 rows and 512 to 32,000 keys
 // (they are off by 2.7 and 5 % on average, 10 and 13 at most, those of attn_cut by 5 and 7; what they choose is 0.2 % behind the
 // faster one, at most 1 % slower than before, and on average 16 % faster for heads of 64 and 10 for 128).  With index sets there is a
-// launch less besides (4.5 us), which the choice leaves out, so that everything selected goes the way of dense calls.
-constexpr int64_t kShortOffsets = 16384;   // that a workgroup looks through: more are k_build_blocklist's
+// launch less besides (4.5 us), which the choice leaves out, so that with every offset selected a call goes the way of the dense one (where columns
+// do not have it put fewer heads into a tile, see heads_per_tile).
 static int attn_short(const vs_params& p, bool dense, bool dca, const AttnCut& c) {
-  const int64_t n_k = p.q_start + p.q_len, n_blk = ceil_div(n_k, kBlock);
+  const int64_t n_blk = ceil_div(p.q_start + p.q_len, kBlock);
   if (dca || !c.queue || c.own_slots || attn_packed_decode(p, dense) || n_blk > kShortBlocks || c.n_qtiles >= kRun || c.n_units > 256) return 0;
   if (g_key_split.load(std::memory_order_relaxed) != 0 || (c.n_split > 1 && c.n_whole > 0)) return 0;
-  if (!dense && c.pack * (p.slash_budget < n_k ? p.slash_budget : n_k) > kShortOffsets) return 0;
+  // (with lists, too, only where it is the dense call's way)
+  if (!dense && attn_short_listed(p, c) && c.pack != heads_per_tile(p.q_len, (int)(p.q_start % kBlock), p.n_q_heads / p.n_kv_heads, n_blk, 0)) return 0;
   const bool wide = p.head_dim == 128;
   double least = wide ? 1.6 + 1.28 * c.steps : 3.8 + 1.03 * c.steps;
   int best = 0;
@@ -2360,7 +2371,7 @@ hipError_t launch_build_blocklist(const vs_params& p, const int32_t* s_idx, cons
     int n_cu = 0;
     const hipError_t e = attn_device_setup(&n_cu);
     if (e != hipSuccess) return e;
-    if (attn_short(p, dense, dca, c) || attn_listless(p, dense, c, attn_members(n_cu))) return hipSuccess;
+    if ((attn_short(p, dense, dca, c) && (dense || !attn_short_listed(p, c))) || attn_listless(p, dense, c, attn_members(n_cu))) return hipSuccess;
   }
   ListArgs a = {};
   a.s_idx = s_idx; a.s_cnt = s_cnt; a.v_cnt = v_cnt; a.s_budget = p.slash_budget;
@@ -2491,10 +2502,19 @@ hipError_t launch_attention(const vs_params& p, const void* q, const DcaArgs* dc
     b.n_k = (int32_t)a.n_k; b.scale_log2 = a.scale_log2;
     b.v_idx = sets.v_idx; b.v_cnt = sets.v_cnt; b.s_idx = sets.s_idx; b.s_cnt = sets.s_cnt;
     b.v_budget = p.vertical_budget; b.s_budget = p.slash_budget;
+    b.bm = a.bm_a; b.bm_words = a.bm_words;
+    const bool listed = attn_short_listed(p, cut);
     const dim3 grid((unsigned)(8 * b.each));
     const auto go = [&](auto&& kernel, int lds) { hipLaunchKernelGGL(kernel, grid, dim3(kShortThreads), lds, st, b); };
-    if (p.head_dim == 128) { if (dense) go(k_attn_short<128, false>, short_lds_bytes<128>()); else go(k_attn_short<128, true>, short_lds_bytes<128>()); }
-    else { if (dense) go(k_attn_short<64, false>, short_lds_bytes<64>()); else go(k_attn_short<64, true>, short_lds_bytes<64>()); }
+    if (p.head_dim == 128) {
+      if (dense) go(k_attn_short<128, false>, short_lds_bytes<128>());
+      else if (listed) go(k_attn_short<128, true, true>, short_lds_bytes<128>());
+      else go(k_attn_short<128, true>, short_lds_bytes<128>());
+    } else {
+      if (dense) go(k_attn_short<64, false>, short_lds_bytes<64>());
+      else if (listed) go(k_attn_short<64, true, true>, short_lds_bytes<64>());
+      else go(k_attn_short<64, true>, short_lds_bytes<64>());
+    }
     if (a.n_split > 1) fold();
     return hipGetLastError();
   }

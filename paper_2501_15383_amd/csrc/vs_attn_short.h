@@ -30,6 +30,9 @@ struct ShortArgs {
   const int32_t* s_idx;
   const int32_t* s_cnt;
   int32_t v_budget, s_budget;
+  // LISTED: the heads' bitmaps and the words of each (see build_list)
+  const uint32_t* bm;
+  int32_t bm_words;
 };
 
 constexpr int kShortBlocks = 512;   // key blocks of a call at most: flags of its diagonals in LDS
@@ -52,8 +55,10 @@ constexpr int short_lds_bytes() {
 // blocks 19.4, 256 of two sets 18.0), which go past the caches (0.4 to 1 us at the end of the launch).
 // Measured (us, before and after): that chunk 45.8 -> 38.5; 70 rows of 28 heads of 128 at 2,048 keys 48.2 -> 42.5, 300 at 2,500 63 -> 55;
 // dense, 2,000 rows of 4 heads at 2,000 keys 21.8 -> 16.7, 138 of 28 at 2,869 29.1 -> 24.5, 4 at 5,000 16.6 -> 14.9.
-template <int D, bool SETS>
+// LISTED: the diagonals come from the bitmaps of k_build_blocklist, where there are too many offsets to look through here (kShortOffsets).
+template <int D, bool SETS, bool LISTED = false>
 __global__ __launch_bounds__(kShortThreads) void k_attn_short(const ShortArgs a) {
+  static_assert(SETS || !LISTED, "dense calls have no lists");
   constexpr int NQB = kAttnQBlocks, DCH = D / 8, DSTEPS = D / 16, DB = D / 32, TILE = 64 * D;
   constexpr int RPG = 512 / D, GPW = 64 / RPG / 4, R = 128 / D, NST = short_stages(D);
   static_assert(NQB == 2, "two query blocks per tile");
@@ -103,9 +108,17 @@ __global__ __launch_bounds__(kShortThreads) void k_attn_short(const ShortArgs a)
   uint32_t heads_bits = (1u << n_heads) - 1u;
   if constexpr (SETS) {
     vcnt_l = a.v_cnt[h + (lane < n_heads ? lane : 0)];
-    for (int x = tid; x < (kShortBlocks * 4 + 16) / 4; x += kShortThreads) ((uint32_t*)flags)[x] = 0u;
-    __syncthreads();
-    collect_flags<kShortThreads, 8>(flags, shift, 0, n_blk, kShortBlocks, a.s_idx + (int64_t)h * a.s_budget, a.s_cnt + h, a.s_budget, n_heads);
+    if constexpr (LISTED) {
+      const uint32_t* const bm = a.bm + (int64_t)h * a.bm_words;
+      for (int x = tid; x < n_blk << shift; x += kShortThreads) {
+        const int p = pack > 1 ? x & 3 : 0, ad = x >> shift;
+        flags[x] = p < n_heads ? (uint8_t)(bm[p * a.bm_words + (ad >> 5)] >> (ad & 31) & 1u) : 0;
+      }
+    } else {
+      for (int x = tid; x < (kShortBlocks * 4 + 16) / 4; x += kShortThreads) ((uint32_t*)flags)[x] = 0u;
+      __syncthreads();
+      collect_flags<kShortThreads, 8>(flags, shift, 0, n_blk, kShortBlocks, a.s_idx + (int64_t)h * a.s_budget, a.s_cnt + h, a.s_budget, n_heads);
+    }
     __syncthreads();
     // a head that has every diagonal has no column left to gather
     uint32_t missing = 0;
