@@ -1851,6 +1851,16 @@ struct AttnCut {
     return even > own_slots ? even : own_slots;
   }
 };
+// Few heads of 64 over many keys, with units for two whole rounds or more and at most 128 over: with index sets the whole units keep pace all the
+// same, by the lists' lengths.  The queues know nothing of these, so the longest may begin last.  Clustered lists, in the queues and keeping pace:
+// 8 heads, 16,512 rows at 300,032 keys (lists of 232 to 465 blocks, 8 units over) 1,300 us and 1,075, 17,536 rows (72 over) 1,297 and 1,171, 24,704 (8) 1,227 and
+// 1,173; 4 heads without groups, 32,896 rows at 400,000 918 and 779.  Not for more: 18,944 rows (160 over) 1,302 and 1,282, of lists that are alike 845 and 925;
+// 16 heads, 12,416 rows at 400,000 (16 over) 1,184 and 1,476.  Where lists are alike it loses: 4 heads of a group, 32,768 rows at 700,032 keys 436 and 494 (487 while
+// heads of 64 kept pace everywhere), scattered ones of 8 heads 3,258 and 3,362.  Nor for dense calls, whose units are alike: 10,830 and 11,140.
+static bool attn_few_over(const vs_params& p, int64_t units) {
+  return p.head_dim == 64 && p.n_q_heads <= 8 && ceil_div(p.q_start + p.q_len, kBlock) >= kPaceBlocks && units > 1024 && units % 512 != 0 &&
+         units % 512 <= 128;
+}
 static AttnCut attn_cut_as(const vs_params& p, bool dense, bool least, int forced) {
   const bool one = attn_packed_decode(p, dense);
   const int group = p.n_q_heads / p.n_kv_heads, row_pad = (int)(p.q_start % kBlock);
@@ -1937,7 +1947,7 @@ static AttnCut attn_cut_as(const vs_params& p, bool dense, bool least, int force
   // Below 1,024 key blocks the ranges that the count makes are as good (40 calls: 2 % either way), and smaller; and ranges of one
   // round that do not keep pace go, with index sets, by the lists' lengths.
   const bool one_round = c.n_split > 1 && (c.n_units - c.n_whole) * (int64_t)c.n_split <= slots && n_blk >= 64 * (int64_t)c.n_split;
-  if (fine && units % slots != 0 && (c.n_split == 1 || long_walk || (n_blk >= 1024 && !one_round))) {
+  if (fine && units % slots != 0 && (c.n_split == 1 || long_walk || attn_few_over(p, units) || (n_blk >= 1024 && !one_round))) {
     cut_rest(units % slots);
     return c;
   }
@@ -2290,6 +2300,8 @@ static hipError_t attn_device_setup(int* n_cu_out) {
         {reinterpret_cast<const void*>(&k_attention_own<64, NQB, true>), lds64},
         {reinterpret_cast<const void*>(&k_attention_paced<128, NQB, false>), lds128},
         {reinterpret_cast<const void*>(&k_attention_paced<128, NQB, true>), lds128},
+        {reinterpret_cast<const void*>(&k_attention_paced<64, NQB, false>), lds64},
+        {reinterpret_cast<const void*>(&k_attention_paced<64, NQB, true>), lds64},
         {reinterpret_cast<const void*>(&k_attention_mixed<128, NQB>), lds128},
         {reinterpret_cast<const void*>(&k_attention_mixed<64, NQB>), lds64},
         {reinterpret_cast<const void*>(&k_attn_short<128, false>), short_lds_bytes<128>()},
@@ -2313,16 +2325,16 @@ static int attn_members(int n_cu) {
   const int members = ((4 / kAttnQBlocks) * n_cu) / 8;
   return members < 1 ? 1 : members;
 }
-// Whole units of a cut launch that keep pace, in a launch of their own (see launch_attention).
-static bool attn_paced(const AttnCut& c, const vs_params& p, int members) {
-  return c.queue && c.n_split > 1 && c.n_whole > 0 && !c.own_slots && c.pack == 1 && members == kRun && p.head_dim == 128 &&
-         ceil_div(p.q_start + p.q_len, kBlock) >= kPaceBlocks;
+// Whole units of a cut launch that keep pace, before the pieces of the others in the same launch (see launch_attention).
+static bool attn_paced(const AttnCut& c, const vs_params& p, bool dense, int members) {
+  return c.queue && c.n_split > 1 && c.n_whole > 0 && !c.own_slots && c.pack == 1 && members == kRun &&
+         ceil_div(p.q_start + p.q_len, kBlock) >= kPaceBlocks && (p.head_dim == 128 || (!dense && attn_few_over(p, c.n_units)));
 }
 // Dense launches of no more pieces than workgroups need neither a list (every block is in it) nor cleared counters (nobody takes
 // a second piece): the list builder is not launched.  34 rows of 28 heads at 11,126 keys 34.5 us -> 31.3, the fold's share
 // of it included; rows of 2 to 391 at 600 to 50,000 keys gain 2 to 11 %.
 static bool attn_listless(const vs_params& p, bool dense, const AttnCut& c, int members) {
-  return dense && c.queue && !attn_paced(c, p, members) &&
+  return dense && c.queue && !attn_paced(c, p, dense, members) &&
          c.n_whole + (int64_t)(c.n_units - c.n_whole) * c.n_split <= 8 * (int64_t)members;
 }
 
@@ -2359,7 +2371,6 @@ static int attn_short(const vs_params& p, bool dense, bool dca, const AttnCut& c
   }
   return best;
 }
-
 // One list per head, or per tile of packed heads (one for all heads when dense); attn: for the attention launch with the
 // counters at sync_ws, which are cleared on the way (null: for k_count_tiles, which packs nothing and has none to clear).
 hipError_t launch_build_blocklist(const vs_params& p, const int32_t* s_idx, const int32_t* s_cnt,
@@ -2528,10 +2539,12 @@ hipError_t launch_attention(const vs_params& p, const void* q, const DcaArgs* dc
   // 35.9 ms against 37.3 without, 9,500 clustered ones at 300K 12.8 against 14.0 (with the pieces in a launch of their own behind them,
   // 34.1 and 11.6 in the same).  Below 256K keys the caches hold what the members of a group are apart, and whole units come out of the
   // queues, too: 2,400 rows at 100K keys 3.44 ms against 3.52, 5,426 clustered ones at 33K 2.31 against 2.46.
-  // Nor heads of 64, whose blocks are half as large: 8 heads, 19,083 rows at 300K keys 3,953 us keeping pace, 3,719 without, 15,000 clustered ones at
-  // 500K 812 and 765, at 1M 1,175 and 1,111; 4 heads, 30,000 clustered rows at 700K 480 and 463; of 17 calls the most that was lost is 873 and 888.
+  // Nor heads of 64, whose blocks are half as large, but for attn_few_over.  Against keeping pace (and fewer pieces) everywhere, attention alone: 8 heads, 19,083 rows at 300K
+  // keys dense 4,095 us -> 3,719, scattered 4,064 -> 3,792, 9,000 clustered ones 762 -> 670, 15,000 at 500K 1,478 -> 1,268.  Whole rounds of clustered
+  // lists are the exception, in whole chunks: 32,768 rows of 8 heads at 600K three sets of keys 2,659, 1,889, 2,064 -> 2,690, 1,950, 2,133 (the attention alone 2,487 -> 2,451, 1,708 ->
+  // 1,681, 1,877 -> 1,851).
   // Not where heads share tiles: the pace-keeping kernel takes one head per unit, with one list per head.
-  if (attn_paced(cut, p, members)) {
+  if (attn_paced(cut, p, dense, members)) {
     PacedArgs b;
     keep_pace(a.n_whole);
     b.whole = a;
@@ -2540,8 +2553,14 @@ hipError_t launch_attention(const vs_params& p, const void* q, const DcaArgs* dc
     a.n_full = a.n_rem = a.n_gr = 0;
     b.cut = a;
     const dim3 grid((unsigned)a.n_wg), block(128 * NQB);
-    if (dca) hipLaunchKernelGGL((k_attention_paced<128, NQB, true>), grid, block, attn_lds_bytes<128>(), st, b);
-    else hipLaunchKernelGGL((k_attention_paced<128, NQB, false>), grid, block, attn_lds_bytes<128>(), st, b);
+    const auto go = [&](auto&& kernel, int lds) { hipLaunchKernelGGL(kernel, grid, block, lds, st, b); };
+    if (p.head_dim == 128) {
+      if (dca) go(k_attention_paced<128, NQB, true>, attn_lds_bytes<128>());
+      else go(k_attention_paced<128, NQB, false>, attn_lds_bytes<128>());
+    } else {
+      if (dca) go(k_attention_paced<64, NQB, true>, attn_lds_bytes<64>());
+      else go(k_attention_paced<64, NQB, false>, attn_lds_bytes<64>());
+    }
     fold();
     return hipGetLastError();
   }

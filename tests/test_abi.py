@@ -254,3 +254,18 @@ def test_batch_argument_checks():
     long = vs.Chunk(4, 1, 64, 5000, 0, 0.125, vertical_budget=8, slash_budget=70).params()
     assert L.vs_attn_batch(C.byref(long), ok, 2, ok, 1 << 30, None) == vs.VS_ERR_UNSUPPORTED
     assert L.vs_batch_workspace_bytes(C.byref(long), 2) == 0
+
+
+def test_the_finest_cut_of_heads_of_64_over_many_keys():
+    """Ranges of the units that whole rounds of 512 leave over, by the workspace they take: 2,048 pieces at most; few units over, after two
+    rounds and more, in 128 ranges each (they follow a walk that keeps pace)."""
+    def pieces(hq, hkv, rows, n_k, bv, bs):
+        ck = vs.Chunk(hq, hkv, 64, rows, n_k - rows, 0.125, vertical_budget=bv, slash_budget=bs)
+        auto = vs.workspace_bytes(ck, vs.VS_WS_SPARSE)
+        vs.set_option(vs.VS_OPT_ATTN_KEY_SPLIT, 1)
+        none = vs.workspace_bytes(ck, vs.VS_WS_SPARSE)
+        vs.set_option(vs.VS_OPT_ATTN_KEY_SPLIT, 0)
+        return (auto - none) / (128 * (64 + 2) * 4)
+    assert pieces(4, 1, 32768, 1 << 20, 300, 700) == 512 * 4
+    assert pieces(4, 1, 32768, 200000 // 64 * 64, 128, 256) == 512 * 4
+    assert pieces(8, 2, 16512, 300032, 300, 700) == 8 * 128

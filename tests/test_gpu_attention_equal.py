@@ -11,12 +11,13 @@ pytestmark = pytest.mark.gpu
 
 # Offsets that a workgroup of the short kernel collects by itself, up to 65,536 of a tile's 4, 2 or 1 heads, and more of them, which come from
 # lists (from 16,385 keys on with four heads per tile, the last of which is not full; the most keys); rows that start inside a block, a few and 64
-# key blocks per range; the general kernel (33,000 keys, 2,000 rows)
+# key blocks per range; the general kernel (33,000 keys, 2,000 rows); whole units that keep pace where those of the dense call do not
 @pytest.mark.parametrize("hq,hkv,d,c,n", [
     (28, 4, 128, 16, 1024), (28, 4, 128, 16, 8000), (28, 4, 128, 4, 5000), (28, 4, 128, 32, 12000), (28, 4, 128, 32, 16384), (28, 4, 128, 32, 16385),
     (28, 4, 128, 9, 20009), (28, 4, 128, 8, 30000), (28, 4, 128, 32, 32768), (8, 1, 64, 32, 32768), (5, 1, 64, 20, 18000), (40, 8, 128, 64, 16000),
     (7, 1, 128, 50, 9000), (3, 1, 128, 300, 16400), (4, 1, 64, 300, 20000), (8, 2, 64, 100, 17000), (8, 2, 64, 64, 25024), (4, 1, 64, 1000, 18000),
-    (4, 1, 64, 200, 16000), (2, 1, 64, 70, 32768), (1, 1, 64, 500, 32767), (4, 1, 64, 17, 33000), (28, 4, 128, 2000, 3000)])
+    (4, 1, 64, 200, 16000), (2, 1, 64, 70, 32768), (1, 1, 64, 500, 32767), (4, 1, 64, 17, 33000), (28, 4, 128, 2000, 3000),
+    (8, 2, 64, 16512, 262272)])
 def test_all_offsets_give_the_bits_of_the_dense_call(hq, hkv, d, c, n):
     gen = torch.Generator(device="cuda").manual_seed(5500 + n + c)
     rnd = lambda *size: torch.randn(size, generator=gen, device="cuda").to(torch.bfloat16)  # noqa: E731

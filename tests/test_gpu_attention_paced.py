@@ -68,3 +68,10 @@ def test_pieces_behind_whole_units(hq, hkv, d, c, n, dca):
             lo = mid
     assert 256 * hi < full
     close(guarded(256 * hi))
+
+
+# heads of 64 that keep pace for all that: two whole rounds and 16, 8, 128 units (whose walks the budgets make short), and, as before, none of them (16 heads)
+@pytest.mark.parametrize("hq,hkv,d,c,n,dca", [(8, 2, 64, 16500, 262144 + 13, False), (8, 8, 64, 16512, 262272, True), (4, 1, 64, 36864, 270016, False),
+                                              (16, 2, 64, 8320, 262272, False)])
+def test_few_heads_of_64_keep_pace(hq, hkv, d, c, n, dca):
+    test_pieces_behind_whole_units(hq, hkv, d, c, n, dca)
