@@ -175,6 +175,7 @@ constexpr int kMaxPieces = 2048, kBatchPieces = 1536;   // pieces with partial r
 constexpr int kMaxQueueUnits = 4096;               // beyond it only what whole rounds leave over is cut; ranges that are asked for are made
 constexpr int64_t kMaxAskedUnits = 1 << 23;        // all the same (128 M pieces of 33 KB and more: no workspace holds them)
 constexpr int kPaceBlocks = 4096;                  // key blocks from which whole units of heads of 128 keep pace (see launch_attention)
+constexpr int kShortList = 1024;                   // steps of a walk below which (by the budgets) heads of 64 over many keys are cut less finely
 constexpr int kRun = 64;                           // workgroup slots of an XCD: members of a pace-keeping group
 constexpr int kQueueStride = 16;                   // words between two queue counters: a cache line each
 constexpr int kListBits = 28;                      // of a bitmap row's word that holds the length of the list (see build_list)
@@ -1880,8 +1881,13 @@ static AttnCut attn_cut_as(const vs_params& p, bool dense, bool least, int force
   // 262,144 146.7 and 142.3; 16,384 rows of 28 at 16,384 dense 2,165 us and 1,766, clustered at 50K 7,562 and 7,046.  Full rounds of more than
   // kMaxQueueUnits units that do not keep pace stay whole, where 136 MB of partial results would be as much as the caches, and come out of
   // the queues: 28 heads at 65,536 dense 20.98 ms keeping pace, 20.33 so (19.57 with the last round cut), clustered 16.21 and 15.12.
+  // Walks that the budgets make short (heads of 64, 256K keys and more) in half as many: the partial results take as much of the caches and of the time
+  // as they save.  4 heads with 256 offsets, clustered: 30,000 rows at 700,000 keys 418, 610, 661 us (three sets of keys), 401, 602, 660 so; 32,768 rows at 1M 484,
+  // 639, 671 and 483, 627, 664 (482, 611, 674 whole); with 700 offsets, 8 heads, 15,000 rows at 500,000 1,443, 1,014, 1,090 and 1,544, 1,019, 1,142.
   const auto cut_rest = [&](int64_t rest) {
-    int64_t n = kMaxPieces / rest;
+    const int64_t listed = dense ? n_blk : 2 * (int64_t)p.slash_budget + 1 + 2 * ((columns + 63) / 64);
+    const bool short_lists = p.head_dim == 64 && n_blk >= kPaceBlocks && listed < kShortList;
+    int64_t n = (short_lists ? kMaxPieces / 2 : kMaxPieces) / rest;
     n = n < n_blk / 16 ? n : n_blk / 16;
     c.queue = true;
     c.n_qtiles = (int32_t)n_qtiles;

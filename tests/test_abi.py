@@ -257,8 +257,8 @@ def test_batch_argument_checks():
 
 
 def test_the_finest_cut_of_heads_of_64_over_many_keys():
-    """Ranges of the units that whole rounds of 512 leave over, by the workspace they take: 2,048 pieces at most; few units over, after two
-    rounds and more, in 128 ranges each (they follow a walk that keeps pace)."""
+    """Ranges of the units that whole rounds of 512 leave over, by the workspace they take: 2,048 pieces at most, half as many where the
+    budgets make walks short; few units over, after two rounds and more, in 128 ranges each (they follow a walk that keeps pace)."""
     def pieces(hq, hkv, rows, n_k, bv, bs):
         ck = vs.Chunk(hq, hkv, 64, rows, n_k - rows, 0.125, vertical_budget=bv, slash_budget=bs)
         auto = vs.workspace_bytes(ck, vs.VS_WS_SPARSE)
@@ -266,6 +266,7 @@ def test_the_finest_cut_of_heads_of_64_over_many_keys():
         none = vs.workspace_bytes(ck, vs.VS_WS_SPARSE)
         vs.set_option(vs.VS_OPT_ATTN_KEY_SPLIT, 0)
         return (auto - none) / (128 * (64 + 2) * 4)
+    assert pieces(4, 1, 32768, 1 << 20, 128, 256) == 512 * 2
     assert pieces(4, 1, 32768, 1 << 20, 300, 700) == 512 * 4
     assert pieces(4, 1, 32768, 200000 // 64 * 64, 128, 256) == 512 * 4
     assert pieces(8, 2, 16512, 300032, 300, 700) == 8 * 128
