@@ -76,13 +76,26 @@ def cpu_baseline(w, pb_kwargs, Q, K, V, sets_host, target_s, dca=None):
     }
 
 
+def kernel_sources(name="paper_2501_15383_amd/csrc/vs_attn.hip"):
+    """The attention kernel's source and whatever it includes of this repository."""
+    import re
+    path = os.path.normpath(os.path.join(ROOT, name))
+    found = [path]
+    for inc in re.findall(r'^\s*#\s*include\s+"([^"]+)"', open(path).read(), flags=re.M):
+        for place in (os.path.dirname(path), os.path.join(ROOT, "include")):
+            if os.path.exists(os.path.join(place, inc)):
+                found += [p for p in kernel_sources(os.path.join(place, inc)) if p not in found]
+                break
+    return found
+
+
 def kernel_source_hash():
     """sha256 of the attention kernel's sources: a counter figure stored under profiles/ is quoted
     only while it was measured on these very sources."""
     import hashlib
     h = hashlib.sha256()
-    for f in ("paper_2501_15383_amd/csrc/vs_attn.hip", "paper_2501_15383_amd/csrc/vs_common.h"):
-        h.update(open(os.path.join(ROOT, f), "rb").read())
+    for f in sorted(kernel_sources()):
+        h.update(os.path.basename(f).encode() + b"\0" + open(f, "rb").read())
     return h.hexdigest()[:16]
 
 

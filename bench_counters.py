@@ -192,7 +192,7 @@ def main():
     out += ["# rocprofv3 summaries: vertical-slash sparse prefill, workload 7b_1m (last 32,768-token chunk of a 1,048,576-token",
             "# context, Hq 28 / Hkv 4 / D 128, W 64, Bv 1000, Bs 6096), one MI355X.  Written by bench_counters.py from the runs",
             "# its header lists (B = python3 bench.py --no-cpu --no-extras --gather-probe); raw outputs are not kept.",
-            f"# sources: sha256[:16] of all of the library = {sources_hash()} in every run; of csrc/vs_attn.hip + csrc/vs_common.h = "
+            f"# sources: sha256[:16] of all of the library = {sources_hash()} in every run; of csrc/vs_attn.hip and what it includes = "
             f"{bench.kernel_source_hash()}", ""]
     # ---- 1. kernel trace
     out += ["## 1. kernel trace",

@@ -34,3 +34,25 @@ def test_cycles_and_times_of_different_work_are_refused():
     assert abs(bc.clock(2.0e6, 1.0, "k") - 2.0) < 1e-12
     with pytest.raises(SystemExit):
         bc.clock(1.367e6, 0.468, "k_est_sums")
+
+
+def test_a_kernel_figure_is_of_all_its_sources(monkeypatch, tmp_path):
+    """A change of any file that the attention kernel is compiled from changes the hash that its stored figures go by."""
+    import os
+    import shutil
+
+    import bench
+    files = sorted(os.path.relpath(f, bench.ROOT) for f in bench.kernel_sources())
+    assert {os.path.basename(f) for f in files} == {"vs_attn.hip", "vs_attn_short.h", "vs_common.h", "vs_decode_walk.h", "vs.h"}
+    for f in files:
+        os.makedirs(tmp_path / os.path.dirname(f), exist_ok=True)
+        shutil.copy(os.path.join(bench.ROOT, f), tmp_path / f)
+    here = bench.kernel_source_hash()
+    monkeypatch.setattr(bench, "ROOT", str(tmp_path))
+    assert bench.kernel_source_hash() == here
+    seen = {here}
+    for f in files:
+        with open(tmp_path / f, "a") as g:
+            g.write("// changed\n")
+        seen.add(bench.kernel_source_hash())
+    assert len(seen) == 1 + len(files)
