@@ -68,7 +68,8 @@ def test_the_dca_kernels_spill_no_more_than_a_handful_of_registers(resources):
 # the estimate's sweeps have 128 (sweep A at head_dim 64 is held to 96, where small workgroups get a fifth wave: 7 heads of their
 # own, 100,000 keys 44 us, 49 with 98), three with Dual Chunk Attention 168 (sweep A at head_dim 128 spills one);
 # a selection row is one workgroup of 16 waves, 128, whatever the scores per lane, and so are a list and the pieces of an uneven cut;
-# the decode kernel's four waves share a compute unit's LDS with nobody
+# the decode kernel's four waves share a compute unit's LDS with nobody; of k_attention's kin two workgroups are on a compute unit, of the
+# kernel of short calls one of eight waves (the walk with Dual Chunk Attention that has pieces behind it spills nine, tiles beside tokens two)
 @pytest.mark.parametrize("source,budgets", [
     ("vs_estimate", {"k_est_sumsILi128ELb0E": (128, 0), "k_est_scoresILi128ELb0E": (128, 0), "k_est_sumsILi64ELb0E": (96, 0),
                      "k_est_scoresILi64ELb0E": (128, 0), "k_est_sumsILi128ELb1E": (168, 2), "k_est_scoresILi128ELb1E": (168, 0),
@@ -78,6 +79,11 @@ def test_the_dca_kernels_spill_no_more_than_a_handful_of_registers(resources):
                    "k_slice_write": (64, 0)}),
     ("vs_attn", {"k_attention_ownILi128ELi2ELb0E": (256, 0), "k_attention_ownILi64ELi2ELb0E": (256, 0),
                  "k_attention_ownILi128ELi2ELb1E": (256, 16), "k_attention_ownILi64ELi2ELb1E": (256, 16), "k_attn_pieces": (128, 0),
+                 "k_attention_pacedILi128ELi2ELb0E": (256, 0), "k_attention_pacedILi64ELi2ELb0E": (256, 0),
+                 "k_attention_pacedILi128ELi2ELb1E": (256, 16), "k_attention_pacedILi64ELi2ELb1E": (256, 0),
+                 "k_attention_mixedILi128ELi2E": (256, 4), "k_attention_mixedILi64ELi2E": (256, 0), "k_mixed_lists": (128, 0),
+                 **{f"k_mixed_combineILi{d}E": (128, 0) for d in (64, 128)},
+                 **{f"k_attn_shortILi{d}ELb{s}ELb{l}E": (256, 0) for d in (64, 128) for s, l in ((0, 0), (1, 0), (1, 1))},
                  **{f"k_attn_combineILi{d}ELb{b}ELb{o}E": (128, 0) for d in (64, 128) for b, o in ((0, 0), (0, 1), (1, 0))},
                  **{f"k_build_blocklistILi2ELb{b}ELb{w}E": (128, 0) for b, w in ((0, 0), (0, 1), (1, 0))}}),
     ("vs_decode", {"k_decodeILi128E": (256, 0), "k_decodeILi64E": (256, 0), "k_decode_lists": (64, 0), "k_decode_pairs": (256, 0),
@@ -91,3 +97,8 @@ def test_the_other_kernels_keep_their_register_budgets(tmp_path_factory, source,
         assert len(found) == 1, (kernel, [n for n, _ in res])
         assert found[0]["vgpr"] <= vgpr and found[0]["spill"] <= spill, (kernel, found[0])
         assert spill or found[0]["scratch"] == 0, (kernel, found[0])
+        assert found[0]["scratch"] <= 128, (kernel, found[0])
+    # and no kernel goes without: those that are not named here (small ones, and k_attention itself, whose budgets are above) do not spill
+    for name, r in res:
+        if not any(kernel in name for kernel in budgets) and "k_attentionILi" not in name:
+            assert r["vgpr"] <= 128 and r["spill"] == 0 and r["scratch"] == 0, (name, r)
