@@ -78,3 +78,45 @@ def test_tokens_beside_longer_requests(hq, hkv, d, specs):
         lo, hi = (lo, mid) if rc == vs.VS_OK else (mid, hi)
     if 256 * hi < full:
         check(256 * hi, 0x5A)
+
+
+# A sparse token beside longer requests whose list takes several windows of diagonals: 4,096 of groups of 9 to 16 heads (262,144 keys), 8,192 of smaller
+# ones (524,288), fewer than a call of its own has.  Offsets and columns crowd on both sides of the windows' edges, other ones for every head; a
+# column is gathered where its head lacks the diagonal.
+@pytest.mark.parametrize("hq,hkv,d,n", [(16, 1, 128, 270000), (12, 1, 64, 2 * 262144 + 777), (24, 2, 128, 262144 + 64), (8, 1, 64, 530001), (28, 4, 128, 525000)])
+def test_lists_of_tokens_in_windows(hq, hkv, d, n):
+    gen = torch.Generator(device="cuda").manual_seed(5700 + n)
+    rnd = lambda *size: torch.randn(size, generator=gen, device="cuda").to(torch.bfloat16)  # noqa: E731
+    draw = lambda lo, hi, count: torch.randint(max(lo, 0), hi, (count,), generator=gen, device="cuda")  # noqa: E731
+    window = 64 * (8192 if hq // hkv <= 8 else 4096)
+    bv, bs = 200, 300
+    edges = [e for e in range(window, n, window)]
+
+    def lines(budget, m, spots):
+        idx = torch.full((hq, budget), -1, dtype=torch.int32, device="cuda")
+        cnt = torch.zeros(hq, dtype=torch.int32, device="cuda")
+        for h in range(hq):
+            x = torch.cat([draw(0, m, 40)] + [draw(lo, min(hi, m), 60) for lo, hi in spots]).unique()
+            idx[h, :len(x)] = x.int()
+            cnt[h] = len(x)
+        return idx, cnt
+    k, v = rnd(n, hkv, d), rnd(n, hkv, d)
+    specs = [(1, n), (40, 5000), (1, n - 70)]
+    reqs, want = [], []
+    for r, m in specs:
+        q = rnd(r, hq, d)
+        # (offset o of the token is key m - 1 - o)
+        sets = (*lines(bv, m, [(m - e - 700, m - e + 700) for e in edges]), *lines(bs, m, [(e - 700, e + 700) for e in edges])) if r == 1 else None
+        ck = vs.Chunk(hq, hkv, d, r, m - r, 1.0 / np.sqrt(d), vertical_budget=bv, slash_budget=bs)
+        one = vs.sparse_attn_prefill(ck, q, k[:m], v[:m], *sets, want_lse=True) if sets else vs.dense_causal_prefill(ck, q, k[:m], v[:m], want_lse=True)
+        want.append(one)
+        reqs.append(dict(q=q, k=k, v=v, out=torch.empty_like(q), lse=torch.empty(hq, r, device="cuda"), q_start=m - r, sets=sets))
+    ck = vs.Chunk(hq, hkv, d, 40, n - 40, 1.0 / np.sqrt(d), vertical_budget=bv, slash_budget=bs)
+    table = vs.request_table(reqs, "cuda")
+    vs.attn_batch(ck, table, len(reqs), reqs[0]["q"], k, v, reqs[0]["out"])
+    torch.cuda.synchronize()
+    for r, (o, l), spec in zip(reqs, want, specs):
+        a, b = r["out"].float(), o.float()
+        # bf16 probabilities and outputs on either side: 2^-9 each, unbiased, about 6e-3 between the two
+        assert ((a - b).norm(dim=2) <= 2e-2 * b.norm(dim=2) + 1e-30).all(), spec
+        np.testing.assert_allclose(r["lse"].cpu().numpy(), l.cpu().numpy(), rtol=2e-5, atol=5e-5, err_msg=str(spec))
