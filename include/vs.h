@@ -78,10 +78,16 @@ typedef struct vs_params {
 /* Bytes of workspace the call named by `which` needs for these parameters
  * (0 on invalid parameters).  Host function; touches no device.  The workspace
  * must be 256-byte aligned.  VS_WS_CHUNK covers vs_prefill_chunk.
- * Most of what short sparse calls ask for is room for partial results of ranges
- * that follow the heads' own lists: 28 heads of 128, 2,000 rows at 150,000 keys
- * VS_WS_SPARSE 137 MB (0.3 without), VS_WS_CHUNK 171 (41).  A sparse, chunk or
- * batch call that is given less, but all that it needs without such ranges (and,
+ * Most of what attention calls ask for is room for the partial results of key
+ * ranges: of long chunks, dense ones too, 2,048 ranges of the units that whole
+ * rounds of workgroups leave over or end with; of short sparse calls, ranges that
+ * follow the heads' own lists.  28 heads of 128, VS_WS_SPARSE / VS_WS_DENSE in MB
+ * (without such ranges in brackets): 32,768 rows at 1,048,576 keys 138 (2.2) /
+ * 137 (0.3), 13,307 at 31,000 127 (0.2) / 127 (0.1), 2,000 at 150,000 137 (0.3) /
+ * 0.03; VS_WS_CHUNK of the first 374 (244).  VS_WS_SELECT holds the candidates of
+ * all rows (28 heads, 300,001 keys 6.0 MB; lists an eighth shorter are made in less).
+ * A sparse, dense, chunk, batch or select (vs_select, vs_select_heads) call that is
+ * given less, but all that it needs with fewer ranges or the shorter lists (and,
  * single tokens, without KV heads side by side), takes it and is slower; with less
  * than that it returns VS_ERR_WORKSPACE. */
 size_t vs_workspace_bytes(const vs_params *p, int which);
@@ -317,12 +323,13 @@ int vs_plan_chunks(int64_t n_ctx, int32_t n_chunks, int32_t model,
  *     blocks are shared through the L2.  Only the timing depends on it.  The
  *     choice changes VS_WS_SPARSE / VS_WS_DENSE / VS_WS_CHUNK sizes, so set it
  *     before asking for them.
- *   VS_OPT_ATTN_KEY_SPLIT  chunks with few (query tile, head) units (a decode step, a short
- *     last chunk) have their key walk cut into ranges, one workgroup each, and a second
- *     kernel folds the partial results: 0 = automatic (up to 128 ranges of at least 2 key
- *     blocks, 8 in a batch, so that the pieces fill 512 workgroup slots evenly; of longer chunks only the
- *     units that whole rounds leave over are cut), 1 = never, 2..16 = that many ranges (at
- *     least 16 key blocks each).
+ *   VS_OPT_ATTN_KEY_SPLIT  the key walk of (query tile, head) units is cut into ranges, one
+ *     workgroup each, and a second kernel folds the partial results: 0 = automatic (chunks
+ *     with few units, as a short last chunk, in up to 128 ranges of at least 2 key blocks, 8
+ *     in a batch, so that the pieces fill 512 workgroup slots evenly; of longer ones the
+ *     units that whole rounds of 512 leave over, and the last round of full ones: of up to
+ *     4,096 units, or of heads of 128 over 262,144 keys and more), 1 = never, 2..16 = that
+ *     many ranges (at least 16 key blocks each).
  *     Results agree within the rounding of the bf16 probabilities (those of a range are
  *     rounded relative to a reference of its own) and of the fp32 partial sums.  Changes the
  *     workspace sizes like the option above: a short call may need more than a longer one.  Single tokens (no DCA, at most 16 query heads per KV

@@ -28,7 +28,7 @@
 //  * the tile walk reads a per-head list of (key block, query-block mask) entries through
 //    a 64-entry lane cache and lives entirely in scalar registers.
 //  * persistent launch: two workgroups per compute unit in eight groups (one per XCD).  Where keys
-//    are many (heads of 128 from 256K keys on) a group works on consecutive query tiles of one
+//    are many (heads of 128 from 256K keys on, and some calls of few heads of 64) a group works on consecutive query tiles of one
 //    head per round and keeps its members within a few sync segments of keys, so that K/V blocks
 //    are shared through the L2.  Which group takes which round is decided on the device from the
 //    lengths of the block lists.  Elsewhere the pieces of the launch wait in one queue per XCD.
@@ -172,7 +172,7 @@ constexpr double kFoldSteps = 0.022;               // folding a row's piece, in 
 constexpr int kBatchSlots = 512, kShortSteps = 64;  // a batch of fewer steps per slot is cut into one piece per slot: 2 requests
                                                     // of 64 rows at 46K keys 134 us -> 107
 constexpr int kMaxPieces = 2048, kBatchPieces = 1536;   // pieces with partial results: a call's, a batch's
-constexpr int kMaxQueueUnits = 4096;               // beyond it only what whole rounds leave over is cut; ranges that are asked for are made
+constexpr int kMaxQueueUnits = 4096;               // beyond it only what whole rounds leave over is cut (see cut_rest); ranges that are asked for are made
 constexpr int64_t kMaxAskedUnits = 1 << 23;        // all the same (128 M pieces of 33 KB and more: no workspace holds them)
 constexpr int kPaceBlocks = 4096;                  // key blocks from which whole units of heads of 128 keep pace (see launch_attention)
 constexpr int kShortList = 1024;                   // steps of a walk below which (by the budgets) heads of 64 over many keys are cut less finely
@@ -1879,8 +1879,10 @@ static AttnCut attn_cut_as(const vs_params& p, bool dense, bool least, int force
   // one, and whole units end as differently as lists are long, rows far from the first key and XCDs fast (workgroups of full rounds
   // ended 2 to 2.5 % before the last one on average).  32,768 rows, full rounds whole and so: 28 heads at 1M keys 225.9 ms and 221.4; 40 heads at
   // 262,144 146.7 and 142.3; 16,384 rows of 28 at 16,384 dense 2,165 us and 1,766, clustered at 50K 7,562 and 7,046.  Full rounds of more than
-  // kMaxQueueUnits units that do not keep pace stay whole, where 136 MB of partial results would be as much as the caches, and come out of
-  // the queues: 28 heads at 65,536 dense 20.98 ms keeping pace, 20.33 so (19.57 with the last round cut), clustered 16.21 and 15.12.
+  // kMaxQueueUnits units that do not keep pace stay whole and come out of the queues: 28 heads at 65,536 dense 20.98 ms keeping pace, 20.33 so,
+  // clustered 16.21 and 15.12.  With their last round cut, too, the dense ones would take 19.57; they are not
+  // because calls of this size have always done without room for partial results (0.24 MB, and 137 then) and are held to it.  No
+  // measurement draws the line at kMaxQueueUnits.
   // Walks that the budgets make short (heads of 64, 256K keys and more) in half as many: the partial results take as much of the caches and of the time
   // as they save.  4 heads with 256 offsets, clustered: 30,000 rows at 700,000 keys 418, 610, 661 us (three sets of keys), 401, 602, 660 so; 32,768 rows at 1M 484,
   // 639, 671 and 483, 627, 664 (482, 611, 674 whole); with 700 offsets, 8 heads, 15,000 rows at 500,000 1,443, 1,014, 1,090 and 1,544, 1,019, 1,142.
@@ -1951,7 +1953,7 @@ static AttnCut attn_cut_as(const vs_params& p, bool dense, bool least, int force
   // at 400K keys 35.2 ms, 34.5, 34.1, with DCA 36.6, 35.8, 35.3; 6,822 rows at 858K (2.95 rounds) 50.2 whole, 48.7.  Shorter ones: 13,307 rows
   // at 31K keys 4,850 us whole, 4,300; 4,096 clustered ones at 8,192 521 and 430; 3,128 of 40 heads at 63K in a few ranges 4,116, 4,043.
   // Below 1,024 key blocks the ranges that the count makes are as good (40 calls: 2 % either way), and smaller; and ranges of one
-  // round that do not keep pace go, with index sets, by the lists' lengths.
+  // round go, with index sets, by the lists' lengths where no whole units keep pace before them.
   const bool one_round = c.n_split > 1 && (c.n_units - c.n_whole) * (int64_t)c.n_split <= slots && n_blk >= 64 * (int64_t)c.n_split;
   if (fine && units % slots != 0 && (c.n_split == 1 || long_walk || attn_few_over(p, units) || (n_blk >= 1024 && !one_round))) {
     cut_rest(units % slots);
